@@ -82,8 +82,10 @@ struct StepPlan {
     // workspace layout (byte offsets)
     size_t off_lse = 0, off_pms = 0, off_pkeys = 0, off_hpack = 0, off_zbuf = 0, bytes = 0;
     bool row_select = false;   // matrix-core path: logits stored, one workgroup per hidden row finishes
-    int extra_rows = 0;        // matrix-core path: tile rows past the 128th (shared by the eight waves, or in LDS beside h)
-    int xoff = 0;              // ... more than 8 hidden rows: LDS offset of their accumulators
+    int extra_rows = 0;        // matrix-core path: tile rows past the 128th
+    // more than 8 hidden rows: 16-row groups of a tile, LDS offset of its target ids, epilogue passes
+    int row_groups = 0, ids_off = 0, passes = 1;
+    bool wide = false;         // more than 64 hidden rows
 };
 
 using vt::kTicketBytes;
@@ -92,6 +94,68 @@ using vt::kTicketBytes;
 struct FixedTiles {
     int nwaves = 0, ksplit = 1, nlists = 0;
 };
+// More than 8 hidden rows, bf16: how the head is cut into tiles (kernel variant, LDS, number of tiles).
+void plan_many_rows(StepPlan &p, int n, int k, int d, int m) {
+    const int CUS = round_workgroups();
+    const int R = (k + CUS - 1) / CUS;                // rows per tile for one tile per CU
+    const int G = (R + 15) / 16;                      // ... in 16-row groups
+    size_t ring, tile;                                // LDS: the stages; the logit tile and the candidate keys after them
+    // Microseconds of `rounds` rounds of tiles of `rows` rows, roughly: W at a CU's share of the HBM rate, h from the L2,
+    // and about 7 us for a round's first loads and its epilogue.
+    const int n_padded = n <= 32 ? 32 : n <= vt::kRowsKernelMaxN ? vt::kRowsKernelMaxN : vt::kMfmaMaxN;
+    auto cost = [&](int rows) {
+        const int tiles = (k + rows - 1) / rows, rounds = (tiles + CUS - 1) / CUS;
+        return rounds * ((double)rows * d * 2 / 25e3 + (double)n_padded * d * 2 / 75e3 + 7.0);
+    };
+    if (n <= vt::kRowsKernelMaxN) {
+        const int NT = n <= 32 ? 2 : 4;
+        p.NT = NT;
+        if (R > vt::kMfmaTileRows && R <= vt::kMfmaTileRows + 16) {
+            // 129 .. 144 rows per tile for one tile per CU (the paper's trimmed sizes): tiles of exactly that many rows
+            p.row_groups = vt::kStepWaves;
+            p.extra_rows = R - vt::kMfmaTileRows;
+        } else if (G <= vt::kMfmaMaxWaves) {
+            // one round: the tile height follows from the head
+            p.row_groups = (G == 5 && NT == 4) ? vt::kStepWaves : G;
+        } else {
+            p.row_groups = vt::kStepWaves;
+            for (int g = vt::kStepWaves + 1; g <= vt::kMfmaMaxWaves; ++g)
+                if (cost(16 * g) < cost(16 * p.row_groups)) p.row_groups = g;
+        }
+        p.nwaves = p.row_groups <= 4 ? vt::kStepWaves : p.row_groups;
+        const int rows_in_lds = 16 * (p.row_groups + (p.extra_rows != 0 ? 1 : 0));
+        ring = vt::rows_ring_bytes(NT, p.row_groups, p.extra_rows != 0);
+        tile = round_up((size_t)n * (rows_in_lds + 1) * sizeof(float), 16);
+    } else {
+        const int NTT = n <= 128 ? 2 : n <= 192 ? 3 : 4;
+        p.wide = true;
+        p.NT = 4 * NTT;
+        // (smaller tiles mean more candidate lists: not where only theirs would outgrow the library's own workspace)
+        auto list_bytes = [&](int rows) { return (size_t)n * ((k + rows - 1) / rows) * (1 + m) * sizeof(unsigned long long); };
+        auto fits = [&](int rows) {
+            return m > vt::kRowSelectMinLManyRows || n * m >= vt::kRowSelectMinWork ||
+                   list_bytes(rows) + 65536 <= (size_t)VT_STATIC_WS_BYTES || list_bytes(rows) <= list_bytes(vt::kMfmaTileRows);
+        };
+        int MT = 4;
+        for (int x : {1, 2, 3, 5})
+            if (fits(32 * x) && cost(32 * x) < cost(32 * MT)) MT = x;
+        p.row_groups = 2 * MT;
+        p.nwaves = vt::kStepWaves;
+        ring = vt::wide_ring_bytes(MT, NTT);
+        tile = round_up((size_t)n * (32 * MT + 1) * sizeof(float), 16);
+        if (tile + vt::kStepWaves * 512 > (size_t)vt::kMaxDynamicLds - 1024) {
+            p.passes = 2;
+            tile = round_up((size_t)32 * NTT * (32 * MT + 1) * sizeof(float), 16);
+        }
+    }
+    const int tile_rows = 16 * p.row_groups + p.extra_rows;
+    p.mfma = true;
+    p.nlists = p.nblocks = (k + tile_rows - 1) / tile_rows;
+    p.L = m < tile_rows ? m : tile_rows;
+    tile += (size_t)p.nwaves * 64 * sizeof(unsigned long long);      // 4 x 16 candidate keys per wave
+    p.ids_off = (int)round_up(ring > tile ? ring : tile, 16);
+    p.lds = (size_t)p.ids_off + vt::kMfmaMaxWaves * 16 * sizeof(int);
+}
 StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, const FixedTiles &fixed = FixedTiles{});
 // force_gemv: the caller needs what only the small-n kernel offers (row picking, the fused tree level)
 StepPlan plan_step(int n, int k, int d, int m, int dtype, bool force_gemv = false) {
@@ -226,50 +290,19 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
     }
     if (!p.gemv) {
         // larger n or d: the matrix-core path (bf16, d a multiple of 128, n <= 256)
-        if (dtype != VT_BF16 || (d % 128) != 0 || n > 256) return p;
-        int NT = 1;
-        while (16 * NT < n) NT *= 2;
-        const bool var_waves = prefer_mfma && nwaves != vt::kStepWaves;
-        size_t stage = NT >= 8 ? vt::mfma_wide_lds_bytes() : vt::mfma_stage_bytes(var_waves ? nwaves : vt::kStepWaves);
-        // More than 8 hidden rows and 129 .. 144 rows per tile for one tile per CU (the paper's trimmed sizes again):
-        // tiles of exactly that many rows (k = 32975, n = 64, d = 4096: 258 tiles of 128 rows took 104 us, a nearly
-        // empty second round).  With two groups of hidden rows (9 .. 16 rows are padded to 32) the columns of the rows
-        // past the 128th sit in LDS beside h's chunk (16 more rows) and their accumulators behind it (3 KiB per
-        // group); with four groups they are multiplied in a pass after the march (measured crossover: the kernel's
-        // comment has the figures).
-        const int Rx = (k + CUS - 1) / CUS;
-        const bool xany = n > vt::kGemvMaxN && NT <= 4 && d >= 1024 && Rx > vt::kMfmaTileRows &&
-                          Rx <= vt::kMfmaTileRows + 16;
-        if (xany && NT == 1) NT = 2;
-        // ... and fewer than 112 rows per tile for one tile per CU: tiles of 5 .. 7 waves (16 rows each) instead of
-        // leaving CUs idle with 128-row tiles
-        const int Gx = (Rx + 15) / 16;
-        // (their threads must still prefetch a chunk of at least three units of h through their registers)
-        const bool few = n > vt::kGemvMaxN && NT <= 4 && !xany && Gx >= 5 && Gx <= vt::kMfmaFewWaves &&
-                         (size_t)vt::kMfmaChunkPieces * Gx * 64 * 16 >= (size_t)16 * (NT < 2 ? 2 : NT) * 2 * 128 * vt::kMfmaPrefetchUnits;
-        if (few && NT == 1) NT = 2;
-        const int NWx = few ? Gx : vt::kStepWaves;      // waves of a workgroup for more than 8 hidden rows
-        if (few) stage = vt::mfma_stage_bytes(NWx);
-        const bool xrows = xany && NT == 2;      // ... in LDS beside the chunk
-        const bool xpass = xany && NT == 4;      // ... after the march
-        const size_t xbytes = xrows ? (size_t)3 * NT * 1024 : 0;
-        int KC = 128;   // NT >= 8: h is not staged at all (B-operands come from L2)
-        if (NT < 8) {
-            // up to 8 hidden rows occupy 8 rows of LDS (the other half of the 16-row operand repeats them)
-            const size_t hrows = (n <= 8 ? 8 : 16 * (size_t)NT) + (xrows ? 16 : 0);
-            const size_t hmax = ((size_t)vt::kMaxDynamicLds - stage - xbytes) / hrows;
+        if (dtype != VT_BF16 || (d % 128) != 0 || n > vt::kMfmaMaxN) return p;
+        if (n > vt::kGemvMaxN) {
+            plan_many_rows(p, n, k, d, m);
+        } else {
+            const bool var_waves = prefer_mfma && nwaves != vt::kStepWaves;
+            const size_t stage = vt::mfma_stage_bytes(var_waves ? nwaves : vt::kStepWaves);
+            // the hidden rows occupy 8 rows of LDS (the other half of the 16-row operand repeats them)
+            const size_t hrows = 8;
+            const size_t hmax = ((size_t)vt::kMaxDynamicLds - stage) / hrows;
             if (hmax < 272) return p;
-            KC = (int)(((hmax - 16) / 2) / 128) * 128;
-            int kc_regs = (int)((vt::kMfmaChunkPieces * (var_waves ? nwaves : NWx) * 64 * 16) / (hrows * 2) / 128 * 128);
-            if (xrows) {
-                // the extra rows' pieces start at a piece number of their own behind h's
-                const int T = vt::kStepWaves * 64;
-                kc_regs = (kc_regs / 128 + 1) * 128;
-                do {
-                    kc_regs -= 128;
-                } while (kc_regs > 0 && (16 * NT * (kc_regs / 8) + T - 1) / T + (16 * (kc_regs / 8) + T - 1) / T > vt::kMfmaChunkPieces);
-                if (kc_regs <= 0) return p;
-            }
+            int KC = (int)(((hmax - 16) / 2) / 128) * 128;
+            const int kc_regs =
+                (int)((vt::kMfmaChunkPieces * (var_waves ? nwaves : vt::kStepWaves) * 64 * 16) / (hrows * 2) / 128 * 128);
             if (KC > kc_regs) KC = kc_regs;   // the chunk must fit the register prefetch
             if (KC >= d) {
                 KC = d;
@@ -282,38 +315,28 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
                 const int nch = (U + umax - 1) / umax;
                 KC = (((U + nch - 1) / nch + P - 1) / P * P) * 128;
             }
-        }
-        p.mfma = true;
-        p.NT = NT;
-        p.KC = KC;
-        p.hpitch = KC * 2 + 16;
-        p.ksplit = (prefer_mfma && KC == d) ? ksplit : 1;
-        p.nwaves = (prefer_mfma && KC == d) ? nwaves : NWx;
-        p.extra_rows = (prefer_mfma && KC == d) ? extra_rows : 0;
-        if (xany) p.extra_rows = Rx - vt::kMfmaTileRows;
-        const int tile_rows = 16 * (p.nwaves / p.ksplit) + p.extra_rows;
-        p.nlists = fixed.nwaves != 0 ? fixed.nlists : (k + tile_rows - 1) / tile_rows;
-        p.L = m < tile_rows ? m : tile_rows;
-        p.nblocks = p.nlists;
-        p.lds = NT >= 8 ? stage : stage + ((n <= 8 ? 8 : 16 * (size_t)NT) + (xrows ? 16 : 0)) * p.hpitch;
-        if (xrows) {
-            p.xoff = (int)((p.lds + 15) & ~(size_t)15);
-            p.lds = (size_t)p.xoff + xbytes;
-        }
-        // logit tile of the epilogue + 4 x 16 candidate keys per wave behind it
-        // (+ the four range sums of 16 rows per hidden row that a pass after the march leaves)
-        size_t tile = (((size_t)p.ksplit * n * (vt::kMfmaTileRows + (xany ? 17 : 1)) * sizeof(float) + 15) & ~(size_t)15) +
-                      (size_t)vt::kStepWaves * 4 * 16 * sizeof(unsigned long long) +
-                      (xpass ? (size_t)4 * n * 16 * sizeof(float) : 0);
-        if (xrows && tile > (size_t)p.xoff) return p;      // (the extra rows' logits are read from behind the chunk into the tile)
-        if (n <= vt::kStepWaves) {      // a wave per row: a candidate key per tile row and wave, not below 8 KiB
+            p.mfma = true;
+            p.NT = 1;
+            p.KC = KC;
+            p.hpitch = KC * 2 + 16;
+            p.ksplit = (prefer_mfma && KC == d) ? ksplit : 1;
+            p.nwaves = (prefer_mfma && KC == d) ? nwaves : vt::kStepWaves;
+            p.extra_rows = (prefer_mfma && KC == d) ? extra_rows : 0;
+            p.row_groups = p.nwaves / p.ksplit;
+            const int tile_rows = 16 * p.row_groups + p.extra_rows;
+            p.nlists = fixed.nwaves != 0 ? fixed.nlists : (k + tile_rows - 1) / tile_rows;
+            p.L = m < tile_rows ? m : tile_rows;
+            p.nblocks = p.nlists;
+            // a wave per row in the epilogue: a candidate key per tile row and wave, not below 8 KiB
             const int tp = (p.extra_rows != 0 ? vt::kMfmaTileRows + 16 : p.nwaves == vt::kStepWaves ? vt::kMfmaTileRows : tile_rows) + 1;
             const size_t zt = ((size_t)p.ksplit * n * tp * sizeof(float) + 15) & ~(size_t)15;
-            tile = (zt > 8192 ? zt : 8192) +
-                   (size_t)p.nwaves * ((p.nwaves == vt::kStepWaves && p.extra_rows == 0) ? 2 : 3) * 64 * sizeof(unsigned long long) +
-                   (p.extra_rows != 0 ? (size_t)8 * n * 16 * sizeof(float) : 0);      // + the shared group's partials
+            const size_t tile =
+                (zt > 8192 ? zt : 8192) +
+                (size_t)p.nwaves * ((p.nwaves == vt::kStepWaves && p.extra_rows == 0) ? 2 : 3) * 64 * sizeof(unsigned long long) +
+                (p.extra_rows != 0 ? (size_t)8 * n * 16 * sizeof(float) : 0);      // + the shared group's partials
+            p.lds = stage + hrows * p.hpitch;
+            if (tile > p.lds) p.lds = tile;
         }
-        if (tile > p.lds) p.lds = tile;
         if (p.lds > (size_t)vt::kMaxDynamicLds) return p;
         const int group = p.nlists < vt::kStepMaxBlocks ? p.nlists : vt::kStepMaxBlocks;
         p.fin_stage_keys = (group + 1) * p.L;
@@ -342,15 +365,32 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
     size_t off = kTicketBytes;
     p.off_lse = off;
     off = round_up(off + (size_t)n * sizeof(float), 256);
+    const size_t pms_bytes = round_up((size_t)p.nblocks * n * sizeof(unsigned long long), 256);
+    const size_t key_bytes = round_up((size_t)n * p.nblocks * p.L * sizeof(unsigned long long), 256);
+    const size_t zbuf_bytes = round_up((size_t)n * k * sizeof(float), 256);
     p.off_pms = off;
-    off = round_up(off + (size_t)p.nblocks * n * sizeof(unsigned long long), 256);
-    p.off_pkeys = off;
-    off = round_up(off + (size_t)n * p.nblocks * p.L * sizeof(unsigned long long), 256);
-    p.off_hpack = off;
-    if (p.mfma && p.NT >= 8) off = round_up(off + (size_t)d * p.NT * 32, 256);
+    p.off_pkeys = off + pms_bytes;
     p.off_zbuf = off;
-    if (p.row_select) off = round_up(off + (size_t)n * k * sizeof(float), 256);
+    if (p.mfma && n > vt::kGemvMaxN && p.row_select) {
+        // the stored logits lie where the lists would (up to 8 tokens per row the larger of the two is reserved: with
+        // fewer hidden rows the same workspace serves lists)
+        off += m <= vt::kRowSelectMinLManyRows && pms_bytes + key_bytes > zbuf_bytes ? pms_bytes + key_bytes : zbuf_bytes;
+    } else {
+        off += pms_bytes + key_bytes;
+        p.off_zbuf = off;
+        if (p.row_select) off += zbuf_bytes;
+    }
+    if (p.wide && (size_t)n * d * 2 >= vt::kPackHBytes) {
+        p.off_hpack = off;
+        off = round_up(off + (size_t)d * p.NT * 32, 256);
+    }
     p.bytes = off;
+    if (p.mfma && n > vt::kGemvMaxN) {
+        // (a workspace for this many hidden rows serves a step of fewer too, whose tiles may be smaller)
+        const int fewer_n = n > vt::kRowsKernelMaxN ? vt::kRowsKernelMaxN : n > 32 ? 32 : vt::kGemvMaxN;
+        const StepPlan fewer = plan_step(fewer_n, k, d, m, dtype);
+        if (fewer.ok && fewer.bytes > p.bytes) p.bytes = fewer.bytes;
+    }
     p.ok = true;
     return p;
 }
@@ -617,13 +657,16 @@ int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_ty
     if (p.gemv) {
         std::snprintf(head, sizeof head, "head_gemv_kernel<%s,%d,%d> workgroups=%d rows_per_workgroup=%d column_segments=%d",
                       w_type == VT_BF16 ? "bf16" : "f32", p.NP, p.CS, p.nblocks, p.rpb, p.S);
-    } else if (p.NT >= 8) {
-        std::snprintf(head, sizeof head, "pack_h_kernel + head_mfma_wide_kernel<%d> workgroups=%d tile_rows=%d", p.NT / 8,
-                      p.nlists, vt::kMfmaTileRows);
+    } else if (p.wide) {
+        std::snprintf(head, sizeof head, "%shead_mfma_wide_kernel<%d> workgroups=%d tile_rows=%d",
+                      p.off_hpack != 0 ? "pack_h_kernel + " : "", p.NT <= 8 ? 1 : 2, p.nlists, 16 * p.row_groups);
     } else {
+        // (the second template argument: the most waves of the instantiation)
         std::snprintf(head, sizeof head, "head_mfma_kernel<%d,%d> workgroups=%d tile_rows=%d waves=%d column_split=%d", p.NT,
-                      p.nwaves == vt::kStepWaves ? vt::kStepWaves : p.NT > 1 ? vt::kMfmaFewWaves : vt::kMfmaMaxWaves, p.nlists,
-                      16 * (p.nwaves / p.ksplit) + p.extra_rows, p.nwaves, p.ksplit);
+                      p.nwaves == vt::kStepWaves                         ? vt::kStepWaves
+                      : p.NT > 1 && p.nwaves <= vt::kMfmaFewWaves ? vt::kMfmaFewWaves
+                                                                         : vt::kMfmaMaxWaves,
+                      p.nlists, 16 * p.row_groups + p.extra_rows, p.nwaves, p.ksplit);
     }
     const char *tail = p.row_select ? " + row_select_kernel" : " + step_finalize_kernel";
     char groups[48] = "";
@@ -1100,7 +1143,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         a.pms = pms;
         a.pkeys = pkeys;
         a.out_logp_full = out_logp_full;
-        a.hpack = p.NT >= 8 ? static_cast<void *>(wsb + p.off_hpack) : nullptr;
+        a.hpack = p.off_hpack != 0 ? static_cast<void *>(wsb + p.off_hpack) : nullptr;
         a.zbuf = nullptr;
         if (p.row_select) a.zbuf = out_logp_full != nullptr ? out_logp_full : reinterpret_cast<float *>(wsb + p.off_zbuf);
         a.row_pack = tf.row_pack;
@@ -1108,9 +1151,13 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         a.ksplit = p.ksplit;
         a.nwaves = p.nwaves;
         a.extra_rows = p.extra_rows;
-        a.xoff = p.xoff;
+        a.row_groups = p.row_groups;
+        a.ids_off = p.ids_off;
+        a.passes = p.passes;
         a.ticket_clear = tf.cum != nullptr ? reinterpret_cast<unsigned *>(wsb) : nullptr;
-        hipError_t e = vt::launch_head_mfma(p.NT, a, p.lds, st);
+        hipError_t e = n <= vt::kGemvMaxN ? vt::launch_head_mfma(a, p.lds, st)
+                       : p.wide           ? vt::launch_head_mfma_wide(p.NT / 4, a, p.lds, st)
+                                          : vt::launch_head_mfma_rows(p.NT, a, p.lds, st);
         if (e != hipSuccess) return device_status(e);
         if (p.row_select) {
             vt::launch_row_select(a.zbuf, map, n, k, m, out_ids, out_logp, out_lse, lse_buf, st);

@@ -1,0 +1,614 @@
+// Draft step for more than 8 hidden rows (tree and batch drafting): z[n, k] = h[n, d] W_trim[k, d]^T on the matrix
+// cores (v_mfma_f32_16x16x32_bf16), bound by the single pass over W_trim up to about 128 hidden rows.
+//
+// Both operands go from memory straight into LDS (global_load_lds_dwordx4: no registers hold data in flight, so the
+// depth of the prefetch is a matter of LDS alone).  A stage is 64 columns (128 bytes) of the tile's rows of W_trim and of
+// all hidden rows; a ring of stages fills LDS and one barrier per stage hands a slot on.  16-byte pieces of a row are
+// stored in the order c ^ ((row / 2) & 7), which the loading lanes do by picking their piece of memory: operand reads
+// (ds_read_b128, 16 rows x 4 pieces) then run at the full LDS rate (535 bytes/ns per CU; 301 at a row pitch of 272 bytes,
+// 151 at 128 bytes unswizzled) and every 8 lanes still load one 128-byte line.
+//
+// The tile's logits meet in LDS (over the ring) and the workgroup epilogue produces (max, sum-exp) and the best
+// candidates per hidden row; a merge kernel finishes the step.  Or the logits are stored for row_select_kernel.
+#include "vt_device.h"
+#include "vt_launch.h"
+#include "vt_step.h"
+#include "vt_step_tail.h"
+
+namespace vt {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+constexpr int kStageCols = 64;                 // columns per stage: 128 bytes per row
+constexpr int kGroupBytes = 16 * 128;          // 16 rows of a stage
+constexpr int kPieceBytes = 1024;              // one load instruction: 8 rows of a stage
+
+// 64 lanes x 16 bytes from base + voff into LDS at lds + 16 * lane.  STREAM: read once (W_trim); otherwise kept in
+// the L2 for the other workgroups (h).
+template <bool STREAM>
+__device__ __forceinline__ void lds_load16(unsigned lds, unsigned voff, const void *base) {
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void lds_load4(unsigned lds, unsigned voff, const void *base) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+}
+// All but the N youngest loads of this wave have landed, its LDS reads are done; then the workgroup's barrier.
+template <int N>
+__device__ __forceinline__ void wait_and_sync() {
+    static_assert(N <= 63, "vmcnt holds six bits");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// The same with `younger` <= MOST stages of LPW loads each behind the one that is needed (fewer only near the end).
+template <int LPW, int MOST>
+__device__ __forceinline__ void wait_stage_and_sync(int younger) {
+    if constexpr (MOST == 0) {
+        wait_and_sync<0>();
+    } else {
+        if (younger >= MOST)
+            wait_and_sync<LPW * MOST>();
+        else
+            wait_stage_and_sync<LPW, MOST - 1>(younger);
+    }
+}
+
+// ---------------------------------------------------------------- column ranges
+// All workgroups march over the columns of their rows in step, and rows of W are d * 2 bytes apart: when that is a
+// multiple of 4 KiB the requests in flight crowd a subset of the HBM channels (n = 64, k = 32768, d = 4096: 63 us; d = 2048:
+// 36 us).  So the contraction is cut into NR ranges of columns and workgroup b starts with range (b / 8) % NR -- b % 8 is
+// the XCD -- and wraps around (NR = 4: 44.5 and 32.9 us, NR = 8: 43.0 and 24.8).  To keep a logit's rounding independent
+// of where its workgroup started (equal rows of W give equal logits in whichever tile they lie) every range is
+// accumulated from zero in ascending order and the sums are added up as a balanced tree,
+// ((R0 + R1) + (R2 + R3)) + ((R4 + R5) + (R6 + R7)): float addition commutes, so the ranges can finish in any rotation.
+// The partial sums a rotation needs to hold: the open half of a pair, one sum per quad, and for an odd start the
+// second half of its pair, whose first half comes last.  NR = 4 and 2 are the same tree, cut off.
+template <int NR, int N>
+struct RangeSums {
+    static constexpr int kSets = NR == 8 ? 4 : NR == 4 ? 2 : NR == 2 ? 1 : 0;
+    f32x4 set[kSets > 0 ? kSets : 1][kSets > 0 ? N : 1];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int s = 0; s < kSets; ++s) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) set[s][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    // The j-th range to finish (range (rot + j) % NR) is complete in acc, which starts from zero again.
+    __device__ __forceinline__ void close(f32x4 (&acc)[N], int rot, int j) {
+        const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (NR == 2) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) set[0][i] += acc[i];
+        } else if constexpr (NR == 4) {
+            // set[x] = R(2x) + R(2x + 1)
+            const bool to1 = (((rot + j) >> 1) & 1) != 0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                set[0][i] += to1 ? zero : acc[i];      // (adding zero changes nothing)
+                set[1][i] += to1 ? acc[i] : zero;
+            }
+        } else if constexpr (NR == 8) {
+            // set[0], set[1]: the quads; set[2]: the open pair's first half; set[3]: an odd start's first range
+            const bool odd = (rot & 1) != 0;
+            if (odd && j == 0) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) set[3][i] = acc[i];
+            } else if (((rot + j) & 1) == 0 && !(odd && j == 7)) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) set[2][i] = acc[i];
+            } else {
+                const bool to1 = (((rot + j) >> 2) & 1) != 0;
+                const bool last = odd && j == 7;
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    const f32x4 pair = (last ? set[3][i] : set[2][i]) + acc[i];
+                    set[0][i] += to1 ? zero : pair;
+                    set[1][i] += to1 ? pair : zero;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = zero;
+    }
+    // the logits, from the closed ranges (and the last one of NR = 2, closed like the others)
+    __device__ __forceinline__ void total(f32x4 (&acc)[N]) const {
+        if constexpr (NR == 2) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i] = set[0][i];
+        } else if constexpr (NR >= 4) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i] = set[0][i] + set[1][i];
+        }
+    }
+};
+
+// Where a workgroup's march over ns stages starts and where its ranges end.
+template <int NR>
+struct March {
+    int ns, rot, start;
+    bool rotate;
+    __device__ __forceinline__ static int bound(int r, int ns) {
+        // NR = 2: the second range starts 2 KiB in (half a row on, or any multiple of 4 KiB, crowds the same channels)
+        return NR == 2 ? r * 16 : r * (ns / NR);
+    }
+    __device__ __forceinline__ March(int ns_, int d) : ns(ns_) {
+        rotate = NR > 1 && d % 2048 == 0 && (NR > 2 || d >= 4096);
+        rot = rotate ? ((int)blockIdx.x >> 3) & (NR - 1) : 0;
+        start = bound(rot, ns);
+    }
+    // stage of the row that is multiplied at step s < ns
+    __device__ __forceinline__ int stage_of(int s) const {
+        const int u = start + s;
+        return u >= ns ? u - ns : u;
+    }
+    // the stage at which range (rot + j) % NR ends (exclusive; ns = the end of the row)
+    __device__ __forceinline__ int end_of(int j) const {
+        const int r = (rot + j) & (NR - 1);
+        return r == NR - 1 ? ns : bound(r + 1, ns);
+    }
+};
+
+// Tile logits in LDS: hidden row i at i * pitch floats.
+__device__ __forceinline__ void store_logits4(float *dst, const f32x4 &v) {
+    dst[0] = v.x;
+    dst[1] = v.y;
+    dst[2] = v.z;
+    dst[3] = v.w;
+}
+
+// Workgroup epilogue on the logit tile of hidden rows i_lo .. i_hi - 1 (row i at zt + (i - i_lo) * tp), Q * 16 >= rows_b.
+template <int Q>
+__device__ __forceinline__ void tile_epilogue(const MfmaArgs &a, const float *zt, int tp, int i_lo, int i_hi, int row0, int rows_b,
+                                              const int *lds_ids, unsigned long long *cand, int nwaves, int w, int lane) {
+    if (a.zbuf != nullptr) {
+        // one wave copies a hidden row's logits of this tile (contiguous in z) at a time
+        for (int i = i_lo + w; i < i_hi; i += nwaves) {
+            const float *src = zt + (size_t)(i - i_lo) * tp;
+            float *dst = a.zbuf + (size_t)i * a.k + row0;
+            for (int t = lane; t < rows_b; t += kWave) dst[t] = src[t];
+        }
+        return;
+    }
+    int idq[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) idq[q] = lds_ids[min((lane & 15) + 16 * q, rows_b - 1)];
+    // (zt is addressed by hidden row: shifted back by the rows that are not in it)
+    const float *z0 = zt - (ptrdiff_t)i_lo * tp;
+    for (int i0 = i_lo + 4 * w; i0 < i_hi; i0 += 4 * nwaves)
+        block_epilogue_rows4<Q>(z0, tp, i0, i_hi, rows_b, a.L, idq, a.out_logp_full, (size_t)a.k, row0, a.pms, a.pkeys, a.nlists,
+                                (int)blockIdx.x, lane, cand + (size_t)w * 64);
+}
+
+// ---------------------------------------------------------------- 9 .. 64 hidden rows
+// A tile is RG groups of 16 rows of W_trim (1 .. 12).  From five groups on a workgroup has a wave per group, which
+// multiplies its 16 rows by all 16 * NT hidden rows (2 + 2 NT operand reads for 2 NT products per stage: well below the LDS
+// rate up to four groups of hidden rows); smaller tiles -- heads of up to 64 rows per CU -- have eight waves that share a
+// row group, TPW groups of hidden rows each (TPW = NT otherwise).
+// X: tiles of 128 + 1 .. 16 rows (the paper's trimmed sizes, so that all 256 CUs stream equal shares): the rows past
+// the 128th are a ninth group in LDS that wave t < NT multiplies by hidden-row group t beside its own rows, the same
+// operand layout, instructions and ranges, so equal rows give equal logits in whichever group they lie.
+// NST stages in LDS; LPW load instructions per wave and stage.
+// k = 32768, d = 4096: n = 64 43.0 us with the logits stored, n = 32 42.1 (a plain read of the 268 MB: 40.8; the
+// register-staged kernel before this one: 52.0 and 46.5).
+template <int NT, int MAXW, int TPW, int NST, int LPW, bool X>
+__global__ void __launch_bounds__(MAXW *kWave) __attribute__((amdgpu_waves_per_eu(1, (MAXW + 3) / 4)))
+head_mfma_kernel(const MfmaArgs a) {
+    static_assert(!X || (MAXW == kStepWaves && TPW == NT), "the ninth group belongs to tiles of eight waves");
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int NR = 8;
+    constexpr int NA = TPW + (X ? 1 : 0);      // accumulators: own row group, and the ninth
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int RG = X ? kStepWaves : a.row_groups;
+    const int GR = RG + (X ? 1 : 0);           // row groups in LDS
+    const int NW = MAXW == kStepWaves ? kStepWaves : a.nwaves;
+    if (a.ticket_clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(a.ticket_clear, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int tile_rows = 16 * RG + (X ? a.extra_rows : 0);
+    const int row0 = blockIdx.x * tile_rows;
+    const int rows_b = min(tile_rows, a.k - row0);
+    const unsigned rs = (unsigned)a.d * 2u;
+    const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs;
+    const char *hb = static_cast<const char *>(a.h);
+    const March<NR> march(a.d / kStageCols, a.d);
+    const unsigned stage_bytes = (unsigned)(GR + NT) * kGroupBytes;
+
+    // Loads of a stage: pieces of 8 rows, first W's (two per group), then h's; the waves take LPW consecutive ones each,
+    // and what is left over repeats pieces of h (the same bytes to the same place).  Rows past the end repeat the last.
+    unsigned voff[LPW], lds_at[LPW];
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+        const int x = w * LPW + j;
+        const bool is_w = x < 2 * GR;
+        const int p = is_w ? x : (x - 2 * GR) % (2 * NT);
+        const int r = 8 * p + (lane >> 3);
+        const int c = (lane & 7) ^ ((r >> 1) & 7);
+        const int row = is_w ? min(r, rows_b - 1) : min(r, a.n - 1);
+        voff[j] = (unsigned)row * rs + (unsigned)c * 16u;
+        lds_at[j] = (unsigned)(is_w ? p : 2 * GR + p) * kPieceBytes;
+    }
+    auto load_stage = [&](int s, int slot) {
+        const size_t col = (size_t)march.stage_of(s) * 128;
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) {
+            const unsigned at = (unsigned)slot * stage_bytes + lds_at[j];
+            if (w * LPW + j < 2 * GR)
+                lds_load16<true>(at, voff[j], Wt + col);
+            else
+                lds_load16<false>(at, voff[j], hb + col);
+        }
+    };
+    // the tile's target ids, ahead of everything else
+    if (w == 0) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            lds_load4((unsigned)a.ids_off + q * kWave * 4, (unsigned)min(q * kWave + lane, rows_b - 1) * 4u, a.map + row0);
+    }
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) {
+        if (s < march.ns) load_stage(s, s);
+    }
+
+    f32x4 acc[NA];
+    RangeSums<NR, NA> sums;
+    sums.clear();
+#pragma unroll
+    for (int t = 0; t < NA; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the wave's row group and hidden-row groups (eight waves on a small tile: some may have none)
+    const int rg = TPW == NT ? w : w % RG, t0 = TPW == NT ? 0 : (w / RG) * TPW;
+    const bool active = t0 < NT;
+    const bool ninth = X && w < NT;
+    // operand reads: lane (row lane % 16, 8 columns lane / 16) of k-step ks
+    const int lrow = lane & 15, lgrp = lane >> 4;
+    const unsigned rd = (unsigned)lrow * 128 + (unsigned)((lgrp ^ ((lrow >> 1) & 7)) * 16);
+    const unsigned rd_w = rd + (unsigned)rg * kGroupBytes, rd_h = rd + (unsigned)(GR + t0) * kGroupBytes;
+    const unsigned rd_xw = rd + (unsigned)kStepWaves * kGroupBytes, rd_xh = rd + (unsigned)(GR + w) * kGroupBytes;
+    auto product = [&](const u32x4 &av, const u32x4 &bv, f32x4 &c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), c, 0, 0, 0);
+    };
+    int slot = 0, closed = 0;
+    int left = march.end_of(0) - march.start;      // stages until the open range ends
+    for (int s = 0; s < march.ns; ++s) {
+        wait_stage_and_sync<LPW, NST - 2>(march.ns - 1 - s);      // stage s is in LDS, the slot of stage s - 1 is free
+        if (s + NST - 1 < march.ns) load_stage(s + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+        if (march.rotate) {
+            if (left == 0) {
+                sums.close(acc, march.rot, closed);
+                ++closed;
+                left = march.ns / NR;
+            }
+            --left;
+        }
+        const unsigned char *sb = smem + (unsigned)slot * stage_bytes;
+        slot = slot == NST - 1 ? 0 : slot + 1;
+        if (active) {
+            u32x4 av[2], bv[2][TPW];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {       // (piece 4 ks + lgrp: bit 2 of the piece number is 64 bytes)
+                av[ks] = *reinterpret_cast<const u32x4 *>(sb + (rd_w ^ (ks * 64u)));
+#pragma unroll
+                for (int t = 0; t < TPW; ++t)
+                    bv[ks][t] = *reinterpret_cast<const u32x4 *>(sb + (rd_h ^ (ks * 64u)) + t * kGroupBytes);
+            }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) product(av[ks], bv[ks][t], acc[t]);
+            }
+        }
+        if constexpr (X) {
+            if (ninth) {
+                u32x4 av[2], bv[2];
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    av[ks] = *reinterpret_cast<const u32x4 *>(sb + (rd_xw ^ (ks * 64u)));
+                    bv[ks] = *reinterpret_cast<const u32x4 *>(sb + (rd_xh ^ (ks * 64u)));
+                }
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) product(av[ks], bv[ks], acc[NA - 1]);
+            }
+        }
+    }
+    if (march.rotate) {
+        sums.close(acc, march.rot, closed);
+        sums.total(acc);
+    }
+    wait_and_sync<0>();      // every wave is done with the ring: it becomes the logit tile
+
+    float *zt = reinterpret_cast<float *>(smem);
+    const int tp = 16 * GR + 1;
+    if (active) {
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            const int i = 16 * (t0 + t) + lrow;
+            if (i < a.n) store_logits4(zt + (size_t)i * tp + 16 * rg + 4 * lgrp, acc[t]);
+        }
+    }
+    if (ninth) {
+        const int i = 16 * w + lrow;
+        if (i < a.n) store_logits4(zt + (size_t)i * tp + kMfmaTileRows + 4 * lgrp, acc[NA - 1]);
+    }
+    __syncthreads();
+    const int *lds_ids = reinterpret_cast<const int *>(smem + a.ids_off);
+    unsigned long long *cand =
+        reinterpret_cast<unsigned long long *>(smem + (((size_t)a.n * tp * sizeof(float) + 15) & ~(size_t)15));
+    constexpr int Q = X ? 9 : MAXW > kStepWaves ? kMfmaMaxWaves : 8;
+    tile_epilogue<Q>(a, zt, tp, 0, a.n, row0, rows_b, lds_ids, cand, NW, w, lane);
+}
+
+// ---------------------------------------------------------------- 65 .. 256 hidden rows
+// Tiles of 32 * MT rows by 64 * NTT hidden rows (NH = 1: up to 128, 2: up to 256), eight waves as a 2 x 4 grid of (16 * MT) x (16 * NTT) each: with more hidden
+// rows than 64 the operand reads of a wave per row group would exceed the LDS rate.  Per stage and wave there are two
+// k-steps of MT * NTT products; the operands of one are read while the other is multiplied, the barrier that hands the
+// slot on sits between them, and the loads of the freed slot are spread over the products that follow it -- issued
+// in one go they kept the wave from its products (n = 256, k = 32768, d = 8192: 149 against 140 us).
+// PACKED: h was re-laid by pack_h_kernel, a stage's pieces one after the other as they lie in LDS.
+template <int NH, int MT, int NTT, int NST, int NR, bool PACKED>
+__global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const MfmaArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int TM = 32 * MT, TN = 64 * NTT;
+    constexpr int kPieces = (TM + TN) / 8, LPW = (kPieces + kStepWaves - 1) / kStepWaves;
+    constexpr unsigned kStage = (TM + TN) * 128u;
+    constexpr int NP = MT * NTT;               // products per k-step
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wn = w & 3, wm = w >> 2;
+    if (a.ticket_clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(a.ticket_clear, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int row0 = blockIdx.x * TM;
+    const int rows_b = min(TM, a.k - row0);
+    const unsigned rs = (unsigned)a.d * 2u;
+    const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs;
+    const char *hb = static_cast<const char *>(a.h);
+    const March<NR> march(a.d / kStageCols, a.d);
+
+    unsigned voff[LPW], lds_at[LPW];
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+        // every wave takes its share of W's pieces and of h's (left-over slots repeat pieces of h)
+        const int x = j * kStepWaves + w;
+        const bool is_w = x < TM / 8;
+        const int p = is_w ? x : (x - TM / 8) % (TN / 8);
+        const int r = 8 * p + (lane >> 3);
+        const int c = (lane & 7) ^ ((r >> 1) & 7);
+        const int row = is_w ? min(r, rows_b - 1) : min(r, a.n - 1);
+        voff[j] = !is_w && PACKED ? (unsigned)(p * kPieceBytes + lane * 16) : (unsigned)row * rs + (unsigned)c * 16u;
+        lds_at[j] = (unsigned)(is_w ? p : TM / 8 + p) * kPieceBytes;
+    }
+    const char *pw = Wt, *ph = hb;
+    unsigned at = 0;
+    auto aim = [&](int s, int slot) {
+        const size_t u = (size_t)march.stage_of(s);
+        pw = Wt + u * 128;
+        ph = PACKED ? static_cast<const char *>(a.hpack) + u * (TN * 128) : hb + u * 128;
+        at = (unsigned)slot * kStage;
+    };
+    auto load_piece = [&](int j) {
+        // (the last of W's rounds may be shared with h: the two differ by wave)
+        if ((j + 1) * kStepWaves <= TM / 8 || (j * kStepWaves < TM / 8 && j * kStepWaves + w < TM / 8))
+            lds_load16<true>(at + lds_at[j], voff[j], pw);
+        else
+            lds_load16<false>(at + lds_at[j], voff[j], ph);
+    };
+    if (w == 0) {
+#pragma unroll
+        for (int q = 0; q < (TM + kWave - 1) / kWave; ++q)
+            lds_load4((unsigned)a.ids_off + q * kWave * 4, (unsigned)min(q * kWave + lane, rows_b - 1) * 4u, a.map + row0);
+    }
+#pragma unroll
+    for (int s = 0; s < NST; ++s) {
+        if (s >= march.ns) break;
+        aim(s, s);
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) load_piece(j);
+    }
+    f32x4 acc[NP];
+    RangeSums<NR, NP> sums;
+    sums.clear();
+#pragma unroll
+    for (int x = 0; x < NP; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int lrow = lane & 15, lgrp = lane >> 4;
+    const unsigned rd = (unsigned)lrow * 128 + (unsigned)((lgrp ^ ((lrow >> 1) & 7)) * 16);
+    const unsigned rd_w = rd + (unsigned)(wm * MT) * kGroupBytes, rd_h = rd + (unsigned)(TM / 16 + wn * NTT) * kGroupBytes;
+    u32x4 a0[MT], b0[NTT], a1[MT], b1[NTT];
+    auto read_operands = [&](u32x4(&av)[MT], u32x4(&bv)[NTT], unsigned ks, int slot) {
+        const unsigned char *sb = smem + (unsigned)slot * kStage;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) av[m] = *reinterpret_cast<const u32x4 *>(sb + (rd_w ^ (ks * 64u)) + m * kGroupBytes);
+#pragma unroll
+        for (int t = 0; t < NTT; ++t) bv[t] = *reinterpret_cast<const u32x4 *>(sb + (rd_h ^ (ks * 64u)) + t * kGroupBytes);
+    };
+    auto product = [&](int x, const u32x4(&av)[MT], const u32x4(&bv)[NTT]) {
+        acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[x / NTT]),
+                                                         __builtin_bit_cast(bf16x8, bv[x % NTT]), acc[x], 0, 0, 0);
+    };
+    wait_stage_and_sync<LPW, NST - 1>(march.ns - 1);
+    int slot = 0, closed = 0;
+    int left = march.end_of(0) - march.start;
+    read_operands(a0, b0, 0, 0);
+    for (int s = 0; s < march.ns; ++s) {
+        read_operands(a1, b1, 1, slot);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < NP; ++x) product(x, a0, b0);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_stage_and_sync<LPW, NST - 2>(march.ns - 2 - s);      // stage s + 1 is in LDS; everyone has read stage s
+        const bool more = s + NST < march.ns;
+        if (more) aim(s + NST, slot);
+        slot = slot == NST - 1 ? 0 : slot + 1;
+        read_operands(a0, b0, 0, slot);            // (past the last stage: an old slot, never used)
+        __builtin_amdgcn_sched_barrier(0);
+        constexpr int kEvery = NP / LPW > 0 ? NP / LPW : 1;
+#pragma unroll
+        for (int x = 0; x < NP; ++x) {
+            if (x % kEvery == 0 && x / kEvery < LPW) {
+                if (more) load_piece(x / kEvery);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            product(x, a1, b1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) {
+            if (j * kEvery >= NP && more) load_piece(j);
+        }
+        if (NR > 1 && march.rotate && --left == 0 && s + 1 < march.ns) {
+            sums.close(acc, march.rot, closed);
+            ++closed;
+            left = march.end_of(closed) - march.bound((march.rot + closed) & (NR - 1), march.ns);
+        }
+    }
+    if (NR > 1 && march.rotate) {
+        sums.close(acc, march.rot, closed);
+        sums.total(acc);
+    }
+    wait_and_sync<0>();      // every wave is done with the ring: it becomes the logit tile
+
+    // logit tile: all hidden rows at once, or (a.passes = 2) the lower and upper half of the wave columns in turn
+    float *zt = reinterpret_cast<float *>(smem);
+    constexpr int tp = TM + 1;
+    const int *lds_ids = reinterpret_cast<const int *>(smem + a.ids_off);
+    const int per_pass = TN / a.passes;            // hidden rows per pass
+    unsigned long long *cand = reinterpret_cast<unsigned long long *>(
+        smem + (((size_t)min(per_pass, a.n) * tp * sizeof(float) + 15) & ~(size_t)15));
+    for (int pass = 0; pass < a.passes; ++pass) {
+        const int i_lo = pass * per_pass, i_hi = min(a.n, i_lo + per_pass);
+        if (i_lo >= i_hi) break;                   // (uniform)
+        if (pass > 0) __syncthreads();             // the tile of the pass before is done with
+#pragma unroll
+        for (int t = 0; t < NTT; ++t) {
+            const int i = 16 * (wn * NTT + t) + lrow;
+            if (i >= i_lo && i < i_hi) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+                    store_logits4(zt + (size_t)(i - i_lo) * tp + 16 * (wm * MT + m) + 4 * lgrp, acc[m * NTT + t]);
+            }
+        }
+        __syncthreads();
+        tile_epilogue<2 * MT>(a, zt, tp, i_lo, i_hi, row0, rows_b, lds_ids, cand, kStepWaves, w, lane);
+    }
+}
+
+// Re-lays h for the kernel above: piece (stage u, 8 rows p) is 1 KiB, lane l's 16 bytes at 16 l (rows past n repeat
+// row n - 1; their products are never read).
+__global__ void __launch_bounds__(256) pack_h_kernel(const u32x4 *__restrict__ h, u32x4 *__restrict__ hp, int n, int d,
+                                                     int pieces, long long total) {
+    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (x >= total) return;
+    const int lane = (int)(x & 63);
+    const long long y = x >> 6;
+    const int p = (int)(y % pieces);
+    const long long u = y / pieces;
+    const int r = 8 * p + (lane >> 3);
+    const int c = (lane & 7) ^ ((r >> 1) & 7);
+    hp[x] = h[(long long)min(r, n - 1) * (d / 8) + u * 8 + c];
+}
+
+template <auto kern>
+hipError_t launch_tile(const MfmaArgs &a, int threads, size_t lds, hipStream_t st) {
+    static LdsLimitOnce lds_limit;
+    const hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(kern)}, kMaxDynamicLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(a.nlists), dim3(threads), lds, st, a);
+    return hipGetLastError();
+}
+
+constexpr int kRingBytes = 156 * 1024;         // LDS for the ring; the ids and what the epilogue needs fit behind it
+
+// Stages of a ring and loads per wave and stage of head_mfma_kernel's variants.
+struct RowsVariant {
+    int max_waves, tpw, stages, loads;
+};
+constexpr RowsVariant rows_variant(int NT, int row_groups, bool extra) {
+    if (extra) return NT == 2 ? RowsVariant{8, 2, 7, 3} : RowsVariant{8, 4, 6, 4};
+    if (row_groups <= 4)
+        return NT == 2 ? RowsVariant{8, 1, 12, 2} : row_groups <= 2 ? RowsVariant{8, 1, 12, 2} : RowsVariant{8, 2, 9, 2};
+    if (row_groups <= kMfmaFewWaves) return NT == 2 ? RowsVariant{7, 2, 8, 3} : RowsVariant{7, 4, 7, 4};
+    if (row_groups == kStepWaves) return NT == 2 ? RowsVariant{8, 2, 7, 3} : RowsVariant{8, 4, 6, 3};
+    return NT == 2 ? RowsVariant{12, 2, 5, 3} : row_groups == 12 ? RowsVariant{12, 4, 4, 3} : RowsVariant{12, 4, 5, 3};
+}
+template <int NT, int RG, bool X>
+hipError_t launch_rows(const MfmaArgs &a, size_t lds, hipStream_t st) {
+    constexpr RowsVariant v = rows_variant(NT, RG, X);
+    return launch_tile<head_mfma_kernel<NT, v.max_waves, v.tpw, v.stages, v.loads, X>>(a, a.nwaves * kWave, lds, st);
+}
+template <int NT>
+hipError_t launch_rows_nt(const MfmaArgs &a, size_t lds, hipStream_t st) {
+    if (a.extra_rows != 0) return launch_rows<NT, 8, true>(a, lds, st);
+    // (one representative row count per variant)
+    if (a.row_groups <= 2) return launch_rows<NT, 2, false>(a, lds, st);
+    if (a.row_groups <= 4) return launch_rows<NT, 4, false>(a, lds, st);
+    if (a.row_groups <= kMfmaFewWaves) return launch_rows<NT, 7, false>(a, lds, st);
+    if (a.row_groups == kStepWaves) return launch_rows<NT, 8, false>(a, lds, st);
+    if (a.row_groups < kMfmaMaxWaves) return launch_rows<NT, 11, false>(a, lds, st);
+    return launch_rows<NT, 12, false>(a, lds, st);
+}
+
+constexpr size_t wide_stage_bytes(int MT, int NTT) { return (size_t)(32 * MT + 64 * NTT) * 128; }
+constexpr int wide_stages(int MT, int NTT) {
+    const int s = (int)(kRingBytes / wide_stage_bytes(MT, NTT));
+    return s < 6 ? s : 6;
+}
+// ranges: as many as the registers (256 per lane) hold sums of beside two sets of operands
+constexpr int wide_ranges(int MT, int NTT) {
+    const int acc = 4 * MT * NTT, ops = 8 * (MT + NTT);
+    return 5 * acc + ops <= 208 ? 8 : 3 * acc + ops <= 208 ? 4 : 2;
+}
+template <int MT, int NTT>
+hipError_t launch_wide(const MfmaArgs &a, size_t lds, hipStream_t st) {
+    constexpr int NST = wide_stages(MT, NTT), NR = wide_ranges(MT, NTT), NH = (NTT + 1) / 2;
+    if (a.hpack == nullptr) return launch_tile<head_mfma_wide_kernel<NH, MT, NTT, NST, NR, false>>(a, kStepWaves * kWave, lds, st);
+    if constexpr (NTT == 4) {
+        const int pieces = 8 * NTT;
+        const long long total = (long long)(a.d / kStageCols) * pieces * kWave;
+        hipLaunchKernelGGL(pack_h_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, static_cast<const u32x4 *>(a.h),
+                           static_cast<u32x4 *>(a.hpack), a.n, a.d, pieces, total);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return launch_tile<head_mfma_wide_kernel<NH, MT, NTT, NST, NR, true>>(a, kStepWaves * kWave, lds, st);
+    }
+    return hipErrorInvalidValue;
+}
+template <int NTT>
+hipError_t launch_wide_ntt(const MfmaArgs &a, size_t lds, hipStream_t st) {
+    switch (a.row_groups) {
+        case 2: return launch_wide<1, NTT>(a, lds, st);
+        case 4: return launch_wide<2, NTT>(a, lds, st);
+        case 6: return launch_wide<3, NTT>(a, lds, st);
+        case 8: return launch_wide<4, NTT>(a, lds, st);
+        case 10: return launch_wide<5, NTT>(a, lds, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------- host side
+size_t rows_ring_bytes(int NT, int row_groups, bool extra) {
+    return (size_t)rows_variant(NT, row_groups, extra).stages * (row_groups + (extra ? 1 : 0) + NT) * kGroupBytes;
+}
+size_t wide_ring_bytes(int MT, int NTT) { return wide_stages(MT, NTT) * wide_stage_bytes(MT, NTT); }
+
+hipError_t launch_head_mfma_rows(int NT, const MfmaArgs &a, size_t lds, hipStream_t st) {
+    switch (NT) {
+        case 2: return launch_rows_nt<2>(a, lds, st);
+        case 4: return launch_rows_nt<4>(a, lds, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_head_mfma_wide(int NTT, const MfmaArgs &a, size_t lds, hipStream_t st) {
+    switch (NTT) {
+        case 2: return launch_wide_ntt<2>(a, lds, st);
+        case 3: return launch_wide_ntt<3>(a, lds, st);
+        case 4: return launch_wide_ntt<4>(a, lds, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace vt

@@ -65,6 +65,11 @@ struct StepArgs {
 
 // ---- matrix-core path (n > 8) ----
 constexpr int kMfmaTileRows = 128;     // rows of W_trim per workgroup (16 per wave)
+constexpr int kMfmaMaxN = 256;         // hidden rows one launch covers
+// from this size on h is re-laid for the wide kernel (an XCD's L2 holds 4 MiB: read in place, hidden rows 2 d bytes apart,
+// it shares its channels with W's lines; n = 256, k = 32768, d = 8192: 137.1 us in place, 136.9 re-laid)
+constexpr size_t kPackHBytes = (size_t)4 << 20;
+constexpr int kRowsKernelMaxN = 64;    // ... by tiles that hold all hidden rows per wave; above: the wide kernel
 constexpr int kRowSelectMinL = 11;      // matrix-core path: with more tokens per row than this (8 with more than 8 hidden rows), or
 constexpr int kRowSelectMinLManyRows = 8;
 // small-n path: the same switch when L > 12 - n / 2 (measured crossovers: L = 8 at n = 8, 10 at n = 4, 11-12 at n = 1)
@@ -74,7 +79,7 @@ constexpr int kRowSelectMinWork = 1280; // with n * min(m, 128) from this value 
 constexpr int kMfmaPrefetchUnits = 3;  // 128-column units of W_trim in flight per wave; an h chunk that has a successor
                                        // is a multiple of this many units
 constexpr int kMfmaChunkPieces = 9;    // an h chunk is prefetched through registers: at most this many
-                                       // 16-byte pieces per thread, i.e. 16 * NT * KC * 2 <= 9 * 512 * 16 bytes
+                                       // 16-byte pieces per thread
 
 struct MfmaArgs {
     const void *h;            // [n, d] bf16
@@ -83,12 +88,12 @@ struct MfmaArgs {
     int n, k, d, m;
     int L;                    // candidates kept per (tile, hidden row) = min(m, 128)
     int nlists;               // number of tiles = workgroups = candidate lists per hidden row
-    int KC;                   // columns of h resident in LDS at a time (multiple of 128)
-    int hpitch;               // bytes per hidden row in LDS = KC * 2 + 16
+    int KC;                   // n <= 8: columns of h resident in LDS at a time (multiple of 128)
+    int hpitch;               // n <= 8: bytes per hidden row in LDS = KC * 2 + 16
     unsigned long long *pms;    // [n, nlists]
     unsigned long long *pkeys;  // [n, nlists, L]
     float *out_logp_full;     // [n, k] or null
-    void *hpack;              // more than 64 hidden rows: h re-laid in operand order, d * NT * 32 bytes
+    void *hpack;              // more than 64 hidden rows: or null; h re-laid stage by stage, d * 512 bytes
     float *zbuf;              // [n, k] or null: store the logits and leave the rest of the step to row_select_kernel
     // indexed != 0 (n <= 8 only): hidden row i is row (row_pack >> 8 i) & 255 of h -- rows picked out of a
     // larger batch (several heads per call); the merge kernel maps the output rows the same way
@@ -102,11 +107,13 @@ struct MfmaArgs {
     int nwaves;
     // extra_rows != 0 (8 waves, no column split): the tile is 128 + extra_rows rows, 1 <= extra_rows <= 16; the rows
     // past the 128th form one more 16-row group -- up to 8 hidden rows (all of h in LDS, d a multiple of 1024) its
-    // columns are shared by the eight waves; with more hidden rows their columns follow h's chunk in LDS (16 more
-    // rows of hpitch bytes) and their accumulators live in 3 * NT KiB of LDS at byte offset xoff (behind the chunk,
-    // clear of the logit tile of the epilogue, inside the launch's LDS)
+    // columns are shared by the eight waves; up to 64 it is shared by hidden-row group
     int extra_rows;
-    int xoff;
+    // more than 8 hidden rows: 16-row groups of the tile (without the extra rows), LDS offset of the tile's target ids
+    // (behind the ring of stages, clear of the logit tile and the candidate keys), passes of the wide kernel's epilogue
+    int row_groups;
+    int ids_off;
+    int passes;
     // or null: a word the kernel sets to zero (the merge kernel behind it counts its workgroups there when a tree
     // level is fused; the kernel boundary orders the two)
     unsigned *ticket_clear;
@@ -151,13 +158,18 @@ struct FinalizeArgs {
 constexpr int kFinalizeTreeMaxN = 512;
 
 constexpr int kMfmaMaxWaves = 12;      // three waves per SIMD: 168 registers each
-constexpr int kMfmaFewWaves = 7;       // more than 8 hidden rows: the instantiation for 5 .. 7 waves (smaller tiles for heads that
+constexpr int kMfmaFewWaves = 7;       // 9 .. 64 hidden rows: the instantiation for 5 .. 7 waves (smaller tiles for heads that
                                        // would leave CUs idle with 128-row tiles)
 
 size_t mfma_stage_bytes(int nwaves);
 
-size_t mfma_wide_lds_bytes();   // NT >= 8: two shared unit buffers
-hipError_t launch_head_mfma(int NT, const MfmaArgs &a, size_t lds, hipStream_t st);
+hipError_t launch_head_mfma(const MfmaArgs &a, size_t lds, hipStream_t st);      // up to 8 hidden rows
+// 9 .. 64 hidden rows (NT = 2, 4 groups of 16) and 65 .. 256 (tiles of 64 * NTT hidden rows, NTT = 2 .. 4): bytes of the ring
+// of stages in LDS, and the launches
+size_t rows_ring_bytes(int NT, int row_groups, bool extra);
+size_t wide_ring_bytes(int MT, int NTT);
+hipError_t launch_head_mfma_rows(int NT, const MfmaArgs &a, size_t lds, hipStream_t st);
+hipError_t launch_head_mfma_wide(int NTT, const MfmaArgs &a, size_t lds, hipStream_t st);
 // a.W, a.map, a.k are not read: the table names every head's; a.nlists = tile_first[n_heads]
 hipError_t launch_head_mfma_multi(const MfmaArgs &a, const MultiHeadTable &t, size_t lds_bytes, hipStream_t st);
 hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t st);

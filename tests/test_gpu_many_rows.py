@@ -1,0 +1,69 @@
+"""Draft steps of 9 .. 256 hidden rows at the edges of the kernels that serve them, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2506_22694_amd as vt
+from paper_2506_22694_amd import synth
+from test_gpu_parity import check_full, check_step, run_step
+
+pytestmark = pytest.mark.gpu
+
+
+# Tile heights follow from k (ceil(k / 256) rows, in 16-row groups, on 256 CUs); d: two stages only, an odd number of
+# them, and 32 (d = 2048, 4096: the start of the march rotates over eight, four or two ranges of columns).
+@pytest.mark.parametrize("n,k,d,m,variant", [
+    # up to 64 hidden rows: 1 .. 12 row groups, fewer than eight of them with waves that share one, tiles with extra rows
+    (9, 300, 128, 4, "<2,8>"), (33, 4096, 256, 8, "<4,8>"), (64, 8000, 128, 8, "<4,8>"), (17, 12000, 640, 5, "<2,8>"),
+    (64, 16384, 2048, 8, "<4,8>"), (32, 20000, 256, 8, "<2,7>"), (64, 24576, 128, 8, "<4,7>"), (12, 28672, 128, 3, "<2,7>"),
+    (64, 32768, 256, 16, "<4,8>"), (31, 32769, 128, 8, "<2,8>"), (64, 36864, 384, 8, "<4,8>"), (64, 40960, 128, 8, "<4,12>"),
+    (33, 45056, 256, 2, "<4,12>"), (32, 49152, 128, 8, "<2,12>"), (64, 49153, 128, 8, "<4,"), (20, 70001, 256, 4, "<2,"),
+    # 65 .. 256: two, three and four columns of hidden rows, 32 .. 160 tile rows, two epilogue passes, h re-laid
+    (65, 31, 128, 8, "wide_kernel<1>"), (128, 5000, 256, 8, "wide_kernel<1>"), (100, 16384, 2048, 8, "wide_kernel<1>"),
+    (129, 16000, 384, 4, "wide_kernel<2>"), (192, 24576, 128, 6, "wide_kernel<2>"), (193, 3000, 4096, 2, "wide_kernel<2>"),
+    (160, 9000, 2048, 8, "wide_kernel<2>"), (80, 40960, 128, 8, "wide_kernel<1>"), (250, 40960, 128, 4, "wide_kernel<2>"),
+    (256, 33000, 128, 16, "wide_kernel<2>"), (256, 600, 8192, 4, "pack_h_kernel + head_mfma_wide_kernel<2>"),
+])
+def test_step_many_rows_at_the_edges_of_the_tiles(n, k, d, m, variant):
+    assert variant in vt.draft_head_step_plan(n, k, d, m)
+    W, map_ = synth.trimmed_head_direct(k, d, seed=700 + n, dtype="bf16")
+    h = synth.hidden_rows(n, d, seed=800 + k, dtype="bf16")
+    # equal rows in other tiles, row groups and at the ragged end: equal logits, bit for bit, whatever the start of the march
+    same = sorted({j for j in (3, 19, 128, 143, k // 2, k - 17, k - 1) if 0 <= j < k})
+    W[same] = W[same[0]]
+    ref = oracle.draft_head_step(h, W, map_, m)
+    oi, ol, lse, full = run_step(h, W, map_, m, return_lse=True, return_full=True)
+    assert check_step(oi, ol, ref, map_, m, lse) <= 2 + n // 32
+    check_full(full, ref)
+    dup = full[:, torch.tensor(same, device=full.device)]
+    assert torch.equal(dup, dup[:, :1].expand_as(dup))
+    oi2, ol2 = run_step(h, W, map_, m)
+    assert torch.equal(oi, oi2) and torch.equal(ol, ol2)
+
+
+def test_step_many_rows_captured_in_a_graph_replays_the_same():
+    cases = []
+    for n, k, d, m in ((40, 5000, 512, 8), (100, 3000, 2048, 4), (256, 700, 8192, 16)):
+        W, map_ = synth.trimmed_head_direct(k, d, seed=31, dtype="bf16")
+        h = torch.randn(n, d, device="cuda").bfloat16()
+        W = torch.from_numpy(W.view(np.int16)).cuda().view(torch.bfloat16)
+        out = (torch.empty(n, m, dtype=torch.int32, device="cuda"), torch.empty(n, m, device="cuda"))
+        cases.append((h, W, torch.from_numpy(map_).cuda(), m, vt.StepWorkspace(n, k, d, m, h.device), out))
+    step = lambda c: vt.draft_head_step(*c[:4], ws=c[4], out_ids=c[5][0], out_logp=c[5][1])
+    for c in cases:
+        step(c)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for c in cases:
+            step(c)
+    for rep in range(4):
+        for c in cases:
+            c[0].copy_(torch.randn_like(c[0]))
+        g.replay()
+        got = [[t.clone() for t in c[5]] for c in cases]
+        for c, (ids, logp) in zip(cases, got):
+            step(c)
+            torch.cuda.synchronize()
+            assert torch.equal(c[5][0], ids) and torch.equal(c[5][1], logp), rep
