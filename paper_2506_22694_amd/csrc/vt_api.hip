@@ -607,16 +607,14 @@ int vt_build_trimmed_head_by_rank(const int64_t *counts, int32_t V, const void *
     (void)hipGetLastError();
     hipStream_t st = static_cast<hipStream_t>(stream);
     // the k best ids in rank order are the first k of the full rank order
-    vt::launch_rank_sort(reinterpret_cast<const long long *>(counts), V, static_cast<char *>(ws) + 256, map, k,
-                         nullptr, st);
+    vt::launch_rank_sort(reinterpret_cast<const long long *>(counts), V, static_cast<char *>(ws) + 256, map, k, st);
     if (W != nullptr) vt::launch_gather_rows(W, row_bytes, map, k, W_trim, st);
     return launch_status();
 }
 
 size_t vt_choose_k_ws_bytes(int32_t V) {
     if (V < 1) return 256;
-    return round_up((size_t)V * sizeof(int32_t), 256) + round_up((size_t)V * sizeof(int64_t), 256) +
-           vt::choose_k_scratch_bytes(V) + vt::rank_sort_scratch_bytes(V);
+    return vt::choose_k_ws_bytes(V);
 }
 
 int vt_choose_k(const int64_t *counts, int32_t V, int mode, double p, int64_t min_count, int64_t *out, void *ws,
@@ -629,14 +627,8 @@ int vt_choose_k(const int64_t *counts, int32_t V, int mode, double p, int64_t mi
     if (ws == nullptr || !aligned(ws, 256) || ws_bytes < vt_choose_k_ws_bytes(V)) return VT_ERR_WORKSPACE;
     (void)hipGetLastError();
     hipStream_t st = static_cast<hipStream_t>(stream);
-    char *wsb = static_cast<char *>(ws);
-    int *ids = reinterpret_cast<int *>(wsb);
-    long long *sorted = reinterpret_cast<long long *>(wsb + round_up((size_t)V * sizeof(int32_t), 256));
-    char *bsum = wsb + round_up((size_t)V * sizeof(int32_t), 256) + round_up((size_t)V * sizeof(int64_t), 256);
-    void *scratch = bsum + vt::choose_k_scratch_bytes(V);
-    const long long *c = reinterpret_cast<const long long *>(counts);
-    vt::launch_rank_sort(c, V, scratch, ids, V, sorted, st);
-    vt::launch_choose_k(sorted, V, mode, p, (long long)min_count, bsum, reinterpret_cast<long long *>(out), st);
+    vt::launch_choose_k(reinterpret_cast<const long long *>(counts), V, mode, p, (long long)min_count, ws,
+                        reinterpret_cast<long long *>(out), st);
     return launch_status();
 }
 
@@ -867,21 +859,18 @@ int vt_build_trimmed_heads(const int64_t *counts, int32_t V, int32_t n_heads, co
     static_assert(VT_MAX_HEADS == vt::kSelectMaxHeads, "heads per batched launch");
     (void)hipGetLastError();
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (256 + (size_t)n_heads * vt::select_scratch_stride(V) <= ws_bytes) {
-        // all heads together: the selection's eleven launches and the row copy once, with the head as grid.y
-        // (the selection is bound by its launches: 60 us for one head or sixteen)
-        vt::launch_select_topk_heads(reinterpret_cast<const long long *>(counts), V, n_heads, k,
-                                     static_cast<char *>(ws) + 256, map, st);
+    // as many heads together as the workspace holds tables for (all of them unless V is small): the selection's four
+    // launches and the row copy once per batch, with the head as grid.y
+    const size_t room = (ws_bytes - 256) / vt::select_scratch_stride(V);
+    const int batch = room < 1 ? 1 : room < (size_t)n_heads ? (int)room : n_heads;
+    for (int h0 = 0; h0 < n_heads; h0 += batch) {
+        const int nh = n_heads - h0 < batch ? n_heads - h0 : batch;
+        vt::launch_select_topk_heads(reinterpret_cast<const long long *>(counts) + (size_t)h0 * V, V, nh, k + h0,
+                                     static_cast<char *>(ws) + 256, map + h0, st);
         if (W != nullptr)
-            vt::launch_gather_rows_heads(W, row_bytes, n_heads, k, const_cast<const int *const *>(map), W_trim, st);
-        return launch_status();
+            vt::launch_gather_rows_heads(W, row_bytes, nh, k + h0, const_cast<const int *const *>(map + h0), W_trim + h0, st);
     }
-    for (int hd = 0; hd < n_heads; ++hd) {
-        const int rc = vt_build_trimmed_head(counts + (size_t)hd * V, V, W, w_type, d, k[hd], map[hd],
-                                             W != nullptr ? W_trim[hd] : nullptr, ws, ws_bytes, stream);
-        if (rc != VT_OK) return rc;
-    }
-    return VT_OK;
+    return launch_status();
 }
 
 int vt_draft_tree_level(const void *h, int h_type, int32_t n, const void *W_trim, int w_type, int32_t k, int32_t d,

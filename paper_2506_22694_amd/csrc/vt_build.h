@@ -36,13 +36,13 @@ void launch_gather_rows_heads(const void *W, size_t row_bytes, int n_heads, cons
 // ---- Sec. 3.2: frequency-rank order, Top-P / minimum-count choice of k ----
 constexpr int kRankSortThreads = 1024;
 size_t rank_sort_scratch_bytes(int n);
-// sorts all n ids by (count desc, id asc); out_ids [n_ids] receives the first n_ids of them, out_counts [n] (or
-// null) all sorted counts
-void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_ids, int n_ids, long long *out_counts,
-                      hipStream_t st);
-// out: [3] = k, mass of the k largest counts, total mass; scratch: choose_k_scratch_bytes(V)
-size_t choose_k_scratch_bytes(int V);
-void launch_choose_k(const long long *sorted_counts, int V, int mode, double P, long long f_min, void *scratch,
-                     long long *out, hipStream_t st);
+// sorts all n ids by (count desc, id asc); out_ids [n_ids] receives the first n_ids of them
+void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_ids, int n_ids, hipStream_t st);
+// out: [3] = k, mass of the k largest counts, total mass; scratch: choose_k_ws_bytes(V)
+size_t choose_k_ws_bytes(int V);
+// up to this V one workgroup does it all (and the workspace holds no tables)
+constexpr int kChooseDirectMaxV = 4096;
+void launch_choose_k(const long long *counts, int V, int mode, double P, long long f_min, void *scratch, long long *out,
+                     hipStream_t st);
 
 }  // namespace vt

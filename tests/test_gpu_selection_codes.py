@@ -1,0 +1,57 @@
+"""Selection, rank order and choice of k where counts leave the exact range of their codes, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2506_22694_amd as vt
+
+pytestmark = pytest.mark.gpu
+
+
+def _counts(kind, V, rng):
+    if kind == "around 2048":              # the last exact histogram bin and the first wide ones
+        return rng.integers(2040, 2120, size=V)
+    if kind == "around 2^19":              # the last count the rank codes hold exactly
+        return rng.integers(2**19 - 40, 2**19 + 40, size=V)
+    if kind == "large and equal":
+        return np.full(V, 3 * 2**30 + 5)
+    if kind == "large, few values":        # equal codes, counts apart in their last bits, in no order
+        return (1 << 40) + rng.integers(0, 3, size=V)
+    if kind == "powers of two":
+        # (the total stays below 2^53: the oracle's ceil(P * total) is exact there)
+        return np.left_shift(1, rng.integers(0, 37, size=V).astype(np.int64))
+    if kind == "heavy tail":
+        return np.floor(1e6 * rng.random(V) ** 12).astype(np.int64) + (rng.random(V) < 0.01) * 10**7
+    raise ValueError(kind)
+
+
+# V: one workgroup, its edge, the largest V that one workgroup chooses k for and one more, many workgroups
+@pytest.mark.parametrize("V", [1, 1024, 1025, 4096, 4097, 30011])
+@pytest.mark.parametrize("kind", ["around 2048", "around 2^19", "large and equal", "large, few values", "powers of two", "heavy tail"])
+def test_selection_at_the_edges_of_the_codes(kind, V):
+    if kind == "large, few values" and V > 4097:
+        V = 4097          # (ordered by counting inside a run: one run of all ids)
+    rng = np.random.default_rng(V + len(kind))
+    c = np.asarray(_counts(kind, V, rng), dtype=np.int64)
+    dc = torch.from_numpy(c).cuda()
+    order = oracle.rank_order(c)
+    for k in sorted({1, V // 7 + 1, V // 2 + 1, V}):
+        a, _ = vt.build_trimmed_head(dc, None, k)
+        assert np.array_equal(a.cpu().numpy(), oracle.select(c, k)), k
+        b, _ = vt.build_trimmed_head(dc, None, k, order="rank")
+        assert np.array_equal(b.cpu().numpy(), order[:k]), k
+    for P in (0.0, 1e-9, 0.25, 0.9, 1.0):
+        assert vt.choose_k(dc, top_p=P) == oracle.choose_k_top_p(c, P), P
+    for f in (0, 1, 2047, 2048, 2049, 2**19, int(c[0]), int(c.max()) + 1):
+        assert vt.choose_k(dc, min_count=f) == oracle.choose_k_min_count(c, f), f
+
+
+@pytest.mark.parametrize("V,heads", [(700, 16), (5000, 5), (20000, 16)])
+def test_several_heads_selected_in_as_many_batches_as_the_workspace_holds(V, heads):
+    rng = np.random.default_rng(heads)
+    c = np.stack([np.asarray(_counts(k, V, rng), dtype=np.int64) for k in
+                  (["heavy tail", "around 2048", "powers of two", "large and equal"] * 4)[:heads]])
+    ks = [int(rng.integers(1, V + 1)) for _ in range(heads)]
+    for (m, _), row, k in zip(vt.build_trimmed_heads(torch.from_numpy(c).cuda(), None, ks), c, ks):
+        assert np.array_equal(m.cpu().numpy(), oracle.select(row, k))
