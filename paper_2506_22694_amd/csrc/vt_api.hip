@@ -563,7 +563,7 @@ int vt_count_tokens(const void *ids, int id_type, int64_t n_ids, int32_t V, int6
     return device_status(vt::launch_count_tokens(ids, id_type == VT_I64, n_ids, V,
                                                  reinterpret_cast<long long *>(counts),
                                                  reinterpret_cast<unsigned long long *>(n_invalid),
-                                                 static_cast<unsigned *>(ws), static_cast<hipStream_t>(stream)));
+                                                 ws, static_cast<hipStream_t>(stream)));
 }
 
 // ------------------------------------------------------------------ Eq. 1

@@ -15,9 +15,9 @@ constexpr int kHistUnroll = 6;            // 16-byte id vectors in flight per th
 
 int hist_num_ranges(int V);
 int hist_num_chunks(int64_t n_ids, int V);
-// partial: [chunks, V rounded up to even] 16-bit scratch
+// partial: [chunks, V rounded up to a multiple of four] bytes (the workspace holds twice that)
 hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V, long long *counts,
-                         unsigned long long *n_invalid, unsigned *partial, hipStream_t st);
+                         unsigned long long *n_invalid, void *partial, hipStream_t st);
 
 // ---- Eq. 1 ----
 constexpr int kSelectThreads = 1024;

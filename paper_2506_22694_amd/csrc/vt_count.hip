@@ -4,9 +4,13 @@
 // are 16 bits wide, two per LDS word, the vocabulary is cut into ranges of 65536 bins (128 KiB of
 // LDS; two ranges for V = 128256) and the id stream into chunks.  Workgroup (chunk, range) reads
 // its chunk with 16-byte loads, counts the ids that fall into its range with LDS atomics (no
-// global atomic sees the Zipf-hot ids more than once per 32768 occurrences), and writes its
-// private histogram to scratch.  A second kernel sums the chunk histograms into the caller's
-// int64 counters.  Ids outside [0, V) are skipped and tallied.
+// global atomic sees the Zipf-hot ids more than once per 32768 occurrences), and writes the low eight bits of
+// its private histogram to scratch (what a bin has beyond them, in a few dozen bins, goes to the result by atomics).
+// A second kernel sums the chunk histograms into the caller's int64 counters.  Ids outside [0, V) are skipped and tallied.
+// What bounds it at 10^8 ids is the reading of the stream once per range: 106 us, of which 100 remain without any LDS
+// atomic and 47 without the loads; a second batch in flight per thread makes it slower (109; 64-bit ids 214 against
+// 168): the two workgroups of a chunk drift apart and miss each other's lines in the L2.  At 10^7 ids (22.8 us; 25.4
+// with 16-bit rows and the last vectors of a chunk requested one by one) a fifth is the loads, a fifth the rows.
 //
 // A 16-bit bin never holds more than 15 bits for long: the increment that sets bit 15 (it sees the
 // old value 0x7FFF) takes 32768 back out of the bin and adds them to the result counter directly.
@@ -37,14 +41,14 @@ int hist_num_chunks(int64_t n_ids, int V) {
 template <bool IDS64>
 __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *__restrict__ ids_v, long long n_ids,
                                                                     int head, int V, int nchunks,
-                                                                    unsigned *__restrict__ partial,
+                                                                    unsigned char *__restrict__ partial,
                                                                     unsigned long long *__restrict__ counts,
                                                                     unsigned long long *__restrict__ n_invalid) {
     extern __shared__ __align__(16) unsigned words[];     // two 16-bit bins per word
     const int chunk = blockIdx.x, range = blockIdx.y;
     const int lo = range * kHistBinsPerBlock;
     const int nb = min(kHistBinsPerBlock, V - lo);
-    const int nw = (nb + 1) >> 1;
+    const int nw = ((nb + 3) & ~3) >> 1;                  // whole groups of four bins: the rows are written by fours
     for (int b = threadIdx.x; b < nw; b += kHistThreads) words[b] = 0u;
     __syncthreads();
 
@@ -150,21 +154,31 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
         unpack(q1, t + IPV0);
         tally_ids(std::integral_constant<int, 2 * IPV0>{}, t);
     };
-    // kHistUnroll vectors per thread are requested before the first is counted: one 16-byte load per
+    // kHistUnroll vectors per thread are requested at a time: one 16-byte load per
     // thread in flight (16 KiB per CU) is far below what the memory latency needs.  Plain (cached) loads:
     // the workgroups of one chunk (one per range) are dispatched to the same XCD and read the same ids at
     // about the same time, so three of the four reads can hit its L2; a streaming hint would drop the
     // lines after the first use (10^7 ids: 41.2 -> 35.1 us)
+    constexpr long long kBatch = (long long)kHistUnroll * kHistThreads;
+    static_assert(kHistUnroll % 2 == 0, "vectors are counted in pairs");
     long long v = v0 + threadIdx.x;
-    for (; v + (long long)(kHistUnroll - 1) * kHistThreads < v1; v += (long long)kHistUnroll * kHistThreads) {
+    for (; v + kBatch - kHistThreads < v1; v += kBatch) {
         u32x4 q[kHistUnroll];
 #pragma unroll
         for (int u = 0; u < kHistUnroll; ++u) q[u] = vp[v + (long long)u * kHistThreads];
-        static_assert(kHistUnroll % 2 == 0, "vectors are counted in pairs");
 #pragma unroll
         for (int u = 0; u < kHistUnroll; u += 2) tally_vec2(q[u], q[u + 1]);
     }
-    for (; v < v1; v += kHistThreads) tally_vec(vp[v]);
+    if (v < v1) {
+        // the last vectors, requested together as well (past the end: the first of them again, not counted)
+        u32x4 q[kHistUnroll - 1];
+#pragma unroll
+        for (int u = 0; u < kHistUnroll - 1; ++u) q[u] = vp[v + (long long)u * kHistThreads < v1 ? v + (long long)u * kHistThreads : v];
+#pragma unroll
+        for (int u = 0; u < kHistUnroll - 1; ++u) {
+            if (v + (long long)u * kHistThreads < v1) tally_vec(q[u]);
+        }
+    }
     if (chunk == 0 && (int)threadIdx.x < head) {   // scalar head
         if constexpr (IDS64) tally(static_cast<const long long *>(ids_v)[threadIdx.x]);
         else tally((long long)static_cast<const int *>(ids_v)[threadIdx.x]);
@@ -177,9 +191,32 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
         }
     }
     __syncthreads();
-    // rows of the scratch are (V rounded up to even) 16-bit bins long: every range starts on a word
-    unsigned *dst = partial + (((size_t)chunk * (size_t)((V + 1) & ~1) + lo) >> 1);
-    for (int b = threadIdx.x; b < nw; b += kHistThreads) dst[b] = words[b];
+    // A row of the scratch holds eight bits per id: what a bin has beyond them goes to the result counter (a few dozen
+    // ids of a chunk), and the rows are written and read back at half the size of the bins.
+    unsigned char *dst = partial + (size_t)chunk * (size_t)((V + 3) & ~3) + lo;
+    auto low_bytes = [&](unsigned w0, unsigned w1, int bin) {      // four bins: two words
+        if (((w0 | w1) & 0xFF00FF00u) != 0u) {
+            const unsigned c4[4] = {w0 & 0xFFFFu, w0 >> 16, w1 & 0xFFFFu, w1 >> 16};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (c4[e] > 255u) atomicAdd(&counts[lo + bin + e], (unsigned long long)(c4[e] & ~255u));
+        }
+        return __builtin_amdgcn_perm(w1, w0, 0x06040200u);      // bytes 0 and 2 of either word
+    };
+    if ((V & 15) == 0) {
+        for (int b = 16 * threadIdx.x; b < nb; b += 16 * kHistThreads) {
+            const u32x4 x0 = *reinterpret_cast<const u32x4 *>(words + b / 2), x1 = *reinterpret_cast<const u32x4 *>(words + b / 2 + 4);
+            u32x4 y;
+            y.x = low_bytes(x0.x, x0.y, b);
+            y.y = low_bytes(x0.z, x0.w, b + 4);
+            y.z = low_bytes(x1.x, x1.y, b + 8);
+            y.w = low_bytes(x1.z, x1.w, b + 12);
+            *reinterpret_cast<u32x4 *>(dst + b) = y;
+        }
+    } else {
+        for (int b = 4 * threadIdx.x; b < nb; b += 4 * kHistThreads)
+            *reinterpret_cast<unsigned *>(dst + b) = low_bytes(words[b / 2], words[b / 2 + 1], b);
+    }
     // every range-workgroup of a chunk sees the same invalid ids: only range 0 reports them
     if (n_invalid != nullptr && range == 0) {
         const int tot = wave_sum_i32((int)invalid);
@@ -187,51 +224,48 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
     }
 }
 
-// A workgroup sums 64 words (128 neighbouring bins) over the chunks: wave g takes the chunks g, g + 4, ..
-// (a load instruction reads 256 consecutive bytes of one chunk's row), the four partial sums meet in LDS.
-__global__ void __launch_bounds__(256) hist_reduce_kernel(const unsigned *__restrict__ partial, int nchunks, int V,
-                                                          long long *__restrict__ counts) {
-    __shared__ long long part[3][2][kWave];
+// A workgroup sums 256 neighbouring ids (a 4-byte word per lane) over the chunks: wave g takes the chunks g, g + 8, ..,
+// sixteen loads in flight; the words' bytes are added as pairs of 16 bits (at most 256 chunks of 255: 65280), and the
+// eight partial sums meet in LDS.
+constexpr int kReduceWaves = 8;
+__global__ void __launch_bounds__(kReduceWaves *kWave) hist_reduce_kernel(const unsigned *__restrict__ partial, int nchunks, int V,
+                                                                          long long *__restrict__ counts) {
+    __shared__ unsigned part[kReduceWaves][2][kWave];
     const int lane = (int)threadIdx.x & 63, g = (int)threadIdx.x >> 6;
     const int wi = blockIdx.x * kWave + lane;
-    const int Vw = (V + 1) >> 1;                   // words per scratch row
-    long long s0 = 0, s1 = 0;
+    const int Vw = (V + 3) >> 2;                   // words per scratch row
+    unsigned even = 0, odd = 0;                    // ids 4 wi, 4 wi + 2 and 4 wi + 1, 4 wi + 3
     if (wi < Vw) {
-        int c = g;
-        for (; c + 12 < nchunks; c += 16) {
-            unsigned t[4];
+        constexpr int kLoads = 16;
+        for (int c = g; c < nchunks; c += kLoads * kReduceWaves) {
+            unsigned t[kLoads];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) t[u] = partial[(size_t)(c + 4 * u) * Vw + wi];
+            for (int u = 0; u < kLoads; ++u)
+                t[u] = c + u * kReduceWaves < nchunks ? partial[(size_t)(c + u * kReduceWaves) * Vw + wi] : 0u;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                s0 += (long long)(t[u] & 0xFFFFu);
-                s1 += (long long)(t[u] >> 16);
+            for (int u = 0; u < kLoads; ++u) {
+                even += t[u] & 0x00FF00FFu;
+                odd += (t[u] >> 8) & 0x00FF00FFu;
             }
         }
-        for (; c < nchunks; c += 4) {
-            const unsigned t = partial[(size_t)c * Vw + wi];
-            s0 += (long long)(t & 0xFFFFu);
-            s1 += (long long)(t >> 16);
-        }
     }
-    if (g > 0) {
-        part[g - 1][0][lane] = s0;
-        part[g - 1][1][lane] = s1;
-    }
+    part[g][0][lane] = even;
+    part[g][1][lane] = odd;
     __syncthreads();
-    if (g == 0 && wi < Vw) {
+    // thread t < 256: id 256 * block + t
+    const int t = (int)threadIdx.x, id = blockIdx.x * 4 * kWave + t;
+    if (t < 4 * kWave && id < V) {
+        unsigned sum = 0;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            s0 += part[q][0][lane];
-            s1 += part[q][1][lane];
-        }
-        counts[2 * wi] += s0;
-        if (2 * wi + 1 < V) counts[2 * wi + 1] += s1;
+        for (int q = 0; q < kReduceWaves; ++q) sum += part[q][t & 1][t >> 2] >> (8 * (t & 2)) & 0xFFFFu;
+        counts[id] += (long long)sum;
     }
 }
+static_assert(kHistBlocks <= 257, "sums over the chunks of eight-bit parts fit 16 bits");
 
 hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V, long long *counts,
-                         unsigned long long *n_invalid, unsigned *partial, hipStream_t st) {
+                         unsigned long long *n_invalid, void *partial, hipStream_t st) {
+    unsigned char *rows = static_cast<unsigned char *>(partial);
     const int nchunks = hist_num_chunks(n_ids, V);
     const int nranges = hist_num_ranges(V);
     const size_t lds = (size_t)kHistBinsPerBlock * sizeof(unsigned short);
@@ -247,12 +281,12 @@ hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V
     if (head > n_ids) head = n_ids;
     if (ids64)
         hipLaunchKernelGGL(hist_partial_kernel<true>, grid, dim3(kHistThreads), lds, st, ids, (long long)n_ids,
-                           (int)head, V, nchunks, partial, reinterpret_cast<unsigned long long *>(counts), n_invalid);
+                           (int)head, V, nchunks, rows, reinterpret_cast<unsigned long long *>(counts), n_invalid);
     else
         hipLaunchKernelGGL(hist_partial_kernel<false>, grid, dim3(kHistThreads), lds, st, ids, (long long)n_ids,
-                           (int)head, V, nchunks, partial, reinterpret_cast<unsigned long long *>(counts), n_invalid);
-    hipLaunchKernelGGL(hist_reduce_kernel, dim3(((V + 1) / 2 + kWave - 1) / kWave), dim3(256), 0, st, partial, nchunks, V,
-                       counts);
+                           (int)head, V, nchunks, rows, reinterpret_cast<unsigned long long *>(counts), n_invalid);
+    hipLaunchKernelGGL(hist_reduce_kernel, dim3(((V + 3) / 4 + kWave - 1) / kWave), dim3(kReduceWaves * kWave), 0, st,
+                       reinterpret_cast<const unsigned *>(rows), nchunks, V, counts);
     return hipGetLastError();
 }
 

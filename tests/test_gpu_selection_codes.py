@@ -55,3 +55,18 @@ def test_several_heads_selected_in_as_many_batches_as_the_workspace_holds(V, hea
     ks = [int(rng.integers(1, V + 1)) for _ in range(heads)]
     for (m, _), row, k in zip(vt.build_trimmed_heads(torch.from_numpy(c).cuda(), None, ks), c, ks):
         assert np.array_equal(m.cpu().numpy(), oracle.select(row, k))
+
+
+# rows of eight bits per id between the two kernels: V on and off the 16-byte stores, one range of bins and its edge;
+# bins of 255, 256 and far more in one chunk, in neighbouring ids; a last batch of every length
+@pytest.mark.parametrize("V", [1, 3, 16, 4098, 65536, 65537, 65552, 131075])
+@pytest.mark.parametrize("dtype", [torch.int32, torch.int64])
+def test_count_bins_beyond_eight_bits(V, dtype):
+    rng = np.random.default_rng(V)
+    hot = [t for t in (0, 1, 2, 3, V // 2, V - 2, V - 1) if 0 <= t < V]
+    parts = [np.full(reps, t) for t, reps in zip(hot, (255, 256, 257, 511, 512, 70000, 40001))]
+    ids = np.concatenate(parts + [rng.integers(0, V, size=150_000 + 1024 * (V % 7) + V % 5)])
+    rng.shuffle(ids)
+    for n in (ids.size, ids.size - 1, ids.size - 4097, 5):
+        c = vt.count_tokens(torch.from_numpy(ids[:n]).to(dtype).cuda(), V)
+        assert np.array_equal(c.cpu().numpy(), np.bincount(ids[:n], minlength=V)), n
