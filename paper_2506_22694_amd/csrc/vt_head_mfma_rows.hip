@@ -61,8 +61,10 @@ __device__ __forceinline__ void wait_stage_and_sync(int younger) {
 // ---------------------------------------------------------------- column ranges
 // All workgroups march over the columns of their rows in step, and rows of W are d * 2 bytes apart: when that is a
 // multiple of 4 KiB the requests in flight crowd a subset of the HBM channels (n = 64, k = 32768, d = 4096: 63 us; d = 2048:
-// 36 us).  So the contraction is cut into NR ranges of columns and workgroup b starts with range (b / 8) % NR -- b % 8 is
-// the XCD -- and wraps around (NR = 4: 44.5 and 32.9 us, NR = 8: 43.0 and 24.8).  To keep a logit's rounding independent
+// 36 us).  So the contraction is cut into NR ranges of columns and workgroup b starts with range (b / 8 + b / 64) % NR --
+// b % 8 is the XCD -- and wraps around (NR = 4: 44.5 and 32.9 us, NR = 8: 43.0 and 24.8; without the b / 64 tiles of 96 or
+// 160 rows, whole multiples of many pages apart, meet again: d = 4096, n = 32, k = 22786 35.0 against 31.6 us, k = 40000
+// 56.7 / 51.7).  To keep a logit's rounding independent
 // of where its workgroup started (equal rows of W give equal logits in whichever tile they lie) every range is
 // accumulated from zero in ascending order and the sums are added up as a balanced tree,
 // ((R0 + R1) + (R2 + R3)) + ((R4 + R5) + (R6 + R7)): float addition commutes, so the ranges can finish in any rotation.
@@ -139,7 +141,7 @@ struct March {
     }
     __device__ __forceinline__ March(int ns_, int d) : ns(ns_) {
         rotate = NR > 1 && d % 2048 == 0 && (NR > 2 || d >= 4096);
-        rot = rotate ? ((int)blockIdx.x >> 3) & (NR - 1) : 0;
+        rot = rotate ? (((int)blockIdx.x >> 3) + ((int)blockIdx.x >> 6)) & (NR - 1) : 0;
         start = bound(rot, ns);
     }
     // stage of the row that is multiplied at step s < ns
@@ -193,10 +195,12 @@ __device__ __forceinline__ void tile_epilogue(const MfmaArgs &a, const float *zt
 // X: tiles of 128 + 1 .. 16 rows (the paper's trimmed sizes, so that all 256 CUs stream equal shares): the rows past
 // the 128th are a ninth group in LDS that wave t < NT multiplies by hidden-row group t beside its own rows, the same
 // operand layout, instructions and ranges, so equal rows give equal logits in whichever group they lie.
+// A stage is KB blocks of 64 columns: one for the tiles whose block is several kilobytes per wave, two for smaller ones,
+// which would spend their time at the barriers (k = 16384, n = 9, d = 2048: 23.4 us with one, 20.2 with two).
 // NST stages in LDS; LPW load instructions per wave and stage.
 // k = 32768, d = 4096: n = 64 43.0 us with the logits stored, n = 32 42.1 (a plain read of the 268 MB: 40.8; the
 // register-staged kernel before this one: 52.0 and 46.5).
-template <int NT, int MAXW, int TPW, int NST, int LPW, bool X>
+template <int NT, int MAXW, int TPW, int KB, int NST, int LPW, bool X>
 __global__ void __launch_bounds__(MAXW *kWave) __attribute__((amdgpu_waves_per_eu(1, (MAXW + 3) / 4)))
 head_mfma_kernel(const MfmaArgs a) {
     static_assert(!X || (MAXW == kStepWaves && TPW == NT), "the ninth group belongs to tiles of eight waves");
@@ -217,7 +221,8 @@ head_mfma_kernel(const MfmaArgs a) {
     const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs;
     const char *hb = static_cast<const char *>(a.h);
     const March<NR> march(a.d / kStageCols, a.d);
-    const unsigned stage_bytes = (unsigned)(GR + NT) * kGroupBytes;
+    const unsigned block_bytes = (unsigned)(GR + NT) * kGroupBytes, stage_bytes = KB * block_bytes;
+    const int nstages = march.ns / KB;             // (d is a multiple of 128: an even number of blocks)
 
     // Loads of a stage: pieces of 8 rows, first W's (two per group), then h's; the waves take LPW consecutive ones each,
     // and what is left over repeats pieces of h (the same bytes to the same place).  Rows past the end repeat the last.
@@ -225,20 +230,22 @@ head_mfma_kernel(const MfmaArgs a) {
 #pragma unroll
     for (int j = 0; j < LPW; ++j) {
         const int x = w * LPW + j;
-        const bool is_w = x < 2 * GR;
-        const int p = is_w ? x : (x - 2 * GR) % (2 * NT);
+        const bool is_w = x < KB * 2 * GR;
+        const int y = is_w ? x : (x - KB * 2 * GR) % (KB * 2 * NT);
+        const int blk = KB == 1 ? 0 : y >= (is_w ? 2 * GR : 2 * NT) ? 1 : 0;
+        const int p = y - blk * (is_w ? 2 * GR : 2 * NT);
         const int r = 8 * p + (lane >> 3);
         const int c = (lane & 7) ^ ((r >> 1) & 7);
         const int row = is_w ? min(r, rows_b - 1) : min(r, a.n - 1);
-        voff[j] = (unsigned)row * rs + (unsigned)c * 16u;
-        lds_at[j] = (unsigned)(is_w ? p : 2 * GR + p) * kPieceBytes;
+        voff[j] = (unsigned)row * rs + (unsigned)(blk * 128 + c * 16);
+        lds_at[j] = (unsigned)blk * block_bytes + (unsigned)(is_w ? p : 2 * GR + p) * kPieceBytes;
     }
     auto load_stage = [&](int s, int slot) {
-        const size_t col = (size_t)march.stage_of(s) * 128;
+        const size_t col = (size_t)march.stage_of(s * KB) * 128;      // (ranges are whole stages)
 #pragma unroll
         for (int j = 0; j < LPW; ++j) {
             const unsigned at = (unsigned)slot * stage_bytes + lds_at[j];
-            if (w * LPW + j < 2 * GR)
+            if (w * LPW + j < KB * 2 * GR)
                 lds_load16<true>(at, voff[j], Wt + col);
             else
                 lds_load16<false>(at, voff[j], hb + col);
@@ -252,7 +259,7 @@ head_mfma_kernel(const MfmaArgs a) {
     }
 #pragma unroll
     for (int s = 0; s < NST - 1; ++s) {
-        if (s < march.ns) load_stage(s, s);
+        if (s < nstages) load_stage(s, s);
     }
 
     f32x4 acc[NA];
@@ -273,36 +280,39 @@ head_mfma_kernel(const MfmaArgs a) {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), c, 0, 0, 0);
     };
     int slot = 0, closed = 0;
-    int left = march.end_of(0) - march.start;      // stages until the open range ends
-    for (int s = 0; s < march.ns; ++s) {
-        wait_stage_and_sync<LPW, NST - 2>(march.ns - 1 - s);      // stage s is in LDS, the slot of stage s - 1 is free
-        if (s + NST - 1 < march.ns) load_stage(s + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+    int left = march.end_of(0) - march.start;      // blocks until the open range ends
+    for (int s = 0; s < nstages; ++s) {
+        wait_stage_and_sync<LPW, NST - 2>(nstages - 1 - s);      // stage s is in LDS, the slot of stage s - 1 is free
+        if (s + NST - 1 < nstages) load_stage(s + NST - 1, slot == 0 ? NST - 1 : slot - 1);
         if (march.rotate) {
             if (left == 0) {
                 sums.close(acc, march.rot, closed);
                 ++closed;
                 left = march.ns / NR;
             }
-            --left;
+            left -= KB;
         }
         const unsigned char *sb = smem + (unsigned)slot * stage_bytes;
         slot = slot == NST - 1 ? 0 : slot + 1;
         if (active) {
-            u32x4 av[2], bv[2][TPW];
+            u32x4 av[2 * KB], bv[2 * KB][TPW];
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {       // (piece 4 ks + lgrp: bit 2 of the piece number is 64 bytes)
-                av[ks] = *reinterpret_cast<const u32x4 *>(sb + (rd_w ^ (ks * 64u)));
+            for (int ks = 0; ks < 2 * KB; ++ks) {       // (piece 4 ks + lgrp: bit 2 of the piece number is 64 bytes)
+                const unsigned char *kb = sb + (ks >> 1) * block_bytes;
+                const unsigned half = (ks & 1) * 64u;
+                av[ks] = *reinterpret_cast<const u32x4 *>(kb + (rd_w ^ half));
 #pragma unroll
                 for (int t = 0; t < TPW; ++t)
-                    bv[ks][t] = *reinterpret_cast<const u32x4 *>(sb + (rd_h ^ (ks * 64u)) + t * kGroupBytes);
+                    bv[ks][t] = *reinterpret_cast<const u32x4 *>(kb + (rd_h ^ half) + t * kGroupBytes);
             }
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
+            for (int ks = 0; ks < 2 * KB; ++ks) {
 #pragma unroll
                 for (int t = 0; t < TPW; ++t) product(av[ks], bv[ks][t], acc[t]);
             }
         }
         if constexpr (X) {
+            static_assert(!X || KB == 1, "tiles with extra rows have stages of one block");
             if (ninth) {
                 u32x4 av[2], bv[2];
 #pragma unroll
@@ -521,22 +531,37 @@ hipError_t launch_tile(const MfmaArgs &a, int threads, size_t lds, hipStream_t s
 
 constexpr int kRingBytes = 156 * 1024;         // LDS for the ring; the ids and what the epilogue needs fit behind it
 
-// Stages of a ring and loads per wave and stage of head_mfma_kernel's variants.
+// Variants of head_mfma_kernel: most waves, hidden-row groups per wave, blocks per stage, stages, loads per wave and stage.
 struct RowsVariant {
-    int max_waves, tpw, stages, loads;
+    int max_waves, tpw, blocks, stages, loads;
 };
 constexpr RowsVariant rows_variant(int NT, int row_groups, bool extra) {
-    if (extra) return NT == 2 ? RowsVariant{8, 2, 7, 3} : RowsVariant{8, 4, 6, 4};
-    if (row_groups <= 4)
-        return NT == 2 ? RowsVariant{8, 1, 12, 2} : row_groups <= 2 ? RowsVariant{8, 1, 12, 2} : RowsVariant{8, 2, 9, 2};
-    if (row_groups <= kMfmaFewWaves) return NT == 2 ? RowsVariant{7, 2, 8, 3} : RowsVariant{7, 4, 7, 4};
-    if (row_groups == kStepWaves) return NT == 2 ? RowsVariant{8, 2, 7, 3} : RowsVariant{8, 4, 6, 3};
-    return NT == 2 ? RowsVariant{12, 2, 5, 3} : row_groups == 12 ? RowsVariant{12, 4, 4, 3} : RowsVariant{12, 4, 5, 3};
+    if (extra) return NT == 2 ? RowsVariant{8, 2, 1, 7, 3} : RowsVariant{8, 4, 1, 6, 4};
+    if (row_groups <= 2) return NT == 2 ? RowsVariant{8, 1, 2, 9, 2} : RowsVariant{8, 1, 2, 6, 3};
+    if (row_groups <= 4) return NT == 2 ? RowsVariant{8, 1, 2, 6, 3} : RowsVariant{8, 2, 2, 4, 4};
+    if (row_groups <= kMfmaFewWaves) return NT == 2 ? RowsVariant{7, 2, 2, 4, 6} : RowsVariant{7, 4, 1, 7, 4};
+    if (row_groups == kStepWaves) return NT == 2 ? RowsVariant{8, 2, 1, 7, 3} : RowsVariant{8, 4, 1, 6, 3};
+    return NT == 2 ? RowsVariant{12, 2, 1, 5, 3} : row_groups == 12 ? RowsVariant{12, 4, 1, 4, 3} : RowsVariant{12, 4, 1, 5, 3};
 }
+// (every piece of a stage has a load; the ring fits)
+constexpr bool rows_variant_ok(int NT, int row_groups, bool extra) {
+    const RowsVariant v = rows_variant(NT, row_groups, extra);
+    const int groups = row_groups + (extra ? 1 : 0) + NT, waves = row_groups <= 4 ? kStepWaves : row_groups;
+    return waves <= v.max_waves && v.loads * waves >= 2 * v.blocks * groups &&
+           v.stages * v.blocks * groups * kGroupBytes <= kRingBytes && v.loads * (v.stages - 2) <= 63 &&
+           v.tpw * (row_groups <= 4 ? kStepWaves / row_groups : 1) >= NT;
+}
+static_assert(rows_variant_ok(2, 8, true) && rows_variant_ok(4, 8, true));
+static_assert(rows_variant_ok(2, 1, false) && rows_variant_ok(2, 2, false) && rows_variant_ok(2, 3, false) && rows_variant_ok(2, 4, false));
+static_assert(rows_variant_ok(2, 5, false) && rows_variant_ok(2, 6, false) && rows_variant_ok(2, 7, false) && rows_variant_ok(2, 8, false));
+static_assert(rows_variant_ok(2, 9, false) && rows_variant_ok(2, 10, false) && rows_variant_ok(2, 11, false) && rows_variant_ok(2, 12, false));
+static_assert(rows_variant_ok(4, 1, false) && rows_variant_ok(4, 2, false) && rows_variant_ok(4, 3, false) && rows_variant_ok(4, 4, false));
+static_assert(rows_variant_ok(4, 5, false) && rows_variant_ok(4, 6, false) && rows_variant_ok(4, 7, false) && rows_variant_ok(4, 8, false));
+static_assert(rows_variant_ok(4, 9, false) && rows_variant_ok(4, 10, false) && rows_variant_ok(4, 11, false) && rows_variant_ok(4, 12, false));
 template <int NT, int RG, bool X>
 hipError_t launch_rows(const MfmaArgs &a, size_t lds, hipStream_t st) {
     constexpr RowsVariant v = rows_variant(NT, RG, X);
-    return launch_tile<head_mfma_kernel<NT, v.max_waves, v.tpw, v.stages, v.loads, X>>(a, a.nwaves * kWave, lds, st);
+    return launch_tile<head_mfma_kernel<NT, v.max_waves, v.tpw, v.blocks, v.stages, v.loads, X>>(a, a.nwaves * kWave, lds, st);
 }
 template <int NT>
 hipError_t launch_rows_nt(const MfmaArgs &a, size_t lds, hipStream_t st) {
@@ -591,7 +616,8 @@ hipError_t launch_wide_ntt(const MfmaArgs &a, size_t lds, hipStream_t st) {
 
 // ---------------------------------------------------------------- host side
 size_t rows_ring_bytes(int NT, int row_groups, bool extra) {
-    return (size_t)rows_variant(NT, row_groups, extra).stages * (row_groups + (extra ? 1 : 0) + NT) * kGroupBytes;
+    const RowsVariant v = rows_variant(NT, row_groups, extra);
+    return (size_t)v.stages * v.blocks * (row_groups + (extra ? 1 : 0) + NT) * kGroupBytes;
 }
 size_t wide_ring_bytes(int MT, int NTT) { return wide_stages(MT, NTT) * wide_stage_bytes(MT, NTT); }
 
