@@ -15,6 +15,7 @@
 //   * a second small kernel merges the tiles: one wave per hidden row.
 #include "vt_device.h"
 #include "vt_launch.h"
+#include "vt_ranges.h"
 #include "vt_step.h"
 #include "vt_step_tail.h"
 #include "vt_tree_dev.h"
@@ -26,7 +27,6 @@ namespace vt {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kUnitCols = 128;                       // columns per staged unit (256 B per row)
 constexpr int kStagePitch = 272;                     // bytes per staged row: 256 + 16 (bank spread)
@@ -141,24 +141,15 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     const int nun = nunits / KS;                       // units of this wave's own rows
     const int PL = nunits / 8;                         // XG: units per column part
     const int ntot = XG ? nun + PL : nun;              // units this wave streams
-    // Every workgroup marches over the columns of its 128 rows; if all of them sat in the same column
-    // stripe of W at the same time (rows are d * 2 bytes apart) the requests would crowd a subset of the
-    // HBM channels (measured: 5.7 instead of 6.7 TB/s).  So the contraction is cut into four column ranges
-    // and workgroup b starts with range (b / 8) % 4 -- b % 8 is the XCD -- and wraps around.  Each range
-    // R0..R3 is accumulated from zero in ascending order and the logit is (R0 + R1) + (R2 + R3); float
-    // addition commutes, so that value does not depend on where the workgroup started (equal rows of W
-    // give equal logits in whichever tile they lie).  Two sets of registers hold the finished ranges:
-    // ranges finish in the order rot, rot + 1, .. and the k-th to finish is added to set
-    // {0, 0, 1, 1}[k] for an even start, {0, 1, 1, 0}[k] for an odd one, which pairs R0 with R1 and R2 with R3.
-    // (Rows a multiple of 4 KiB apart are the ones that crowd; at d = 3072 the plain march is 0.6 us faster.)
+    // The start of the march rotates over column ranges (vt_ranges.h) where rows are a multiple of 4 KiB apart, the ones
+    // that crowd (at d = 3072 the plain march is 0.6 us faster).  Eight ranges for tiles of eight waves (k = 32768, d = 2048:
+    // 25.9 us for one hidden row and 28.8 for eight; 27.6 and 30.4 with four), four for any number of waves, whose tiles lie
+    // a different number of pages apart at every height (k = 40000, d = 4096, n = 8: 59.0 against 60.7).
+    constexpr int NR = MAXW > kStepWaves ? 4 : 8;
     const bool rotate = KS == 1 && nunits >= 8 && a.d % 2048 == 0;
-    const int rot = rotate ? ((int)blockIdx.x >> 3) & 3 : 0;
-    // first units of ranges 1..3.  When a quarter of a row is itself a multiple of 4 KiB (d = 8192) quarter starts
-    // would crowd the same channels again: the boundaries are skewed by 1, 2 and 3 KiB (any fixed partition of the
-    // columns keeps the rounding independent of the start)
-    const int skew = ((nunits / 4) * kUnitCols * 2) % 4096 == 0 ? 4 : 0;
-    const int rb1 = nunits / 4 + skew, rb2 = nunits / 2 + 2 * skew, rb3 = (3 * nunits) / 4 + 3 * skew;
-    const int ustart = KS > 1 ? ksi * nun : rot == 0 ? 0 : rot == 1 ? rb1 : rot == 2 ? rb2 : rb3;
+    const int rot = !rotate ? 0 : NR == 4 ? ((int)blockIdx.x >> 3) & 3 : first_range<NR>((int)blockIdx.x);
+    const int upr = nunits / NR;                       // units per range (XG: per column part)
+    const int ustart = KS > 1 ? ksi * nun : rot * upr;
     const int hstart = KS > 1 ? 0 : ustart;            // first unit of h's layout in LDS (the same for all waves)
     // unit processed at step s (0 <= s < nun)
     auto unit_of = [&](int s) {
@@ -182,37 +173,13 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     u32x4 areg[kPrefetchUnits][4];
 
     f32x4 acc[NT];
-    f32x4 pair0[NT], pair1[NT];
+    RangeSums<NR, NT> sums;
+    sums.clear();
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = pair0[t] = pair1[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     int closed = 0;        // ranges finished so far
-#define VT_CLOSE_RANGE()                                                              \
-    {                                                                                 \
-        const bool to1 = (rot & 1) ? (closed == 1 || closed == 2) : closed >= 2;      \
-        _Pragma("unroll") for (int t = 0; t < NT; ++t) {                              \
-            const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};                             \
-            pair0[t] += to1 ? zero : acc[t];      /* adding zero changes nothing */   \
-            pair1[t] += to1 ? acc[t] : zero;                                          \
-            acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};                                       \
-        }                                                                             \
-        ++closed;                                                                     \
-    }
-    // XG: a range is two column parts.  The first of them waits in `stash`; when the second is complete their sum
-    // goes the way of a range above.  (Ranges start at even parts, so the parts of a range follow one another.)
-    f32x4 stash = f32x4{0.f, 0.f, 0.f, 0.f};
-    int pcount = 0;        // units of the current part done so far
-    bool second = false;   // the current part is the second of its range
-    auto close_part = [&]() {
-        if (!second) {
-            stash = acc[0];
-            acc[0] = f32x4{0.f, 0.f, 0.f, 0.f};
-        } else {
-            acc[0] = stash + acc[0];
-            VT_CLOSE_RANGE()
-        }
-        second = !second;
-        pcount = 0;
-    };
+    int in_range = 0;      // units of the open range done so far
+    f32x4 own = f32x4{0.f, 0.f, 0.f, 0.f};      // XG: the logits of the wave's own rows
 
     unsigned char *my_stage = stage + (size_t)w * 2 * kStageUnitBytes;
     // staging writes: instruction j, lane (row 4j + lgrp, 16-byte chunk lrow)
@@ -305,22 +272,23 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
         for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4 *>(sb + 4 * j * kStagePitch + wr_off) = ar[j];
         load_unit(u + kPrefetchUnits, ar);
         const unsigned char *hb = hbuf + hrow_off + (size_t)uc * (kUnitCols * 2);
-        if constexpr (XG) {
-            if (pcount == PL) close_part();      // (at u == nun this closes the last part of the wave's own rows)
-            if (u == nun) {
-                // own rows complete: their logits wait in pair0; the shared group's part starts from zero
-                pair0[0] = pair0[0] + pair1[0];
+        if (XG || rotate) {
+            if (in_range == upr) {      // (XG: at u == nun this closes the last part of the wave's own rows)
+                sums.close(acc, rot, closed);
+                ++closed;
+                in_range = 0;
             }
+            ++in_range;
+        }
+        if constexpr (XG) {
+            // own rows complete: their logits wait; the shared group's part starts from zero
+            if (u == nun) own = sums.set[0][0] + sums.set[1][0];
             if (u >= nun) {
                 // the shared group's unit w PL + (u - nun): where it lies in h's (rotated) layout in LDS
                 int pos = w * PL + (u - nun) - hstart;
                 pos = pos < 0 ? pos + nunits : pos;
                 hb = hbuf + hrow_off + (size_t)pos * (kUnitCols * 2);
             }
-            ++pcount;
-        } else if (rotate && u > 0) {
-            const int ua = unit_of(u);
-            if (ua == 0 || ua == rb1 || ua == rb2 || ua == rb3) VT_CLOSE_RANGE()
         }
         // operands of two k-steps are read before their MFMAs are issued, so that the LDS latency is paid
         // once per pair and not once per MFMA
@@ -378,13 +346,11 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     for (int x = 0; x < kPrefetchUnits; ++x) wait_unit<0>(areg[x]);
 
     if constexpr (XG) {
-        // acc[0]: the shared group's partial logits over this wave's column part; pair0[0]: the own rows' logits
+        // acc[0]: the shared group's partial logits over this wave's column part; own: the own rows' logits
     } else if (rotate) {
-        VT_CLOSE_RANGE()
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = pair0[t] + pair1[t];
+        sums.close(acc, rot, closed);
+        sums.total(acc);
     }
-#undef VT_CLOSE_RANGE
 
     // ---- logits of this tile -> LDS tile zt[i][t] (aliases staging and h)
     __syncthreads();
@@ -394,7 +360,7 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
         const int i = 16 * t + lrow;       // hidden row of this lane
         if (i < a.n) {
             float *dst = zt + ((size_t)ksi * a.n + i) * tp + 16 * rg + 4 * lgrp;      // partial ksi of row i
-            const f32x4 v = XG ? pair0[t] : acc[t];
+            const f32x4 v = XG ? own : acc[t];
             dst[0] = v.x;
             dst[1] = v.y;
             dst[2] = v.z;
