@@ -94,6 +94,17 @@ using vt::kTicketBytes;
 struct FixedTiles {
     int nwaves = 0, ksplit = 1, nlists = 0;
 };
+// More than 8 hidden rows: whether the kernel stores its logits and a workgroup per hidden row finishes the step
+// (the alternative: candidate lists per tile, merged by step_finalize_kernel).  The tile epilogue selects by threshold up
+// to 8 tokens per row (four rows per wave, 16 candidate slots each) and takes a round per token beyond: there the stored
+// logits win (k = 32768, d = 4096: n = 64, m = 9: 58.4 against 60.1 us, m = 11: 58.5 / 61.8; n = 32, m = 10: 53.8 /
+// 55.1).  Up to 8 tokens the epilogue costs a tile the same few microseconds whatever its height, the logits as much as
+// the tile holds: from about 224 rows of 8 tokens on they win where tiles are below 128 rows (n = 256, m = 8, lists
+// against logits: k = 16384, d = 4096 68.5 / 61.6 us, k = 22786 76.4 / 73.7; but k = 32768, d = 8192 155.6 / 160.8, k = 65536,
+// d = 2048 102.7 / 111.5; n = 200, k = 8000, d = 2048 32.7 / 34.2).
+bool stores_logits(int n, int m, int tile_rows) {
+    return m > vt::kRowSelectMinLManyRows || (n * m >= vt::kRowSelectMinWork && tile_rows < vt::kMfmaTileRows);
+}
 // More than 8 hidden rows, bf16: how the head is cut into tiles (kernel variant, LDS, number of tiles).
 void plan_many_rows(StepPlan &p, int n, int k, int d, int m) {
     const int CUS = round_workgroups();
@@ -133,8 +144,8 @@ void plan_many_rows(StepPlan &p, int n, int k, int d, int m) {
         // (smaller tiles mean more candidate lists: not where only theirs would outgrow the library's own workspace)
         auto list_bytes = [&](int rows) { return (size_t)n * ((k + rows - 1) / rows) * (1 + m) * sizeof(unsigned long long); };
         auto fits = [&](int rows) {
-            return m > vt::kRowSelectMinLManyRows || n * m >= vt::kRowSelectMinWork ||
-                   list_bytes(rows) + 65536 <= (size_t)VT_STATIC_WS_BYTES || list_bytes(rows) <= list_bytes(vt::kMfmaTileRows);
+            return stores_logits(n, m, rows) || list_bytes(rows) + 65536 <= (size_t)VT_STATIC_WS_BYTES ||
+                   list_bytes(rows) <= list_bytes(vt::kMfmaTileRows);
         };
         int MT = 4;
         for (int x : {1, 2, 3, 5})
@@ -341,15 +352,11 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
         const int group = p.nlists < vt::kStepMaxBlocks ? p.nlists : vt::kStepMaxBlocks;
         p.fin_stage_keys = (group + 1) * p.L;
         const int fc = (int)(vt::kFinalizeLdsBytes / ((size_t)p.fin_stage_keys * sizeof(unsigned long long)));
-        // The per-tile candidate lists cost n * L selection rounds per tile and grow to megabytes; beyond a point
-        // (measured: 12 or more tokens per row, or n * L from about 1280; always when the lists no longer fit the
-        // merge's LDS staging) the kernel stores its logits instead and a workgroup per hidden row finishes the step.
-        // With more than 8 hidden rows the tile epilogue selects by threshold only up to 8 tokens per row (four rows per
-        // wave, 16 candidate slots each) and takes L rounds beyond: there the per-row tail wins from 9 tokens on
-        // (measured, k = 32768, d = 4096: n = 64, m = 9: 58.4 against 60.1 us, m = 11: 58.5 / 61.8; n = 32, m = 10:
-        // 53.8 / 55.1).
-        const int max_list = n > vt::kGemvMaxN ? vt::kRowSelectMinLManyRows : vt::kRowSelectMinL;
-        p.row_select = p.L > max_list || n * p.L >= vt::kRowSelectMinWork || fc < 1;
+        // Many tokens per row: the candidate lists cost L selection rounds per tile; the kernel stores its logits instead
+        // and a workgroup per hidden row finishes the step (measured: 12 or more tokens with up to 8 hidden rows; above,
+        // see stores_logits()).  Always when the lists of a row no longer fit the merge's LDS staging.
+        p.row_select = fc < 1 || (n > vt::kGemvMaxN ? stores_logits(n, p.L, 16 * p.row_groups + p.extra_rows)
+                                                    : p.L > vt::kRowSelectMinL);
         // one hidden row per workgroup: n <= 256 rows spread over as many CUs, and a merging wave has its
         // SIMD to itself (the selection rounds are bound by instruction issue)
         p.fin_conc = 1;

@@ -440,19 +440,28 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
 // written through to memory) and takes a ticket; the workgroup that draws the last ticket ranks all n * m
 // candidates, reading the other rows' results with loads that bypass its caches.
 // T threads: 64 when n * m <= 64, else 512 (the waves beyond the first only help with the ranking; with more
-// threads the merging wave would not have the registers it needs).
-template <int T>
+// threads the merging wave would not have the registers it needs).  BLOCK: all eight waves merge.
+template <int T, bool BLOCK>
 __global__ void __launch_bounds__(T) step_finalize_tree_kernel(const FinalizeArgs f) {
+    static_assert(!BLOCK || T == kBlockMergeThreads, "one workgroup size for the merge by eight waves");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_last;
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int i = blockIdx.x;
+    bool merged = false;
+    if constexpr (BLOCK) {
+        merged = merge_row_block(f, i, i, *reinterpret_cast<BlockMergeLds *>(smem), lane, w);
+        wait_stores_done();
+        __syncthreads();
+    }
     if (w == 0) {
-        unsigned long long *stage = reinterpret_cast<unsigned long long *>(smem);
-        finalize_row<true>(f.pms + (size_t)i * f.nlists, f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m, stage,
-                           f.out_ids + (size_t)i * f.m, f.out_logp + (size_t)i * f.m, f.out_lse ? f.out_lse + i : nullptr,
-                           f.lse_buf + i, lane);
+        if (!merged) {
+            unsigned long long *stage = reinterpret_cast<unsigned long long *>(smem);
+            finalize_row<true>(f.pms + (size_t)i * f.nlists, f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m,
+                               stage, f.out_ids + (size_t)i * f.m, f.out_logp + (size_t)i * f.m,
+                               f.out_lse ? f.out_lse + i : nullptr, f.lse_buf + i, lane);
+        }
         wait_stores_done();       // the row's results are written through: visible to whoever draws the last ticket
         if (lane == 0) {
             const unsigned v = __hip_atomic_fetch_add(f.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -480,6 +489,19 @@ __global__ void __launch_bounds__(T) step_finalize_tree_kernel(const FinalizeArg
     unsigned *cnt = reinterpret_cast<unsigned *>(smem + (size_t)N2 * 8);
     int *wave_tot = reinterpret_cast<int *>(smem + (size_t)N2 * 12);
     tree_select_by_count<T, true>(t, N2, keys, cnt, wave_tot);
+}
+
+// Merges the per-tile partials, many lists of them: eight waves per hidden row.
+__global__ void __launch_bounds__(kBlockMergeThreads) step_finalize_block_kernel(const FinalizeArgs f) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int i = blockIdx.x;
+    const int o = f.indexed ? (int)((f.row_pack >> (8 * (i & 7))) & 0xFFull) : i;      // output row
+    if (merge_row_block(f, i, o, *reinterpret_cast<BlockMergeLds *>(smem), lane, w) || w != 0) return;
+    finalize_row<true>(f.pms + (size_t)i * f.nlists, f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m,
+                       reinterpret_cast<unsigned long long *>(smem), f.out_ids + (size_t)o * f.m,
+                       f.out_logp + (size_t)o * f.m, f.out_lse ? f.out_lse + o : nullptr, f.lse_buf + i, lane);
 }
 
 // Merges the per-tile partials: one wave per hidden row.
@@ -571,8 +593,16 @@ hipError_t launch_head_mfma_multi(const MfmaArgs &a, const MultiHeadTable &t, si
 
 hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t st) {
     static LdsLimitOnce lds_limit;
-    hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(step_finalize_kernel)}, kMaxDynamicLds);
+    hipError_t e = allow_dynamic_lds(lds_limit,
+                                     {reinterpret_cast<const void *>(step_finalize_kernel),
+                                      reinterpret_cast<const void *>(step_finalize_block_kernel),
+                                      reinterpret_cast<const void *>(step_finalize_tree_kernel<64, false>),
+                                      reinterpret_cast<const void *>(step_finalize_tree_kernel<512, false>),
+                                      reinterpret_cast<const void *>(step_finalize_tree_kernel<512, true>)},
+                                     kMaxDynamicLds);
     if (e != hipSuccess) return e;
+    const bool block = block_merge_pays(f.n, f.nlists, f.L, f.m);
+    if (block && lds < sizeof(BlockMergeLds)) lds = sizeof(BlockMergeLds);
     if (f.tree_cum != nullptr) {
         // one hidden row per workgroup; LDS: the merge's staging, then the ranking's keys and counters
         const int N = f.n * f.m;
@@ -581,15 +611,16 @@ hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t s
         while (N2 < N) N2 <<= 1;
         const size_t need = (size_t)N2 * 12 + 256;
         const size_t bytes = lds > need ? lds : need;
-        static LdsLimitOnce tree_lds_limit;
-        e = allow_dynamic_lds(tree_lds_limit, {reinterpret_cast<const void *>(step_finalize_tree_kernel<64>),
-                                               reinterpret_cast<const void *>(step_finalize_tree_kernel<512>)},
-                              kMaxDynamicLds);
-        if (e != hipSuccess) return e;
-        if (N <= kWave)
-            hipLaunchKernelGGL(step_finalize_tree_kernel<64>, dim3(f.n), dim3(64), bytes, st, f);
+        if (block)
+            hipLaunchKernelGGL((step_finalize_tree_kernel<512, true>), dim3(f.n), dim3(512), bytes, st, f);
+        else if (N <= kWave)
+            hipLaunchKernelGGL((step_finalize_tree_kernel<64, false>), dim3(f.n), dim3(64), bytes, st, f);
         else
-            hipLaunchKernelGGL(step_finalize_tree_kernel<512>, dim3(f.n), dim3(512), bytes, st, f);
+            hipLaunchKernelGGL((step_finalize_tree_kernel<512, false>), dim3(f.n), dim3(512), bytes, st, f);
+        return hipGetLastError();
+    }
+    if (block) {
+        hipLaunchKernelGGL(step_finalize_block_kernel, dim3(f.n), dim3(kBlockMergeThreads), lds, st, f);
         return hipGetLastError();
     }
     const int grid = (f.n + f.conc - 1) / f.conc;

@@ -70,12 +70,13 @@ constexpr int kMfmaMaxN = 256;         // hidden rows one launch covers
 // it shares its channels with W's lines; n = 256, k = 32768, d = 8192: 137.1 us in place, 136.9 re-laid)
 constexpr size_t kPackHBytes = (size_t)4 << 20;
 constexpr int kRowsKernelMaxN = 64;    // ... by tiles that hold all hidden rows per wave; above: the wide kernel
-constexpr int kRowSelectMinL = 11;      // matrix-core path: with more tokens per row than this (8 with more than 8 hidden rows), or
+// With more tokens per row than this the matrix-core kernel stores its logits and a workgroup per hidden row finishes the
+// step: up to 8 hidden rows, and beyond ...
+constexpr int kRowSelectMinL = 11;
 constexpr int kRowSelectMinLManyRows = 8;
+constexpr int kRowSelectMinWork = 1792; // ... where also many rows with many tokens on small tiles do (n * min(m, tile rows))
 // small-n path: the same switch when L > 12 - n / 2 (measured crossovers: L = 8 at n = 8, 10 at n = 4, 11-12 at n = 1)
 constexpr int kGemvRowSelectBase = 12;
-constexpr int kRowSelectMinWork = 1280; // with n * min(m, 128) from this value on, the kernel stores its logits and a
-                                        // workgroup per hidden row finishes the step
 constexpr int kMfmaPrefetchUnits = 3;  // 128-column units of W_trim in flight per wave; an h chunk that has a successor
                                        // is a multiple of this many units
 constexpr int kMfmaChunkPieces = 9;    // an h chunk is prefetched through registers: at most this many

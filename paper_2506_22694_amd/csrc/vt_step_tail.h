@@ -279,7 +279,7 @@ __device__ __forceinline__ void block_epilogue_large(const float *zrow, int S, i
 // Tiles of at most 16 Q logits per hidden row (Q = 8: 128 rows, Q = 9: 144) and L <= 16: the 16 lanes of DPP row g
 // rank hidden row i0 + g (Q logits per lane), so a wave finishes four hidden rows in
 // the time of one.  zt: logit tile [hidden row][tp]; idq: ids of tile rows gl + 16 q.
-template <int Q, bool GUARDED = false>
+template <int Q>
 __device__ __forceinline__ void block_epilogue_rows4(const float *zt, int tp, int i0, int n, int rows_b, int L,
                                                      const int (&idq)[Q], float *__restrict__ logp_full, size_t k,
                                                      int row0, unsigned long long *__restrict__ pms,
@@ -293,41 +293,23 @@ __device__ __forceinline__ void block_epilogue_rows4(const float *zt, int tp, in
     int id[Q];
     float zq[Q];
     float lmax = -INFINITY;
-    if constexpr (GUARDED) {
-        // (a branch per logit: fewer registers live at once -- the many-row kernel has none to spare)
+    // every lane reads -- past the tile's end its last logit again -- and selects afterwards: no branch per logit
+    // (a third of the instructions of a pass were those branches)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int t = gl + 16 * q;
+        const bool ok = active && t < rows_b;
+        const float z = zrow[min(t, rows_b - 1)];
+        id[q] = idq[q];
+        zq[q] = ok ? z : -INFINITY;
+        ord[q] = ok ? orderable_f32(z) : 0u;
+        lmax = fmaxf(lmax, zq[q]);
+    }
+    if (logp_full != nullptr) {
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int t = gl + 16 * q;
-            ord[q] = 0u;
-            id[q] = idq[q];
-            zq[q] = -INFINITY;
-            if (active && t < rows_b) {
-                const float z = zrow[t];
-                if (logp_full) logp_full[(size_t)i * k + row0 + t] = z;
-                zq[q] = z;
-                ord[q] = orderable_f32(z);
-                lmax = fmaxf(lmax, z);
-            }
-        }
-    } else {
-        // every lane reads -- past the tile's end its last logit again -- and selects afterwards: no branch per logit
-        // (a third of the instructions of a pass were those branches)
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int t = gl + 16 * q;
-            const bool ok = active && t < rows_b;
-            const float z = zrow[min(t, rows_b - 1)];
-            id[q] = idq[q];
-            zq[q] = ok ? z : -INFINITY;
-            ord[q] = ok ? orderable_f32(z) : 0u;
-            lmax = fmaxf(lmax, zq[q]);
-        }
-        if (logp_full != nullptr) {
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const int t = gl + 16 * q;
-                if (active && t < rows_b) logp_full[(size_t)i * k + row0 + t] = zq[q];
-            }
+            if (active && t < rows_b) logp_full[(size_t)i * k + row0 + t] = zq[q];
         }
     }
     const float M = __uint_as_float(row16_allreduce_u32(__float_as_uint(lmax), OpMaxF32{}));
@@ -746,6 +728,136 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
         *lse_buf_i = lse;
         if (out_lse_i) *out_lse_i = lse;
     }
+}
+
+// ------------------------------------------------------------------ merge of many lists (eight waves per hidden row)
+// More keys than one wave holds in registers (more than 256 lists, or more than 3072 keys): the row's workgroup of
+// eight waves holds them all (up to 2048 lists and 16384 keys; a head of 262144 rows has at most 1490 and 11920), one key per load and thread, and selects by threshold like the direct merge above.  The
+// waves form the groups: each finds the ceil(m / 8)-th largest of its lanes' best logits, so at least m keys reach T,
+// the smallest of the eight values -- about three times m do.  They are compacted into `cand` and ranked by counting.
+// What it replaces there, one wave that merges 256 sorted lists at a time in m dependent rounds, was bound by those
+// rounds: m = 8, k = 65536 (512 lists) 10.0 -> 5.2 us, k = 128256 (668 lists of 64 hidden rows) 15.3 -> 5.4.  With more
+// than 8 hidden rows it is also the faster one for lists that one wave could hold (256 lists of 8 keys: n = 64 6.1 -> 5.4,
+// n = 128 6.7 -> 4.9); up to 8 rows the two tie (n = 8: 4.6 / 4.6), and so do they below about 1000 keys.
+// Returns false, having written nothing, when more than kBlockMaxCand keys reach T (massive ties).
+constexpr int kBlockMergeWaves = 8;
+constexpr int kBlockMergeThreads = kBlockMergeWaves * kWave;
+constexpr int kBlockMergeMaxKeys = 32 * kBlockMergeThreads;
+constexpr int kBlockMergeMaxLists = 4 * kBlockMergeThreads;
+constexpr int kBlockMaxCand = 1024;
+
+struct BlockMergeLds {
+    unsigned long long cand[kBlockMaxCand];
+    float wave_max[kBlockMergeWaves], wave_sum[kBlockMergeWaves];
+    unsigned wave_kth[kBlockMergeWaves];
+    int ncand;
+};
+
+__host__ __device__ __forceinline__ bool block_merge_pays(int n, int B, int L, int m) {
+    const int total = B * L;
+    return m <= kWave && B <= kBlockMergeMaxLists && total <= kBlockMergeMaxKeys &&
+           (B > kStepMaxBlocks || total > kDirectKeysPerLane * kWave || (n > kGemvMaxN && total > 1024));
+}
+
+template <int U>
+__device__ __forceinline__ bool finalize_row_block(const unsigned long long *__restrict__ pms_row,
+                                                   const unsigned long long *__restrict__ pkeys_row, int B, int total,
+                                                   int m, BlockMergeLds &s, int *__restrict__ out_ids_row,
+                                                   float *__restrict__ out_logp_row, float *__restrict__ out_lse_i,
+                                                   float *__restrict__ lse_buf_i, int lane, int w) {
+    constexpr int MS = kBlockMergeMaxLists / kBlockMergeThreads;
+    const int tid = w * kWave + lane;
+    unsigned long long ms[MS], key[U];
+#pragma unroll
+    for (int q = 0; q < MS; ++q) ms[q] = acquire_u64(pms_row + min(tid + kBlockMergeThreads * q, B - 1));
+#pragma unroll
+    for (int u = 0; u < U; ++u) key[u] = acquire_u64(pkeys_row + min(u * kBlockMergeThreads + tid, total - 1));
+    float lm = -INFINITY, ls = 0.f;
+#pragma unroll
+    for (int q = 0; q < MS; ++q) {
+        if (tid + kBlockMergeThreads * q < B) {
+            const float Mb = __uint_as_float((unsigned)ms[q]);
+            const float Sb = __uint_as_float((unsigned)(ms[q] >> 32));
+            const float Mn = fmaxf(lm, Mb);
+            ls = ls * __expf(lm - Mn) + Sb * __expf(Mb - Mn);   // exp(-inf) = 0 on the first term
+            lm = Mn;
+        }
+    }
+    unsigned top = 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (u * kBlockMergeThreads + tid >= total) key[u] = kNoKey;
+        const unsigned o = (unsigned)(key[u] >> 32);
+        top = o > top ? o : top;
+    }
+    const float Mw = wave_max(lm);
+    const float Sw = w * kWave < B ? wave_sum(ls * __expf(lm - Mw)) : 0.f;
+    const unsigned kth = m <= kBlockMergeWaves ? wave_max_u32(top)
+                                               : wave_kth_largest_prefix16(top, (m + kBlockMergeWaves - 1) / kBlockMergeWaves);
+    if (lane == 0) {
+        s.wave_max[w] = Mw;
+        s.wave_sum[w] = Sw;
+        s.wave_kth[w] = kth;
+    }
+    if (tid == 0) s.ncand = 0;
+    __syncthreads();
+    float M = s.wave_max[0];
+    unsigned T = s.wave_kth[0];
+#pragma unroll
+    for (int q = 1; q < kBlockMergeWaves; ++q) {
+        M = fmaxf(M, s.wave_max[q]);
+        T = s.wave_kth[q] < T ? s.wave_kth[q] : T;
+    }
+    float S = 0.f;
+#pragma unroll
+    for (int q = 0; q < kBlockMergeWaves; ++q) S += s.wave_sum[q] * __expf(s.wave_max[q] - M);    // fixed order
+    const float lse = lane_uniform(M + __logf(S));
+    T = T == 0u ? 1u : T;               // a wave without keys: every real key is a candidate
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if ((unsigned)(key[u] >> 32) >= T) {
+            const int slot = atomicAdd(&s.ncand, 1);
+            if (slot < kBlockMaxCand) s.cand[slot] = key[u];
+        }
+    }
+    __syncthreads();
+    const int ncand = s.ncand;
+    if (ncand > kBlockMaxCand) {
+        __syncthreads();                // the caller reuses this LDS
+        return false;
+    }
+    for (int c = tid; c < ncand; c += kBlockMergeThreads) {
+        const unsigned long long mine = s.cand[c];
+        int above = 0;
+        int x = 0;
+        for (; x + 8 <= ncand; x += 8) {
+            unsigned long long t[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) t[q] = s.cand[x + q];      // every lane reads the same key: a broadcast
+#pragma unroll
+            for (int q = 0; q < 8; ++q) above += t[q] > mine ? 1 : 0;
+        }
+        for (; x < ncand; ++x) above += s.cand[x] > mine ? 1 : 0;
+        if (above < m) store_result(out_ids_row, out_logp_row, above, key_id(mine), key_logit(mine) - lse);
+    }
+    if (tid == 0) {
+        *lse_buf_i = lse;
+        if (out_lse_i) *out_lse_i = lse;
+    }
+    return true;
+}
+
+// Merges hidden row i of `f` with all eight waves; false: nothing written (massive ties), the rounds have to do it.
+__device__ __forceinline__ bool merge_row_block(const FinalizeArgs &f, int i, int o, BlockMergeLds &s, int lane, int w) {
+    const unsigned long long *pms = f.pms + (size_t)i * f.nlists, *pkeys = f.pkeys + (size_t)i * f.nlists * f.L;
+    int *ids = f.out_ids + (size_t)o * f.m;
+    float *logp = f.out_logp + (size_t)o * f.m, *lse = f.out_lse ? f.out_lse + o : nullptr;
+    const int total = f.nlists * f.L;
+    if (total <= 8 * kBlockMergeThreads)
+        return finalize_row_block<8>(pms, pkeys, f.nlists, total, f.m, s, ids, logp, lse, f.lse_buf + i, lane, w);
+    if (total <= 16 * kBlockMergeThreads)
+        return finalize_row_block<16>(pms, pkeys, f.nlists, total, f.m, s, ids, logp, lse, f.lse_buf + i, lane, w);
+    return finalize_row_block<32>(pms, pkeys, f.nlists, total, f.m, s, ids, logp, lse, f.lse_buf + i, lane, w);
 }
 
 }  // namespace vt

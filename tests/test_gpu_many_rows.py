@@ -67,3 +67,39 @@ def test_step_many_rows_captured_in_a_graph_replays_the_same():
             step(c)
             torch.cuda.synchronize()
             assert torch.equal(c[5][0], ids) and torch.equal(c[5][1], logp), rep
+
+
+# Merges of more lists than one wave holds: keys per thread 8 / 16 / 32 (512 lists and fewer tokens, 669, 1366 lists),
+# the edge of 256 lists, one token, and a row whose logits are all equal (more candidates than the merge holds).
+@pytest.mark.parametrize("n,k,m", [
+    (9, 65537, 8), (64, 65536, 4), (12, 128256, 8), (17, 262144, 8), (10, 49153, 1), (33, 49280, 8), (70, 40961, 8)])
+def test_merge_of_many_lists(n, k, m):
+    W, map_ = synth.trimmed_head_direct(k, 128, seed=900 + n, dtype="bf16")
+    h = synth.hidden_rows(n, 128, seed=k, dtype="bf16")
+    h[n // 2] = 0
+    ref = oracle.draft_head_step(h, W, map_, m)
+    oi, ol, lse = run_step(h, W, map_, m, return_lse=True)
+    assert check_step(oi, ol, ref, map_, m, lse) <= 2 + n // 32
+    assert oi[n // 2].tolist() == sorted(map_)[:m]
+    if n * m <= 512:        # the same merge with a tree level behind it
+        put = lambda a: torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16)
+        cum = torch.linspace(0.0, -1.0, n, device="cuda")
+        K = min(8, n * m)
+        got = vt.draft_tree_level(put(h), put(W), torch.from_numpy(map_).cuda(), m, cum, K)
+        want = vt.tree_expand(cum, ol, oi, K)
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+
+
+def test_merge_of_many_lists_with_more_tokens_than_waves():
+    n, k, d, m = 8, 100352, 6400, 11
+    assert "mfma" in vt.draft_head_step_plan(n, k, d, m)
+    W = torch.randn(k, d, device="cuda", dtype=torch.bfloat16)
+    h = torch.randn(n, d, device="cuda").mul_(0.02).bfloat16()
+    map_ = torch.arange(k, dtype=torch.int32, device="cuda") * 2
+    ids, logp = vt.draft_head_step(h, W, map_, m)
+    z = torch.cat([h.double() @ W[a:a + 8192].double().t() for a in range(0, k, 8192)], 1)
+    top = (z - z.logsumexp(1, keepdim=True)).topk(m, 1)
+    # fp32 sums of 6400 products of size |h| |w| ~ 0.02: far below 1e-4; neighbours closer than that may swap
+    assert (logp - top.values).abs().max().item() < 1e-4
+    assert (ids.long() != 2 * top.indices).sum().item() <= 2
