@@ -9,7 +9,8 @@
 //   pass 1  every thread (1024 per row) folds its share of the row into (max, sum-exp) and keeps its largest logit;
 //   T       a threshold that at least m logits reach, from the lanes' maxima (bit-serial selection inside each wave),
 //           so the m best logits are all >= T;
-//   pass 2  logits >= T become candidate keys in LDS (typically a few dozen), ranked by counting;
+//   pass 2  logits >= T become candidate keys in LDS (typically a few dozen), ranked by counting (rows of up to 32768
+//           logits stay in registers in between, longer ones are sifted as they go by: row_select_kernel);
 //   if more than 1024 logits reach T (massive ties, e.g. h = 0) the m best are extracted one by one.
 #include "vt_device.h"
 #include "vt_step.h"
@@ -21,6 +22,7 @@ namespace {
 constexpr int kRowThreads = 1024;
 constexpr int kRowWaves = kRowThreads / kWave;
 constexpr int kRowMaxCand = 1024;
+constexpr int kRowMaxRaw = 4096;      // rows of several stretches: logits above the first stretch's threshold
 
 __device__ __forceinline__ float block_sum_f32(float v, float *red, int lane, int w) {
     v = wave_sum(v);
@@ -80,45 +82,12 @@ __device__ __forceinline__ void load_stretch(const float *__restrict__ zr, int b
     }
 }
 
-// KEEP: the row fits one stretch (k <= 32768), so its logits stay in registers for the second pass.
-template <bool KEEP, bool VEC>
-__global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__restrict__ z, const int *__restrict__ map,
-                                                                 int k, int m, int *__restrict__ out_ids,
-                                                                 float *__restrict__ out_logp,
-                                                                 float *__restrict__ out_lse,
-                                                                 float *__restrict__ lse_buf) {
-    __shared__ float redf[kRowWaves];
-    __shared__ unsigned long long red64[kRowWaves];
-    __shared__ unsigned tmax[2 * kRowWaves];
-    __shared__ unsigned long long cand[kRowMaxCand];
-    __shared__ int candj[kRowMaxCand];
-    __shared__ unsigned s_ncand;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int i = blockIdx.x;
-    const float *zr = z + (size_t)i * k;
-    float v[kRowVals];
-
-    // ---- pass 1: (max, sum-exp) and the thread's largest logit
-    float lm = -INFINITY, ls = 0.f;
-    for (int base = 0; base < k; base += kRowSpan) {
-        load_stretch<VEC>(zr, base, k, tid, v);
-        float cm = v[0];
-#pragma unroll
-        for (int u = 1; u < kRowVals; ++u) cm = fmaxf(cm, v[u]);
-        const float mn = fmaxf(lm, cm);
-        if (mn != -INFINITY) {
-            float cs = 0.f;
-#pragma unroll
-            for (int u = 0; u < kRowVals; ++u) cs += __expf(v[u] - mn);     // exp(-inf) = 0 past the end
-            ls = ls * __expf(lm - mn) + cs;
-            lm = mn;
-        }
-    }
-    // ---- one exchange through LDS gives the row maximum M and the threshold T, a value that at least m logits
-    // reach: every wave finds the ceil(m / 16)-th largest of its lanes' maxima (the wave maximum itself for
-    // m <= 16, otherwise bit by bit with ballots); each wave's share then holds that many logits >= its value,
-    // so the smallest of the sixteen values is reached by at least 16 * ceil(m / 16) >= m logits.  (Lanes
-    // without an element hold the lowest code.)
+// One exchange through LDS gives the row maximum M and a value T that at least m of the logits seen so far reach: every
+// wave finds the ceil(m / 16)-th largest of its lanes' maxima (the wave maximum itself for m <= 16, otherwise bit by bit
+// with ballots); each wave's share then holds that many logits >= its value, so the smallest of the sixteen values is
+// reached by at least 16 * ceil(m / 16) >= m logits.  (Lanes without an element hold the lowest code.)  lm: the lane's
+// maximum.  Contains one barrier; tmax must not be in use.
+__device__ __forceinline__ void row_threshold(float lm, int m, unsigned *tmax, int lane, int w, unsigned &T, unsigned &Mo) {
     const unsigned mine = lm == -INFINITY ? 0u : orderable_f32(lm);
     const unsigned wtop = wave_max_u32(mine);
     unsigned Tw = wtop;
@@ -138,48 +107,153 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
             }
         }
     }
-    if (tid == 0) s_ncand = 0u;
     if (lane == 0) {
         tmax[w] = Tw;
         tmax[kRowWaves + w] = wtop;
     }
     __syncthreads();
-    unsigned T = tmax[0], Mo = tmax[kRowWaves];
+    T = tmax[0], Mo = tmax[kRowWaves];
 #pragma unroll
     for (int q = 1; q < kRowWaves; ++q) {
         T = tmax[q] < T ? tmax[q] : T;
         Mo = tmax[kRowWaves + q] > Mo ? tmax[kRowWaves + q] : Mo;
     }
-    const float M = from_orderable_f32(Mo);      // k >= 1: some lane holds an element
-    const float S = block_sum_f32(lm == -INFINITY ? 0.f : ls * __expf(lm - M), redf, lane, w);
-    const float lse = M + __logf(S);
-    // compared as a float below (the order code is monotone; code 0 = no element maps to "everything passes")
-    const float Tf = T == 0u ? -INFINITY : from_orderable_f32(T);
+}
+// (the order code is monotone; code 0 = no element maps to "everything passes")
+__device__ __forceinline__ float threshold_f32(unsigned T) { return T == 0u ? -INFINITY : from_orderable_f32(T); }
 
-    // ---- pass 2: every logit >= T is a candidate
-    for (int base = 0; base < k; base += kRowSpan) {
-        if (!KEEP) load_stretch<VEC>(zr, base, k, tid, v);
+// Folds one stretch into the lane's (max, sum-exp).
+__device__ __forceinline__ void fold_stretch(const float (&v)[kRowVals], float &lm, float &ls) {
+    float cm = v[0];
 #pragma unroll
-        for (int u = 0; u < kRowVals; ++u) {
-            const int j = stretch_index<VEC>(base, u, tid);
-            if (j < k && v[u] >= Tf) {
-                // logit and position now, the target id later: a load from the map here would put a trip to
-                // memory behind every candidate a wave finds, one after the other
-                const unsigned slot = atomicAdd(&s_ncand, 1u);
-                if (slot < (unsigned)kRowMaxCand) {
-                    cand[slot] = (unsigned long long)__float_as_uint(v[u]);
-                    candj[slot] = j;
+    for (int u = 1; u < kRowVals; ++u) cm = fmaxf(cm, v[u]);
+    const float mn = fmaxf(lm, cm);
+    if (mn != -INFINITY) {
+        float cs = 0.f;
+#pragma unroll
+        for (int u = 0; u < kRowVals; ++u) cs += __expf(v[u] - mn);     // exp(-inf) = 0 past the end
+        ls = ls * __expf(lm - mn) + cs;
+        lm = mn;
+    }
+}
+
+// Every logit of a stretch that reaches Tf, with its position, into `val` / `pos` (cap entries; n counts on).
+template <bool VEC>
+__device__ __forceinline__ void collect_stretch(const float (&v)[kRowVals], int base, int k, int tid, float Tf, float *val,
+                                                int *pos, unsigned *n, unsigned cap) {
+#pragma unroll
+    for (int g = 0; g < kRowVals; g += 4) {
+        // (four logits to a branch: a dozen of a thousand threads' groups holds one)
+        if (fmaxf(fmaxf(v[g], v[g + 1]), fmaxf(v[g + 2], v[g + 3])) >= Tf) {
+#pragma unroll
+            for (int u = g; u < g + 4; ++u) {
+                const int j = stretch_index<VEC>(base, u, tid);
+                if (j < k && v[u] >= Tf) {
+                    // logit and position now, the target id later: a load from the map here would put a trip to
+                    // memory behind every candidate a wave finds, one after the other
+                    const unsigned slot = atomicAdd(n, 1u);
+                    if (slot < cap) {
+                        val[slot] = v[u];
+                        pos[slot] = j;
+                    }
                 }
             }
         }
     }
-    __syncthreads();
-    const int ncand = (int)s_ncand;
-    if (ncand <= kRowMaxCand) {
-        // the candidates' target ids, all requested at once
-        for (int c = tid; c < ncand; c += kRowThreads)
-            cand[c] = make_key(__uint_as_float((unsigned)cand[c]), map[candj[c]]);
+}
+
+// ONE: the row fits one stretch (k <= 32768), which stays in registers for the second pass.  Longer rows are read once,
+// too: the first stretch's threshold is one that m logits of the row reach, so what later stretches have to offer above it
+// is collected as they go by (with the next stretch requested before the one at hand is folded), and the row's own
+// threshold thins that out at the end.  A row whose first stretch says little (more than kRowMaxRaw logits above its
+// threshold) is read again.  Reading longer rows twice cost k = 65536, n = 256 24.3 us (now 21.0),
+// k = 128256, n = 256 40.6 (27.9), n = 16 20.5 (17.3): up to 64 rows what is left is the rate at which one CU reads a row.
+template <bool ONE, bool VEC>
+__global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__restrict__ z, const int *__restrict__ map,
+                                                                 int k, int m, int *__restrict__ out_ids,
+                                                                 float *__restrict__ out_logp,
+                                                                 float *__restrict__ out_lse,
+                                                                 float *__restrict__ lse_buf) {
+    constexpr unsigned kRaw = ONE ? kRowMaxCand : kRowMaxRaw;
+    __shared__ float redf[kRowWaves];
+    __shared__ unsigned long long red64[kRowWaves];
+    __shared__ unsigned tmax[2 * kRowWaves], tmax_first[2 * kRowWaves];
+    __shared__ unsigned long long cand[kRowMaxCand];
+    __shared__ float rawv[kRaw];
+    __shared__ int rawj[kRaw];
+    __shared__ unsigned s_nraw, s_ncand;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int i = blockIdx.x;
+    const float *zr = z + (size_t)i * k;
+    float v[kRowVals];
+    if (tid == 0) {
+        s_nraw = 0u;       // (both are first used behind the barrier of row_threshold)
+        s_ncand = 0u;
+    }
+
+    // ---- pass 1: (max, sum-exp) and the thread's largest logit
+    float lm = -INFINITY, ls = 0.f;
+    load_stretch<VEC>(zr, 0, k, tid, v);
+    unsigned T, Mo;
+    if constexpr (ONE) {
+        fold_stretch(v, lm, ls);
+    } else {
+        float v2[kRowVals];
+        load_stretch<VEC>(zr, kRowSpan, k, tid, v2);
+        fold_stretch(v, lm, ls);
+        row_threshold(lm, m, tmax_first, lane, w, T, Mo);
+        const float Tf1 = threshold_f32(T);
+        collect_stretch<VEC>(v, 0, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+        for (int base = kRowSpan; base < k; base += 2 * kRowSpan) {
+            load_stretch<VEC>(zr, base + kRowSpan, k, tid, v);
+            fold_stretch(v2, lm, ls);
+            collect_stretch<VEC>(v2, base, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+            if (base + kRowSpan < k) {
+                load_stretch<VEC>(zr, base + 2 * kRowSpan, k, tid, v2);
+                fold_stretch(v, lm, ls);
+                collect_stretch<VEC>(v, base + kRowSpan, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+            }
+        }
+    }
+    row_threshold(lm, m, tmax, lane, w, T, Mo);
+    const float M = from_orderable_f32(Mo);      // k >= 1: some lane holds an element
+    const float S = block_sum_f32(lm == -INFINITY ? 0.f : ls * __expf(lm - M), redf, lane, w);
+    const float lse = M + __logf(S);
+    const float Tf = threshold_f32(T);
+
+    // ---- pass 2: every logit >= T is a candidate
+    if constexpr (ONE) {
+        collect_stretch<VEC>(v, 0, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
         __syncthreads();
+    } else if (s_nraw > kRaw) {
+        __syncthreads();
+        if (tid == 0) s_nraw = 0u;
+        __syncthreads();
+        for (int base = 0; base < k; base += kRowSpan) {
+            load_stretch<VEC>(zr, base, k, tid, v);
+            collect_stretch<VEC>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+        }
+        __syncthreads();
+    }
+    const int nraw = (int)s_nraw;
+    int ncand = nraw;
+    if (nraw <= (int)kRaw) {
+        // the candidates' target ids, all requested at once
+        if constexpr (ONE) {
+            for (int c = tid; c < nraw; c += kRowThreads) cand[c] = make_key(rawv[c], map[rawj[c]]);
+            __syncthreads();
+        } else {
+            for (int c = tid; c < nraw; c += kRowThreads) {
+                if (rawv[c] >= Tf) {
+                    const unsigned slot = atomicAdd(&s_ncand, 1u);
+                    if (slot < (unsigned)kRowMaxCand) cand[slot] = make_key(rawv[c], map[rawj[c]]);
+                }
+            }
+            __syncthreads();
+            ncand = (int)s_ncand;
+        }
+    }
+    if (ncand <= kRowMaxCand) {
         // rank by counting: keys are distinct (distinct target ids)
         for (int c = tid; c < ncand; c += kRowThreads) {
             const unsigned long long key = cand[c];
@@ -204,7 +278,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         for (int r = 0; r < m; ++r) {
             unsigned long long best = kNoKey;
             for (int base = 0; base < k; base += kRowSpan) {
-                if (!KEEP) load_stretch<VEC>(zr, base, k, tid, v);
+                if (!ONE) load_stretch<VEC>(zr, base, k, tid, v);
 #pragma unroll
                 for (int u = 0; u < kRowVals; ++u) {
                     const int j = stretch_index<VEC>(base, u, tid);

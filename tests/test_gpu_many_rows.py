@@ -103,3 +103,21 @@ def test_merge_of_many_lists_with_more_tokens_than_waves():
     # fp32 sums of 6400 products of size |h| |w| ~ 0.02: far below 1e-4; neighbours closer than that may swap
     assert (logp - top.values).abs().max().item() < 1e-4
     assert (ids.long() != 2 * top.indices).sum().item() <= 2
+
+
+# Rows of stored logits longer than one stretch of 32768: a second stretch of one logit, whole stretches, a ragged fifth;
+# more tokens than waves; `late`: the first stretch's logits say nothing about the rest, which overflows the collection
+# (the row is read again); a row whose logits are all equal.
+@pytest.mark.parametrize("n,k,m,late", [
+    (9, 32769, 16, False), (10, 65536, 16, False), (9, 131076, 64, False), (12, 98304, 10, True), (9, 40001, 33, True)])
+def test_stored_logits_longer_than_one_stretch(n, k, m, late):
+    assert "row_select" in vt.draft_head_step_plan(n, k, 128, m)
+    W, map_ = synth.trimmed_head_direct(k, 128, seed=1000 + n, dtype="bf16")
+    if late:
+        W[:32768] = 0
+    h = synth.hidden_rows(n, 128, seed=k, dtype="bf16")
+    h[n // 2] = 0
+    ref = oracle.draft_head_step(h, W, map_, m)
+    oi, ol, lse = run_step(h, W, map_, m, return_lse=True)
+    assert check_step(oi, ol, ref, map_, m, lse) <= 2 + n * m // 256
+    assert oi[n // 2].tolist() == sorted(map_)[:m]
