@@ -85,6 +85,7 @@ struct StepPlan {
     int extra_rows = 0;        // matrix-core path: tile rows past the 128th
     // more than 8 hidden rows: 16-row groups of a tile, LDS offset of its target ids, epilogue passes
     int row_groups = 0, ids_off = 0, passes = 1;
+    bool twin = false;
     bool wide = false;         // more than 64 hidden rows
 };
 
@@ -129,13 +130,23 @@ void plan_many_rows(StepPlan &p, int n, int k, int d, int m) {
             // one round: the tile height follows from the head
             p.row_groups = (G == 5 && NT == 4) ? vt::kStepWaves : G;
         } else {
-            p.row_groups = vt::kStepWaves;
-            for (int g = vt::kStepWaves + 1; g <= vt::kMfmaMaxWaves; ++g)
+            // several rounds: two 128-row tiles on a CU at a time, half of its LDS each, so that one streams while the other
+            // starts or finishes -- or tiles of up to 192 rows where those come out even (one tile per CU against
+            // two: k = 65536, n = 64, d = 2048 57.3 / 51.4 us, n = 9 50.8 / 46.6, k = 128256, n = 64 104.0 / 94.9,
+            // k = 60000, n = 20, d = 1024 31.3 / 27.1; but k = 90000, n = 64, d = 3072, 704 tiles against 512 of 176
+            // rows: 102.5 / 107.1).  A CU with two tiles pays half of a round's 7 us, one left over all of it.
+            const int tiles = (k + vt::kMfmaTileRows - 1) / vt::kMfmaTileRows, rest = tiles % (2 * CUS);
+            const double one = cost(vt::kMfmaTileRows) / ((tiles + CUS - 1) / CUS), pair = 2 * one - 10.5;
+            const double paired = tiles / (2 * CUS) * pair + (rest == 0 ? 0.0 : rest <= CUS ? one : pair);
+            p.row_groups = vt::kStepWaves + 1;
+            for (int g = p.row_groups + 1; g <= vt::kMfmaMaxWaves; ++g)
                 if (cost(16 * g) < cost(16 * p.row_groups)) p.row_groups = g;
+            p.twin = paired <= cost(16 * p.row_groups);
+            if (p.twin) p.row_groups = vt::kStepWaves;
         }
         p.nwaves = p.row_groups <= 4 ? vt::kStepWaves : p.row_groups;
         const int rows_in_lds = 16 * (p.row_groups + (p.extra_rows != 0 ? 1 : 0));
-        ring = vt::rows_ring_bytes(NT, p.row_groups, p.extra_rows != 0);
+        ring = vt::rows_ring_bytes(NT, p.row_groups, p.extra_rows != 0, p.twin);
         tile = round_up((size_t)n * (rows_in_lds + 1) * sizeof(float), 16);
     } else {
         const int NTT = n <= 128 ? 2 : n <= 192 ? 3 : 4;
@@ -1150,6 +1161,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         a.row_groups = p.row_groups;
         a.ids_off = p.ids_off;
         a.passes = p.passes;
+        a.twin = p.twin ? 1 : 0;
         a.ticket_clear = tf.cum != nullptr ? reinterpret_cast<unsigned *>(wsb) : nullptr;
         hipError_t e = n <= vt::kGemvMaxN ? vt::launch_head_mfma(a, p.lds, st)
                        : p.wide           ? vt::launch_head_mfma_wide(p.NT / 4, a, p.lds, st)

@@ -126,10 +126,13 @@ __device__ __forceinline__ void tile_epilogue(const MfmaArgs &a, const float *zt
 // A stage is KB blocks of 64 columns: one for the tiles whose block is several kilobytes per wave, two for smaller ones,
 // which would spend their time at the barriers (k = 16384, n = 9, d = 2048: 23.4 us with one, 20.2 with two).
 // NST stages in LDS; LPW load instructions per wave and stage.
+// WGS = 2: heads of several rounds have two workgroups on a CU, with three stages and half of the registers each (two rings
+// of two stages in flight hold what one of five does): a round's first loads and its epilogue, about 7 us in which the CU
+// reads nothing, are hidden behind the other one's march.  k = 65536, n = 64, d = 2048 57.3 -> 51.4 us, n = 9 50.8 -> 46.6.
 // k = 32768, d = 4096: n = 64 43.0 us with the logits stored, n = 32 42.1 (a plain read of the 268 MB: 40.8; the
 // register-staged kernel before this one: 52.0 and 46.5).
-template <int NT, int MAXW, int TPW, int KB, int NST, int LPW, bool X>
-__global__ void __launch_bounds__(MAXW *kWave) __attribute__((amdgpu_waves_per_eu(1, (MAXW + 3) / 4)))
+template <int NT, int MAXW, int TPW, int KB, int NST, int LPW, bool X, int WGS>
+__global__ void __launch_bounds__(MAXW *kWave) __attribute__((amdgpu_waves_per_eu(WGS == 1 ? 1 : WGS * ((MAXW + 3) / 4), WGS * ((MAXW + 3) / 4))))
 head_mfma_kernel(const MfmaArgs a) {
     static_assert(!X || (MAXW == kStepWaves && TPW == NT), "the ninth group belongs to tiles of eight waves");
     extern __shared__ __align__(16) unsigned char smem[];
@@ -457,13 +460,15 @@ hipError_t launch_tile(const MfmaArgs &a, int threads, size_t lds, hipStream_t s
     return hipGetLastError();
 }
 
+constexpr int kTwinRingBytes = 79 * 1024;     // ... of two workgroups on a CU, each
 constexpr int kRingBytes = 156 * 1024;         // LDS for the ring; the ids and what the epilogue needs fit behind it
 
 // Variants of head_mfma_kernel: most waves, hidden-row groups per wave, blocks per stage, stages, loads per wave and stage.
 struct RowsVariant {
     int max_waves, tpw, blocks, stages, loads;
 };
-constexpr RowsVariant rows_variant(int NT, int row_groups, bool extra) {
+constexpr RowsVariant rows_variant(int NT, int row_groups, bool extra, bool twin = false) {
+    if (twin) return NT == 2 ? RowsVariant{8, 2, 1, 3, 3} : RowsVariant{8, 4, 1, 3, 3};
     if (extra) return NT == 2 ? RowsVariant{8, 2, 1, 7, 3} : RowsVariant{8, 4, 1, 6, 4};
     if (row_groups <= 2) return NT == 2 ? RowsVariant{8, 1, 2, 9, 2} : RowsVariant{8, 1, 2, 6, 3};
     if (row_groups <= 4) return NT == 2 ? RowsVariant{8, 1, 2, 6, 3} : RowsVariant{8, 2, 2, 4, 4};
@@ -472,13 +477,14 @@ constexpr RowsVariant rows_variant(int NT, int row_groups, bool extra) {
     return NT == 2 ? RowsVariant{12, 2, 1, 5, 3} : row_groups == 12 ? RowsVariant{12, 4, 1, 4, 3} : RowsVariant{12, 4, 1, 5, 3};
 }
 // (every piece of a stage has a load; the ring fits)
-constexpr bool rows_variant_ok(int NT, int row_groups, bool extra) {
-    const RowsVariant v = rows_variant(NT, row_groups, extra);
+constexpr bool rows_variant_ok(int NT, int row_groups, bool extra, bool twin = false) {
+    const RowsVariant v = rows_variant(NT, row_groups, extra, twin);
     const int groups = row_groups + (extra ? 1 : 0) + NT, waves = row_groups <= 4 ? kStepWaves : row_groups;
     return waves <= v.max_waves && v.loads * waves >= 2 * v.blocks * groups &&
-           v.stages * v.blocks * groups * kGroupBytes <= kRingBytes && v.loads * (v.stages - 2) <= 63 &&
+           v.stages * v.blocks * groups * kGroupBytes <= (twin ? kTwinRingBytes : kRingBytes) && v.loads * (v.stages - 2) <= 63 &&
            v.tpw * (row_groups <= 4 ? kStepWaves / row_groups : 1) >= NT;
 }
+static_assert(rows_variant_ok(2, 8, false, true) && rows_variant_ok(4, 8, false, true));
 static_assert(rows_variant_ok(2, 8, true) && rows_variant_ok(4, 8, true));
 static_assert(rows_variant_ok(2, 1, false) && rows_variant_ok(2, 2, false) && rows_variant_ok(2, 3, false) && rows_variant_ok(2, 4, false));
 static_assert(rows_variant_ok(2, 5, false) && rows_variant_ok(2, 6, false) && rows_variant_ok(2, 7, false) && rows_variant_ok(2, 8, false));
@@ -486,14 +492,15 @@ static_assert(rows_variant_ok(2, 9, false) && rows_variant_ok(2, 10, false) && r
 static_assert(rows_variant_ok(4, 1, false) && rows_variant_ok(4, 2, false) && rows_variant_ok(4, 3, false) && rows_variant_ok(4, 4, false));
 static_assert(rows_variant_ok(4, 5, false) && rows_variant_ok(4, 6, false) && rows_variant_ok(4, 7, false) && rows_variant_ok(4, 8, false));
 static_assert(rows_variant_ok(4, 9, false) && rows_variant_ok(4, 10, false) && rows_variant_ok(4, 11, false) && rows_variant_ok(4, 12, false));
-template <int NT, int RG, bool X>
+template <int NT, int RG, bool X, bool TWIN = false>
 hipError_t launch_rows(const MfmaArgs &a, size_t lds, hipStream_t st) {
-    constexpr RowsVariant v = rows_variant(NT, RG, X);
-    return launch_tile<head_mfma_kernel<NT, v.max_waves, v.tpw, v.blocks, v.stages, v.loads, X>>(a, a.nwaves * kWave, lds, st);
+    constexpr RowsVariant v = rows_variant(NT, RG, X, TWIN);
+    return launch_tile<head_mfma_kernel<NT, v.max_waves, v.tpw, v.blocks, v.stages, v.loads, X, TWIN ? 2 : 1>>(a, a.nwaves * kWave, lds, st);
 }
 template <int NT>
 hipError_t launch_rows_nt(const MfmaArgs &a, size_t lds, hipStream_t st) {
     if (a.extra_rows != 0) return launch_rows<NT, 8, true>(a, lds, st);
+    if (a.twin != 0) return a.row_groups == kStepWaves ? launch_rows<NT, 8, false, true>(a, lds, st) : hipErrorInvalidValue;
     // (one representative row count per variant)
     if (a.row_groups <= 2) return launch_rows<NT, 2, false>(a, lds, st);
     if (a.row_groups <= 4) return launch_rows<NT, 4, false>(a, lds, st);
@@ -543,8 +550,8 @@ hipError_t launch_wide_ntt(const MfmaArgs &a, size_t lds, hipStream_t st) {
 }  // namespace
 
 // ---------------------------------------------------------------- host side
-size_t rows_ring_bytes(int NT, int row_groups, bool extra) {
-    const RowsVariant v = rows_variant(NT, row_groups, extra);
+size_t rows_ring_bytes(int NT, int row_groups, bool extra, bool twin) {
+    const RowsVariant v = rows_variant(NT, row_groups, extra, twin);
     return (size_t)v.stages * v.blocks * (row_groups + (extra ? 1 : 0) + NT) * kGroupBytes;
 }
 size_t wide_ring_bytes(int MT, int NTT) { return wide_stages(MT, NTT) * wide_stage_bytes(MT, NTT); }

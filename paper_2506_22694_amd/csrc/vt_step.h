@@ -115,6 +115,7 @@ struct MfmaArgs {
     int row_groups;
     int ids_off;
     int passes;
+    int twin;                 // tiles of half a CU's LDS: two workgroups per CU
     // or null: a word the kernel sets to zero (the merge kernel behind it counts its workgroups there when a tree
     // level is fused; the kernel boundary orders the two)
     unsigned *ticket_clear;
@@ -167,7 +168,7 @@ size_t mfma_stage_bytes(int nwaves);
 hipError_t launch_head_mfma(const MfmaArgs &a, size_t lds, hipStream_t st);      // up to 8 hidden rows
 // 9 .. 64 hidden rows (NT = 2, 4 groups of 16) and 65 .. 256 (tiles of 64 * NTT hidden rows, NTT = 2 .. 4): bytes of the ring
 // of stages in LDS, and the launches
-size_t rows_ring_bytes(int NT, int row_groups, bool extra);
+size_t rows_ring_bytes(int NT, int row_groups, bool extra, bool twin);
 size_t wide_ring_bytes(int MT, int NTT);
 hipError_t launch_head_mfma_rows(int NT, const MfmaArgs &a, size_t lds, hipStream_t st);
 hipError_t launch_head_mfma_wide(int NTT, const MfmaArgs &a, size_t lds, hipStream_t st);

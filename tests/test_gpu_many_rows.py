@@ -121,3 +121,19 @@ def test_stored_logits_longer_than_one_stretch(n, k, m, late):
     oi, ol, lse = run_step(h, W, map_, m, return_lse=True)
     assert check_step(oi, ol, ref, map_, m, lse) <= 2 + n * m // 256
     assert oi[n // 2].tolist() == sorted(map_)[:m]
+
+
+# Two workgroups to a CU (heads of several rounds of tiles): just past one round, a ragged second round, rotated starts
+@pytest.mark.parametrize("n,k,d,m", [(9, 49153, 128, 8), (32, 65536, 256, 8), (33, 60001, 128, 16), (64, 65536, 1024, 8)])
+def test_step_of_several_rounds_of_tiles(n, k, d, m):
+    assert "tile_rows=128 waves=8" in vt.draft_head_step_plan(n, k, d, m)
+    W, map_ = synth.trimmed_head_direct(k, d, seed=1100 + n, dtype="bf16")
+    h = synth.hidden_rows(n, d, seed=k, dtype="bf16")
+    same = [3, 143, 128 * 255 + 5, 128 * 256 + 70, k - 1]
+    W[same] = W[same[0]]
+    ref = oracle.draft_head_step(h, W, map_, m)
+    oi, ol, lse, full = run_step(h, W, map_, m, return_lse=True, return_full=True)
+    assert check_step(oi, ol, ref, map_, m, lse) <= 2 + n // 32
+    check_full(full, ref)
+    dup = full[:, torch.tensor(same, device=full.device)]
+    assert torch.equal(dup, dup[:, :1].expand_as(dup))
