@@ -383,7 +383,7 @@ def main():
             mstep(r, hor_mixed)
         us_split = time_region(lambda r: mstep(r, hor_split), 200)
         us_mixed = time_region(lambda r: mstep(r, hor_mixed), 200)
-        # Eq. 1 for both heads in one call (the selection is bound by its eleven launches, taken once for all heads)
+        # Eq. 1 for both heads in one call (the selection is bound by its four launches, taken once for all heads)
         counts2 = torch.stack([torch.randint(0, 50, (V,), device=dev, dtype=torch.int64) for _ in range(2)]).contiguous()
         for _ in range(3):
             vt.build_trimmed_heads(counts2, None, [k, kt])
