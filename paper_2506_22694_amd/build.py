@@ -47,6 +47,9 @@ NO_SCRATCH = ("vt_head_", "vt_row_select")
 # and far above zero).  The model was validated against the assembly of AMD clang 20 (ROCm 7.2.0), -O3, gfx950.
 MIN_HAND_LOADS = {"vt_head_mfma.hip": 250, "vt_head_gemv_np1.hip": 150, "vt_head_gemv_np2.hip": 150,
                   "vt_head_gemv_np4.hip": 150, "vt_head_gemv_np8.hip": 36}
+# Likewise the hand-written loads straight into LDS, which are checked for the wait state behind the write of M0
+# (1138 today).
+MIN_LDS_LOADS = {"vt_head_mfma_rows.hip": 500}
 
 
 def _scratch_users(remarks: str):
@@ -73,13 +76,21 @@ def _inflight_violations(src: str):
     if r.returncode != 0:
         raise RuntimeError(f"hipcc -S failed on {src}:\n{r.stderr}")
     with open(asm) as f:
-        bad, followed = inflight_lint.check_asm(f.read())
+        text = f.read()
     os.remove(asm)
+    bad, followed = inflight_lint.check_asm(text)
+    hazards, into_lds = inflight_lint.check_m0(text)
     floor = MIN_HAND_LOADS.get(os.path.basename(src), 0)
     if followed < floor:
         raise RuntimeError(f"{os.path.basename(src)}: the in-flight register check followed {followed} hand-issued "
                            f"loads, fewer than the {floor} this source is known to hold: it no longer recognises "
                            "them (compiler output changed?) and would pass anything")
+    if into_lds < MIN_LDS_LOADS.get(os.path.basename(src), 0):
+        raise RuntimeError(f"{os.path.basename(src)}: {into_lds} hand-written loads into LDS found, fewer than the "
+                           f"{MIN_LDS_LOADS[os.path.basename(src)]} this source is known to hold")
+    if hazards:
+        raise RuntimeError(f"{os.path.basename(src)}: loads into LDS directly behind the write of M0 they read "
+                           f"(kernel, line in the device assembly, text): {hazards[:5]}")
     return bad
 
 

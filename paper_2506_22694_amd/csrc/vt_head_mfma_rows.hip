@@ -27,16 +27,17 @@ constexpr int kGroupBytes = 16 * 128;          // 16 rows of a stage
 constexpr int kPieceBytes = 1024;              // one load instruction: 8 rows of a stage
 
 // 64 lanes x 16 bytes from base + voff into LDS at lds + 16 * lane.  STREAM: read once (W_trim); otherwise kept in
-// the L2 for the other workgroups (h).
+// the L2 for the other workgroups (h).  M0 holds the LDS address, and a load that reads it needs a wait state behind the
+// scalar write (the compiler puts one there by itself, but not inside a string of ours: the build looks for it).
 template <bool STREAM>
 __device__ __forceinline__ void lds_load16(unsigned lds, unsigned voff, const void *base) {
     if constexpr (STREAM)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
     else
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_load4(unsigned lds, unsigned voff, const void *base) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
 // All but the N youngest loads of this wave have landed, its LDS reads are done; then the workgroup's barrier.
 template <int N>

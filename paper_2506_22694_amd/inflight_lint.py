@@ -9,6 +9,11 @@ module reads the device assembly the compiler produced and follows every path fr
 first wait that is certain to cover it; any instruction on the way that names one of the load's
 destination registers is reported.
 
+Loads straight into LDS hold no register in flight, but they read the LDS address from M0: between a scalar
+write of M0 and such a load there must be a wait state (any other instruction).  The compiler takes care of that
+for its own instructions and not inside inline assembly, so `check_m0` reports every hand-written load that
+directly follows a write of M0 on some path.
+
 Model: loads return in the order they were issued, so after `s_waitcnt vmcnt(N)` a load is complete if at
 least N vector-memory loads were issued after it (stores and atomics are not counted: they may complete
 out of order with loads, which can only make the wait stronger than assumed here).
@@ -132,6 +137,25 @@ def check_function(name, ins, labels, drains=None):
     return bad
 
 
+_WRITES_M0 = re.compile(r"^s_\w+\s+m0\b")
+
+
+def check_m0(asm: str):
+    """(violations, hand-written loads into LDS): a load whose predecessor on some path writes M0 is a violation."""
+    bad, loads = [], 0
+    for name, ins, labels in _functions(asm):
+        after_write = set()
+        for i, x in enumerate(ins):
+            if _WRITES_M0.match(x.text):
+                after_write.update(_successors(ins, labels, i))
+        for i, x in enumerate(ins):
+            if x.by_hand and x.text.startswith(_LOADS) and "_lds_" in x.text.split()[0]:
+                loads += 1
+                if i in after_write:
+                    bad.append((name, x.line, x.text))
+    return bad, loads
+
+
 def check_asm(asm: str, drains=None):
     """All violations in an assembly file, and the number of hand-issued loads that were followed."""
     bad, loads = [], 0
@@ -145,9 +169,13 @@ if __name__ == "__main__":
     status = 0
     for path in sys.argv[1:]:
         compiler_waits = set()
-        violations, n = check_asm(open(path).read(), compiler_waits)
+        text = open(path).read()
+        violations, n = check_asm(text, compiler_waits)
+        m0, n_lds = check_m0(text)
         print(f"{path}: {n} hand-issued loads, {len(violations)} violations, "
-              f"{len(compiler_waits)} compiler-inserted waits that cover hand-issued loads")
+              f"{len(compiler_waits)} compiler-inserted waits that cover hand-issued loads; "
+              f"{n_lds} hand-written loads into LDS, {len(m0)} directly behind a write of M0")
+        violations += m0
         for v in violations[:20]:
             print("  ", v)
         for v in sorted(compiler_waits)[:20]:
