@@ -398,7 +398,7 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
         p.off_zbuf = off;
         if (p.row_select) off += zbuf_bytes;
     }
-    if (p.wide && (size_t)n * d * 2 >= vt::kPackHBytes) {
+    if (p.wide && vt::packs_h(p.NT / 4, n, d)) {
         p.off_hpack = off;
         off = round_up(off + (size_t)d * p.NT * 32, 256);
     }

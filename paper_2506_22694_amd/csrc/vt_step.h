@@ -66,10 +66,11 @@ struct StepArgs {
 // ---- matrix-core path (n > 8) ----
 constexpr int kMfmaTileRows = 128;     // rows of W_trim per workgroup (16 per wave)
 constexpr int kMfmaMaxN = 256;         // hidden rows one launch covers
-// from this size on h is re-laid for the wide kernel (an XCD's L2 holds 4 MiB: read in place, hidden rows 2 d bytes apart,
-// it shares its channels with W's lines; n = 256, k = 32768, d = 8192: 137.1 us in place, 136.9 re-laid)
-constexpr size_t kPackHBytes = (size_t)4 << 20;
 constexpr int kRowsKernelMaxN = 64;    // ... by tiles that hold all hidden rows per wave; above: the wide kernel
+// Whether h is re-laid for the wide kernel (tiles of 64 * NTT hidden rows): more than 192 rows of 4 MiB and more, what an
+// XCD's L2 holds -- read in place, hidden rows 2 d bytes apart, h shares its channels with W's lines (n = 256, k = 32768,
+// d = 8192: 137.1 us in place, 136.9 re-laid).  Up to 192 rows only the kernel that reads in place is built.
+inline bool packs_h(int NTT, int n, int d) { return NTT == 4 && (size_t)n * d * 2 >= ((size_t)4 << 20); }
 // With more tokens per row than this the matrix-core kernel stores its logits and a workgroup per hidden row finishes the
 // step: up to 8 hidden rows, and beyond ...
 constexpr int kRowSelectMinL = 11;

@@ -137,3 +137,18 @@ def test_step_of_several_rounds_of_tiles(n, k, d, m):
     check_full(full, ref)
     dup = full[:, torch.tensor(same, device=full.device)]
     assert torch.equal(dup, dup[:, :1].expand_as(dup))
+
+
+# 4 MiB of h and more with 65 .. 192 hidden rows (h is read in place there), at the threshold, and a last group of that many
+@pytest.mark.parametrize("n,k,d,m", [(127, 600, 16384, 4), (128, 600, 16384, 8), (192, 500, 12288, 4), (400, 300, 16384, 4)])
+def test_step_of_many_long_rows(n, k, d, m):
+    W, map_ = synth.trimmed_head_direct(k, d, seed=1200 + n, dtype="bf16")
+    h = synth.hidden_rows(n, d, seed=k, dtype="bf16")
+    same = [3, 140, k - 1]
+    W[same] = W[same[0]]
+    ref = oracle.draft_head_step(h, W, map_, m)
+    oi, ol, lse, full = run_step(h, W, map_, m, return_lse=True, return_full=True)
+    assert check_step(oi, ol, ref, map_, m, lse) <= 2 + n // 32
+    check_full(full, ref)
+    dup = full[:, torch.tensor(same, device=full.device)]
+    assert torch.equal(dup, dup[:, :1].expand_as(dup))
