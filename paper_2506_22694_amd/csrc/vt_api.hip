@@ -87,6 +87,7 @@ struct StepPlan {
     int row_groups = 0, ids_off = 0, passes = 1;
     bool twin = false;
     bool wide = false;         // more than 64 hidden rows
+    size_t list_room = 0;      // ... bytes that the lists of fewer hidden rows may take on smaller tiles
 };
 
 using vt::kTicketBytes;
@@ -161,6 +162,9 @@ void plan_many_rows(StepPlan &p, int n, int k, int d, int m) {
         int MT = 4;
         for (int x : {1, 2, 3, 5})
             if (fits(32 * x) && cost(32 * x) < cost(32 * MT)) MT = x;
+        // (fewer hidden rows take the cheaper tiles, as long as their lists stay within that bound)
+        for (int x : {1, 2, 3, 5})
+            if (!fits(32 * x) && cost(32 * x) <= cost(32 * MT)) p.list_room = (size_t)VT_STATIC_WS_BYTES - 65536;
         p.row_groups = 2 * MT;
         p.nwaves = vt::kStepWaves;
         ring = vt::wide_ring_bytes(MT, NTT);
@@ -392,9 +396,11 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
     if (p.mfma && n > vt::kGemvMaxN && p.row_select) {
         // the stored logits lie where the lists would (up to 8 tokens per row the larger of the two is reserved: with
         // fewer hidden rows the same workspace serves lists)
-        off += m <= vt::kRowSelectMinLManyRows && pms_bytes + key_bytes > zbuf_bytes ? pms_bytes + key_bytes : zbuf_bytes;
+        size_t room = zbuf_bytes;
+        if (m <= vt::kRowSelectMinLManyRows && pms_bytes + key_bytes > room) room = pms_bytes + key_bytes;
+        off += p.list_room > room ? p.list_room : room;
     } else {
-        off += pms_bytes + key_bytes;
+        off += p.list_room > pms_bytes + key_bytes ? p.list_room : pms_bytes + key_bytes;
         p.off_zbuf = off;
         if (p.row_select) off += zbuf_bytes;
     }
@@ -403,12 +409,6 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
         off = round_up(off + (size_t)d * p.NT * 32, 256);
     }
     p.bytes = off;
-    if (p.mfma && n > vt::kGemvMaxN) {
-        // (a workspace for this many hidden rows serves a step of fewer too, whose tiles may be smaller)
-        const int fewer_n = n > vt::kRowsKernelMaxN ? vt::kRowsKernelMaxN : n > 32 ? 32 : vt::kGemvMaxN;
-        const StepPlan fewer = plan_step(fewer_n, k, d, m, dtype);
-        if (fewer.ok && fewer.bytes > p.bytes) p.bytes = fewer.bytes;
-    }
     p.ok = true;
     return p;
 }
@@ -458,9 +458,15 @@ int run_step_rows(const void *h, int n, const void *W_trim, int w_type, int k, i
     return VT_OK;
 }
 
-// Workspace a step of up to n rows on a head of k rows may need, whatever the element type
+// Workspace a step of up to n rows on a head of k rows may need, whatever the element type.  A workspace for n rows serves
+// a step of fewer (from 8 on) too, whose kernel and tiles may be others: inside a kernel's range the size grows with the rows
+// (list_room takes care of the one choice of tiles that the rows decide), so the ends of the ranges below n are looked at.
 size_t step_ws_bytes(int n, int k, int d, int m) {
-    size_t b = 0;
+    size_t b = n > vt::kMfmaMaxN          ? step_ws_bytes(vt::kMfmaMaxN, k, d, m)
+               : n > vt::kRowsKernelMaxN ? step_ws_bytes(vt::kRowsKernelMaxN, k, d, m)
+               : n > 32                   ? step_ws_bytes(32, k, d, m)
+               : n > vt::kGemvMaxN       ? step_ws_bytes(vt::kGemvMaxN, k, d, m)
+                                          : 0;
     for (int dtype : {VT_BF16, VT_F32}) {
         const int c = pick_chunk(n, k, d, m, dtype);
         if (c == 0) continue;
