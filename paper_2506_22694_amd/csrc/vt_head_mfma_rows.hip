@@ -461,6 +461,9 @@ hipError_t launch_tile(const MfmaArgs &a, int threads, size_t lds, hipStream_t s
     return hipGetLastError();
 }
 
+// A lane's offset inside a tile or h is 32 bits: 255 rows of less than 16 MiB.
+bool offsets_fit(const MfmaArgs &a) { return (size_t)a.d * 2 < ((size_t)1 << 24); }
+
 constexpr int kTwinRingBytes = 79 * 1024;     // ... of two workgroups on a CU, each
 constexpr int kRingBytes = 156 * 1024;         // LDS for the ring; the ids and what the epilogue needs fit behind it
 
@@ -558,6 +561,7 @@ size_t rows_ring_bytes(int NT, int row_groups, bool extra, bool twin) {
 size_t wide_ring_bytes(int MT, int NTT) { return wide_stages(MT, NTT) * wide_stage_bytes(MT, NTT); }
 
 hipError_t launch_head_mfma_rows(int NT, const MfmaArgs &a, size_t lds, hipStream_t st) {
+    if (!offsets_fit(a)) return hipErrorInvalidValue;
     switch (NT) {
         case 2: return launch_rows_nt<2>(a, lds, st);
         case 4: return launch_rows_nt<4>(a, lds, st);
@@ -565,6 +569,7 @@ hipError_t launch_head_mfma_rows(int NT, const MfmaArgs &a, size_t lds, hipStrea
     }
 }
 hipError_t launch_head_mfma_wide(int NTT, const MfmaArgs &a, size_t lds, hipStream_t st) {
+    if (!offsets_fit(a)) return hipErrorInvalidValue;
     switch (NTT) {
         case 2: return launch_wide_ntt<2>(a, lds, st);
         case 3: return launch_wide_ntt<3>(a, lds, st);

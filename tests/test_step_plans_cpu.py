@@ -2,6 +2,7 @@
 import ctypes
 
 import pytest
+import torch
 
 from test_boundary_cpu import _plan, lib  # noqa: F401  (lib: a fixture)
 
@@ -30,3 +31,15 @@ def test_lists_that_keep_within_the_librarys_own_workspace_still_do(lib):
     own = 4 << 20
     for n, k, d, m in ((112, 48500, 4096, 8), (127, 48500, 4096, 8), (241, 41000, 4096, 4), (64, 65536, 4096, 8)):
         assert 0 < lib.vt_draft_head_step_ws_bytes(n, k, d, m) <= own
+
+
+# Rows of 16 MiB and more are refused before anything is launched: offsets inside a tile are 32-bit (24-bit factors up to 8 rows)
+@pytest.mark.parametrize("n", [9, 64, 65, 200, 256])
+def test_rows_too_long_for_the_offsets_inside_a_tile_are_refused(lib, n):
+    A = ctypes.c_void_p(0x10000)
+    lib.vt_last_device_error.restype = ctypes.c_char_p
+    d = 1 << 23
+    step = lambda dd: lib.vt_draft_head_step(A, 1, n, A, 1, 300, dd, A, 4, A, A, None, None, A, ctypes.c_size_t(1 << 60), None)
+    assert step(d) == 6 and b"invalid argument" in lib.vt_last_device_error()
+    if not torch.cuda.is_available():      # (never launched on the fake addresses where there is a device)
+        assert step(d - 128) == 6 and b"invalid argument" not in lib.vt_last_device_error()
