@@ -376,6 +376,7 @@ __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const lon
     unsigned long long upto_m = mass;
     block_scan2(upto_n, upto_m, pn, pm);
     if (tid == kRankSortThreads - 1) s_total = upto_m;
+    if (tid == 0) s_bin = -1;
     __syncthreads();
     const unsigned long long total = s_total;
     // one fp64 product, then its ceiling; never above the total (beyond 2^53 tokens the product of P = 1
@@ -397,6 +398,10 @@ __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const lon
     }
     __syncthreads();
     const int bin = s_bin;
+    if (bin < 0) {      // no bin reaches it: counts below zero, or a mass of 2^63 and more
+        if (tid < 3) out[tid] = tid == 2 ? (long long)total : 0;
+        return;
+    }
     unsigned before_n = s_n;
     unsigned long long before_m = s_m, T = (unsigned)bin;
     if (bin >= kBinExact) {
@@ -444,6 +449,7 @@ __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const lon
         unsigned long long take = 1;
         if (target > before_m && T > 0) {
             take = (target - before_m + T - 1) / T;
+            if (take > (unsigned)V - before_n) take = (unsigned)V - before_n;      // (only where the mass has wrapped around)
         }
         out[0] = (long long)(before_n + take);
         out[1] = (long long)(before_m + take * T);

@@ -70,3 +70,13 @@ def test_count_bins_beyond_eight_bits(V, dtype):
     for n in (ids.size, ids.size - 1, ids.size - 4097, 5):
         c = vt.count_tokens(torch.from_numpy(ids[:n]).to(dtype).cuda(), V)
         assert np.array_equal(c.cpu().numpy(), np.bincount(ids[:n], minlength=V)), n
+
+
+# Counts outside what choose_k is for (values >= 0, their sum below 2^63): it answers, and ends
+@pytest.mark.parametrize("V", [3, 4096, 5000])
+@pytest.mark.parametrize("low,high", [(-5, 6), (-2**62, 2**62), (2**61, 2**62), (-9, 0)])
+def test_choose_k_ends_on_counts_outside_its_range(V, low, high):
+    c = np.random.default_rng(V).integers(low, high, size=V, dtype=np.int64)
+    for P in (0.0, 0.5, 1.0):
+        k, _, total = vt.choose_k(torch.from_numpy(c).cuda(), top_p=P)
+        assert 0 <= k <= V and total == int(c.view(np.uint64).sum().astype(np.int64))
