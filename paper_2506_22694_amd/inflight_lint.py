@@ -66,21 +66,20 @@ def _functions(asm: str):
         m = _LABEL.match(s)
         if m:
             lab = m.group(1)
+            if lab.startswith(".Lfunc_end") and name is not None:      # (s_endpgm may stand anywhere in a function)
+                yield name, ins, labels
+                name = None
+                continue
             if not lab.startswith(".L") and name is None:
                 name, ins, labels = lab, [], {}
             elif name is not None:
                 labels[lab] = len(ins)
             continue
         if s.startswith("."):
-            if s.startswith(".Lfunc_end") or s.startswith(".size"):
-                pass
             continue
         if name is None:
             continue
         ins.append(Ins(s, no, by_hand, _regs(s.split(None, 1)[1]) if " " in s or "\t" in s else frozenset()))
-        if s.startswith("s_endpgm"):
-            yield name, ins, labels
-            name = None
     if name is not None and ins:
         yield name, ins, labels
 

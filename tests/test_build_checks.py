@@ -32,3 +32,13 @@ def test_the_source_with_loads_into_lds_is_checked():
         src = open(f"{build.CSRC}/{name}").read()
         writes = src.count("s_mov_b32 m0")
         assert writes > 0 and src.count("s_mov_b32 m0, %0\\n\\ts_nop 0\\n\\tglobal_load_lds_") == writes
+
+
+def test_a_function_may_end_in_several_places():
+    load, wait = "\t;;#ASMSTART\n\tglobal_load_dwordx4 v[4:7], v1, s[2:3]\n\t;;#ASMEND\n", "\ts_waitcnt vmcnt(0)\n"
+    tail = "\ts_cbranch_scc1 .LBB0_2\n\ts_endpgm\n.LBB0_2:\n"
+    end = "\ts_endpgm\n.Lfunc_end0:\n\t.size kern, .Lfunc_end0-kern\n"
+    other = "other:\n\tv_mov_b32_e32 v40, v4\n\ts_endpgm\n.Lfunc_end1:\n"
+    assert inflight_lint.check_asm(_HEAD + load + tail + wait + "\tv_mov_b32_e32 v9, v4\n" + end + other) == ([], 1)
+    bad, loads = inflight_lint.check_asm(_HEAD + load + tail + "\tv_mov_b32_e32 v9, v4\n" + wait + end + other)
+    assert [b[3] for b in bad] == ["v_mov_b32_e32 v9, v4"] and loads == 1
