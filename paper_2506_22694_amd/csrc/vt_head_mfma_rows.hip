@@ -62,17 +62,16 @@ __device__ __forceinline__ void wait_stage_and_sync(int younger) {
 // Where a workgroup's march over ns stages starts and where its ranges end.
 template <int NR>
 struct March {
-    int ns, rot, start;
+    int ns, rot, start, step;
     bool rotate;
-    __device__ __forceinline__ static int bound(int r, int ns) {
-        // NR = 2: the second range starts 2 KiB in (half a row on, or any multiple of 4 KiB, crowds the same channels)
-        return NR == 2 ? r * 16 : r * (ns / NR);
-    }
     __device__ __forceinline__ March(int ns_, int d) : ns(ns_) {
         rotate = NR > 1 && d % 2048 == 0 && (NR > 2 || d >= 4096);
         rot = rotate ? first_range<NR>((int)blockIdx.x) : 0;
-        start = bound(rot, ns);
+        // stages from one start to the next
+        step = NR == 2 ? 16 : range_step<NR>(ns, d);
+        start = bound(rot);
     }
+    __device__ __forceinline__ int bound(int r) const { return r * step; }
     // stage of the row that is multiplied at step s < ns
     __device__ __forceinline__ int stage_of(int s) const {
         const int u = start + s;
@@ -81,8 +80,10 @@ struct March {
     // the stage at which range (rot + j) % NR ends (exclusive; ns = the end of the row)
     __device__ __forceinline__ int end_of(int j) const {
         const int r = (rot + j) & (NR - 1);
-        return r == NR - 1 ? ns : bound(r + 1, ns);
+        return r == NR - 1 ? ns : bound(r + 1);
     }
+    // ... and the number of stages in it
+    __device__ __forceinline__ int length_of(int j) const { return end_of(j) - bound((rot + j) & (NR - 1)); }
 };
 
 // Tile logits in LDS: hidden row i at i * pitch floats.
@@ -212,7 +213,7 @@ head_mfma_kernel(const MfmaArgs a) {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), c, 0, 0, 0);
     };
     int slot = 0, closed = 0;
-    int left = march.end_of(0) - march.start;      // blocks until the open range ends
+    int left = march.length_of(0);      // blocks until the open range ends
     for (int s = 0; s < nstages; ++s) {
         wait_stage_and_sync<LPW, NST - 2>(nstages - 1 - s);      // stage s is in LDS, the slot of stage s - 1 is free
         if (s + NST - 1 < nstages) load_stage(s + NST - 1, slot == 0 ? NST - 1 : slot - 1);
@@ -220,7 +221,7 @@ head_mfma_kernel(const MfmaArgs a) {
             if (left == 0) {
                 sums.close(acc, march.rot, closed);
                 ++closed;
-                left = march.ns / NR;
+                left = march.length_of(closed);
             }
             left -= KB;
         }
@@ -372,7 +373,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
     };
     wait_stage_and_sync<LPW, NST - 1>(march.ns - 1);
     int slot = 0, closed = 0;
-    int left = march.end_of(0) - march.start;
+    int left = march.length_of(0);
     read_operands(a0, b0, 0, 0);
     for (int s = 0; s < march.ns; ++s) {
         read_operands(a1, b1, 1, slot);
@@ -403,7 +404,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
         if (NR > 1 && march.rotate && --left == 0 && s + 1 < march.ns) {
             sums.close(acc, march.rot, closed);
             ++closed;
-            left = march.end_of(closed) - march.bound((march.rot + closed) & (NR - 1), march.ns);
+            left = march.length_of(closed);
         }
     }
     if (NR > 1 && march.rotate) {

@@ -78,6 +78,17 @@ struct RangeSums {
     }
 };
 
+// Columns from one range's start to the next, in units of which a row of d holds `units`.  NR equal ranges; four that
+// would start whole multiples of 4 KiB apart, on the same channels again, are a further 1 KiB apart each, and the last
+// one is shorter (d = 8192: n = 100, k = 40000 146.6 -> 122.9 us, n = 160, k = 32768 134.0 / 124.5, k = 24576 112.2 /
+// 107.7, n = 100, k = 32768 100.8 / 101.8).  Eight ranges are equal at any d: 512 bytes more each at d = 16384 gained at
+// some sizes what it lost at others (n = 64: k = 20000 146.1 / 138.4, k = 32768 162.8 / 165.8; n = 6, k = 30000 153.5 / 157.0).
+template <int NR>
+__device__ __forceinline__ int range_step(int units, int d) {
+    const int step = units / NR;
+    return NR == 4 && d % 8192 == 0 ? step + units * 512 / d : step;
+}
+
 // The range workgroup b starts with.
 template <int NR>
 __device__ __forceinline__ int first_range(int b) {
