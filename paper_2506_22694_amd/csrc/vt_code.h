@@ -25,4 +25,41 @@ __device__ __forceinline__ int count_bin(unsigned long long c) { return (int)cou
 __device__ __forceinline__ int bin_shift(int bin) { return 11 + ((bin - kBinExact) >> 5) - 5; }
 __device__ __forceinline__ unsigned long long bin_prefix(int bin) { return 32ull + (unsigned)((bin - kBinExact) & 31); }
 
+// ---- what a bin of several values leaves open, below its prefix
+// The next level of the histogram: kDigitBits of the bits below the prefix.  6 + 11 highest bits of a count are then known,
+// all of them below 2^17.
+constexpr int kDigitBits = 11;
+constexpr int kDigitBins = 1 << kDigitBits;
+
+__device__ __forceinline__ unsigned long long low_bits(int n) { return (1ull << n) - 1ull; }      // n < 64
+
+// OR over the wave
+__device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v |= __shfl_xor(v, o);
+    return v;
+}
+
+// h[d] += 1 for every lane with `in` (all lanes call): the lanes that share the first one's digit are added at once --
+// counts are often all the same, and 64 LDS atomics on one address queue.
+__device__ __forceinline__ void wave_tally(unsigned *h, int d, bool in) {
+    const unsigned long long live = __ballot(in);
+    if (live == 0ull) return;
+    const int leader = __ffsll((long long)live) - 1;
+    const int first = __builtin_amdgcn_readlane(d, leader);
+    const unsigned long long same = __ballot(in && d == first);
+    if (in && d != first) atomicAdd(&h[d], 1u);
+    if ((int)(threadIdx.x & 63) == leader) atomicAdd(&h[first], (unsigned)__popcll(same));
+}
+
+// The bits below the prefix that some ids of a bin have set and some have not (`ones`: set in any, `zeros`: clear in any).
+// The others are common to all of them: what is left to find of a value of `left` open bits then starts at the highest bit
+// that varies.  T: the bits above; takes the common bits over and returns how many stay open.
+__device__ __forceinline__ int skip_common_bits(unsigned long long &T, int left, unsigned long long ones, unsigned long long zeros) {
+    const unsigned long long vary = ones & zeros & low_bits(left);
+    const int open = vary == 0ull ? 0 : 64 - __clzll((long long)vary);
+    T = (T << (left - open)) | ((ones & low_bits(left)) >> open);
+    return open;
+}
+
 }  // namespace vt

@@ -80,3 +80,36 @@ def test_choose_k_ends_on_counts_outside_its_range(V, low, high):
     for P in (0.0, 0.5, 1.0):
         k, _, total = vt.choose_k(torch.from_numpy(c).cuda(), top_p=P)
         assert 0 <= k <= V and total == int(c.view(np.uint64).sum().astype(np.int64))
+
+
+def _large_counts(kind, V, rng):
+    if kind == "close together":           # one bin, one next digit, twenty open bits
+        return (1 << 40) + rng.integers(0, 1 << 20, size=V)
+    if kind == "few values":               # ... and two, in no order
+        return (1 << 40) + rng.integers(0, 3, size=V)
+    if kind == "mixed":                    # exact bins, wide bins and one crowded one
+        return np.where(rng.random(V) < 0.5, rng.integers(0, 5000, size=V), (1 << 35) + rng.integers(0, 1 << 13, size=V))
+    if kind == "around 2^17":              # the last values that a bin and its next digit tell apart
+        return rng.integers(2**17 - 300, 2**17 + 300, size=V)
+    if kind == "all bits":
+        return rng.integers(0, 2**63 - 1, size=V, dtype=np.int64) >> rng.integers(0, 63, size=V)
+    if kind == "equal":
+        return np.full(V, (1 << 45) + 12345)
+    raise ValueError(kind)
+
+
+# A k-th largest count of 2048 and more: found by all workgroups and the last of them; one workgroup, its edge, many
+@pytest.mark.parametrize("V", [5, 1024, 1025, 30011, 128256])
+@pytest.mark.parametrize("kind", ["close together", "few values", "mixed", "around 2^17", "all bits", "equal"])
+def test_selection_of_large_counts(kind, V):
+    rng = np.random.default_rng(V)
+    c = np.asarray(_large_counts(kind, V, rng), dtype=np.int64)
+    dc = torch.from_numpy(c).cuda()
+    order = np.lexsort((np.arange(V), -c))          # (count descending, id ascending; the oracle's sort takes seconds here)
+    for k in sorted({1, 2, V // 50 + 1, V // 3 + 1, V // 2 + 1, V - 1, V}):
+        a, _ = vt.build_trimmed_head(dc, None, k)
+        assert np.array_equal(a.cpu().numpy(), np.sort(order[:k])), k
+    both = np.stack([c, np.arange(V) % 7])          # beside a head whose bins are exact
+    for row, (a, _) in zip(both, vt.build_trimmed_heads(torch.from_numpy(both).cuda(), None, [V // 3 + 1, V // 2 + 1])):
+        k = a.numel()
+        assert np.array_equal(a.cpu().numpy(), np.sort(np.lexsort((np.arange(V), -row))[:k]))
