@@ -19,9 +19,13 @@
 //   Eight launches in a fixed sequence; nothing is read back.  A pass whose digit is the same for every key moves
 //   nothing and is skipped: each kernel derives that, and which buffer holds the data, from the digit totals alone.
 //   (Eight passes over the bytes of the counts, nineteen launches, took 72 us at V = 128256 after 10^7 tokens; now 42.)
-// choose_*: no sort: a histogram over bins of counts (exact below 2048) with the mass of every bin; one workgroup walks
-//   it from the largest counts down and divides inside the bin in which the mass reaches ceil(P * total).
-//   (With the read-back of k 107 us behind a full sort, now 31.)
+// choose_*: no sort: a histogram over bins of counts (exact below 2048) with the mass of every bin, walked from the
+//   largest counts down to the bin in which the mass reaches ceil(P * total).  With the read-back of k 107 us behind a full
+//   sort, now 31.  Where that bin holds several values all workgroups histogram the next eleven bits of its ids, and the
+//   one that is done last divides further; it reads all counts once per eleven bits that are still open, only where the
+//   target falls between ids that share the 17 highest bits.
+//   V = 128256, P = 0.25 after 10^7 tokens 18 us (48 with one workgroup for the whole division, 80 behind the sort), P = 0.9
+//   after 10^9 22 (31, 92), equal counts 21 (870, 61), all counts in 2^40 .. 2^40 + 2^20 91 (412, 79).
 #include "vt_build.h"
 #include "vt_code.h"
 #include "vt_device.h"
@@ -250,14 +254,21 @@ __global__ void __launch_bounds__(256) rsort_out_kernel(const long long *__restr
 namespace {
 
 constexpr int kWideBins = kBins - kBinExact;      // bins of more than one value: their mass is summed
+// of the bin that is divided: digits of its ids, their mass, and the bits below its prefix that are set in any / clear in any
 struct ChooseBufs {
-    unsigned long long *mass;      // [kWideBins]
-    unsigned *hist;                // [kBins]
+    unsigned long long *mass;          // [kWideBins]
+    unsigned long long *digit_mass;    // [kDigitBins]
+    unsigned long long *bits;          // [2]
+    unsigned *hist;                    // [kBins]
+    unsigned *digits;                  // [kDigitBins]
+    unsigned *done;                    // [2] workgroups that have added theirs
 };
+constexpr int kChooseZeroWords = kWideBins + kDigitBins + 2 + (kBins + kDigitBins + 2) / 2;      // 64-bit words, mass .. done
+static_assert((kBins + kDigitBins) % 2 == 0, "whole 64-bit words");
 
 __global__ void __launch_bounds__(kRankSortThreads) choose_zero_kernel(ChooseBufs b) {
-    for (int i = threadIdx.x; i < kBins; i += kRankSortThreads) b.hist[i] = 0u;
-    for (int i = threadIdx.x; i < kWideBins; i += kRankSortThreads) b.mass[i] = 0ull;
+    const int i = blockIdx.x * kRankSortThreads + threadIdx.x;
+    if (i < kChooseZeroWords) b.mass[i] = 0ull;
 }
 __global__ void __launch_bounds__(64) choose_clear_kernel(long long *__restrict__ out) {
     if (threadIdx.x < 3) out[threadIdx.x] = 0;
@@ -291,16 +302,35 @@ __global__ void __launch_bounds__(kRankSortThreads) choose_min_kernel(const long
     }
 }
 
+// As wave_tally, with the mass c of the ids; digits below `exact` have none (it follows from their number).
+__device__ __forceinline__ void wave_tally_mass(unsigned *h, unsigned long long *m, int exact, int d, bool in, unsigned long long c) {
+    const unsigned long long live = __ballot(in);
+    if (live == 0ull) return;
+    const int leader = __ffsll((long long)live) - 1;
+    const int first = __builtin_amdgcn_readlane(d, leader);
+    const bool same = in && d == first;
+    const unsigned long long group = __ballot(same);
+    if (in && !same) {
+        atomicAdd(&h[d], 1u);
+        if (d >= exact) atomicAdd(&m[d - exact], c);
+    }
+    unsigned long long sum = same ? c : 0ull;
+    if (first >= exact && __popcll(group) > 1) sum = (unsigned long long)wave_sum_i64((long long)sum);
+    if (lane_id() == leader) {
+        atomicAdd(&h[first], (unsigned)__popcll(group));
+        if (first >= exact) atomicAdd(&m[first - exact], sum);
+    }
+}
+
 // The counts of this workgroup (all of them when gridDim.x = 1) into bins of LDS, ids and -- above 2048 -- mass.
 __device__ __forceinline__ void bin_counts(const long long *__restrict__ counts, int V, unsigned *h, unsigned long long *m) {
     for (int i = threadIdx.x; i < kBins; i += kRankSortThreads) h[i] = 0u;
     for (int i = threadIdx.x; i < kWideBins; i += kRankSortThreads) m[i] = 0ull;
     __syncthreads();
-    for (int j = blockIdx.x * kRankSortThreads + threadIdx.x; j < V; j += gridDim.x * kRankSortThreads) {
-        const unsigned long long c = (unsigned long long)counts[j];
-        const int bin = count_bin(c);
-        atomicAdd(&h[bin], 1u);
-        if (bin >= kBinExact) atomicAdd(&m[bin - kBinExact], c);
+    for (unsigned base = blockIdx.x * kRankSortThreads; base < (unsigned)V; base += gridDim.x * kRankSortThreads) {
+        const bool in = base + threadIdx.x < (unsigned)V;
+        const unsigned long long c = in ? (unsigned long long)counts[base + threadIdx.x] : 0ull;
+        wave_tally_mass(h, m, kBinExact, count_bin(c), in, c);
     }
     __syncthreads();
 }
@@ -345,19 +375,20 @@ __device__ __forceinline__ void block_scan2(unsigned &n, unsigned long long &mas
     mass += bm;
 }
 
-// One workgroup.  DIRECT: it bins all counts itself (small V).
+// DIRECT: one workgroup, which bins all counts itself (small V).
+constexpr int kChooseMaxBlocks = 128;
 template <bool DIRECT>
 __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const long long *__restrict__ counts, int V, double P,
                                                                        ChooseBufs b, long long *__restrict__ out) {
-    __shared__ unsigned h[DIRECT ? kBins : 256];
-    __shared__ unsigned long long m[DIRECT ? kWideBins : 256];
+    __shared__ unsigned h[DIRECT ? kBins : kDigitBins];
+    __shared__ unsigned long long m[kDigitBins > kWideBins ? kDigitBins : kWideBins];
     __shared__ unsigned pn[kSortWaves];
     __shared__ unsigned long long pm[kSortWaves];
-    __shared__ int s_bin;
-    __shared__ unsigned s_n;
-    __shared__ unsigned long long s_m, s_total;
+    __shared__ int s_bin, s_last;
+    __shared__ unsigned s_n, s_ids;
+    __shared__ unsigned long long s_m, s_mass, s_total, s_ones, s_zeros;
     constexpr int kPer = (kBins + kRankSortThreads - 1) / kRankSortThreads;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     if constexpr (DIRECT) bin_counts(counts, V, h, m);
     // bins from the highest down
     unsigned vn[kPer], n = 0;
@@ -376,7 +407,10 @@ __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const lon
     unsigned long long upto_m = mass;
     block_scan2(upto_n, upto_m, pn, pm);
     if (tid == kRankSortThreads - 1) s_total = upto_m;
-    if (tid == 0) s_bin = -1;
+    if (tid == 0) {
+        s_bin = -1;
+        s_ones = s_zeros = 0ull;
+    }
     __syncthreads();
     const unsigned long long total = s_total;
     // one fp64 product, then its ceiling; never above the total (beyond 2^53 tokens the product of P = 1
@@ -384,64 +418,143 @@ __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const lon
     const unsigned long long want = (unsigned long long)ceil(P * (double)(long long)total);
     const unsigned long long target = want > total ? total : want;
     // the first bin, from above, that holds ids and with which the mass reaches the target (k >= 1: a target of 0 too)
-    unsigned above_n = upto_n - n;
-    unsigned long long above_m = upto_m - mass;
+    auto reaches = [&](unsigned ids, unsigned long long ids_mass, unsigned above_n, unsigned long long above_m) {
+        return ids != 0u && above_m + ids_mass >= target && (above_m < target || above_n == 0u);
+    };
+    auto found = [&](int bin, unsigned ids, unsigned long long ids_mass, unsigned above_n, unsigned long long above_m) {
+        s_bin = bin;
+        s_ids = ids;
+        s_mass = ids_mass;
+        s_n = above_n;
+        s_m = above_m;
+    };
+    {
+        unsigned above_n = upto_n - n;
+        unsigned long long above_m = upto_m - mass;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        if (vn[i] != 0u && above_m + vm[i] >= target && (above_m < target || above_n == 0u)) {
-            s_bin = kBins - 1 - (kPer * tid + i);
-            s_n = above_n;
-            s_m = above_m;
+        for (int i = 0; i < kPer; ++i) {
+            if (reaches(vn[i], vm[i], above_n, above_m)) found(kBins - 1 - (kPer * tid + i), vn[i], vm[i], above_n, above_m);
+            above_n += vn[i];
+            above_m += vm[i];
         }
-        above_n += vn[i];
-        above_m += vm[i];
     }
     __syncthreads();
     const int bin = s_bin;
     if (bin < 0) {      // no bin reaches it: counts below zero, or a mass of 2^63 and more
-        if (tid < 3) out[tid] = tid == 2 ? (long long)total : 0;
+        if (blockIdx.x == 0 && tid < 3) out[tid] = tid == 2 ? (long long)total : 0;
         return;
     }
-    unsigned before_n = s_n;
-    unsigned long long before_m = s_m, T = (unsigned)bin;
+    if (!DIRECT && bin < kBinExact && blockIdx.x != 0) return;
+    unsigned before_n = s_n, ids = s_ids;
+    unsigned long long before_m = s_m, ids_mass = s_mass, T = (unsigned)bin;
     if (bin >= kBinExact) {
-        // several values share the bin: the value at which the target is reached, up to eight bits at a time, from the
-        // counts that agree with it so far
+        // several values share the bin: the value at which the target is reached, digit by digit
         T = bin_prefix(bin);
-        for (int left = bin_shift(bin); left > 0;) {
-            const int bits = left < 8 ? left : 8;
-            left -= bits;
-            __syncthreads();
-            if (tid < 256) {
-                h[tid] = 0u;
-                m[tid] = 0ull;
+        int left = bin_shift(bin), nbits = left < kDigitBits ? left : kDigitBits;
+        __syncthreads();                // (h and m are read, s_* too)
+        auto clear = [&]() {
+            for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
+                h[i] = 0u;
+                m[i] = 0ull;
             }
             __syncthreads();
-            for (int x = tid; x < V; x += kRankSortThreads) {
-                const unsigned long long c = (unsigned long long)counts[x];
-                if ((c >> (left + bits)) == T) {
-                    const unsigned d = (unsigned)(c >> left) & ((1u << bits) - 1u);
-                    atomicAdd(&h[d], 1u);
-                    atomicAdd(&m[d], c);
+        };
+        clear();
+        {
+            unsigned long long ones = 0, zeros = 0;
+            for (unsigned base = blockIdx.x * kRankSortThreads; base < (unsigned)V; base += gridDim.x * kRankSortThreads) {
+                const unsigned x = base + tid;
+                const unsigned long long c = x < (unsigned)V ? (unsigned long long)counts[x] : 0ull;
+                const bool in = (c >> left) == T;      // (zero past the end: T > 0)
+                wave_tally_mass(h, m, 0, (int)((c >> (left - nbits)) & low_bits(nbits)), in, c);
+                ones |= in ? c & low_bits(left) : 0ull;
+                zeros |= in ? ~c & low_bits(left) : 0ull;
+            }
+            if (__ballot((ones | zeros) != 0ull) != 0ull) {
+                ones = wave_or_u64(ones);
+                zeros = wave_or_u64(zeros);
+                if (lane == 0) {
+                    atomicOr(&s_ones, ones);
+                    atomicOr(&s_zeros, zeros);
                 }
             }
             __syncthreads();
-            const unsigned dn = tid < 256 ? h[255 - tid] : 0u;
-            const unsigned long long dm = tid < 256 ? m[255 - tid] : 0ull;
-            unsigned un = dn;
-            unsigned long long um = dm;
-            block_scan2(un, um, pn, pm);
-            const unsigned an = before_n + un - dn;
-            const unsigned long long am = before_m + um - dm;
-            if (dn != 0u && am + dm >= target && (am < target || an == 0u)) {
-                s_bin = 255 - tid;
-                s_n = an;
-                s_m = am;
+        }
+        if constexpr (!DIRECT) {
+            for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
+                if (h[i] != 0u) {
+                    atomicAdd(&b.digits[i], h[i]);
+                    atomicAdd(&b.digit_mass[i], m[i]);
+                }
+            }
+            if (tid == 0 && (s_ones | s_zeros) != 0ull) {
+                atomicOr(&b.bits[0], s_ones);
+                atomicOr(&b.bits[1], s_zeros);
+            }
+            wait_stores_done();      // this wave's atomics have been performed
+            __syncthreads();
+            if (tid == 0) s_last = __hip_atomic_fetch_add(b.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+            __syncthreads();
+            if (!s_last) return;
+            // the last workgroup goes on with everybody's digits
+            for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
+                h[i] = __hip_atomic_load(&b.digits[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                m[i] = acquire_u64(&b.digit_mass[i]);
+            }
+            if (tid == 0) {
+                s_ones = acquire_u64(&b.bits[0]);
+                s_zeros = acquire_u64(&b.bits[1]);
             }
             __syncthreads();
-            T = (T << bits) | (unsigned)s_bin;
+        }
+        const unsigned long long ones = s_ones, zeros = s_zeros;
+        // Appends the digit at which the target is reached, of the ids in h and m.
+        static_assert(kDigitBins == 2 * kRankSortThreads, "two digits per thread");
+        auto find_digit = [&]() {
+            const int d = kDigitBins - 1 - 2 * tid;      // and the one below
+            const unsigned n0 = h[d], n1 = h[d - 1];
+            const unsigned long long m0 = m[d], m1 = m[d - 1];
+            unsigned un = n0 + n1;
+            unsigned long long um = m0 + m1;
+            if (tid == 0) found(0, 0u, 0ull, before_n, before_m);      // (found by some thread unless the mass wraps around)
+            block_scan2(un, um, pn, pm);
+            const unsigned above_n = before_n + un - n0 - n1;
+            const unsigned long long above_m = before_m + um - m0 - m1;
+            if (reaches(n0, m0, above_n, above_m)) found(d, n0, m0, above_n, above_m);
+            if (reaches(n1, m1, above_n + n0, above_m + m0)) found(d - 1, n1, m1, above_n + n0, above_m + m0);
+            __syncthreads();
+            T = (T << nbits) | (unsigned)s_bin;
+            left -= nbits;
             before_n = s_n;
             before_m = s_m;
+            ids = s_ids;
+            ids_mass = s_mass;
+            __syncthreads();
+        };
+        find_digit();
+        while (left > 0) {
+            if (ids == 1u) {      // its mass is its count
+                T = ids_mass;
+                break;
+            }
+            left = skip_common_bits(T, left, ones, zeros);
+            if (left == 0) break;
+            nbits = left < kDigitBits ? left : kDigitBits;
+            clear();
+            constexpr int kInFlight = 8;
+            for (unsigned x0 = 0; x0 < (unsigned)V; x0 += kInFlight * kRankSortThreads) {
+                unsigned long long cx[kInFlight];
+#pragma unroll
+                for (int u = 0; u < kInFlight; ++u) {
+                    const unsigned x = x0 + u * kRankSortThreads + tid;
+                    cx[u] = x < (unsigned)V ? (unsigned long long)counts[x] : 0ull;
+                }
+#pragma unroll
+                for (int u = 0; u < kInFlight; ++u)
+                    wave_tally_mass(h, m, 0, (int)((cx[u] >> (left - nbits)) & low_bits(nbits)), (cx[u] >> left) == T, cx[u]);
+            }
+            __syncthreads();
+            find_digit();
         }
     }
     if (tid == 0) {
@@ -497,7 +610,11 @@ void launch_choose_k(const long long *counts, int V, int mode, double P, long lo
     const int nblk = (V + kRankSortThreads - 1) / kRankSortThreads;
     ChooseBufs b;
     b.mass = static_cast<unsigned long long *>(scratch);
-    b.hist = reinterpret_cast<unsigned *>(b.mass + kWideBins);
+    b.digit_mass = b.mass + kWideBins;
+    b.bits = b.digit_mass + kDigitBins;
+    b.hist = reinterpret_cast<unsigned *>(b.bits + 2);
+    b.digits = b.hist + kBins;
+    b.done = b.digits + kDigitBins;
     if (mode == 0 && V <= kChooseDirectMaxV) {
         hipLaunchKernelGGL(choose_mass_kernel<true>, dim3(1), dim3(kRankSortThreads), 0, st, counts, V, P, b, out);
         return;
@@ -507,9 +624,11 @@ void launch_choose_k(const long long *counts, int V, int mode, double P, long lo
         hipLaunchKernelGGL(choose_min_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, V, f_min, out);
         return;
     }
-    hipLaunchKernelGGL(choose_zero_kernel, dim3(1), dim3(kRankSortThreads), 0, st, b);
+    hipLaunchKernelGGL(choose_zero_kernel, dim3((kChooseZeroWords + kRankSortThreads - 1) / kRankSortThreads),
+                       dim3(kRankSortThreads), 0, st, b);
     hipLaunchKernelGGL(choose_hist_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, V, b);
-    hipLaunchKernelGGL(choose_mass_kernel<false>, dim3(1), dim3(kRankSortThreads), 0, st, counts, V, P, b, out);
+    // (every workgroup walks the bins, so no more of them than a division needs)
+    hipLaunchKernelGGL(choose_mass_kernel<false>, dim3(nblk < kChooseMaxBlocks ? nblk : kChooseMaxBlocks), dim3(kRankSortThreads), 0, st, counts, V, P, b, out);
 }
 
 }  // namespace vt

@@ -113,3 +113,15 @@ def test_selection_of_large_counts(kind, V):
     for row, (a, _) in zip(both, vt.build_trimmed_heads(torch.from_numpy(both).cuda(), None, [V // 3 + 1, V // 2 + 1])):
         k = a.numel()
         assert np.array_equal(a.cpu().numpy(), np.sort(np.lexsort((np.arange(V), -row))[:k]))
+
+
+# The same counts' choice of k: the bin in which the mass reaches the target is divided further
+@pytest.mark.parametrize("V", [5, 1024, 4096, 4097, 30011, 128256])
+@pytest.mark.parametrize("kind", ["close together", "few values", "mixed", "around 2^17", "equal", "all bits"])
+def test_choice_of_k_among_large_counts(kind, V):
+    c = np.asarray(_large_counts(kind, V, np.random.default_rng(V)), dtype=np.int64)
+    # keep the total below 2^53, where the oracle's ceil(P * total) is exact
+    c >>= max(0, int(c.astype(np.float64).sum()).bit_length() - 53)
+    dc = torch.from_numpy(c).cuda()
+    for P in (0.0, 1e-9, 1e-4, 0.25, 0.6, 0.9, 0.999, 1.0):
+        assert vt.choose_k(dc, top_p=P) == oracle.choose_k_top_p(c, P), P
