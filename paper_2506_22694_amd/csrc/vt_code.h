@@ -4,7 +4,7 @@
 // 128256 below 2048), and those few spread over many powers of two.  A code keeps small counts as they are and of larger
 // ones the highest bits, like a floating-point number, so that one histogram or a few digits cover every int64.
 #pragma once
-#include <hip/hip_runtime.h>
+#include "vt_device.h"
 
 namespace vt {
 
@@ -35,9 +35,11 @@ __device__ __forceinline__ unsigned long long low_bits(int n) { return (1ull << 
 
 // OR over the wave
 __device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v |= __shfl_xor(v, o);
-    return v;
+    struct Or {
+        __device__ __forceinline__ unsigned operator()(unsigned a, unsigned b) const { return a | b; }
+    };
+    const unsigned lo = wave_allreduce_u32((unsigned)v, Or{}), hi = wave_allreduce_u32((unsigned)(v >> 32), Or{});
+    return ((unsigned long long)hi << 32) | lo;
 }
 
 // h[d] += 1 for every lane with `in` (all lanes call): the lanes that share the first one's digit are added at once --

@@ -7,7 +7,11 @@
 // rsort_*: stable LSD radix sort over the whole device of (code, id) pairs, 8 bits per pass.  The code (vt_code.h) is
 //   the count itself below 2^19 and its 19 highest bits with their exponent above -- 24 bits, three passes for any
 //   int64.  The ids start ascending and every pass is stable, so equal codes stay in ascending-id order; where counts
-//   of 2^19 and more share a code (a handful of ids, if any) the last kernel orders them by counting.
+//   of 2^19 and more share a code (a handful of ids, if any) the last kernel orders the run: up to 16 ids by counting in
+//   each id's thread, up to 256 in a wave, up to 1024 in a workgroup, longer ones by radix passes of one workgroup (time
+//   grows with the run and not with its square).
+//   Where all counts of 2^19 and more agree above their 23 low bits (and have bits there) their code is those bits
+//   instead, which leaves out nothing: every kernel derives that from what the first one found.
 //   One workgroup per 1024 consecutive elements; a wave takes 64 consecutive elements, lanes with
 //   equal digits find each other with nine ballots and rank themselves by population count, so
 //   "earlier in the input" is (workgroup, wave, lane) order and no per-thread histogram is needed.
@@ -18,7 +22,10 @@
 //     rsort_out      the ids in order
 //   Eight launches in a fixed sequence; nothing is read back.  A pass whose digit is the same for every key moves
 //   nothing and is skipped: each kernel derives that, and which buffer holds the data, from the digit totals alone.
-//   (Eight passes over the bytes of the counts, nineteen launches, took 72 us at V = 128256 after 10^7 tokens; now 42.)
+//   (Eight passes over the bytes of the counts, nineteen launches, took 72 us at V = 128256 after 10^7 tokens; now 43.)
+//   V = 128256: after 10^11 tokens 47 us (86 with two global atomics per large count, 95 over the bytes); all counts in
+//   2^40 .. 2^40 + 2^20 48 (more than 100000 with every thread walking its run, 74); half of them in 2^35 .. 2^35 + 2^13 52
+//   (75).  Slower than over the bytes: runs of 200 to 400 ids, V = 32000 around 2^19, 95 (441, 55).
 // choose_*: no sort: a histogram over bins of counts (exact below 2048) with the mass of every bin, walked from the
 //   largest counts down to the bin in which the mass reaches ceil(P * total).  With the read-back of k 107 us behind a full
 //   sort, now 31.  Where that bin holds several values all workgroups histogram the next eleven bits of its ids, and the
@@ -43,11 +50,17 @@ constexpr unsigned kRankExact = 1u << 19;      // codes below are counts
 
 struct SortBufs {
     unsigned long long *pairs[2];      // code << 32 | id
-    unsigned *gtot;      // [kPasses][kDigits] digit totals over all elements
-    // what the codes of counts >= kRankExact leave out: the bits set in any of them, and those clear in any
-    unsigned long long *rest;
+    unsigned *gtot;      // [2][kPasses][kDigits] digit totals over all elements, and what is added for the codes of low bits
+    // of the counts >= kRankExact: the bits that their codes leave out, set in any of them and clear in any, and the same of
+    // the bits above the low ones
+    unsigned long long *rest;      // [4]
     unsigned *hist;      // [nblk][kDigits] per-workgroup digit counts of the current pass, descending digit first
+    unsigned *hist_low;  // ... and of the first pass with codes of low bits
 };
+constexpr int kTotals = 2 * kPasses * kDigits;
+constexpr int kLowBits = 23;
+// the code of low bits of a count >= kRankExact, above all smaller counts' codes
+__device__ __forceinline__ unsigned low_code(unsigned long long c) { return (1u << kLowBits) | ((unsigned)c & ((1u << kLowBits) - 1u)); }
 
 // lanes of the wave whose `dgt` (0..256, 256 = not an element) equals this lane's
 __device__ __forceinline__ unsigned long long match_digit9(int dgt) {
@@ -78,26 +91,42 @@ __device__ __forceinline__ int source_buffer(const unsigned *__restrict__ gtot, 
     return moved & 1;
 }
 
-// Every later kernel copies the digit totals (8 KiB) into LDS first: pass_active / source_buffer read them
-// many times over.
-template <int T>
-__device__ __forceinline__ void stage_totals(const unsigned *__restrict__ gtot, unsigned *gs) {
-    for (int i = threadIdx.x; i < kPasses * kDigits; i += T) gs[i] = gtot[i];
+// Every later kernel copies the digit totals (3 KiB) into LDS first: pass_active / source_buffer read them
+// many times over.  Returns whether the codes of counts >= kRankExact are their low bits: the usual ones leave out bits that
+// differ, and all those counts agree above the low bits, in bits that are not all zero (smaller counts share their codes too
+// seldom for the counts to be read again in every pass).
+__device__ __forceinline__ bool stage_totals(const SortBufs &b, unsigned *gs) {
+    const unsigned long long above = b.rest[2];
+    const bool low = above != 0ull && (above & b.rest[3]) == 0ull && (b.rest[0] & b.rest[1]) != 0ull;      // (uniform)
+    if (threadIdx.x < kPasses * kDigits) {
+        unsigned t = b.gtot[threadIdx.x];      // (requested with the flags)
+        if (low) t += b.gtot[kPasses * kDigits + threadIdx.x];
+        gs[threadIdx.x] = t;
+    }
     __syncthreads();
+    return low;
+}
+static_assert(kPasses * kDigits <= kRankSortThreads, "one total per thread");
+// What a pass sorts the element of this pair by.
+__device__ __forceinline__ unsigned sort_key(unsigned long long pair, bool low, const long long *__restrict__ counts) {
+    const unsigned code = (unsigned)(pair >> 32);
+    return low && code >= kRankExact ? low_code((unsigned long long)counts[(unsigned)pair]) : code;
 }
 
-__global__ void __launch_bounds__(256) rsort_zero_kernel(unsigned *gtot) {
-    for (int i = threadIdx.x; i < kPasses * kDigits + 4; i += 256) gtot[i] = 0u;      // (and `rest` behind them)
+__global__ void __launch_bounds__(kRankSortThreads) rsort_zero_kernel(unsigned *gtot) {
+    for (int i = threadIdx.x; i < kTotals + 8; i += kRankSortThreads) gtot[i] = 0u;      // (and `rest` behind them)
 }
 
 __global__ void __launch_bounds__(kRankSortThreads) rsort_init_kernel(const long long *__restrict__ counts, int n,
                                                                       SortBufs b) {
-    __shared__ unsigned h[kPasses * kDigits];
+    __shared__ unsigned h[kTotals];
+    __shared__ unsigned long long s_rest[4];
     const int j = blockIdx.x * kRankSortThreads + threadIdx.x;
     const bool in = j < n;
     const unsigned long long c = in ? (unsigned long long)counts[j] : 0ull;
     const unsigned code = count_code<19, 18>(c);
-    for (int i = threadIdx.x; i < kPasses * kDigits; i += kRankSortThreads) h[i] = 0u;
+    for (int i = threadIdx.x; i < kTotals; i += kRankSortThreads) h[i] = 0u;
+    if (threadIdx.x < 4) s_rest[threadIdx.x] = 0ull;
     __syncthreads();
     if (in) b.pairs[0][j] = ((unsigned long long)code << 32) | (unsigned)j;
     // the upper digits are the same in nearly every code (zero): when a whole wave agrees on a digit one lane
@@ -115,26 +144,55 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_init_kernel(const long
             atomicAdd(&h[p * kDigits + dg], 1u);
         }
     }
-    if (code >= kRankExact) {
-        const unsigned long long left_out = c & ((1ull << (63 - __clzll((long long)c) - 18)) - 1ull);
-        atomicOr(&b.rest[0], left_out);
-        atomicOr(&b.rest[1], ~left_out);
+    const bool large = code >= kRankExact;
+    const unsigned long long any_large = __ballot(large);
+    if (any_large != 0ull) {
+        const unsigned long long left_out = large ? c & low_bits(63 - __clzll((long long)c) - 18) : 0ull;
+        const unsigned long long r[4] = {left_out, large ? ~left_out : 0ull, large ? c >> kLowBits : 0ull, large ? ~(c >> kLowBits) : 0ull};
+        if (any_large != live) {      // (a few lanes, as a rule)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (large) atomicOr(&s_rest[q], r[q]);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const unsigned long long v = wave_or_u64(r[q]);
+                if ((threadIdx.x & 63) == 0) atomicOr(&s_rest[q], v);
+            }
+        }
+        const unsigned other = low_code(c);
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            const unsigned from = (code >> (8 * p)) & 255u, to = (other >> (8 * p)) & 255u;
+            if (large && from != to) {
+                atomicAdd(&h[(kPasses + p) * kDigits + from], ~0u);      // (one less; sums wrap around)
+                atomicAdd(&h[(kPasses + p) * kDigits + to], 1u);
+            }
+        }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kPasses * kDigits; i += kRankSortThreads) {
-        if (h[i] != 0u) atomicAdd(&b.gtot[i], h[i]);
+    const int tid = threadIdx.x;
+    if (tid < kPasses * kDigits && h[tid] != 0u) atomicAdd(&b.gtot[tid], h[tid]);
+    if (tid < kDigits) {
+        b.hist[blockIdx.x * kDigits + tid] = h[255 - tid];
+        b.hist_low[blockIdx.x * kDigits + tid] = h[255 - tid] + h[kPasses * kDigits + 255 - tid];
     }
-    if (threadIdx.x < kDigits) b.hist[blockIdx.x * kDigits + threadIdx.x] = h[255 - threadIdx.x];
+    if (s_rest[3] != 0ull) {      // (uniform) there are counts of 2^19 and more
+        if (tid < 4) atomicOr(&b.rest[tid], s_rest[tid]);
+        if (tid < kPasses * kDigits && h[kPasses * kDigits + tid] != 0u) atomicAdd(&b.gtot[kPasses * kDigits + tid], h[kPasses * kDigits + tid]);
+    }
 }
 
-__global__ void __launch_bounds__(kRankSortThreads) rsort_hist_kernel(int n, int p, SortBufs b) {
+__global__ void __launch_bounds__(kRankSortThreads) rsort_hist_kernel(const long long *__restrict__ counts, int n, int p,
+                                                                      SortBufs b) {
     __shared__ unsigned h[kDigits];
     __shared__ unsigned gs[kPasses * kDigits];
-    stage_totals<kRankSortThreads>(b.gtot, gs);
+    const bool low = stage_totals(b, gs);
     if (!pass_active(gs, p, n)) return;
     const int src = source_buffer(gs, p, n);
     const int j = blockIdx.x * kRankSortThreads + threadIdx.x;
-    const unsigned code = j < n ? (unsigned)(b.pairs[src][j] >> 32) : 0u;
+    const unsigned code = j < n ? sort_key(b.pairs[src][j], low, counts) : 0u;
     if (threadIdx.x < kDigits) h[threadIdx.x] = 0u;
     __syncthreads();
     if (j < n) atomicAdd(&h[255 - (int)((code >> (8 * p)) & 255u)], 1u);
@@ -142,14 +200,16 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_hist_kernel(int n, int
     if (threadIdx.x < kDigits) b.hist[blockIdx.x * kDigits + threadIdx.x] = h[threadIdx.x];
 }
 
-__global__ void __launch_bounds__(kRankSortThreads) rsort_scatter_kernel(int n, int p, SortBufs b) {
+__global__ void __launch_bounds__(kRankSortThreads) rsort_scatter_kernel(const long long *__restrict__ counts, int n, int p,
+                                                                         SortBufs b) {
     __shared__ unsigned wcnt[kSortWaves * kDigits];   // [wave][digit]: elements of that digit in earlier waves
     __shared__ unsigned part[4 * kDigits];            // sums over a quarter of the earlier workgroups
     __shared__ unsigned offs[kDigits];                // first output slot of this workgroup's run of each digit
     __shared__ unsigned gs[kPasses * kDigits];
-    stage_totals<kRankSortThreads>(b.gtot, gs);
+    const bool low = stage_totals(b, gs);
     if (!pass_active(gs, p, n)) return;
     const int src = source_buffer(gs, p, n);
+    const unsigned *hist = low && p == 0 ? b.hist_low : b.hist;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int blk = blockIdx.x;
 
@@ -157,6 +217,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_scatter_kernel(int n, 
     const int j = blk * kRankSortThreads + tid;
     const bool in = j < n;
     const unsigned long long pair = in ? b.pairs[src][j] : 0ull;
+    const unsigned key = in ? sort_key(pair, low, counts) : 0u;
     for (int i = tid; i < kSortWaves * kDigits; i += kRankSortThreads) wcnt[i] = 0u;
     // this workgroup's offsets: (elements with an earlier digit anywhere) + (same digit, earlier workgroups)
     {
@@ -164,7 +225,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_scatter_kernel(int n, 
         const int d = tid & 255, q = tid >> 8;
         unsigned before = 0;
         const int b1 = blk * (q + 1) / 4;
-        const unsigned *col = b.hist + d;
+        const unsigned *col = hist + d;
         int x = blk * q / 4;
         for (; x + 16 <= b1; x += 16) {         // sixteen independent loads at a time
             unsigned t[16];
@@ -198,7 +259,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_scatter_kernel(int n, 
     if (tid < kDigits) offs[tid] = my_off;
 
     // ---- ranks inside the workgroup
-    const int dgt = in ? 255 - (int)((pair >> (32 + 8 * p)) & 255ull) : 256;
+    const int dgt = in ? 255 - (int)((key >> (8 * p)) & 255u) : 256;
     const unsigned long long m = match_digit9(dgt);
     const int below = lanes_below(m);
     if (in && below == 0) wcnt[w * kDigits + dgt] = (unsigned)__popcll(m);
@@ -218,32 +279,275 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_scatter_kernel(int n, 
     }
 }
 
-__global__ void __launch_bounds__(256) rsort_out_kernel(const long long *__restrict__ counts, int n, int n_ids, SortBufs b,
-                                                        int *__restrict__ out_ids) {
-    __shared__ unsigned gs[kPasses * kDigits];
-    stage_totals<256>(b.gtot, gs);
-    const unsigned long long *__restrict__ pairs = b.pairs[source_buffer(gs, kPasses, n)];
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= n) return;
-    const unsigned long long pair = pairs[j];
-    const unsigned code = (unsigned)(pair >> 32);
-    const int id = (int)(unsigned)pair;
-    int pos = j;
-    if (code >= kRankExact && (b.rest[0] & b.rest[1]) != 0ull) {      // (none when all of them leave out the same)
-        // counts that share a code: their order among themselves (the run is in ascending-id order)
-        const long long c = counts[id];
-        for (int x = j - 1; x >= 0; --x) {
-            const unsigned long long q = pairs[x];
-            if ((unsigned)(q >> 32) != code) break;
-            if (counts[(int)(unsigned)q] < c) --pos;           // smaller and before: goes behind
+// ---- runs of equal codes whose counts differ (rsort_out)
+constexpr int kShortRun = 16;                        // ordered by counting in every id's thread
+constexpr int kWaveRun = 4 * kWave;                  // ... in a wave of the workgroup that the run starts in
+constexpr int kGroupRun = kRankSortThreads;          // ... in that workgroup; longer: radix passes
+constexpr int kRunPer = 4;                           // elements per thread and step of those
+constexpr int kRunStep = kRunPer * kRankSortThreads, kRunGroups = kRunStep / kWave;
+
+struct RunLds {
+    int starts[kRankSortThreads / kShortRun + 1], long_starts[kRankSortThreads / kShortRun + 1];
+    int n_starts, n_long, n_same;
+    unsigned long long ones, zeros;
+    unsigned base[kDigits];                          // next slot of each digit, descending
+    unsigned part[kRunPer * kDigits];
+    union {
+        unsigned long long wave_count[kSortWaves][kWaveRun];      // run_key
+        unsigned long long count[kGroupRun];
+        unsigned short before[kRunGroups * kDigits]; // elements of a digit in the step's groups of 64 before
+    };
+};
+
+// (count descending, place in the run ascending) as one number: the bits that a run's counts share may go
+__device__ __forceinline__ unsigned long long run_key(long long c, int place) {
+    return ((unsigned long long)c << 10) | (unsigned)(kGroupRun - 1 - place);
+}
+static_assert(kGroupRun == 1 << 10, "ten bits for the place; codes tell 19 bits apart");
+// f(v[x]) for all x < n, eight of them read at a time (every lane the same one: a broadcast).
+template <typename F>
+__device__ __forceinline__ void for_each_key(const unsigned long long *v, int n, F &&f) {
+    int x = 0;
+    for (; x + 8 <= n; x += 8) {
+        unsigned long long t[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t[q] = v[x + q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) f(t[q]);
+    }
+    for (; x < n; ++x) f(v[x]);
+}
+
+// One run [lo, lo + length), longer than kGroupRun, by its counts: LSD passes of this workgroup over the digits in which the
+// counts differ, between the two buffers.  Nobody else touches the run's ids (its codes stay what they are).
+__device__ __forceinline__ void sort_long_run(const long long *__restrict__ counts, const SortBufs &b, int src, unsigned lo,
+                                              unsigned length, int n_ids, int *__restrict__ out_ids, RunLds &s) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (tid == 0) s.ones = s.zeros = 0ull;
+    __syncthreads();
+    unsigned long long ones = 0, zeros = 0;
+    for (unsigned x = tid; x < length; x += kRankSortThreads) {
+        const unsigned long long c = (unsigned long long)counts[(unsigned)b.pairs[src][lo + x]];
+        ones |= c;
+        zeros |= ~c;
+    }
+    ones = wave_or_u64(ones);
+    zeros = wave_or_u64(zeros);
+    if (lane == 0) {
+        atomicOr(&s.ones, ones);
+        atomicOr(&s.zeros, zeros);
+    }
+    __syncthreads();
+    const unsigned long long differ = s.ones & s.zeros;
+    for (int shift = 0; shift < 64; shift += 8) {
+        if (((differ >> shift) & 255ull) == 0ull) continue;      // (uniform)
+        const unsigned long long *from = b.pairs[src] + lo;
+        unsigned long long *to = b.pairs[src ^ 1] + lo;
+        // element x0 + (u 16 + w) 64 + lane of the run, and 255 - its digit (256: past the end)
+        unsigned long long pair[kRunPer];
+        int dgt[kRunPer];
+        auto load_step = [&](unsigned x0) {
+#pragma unroll
+            for (int u = 0; u < kRunPer; ++u) {
+                const unsigned x = x0 + u * kRankSortThreads + tid;
+                pair[u] = x < length ? from[x] : 0ull;
+            }
+#pragma unroll
+            for (int u = 0; u < kRunPer; ++u) {
+                const unsigned x = x0 + u * kRankSortThreads + tid;
+                dgt[u] = x < length ? 255 - (int)(((unsigned long long)counts[(unsigned)pair[u]] >> shift) & 255ull) : 256;
+            }
+        };
+        if (tid < kDigits) s.base[tid] = 0u;
+        __syncthreads();
+        for (unsigned x0 = 0; x0 < length; x0 += kRunStep) {
+            load_step(x0);
+#pragma unroll
+            for (int u = 0; u < kRunPer; ++u) wave_tally(s.base, dgt[u], dgt[u] < kDigits);
         }
-        for (int x = j + 1; x < n; ++x) {
-            const unsigned long long q = pairs[x];
-            if ((unsigned)(q >> 32) != code) break;
-            if (counts[(int)(unsigned)q] > c) ++pos;           // larger and after: goes ahead
+        __syncthreads();
+        // counts of the digits -> first slots: four waves scan, then add what lies in the waves before
+        unsigned mine = 0, inc = 0;
+        if (tid < kDigits) {
+            mine = inc = s.base[tid];
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const unsigned t = __shfl_up(inc, o);
+                if (lane >= o) inc += t;
+            }
+            if (lane == kWave - 1) s.part[w] = inc;
+        }
+        __syncthreads();
+        if (tid < kDigits) {
+            for (int ww = 0; ww < w; ++ww) inc += s.part[ww];
+            s.base[tid] = inc - mine;
+        }
+        for (unsigned x0 = 0; x0 < length; x0 += kRunStep) {
+            load_step(x0);
+            unsigned long long same[kRunPer];
+#pragma unroll
+            for (int u = 0; u < kRunPer; ++u) same[u] = match_digit9(dgt[u]);
+            __syncthreads();            // the step before is done with `before`, `part` and `base`
+            for (int i = tid; i < kRunGroups * kDigits / 2; i += kRankSortThreads) reinterpret_cast<unsigned *>(s.before)[i] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kRunPer; ++u) {
+                if (dgt[u] < kDigits && lanes_below(same[u]) == 0)
+                    s.before[(u * kSortWaves + w) * kDigits + dgt[u]] = (unsigned short)__popcll(same[u]);
+            }
+            __syncthreads();
+            {
+                // thread (digit, quarter u of the groups)
+                const int d = tid & 255, q = tid >> 8;
+                unsigned run = 0;
+#pragma unroll
+                for (int i = 0; i < kSortWaves; ++i) {
+                    unsigned short &x = s.before[(q * kSortWaves + i) * kDigits + d];
+                    const unsigned c = x;
+                    x = (unsigned short)run;
+                    run += c;
+                }
+                s.part[q * kDigits + d] = run;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kRunPer; ++u) {
+                if (dgt[u] < kDigits) {
+                    unsigned pos = s.base[dgt[u]] + s.before[(u * kSortWaves + w) * kDigits + dgt[u]] + (unsigned)lanes_below(same[u]);
+#pragma unroll
+                    for (int q = 0; q < u; ++q) pos += s.part[q * kDigits + dgt[u]];
+                    to[pos] = pair[u];
+                }
+            }
+            __syncthreads();
+            if (tid < kDigits) {
+#pragma unroll
+                for (int q = 0; q < kRunPer; ++q) s.base[tid] += s.part[q * kDigits + tid];
+            }
+        }
+        __syncthreads();                // what was written is read by other waves
+        src ^= 1;
+    }
+    static_assert(kRunPer * kDigits == kRankSortThreads, "a thread per digit and quarter");
+    for (unsigned x = tid; x < length && lo + x < (unsigned)n_ids; x += kRankSortThreads)
+        out_ids[lo + x] = (int)(unsigned)b.pairs[src][lo + x];
+    __syncthreads();
+}
+
+__global__ void __launch_bounds__(kRankSortThreads) rsort_out_kernel(const long long *__restrict__ counts, int n, int n_ids, SortBufs b,
+                                                                     int *__restrict__ out_ids) {
+    __shared__ unsigned gs[kPasses * kDigits];
+    __shared__ RunLds s;
+    const bool low = stage_totals(b, gs);
+    const int src = source_buffer(gs, kPasses, n);
+    const unsigned long long *pairs = b.pairs[src];      // (sort_long_run writes there)
+    const int tid = threadIdx.x;
+    const unsigned j = blockIdx.x * kRankSortThreads + tid;
+    const bool in = j < (unsigned)n;
+    const unsigned long long pair = in ? pairs[j] : 0ull;
+    const int id = (int)(unsigned)pair;
+    if (low || (b.rest[0] & b.rest[1]) == 0ull) {      // (uniform) the codes leave out nothing that differs
+        if (in && j < (unsigned)n_ids) out_ids[j] = id;
+        return;
+    }
+    const unsigned code = (unsigned)(pair >> 32);
+    auto code_of = [&](unsigned x) { return (unsigned)(pairs[x] >> 32); };
+    if (tid == 0) s.n_starts = s.n_long = 0;
+    __syncthreads();
+    if (in) {
+        int before = 0, after = 0;
+        if (code >= kRankExact) {
+            while (before < kShortRun && before < (int)j && code_of(j - 1 - before) == code) ++before;
+            while (after < kShortRun && (unsigned)after + 1 < (unsigned)n - j && code_of(j + 1 + after) == code) ++after;
+        }
+        if (before + after + 1 <= kShortRun) {
+            // the order among themselves (the run is in ascending-id order)
+            unsigned pos = j;
+            if (before + after > 0) {
+                const long long c = counts[id];
+                for (int x = 1; x <= before; ++x) pos -= counts[(unsigned)pairs[j - x]] < c ? 1u : 0u;      // goes behind
+                for (int x = 1; x <= after; ++x) pos += counts[(unsigned)pairs[j + x]] > c ? 1u : 0u;       // goes ahead
+            }
+            if (pos < (unsigned)n_ids) out_ids[pos] = id;
+        } else if (before == 0) {
+            s.starts[atomicAdd(&s.n_starts, 1)] = (int)j;      // (more than kShortRun apart)
         }
     }
-    if (pos < n_ids) out_ids[pos] = id;
+    __syncthreads();
+    const int lane = tid & 63, w = tid >> 6;
+    for (int q = w; q < s.n_starts; q += kSortWaves) {
+        const unsigned lo = (unsigned)s.starts[q];
+        if (lo >= (unsigned)n_ids) continue;      // nobody asks for them
+        const unsigned run_code = code_of(lo);
+        unsigned long long p[kWaveRun / kWave];
+        int length = 0;
+#pragma unroll
+        for (int u = 0; u < kWaveRun / kWave; ++u) p[u] = lo + u * kWave + lane < (unsigned)n ? pairs[lo + u * kWave + lane] : 0ull;
+#pragma unroll
+        for (int u = 0; u < kWaveRun / kWave; ++u) length += __popcll(__ballot((unsigned)(p[u] >> 32) == run_code));
+        if (length == kWaveRun && lo + kWaveRun < (unsigned)n && code_of(lo + kWaveRun) == run_code) {
+            if (lane == 0) s.long_starts[atomicAdd(&s.n_long, 1)] = (int)lo;
+            continue;
+        }
+        unsigned long long c[kWaveRun / kWave];
+#pragma unroll
+        for (int u = 0; u < kWaveRun / kWave; ++u) {
+            const bool mine = u * kWave + lane < length;
+            c[u] = mine ? run_key(counts[(unsigned)p[u]], u * kWave + lane) : 0ull;
+            if (mine) s.wave_count[w][u * kWave + lane] = c[u];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        unsigned pos[kWaveRun / kWave] = {};
+        for_each_key(s.wave_count[w], length, [&](unsigned long long other) {
+#pragma unroll
+            for (int u = 0; u < kWaveRun / kWave; ++u) pos[u] += other > c[u] ? 1u : 0u;
+        });
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < kWaveRun / kWave; ++u) {
+            if (u * kWave + lane < length && lo + pos[u] < (unsigned)n_ids) out_ids[lo + pos[u]] = (int)(unsigned)p[u];
+        }
+    }
+    __syncthreads();
+    const int n_long = s.n_long;
+    for (int q = 0; q < n_long; ++q) {
+        const unsigned lo = (unsigned)s.long_starts[q];
+        const unsigned run_code = code_of(lo);
+        // the run's end: element a has the code, element e (if there is one) has not
+        unsigned a = lo, e = (unsigned)n;
+        while (e - a > 1) {
+            const unsigned step = (e - a + kRankSortThreads - 1) / kRankSortThreads;
+            const unsigned off = (unsigned)tid * step;
+            const bool same = off < e - a && code_of(a + off) == run_code;
+            const int c = __popcll(__ballot(same));
+            __syncthreads();
+            if (tid == 0) s.n_same = 0;
+            __syncthreads();
+            if (lane == 0 && c != 0) atomicAdd(&s.n_same, c);
+            __syncthreads();
+            const unsigned n_same = (unsigned)s.n_same;      // (the first ones: a itself, and on)
+            if (n_same * step < e - a) e = a + n_same * step;
+            a += (n_same - 1) * step;
+        }
+        const unsigned length = e - lo;
+        if (length > kGroupRun) {
+            sort_long_run(counts, b, src, lo, length, n_ids, out_ids, s);
+            continue;
+        }
+        const bool mine = (unsigned)tid < length;
+        const int my_id = mine ? (int)(unsigned)pairs[lo + tid] : 0;
+        const unsigned long long c = mine ? run_key(counts[my_id], tid) : 0ull;
+        __syncthreads();
+        s.count[tid] = c;
+        __syncthreads();
+        if (mine) {
+            unsigned pos = lo;
+            for_each_key(s.count, (int)length, [&](unsigned long long other) { pos += other > c ? 1u : 0u; });
+            if (pos < (unsigned)n_ids) out_ids[pos] = my_id;
+        }
+    }
 }
 
 }  // namespace
@@ -314,11 +618,14 @@ __device__ __forceinline__ void wave_tally_mass(unsigned *h, unsigned long long 
         atomicAdd(&h[d], 1u);
         if (d >= exact) atomicAdd(&m[d - exact], c);
     }
-    unsigned long long sum = same ? c : 0ull;
-    if (first >= exact && __popcll(group) > 1) sum = (unsigned long long)wave_sum_i64((long long)sum);
-    if (lane_id() == leader) {
-        atomicAdd(&h[first], (unsigned)__popcll(group));
-        if (first >= exact) atomicAdd(&m[first - exact], sum);
+    if (lane_id() == leader) atomicAdd(&h[first], (unsigned)__popcll(group));
+    if (first >= exact) {
+        if (__popcll(group) <= 8) {      // (few lanes queue faster than a sum over the wave is made)
+            if (same) atomicAdd(&m[first - exact], c);
+        } else {
+            const long long sum = wave_sum_i64(same ? (long long)c : 0ll);
+            if (lane_id() == leader) atomicAdd(&m[first - exact], (unsigned long long)sum);
+        }
     }
 }
 
@@ -588,15 +895,16 @@ void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_id
     b.pairs[0] = reinterpret_cast<unsigned long long *>(p);
     b.pairs[1] = reinterpret_cast<unsigned long long *>(p + kb);
     b.gtot = reinterpret_cast<unsigned *>(p + 2 * kb);
-    b.rest = reinterpret_cast<unsigned long long *>(b.gtot + kPasses * kDigits);
-    b.hist = reinterpret_cast<unsigned *>(p + 2 * kb + round256((kPasses * kDigits + 4) * 4));
-    hipLaunchKernelGGL(rsort_zero_kernel, dim3(1), dim3(256), 0, st, b.gtot);
+    b.rest = reinterpret_cast<unsigned long long *>(b.gtot + kTotals);
+    b.hist = reinterpret_cast<unsigned *>(p + 2 * kb + round256((kTotals + 8) * 4));
+    b.hist_low = b.hist + (size_t)nblk * kDigits;
+    hipLaunchKernelGGL(rsort_zero_kernel, dim3(1), dim3(kRankSortThreads), 0, st, b.gtot);
     hipLaunchKernelGGL(rsort_init_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, b);
     for (int pass = 0; pass < kPasses; ++pass) {
-        if (pass > 0) hipLaunchKernelGGL(rsort_hist_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, n, pass, b);
-        hipLaunchKernelGGL(rsort_scatter_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, n, pass, b);
+        if (pass > 0) hipLaunchKernelGGL(rsort_hist_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, pass, b);
+        hipLaunchKernelGGL(rsort_scatter_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, pass, b);
     }
-    hipLaunchKernelGGL(rsort_out_kernel, dim3((n + 255) / 256), dim3(256), 0, st, counts, n, n_ids, b, out_ids);
+    hipLaunchKernelGGL(rsort_out_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
 }
 
 // (likewise: ids and counts in order, sums per workgroup, and the sort's buffers)
@@ -610,11 +918,11 @@ void launch_choose_k(const long long *counts, int V, int mode, double P, long lo
     const int nblk = (V + kRankSortThreads - 1) / kRankSortThreads;
     ChooseBufs b;
     b.mass = static_cast<unsigned long long *>(scratch);
-    b.digit_mass = b.mass + kWideBins;
-    b.bits = b.digit_mass + kDigitBins;
-    b.hist = reinterpret_cast<unsigned *>(b.bits + 2);
-    b.digits = b.hist + kBins;
-    b.done = b.digits + kDigitBins;
+    b.hist = reinterpret_cast<unsigned *>(b.mass + kWideBins);      // (every array on whole cache lines)
+    b.digit_mass = reinterpret_cast<unsigned long long *>(b.hist + kBins);
+    b.digits = reinterpret_cast<unsigned *>(b.digit_mass + kDigitBins);
+    b.bits = reinterpret_cast<unsigned long long *>(b.digits + kDigitBins);
+    b.done = reinterpret_cast<unsigned *>(b.bits + 2);
     if (mode == 0 && V <= kChooseDirectMaxV) {
         hipLaunchKernelGGL(choose_mass_kernel<true>, dim3(1), dim3(kRankSortThreads), 0, st, counts, V, P, b, out);
         return;

@@ -95,6 +95,8 @@ def _large_counts(kind, V, rng):
         return rng.integers(0, 2**63 - 1, size=V, dtype=np.int64) >> rng.integers(0, 63, size=V)
     if kind == "equal":
         return np.full(V, (1 << 45) + 12345)
+    if kind == "mixed, one bit more":      # large counts that agree above 24 low bits, not above 23
+        return np.where(rng.random(V) < 0.5, rng.integers(0, 5000, size=V), (1 << 35) + rng.integers(0, 2, size=V) * (1 << 23) + rng.integers(0, 50, size=V))
     raise ValueError(kind)
 
 
@@ -125,3 +127,27 @@ def test_choice_of_k_among_large_counts(kind, V):
     dc = torch.from_numpy(c).cuda()
     for P in (0.0, 1e-9, 1e-4, 0.25, 0.6, 0.9, 0.999, 1.0):
         assert vt.choose_k(dc, top_p=P) == oracle.choose_k_top_p(c, P), P
+
+
+# Rank order: counts of 2^19 and more that share a code, in runs around the lengths that are ordered differently (16, 256, 1024)
+def _counts_in_runs(lengths, V, rng):
+    c = rng.integers(0, 1000, size=V)
+    at = 0
+    for q, n in enumerate(lengths):                  # run q: one code (19 highest bits), 14 open bits
+        n = min(n, V - at)
+        c[at:at + n] = (1 << 33) + (q << 24) + rng.integers(0, 1 << 14, size=n)
+        at += n
+    return rng.permutation(c)
+
+
+@pytest.mark.parametrize("V", [5, 1024, 1025, 30011, 128256])
+@pytest.mark.parametrize("kind", ["close together", "few values", "mixed", "around 2^17", "all bits", "equal", "mixed, one bit more", "short runs", "medium runs", "long runs"])
+def test_rank_order_of_large_counts(kind, V):
+    rng = np.random.default_rng(V)
+    runs = {"short runs": [1, 2, 15, 16, 17, 18, 33, 64, 65] * 30, "medium runs": [255, 256, 257, 258, 1023, 1024, 1025, 500, 40] * 3, "long runs": [1025, 4095, 4096, 4097, 9000, 1]}
+    c = np.asarray(_counts_in_runs(runs[kind], V, rng) if kind in runs else _large_counts(kind, V, rng), dtype=np.int64)
+    dc = torch.from_numpy(c).cuda()
+    order = np.lexsort((np.arange(V), -c))
+    for k in sorted({1, V // 100 + 1, V // 3 + 1, V}):
+        a, _ = vt.build_trimmed_head(dc, None, k, order="rank")
+        assert np.array_equal(a.cpu().numpy(), order[:k]), k
