@@ -15,7 +15,8 @@ constexpr int kHistUnroll = 6;            // 16-byte id vectors in flight per th
 
 int hist_num_ranges(int V);
 int hist_num_chunks(int64_t n_ids, int V);
-// partial: [chunks, V rounded up to a multiple of four] bytes (the workspace holds twice that)
+size_t hist_scratch_bytes(int V, int64_t n_ids);
+// partial: hist_scratch_bytes(V, n_ids), no initialisation
 hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V, long long *counts,
                          unsigned long long *n_invalid, void *partial, hipStream_t st);
 

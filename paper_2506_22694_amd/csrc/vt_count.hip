@@ -4,8 +4,9 @@
 // are 16 bits wide, two per LDS word, the vocabulary is cut into ranges of 65536 bins (128 KiB of
 // LDS; two ranges for V = 128256) and the id stream into chunks.  Workgroup (chunk, range) reads
 // its chunk with 16-byte loads, counts the ids that fall into its range with LDS atomics (no
-// global atomic sees the Zipf-hot ids more than once per 32768 occurrences), and writes the low eight bits of
-// its private histogram to scratch (what a bin has beyond them, in a few dozen bins, goes to the result by atomics).
+// global atomic sees the Zipf-hot ids more than once per 32768 occurrences), and writes its private histogram to scratch:
+// the low eight bits of every bin, and the upper eight of those groups of 256 ids that have any, which a flag tells (a few
+// dozen ids of a chunk exceed 255, next to each other where ids follow the frequency).
 // A second kernel sums the chunk histograms into the caller's int64 counters.  Ids outside [0, V) are skipped and tallied.
 // What bounds it at 10^8 ids is the reading of the stream once per range: 106 us, of which 100 remain without any LDS
 // atomic and 47 without the loads; a second batch in flight per thread makes it slower (109; 64-bit ids 214 against
@@ -37,11 +38,30 @@ int hist_num_chunks(int64_t n_ids, int V) {
     return (int)c;
 }
 
+// What lies between the two kernels: rows of the low bytes and of the upper bytes of the chunks' bins, and a flag per group of
+// 256 ids and chunk: whether the group's upper bytes are there.
+constexpr int kGroupIds = 256;
+struct HistScratch {
+    size_t pitch, groups;                          // bytes per row: V rounded up to four; groups of 256 ids
+    unsigned char *low, *high, *flags;             // [nchunks][pitch] twice, [nchunks][groups]
+    __host__ __device__ HistScratch(unsigned char *p, int V, int nchunks) {
+        pitch = ((size_t)V + 3) & ~(size_t)3;
+        groups = ((size_t)V + kGroupIds - 1) / kGroupIds;
+        low = p;
+        high = low + pitch * nchunks;
+        flags = high + pitch * nchunks;
+    }
+};
+size_t hist_scratch_bytes(int V, int64_t n_ids) {
+    const HistScratch sc(nullptr, V, hist_num_chunks(n_ids, V));
+    return (size_t)hist_num_chunks(n_ids, V) * (2 * sc.pitch + sc.groups);
+}
+
 // `head` ids (fewer than one 16-byte vector) precede the first 16-byte aligned id.
 template <bool IDS64>
 __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *__restrict__ ids_v, long long n_ids,
                                                                     int head, int V, int nchunks,
-                                                                    unsigned char *__restrict__ partial,
+                                                                    unsigned char *partial,
                                                                     unsigned long long *__restrict__ counts,
                                                                     unsigned long long *__restrict__ n_invalid) {
     extern __shared__ __align__(16) unsigned words[];     // two 16-bit bins per word
@@ -191,31 +211,43 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
         }
     }
     __syncthreads();
-    // A row of the scratch holds eight bits per id: what a bin has beyond them goes to the result counter (a few dozen
-    // ids of a chunk), and the rows are written and read back at half the size of the bins.
-    unsigned char *dst = partial + (size_t)chunk * (size_t)((V + 3) & ~3) + lo;
-    auto low_bytes = [&](unsigned w0, unsigned w1, int bin) {      // four bins: two words
-        if (((w0 | w1) & 0xFF00FF00u) != 0u) {
-            const unsigned c4[4] = {w0 & 0xFFFFu, w0 >> 16, w1 & 0xFFFFu, w1 >> 16};
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (c4[e] > 255u) atomicAdd(&counts[lo + bin + e], (unsigned long long)(c4[e] & ~255u));
-        }
-        return __builtin_amdgcn_perm(w1, w0, 0x06040200u);      // bytes 0 and 2 of either word
-    };
+    // A row of the scratch holds eight bits per id, half the size of the bins; rows of the upper eight bits lie behind them
+    // and are written, and read back, for the groups of 256 ids alone that have any.  (Those bits added to the result by
+    // atomics instead: all chunks to the same few counters, one behind the other where hot ids share a cache line -- Zipf ids
+    // in order of frequency, V = 128256, 10^7 45.9 us against 26.4, V = 32000, 10^8 131 / 94; in random order 24.7 / 25.0.)
+    const HistScratch sc(partial, V, nchunks);
+    unsigned char *dst = sc.low + (size_t)chunk * sc.pitch + lo, *dst_hi = sc.high + (size_t)chunk * sc.pitch + lo;
+    unsigned char *flags = sc.flags + (size_t)chunk * sc.groups + lo / kGroupIds;
+    auto low_bytes = [](unsigned w0, unsigned w1) { return __builtin_amdgcn_perm(w1, w0, 0x06040200u); };      // of two words, four bins
+    auto high_bytes = [](unsigned w0, unsigned w1) { return __builtin_amdgcn_perm(w1, w0, 0x07050301u); };
     if ((V & 15) == 0) {
-        for (int b = 16 * threadIdx.x; b < nb; b += 16 * kHistThreads) {
+        for (int b = 16 * threadIdx.x; b < nb; b += 16 * kHistThreads) {      // sixteen lanes hold a group
             const u32x4 x0 = *reinterpret_cast<const u32x4 *>(words + b / 2), x1 = *reinterpret_cast<const u32x4 *>(words + b / 2 + 4);
+            const unsigned any = (x0.x | x0.y | x0.z | x0.w | x1.x | x1.y | x1.z | x1.w) & 0xFF00FF00u;
+            const bool flagged = (__ballot(any != 0u) >> (threadIdx.x & 48) & 0xFFFFull) != 0ull;
             u32x4 y;
-            y.x = low_bytes(x0.x, x0.y, b);
-            y.y = low_bytes(x0.z, x0.w, b + 4);
-            y.z = low_bytes(x1.x, x1.y, b + 8);
-            y.w = low_bytes(x1.z, x1.w, b + 12);
+            y.x = low_bytes(x0.x, x0.y);
+            y.y = low_bytes(x0.z, x0.w);
+            y.z = low_bytes(x1.x, x1.y);
+            y.w = low_bytes(x1.z, x1.w);
             *reinterpret_cast<u32x4 *>(dst + b) = y;
+            if (flagged) {
+                y.x = high_bytes(x0.x, x0.y);
+                y.y = high_bytes(x0.z, x0.w);
+                y.z = high_bytes(x1.x, x1.y);
+                y.w = high_bytes(x1.z, x1.w);
+                *reinterpret_cast<u32x4 *>(dst_hi + b) = y;
+            }
+            if ((threadIdx.x & 15) == 0) flags[b / kGroupIds] = flagged ? 1 : 0;
         }
     } else {
-        for (int b = 4 * threadIdx.x; b < nb; b += 4 * kHistThreads)
-            *reinterpret_cast<unsigned *>(dst + b) = low_bytes(words[b / 2], words[b / 2 + 1], b);
+        for (int b = 4 * threadIdx.x; b < nb; b += 4 * kHistThreads) {      // a wave holds a group
+            const unsigned w0 = words[b / 2], w1 = words[b / 2 + 1];
+            const bool flagged = __ballot(((w0 | w1) & 0xFF00FF00u) != 0u) != 0ull;
+            *reinterpret_cast<unsigned *>(dst + b) = low_bytes(w0, w1);
+            if (flagged) *reinterpret_cast<unsigned *>(dst_hi + b) = high_bytes(w0, w1);
+            if ((threadIdx.x & 63) == 0) flags[b / kGroupIds] = flagged ? 1 : 0;
+        }
     }
     // every range-workgroup of a chunk sees the same invalid ids: only range 0 reports them
     if (n_invalid != nullptr && range == 0) {
@@ -224,69 +256,100 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
     }
 }
 
-// A workgroup sums 256 neighbouring ids (a 4-byte word per lane) over the chunks: wave g takes the chunks g, g + 8, ..,
-// sixteen loads in flight; the words' bytes are added as pairs of 16 bits (at most 256 chunks of 255: 65280), and the
-// eight partial sums meet in LDS.
+// A workgroup sums a group of 256 neighbouring ids (a 4-byte word per lane) over the chunks: wave g takes the chunks g,
+// g + 8, .., sixteen loads in flight; the words' bytes are added as pairs of 16 bits (at most 256 chunks of 255: 65280), and
+// the eight partial sums meet in LDS.
 constexpr int kReduceWaves = 8;
-__global__ void __launch_bounds__(kReduceWaves *kWave) hist_reduce_kernel(const unsigned *__restrict__ partial, int nchunks, int V,
+__global__ void __launch_bounds__(kReduceWaves *kWave) hist_reduce_kernel(unsigned char *partial, int nchunks, int V,
                                                                           long long *__restrict__ counts) {
-    __shared__ unsigned part[kReduceWaves][2][kWave];
+    __shared__ unsigned part[kReduceWaves][4][kWave];
+    const HistScratch sc(partial, V, nchunks);
     const int lane = (int)threadIdx.x & 63, g = (int)threadIdx.x >> 6;
     const int wi = blockIdx.x * kWave + lane;
-    const int Vw = (V + 3) >> 2;                   // words per scratch row
+    const int Vw = (int)(sc.pitch >> 2);           // words per scratch row
+    const unsigned *low = reinterpret_cast<const unsigned *>(sc.low), *high = reinterpret_cast<const unsigned *>(sc.high);
+    // the wave's chunks g + 8 l whose upper bits have to be read (requested with the first rows)
+    const int mine = g + kReduceWaves * lane;
+    const unsigned char flag = sc.flags[(size_t)min(mine, nchunks - 1) * sc.groups + blockIdx.x];
+    // (every load is made, past the end that of the last word or chunk: a branch around one would wait for it)
+    const int at = min(wi, Vw - 1);
     unsigned even = 0, odd = 0;                    // ids 4 wi, 4 wi + 2 and 4 wi + 1, 4 wi + 3
-    if (wi < Vw) {
-        constexpr int kLoads = 16;
-        for (int c = g; c < nchunks; c += kLoads * kReduceWaves) {
-            unsigned t[kLoads];
+    unsigned even_hi = 0, odd_hi = 0;
+    constexpr int kLoads = 16;
+    unsigned upper = 0;                            // bit l: chunk g + 8 l
+    for (int l0 = 0; g + kReduceWaves * l0 < nchunks; l0 += kLoads) {
+        unsigned t[kLoads], t_hi[kLoads] = {};
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            const int c = g + kReduceWaves * (l0 + u);
+            t[u] = low[(size_t)min(c, nchunks - 1) * Vw + at];
+        }
+        if (l0 == 0) {
+            // the flags are the oldest load: the rows stay in flight (the test is kept from moving up ahead of them)
+            unsigned f = flag;
+            asm volatile("" : "+v"(f));
+            upper = (unsigned)__ballot(f != 0u && mine < nchunks);
+        }
+        const unsigned now = upper >> l0 & ((1u << kLoads) - 1u);
+        if (now != 0u) {
 #pragma unroll
             for (int u = 0; u < kLoads; ++u)
-                t[u] = c + u * kReduceWaves < nchunks ? partial[(size_t)(c + u * kReduceWaves) * Vw + wi] : 0u;
+                t_hi[u] = high[(size_t)min(g + kReduceWaves * (l0 + u), nchunks - 1) * Vw + at];
+        }
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            const unsigned x = g + kReduceWaves * (l0 + u) < nchunks ? t[u] : 0u;
+            even += x & 0x00FF00FFu;
+            odd += (x >> 8) & 0x00FF00FFu;
+        }
+        if (now != 0u) {
 #pragma unroll
             for (int u = 0; u < kLoads; ++u) {
-                even += t[u] & 0x00FF00FFu;
-                odd += (t[u] >> 8) & 0x00FF00FFu;
+                const unsigned x = (now >> u & 1u) != 0u ? t_hi[u] : 0u;      // (the others were never written)
+                even_hi += x & 0x00FF00FFu;
+                odd_hi += (x >> 8) & 0x00FF00FFu;
             }
         }
     }
+    static_assert(kHistBlocks / kReduceWaves <= 32, "a bit per chunk of a wave");
     part[g][0][lane] = even;
     part[g][1][lane] = odd;
+    part[g][2][lane] = even_hi;
+    part[g][3][lane] = odd_hi;
     __syncthreads();
     // thread t < 256: id 256 * block + t
-    const int t = (int)threadIdx.x, id = blockIdx.x * 4 * kWave + t;
-    if (t < 4 * kWave && id < V) {
-        unsigned sum = 0;
+    const int t = (int)threadIdx.x, id = blockIdx.x * kGroupIds + t;
+    if (t < kGroupIds && id < V) {
+        unsigned sum = 0, sum_hi = 0;
 #pragma unroll
-        for (int q = 0; q < kReduceWaves; ++q) sum += part[q][t & 1][t >> 2] >> (8 * (t & 2)) & 0xFFFFu;
-        counts[id] += (long long)sum;
+        for (int q = 0; q < kReduceWaves; ++q) {
+            sum += part[q][t & 1][t >> 2] >> (8 * (t & 2)) & 0xFFFFu;
+            sum_hi += part[q][2 + (t & 1)][t >> 2] >> (8 * (t & 2)) & 0xFFFFu;
+        }
+        counts[id] += (long long)(sum + (sum_hi << 8));
     }
 }
 static_assert(kHistBlocks <= 257, "sums over the chunks of eight-bit parts fit 16 bits");
 
 hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V, long long *counts,
                          unsigned long long *n_invalid, void *partial, hipStream_t st) {
-    unsigned char *rows = static_cast<unsigned char *>(partial);
     const int nchunks = hist_num_chunks(n_ids, V);
-    const int nranges = hist_num_ranges(V);
     const size_t lds = (size_t)kHistBinsPerBlock * sizeof(unsigned short);
     static LdsLimitOnce lds_limit;
     hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(hist_partial_kernel<false>),
                                                  reinterpret_cast<const void *>(hist_partial_kernel<true>)}, (int)lds);
     if (e != hipSuccess) return e;
-    dim3 grid(nchunks, nranges);
     // ids before the first 16-byte boundary are counted one by one
     const int idb = ids64 ? 8 : 4;
     const uintptr_t mis = reinterpret_cast<uintptr_t>(ids) & 15u;
     long long head = mis ? (long long)((16 - mis) / idb) : 0;
     if (head > n_ids) head = n_ids;
-    if (ids64)
-        hipLaunchKernelGGL(hist_partial_kernel<true>, grid, dim3(kHistThreads), lds, st, ids, (long long)n_ids,
-                           (int)head, V, nchunks, rows, reinterpret_cast<unsigned long long *>(counts), n_invalid);
-    else
-        hipLaunchKernelGGL(hist_partial_kernel<false>, grid, dim3(kHistThreads), lds, st, ids, (long long)n_ids,
-                           (int)head, V, nchunks, rows, reinterpret_cast<unsigned long long *>(counts), n_invalid);
-    hipLaunchKernelGGL(hist_reduce_kernel, dim3(((V + 3) / 4 + kWave - 1) / kWave), dim3(kReduceWaves * kWave), 0, st,
-                       reinterpret_cast<const unsigned *>(rows), nchunks, V, counts);
+    unsigned char *scratch = static_cast<unsigned char *>(partial);
+    auto partial_kernel = ids64 ? hist_partial_kernel<true> : hist_partial_kernel<false>;
+    hipLaunchKernelGGL(partial_kernel, dim3(nchunks, hist_num_ranges(V)), dim3(kHistThreads), lds, st, ids, (long long)n_ids,
+                       (int)head, V, nchunks, scratch, reinterpret_cast<unsigned long long *>(counts), n_invalid);
+    hipLaunchKernelGGL(hist_reduce_kernel, dim3((V + kGroupIds - 1) / kGroupIds), dim3(kReduceWaves * kWave), 0, st, scratch,
+                       nchunks, V, counts);
     return hipGetLastError();
 }
 

@@ -151,3 +151,22 @@ def test_rank_order_of_large_counts(kind, V):
     for k in sorted({1, V // 100 + 1, V // 3 + 1, V}):
         a, _ = vt.build_trimmed_head(dc, None, k, order="rank")
         assert np.array_equal(a.cpu().numpy(), order[:k]), k
+
+
+# The upper eight bits of the bins are there for the groups of 256 ids that have any: hot ids in one group, at the edges of
+# groups and ranges, in none and in all; more and fewer chunks than a wave of the sum takes
+@pytest.mark.parametrize("V,n_ids,hot", [
+    (65536 + 512, 2_000_000, [0, 255, 256, 65535, 65536, 66047]), (128256, 9_000_000, list(range(40))), (700, 3_000_000, []),
+    (4097, 20_000_000, [4096]), (300, 16_000_000, [1, 299]), (257, 100_000, [256])])
+@pytest.mark.parametrize("dtype", [torch.int32, torch.int64])
+def test_count_hot_ids_side_by_side(V, n_ids, hot, dtype):
+    rng = np.random.default_rng(V)
+    ids = rng.integers(0, V, size=n_ids)
+    if hot:
+        some = rng.random(n_ids) < 0.4
+        ids[some] = rng.choice(hot, size=int(some.sum()))
+    c = vt.count_tokens(torch.from_numpy(ids).to(dtype).cuda(), V)
+    assert np.array_equal(c.cpu().numpy(), np.bincount(ids, minlength=V))
+    ws = torch.full((vt.load_library().vt_count_tokens_ws_bytes(V, n_ids),), 255, dtype=torch.uint8, device="cuda")
+    c = vt.count_tokens(torch.from_numpy(ids).to(dtype).cuda(), V, c, ws=ws)      # on top, with a workspace that held other things
+    assert np.array_equal(c.cpu().numpy(), 2 * np.bincount(ids, minlength=V))
