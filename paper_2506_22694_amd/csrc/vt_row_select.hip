@@ -137,8 +137,9 @@ __device__ __forceinline__ void fold_stretch(const float (&v)[kRowVals], float &
     }
 }
 
-// Every logit of a stretch that reaches Tf, with its position, into `val` / `pos` (cap entries; n counts on).
-template <bool VEC>
+// Every logit of a stretch that reaches Tf, with its position, into `val` / `pos` (cap entries; n counts on -- STOP: a lane
+// that finds no room goes on no further: where everything reaches Tf tens of thousands of increments queue on one address).
+template <bool VEC, bool STOP>
 __device__ __forceinline__ void collect_stretch(const float (&v)[kRowVals], int base, int k, int tid, float Tf, float *val,
                                                 int *pos, unsigned *n, unsigned cap) {
 #pragma unroll
@@ -156,6 +157,7 @@ __device__ __forceinline__ void collect_stretch(const float (&v)[kRowVals], int 
                         val[slot] = v[u];
                         pos[slot] = j;
                     }
+                    if (STOP && slot >= cap) Tf = INFINITY;
                 }
             }
         }
@@ -203,15 +205,15 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         fold_stretch(v, lm, ls);
         row_threshold(lm, m, tmax_first, lane, w, T, Mo);
         const float Tf1 = threshold_f32(T);
-        collect_stretch<VEC>(v, 0, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, !ONE>(v, 0, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
         for (int base = kRowSpan; base < k; base += 2 * kRowSpan) {
             load_stretch<VEC>(zr, base + kRowSpan, k, tid, v);
             fold_stretch(v2, lm, ls);
-            collect_stretch<VEC>(v2, base, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+            collect_stretch<VEC, !ONE>(v2, base, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
             if (base + kRowSpan < k) {
                 load_stretch<VEC>(zr, base + 2 * kRowSpan, k, tid, v2);
                 fold_stretch(v, lm, ls);
-                collect_stretch<VEC>(v, base + kRowSpan, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+                collect_stretch<VEC, !ONE>(v, base + kRowSpan, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
             }
         }
     }
@@ -223,7 +225,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
 
     // ---- pass 2: every logit >= T is a candidate
     if constexpr (ONE) {
-        collect_stretch<VEC>(v, 0, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, !ONE>(v, 0, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
         __syncthreads();
     } else if (s_nraw > kRaw) {
         __syncthreads();
@@ -231,7 +233,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         __syncthreads();
         for (int base = 0; base < k; base += kRowSpan) {
             load_stretch<VEC>(zr, base, k, tid, v);
-            collect_stretch<VEC>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+            collect_stretch<VEC, !ONE>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
         }
         __syncthreads();
     }

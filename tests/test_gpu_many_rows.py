@@ -109,7 +109,8 @@ def test_merge_of_many_lists_with_more_tokens_than_waves():
 # more tokens than waves; `late`: the first stretch's logits say nothing about the rest, which overflows the collection
 # (the row is read again); a row whose logits are all equal.
 @pytest.mark.parametrize("n,k,m,late", [
-    (9, 32769, 16, False), (10, 65536, 16, False), (9, 131076, 64, False), (12, 98304, 10, True), (9, 40001, 33, True)])
+    (9, 32769, 16, False), (10, 65536, 16, False), (9, 131076, 64, False), (12, 98304, 10, True), (9, 40001, 33, True),
+    (16, 65536, 16, True)])
 def test_stored_logits_longer_than_one_stretch(n, k, m, late):
     assert "row_select" in vt.draft_head_step_plan(n, k, 128, m)
     W, map_ = synth.trimmed_head_direct(k, 128, seed=1000 + n, dtype="bf16")
