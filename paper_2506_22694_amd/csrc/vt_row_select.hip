@@ -164,19 +164,24 @@ __device__ __forceinline__ void collect_stretch(const float (&v)[kRowVals], int 
     }
 }
 
-// ONE: the row fits one stretch (k <= 32768), which stays in registers for the second pass.  Longer rows are read once,
-// too: the first stretch's threshold is one that m logits of the row reach, so what later stretches have to offer above it
+// kRowWhole: the row fits one stretch (k <= 32768), which stays in registers for the second pass.  kRowSift: longer rows are
+// read once, too: the first stretch's threshold is one that m logits of the row reach, so what later stretches have to offer above it
 // is collected as they go by (with the next stretch requested before the one at hand is folded), and the row's own
 // threshold thins that out at the end.  A row whose first stretch says little (more than kRowMaxRaw logits above its
 // threshold) is read again.  Reading longer rows twice cost k = 65536, n = 256 24.3 us (now 21.0),
 // k = 128256, n = 256 40.6 (27.9), n = 16 20.5 (17.3): up to 64 rows what is left is the rate at which one CU reads a row.
-template <bool ONE, bool VEC>
+// kRowTwice: up to 8 hidden rows of more than 16 tokens are read twice all the same: the first stretch's threshold is then
+// found bit by bit, and passes several times as many logits as the row's own (whole step, once against twice: n = 1,
+// k = 63000, m = 24 28.2 / 24.8 us, n = 4, k = 128256, m = 64 47.7 / 43.3; but n = 16, k = 65536, m = 24 30.6 / 32).
+enum RowMode { kRowWhole, kRowSift, kRowTwice };
+template <RowMode MODE, bool VEC>
 __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__restrict__ z, const int *__restrict__ map,
                                                                  int k, int m, int *__restrict__ out_ids,
                                                                  float *__restrict__ out_logp,
                                                                  float *__restrict__ out_lse,
                                                                  float *__restrict__ lse_buf) {
-    constexpr unsigned kRaw = ONE ? kRowMaxCand : kRowMaxRaw;
+    constexpr bool SIFT = MODE == kRowSift;
+    constexpr unsigned kRaw = SIFT ? kRowMaxRaw : kRowMaxCand;
     __shared__ float redf[kRowWaves];
     __shared__ unsigned long long red64[kRowWaves];
     __shared__ unsigned tmax[2 * kRowWaves], tmax_first[2 * kRowWaves];
@@ -197,23 +202,27 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     float lm = -INFINITY, ls = 0.f;
     load_stretch<VEC>(zr, 0, k, tid, v);
     unsigned T, Mo;
-    if constexpr (ONE) {
+    if constexpr (!SIFT) {
         fold_stretch(v, lm, ls);
+        for (int base = kRowSpan; MODE == kRowTwice && base < k; base += kRowSpan) {
+            load_stretch<VEC>(zr, base, k, tid, v);
+            fold_stretch(v, lm, ls);
+        }
     } else {
         float v2[kRowVals];
         load_stretch<VEC>(zr, kRowSpan, k, tid, v2);
         fold_stretch(v, lm, ls);
         row_threshold(lm, m, tmax_first, lane, w, T, Mo);
         const float Tf1 = threshold_f32(T);
-        collect_stretch<VEC, !ONE>(v, 0, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, SIFT>(v, 0, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
         for (int base = kRowSpan; base < k; base += 2 * kRowSpan) {
             load_stretch<VEC>(zr, base + kRowSpan, k, tid, v);
             fold_stretch(v2, lm, ls);
-            collect_stretch<VEC, !ONE>(v2, base, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+            collect_stretch<VEC, SIFT>(v2, base, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
             if (base + kRowSpan < k) {
                 load_stretch<VEC>(zr, base + 2 * kRowSpan, k, tid, v2);
                 fold_stretch(v, lm, ls);
-                collect_stretch<VEC, !ONE>(v, base + kRowSpan, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+                collect_stretch<VEC, SIFT>(v, base + kRowSpan, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
             }
         }
     }
@@ -224,8 +233,11 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     const float Tf = threshold_f32(T);
 
     // ---- pass 2: every logit >= T is a candidate
-    if constexpr (ONE) {
-        collect_stretch<VEC, !ONE>(v, 0, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+    if constexpr (!SIFT) {
+        for (int base = 0; base < (MODE == kRowTwice ? k : 1); base += kRowSpan) {
+            if (MODE == kRowTwice) load_stretch<VEC>(zr, base, k, tid, v);
+            collect_stretch<VEC, SIFT>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+        }
         __syncthreads();
     } else if (s_nraw > kRaw) {
         __syncthreads();
@@ -233,7 +245,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         __syncthreads();
         for (int base = 0; base < k; base += kRowSpan) {
             load_stretch<VEC>(zr, base, k, tid, v);
-            collect_stretch<VEC, !ONE>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+            collect_stretch<VEC, SIFT>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
         }
         __syncthreads();
     }
@@ -241,7 +253,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     int ncand = nraw;
     if (nraw <= (int)kRaw) {
         // the candidates' target ids, all requested at once
-        if constexpr (ONE) {
+        if constexpr (!SIFT) {
             for (int c = tid; c < nraw; c += kRowThreads) cand[c] = make_key(rawv[c], map[rawj[c]]);
             __syncthreads();
         } else {
@@ -280,7 +292,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         for (int r = 0; r < m; ++r) {
             unsigned long long best = kNoKey;
             for (int base = 0; base < k; base += kRowSpan) {
-                if (!ONE) load_stretch<VEC>(zr, base, k, tid, v);
+                if (MODE != kRowWhole) load_stretch<VEC>(zr, base, k, tid, v);
 #pragma unroll
                 for (int u = 0; u < kRowVals; ++u) {
                     const int j = stretch_index<VEC>(base, u, tid);
@@ -307,9 +319,9 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
 void launch_row_select(const float *z, const int *map, int n, int k, int m, int *out_ids, float *out_logp,
                        float *out_lse, float *lse_buf, hipStream_t st) {
     const bool vec = (k & 3) == 0 && (reinterpret_cast<uintptr_t>(z) & 15) == 0;
-    const bool keep = k <= kRowSpan;
-    auto kern = keep ? (vec ? row_select_kernel<true, true> : row_select_kernel<true, false>)
-                     : (vec ? row_select_kernel<false, true> : row_select_kernel<false, false>);
+    auto pick = [&](auto whole, auto sift, auto twice) { return k <= kRowSpan ? whole : n <= kGemvMaxN && m > kRowWaves ? twice : sift; };
+    auto kern = vec ? pick(&row_select_kernel<kRowWhole, true>, &row_select_kernel<kRowSift, true>, &row_select_kernel<kRowTwice, true>)
+                    : pick(&row_select_kernel<kRowWhole, false>, &row_select_kernel<kRowSift, false>, &row_select_kernel<kRowTwice, false>);
     hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, out_ids, out_logp, out_lse, lse_buf);
 }
 

@@ -175,3 +175,20 @@ def test_step_with_unequal_ranges_of_columns(n, k, d, m, rows):
     assert (logp - ref.topk(m, 1).values).abs().max().item() < 5e-5
     dup = full[:, torch.tensor(same, device="cuda")]
     assert torch.equal(dup, dup[:, :1].expand_as(dup))
+
+
+# The same with up to 8 hidden rows and more than 16 tokens (rows read twice): small kernels, whole and ragged stretches, equal logits
+@pytest.mark.parametrize("n,k,m,late", [(1, 32769, 64, False), (8, 65536, 17, False), (3, 98309, 33, True), (2, 131072, 64, True), (5, 40000, 16, True)])
+def test_stored_logits_of_few_rows_longer_than_one_stretch(n, k, m, late):
+    assert "row_select" in vt.draft_head_step_plan(n, k, 128, m)
+    W, map_ = synth.trimmed_head_direct(k, 128, seed=1300 + n, dtype="bf16")
+    if late:
+        W[:32768] = 0
+    h = synth.hidden_rows(n, 128, seed=k, dtype="bf16")
+    if n > 1:
+        h[n // 2] = 0
+    ref = oracle.draft_head_step(h, W, map_, m)
+    oi, ol, lse = run_step(h, W, map_, m, return_lse=True)
+    assert check_step(oi, ol, ref, map_, m, lse) <= 2 + n * m // 256
+    if n > 1:
+        assert oi[n // 2].tolist() == sorted(map_)[:m]
