@@ -145,6 +145,9 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     // that crowd (at d = 3072 the plain march is 0.6 us faster).  Eight ranges for tiles of eight waves (k = 32768, d = 2048:
     // 25.9 us for one hidden row and 28.8 for eight; 27.6 and 30.4 with four), four for any number of waves, whose tiles lie
     // a different number of pages apart at every height (k = 40000, d = 4096, n = 8: 59.0 against 60.7).
+    // The ranges are equal at d = 16384 too, where they lie whole multiples of 4 KiB apart: starts 512 bytes off gained at
+    // some sizes what they lost at others (n = 8: k = 20000 116.7 / 113.8 us, k = 32768 167.4 / 168.2; n = 6, k = 30000
+    // 153.5 / 157.0).
     constexpr int NR = MAXW > kStepWaves ? 4 : 8;
     const bool rotate = KS == 1 && nunits >= 8 && a.d % 2048 == 0;
     const int rot = !rotate ? 0 : NR == 4 ? ((int)blockIdx.x >> 3) & 3 : first_range<NR>((int)blockIdx.x);

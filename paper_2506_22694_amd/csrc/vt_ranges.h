@@ -78,15 +78,15 @@ struct RangeSums {
     }
 };
 
-// Columns from one range's start to the next, in units of which a row of d holds `units`.  NR equal ranges; four that
-// would start whole multiples of 4 KiB apart, on the same channels again, are a further 1 KiB apart each, and the last
-// one is shorter (d = 8192: n = 100, k = 40000 146.6 -> 122.9 us, n = 160, k = 32768 134.0 / 124.5, k = 24576 112.2 /
-// 107.7, n = 100, k = 32768 100.8 / 101.8).  Eight ranges are equal at any d: 512 bytes more each at d = 16384 gained at
-// some sizes what it lost at others (n = 64: k = 20000 146.1 / 138.4, k = 32768 162.8 / 165.8; n = 6, k = 30000 153.5 / 157.0).
+// Columns from one range's start to the next, in units of which a row of d holds `units`: NR equal ranges -- where those
+// would start whole multiples of 4 KiB apart, on the same channels again, each is longer by 4 KiB / NR and the last one
+// shorter.  Four ranges, d = 8192: n = 100, k = 40000 146.6 -> 122.9 us, n = 160, k = 32768 134.0 -> 124.5, n = 100,
+// k = 32768 100.8 / 101.8.  Eight, d = 16384: n = 20, k = 24445 145.6 -> 128.9, n = 64 156.4 -> 144.5, k = 40000 228 -> 205,
+// but k = 33000 174 / 179.  (The kernel for up to 8 hidden rows keeps equal ranges, see there.)
 template <int NR>
 __device__ __forceinline__ int range_step(int units, int d) {
     const int step = units / NR;
-    return NR == 4 && d % 8192 == 0 ? step + units * 512 / d : step;
+    return NR > 1 && d % (NR * 2048) == 0 ? step + units * (2048 / NR) / d : step;
 }
 
 // The range workgroup b starts with.

@@ -155,22 +155,25 @@ def test_step_of_many_long_rows(n, k, d, m):
     assert torch.equal(dup, dup[:, :1].expand_as(dup))
 
 
-# Four ranges of columns that would start whole multiples of 4 KiB apart (d a multiple of 8192) are cut unequally: tiles of 96,
-# 128 and 160 rows, in several rotations
-@pytest.mark.parametrize("n,k,d,m,rows", [(160, 24000, 8192, 8, 96), (190, 32000, 8192, 8, 128), (70, 39000, 8192, 8, 160)])
-def test_step_with_unequal_ranges_of_columns(n, k, d, m, rows):
+# Ranges of columns that would start whole multiples of 4 KiB apart are cut unequally, in several rotations: four (d a multiple
+# of 8192, tiles of 96, 128 and 160 rows), eight (d a multiple of 16384: stages of one block and of two, extra rows, twin tiles)
+@pytest.mark.parametrize("n,k,d,m,rows,kernel", [
+    (160, 24000, 8192, 8, 96, "wide_kernel<2>"), (190, 32000, 8192, 8, 128, "wide_kernel<2>"), (70, 39000, 8192, 8, 160, "wide_kernel<1>"),
+    (9, 9000, 16384, 8, 48, "<2,8>"), (40, 20000, 16384, 8, 128, "<4,8>"), (20, 33000, 16384, 8, 129, "<2,8>"), (70, 8000, 16384, 4, 32, "wide_kernel<1>"),
+    (16, 12000, 32768, 8, 48, "<2,8>"), (64, 24000, 16384, 8, 96, "<4,7>")])
+def test_step_with_unequal_ranges_of_columns(n, k, d, m, rows, kernel):
     plan = vt.draft_head_step_plan(n, k, d, m)
-    assert "wide_kernel" in plan and f"tile_rows={rows} " in plan
+    assert kernel in plan and f"tile_rows={rows} " in plan, plan
     g = torch.Generator(device="cuda").manual_seed(n)
     W = torch.randn(k, d, generator=g, device="cuda", dtype=torch.bfloat16).mul_(0.02)
     h = torch.randn(n, d, generator=g, device="cuda", dtype=torch.bfloat16)
-    same = [b * rows + 5 for b in (0, 8, 16, 24, 40, 72)] + [k - 1]
+    same = [b * rows + 5 for b in (0, 8, 16, 24, 32, 40, 48, 56, 72) if b * rows + 5 < k] + [k - 1]
     W[same] = W[same[0]].clone()
     map_ = torch.arange(k, dtype=torch.int32, device="cuda")
     ids, logp, lse, full = vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True)
     z = torch.cat([h.double() @ W[a:a + 4000].double().t() for a in range(0, k, 4000)], 1)
     ref = z - z.logsumexp(1, keepdim=True)
-    # fp32 sums of 8192 products of size 0.02, |logit| <= 10: a few ulp of 10 per range and of the log-sum-exp
+    # fp32 sums of d products of size 0.02, |logit| <= 20: a few ulp of 20 (2e-6) per range and of the log-sum-exp
     assert (full - ref).abs().max().item() < 5e-5
     assert (logp - ref.topk(m, 1).values).abs().max().item() < 5e-5
     dup = full[:, torch.tensor(same, device="cuda")]
