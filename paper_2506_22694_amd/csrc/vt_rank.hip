@@ -24,8 +24,8 @@
 //   nothing and is skipped: each kernel derives that, and which buffer holds the data, from the digit totals alone.
 //   (Eight passes over the bytes of the counts, nineteen launches, took 72 us at V = 128256 after 10^7 tokens; now 43.)
 //   V = 128256: after 10^11 tokens 47 us (86 with two global atomics per large count, 95 over the bytes); all counts in
-//   2^40 .. 2^40 + 2^20 48 (more than 100000 with every thread walking its run, 74); half of them in 2^35 .. 2^35 + 2^13 52
-//   (75).  Slower than over the bytes: runs of 200 to 400 ids, V = 32000 around 2^19, 95 (441, 55).
+//   2^40 .. 2^40 + 2^20 48 (74; V = 32000 40, 6475 with every thread walking its run, 56); half of them in
+//   2^35 .. 2^35 + 2^13 52 (75).  Slower than over the bytes: runs of 200 to 400 ids, V = 32000 around 2^19, 95 (441, 55).
 // choose_*: no sort: a histogram over bins of counts (exact below 2048) with the mass of every bin, walked from the
 //   largest counts down to the bin in which the mass reaches ceil(P * total).  With the read-back of k 107 us behind a full
 //   sort, now 31.  Where that bin holds several values all workgroups histogram the next eleven bits of its ids, and the
@@ -95,9 +95,12 @@ __device__ __forceinline__ int source_buffer(const unsigned *__restrict__ gtot, 
 // many times over.  Returns whether the codes of counts >= kRankExact are their low bits: the usual ones leave out bits that
 // differ, and all those counts agree above the low bits, in bits that are not all zero (smaller counts share their codes too
 // seldom for the counts to be read again in every pass).
-__device__ __forceinline__ bool stage_totals(const SortBufs &b, unsigned *gs) {
-    const unsigned long long above = b.rest[2];
-    const bool low = above != 0ull && (above & b.rest[3]) == 0ull && (b.rest[0] & b.rest[1]) != 0ull;      // (uniform)
+// differ: the usual codes leave out bits that differ.
+__device__ __forceinline__ bool stage_totals(const SortBufs &b, unsigned *gs, bool &differ) {
+    // (one request for the four words, and no branch on one before the others)
+    const unsigned long long left_out = b.rest[0] & b.rest[1], above = b.rest[2], above_differ = b.rest[2] & b.rest[3];
+    differ = left_out != 0ull;
+    const bool low = (above != 0ull) & (above_differ == 0ull) & differ;      // (uniform)
     if (threadIdx.x < kPasses * kDigits) {
         unsigned t = b.gtot[threadIdx.x];      // (requested with the flags)
         if (low) t += b.gtot[kPasses * kDigits + threadIdx.x];
@@ -188,7 +191,8 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_hist_kernel(const long
                                                                       SortBufs b) {
     __shared__ unsigned h[kDigits];
     __shared__ unsigned gs[kPasses * kDigits];
-    const bool low = stage_totals(b, gs);
+    bool differ;
+    const bool low = stage_totals(b, gs, differ);
     if (!pass_active(gs, p, n)) return;
     const int src = source_buffer(gs, p, n);
     const int j = blockIdx.x * kRankSortThreads + threadIdx.x;
@@ -206,7 +210,8 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_scatter_kernel(const l
     __shared__ unsigned part[4 * kDigits];            // sums over a quarter of the earlier workgroups
     __shared__ unsigned offs[kDigits];                // first output slot of this workgroup's run of each digit
     __shared__ unsigned gs[kPasses * kDigits];
-    const bool low = stage_totals(b, gs);
+    bool differ;
+    const bool low = stage_totals(b, gs, differ);
     if (!pass_active(gs, p, n)) return;
     const int src = source_buffer(gs, p, n);
     const unsigned *hist = low && p == 0 ? b.hist_low : b.hist;
@@ -438,7 +443,8 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_out_kernel(const long 
                                                                      int *__restrict__ out_ids) {
     __shared__ unsigned gs[kPasses * kDigits];
     __shared__ RunLds s;
-    const bool low = stage_totals(b, gs);
+    bool differ;
+    const bool low = stage_totals(b, gs, differ);
     const int src = source_buffer(gs, kPasses, n);
     const unsigned long long *pairs = b.pairs[src];      // (sort_long_run writes there)
     const int tid = threadIdx.x;
@@ -446,7 +452,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_out_kernel(const long 
     const bool in = j < (unsigned)n;
     const unsigned long long pair = in ? pairs[j] : 0ull;
     const int id = (int)(unsigned)pair;
-    if (low || (b.rest[0] & b.rest[1]) == 0ull) {      // (uniform) the codes leave out nothing that differs
+    if (low || !differ) {      // (uniform) the codes leave out nothing that differs
         if (in && j < (unsigned)n_ids) out_ids[j] = id;
         return;
     }
@@ -474,8 +480,10 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_out_kernel(const long 
         }
     }
     __syncthreads();
+    const int n_starts = s.n_starts;
+    if (n_starts == 0) return;      // (as a rule; the code below is far from being fetched)
     const int lane = tid & 63, w = tid >> 6;
-    for (int q = w; q < s.n_starts; q += kSortWaves) {
+    for (int q = w; q < n_starts; q += kSortWaves) {
         const unsigned lo = (unsigned)s.starts[q];
         if (lo >= (unsigned)n_ids) continue;      // nobody asks for them
         const unsigned run_code = code_of(lo);
@@ -751,121 +759,8 @@ __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const lon
         if (blockIdx.x == 0 && tid < 3) out[tid] = tid == 2 ? (long long)total : 0;
         return;
     }
-    if (!DIRECT && bin < kBinExact && blockIdx.x != 0) return;
-    unsigned before_n = s_n, ids = s_ids;
-    unsigned long long before_m = s_m, ids_mass = s_mass, T = (unsigned)bin;
-    if (bin >= kBinExact) {
-        // several values share the bin: the value at which the target is reached, digit by digit
-        T = bin_prefix(bin);
-        int left = bin_shift(bin), nbits = left < kDigitBits ? left : kDigitBits;
-        __syncthreads();                // (h and m are read, s_* too)
-        auto clear = [&]() {
-            for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
-                h[i] = 0u;
-                m[i] = 0ull;
-            }
-            __syncthreads();
-        };
-        clear();
-        {
-            unsigned long long ones = 0, zeros = 0;
-            for (unsigned base = blockIdx.x * kRankSortThreads; base < (unsigned)V; base += gridDim.x * kRankSortThreads) {
-                const unsigned x = base + tid;
-                const unsigned long long c = x < (unsigned)V ? (unsigned long long)counts[x] : 0ull;
-                const bool in = (c >> left) == T;      // (zero past the end: T > 0)
-                wave_tally_mass(h, m, 0, (int)((c >> (left - nbits)) & low_bits(nbits)), in, c);
-                ones |= in ? c & low_bits(left) : 0ull;
-                zeros |= in ? ~c & low_bits(left) : 0ull;
-            }
-            if (__ballot((ones | zeros) != 0ull) != 0ull) {
-                ones = wave_or_u64(ones);
-                zeros = wave_or_u64(zeros);
-                if (lane == 0) {
-                    atomicOr(&s_ones, ones);
-                    atomicOr(&s_zeros, zeros);
-                }
-            }
-            __syncthreads();
-        }
-        if constexpr (!DIRECT) {
-            for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
-                if (h[i] != 0u) {
-                    atomicAdd(&b.digits[i], h[i]);
-                    atomicAdd(&b.digit_mass[i], m[i]);
-                }
-            }
-            if (tid == 0 && (s_ones | s_zeros) != 0ull) {
-                atomicOr(&b.bits[0], s_ones);
-                atomicOr(&b.bits[1], s_zeros);
-            }
-            wait_stores_done();      // this wave's atomics have been performed
-            __syncthreads();
-            if (tid == 0) s_last = __hip_atomic_fetch_add(b.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-            __syncthreads();
-            if (!s_last) return;
-            // the last workgroup goes on with everybody's digits
-            for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
-                h[i] = __hip_atomic_load(&b.digits[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                m[i] = acquire_u64(&b.digit_mass[i]);
-            }
-            if (tid == 0) {
-                s_ones = acquire_u64(&b.bits[0]);
-                s_zeros = acquire_u64(&b.bits[1]);
-            }
-            __syncthreads();
-        }
-        const unsigned long long ones = s_ones, zeros = s_zeros;
-        // Appends the digit at which the target is reached, of the ids in h and m.
-        static_assert(kDigitBins == 2 * kRankSortThreads, "two digits per thread");
-        auto find_digit = [&]() {
-            const int d = kDigitBins - 1 - 2 * tid;      // and the one below
-            const unsigned n0 = h[d], n1 = h[d - 1];
-            const unsigned long long m0 = m[d], m1 = m[d - 1];
-            unsigned un = n0 + n1;
-            unsigned long long um = m0 + m1;
-            if (tid == 0) found(0, 0u, 0ull, before_n, before_m);      // (found by some thread unless the mass wraps around)
-            block_scan2(un, um, pn, pm);
-            const unsigned above_n = before_n + un - n0 - n1;
-            const unsigned long long above_m = before_m + um - m0 - m1;
-            if (reaches(n0, m0, above_n, above_m)) found(d, n0, m0, above_n, above_m);
-            if (reaches(n1, m1, above_n + n0, above_m + m0)) found(d - 1, n1, m1, above_n + n0, above_m + m0);
-            __syncthreads();
-            T = (T << nbits) | (unsigned)s_bin;
-            left -= nbits;
-            before_n = s_n;
-            before_m = s_m;
-            ids = s_ids;
-            ids_mass = s_mass;
-            __syncthreads();
-        };
-        find_digit();
-        while (left > 0) {
-            if (ids == 1u) {      // its mass is its count
-                T = ids_mass;
-                break;
-            }
-            left = skip_common_bits(T, left, ones, zeros);
-            if (left == 0) break;
-            nbits = left < kDigitBits ? left : kDigitBits;
-            clear();
-            constexpr int kInFlight = 8;
-            for (unsigned x0 = 0; x0 < (unsigned)V; x0 += kInFlight * kRankSortThreads) {
-                unsigned long long cx[kInFlight];
-#pragma unroll
-                for (int u = 0; u < kInFlight; ++u) {
-                    const unsigned x = x0 + u * kRankSortThreads + tid;
-                    cx[u] = x < (unsigned)V ? (unsigned long long)counts[x] : 0ull;
-                }
-#pragma unroll
-                for (int u = 0; u < kInFlight; ++u)
-                    wave_tally_mass(h, m, 0, (int)((cx[u] >> (left - nbits)) & low_bits(nbits)), (cx[u] >> left) == T, cx[u]);
-            }
-            __syncthreads();
-            find_digit();
-        }
-    }
-    if (tid == 0) {
-        // ids of count T, one after the other, until the target is reached; at least one
+    // ids of count T, one after the other, until the target is reached; at least one
+    auto finish = [&](unsigned long long T, unsigned before_n, unsigned long long before_m) {
         unsigned long long take = 1;
         if (target > before_m && T > 0) {
             take = (target - before_m + T - 1) / T;
@@ -874,7 +769,121 @@ __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const lon
         out[0] = (long long)(before_n + take);
         out[1] = (long long)(before_m + take * T);
         out[2] = (long long)total;
+    };
+    if (bin < kBinExact) {      // (not at the end of the kernel: its code would have to be fetched from there)
+        if (blockIdx.x == 0 && tid == 0) finish((unsigned)bin, s_n, s_m);
+        return;
     }
+    // several values share the bin: the value at which the target is reached, digit by digit
+    unsigned before_n = s_n, ids = s_ids;
+    unsigned long long before_m = s_m, ids_mass = s_mass, T = bin_prefix(bin);
+    int left = bin_shift(bin), nbits = left < kDigitBits ? left : kDigitBits;
+    __syncthreads();                // (h and m are read, s_* too)
+    auto clear = [&]() {
+        for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
+            h[i] = 0u;
+            m[i] = 0ull;
+        }
+        __syncthreads();
+    };
+    clear();
+    {
+        unsigned long long ones = 0, zeros = 0;
+        for (unsigned base = blockIdx.x * kRankSortThreads; base < (unsigned)V; base += gridDim.x * kRankSortThreads) {
+            const unsigned x = base + tid;
+            const unsigned long long c = x < (unsigned)V ? (unsigned long long)counts[x] : 0ull;
+            const bool in = (c >> left) == T;      // (zero past the end: T > 0)
+            wave_tally_mass(h, m, 0, (int)((c >> (left - nbits)) & low_bits(nbits)), in, c);
+            ones |= in ? c & low_bits(left) : 0ull;
+            zeros |= in ? ~c & low_bits(left) : 0ull;
+        }
+        if (__ballot((ones | zeros) != 0ull) != 0ull) {
+            ones = wave_or_u64(ones);
+            zeros = wave_or_u64(zeros);
+            if (lane == 0) {
+                atomicOr(&s_ones, ones);
+                atomicOr(&s_zeros, zeros);
+            }
+        }
+        __syncthreads();
+    }
+    if constexpr (!DIRECT) {
+        for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
+            if (h[i] != 0u) {
+                atomicAdd(&b.digits[i], h[i]);
+                atomicAdd(&b.digit_mass[i], m[i]);
+            }
+        }
+        if (tid == 0 && (s_ones | s_zeros) != 0ull) {
+            atomicOr(&b.bits[0], s_ones);
+            atomicOr(&b.bits[1], s_zeros);
+        }
+        wait_stores_done();      // this wave's atomics have been performed
+        __syncthreads();
+        if (tid == 0) s_last = __hip_atomic_fetch_add(b.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        __syncthreads();
+        if (!s_last) return;
+        // the last workgroup goes on with everybody's digits
+        for (int i = tid; i < kDigitBins; i += kRankSortThreads) {
+            h[i] = __hip_atomic_load(&b.digits[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            m[i] = acquire_u64(&b.digit_mass[i]);
+        }
+        if (tid == 0) {
+            s_ones = acquire_u64(&b.bits[0]);
+            s_zeros = acquire_u64(&b.bits[1]);
+        }
+        __syncthreads();
+    }
+    const unsigned long long ones = s_ones, zeros = s_zeros;
+    // Appends the digit at which the target is reached, of the ids in h and m.
+    static_assert(kDigitBins == 2 * kRankSortThreads, "two digits per thread");
+    auto find_digit = [&]() {
+        const int d = kDigitBins - 1 - 2 * tid;      // and the one below
+        const unsigned n0 = h[d], n1 = h[d - 1];
+        const unsigned long long m0 = m[d], m1 = m[d - 1];
+        unsigned un = n0 + n1;
+        unsigned long long um = m0 + m1;
+        if (tid == 0) found(0, 0u, 0ull, before_n, before_m);      // (found by some thread unless the mass wraps around)
+        block_scan2(un, um, pn, pm);
+        const unsigned above_n = before_n + un - n0 - n1;
+        const unsigned long long above_m = before_m + um - m0 - m1;
+        if (reaches(n0, m0, above_n, above_m)) found(d, n0, m0, above_n, above_m);
+        if (reaches(n1, m1, above_n + n0, above_m + m0)) found(d - 1, n1, m1, above_n + n0, above_m + m0);
+        __syncthreads();
+        T = (T << nbits) | (unsigned)s_bin;
+        left -= nbits;
+        before_n = s_n;
+        before_m = s_m;
+        ids = s_ids;
+        ids_mass = s_mass;
+        __syncthreads();
+    };
+    find_digit();
+    while (left > 0) {
+        if (ids == 1u) {      // its mass is its count
+            T = ids_mass;
+            break;
+        }
+        left = skip_common_bits(T, left, ones, zeros);
+        if (left == 0) break;
+        nbits = left < kDigitBits ? left : kDigitBits;
+        clear();
+        constexpr int kInFlight = 8;
+        for (unsigned x0 = 0; x0 < (unsigned)V; x0 += kInFlight * kRankSortThreads) {
+            unsigned long long cx[kInFlight];
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) {
+                const unsigned x = x0 + u * kRankSortThreads + tid;
+                cx[u] = x < (unsigned)V ? (unsigned long long)counts[x] : 0ull;
+            }
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u)
+                wave_tally_mass(h, m, 0, (int)((cx[u] >> (left - nbits)) & low_bits(nbits)), (cx[u] >> left) == T, cx[u]);
+        }
+        __syncthreads();
+        find_digit();
+    }
+    if (tid == 0) finish(T, before_n, before_m);
 }
 
 }  // namespace
