@@ -202,9 +202,11 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     float lm = -INFINITY, ls = 0.f;
     load_stretch<VEC>(zr, 0, k, tid, v);
     unsigned T, Mo;
-    if constexpr (!SIFT) {
+    if constexpr (MODE == kRowWhole) {
         fold_stretch(v, lm, ls);
-        for (int base = kRowSpan; MODE == kRowTwice && base < k; base += kRowSpan) {
+    } else if constexpr (MODE == kRowTwice) {
+        fold_stretch(v, lm, ls);
+        for (int base = kRowSpan; base < k; base += kRowSpan) {
             load_stretch<VEC>(zr, base, k, tid, v);
             fold_stretch(v, lm, ls);
         }
@@ -233,9 +235,12 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     const float Tf = threshold_f32(T);
 
     // ---- pass 2: every logit >= T is a candidate
-    if constexpr (!SIFT) {
-        for (int base = 0; base < (MODE == kRowTwice ? k : 1); base += kRowSpan) {
-            if (MODE == kRowTwice) load_stretch<VEC>(zr, base, k, tid, v);
+    if constexpr (MODE == kRowWhole) {
+        collect_stretch<VEC, SIFT>(v, 0, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+        __syncthreads();
+    } else if constexpr (MODE == kRowTwice) {
+        for (int base = 0; base < k; base += kRowSpan) {
+            load_stretch<VEC>(zr, base, k, tid, v);
             collect_stretch<VEC, SIFT>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
         }
         __syncthreads();
