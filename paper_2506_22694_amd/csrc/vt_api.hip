@@ -678,11 +678,11 @@ int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_ty
                       p.off_hpack != 0 ? "pack_h_kernel + " : "", p.NT <= 8 ? 1 : 2, p.nlists, 16 * p.row_groups);
     } else {
         // (the second template argument: the most waves of the instantiation)
-        std::snprintf(head, sizeof head, "head_mfma_kernel<%d,%d> workgroups=%d tile_rows=%d waves=%d column_split=%d", p.NT,
+        std::snprintf(head, sizeof head, "head_mfma_kernel<%d,%d> workgroups=%d tile_rows=%d waves=%d column_split=%d%s", p.NT,
                       p.nwaves == vt::kStepWaves                         ? vt::kStepWaves
                       : p.NT > 1 && p.nwaves <= vt::kMfmaFewWaves ? vt::kMfmaFewWaves
                                                                          : vt::kMfmaMaxWaves,
-                      p.nlists, 16 * p.row_groups + p.extra_rows, p.nwaves, p.ksplit);
+                      p.nlists, 16 * p.row_groups + p.extra_rows, p.nwaves, p.ksplit, p.twin ? " workgroups_per_cu=2" : "");
     }
     const char *tail = p.row_select ? " + row_select_kernel" : " + step_finalize_kernel";
     char groups[48] = "";

@@ -62,7 +62,7 @@ __device__ __forceinline__ void wait_unit(u32x4 (&b)[4]) {
 }
 
 // MAXW: most waves a workgroup of this instantiation is launched with.  Eight is the rule: a wave per 16 rows of a
-// 128-row tile.  Up to 8 hidden rows (NT = 1, all of h in LDS) the workgroup may have any number of waves up to
+// 128-row tile.  With all of h in LDS the workgroup may have any number of waves up to
 // MAXW = 12: the tile is then 16 * (waves / KS) rows, so that a head of any size up to 256 * 192 rows is cut into
 // at most 256 tiles -- one round on 256 CUs -- instead of a second, nearly empty round of 128-row tiles.
 // XG (eight waves, up to 8 hidden rows, d a multiple of 1024): the tile has 128 + extra_rows rows.  The rows past
@@ -70,24 +70,23 @@ __device__ __forceinline__ void wait_unit(u32x4 (&b)[4]) {
 // all waves stream equal shares whatever the tile height is -- a head of k = 32975 rows is 256 tiles of 129 rows,
 // one per CU, instead of 258 tiles of 128.  To keep a row's logit independent of the group it lies in, every logit is
 // then formed from the partial sums P0 .. P7 of the eight column parts, each accumulated from zero in ascending
-// order, as ((P0 + P1) + (P2 + P3)) + ((P4 + P5) + (P6 + P7)) -- in registers for a wave's own rows (two parts make
-// one of the ranges described below), from LDS for the shared group.  All waves march over the columns of their
+// order, as ((P0 + P1) + (P2 + P3)) + ((P4 + P5) + (P6 + P7)) -- in registers for a wave's own rows (the parts are
+// the ranges described below), from LDS for the shared group.  All waves march over the columns of their
 // own rows in step, as without the shared group.  (Measured alternatives at k = 32975, n = 8, d = 3072 / 4096:
 // this kernel 40.1 / 54.0 us; every wave starting at another part, the eight partial sums kept in registers:
 // 40.8 / 57.4; all rows cut into near-equal groups whose (group, part) tasks are dealt to the waves: 40.8 / 50.5;
 // nine waves of 16 rows on 229 CUs: 41.4 / 51.4; the small-n kernel: 41.8 / 51.7.  The planner uses it where rows
 // are not a multiple of 2 KiB.)
 // MH: the tiles of several heads in one launch (see MultiHeadTable); one group of hidden rows, all of h in LDS.
-template <int NT, int MAXW, bool XG = false, bool MH = false>
+template <int MAXW, bool XG = false, bool MH = false>
 __global__ void __launch_bounds__(MAXW *kWave) __attribute__((amdgpu_waves_per_eu(1, (MAXW + 3) / 4)))
 head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, SingleHead> mh) {
-    static_assert(NT == 1, "one group of 16 hidden rows");
     static_assert(!MH || !XG, "several heads per launch: plain tiles");
     static_assert(!XG || MAXW == kStepWaves, "the shared row group is built for eight waves");
     extern __shared__ __align__(16) unsigned char smem[];
     const int NW = MAXW == kStepWaves ? kStepWaves : a.nwaves;     // waves of this workgroup
     unsigned char *stage = smem;                       // [waves][2][16][272]
-    unsigned char *hbuf = smem + (size_t)NW * 2 * kStageUnitBytes;   // [16 * NT or 8][hpitch]
+    unsigned char *hbuf = smem + (size_t)NW * 2 * kStageUnitBytes;   // [8][hpitch]
     float *zt = reinterpret_cast<float *>(smem);       // logit tile, aliases both after the contraction
 
     const int lane = lane_id();
@@ -175,11 +174,10 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     };
     u32x4 areg[kPrefetchUnits][4];
 
-    f32x4 acc[NT];
-    RangeSums<NR, NT> sums;
+    f32x4 acc[1];
+    RangeSums<NR, 1> sums;
     sums.clear();
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    acc[0] = f32x4{0.f, 0.f, 0.f, 0.f};
     int closed = 0;        // ranges finished so far
     int in_range = 0;      // units of the open range done so far
     f32x4 own = f32x4{0.f, 0.f, 0.f, 0.f};      // XG: the logits of the wave's own rows
@@ -191,10 +189,10 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     const int rd_off = lrow * kStagePitch + lgrp * 16;
     // up to 8 hidden rows: LDS holds 8 rows of h and lanes 8..15 of the operand repeat them (their products
     // are never read)
-    const int hrows = a.n <= 8 ? 8 : 16 * NT;
+    constexpr int hrows = 8;
     const int hrow_off = (lrow & (hrows - 1)) * a.hpitch + lgrp * 16;
 
-    // ---- h chunks: the columns of KC / 128 consecutive steps, of every hidden row (zero rows up to 16 * NT), live in LDS.  The next
+    // ---- h chunks: the columns of KC / 128 consecutive steps, of every hidden row (zero rows up to 8), live in LDS.  The next
     // chunk is fetched into registers while the current one is consumed, so its L2 latency is hidden;
     // two barriers per chunk swap it in.
     const int units_per_chunk = a.KC / kUnitCols;
@@ -297,22 +295,16 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
         // once per pair and not once per MFMA
 #pragma unroll
         for (int kp = 0; kp < 4; kp += 2) {
-            u32x4 av[2], bv[2][NT];
+            u32x4 av[2], bv[2];
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 av[ks] = *reinterpret_cast<const u32x4 *>(sb + rd_off + (kp + ks) * 64);
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    bv[ks][t] = *reinterpret_cast<const u32x4 *>(hb + (size_t)t * 16 * a.hpitch + (kp + ks) * 64);
+                bv[ks] = *reinterpret_cast<const u32x4 *>(hb + (kp + ks) * 64);
             }
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[ks]),
-                                                                     __builtin_bit_cast(bf16x8, bv[ks][t]), acc[t],
-                                                                     0, 0, 0);
-            }
+            for (int ks = 0; ks < 2; ++ks)
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[ks]),
+                                                                 __builtin_bit_cast(bf16x8, bv[ks]), acc[0], 0, 0, 0);
         }
         ++u;
     };
@@ -358,17 +350,13 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     // ---- logits of this tile -> LDS tile zt[i][t] (aliases staging and h)
     __syncthreads();
     const int tp = (XG ? kMfmaTileRows + 16 : MAXW == kStepWaves ? kMfmaTileRows : tile_rows) + 1;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int i = 16 * t + lrow;       // hidden row of this lane
-        if (i < a.n) {
-            float *dst = zt + ((size_t)ksi * a.n + i) * tp + 16 * rg + 4 * lgrp;      // partial ksi of row i
-            const f32x4 v = XG ? own : acc[t];
-            dst[0] = v.x;
-            dst[1] = v.y;
-            dst[2] = v.z;
-            dst[3] = v.w;
-        }
+    if (lrow < a.n) {                      // hidden row of this lane
+        float *dst = zt + ((size_t)ksi * a.n + lrow) * tp + 16 * rg + 4 * lgrp;      // partial ksi of the row
+        const f32x4 v = XG ? own : acc[0];
+        dst[0] = v.x;
+        dst[1] = v.y;
+        dst[2] = v.z;
+        dst[3] = v.w;
     }
     if constexpr (XG) {
         // the shared group: the eight waves' partials xq[part][hidden row][16] behind the tile and its candidate
@@ -411,9 +399,7 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
         const size_t ztile = ((size_t)KS * a.n * tp * sizeof(float) + 15) & ~(size_t)15;
         constexpr int kCandPerWave = (MAXW > kStepWaves || XG) ? 3 * kWave : 2 * kWave;      // one key per tile row
         unsigned long long *cand =
-            a.n <= kStepWaves
-                ? reinterpret_cast<unsigned long long *>(smem + (ztile > 8192 ? ztile : 8192)) + (size_t)w * kCandPerWave
-                : nullptr;
+            reinterpret_cast<unsigned long long *>(smem + (ztile > 8192 ? ztile : 8192)) + (size_t)w * kCandPerWave;
         for (int i = w; i < a.n; i += NW) {
             const float *zrow = zt + (size_t)i * tp;
             float *full = a.out_logp_full ? a.out_logp_full + (size_t)i * a.k + row0 : nullptr;
@@ -522,9 +508,9 @@ __global__ void __launch_bounds__(kStepWaves *kWave) step_finalize_kernel(const 
                  f.lse_buf + i, lane);
 }
 
-template <int NT, int MAXW, bool XG = false>
+template <int MAXW, bool XG = false>
 hipError_t launch_mfma_inst(const MfmaArgs &a, size_t lds, hipStream_t st) {
-    auto kern = head_mfma_kernel<NT, MAXW, XG, false>;
+    auto kern = head_mfma_kernel<MAXW, XG, false>;
     static LdsLimitOnce lds_limit;
     hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(kern)}, kMaxDynamicLds);
     if (e != hipSuccess) return e;
@@ -534,7 +520,7 @@ hipError_t launch_mfma_inst(const MfmaArgs &a, size_t lds, hipStream_t st) {
 }
 template <int MAXW>
 hipError_t launch_mfma_multi_inst(const MfmaArgs &a, const MultiHeadTable &t, size_t lds, hipStream_t st) {
-    auto kern = head_mfma_kernel<1, MAXW, false, true>;
+    auto kern = head_mfma_kernel<MAXW, false, true>;
     static LdsLimitOnce lds_limit;
     hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(kern)}, kMaxDynamicLds);
     if (e != hipSuccess) return e;
@@ -568,8 +554,8 @@ hipError_t launch_head_mfma(const MfmaArgs &a, size_t lds, hipStream_t st) {
         if (a.nlists != (a.k + tile_rows - 1) / tile_rows) return hipErrorInvalidValue;
     }
     if ((size_t)a.d * 2 >= ((size_t)1 << 24)) return hipErrorInvalidValue;      // row offsets inside a tile: 24-bit factors
-    if (a.extra_rows != 0) return launch_mfma_inst<1, kStepWaves, true>(a, lds, st);
-    return a.nwaves == kStepWaves ? launch_mfma_inst<1, kStepWaves>(a, lds, st) : launch_mfma_inst<1, kMfmaMaxWaves>(a, lds, st);
+    if (a.extra_rows != 0) return launch_mfma_inst<kStepWaves, true>(a, lds, st);
+    return a.nwaves == kStepWaves ? launch_mfma_inst<kStepWaves>(a, lds, st) : launch_mfma_inst<kMfmaMaxWaves>(a, lds, st);
 }
 
 hipError_t launch_head_mfma_multi(const MfmaArgs &a, const MultiHeadTable &t, size_t lds, hipStream_t st) {

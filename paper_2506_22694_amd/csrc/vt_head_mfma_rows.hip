@@ -77,13 +77,8 @@ struct March {
         const int u = start + s;
         return u >= ns ? u - ns : u;
     }
-    // the stage at which range (rot + j) % NR ends (exclusive; ns = the end of the row)
-    __device__ __forceinline__ int end_of(int j) const {
-        const int r = (rot + j) & (NR - 1);
-        return r == NR - 1 ? ns : bound(r + 1);
-    }
-    // ... and the number of stages in it
-    __device__ __forceinline__ int length_of(int j) const { return end_of(j) - bound((rot + j) & (NR - 1)); }
+    // the number of stages in range (rot + j) % NR, the j-th to be marched through
+    __device__ __forceinline__ int length_of(int j) const { return ((rot + j) & (NR - 1)) == NR - 1 ? ns - (NR - 1) * step : step; }
 };
 
 // Tile logits in LDS: hidden row i at i * pitch floats.
@@ -286,13 +281,13 @@ head_mfma_kernel(const MfmaArgs a) {
 }
 
 // ---------------------------------------------------------------- 65 .. 256 hidden rows
-// Tiles of 32 * MT rows by 64 * NTT hidden rows (NH = 1: up to 128, 2: up to 256), eight waves as a 2 x 4 grid of (16 * MT) x (16 * NTT) each: with more hidden
+// Tiles of 32 * MT rows by 64 * NTT hidden rows, eight waves as a 2 x 4 grid of (16 * MT) x (16 * NTT) each: with more hidden
 // rows than 64 the operand reads of a wave per row group would exceed the LDS rate.  Per stage and wave there are two
 // k-steps of MT * NTT products; the operands of one are read while the other is multiplied, the barrier that hands the
 // slot on sits between them, and the loads of the freed slot are spread over the products that follow it -- issued
 // in one go they kept the wave from its products (n = 256, k = 32768, d = 8192: 149 against 140 us).
 // PACKED: h was re-laid by pack_h_kernel, a stage's pieces one after the other as they lie in LDS.
-template <int NH, int MT, int NTT, int NST, int NR, bool PACKED>
+template <int MT, int NTT, int NST, int NR, bool PACKED>
 __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const MfmaArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int TM = 32 * MT, TN = 64 * NTT;
@@ -527,8 +522,8 @@ constexpr int wide_ranges(int MT, int NTT) {
 }
 template <int MT, int NTT>
 hipError_t launch_wide(const MfmaArgs &a, size_t lds, hipStream_t st) {
-    constexpr int NST = wide_stages(MT, NTT), NR = wide_ranges(MT, NTT), NH = (NTT + 1) / 2;
-    if (a.hpack == nullptr) return launch_tile<head_mfma_wide_kernel<NH, MT, NTT, NST, NR, false>>(a, kStepWaves * kWave, lds, st);
+    constexpr int NST = wide_stages(MT, NTT), NR = wide_ranges(MT, NTT);
+    if (a.hpack == nullptr) return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, NR, false>>(a, kStepWaves * kWave, lds, st);
     if constexpr (NTT == 4) {
         const int pieces = 8 * NTT;
         const long long total = (long long)(a.d / kStageCols) * pieces * kWave;
@@ -536,7 +531,7 @@ hipError_t launch_wide(const MfmaArgs &a, size_t lds, hipStream_t st) {
                            static_cast<u32x4 *>(a.hpack), a.n, a.d, pieces, total);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        return launch_tile<head_mfma_wide_kernel<NH, MT, NTT, NST, NR, true>>(a, kStepWaves * kWave, lds, st);
+        return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, NR, true>>(a, kStepWaves * kWave, lds, st);
     }
     return hipErrorInvalidValue;
 }

@@ -732,7 +732,8 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
 
 // ------------------------------------------------------------------ merge of many lists (eight waves per hidden row)
 // More keys than one wave holds in registers (more than 256 lists, or more than 3072 keys): the row's workgroup of
-// eight waves holds them all (up to 2048 lists and 16384 keys; a head of 262144 rows has at most 1490 and 11920), one key per load and thread, and selects by threshold like the direct merge above.  The
+// eight waves holds them all (up to 2048 lists and 16384 keys, what the
+// largest head has in tiles of 128 rows with 8 tokens), one key per load and thread, and selects by threshold like the direct merge above.  The
 // waves form the groups: each finds the ceil(m / 8)-th largest of its lanes' best logits, so at least m keys reach T,
 // the smallest of the eight values -- about three times m do.  They are compacted into `cand` and ranked by counting.
 // What it replaces there, one wave that merges 256 sorted lists at a time in m dependent rounds, was bound by those
@@ -745,6 +746,8 @@ constexpr int kBlockMergeThreads = kBlockMergeWaves * kWave;
 constexpr int kBlockMergeMaxKeys = 32 * kBlockMergeThreads;
 constexpr int kBlockMergeMaxLists = 4 * kBlockMergeThreads;
 constexpr int kBlockMaxCand = 1024;
+static_assert(kStepMaxK / kMfmaTileRows <= kBlockMergeMaxLists && kStepMaxK / kMfmaTileRows * kRowSelectMinLManyRows <= kBlockMergeMaxKeys,
+              "the lists of the largest head in tiles of 128 rows");
 
 struct BlockMergeLds {
     unsigned long long cand[kBlockMaxCand];
