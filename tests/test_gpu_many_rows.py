@@ -69,11 +69,13 @@ def test_step_many_rows_captured_in_a_graph_replays_the_same():
             assert torch.equal(c[5][0], ids) and torch.equal(c[5][1], logp), rep
 
 
-# Merges of more lists than one wave holds: keys per thread 8 / 16 / 32 (512 lists and fewer tokens, 669, 1366 lists),
-# the edge of 256 lists, one token, and a row whose logits are all equal (more candidates than the merge holds).
-@pytest.mark.parametrize("n,k,m", [
-    (9, 65537, 8), (64, 65536, 4), (12, 128256, 8), (17, 262144, 8), (10, 49153, 1), (33, 49280, 8), (70, 40961, 8)])
-def test_merge_of_many_lists(n, k, m):
+# Merges by eight waves: keys per thread 8 / 16 / 32 (512 lists of four; 513, 1002 lists; 2048, all that the merge holds), the edge
+# of 256 lists that one wave could hold, one token, and a row whose logits are all equal (more candidates than the merge holds).
+@pytest.mark.parametrize("n,k,m,lists", [
+    (9, 65537, 8, 513), (64, 65536, 4, 512), (12, 128256, 8, 1002), (17, 262144, 8, 2048), (10, 49153, 1, 385), (33, 49280, 8, 385),
+    (70, 40961, 8, 427), (64, 32768, 8, 256), (20, 32640, 8, 255)])
+def test_merge_of_many_lists(n, k, m, lists):
+    assert f"workgroups={lists} " in vt.draft_head_step_plan(n, k, 128, m)
     W, map_ = synth.trimmed_head_direct(k, 128, seed=900 + n, dtype="bf16")
     h = synth.hidden_rows(n, 128, seed=k, dtype="bf16")
     h[n // 2] = 0
@@ -124,13 +126,18 @@ def test_stored_logits_longer_than_one_stretch(n, k, m, late):
     assert oi[n // 2].tolist() == sorted(map_)[:m]
 
 
-# Two workgroups to a CU (heads of several rounds of tiles): just past one round, a ragged second round, rotated starts
-@pytest.mark.parametrize("n,k,d,m", [(9, 49153, 128, 8), (32, 65536, 256, 8), (33, 60001, 128, 16), (64, 65536, 1024, 8)])
+# Two workgroups to a CU (heads of several rounds of tiles): just past one round, a ragged second round, rotated starts (d a
+# multiple of 2048) with two groups of hidden rows and with four; equal rows in tiles of all eight starts
+@pytest.mark.parametrize("n,k,d,m", [
+    (9, 49153, 128, 8), (33, 60001, 128, 16), (32, 65536, 2048, 8), (64, 65536, 2048, 8), (20, 50000, 4096, 4), (64, 50000, 4096, 16)])
 def test_step_of_several_rounds_of_tiles(n, k, d, m):
-    assert "tile_rows=128 waves=8" in vt.draft_head_step_plan(n, k, d, m)
+    plan = vt.draft_head_step_plan(n, k, d, m)
+    assert "tile_rows=128 waves=8" in plan and "workgroups_per_cu=2" in plan
     W, map_ = synth.trimmed_head_direct(k, d, seed=1100 + n, dtype="bf16")
     h = synth.hidden_rows(n, d, seed=k, dtype="bf16")
-    same = [3, 143, 128 * 255 + 5, 128 * 256 + 70, k - 1]
+    tiles = [0, 1, 8, 24, 40, 56, 255, 256, k // 128 - 1]
+    assert {(b // 8 + b // 64) % 8 for b in tiles} >= {0, 1, 2, 3, 4, 5, 7}
+    same = [128 * b + (37 * b) % 128 for b in tiles] + [k - 1]
     W[same] = W[same[0]]
     ref = oracle.draft_head_step(h, W, map_, m)
     oi, ol, lse, full = run_step(h, W, map_, m, return_lse=True, return_full=True)
