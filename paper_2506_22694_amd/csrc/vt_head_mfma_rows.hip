@@ -62,7 +62,7 @@ __device__ __forceinline__ void wait_stage_and_sync(int younger) {
 // Where a workgroup's march over ns stages starts and where its ranges end.
 template <int NR>
 struct March {
-    int ns, rot, start, step;
+    int ns, rot, start, step, last, last_length;
     bool rotate;
     __device__ __forceinline__ March(int ns_, int d) : ns(ns_) {
         rotate = NR > 1 && d % 2048 == 0 && (NR > 2 || d >= 4096);
@@ -70,6 +70,8 @@ struct March {
         // stages from one start to the next
         step = NR == 2 ? 16 : range_step<NR>(ns, d);
         start = bound(rot);
+        last = NR - 1 - rot;
+        last_length = ns - bound(NR - 1);
     }
     __device__ __forceinline__ int bound(int r) const { return r * step; }
     // stage of the row that is multiplied at step s < ns
@@ -78,7 +80,7 @@ struct March {
         return u >= ns ? u - ns : u;
     }
     // the number of stages in range (rot + j) % NR, the j-th to be marched through
-    __device__ __forceinline__ int length_of(int j) const { return ((rot + j) & (NR - 1)) == NR - 1 ? ns - (NR - 1) * step : step; }
+    __device__ __forceinline__ int length_of(int j) const { return j == last ? last_length : step; }
 };
 
 // Tile logits in LDS: hidden row i at i * pitch floats.
