@@ -4,28 +4,29 @@
 // Rank order = all V ids sorted by (count descending, id ascending), the order in which
 // Top-K(c, k) takes ids; every prefix is the selection for a smaller k.
 //
-// rsort_*: stable LSD radix sort over the whole device of (code, id) pairs, 8 bits per pass.  The code (vt_code.h) is
-//   the count itself below 2^19 and its 19 highest bits with their exponent above -- 24 bits, three passes for any
-//   int64.  The ids start ascending and every pass is stable, so equal codes stay in ascending-id order; where counts
-//   of 2^19 and more share a code (a handful of ids, if any) the last kernel orders the run: up to 16 ids by counting in
-//   each id's thread, up to 256 in a wave, up to 1024 in a workgroup, longer ones by radix passes of one workgroup (time
-//   grows with the run and not with its square).
-//   Where all counts of 2^19 and more agree above their 23 low bits (and have bits there) their code is those bits
-//   instead, which leaves out nothing: every kernel derives that from what the first one found.
-//   One workgroup per 1024 consecutive elements; a wave takes 64 consecutive elements, lanes with
-//   equal digits find each other with nine ballots and rank themselves by population count, so
-//   "earlier in the input" is (workgroup, wave, lane) order and no per-thread histogram is needed.
-//     rsort_init     pairs from the counts, the digit totals of the three passes, per-workgroup digits of the first
-//     rsort_hist     per-workgroup digit histogram of a later pass
-//     rsort_scatter  every workgroup derives its own output offsets from the histogram table
-//                    (sum over earlier digits and over earlier workgroups), then scatters
-//     rsort_out      the ids in order
-//   Eight launches in a fixed sequence; nothing is read back.  A pass whose digit is the same for every key moves
-//   nothing and is skipped: each kernel derives that, and which buffer holds the data, from the digit totals alone.
-//   (Eight passes over the bytes of the counts, nineteen launches, took 72 us at V = 128256 after 10^7 tokens; now 43.)
-//   V = 128256: after 10^11 tokens 47 us (86 with two global atomics per large count, 95 over the bytes); all counts in
-//   2^40 .. 2^40 + 2^20 48 (74; V = 32000 40, 6475 with every thread walking its run, 56); half of them in
-//   2^35 .. 2^35 + 2^13 52 (75).  Slower than over the bytes: runs of 200 to 400 ids, V = 32000 around 2^19, 95 (441, 55).
+// rank_*: a counting sort over bins that follow the counts, then a sort inside the bins that hold several values.
+//   Counts below 2048 have a bin each (all but a few hundred of a vocabulary's counts, after 10^7 tokens).  Larger counts are
+//   told apart by up to 512 splitters, counts of a fixed sample of 1024 ids (every second one where more of them are large): a bin for every splitter's own value and one
+//   for what lies between two of them, so that a bin of several values holds a few hundred ids wherever the counts lie, and
+//   values that many ids share have bins of their own.
+//   One workgroup per 1024 consecutive ids; "earlier in the input" is (workgroup, wave, lane) order, so that equal counts
+//   stay in ascending-id order:
+//     rank_hist     every workgroup sorts the sample (the same one) and tallies its ids per bin
+//     rank_scan     sums the tallies up over the workgroups, bin by bin
+//     rank_scatter  places every id: its bin, the workgroups before, the waves before (a byte per bin and wave in LDS), the
+//                   lanes before (lanes of one bin find each other with twelve ballots).  Ids of one-value bins go to the
+//                   result at once
+//     rank_runs     a workgroup per bin of several values orders its ids by (count, id) in LDS; more than 8192 of them, or
+//                   counts 2^51 apart, by radix passes of that workgroup
+//   Four launches in a fixed sequence, nothing read back; launches are most of what it costs (a kernel of the chain 3 to 4 us,
+//   whatever it does).  Up to 8192 ids the last kernel alone, on one bin of all ids.
+//   Against eight launches of LSD passes over 24-bit codes (us): V = 128256 after 10^7 tokens 43.8 -> 18.9, 10^9 44 -> 25, 10^11
+//   47 -> 31; uniform below 2^20 53 -> 34, in 2^40 .. 2^40 + 2^20 49 -> 31, half of them in 2^35 .. 2^35 + 2^13 52 -> 37; V = 32000
+//   after 10^7 35 -> 17; V = 10^6 138 -> 42.  Slower at V = 10^6, where a bin between splitters holds 2000 ids, for counts below
+//   4000 in equal shares (103 -> 130) and for equal counts of 2048 and more (52 -> 57).
+//   The splitters are sorted in every workgroup: a launch of its own for them costs more than the 5 us that 1024 large samples
+//   take (a handful, as a rule: half a microsecond).  512 samples instead of 1024 take 2 us less there and leave bins twice as
+//   long (2^40 .. 2^40 + 2^20: 56 against 31).
 // choose_*: no sort: a histogram over bins of counts (exact below 2048) with the mass of every bin, walked from the
 //   largest counts down to the bin in which the mass reaches ceil(P * total).  With the read-back of k 107 us behind a full
 //   sort, now 31.  Where that bin holds several values all workgroups histogram the next eleven bits of its ids, and the
@@ -45,288 +46,296 @@ inline size_t round256(size_t x) { return (x + 255) / 256 * 256; }
 
 constexpr int kSortWaves = kRankSortThreads / kWave;   // 16
 constexpr int kDigits = 256;
-constexpr int kPasses = 3;
-constexpr unsigned kRankExact = 1u << 19;      // codes below are counts
+constexpr int kSplitters = 512;
+constexpr int kWideBins = 2 * kSplitters + 4;                // 2 i: counts between splitters i - 1 and i, 2 i + 1: splitter i (2 kSplitters + 1 of them)
+constexpr int kRankBins = kWideBins + kBinExact;             // from the largest counts down
+constexpr int kBinWords = kRankBins / 4;                     // by fours
+static_assert(kRankBins % 4 == 0 && kWideBins % 4 == 0 && kBinWords <= kRankSortThreads && kRankBins <= 1 << 12, "four bins to a thread");
+constexpr int kScanBlocks = (kRankBins + kWave - 1) / kWave;
+constexpr int kRunMax = 8192;         // ids that are ordered in LDS: keys of 51 bits of count and 13 of place
+constexpr int kPlaceBits = 13;
+static_assert(kRunMax == 1 << kPlaceBits);
 
-struct SortBufs {
-    unsigned long long *pairs[2];      // code << 32 | id
-    unsigned *gtot;      // [2][kPasses][kDigits] digit totals over all elements, and what is added for the codes of low bits
-    // of the counts >= kRankExact: the bits that their codes leave out, set in any of them and clear in any, and the same of
-    // the bits above the low ones
-    unsigned long long *rest;      // [4]
-    unsigned *hist;      // [nblk][kDigits] per-workgroup digit counts of the current pass, descending digit first
-    unsigned *hist_low;  // ... and of the first pass with codes of low bits
+struct RankBufs {
+    unsigned *rows;                // [nblk][kRankBins] ids of every workgroup per bin; after rank_scan those of the workgroups before
+    unsigned *totals;              // [kRankBins]
+    unsigned *start;               // [kWideBins] place of the first id of each bin of large counts
+    unsigned long long *splitters; // [kSplitters] descending, zeros behind
+    unsigned long long *pairs[2];  // ids of the bins of several values, by place; what the radix passes move them to (where `rows` are)
 };
-constexpr int kTotals = 2 * kPasses * kDigits;
-constexpr int kLowBits = 23;
-// the code of low bits of a count >= kRankExact, above all smaller counts' codes
-__device__ __forceinline__ unsigned low_code(unsigned long long c) { return (1u << kLowBits) | ((unsigned)c & ((1u << kLowBits) - 1u)); }
 
-// lanes of the wave whose `dgt` (0..256, 256 = not an element) equals this lane's
-__device__ __forceinline__ unsigned long long match_digit9(int dgt) {
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+// lanes of the wave whose value agrees with this one's in the lowest BITS bits
+template <int BITS>
+__device__ __forceinline__ unsigned long long match_lanes(int v) {
     unsigned long long m = ~0ull;
 #pragma unroll
-    for (int b = 0; b < 9; ++b) {
-        const bool bit = (dgt >> b) & 1;
+    for (int b = 0; b < BITS; ++b) {
+        const bool bit = (v >> b) & 1;
         const unsigned long long B = __ballot(bit);
         m &= bit ? B : ~B;
     }
     return m;
 }
-__device__ __forceinline__ int lanes_below(unsigned long long m) {
-    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+
+// The value of lane `lane ^ X`.
+template <int X>
+__device__ __forceinline__ unsigned lane_xor(unsigned v, int lane) {
+    if constexpr (X == 1) return dpp_mov<0xB1>(v);                      // quad_perm [1,0,3,2]
+    else if constexpr (X == 2) return dpp_mov<0x4E>(v);                 // quad_perm [2,3,0,1]
+    else if constexpr (X == 4) return dpp_mov<0x1B>(dpp_mov<0x141>(v)); // row_half_mirror, quad_perm [3,2,1,0]
+    else if constexpr (X == 8) return dpp_mov<0x128>(v);                // row_ror:8
+    else if constexpr (X == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (lane & 16) != 0 ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return (lane & 32) != 0 ? r[0] : r[1];
+    }
+}
+template <int SIZE, int STRIDE>
+__device__ __forceinline__ void wave_sort_steps(unsigned long long &v, int lane) {
+    if constexpr (STRIDE > 0) {
+        const unsigned long long other =
+            ((unsigned long long)lane_xor<STRIDE>((unsigned)(v >> 32), lane) << 32) | lane_xor<STRIDE>((unsigned)v, lane);
+        const bool keep_larger = ((lane & SIZE) == 0 || SIZE == kWave) == ((lane & STRIDE) == 0);
+        v = (other > v) == keep_larger ? other : v;
+        wave_sort_steps<SIZE, STRIDE / 2>(v, lane);
+    } else if constexpr (SIZE < kWave) {
+        wave_sort_steps<2 * SIZE, SIZE>(v, lane);
+    }
 }
 
-// A pass is idle iff one digit bin holds all n elements.  Every wave of every kernel evaluates this
-// the same way from the digit totals (call with all 64 lanes active).
-__device__ __forceinline__ bool pass_active(const unsigned *__restrict__ gtot, int p, int n) {
-    bool idle = false;
-    for (int d = (int)threadIdx.x & 63; d < kDigits; d += kWave) idle |= gtot[p * kDigits + d] == (unsigned)n;
-    return __ballot(idle) == 0ull;
-}
-// Buffer (0 or 1) that holds the data before pass p: the parity of the active passes before it.
-__device__ __forceinline__ int source_buffer(const unsigned *__restrict__ gtot, int p, int n) {
-    int moved = 0;
-    for (int q = 0; q < p; ++q) moved += pass_active(gtot, q, n) ? 1 : 0;
-    return moved & 1;
-}
-
-// Every later kernel copies the digit totals (3 KiB) into LDS first: pass_active / source_buffer read them
-// many times over.  Returns whether the codes of counts >= kRankExact are their low bits: the usual ones leave out bits that
-// differ, and all those counts agree above the low bits, in bits that are not all zero (smaller counts share their codes too
-// seldom for the counts to be read again in every pass).
-// differ: the usual codes leave out bits that differ.
-__device__ __forceinline__ bool stage_totals(const SortBufs &b, unsigned *gs, bool &differ) {
-    // (one request for the four words, and no branch on one before the others)
-    const unsigned long long left_out = b.rest[0] & b.rest[1], above = b.rest[2], above_differ = b.rest[2] & b.rest[3];
-    differ = left_out != 0ull;
-    const bool low = (above != 0ull) & (above_differ == 0ull) & differ;      // (uniform)
-    if (threadIdx.x < kPasses * kDigits) {
-        unsigned t = b.gtot[threadIdx.x];      // (requested with the flags)
-        if (low) t += b.gtot[kPasses * kDigits + threadIdx.x];
-        gs[threadIdx.x] = t;
+// Merges R <= 8 neighbouring runs of len = 2^lg values each, all over v[0 .. N): every value looks up how many go ahead of it in
+// the other runs, searches that do not wait for each other.  Up to PER values per thread.
+template <int PER>
+__device__ __forceinline__ void merge_runs(unsigned long long *v, int N, int lg, int R) {
+    const int tid = threadIdx.x, len = 1 << lg;
+    unsigned long long x[PER];
+    int place[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int i = r * kRankSortThreads + tid;
+        x[r] = 0ull;
+        place[r] = 0;
+        if (i >= N) continue;
+        x[r] = v[i];
+        const int run = (i >> lg) & (R - 1);
+        const unsigned long long *first = v + (i & ~(R * len - 1));
+        place[r] = (i & ~(R * len - 1)) + (i & (len - 1));
+        int ahead[8] = {};
+        // (steps len / 2, .., 2, 1 and 1 once more: as many as len values go ahead)
+        for (int l = lg - 1; l >= -1; --l) {
+            const int step = 1 << max(l, 0);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (q < R) {      // (uniform)
+                    const unsigned long long t = first[(q << lg) + ahead[q] + step - 1];
+                    ahead[q] += t > x[r] || (t == x[r] && q < run) ? step : 0;      // of equal values the earlier run's go ahead
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) place[r] += q < R && q != run ? ahead[q] : 0;
     }
     __syncthreads();
-    return low;
-}
-static_assert(kPasses * kDigits <= kRankSortThreads, "one total per thread");
-// What a pass sorts the element of this pair by.
-__device__ __forceinline__ unsigned sort_key(unsigned long long pair, bool low, const long long *__restrict__ counts) {
-    const unsigned code = (unsigned)(pair >> 32);
-    return low && code >= kRankExact ? low_code((unsigned long long)counts[(unsigned)pair]) : code;
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        if (r * kRankSortThreads + tid < N) v[place[r]] = x[r];
+    }
+    __syncthreads();
 }
 
-__global__ void __launch_bounds__(kRankSortThreads) rsort_zero_kernel(unsigned *gtot) {
-    for (int i = threadIdx.x; i < kTotals + 8; i += kRankSortThreads) gtot[i] = 0u;      // (and `rest` behind them)
+// Sorts v[0 .. N) in LDS, largest first; N a power of two, 64 .. kRunMax.  All threads of the workgroup call it behind a
+// barrier and find the result behind another.  64 values at a time are sorted in a wave's registers, then runs are merged,
+// eight at a time, longer ones four (fewer searches per value, where there are several values per thread).
+// 512 values by bitonic steps in LDS took 10 us, this way 1.5.
+__device__ __forceinline__ void sort_descending(unsigned long long *v, int N) {
+    const int lane = lane_id();
+    for (int i = threadIdx.x; i < N; i += kRankSortThreads) {
+        unsigned long long x = v[i];
+        wave_sort_steps<2, 1>(x, lane);
+        v[i] = x;
+    }
+    __syncthreads();
+    if (N <= kRankSortThreads) {
+        if (N > kWave) merge_runs<1>(v, N, 6, min(N >> 6, 8));
+        if (N > 8 * kWave) merge_runs<1>(v, N, 9, N >> 9);
+    } else {
+        constexpr int kPer = kRunMax / kRankSortThreads;
+        merge_runs<kPer>(v, N, 6, 8);
+        merge_runs<kPer>(v, N, 9, min(N >> 9, 4));
+        if (N > 32 * kWave) merge_runs<kPer>(v, N, 11, N >> 11);
+    }
 }
+__device__ __forceinline__ int sort_size(int n) { return n <= kWave ? kWave : 1 << (32 - __clz(n - 1)); }
 
-__global__ void __launch_bounds__(kRankSortThreads) rsort_init_kernel(const long long *__restrict__ counts, int n,
-                                                                      SortBufs b) {
-    __shared__ unsigned h[kTotals];
-    __shared__ unsigned long long s_rest[4];
-    const int j = blockIdx.x * kRankSortThreads + threadIdx.x;
+// The id whose count is sample i of 1024: one of every n / 1024 neighbours, not the same of all.
+__device__ __forceinline__ int sample_id(int i, int n) {
+    const unsigned long long at = ((unsigned long long)i << 16) | ((unsigned)(i * 40503) & 0xFFFFu);
+    return (int)(at * (unsigned)n / ((unsigned long long)kRankSortThreads << 16));
+}
+// The bin of a count; sp: the splitters in LDS.
+__device__ __forceinline__ int rank_bin(unsigned long long c, const unsigned long long *sp) {
+    if (c < kBinExact) return kRankBins - 1 - (int)c;
+    int i = 0;                            // splitters above c
+#pragma unroll
+    for (int step = kSplitters / 2; step > 0; step >>= 1) i += sp[i + step - 1] > c ? step : 0;
+    i += sp[i] > c ? 1 : 0;
+    return 2 * i + (i < kSplitters && sp[min(i, kSplitters - 1)] == c ? 1 : 0);
+}
+__device__ __forceinline__ bool one_value(int bin) { return bin >= kWideBins || (bin & 1) != 0; }
+
+__global__ void __launch_bounds__(kRankSortThreads) rank_hist_kernel(const long long *__restrict__ counts, int n, RankBufs b) {
+    __shared__ unsigned h[kRankBins];
+    __shared__ unsigned long long sp[kRankSortThreads];
+    __shared__ int s_n;
+    const int tid = threadIdx.x;
+    const int j = blockIdx.x * kRankSortThreads + tid;
     const bool in = j < n;
     const unsigned long long c = in ? (unsigned long long)counts[j] : 0ull;
-    const unsigned code = count_code<19, 18>(c);
-    for (int i = threadIdx.x; i < kTotals; i += kRankSortThreads) h[i] = 0u;
-    if (threadIdx.x < 4) s_rest[threadIdx.x] = 0ull;
+    const unsigned long long v = (unsigned long long)counts[sample_id(tid, n)];
+    for (int i = tid; i < kRankBins; i += kRankSortThreads) h[i] = 0u;
+    sp[tid] = 0ull;
+    if (tid == 0) s_n = 0;
     __syncthreads();
-    if (in) b.pairs[0][j] = ((unsigned long long)code << 32) | (unsigned)j;
-    // the upper digits are the same in nearly every code (zero): when a whole wave agrees on a digit one lane
-    // adds for all, instead of 64 LDS atomics queueing on one address
-    const unsigned long long live = __ballot(in);
-#pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-        const int dg = (int)((code >> (8 * p)) & 255u);
-        const int first = __builtin_amdgcn_readfirstlane(dg);
-        const unsigned long long same = __ballot(in && dg == first);
-        if (same == live && live != 0ull) {
-            if ((threadIdx.x & 63) == (unsigned)(__ffsll((long long)live) - 1))
-                atomicAdd(&h[p * kDigits + dg], (unsigned)__popcll(live));
-        } else if (in) {
-            atomicAdd(&h[p * kDigits + dg], 1u);
-        }
-    }
-    const bool large = code >= kRankExact;
-    const unsigned long long any_large = __ballot(large);
-    if (any_large != 0ull) {
-        const unsigned long long left_out = large ? c & low_bits(63 - __clzll((long long)c) - 18) : 0ull;
-        const unsigned long long r[4] = {left_out, large ? ~left_out : 0ull, large ? c >> kLowBits : 0ull, large ? ~(c >> kLowBits) : 0ull};
-        if (any_large != live) {      // (a few lanes, as a rule)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (large) atomicOr(&s_rest[q], r[q]);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const unsigned long long v = wave_or_u64(r[q]);
-                if ((threadIdx.x & 63) == 0) atomicOr(&s_rest[q], v);
-            }
-        }
-        const unsigned other = low_code(c);
-#pragma unroll
-        for (int p = 0; p < kPasses; ++p) {
-            const unsigned from = (code >> (8 * p)) & 255u, to = (other >> (8 * p)) & 255u;
-            if (large && from != to) {
-                atomicAdd(&h[(kPasses + p) * kDigits + from], ~0u);      // (one less; sums wrap around)
-                atomicAdd(&h[(kPasses + p) * kDigits + to], 1u);
-            }
-        }
+    const unsigned long long large = __ballot(v >= kBinExact);
+    if (large != 0ull) {
+        int at = 0;
+        if ((tid & 63) == 0) at = atomicAdd(&s_n, __popcll(large));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (v >= kBinExact) sp[at + lanes_below(large)] = v;
     }
     __syncthreads();
-    const int tid = threadIdx.x;
-    if (tid < kPasses * kDigits && h[tid] != 0u) atomicAdd(&b.gtot[tid], h[tid]);
-    if (tid < kDigits) {
-        b.hist[blockIdx.x * kDigits + tid] = h[255 - tid];
-        b.hist_low[blockIdx.x * kDigits + tid] = h[255 - tid] + h[kPasses * kDigits + 255 - tid];
+    const int n_sp = s_n;
+    if (n_sp > 1) sort_descending(sp, sort_size(n_sp));
+    if (n_sp > kSplitters) {      // (uniform) every second one
+        const unsigned long long x = sp[(2 * tid + 1) & (kRankSortThreads - 1)];
+        __syncthreads();
+        if (tid < kSplitters) sp[tid] = x;
+        __syncthreads();
     }
-    if (s_rest[3] != 0ull) {      // (uniform) there are counts of 2^19 and more
-        if (tid < 4) atomicOr(&b.rest[tid], s_rest[tid]);
-        if (tid < kPasses * kDigits && h[kPasses * kDigits + tid] != 0u) atomicAdd(&b.gtot[kPasses * kDigits + tid], h[kPasses * kDigits + tid]);
-    }
+    if (blockIdx.x == 0 && tid < kSplitters) b.splitters[tid] = sp[tid];
+    wave_tally(h, rank_bin(c, sp), in);
+    __syncthreads();
+    uint4 *row = reinterpret_cast<uint4 *>(b.rows + (size_t)blockIdx.x * kRankBins);
+    if (tid < kBinWords) row[tid] = *reinterpret_cast<const uint4 *>(h + 4 * tid);
 }
 
-__global__ void __launch_bounds__(kRankSortThreads) rsort_hist_kernel(const long long *__restrict__ counts, int n, int p,
-                                                                      SortBufs b) {
-    __shared__ unsigned h[kDigits];
-    __shared__ unsigned gs[kPasses * kDigits];
-    bool differ;
-    const bool low = stage_totals(b, gs, differ);
-    if (!pass_active(gs, p, n)) return;
-    const int src = source_buffer(gs, p, n);
-    const int j = blockIdx.x * kRankSortThreads + threadIdx.x;
-    const unsigned code = j < n ? sort_key(b.pairs[src][j], low, counts) : 0u;
-    if (threadIdx.x < kDigits) h[threadIdx.x] = 0u;
-    __syncthreads();
-    if (j < n) atomicAdd(&h[255 - (int)((code >> (8 * p)) & 255u)], 1u);
-    __syncthreads();
-    if (threadIdx.x < kDigits) b.hist[blockIdx.x * kDigits + threadIdx.x] = h[threadIdx.x];
+// A workgroup takes 64 bins, a wave ROWS workgroups' rows of them at a time: 8, one round of which covers 131072 ids, or 32 for
+// more (the rounds wait for memory one after the other: V = 10^6 39.8 -> 34.6 us).
+template <int ROWS>
+__global__ void __launch_bounds__(kRankSortThreads) rank_scan_kernel(int nblk, RankBufs b) {
+    __shared__ unsigned part[kSortWaves][kWave];
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
+    const int at = min((int)blockIdx.x * kWave + lane, kRankBins - 1);      // (past the end: the last one again)
+    unsigned carry = 0u;
+    for (int r0 = 0; r0 < nblk; r0 += kSortWaves * ROWS) {
+        unsigned x[ROWS], own = 0u;
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) x[u] = b.rows[(size_t)min(r0 + w * ROWS + u, nblk - 1) * kRankBins + at];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            x[u] = r0 + w * ROWS + u < nblk ? x[u] : 0u;
+            own += x[u];
+        }
+        part[w][lane] = own;
+        __syncthreads();
+        unsigned run = carry;
+#pragma unroll
+        for (int q = 0; q < kSortWaves; ++q) {
+            const unsigned p = part[q][lane];
+            run += q < w ? p : 0u;
+            carry += p;
+        }
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const int r = r0 + w * ROWS + u;
+            if (r < nblk) b.rows[(size_t)r * kRankBins + at] = run;
+            run += x[u];
+        }
+        __syncthreads();
+    }
+    if (w == 0) b.totals[at] = carry;
 }
 
-__global__ void __launch_bounds__(kRankSortThreads) rsort_scatter_kernel(const long long *__restrict__ counts, int n, int p,
-                                                                         SortBufs b) {
-    __shared__ unsigned wcnt[kSortWaves * kDigits];   // [wave][digit]: elements of that digit in earlier waves
-    __shared__ unsigned part[4 * kDigits];            // sums over a quarter of the earlier workgroups
-    __shared__ unsigned offs[kDigits];                // first output slot of this workgroup's run of each digit
-    __shared__ unsigned gs[kPasses * kDigits];
-    bool differ;
-    const bool low = stage_totals(b, gs, differ);
-    if (!pass_active(gs, p, n)) return;
-    const int src = source_buffer(gs, p, n);
-    const unsigned *hist = low && p == 0 ? b.hist_low : b.hist;
+__global__ void __launch_bounds__(kRankSortThreads) rank_scatter_kernel(const long long *__restrict__ counts, int n, int n_ids,
+                                                                        RankBufs b, int *__restrict__ out_ids) {
+    __shared__ __align__(16) unsigned char wcnt[kRankBins * kSortWaves];      // [bin][wave] ids
+    __shared__ __align__(16) unsigned base[kRankBins];      // place of this workgroup's first id of the bin
+    __shared__ unsigned long long sp[kSplitters];
+    __shared__ unsigned part[kSortWaves];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int blk = blockIdx.x;
-
-    // (requested ahead of the offsets: it depends on nothing)
-    const int j = blk * kRankSortThreads + tid;
+    const int j = blockIdx.x * kRankSortThreads + tid;
     const bool in = j < n;
-    const unsigned long long pair = in ? b.pairs[src][j] : 0ull;
-    const unsigned key = in ? sort_key(pair, low, counts) : 0u;
-    for (int i = tid; i < kSortWaves * kDigits; i += kRankSortThreads) wcnt[i] = 0u;
-    // this workgroup's offsets: (elements with an earlier digit anywhere) + (same digit, earlier workgroups)
-    {
-        // (a wave reads 64 digits of one workgroup's row at a time, a quarter of the earlier workgroups per thread)
-        const int d = tid & 255, q = tid >> 8;
-        unsigned before = 0;
-        const int b1 = blk * (q + 1) / 4;
-        const unsigned *col = hist + d;
-        int x = blk * q / 4;
-        for (; x + 16 <= b1; x += 16) {         // sixteen independent loads at a time
-            unsigned t[16];
+    // everything is requested at once: the count, the splitters, and of four bins the totals and what lies before
+    const unsigned long long c = in ? (unsigned long long)counts[j] : 0ull;
+    const unsigned long long splitter = tid < kSplitters ? b.splitters[tid] : 0ull;
+    uint4 tot = make_uint4(0u, 0u, 0u, 0u), bef = tot;
+    if (tid < kBinWords) {
+        tot = reinterpret_cast<const uint4 *>(b.totals)[tid];
+        bef = reinterpret_cast<const uint4 *>(b.rows + (size_t)blockIdx.x * kRankBins)[tid];
+    }
+    for (int i = tid; i < kRankBins * kSortWaves / 16; i += kRankSortThreads) reinterpret_cast<uint4 *>(wcnt)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < kSplitters) sp[tid] = splitter;
+    const unsigned sum = tot.x + tot.y + tot.z + tot.w;
+    unsigned upto = sum;
 #pragma unroll
-            for (int u = 0; u < 16; ++u) t[u] = col[(size_t)(x + u) * kDigits];
+    for (int o = 1; o < kWave; o <<= 1) {
+        const unsigned t = __shfl_up(upto, o);
+        if (lane >= o) upto += t;
+    }
+    if (lane == kWave - 1) part[w] = upto;
+    __syncthreads();
+    unsigned above = upto - sum;
 #pragma unroll
-            for (int u = 0; u < 16; ++u) before += t[u];
-        }
-        for (; x < b1; ++x) before += col[(size_t)x * kDigits];
-        part[q * kDigits + d] = before;
+    for (int q = 0; q < kSortWaves; ++q) above += q < w ? part[q] : 0u;
+    if (tid < kBinWords) {
+        const uint4 first = make_uint4(above, above + tot.x, above + tot.x + tot.y, above + tot.x + tot.y + tot.z);
+        *reinterpret_cast<uint4 *>(base + 4 * tid) = make_uint4(first.x + bef.x, first.y + bef.y, first.z + bef.z, first.w + bef.w);
+        if (blockIdx.x == 0 && tid < kWideBins / 4) reinterpret_cast<uint4 *>(b.start)[tid] = first;
     }
-    unsigned tot = 0, inc = 0;
-    if (tid < kDigits) {
-        tot = gs[p * kDigits + (255 - tid)];          // digit totals in descending-digit order
-        inc = tot;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {         // inclusive scan inside each of the four waves
-            const unsigned t = __shfl_up(inc, o);
-            if (lane >= o) inc += t;
-        }
-        offs[tid] = inc;
-    }
+    const int bin = rank_bin(c, sp);
+    const unsigned long long same = match_lanes<12>(bin) & __ballot(in);
+    const int below = lanes_below(same);
+    if (in && below == 0) wcnt[bin * kSortWaves + w] = (unsigned char)__popcll(same);
     __syncthreads();
-    unsigned my_off = 0;
-    if (tid < kDigits) {
-        unsigned carry = 0;
-        for (int ww = 0; ww < w; ++ww) carry += offs[ww * kWave + kWave - 1];
-        my_off = carry + inc - tot + part[tid] + part[kDigits + tid] + part[2 * kDigits + tid] + part[3 * kDigits + tid];
-    }
-    __syncthreads();
-    if (tid < kDigits) offs[tid] = my_off;
-
-    // ---- ranks inside the workgroup
-    const int dgt = in ? 255 - (int)((key >> (8 * p)) & 255u) : 256;
-    const unsigned long long m = match_digit9(dgt);
-    const int below = lanes_below(m);
-    if (in && below == 0) wcnt[w * kDigits + dgt] = (unsigned)__popcll(m);
-    __syncthreads();
-    if (tid < kDigits) {
-        unsigned run = 0;
-        for (int ww = 0; ww < kSortWaves; ++ww) {
-            const unsigned c = wcnt[ww * kDigits + tid];
-            wcnt[ww * kDigits + tid] = run;
-            run += c;
-        }
-    }
-    __syncthreads();
+    // ids of the bin in the waves before: bytes 0 .. w - 1 of sixteen
+    const uint4 x = *reinterpret_cast<const uint4 *>(wcnt + bin * kSortWaves);
+    auto bytes_before = [&](unsigned v, int first) {
+        const int take = min(max(w - first, 0), 4);
+        return take == 4 ? v : v & ((1u << (8 * take)) - 1u);
+    };
+    unsigned place = base[bin] + (unsigned)below;
+    place = __builtin_amdgcn_sad_u8(bytes_before(x.x, 0), 0u, place);
+    place = __builtin_amdgcn_sad_u8(bytes_before(x.y, 4), 0u, place);
+    place = __builtin_amdgcn_sad_u8(bytes_before(x.z, 8), 0u, place);
+    place = __builtin_amdgcn_sad_u8(bytes_before(x.w, 12), 0u, place);
     if (in) {
-        const unsigned pos = offs[dgt] + wcnt[w * kDigits + dgt] + (unsigned)below;
-        b.pairs[src ^ 1][pos] = pair;
+        if (!one_value(bin))
+            b.pairs[0][place] = (unsigned)j;
+        else if (place < (unsigned)n_ids)
+            out_ids[place] = j;
     }
 }
 
-// ---- runs of equal codes whose counts differ (rsort_out)
-constexpr int kShortRun = 16;                        // ordered by counting in every id's thread
-constexpr int kWaveRun = 4 * kWave;                  // ... in a wave of the workgroup that the run starts in
-constexpr int kGroupRun = kRankSortThreads;          // ... in that workgroup; longer: radix passes
-constexpr int kRunPer = 4;                           // elements per thread and step of those
+// ---- the ids of a bin of several values
+constexpr int kRunPer = 4;                           // elements per thread and step of the radix passes
 constexpr int kRunStep = kRunPer * kRankSortThreads, kRunGroups = kRunStep / kWave;
-
-struct RunLds {
-    int starts[kRankSortThreads / kShortRun + 1], long_starts[kRankSortThreads / kShortRun + 1];
-    int n_starts, n_long, n_same;
+struct RadixLds {
     unsigned long long ones, zeros;
     unsigned base[kDigits];                          // next slot of each digit, descending
     unsigned part[kRunPer * kDigits];
-    union {
-        unsigned long long wave_count[kSortWaves][kWaveRun];      // run_key
-        unsigned long long count[kGroupRun];
-        unsigned short before[kRunGroups * kDigits]; // elements of a digit in the step's groups of 64 before
-    };
+    unsigned short before[kRunGroups * kDigits];     // elements of a digit in the step's groups of 64 before
 };
 
-// (count descending, place in the run ascending) as one number: the bits that a run's counts share may go
-__device__ __forceinline__ unsigned long long run_key(long long c, int place) {
-    return ((unsigned long long)c << 10) | (unsigned)(kGroupRun - 1 - place);
-}
-static_assert(kGroupRun == 1 << 10, "ten bits for the place; codes tell 19 bits apart");
-// f(v[x]) for all x < n, eight of them read at a time (every lane the same one: a broadcast).
-template <typename F>
-__device__ __forceinline__ void for_each_key(const unsigned long long *v, int n, F &&f) {
-    int x = 0;
-    for (; x + 8 <= n; x += 8) {
-        unsigned long long t[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) t[q] = v[x + q];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) f(t[q]);
-    }
-    for (; x < n; ++x) f(v[x]);
-}
-
-// One run [lo, lo + length), longer than kGroupRun, by its counts: LSD passes of this workgroup over the digits in which the
-// counts differ, between the two buffers.  Nobody else touches the run's ids (its codes stay what they are).
-__device__ __forceinline__ void sort_long_run(const long long *__restrict__ counts, const SortBufs &b, int src, unsigned lo,
-                                              unsigned length, int n_ids, int *__restrict__ out_ids, RunLds &s) {
+// Places [lo, lo + length) of pairs[0] by their counts: LSD passes of this workgroup over the digits in which the
+// counts differ, between the two buffers.  Nobody else touches those places.
+__device__ __forceinline__ void sort_by_radix(const long long *__restrict__ counts, const RankBufs &b, unsigned lo,
+                                              unsigned length, int n_ids, int *__restrict__ out_ids, RadixLds &s) {
+    int src = 0;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (tid == 0) s.ones = s.zeros = 0ull;
     __syncthreads();
@@ -391,7 +400,7 @@ __device__ __forceinline__ void sort_long_run(const long long *__restrict__ coun
             load_step(x0);
             unsigned long long same[kRunPer];
 #pragma unroll
-            for (int u = 0; u < kRunPer; ++u) same[u] = match_digit9(dgt[u]);
+            for (int u = 0; u < kRunPer; ++u) same[u] = match_lanes<9>(dgt[u]);
             __syncthreads();            // the step before is done with `before`, `part` and `base`
             for (int i = tid; i < kRunGroups * kDigits / 2; i += kRankSortThreads) reinterpret_cast<unsigned *>(s.before)[i] = 0u;
             __syncthreads();
@@ -439,122 +448,54 @@ __device__ __forceinline__ void sort_long_run(const long long *__restrict__ coun
     __syncthreads();
 }
 
-__global__ void __launch_bounds__(kRankSortThreads) rsort_out_kernel(const long long *__restrict__ counts, int n, int n_ids, SortBufs b,
+// WHOLE: one bin of all n ids.
+template <bool WHOLE>
+__global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long long *__restrict__ counts, int n, int n_ids, RankBufs b,
                                                                      int *__restrict__ out_ids) {
-    __shared__ unsigned gs[kPasses * kDigits];
-    __shared__ RunLds s;
-    bool differ;
-    const bool low = stage_totals(b, gs, differ);
-    const int src = source_buffer(gs, kPasses, n);
-    const unsigned long long *pairs = b.pairs[src];      // (sort_long_run writes there)
+    __shared__ union {
+        unsigned long long key[kRunMax];
+        RadixLds radix;
+    } s;
+    __shared__ int s_far;
     const int tid = threadIdx.x;
-    const unsigned j = blockIdx.x * kRankSortThreads + tid;
-    const bool in = j < (unsigned)n;
-    const unsigned long long pair = in ? pairs[j] : 0ull;
-    const int id = (int)(unsigned)pair;
-    if (low || !differ) {      // (uniform) the codes leave out nothing that differs
-        if (in && j < (unsigned)n_ids) out_ids[j] = id;
+    unsigned lo = 0, length = (unsigned)n;
+    unsigned long long lower = 0;         // below all counts of the bin
+    if constexpr (!WHOLE) {
+        lo = b.start[2 * blockIdx.x];
+        length = b.start[2 * blockIdx.x + 1] - lo;
+        if (blockIdx.x < kSplitters) lower = b.splitters[blockIdx.x];
+        if (length == 0u || lo >= (unsigned)n_ids) return;      // (uniform) nothing there, or nobody asks for it
+    }
+    auto id_at = [&](unsigned x) { return WHOLE ? x : (unsigned)b.pairs[0][lo + x]; };
+    const int N = sort_size((int)min(length, (unsigned)kRunMax));
+    if (tid == 0) s_far = length > (unsigned)kRunMax ? 1 : 0;
+    __syncthreads();
+    if (length <= (unsigned)kRunMax) {
+        bool far = false;
+        for (int x = tid; x < N; x += kRankSortThreads) {
+            unsigned long long key = 0ull;
+            if (x < (int)length) {
+                const unsigned long long above = (unsigned long long)counts[id_at((unsigned)x)] - lower;
+                far |= (above >> (64 - kPlaceBits)) != 0ull;
+                key = (above << kPlaceBits) | (unsigned)(kRunMax - 1 - x);
+            }
+            s.key[x] = key;
+        }
+        if (__ballot(far) != 0ull && (tid & 63) == 0) s_far = 1;
+        __syncthreads();
+    }
+    if (s_far != 0) {                     // (uniform)
+        __syncthreads();
+        if constexpr (WHOLE) {
+            for (int x = tid; x < n; x += kRankSortThreads) b.pairs[0][x] = (unsigned)x;
+            __syncthreads();
+        }
+        sort_by_radix(counts, b, lo, length, n_ids, out_ids, s.radix);
         return;
     }
-    const unsigned code = (unsigned)(pair >> 32);
-    auto code_of = [&](unsigned x) { return (unsigned)(pairs[x] >> 32); };
-    if (tid == 0) s.n_starts = s.n_long = 0;
-    __syncthreads();
-    if (in) {
-        int before = 0, after = 0;
-        if (code >= kRankExact) {
-            while (before < kShortRun && before < (int)j && code_of(j - 1 - before) == code) ++before;
-            while (after < kShortRun && (unsigned)after + 1 < (unsigned)n - j && code_of(j + 1 + after) == code) ++after;
-        }
-        if (before + after + 1 <= kShortRun) {
-            // the order among themselves (the run is in ascending-id order)
-            unsigned pos = j;
-            if (before + after > 0) {
-                const long long c = counts[id];
-                for (int x = 1; x <= before; ++x) pos -= counts[(unsigned)pairs[j - x]] < c ? 1u : 0u;      // goes behind
-                for (int x = 1; x <= after; ++x) pos += counts[(unsigned)pairs[j + x]] > c ? 1u : 0u;       // goes ahead
-            }
-            if (pos < (unsigned)n_ids) out_ids[pos] = id;
-        } else if (before == 0) {
-            s.starts[atomicAdd(&s.n_starts, 1)] = (int)j;      // (more than kShortRun apart)
-        }
-    }
-    __syncthreads();
-    const int n_starts = s.n_starts;
-    if (n_starts == 0) return;      // (as a rule; the code below is far from being fetched)
-    const int lane = tid & 63, w = tid >> 6;
-    for (int q = w; q < n_starts; q += kSortWaves) {
-        const unsigned lo = (unsigned)s.starts[q];
-        if (lo >= (unsigned)n_ids) continue;      // nobody asks for them
-        const unsigned run_code = code_of(lo);
-        unsigned long long p[kWaveRun / kWave];
-        int length = 0;
-#pragma unroll
-        for (int u = 0; u < kWaveRun / kWave; ++u) p[u] = lo + u * kWave + lane < (unsigned)n ? pairs[lo + u * kWave + lane] : 0ull;
-#pragma unroll
-        for (int u = 0; u < kWaveRun / kWave; ++u) length += __popcll(__ballot((unsigned)(p[u] >> 32) == run_code));
-        if (length == kWaveRun && lo + kWaveRun < (unsigned)n && code_of(lo + kWaveRun) == run_code) {
-            if (lane == 0) s.long_starts[atomicAdd(&s.n_long, 1)] = (int)lo;
-            continue;
-        }
-        unsigned long long c[kWaveRun / kWave];
-#pragma unroll
-        for (int u = 0; u < kWaveRun / kWave; ++u) {
-            const bool mine = u * kWave + lane < length;
-            c[u] = mine ? run_key(counts[(unsigned)p[u]], u * kWave + lane) : 0ull;
-            if (mine) s.wave_count[w][u * kWave + lane] = c[u];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        unsigned pos[kWaveRun / kWave] = {};
-        for_each_key(s.wave_count[w], length, [&](unsigned long long other) {
-#pragma unroll
-            for (int u = 0; u < kWaveRun / kWave; ++u) pos[u] += other > c[u] ? 1u : 0u;
-        });
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < kWaveRun / kWave; ++u) {
-            if (u * kWave + lane < length && lo + pos[u] < (unsigned)n_ids) out_ids[lo + pos[u]] = (int)(unsigned)p[u];
-        }
-    }
-    __syncthreads();
-    const int n_long = s.n_long;
-    for (int q = 0; q < n_long; ++q) {
-        const unsigned lo = (unsigned)s.long_starts[q];
-        const unsigned run_code = code_of(lo);
-        // the run's end: element a has the code, element e (if there is one) has not
-        unsigned a = lo, e = (unsigned)n;
-        while (e - a > 1) {
-            const unsigned step = (e - a + kRankSortThreads - 1) / kRankSortThreads;
-            const unsigned off = (unsigned)tid * step;
-            const bool same = off < e - a && code_of(a + off) == run_code;
-            const int c = __popcll(__ballot(same));
-            __syncthreads();
-            if (tid == 0) s.n_same = 0;
-            __syncthreads();
-            if (lane == 0 && c != 0) atomicAdd(&s.n_same, c);
-            __syncthreads();
-            const unsigned n_same = (unsigned)s.n_same;      // (the first ones: a itself, and on)
-            if (n_same * step < e - a) e = a + n_same * step;
-            a += (n_same - 1) * step;
-        }
-        const unsigned length = e - lo;
-        if (length > kGroupRun) {
-            sort_long_run(counts, b, src, lo, length, n_ids, out_ids, s);
-            continue;
-        }
-        const bool mine = (unsigned)tid < length;
-        const int my_id = mine ? (int)(unsigned)pairs[lo + tid] : 0;
-        const unsigned long long c = mine ? run_key(counts[my_id], tid) : 0ull;
-        __syncthreads();
-        s.count[tid] = c;
-        __syncthreads();
-        if (mine) {
-            unsigned pos = lo;
-            for_each_key(s.count, (int)length, [&](unsigned long long other) { pos += other > c ? 1u : 0u; });
-            if (pos < (unsigned)n_ids) out_ids[pos] = my_id;
-        }
+    if (length > 1u) sort_descending(s.key, N);
+    for (unsigned x = tid; x < length; x += kRankSortThreads) {
+        if (lo + x < (unsigned)n_ids) out_ids[lo + x] = (int)id_at(kRunMax - 1 - ((unsigned)s.key[x] & (kRunMax - 1)));
     }
 }
 
@@ -565,17 +506,17 @@ __global__ void __launch_bounds__(kRankSortThreads) rsort_out_kernel(const long 
 //   mode 0: smallest k >= 1 with S_k >= ceil(P * total);  mode 1: k = #{c >= f_min}.
 namespace {
 
-constexpr int kWideBins = kBins - kBinExact;      // bins of more than one value: their mass is summed
+constexpr int kMassBins = kBins - kBinExact;      // bins of more than one value: their mass is summed
 // of the bin that is divided: digits of its ids, their mass, and the bits below its prefix that are set in any / clear in any
 struct ChooseBufs {
-    unsigned long long *mass;          // [kWideBins]
+    unsigned long long *mass;          // [kMassBins]
     unsigned long long *digit_mass;    // [kDigitBins]
     unsigned long long *bits;          // [2]
     unsigned *hist;                    // [kBins]
     unsigned *digits;                  // [kDigitBins]
     unsigned *done;                    // [2] workgroups that have added theirs
 };
-constexpr int kChooseZeroWords = kWideBins + kDigitBins + 2 + (kBins + kDigitBins + 2) / 2;      // 64-bit words, mass .. done
+constexpr int kChooseZeroWords = kMassBins + kDigitBins + 2 + (kBins + kDigitBins + 2) / 2;      // 64-bit words, mass .. done
 static_assert((kBins + kDigitBins) % 2 == 0, "whole 64-bit words");
 
 __global__ void __launch_bounds__(kRankSortThreads) choose_zero_kernel(ChooseBufs b) {
@@ -640,7 +581,7 @@ __device__ __forceinline__ void wave_tally_mass(unsigned *h, unsigned long long 
 // The counts of this workgroup (all of them when gridDim.x = 1) into bins of LDS, ids and -- above 2048 -- mass.
 __device__ __forceinline__ void bin_counts(const long long *__restrict__ counts, int V, unsigned *h, unsigned long long *m) {
     for (int i = threadIdx.x; i < kBins; i += kRankSortThreads) h[i] = 0u;
-    for (int i = threadIdx.x; i < kWideBins; i += kRankSortThreads) m[i] = 0ull;
+    for (int i = threadIdx.x; i < kMassBins; i += kRankSortThreads) m[i] = 0ull;
     __syncthreads();
     for (unsigned base = blockIdx.x * kRankSortThreads; base < (unsigned)V; base += gridDim.x * kRankSortThreads) {
         const bool in = base + threadIdx.x < (unsigned)V;
@@ -652,12 +593,12 @@ __device__ __forceinline__ void bin_counts(const long long *__restrict__ counts,
 
 __global__ void __launch_bounds__(kRankSortThreads) choose_hist_kernel(const long long *__restrict__ counts, int V, ChooseBufs b) {
     __shared__ unsigned h[kBins];
-    __shared__ unsigned long long m[kWideBins];
+    __shared__ unsigned long long m[kMassBins];
     bin_counts(counts, V, h, m);
     for (int i = threadIdx.x; i < kBins; i += kRankSortThreads) {
         if (h[i] != 0u) atomicAdd(&b.hist[i], h[i]);
     }
-    for (int i = threadIdx.x; i < kWideBins; i += kRankSortThreads) {
+    for (int i = threadIdx.x; i < kMassBins; i += kRankSortThreads) {
         if (m[i] != 0ull) atomicAdd(&b.mass[i], m[i]);
     }
 }
@@ -696,7 +637,7 @@ template <bool DIRECT>
 __global__ void __launch_bounds__(kRankSortThreads) choose_mass_kernel(const long long *__restrict__ counts, int V, double P,
                                                                        ChooseBufs b, long long *__restrict__ out) {
     __shared__ unsigned h[DIRECT ? kBins : kDigitBins];
-    __shared__ unsigned long long m[kDigitBins > kWideBins ? kDigitBins : kWideBins];
+    __shared__ unsigned long long m[kDigitBins > kMassBins ? kDigitBins : kMassBins];
     __shared__ unsigned pn[kSortWaves];
     __shared__ unsigned long long pm[kSortWaves];
     __shared__ int s_bin, s_last;
@@ -898,23 +839,30 @@ size_t rank_sort_scratch_bytes(int n) {
 // Sorts all n ids by (count desc, id asc); writes the first n_ids of them.
 void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_ids, int n_ids, hipStream_t st) {
     char *p = static_cast<char *>(scratch);
-    const size_t kb = round256((size_t)n * 8);
     const int nblk = (n + kRankSortThreads - 1) / kRankSortThreads;
-    SortBufs b;
+    RankBufs b{};
     b.pairs[0] = reinterpret_cast<unsigned long long *>(p);
-    b.pairs[1] = reinterpret_cast<unsigned long long *>(p + kb);
-    b.gtot = reinterpret_cast<unsigned *>(p + 2 * kb);
-    b.rest = reinterpret_cast<unsigned long long *>(b.gtot + kTotals);
-    b.hist = reinterpret_cast<unsigned *>(p + 2 * kb + round256((kTotals + 8) * 4));
-    b.hist_low = b.hist + (size_t)nblk * kDigits;
-    hipLaunchKernelGGL(rsort_zero_kernel, dim3(1), dim3(kRankSortThreads), 0, st, b.gtot);
-    hipLaunchKernelGGL(rsort_init_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, b);
-    for (int pass = 0; pass < kPasses; ++pass) {
-        if (pass > 0) hipLaunchKernelGGL(rsort_hist_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, pass, b);
-        hipLaunchKernelGGL(rsort_scatter_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, pass, b);
+    p += round256((size_t)n * 8);
+    b.pairs[1] = reinterpret_cast<unsigned long long *>(p);
+    if (n <= kRunMax) {
+        hipLaunchKernelGGL(rank_runs_kernel<true>, dim3(1), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
+        return;
     }
-    hipLaunchKernelGGL(rsort_out_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
+    // (12 KiB per 1024 ids, more than the 8 KiB that the radix passes write there)
+    b.rows = reinterpret_cast<unsigned *>(p);
+    p += round256((size_t)nblk * kRankBins * 4);
+    b.totals = reinterpret_cast<unsigned *>(p);
+    p += round256(kRankBins * 4);
+    b.start = reinterpret_cast<unsigned *>(p);
+    p += round256(kWideBins * 4);
+    b.splitters = reinterpret_cast<unsigned long long *>(p);
+    hipLaunchKernelGGL(rank_hist_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, b);
+    auto scan = nblk <= 8 * kSortWaves ? rank_scan_kernel<8> : rank_scan_kernel<32>;
+    hipLaunchKernelGGL(scan, dim3(kScanBlocks), dim3(kRankSortThreads), 0, st, nblk, b);
+    hipLaunchKernelGGL(rank_scatter_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
+    hipLaunchKernelGGL(rank_runs_kernel<false>, dim3(kSplitters + 1), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
 }
+static_assert(kRankBins * 4 >= 8 * kRankSortThreads, "the radix passes' second buffer lies where the rows are");
 
 // (likewise: ids and counts in order, sums per workgroup, and the sort's buffers)
 size_t choose_k_ws_bytes(int V) {
@@ -927,7 +875,7 @@ void launch_choose_k(const long long *counts, int V, int mode, double P, long lo
     const int nblk = (V + kRankSortThreads - 1) / kRankSortThreads;
     ChooseBufs b;
     b.mass = static_cast<unsigned long long *>(scratch);
-    b.hist = reinterpret_cast<unsigned *>(b.mass + kWideBins);      // (every array on whole cache lines)
+    b.hist = reinterpret_cast<unsigned *>(b.mass + kMassBins);      // (every array on whole cache lines)
     b.digit_mass = reinterpret_cast<unsigned long long *>(b.hist + kBins);
     b.digits = reinterpret_cast<unsigned *>(b.digit_mass + kDigitBins);
     b.bits = reinterpret_cast<unsigned long long *>(b.digits + kDigitBins);

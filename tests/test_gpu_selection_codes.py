@@ -170,3 +170,23 @@ def test_count_hot_ids_side_by_side(V, n_ids, hot, dtype):
     ws = torch.full((vt.load_library().vt_count_tokens_ws_bytes(V, n_ids),), 255, dtype=torch.uint8, device="cuda")
     c = vt.count_tokens(torch.from_numpy(ids).to(dtype).cuda(), V, c, ws=ws)      # on top, with a workspace that held other things
     assert np.array_equal(c.cpu().numpy(), 2 * np.bincount(ids, minlength=V))
+
+
+# Rank order by bins: all ids in one workgroup and one more, a ragged last one, one round of the sum over workgroups and two;
+# `crowded`: no id of the sample is large, so one bin holds all large counts; `far`: counts of a bin too far apart for keys in LDS
+@pytest.mark.parametrize("V", [1, 64, 8191, 8192, 8193, 131072, 131073])
+@pytest.mark.parametrize("kind", ["uniform", "crowded", "far", "shared"])
+def test_rank_order_by_bins_of_sampled_counts(kind, V):
+    rng = np.random.default_rng(V)
+    if kind == "shared":                   # large values that a dozen ids share, around the last one with a bin of its own
+        c = rng.integers(2040, 2040 + V // 12 + 20, size=V)
+    else:
+        c = rng.integers(0, 1 << (61 if kind == "far" else 24), size=V)
+    if kind == "crowded":
+        i = np.arange(1024, dtype=np.uint64)
+        c[((i << np.uint64(16) | i * np.uint64(40503) & np.uint64(0xFFFF)) * np.uint64(V)) // np.uint64(1 << 26)] = 5
+    dc = torch.from_numpy(c).cuda()
+    order = np.lexsort((np.arange(V), -c))
+    for k in sorted({1, V // 3 + 1, V}):
+        a, _ = vt.build_trimmed_head(dc, None, k, order="rank")
+        assert np.array_equal(a.cpu().numpy(), order[:k]), k
