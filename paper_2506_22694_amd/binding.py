@@ -109,12 +109,15 @@ def _check(status: int) -> None:
         raise VocabTrimError(status)
 
 
+# The handle of the current stream, without a Stream object around it (0.1 us; torch.cuda.current_stream takes 2.3, a sixth of
+# a draft step's way through this module).
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
+# (the prototypes below take plain integers for pointers: an object around each costs 0.1 us)
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -307,8 +310,7 @@ def _host_i32(values):
 
 
 def _host_ptrs(tensors):
-    arr = (ctypes.c_void_p * len(tensors))(*[_ptr(t) for t in tensors])
-    return arr
+    return (ctypes.c_void_p * len(tensors))(*[_ptr(t) for t in tensors])
 
 
 def build_trimmed_heads(counts: torch.Tensor, W: torch.Tensor | None, ks, ws: torch.Tensor | None = None):
