@@ -77,7 +77,7 @@ struct StepPlan {
     int NP = 0, CS = 0, S = 0;
     int NT = 0, nlists = 0, KC = 0, hpitch = 0, fin_stage_keys = 0, ksplit = 1, nwaves = vt::kStepWaves;
     size_t fin_lds = 0;
-    int rpb = 0, nblocks = 0, tpitch = 0, L = 0, fin_conc = 0;
+    int rpb = 0, nblocks = 0, tpitch = 0, L = 0;
     size_t lds = 0;
     // workspace layout (byte offsets)
     size_t off_lse = 0, off_pms = 0, off_pkeys = 0, off_hpack = 0, off_zbuf = 0, bytes = 0;
@@ -199,7 +199,6 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
     p.nblocks = (k + rpb - 1) / rpb;
     p.tpitch = rpb + 1;
     p.L = m < rpb ? m : rpb;
-    p.fin_conc = 1;      // the merge kernel takes one hidden row per workgroup
 
     // Up to 8 rows on the matrix-core kernel: its tiles must fill most of the 256 CUs in exactly one round.  A
     // tile is 16 rows per group of KS waves (KS = 1, 2, 4 waves share a group's columns) and a workgroup has up to
@@ -374,8 +373,7 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
                                                     : p.L > vt::kRowSelectMinL);
         // one hidden row per workgroup: n <= 256 rows spread over as many CUs, and a merging wave has its
         // SIMD to itself (the selection rounds are bound by instruction issue)
-        p.fin_conc = 1;
-        p.fin_lds = (size_t)p.fin_conc * p.fin_stage_keys * sizeof(unsigned long long);
+        p.fin_lds = (size_t)p.fin_stage_keys * sizeof(unsigned long long);
         // (Merging in the main kernel's last workgroup to arrive was measured for n <= 8: 41.1 against 39.9 us --
         // eight merge workgroups on eight CUs beat eight waves on one; and for n <= 3 once more: 39.6 against 35.3.)
     } else {
@@ -1035,8 +1033,6 @@ int run_step_heads_fused(const void *h, int n, int d, const void *const *W_trim,
     f.L = p.L;
     f.n = n;
     f.m = m;
-    f.conc = p.fin_conc;
-    f.stage_keys = p.fin_stage_keys;
     f.out_ids = out_ids;
     f.out_logp = out_logp;
     f.out_lse = out_lse;
@@ -1099,8 +1095,6 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
             f.L = p.L;
             f.n = n;
             f.m = m;
-            f.conc = 1;
-            f.stage_keys = (p.nblocks + 1) * p.L;
             f.out_ids = out_ids;
             f.out_logp = out_logp;
             f.out_lse = out_lse;
@@ -1113,7 +1107,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
             f.tree_token = tf.token;
             f.tree_score = tf.score;
             f.ticket = reinterpret_cast<unsigned *>(wsb);
-            e = vt::launch_step_finalize(f, (size_t)f.stage_keys * sizeof(unsigned long long), st);
+            e = vt::launch_step_finalize(f, (size_t)(p.nblocks + 1) * p.L * sizeof(unsigned long long), st);
             if (e != hipSuccess) return device_status(e);
         }
         if (p.row_select) {
@@ -1187,9 +1181,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         f.L = p.L;
         f.n = n;
         f.m = m;
-        f.conc = p.fin_conc;
-        f.stage_keys = p.fin_stage_keys;
-        f.out_ids = out_ids;
+                f.out_ids = out_ids;
         f.out_logp = out_logp;
         f.out_lse = out_lse;
         f.lse_buf = lse_buf;

@@ -428,29 +428,28 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
 // The merge of one hidden row per workgroup with a tree level behind it: wave 0 merges the row (its results are
 // written through to memory) and takes a ticket; the workgroup that draws the last ticket ranks all n * m
 // candidates, reading the other rows' results with loads that bypass its caches.
-// T threads: 64 when n * m <= 64, else 512 (the waves beyond the first only help with the ranking; with more
+// T threads: 128 when n * m <= 64, else 512 (the waves beyond the second only help with the ranking; with more
 // threads the merging wave would not have the registers it needs).  BLOCK: all eight waves merge.
 template <int T, bool BLOCK>
 __global__ void __launch_bounds__(T) step_finalize_tree_kernel(const FinalizeArgs f) {
     static_assert(!BLOCK || T == kBlockMergeThreads, "one workgroup size for the merge by eight waves");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_last;
+    __shared__ float s_lse;
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int i = blockIdx.x;
     bool merged = false;
+    unsigned long long *stage = reinterpret_cast<unsigned long long *>(smem);
     if constexpr (BLOCK) {
         merged = merge_row_block(f, i, i, *reinterpret_cast<BlockMergeLds *>(smem), lane, w);
         wait_stores_done();
         __syncthreads();
+    } else {
+        finalize_row_pair(f, i, i, stage, &s_lse, lane, w);
     }
     if (w == 0) {
-        if (!merged) {
-            unsigned long long *stage = reinterpret_cast<unsigned long long *>(smem);
-            finalize_row<true>(f.pms + (size_t)i * f.nlists, f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m,
-                               stage, f.out_ids + (size_t)i * f.m, f.out_logp + (size_t)i * f.m,
-                               f.out_lse ? f.out_lse + i : nullptr, f.lse_buf + i, lane);
-        }
+        if (BLOCK && !merged) finalize_row_alone(f, i, i, stage, lane);
         wait_stores_done();       // the row's results are written through: visible to whoever draws the last ticket
         if (lane == 0) {
             const unsigned v = __hip_atomic_fetch_add(f.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -488,24 +487,17 @@ __global__ void __launch_bounds__(kBlockMergeThreads) step_finalize_block_kernel
     const int i = blockIdx.x;
     const int o = f.indexed ? (int)((f.row_pack >> (8 * (i & 7))) & 0xFFull) : i;      // output row
     if (merge_row_block(f, i, o, *reinterpret_cast<BlockMergeLds *>(smem), lane, w) || w != 0) return;
-    finalize_row<true>(f.pms + (size_t)i * f.nlists, f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m,
-                       reinterpret_cast<unsigned long long *>(smem), f.out_ids + (size_t)o * f.m,
-                       f.out_logp + (size_t)o * f.m, f.out_lse ? f.out_lse + o : nullptr, f.lse_buf + i, lane);
+    finalize_row_alone(f, i, o, reinterpret_cast<unsigned long long *>(smem), lane);
 }
 
-// Merges the per-tile partials: one wave per hidden row.
-__global__ void __launch_bounds__(kStepWaves *kWave) step_finalize_kernel(const FinalizeArgs f) {
+// Merges the per-tile partials: one wave per hidden row, beside one for its log-sum-exp.
+__global__ void __launch_bounds__(2 * kWave) step_finalize_kernel(const FinalizeArgs f) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = lane_id();
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (w >= f.conc) return;
-    const int i = blockIdx.x * f.conc + w;
-    if (i >= f.n) return;
-    unsigned long long *stage = reinterpret_cast<unsigned long long *>(smem) + (size_t)w * f.stage_keys;
+    __shared__ float s_lse;
+    const int i = blockIdx.x;
     const int o = f.indexed ? (int)((f.row_pack >> (8 * (i & 7))) & 0xFFull) : i;      // output row
-    finalize_row<true>(f.pms + (size_t)i * f.nlists, f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m, stage,
-                 f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, f.out_lse ? f.out_lse + o : nullptr,
-                 f.lse_buf + i, lane);
+    finalize_row_pair(f, i, o, reinterpret_cast<unsigned long long *>(smem), &s_lse, lane_id(),
+                      __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
 }
 
 template <int MAXW, bool XG = false>
@@ -585,17 +577,18 @@ hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t s
     hipError_t e = allow_dynamic_lds(lds_limit,
                                      {reinterpret_cast<const void *>(step_finalize_kernel),
                                       reinterpret_cast<const void *>(step_finalize_block_kernel),
-                                      reinterpret_cast<const void *>(step_finalize_tree_kernel<64, false>),
+                                      reinterpret_cast<const void *>(step_finalize_tree_kernel<128, false>),
                                       reinterpret_cast<const void *>(step_finalize_tree_kernel<512, false>),
                                       reinterpret_cast<const void *>(step_finalize_tree_kernel<512, true>)},
                                      kMaxDynamicLds);
     if (e != hipSuccess) return e;
     const bool block = block_merge_pays(f.n, f.nlists, f.L, f.m);
+    lds += kDirectPad * sizeof(unsigned long long);
     if (block && lds < sizeof(BlockMergeLds)) lds = sizeof(BlockMergeLds);
     if (f.tree_cum != nullptr) {
         // one hidden row per workgroup; LDS: the merge's staging, then the ranking's keys and counters
         const int N = f.n * f.m;
-        if (f.conc != 1 || f.indexed || N > kFinalizeTreeMaxN || f.ticket == nullptr) return hipErrorInvalidValue;
+        if (f.indexed || N > kFinalizeTreeMaxN || f.ticket == nullptr) return hipErrorInvalidValue;
         int N2 = kWave;
         while (N2 < N) N2 <<= 1;
         const size_t need = (size_t)N2 * 12 + 256;
@@ -603,7 +596,7 @@ hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t s
         if (block)
             hipLaunchKernelGGL((step_finalize_tree_kernel<512, true>), dim3(f.n), dim3(512), bytes, st, f);
         else if (N <= kWave)
-            hipLaunchKernelGGL((step_finalize_tree_kernel<64, false>), dim3(f.n), dim3(64), bytes, st, f);
+            hipLaunchKernelGGL((step_finalize_tree_kernel<128, false>), dim3(f.n), dim3(128), bytes, st, f);
         else
             hipLaunchKernelGGL((step_finalize_tree_kernel<512, false>), dim3(f.n), dim3(512), bytes, st, f);
         return hipGetLastError();
@@ -612,8 +605,7 @@ hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t s
         hipLaunchKernelGGL(step_finalize_block_kernel, dim3(f.n), dim3(kBlockMergeThreads), lds, st, f);
         return hipGetLastError();
     }
-    const int grid = (f.n + f.conc - 1) / f.conc;
-    hipLaunchKernelGGL(step_finalize_kernel, dim3(grid), dim3(f.conc * kWave), lds, st, f);
+    hipLaunchKernelGGL(step_finalize_kernel, dim3(f.n), dim3(2 * kWave), lds, st, f);
     return hipGetLastError();
 }
 

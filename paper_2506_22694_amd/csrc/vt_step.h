@@ -140,8 +140,6 @@ struct FinalizeArgs {
     const unsigned long long *pms;
     const unsigned long long *pkeys;
     int nlists, L, n, m;
-    int conc;                 // hidden rows (waves) per workgroup
-    int stage_keys;           // LDS keys reserved per wave
     int *out_ids;
     float *out_logp;
     float *out_lse;           // or null

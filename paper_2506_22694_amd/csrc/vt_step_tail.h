@@ -404,43 +404,41 @@ __device__ __forceinline__ void store_result(int *__restrict__ ids_row, float *_
 }
 
 // ------------------------------------------------------------------ direct merge of at most 2048 keys (one wave)
-// Butterfly over the wave whose first `gsteps` steps take the maximum (inside groups of 2^gsteps
-// lanes) and whose remaining steps take the minimum over those groups: the smallest group maximum.
+// Butterfly over the wave whose first `gsteps` steps take the maximum (inside groups of lanes that agree in their lowest bits)
+// and whose remaining steps take the minimum over those groups: the smallest group maximum.  (Groups of neighbouring
+// lanes would be empty where few neighbouring lists hold keys, as for a small head's rows beside a large one.)
 __device__ __forceinline__ unsigned wave_min_of_group_max_u32(unsigned v, int gsteps) {
-    unsigned t = dpp_mov<0xB1>(v);      // quad_perm [1,0,3,2]
-    v = gsteps > 0 ? (v > t ? v : t) : (v < t ? v : t);
-    t = dpp_mov<0x4E>(v);               // quad_perm [2,3,0,1]
-    v = gsteps > 1 ? (v > t ? v : t) : (v < t ? v : t);
-    t = dpp_mov<0x141>(v);              // row_half_mirror
+    auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = gsteps > 0 ? (r[0] > r[1] ? r[0] : r[1]) : (r[0] < r[1] ? r[0] : r[1]);
+    r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = gsteps > 1 ? (r[0] > r[1] ? r[0] : r[1]) : (r[0] < r[1] ? r[0] : r[1]);
+    unsigned t = dpp_mov<0x128>(v);     // row_ror:8
     v = gsteps > 2 ? (v > t ? v : t) : (v < t ? v : t);
-    t = dpp_mov<0x140>(v);              // row_mirror
+    t = dpp_mov<0x141>(v);              // row_half_mirror
     v = gsteps > 3 ? (v > t ? v : t) : (v < t ? v : t);
-    auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = gsteps > 4 ? (r[0] > r[1] ? r[0] : r[1]) : (r[0] < r[1] ? r[0] : r[1]);
-    r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return gsteps > 5 ? (r[0] > r[1] ? r[0] : r[1]) : (r[0] < r[1] ? r[0] : r[1]);
+    t = dpp_mov<0x4E>(v);               // quad_perm [2,3,0,1]
+    v = gsteps > 4 ? (v > t ? v : t) : (v < t ? v : t);
+    t = dpp_mov<0xB1>(v);               // quad_perm [1,0,3,2]
+    return gsteps > 5 ? (v > t ? v : t) : (v < t ? v : t);
 }
 
-constexpr int kDirectKeysPerLane = 48;      // up to 3072 keys stay in registers (256 lists of 12)
 constexpr int kDirectMaxCand = 128;
+constexpr int kDirectPad = 8;               // keys read at a time when the candidates are ranked
+constexpr int kDirectLists = kStepMaxBlocks / kWave;      // lists per lane: up to 256 in all
+constexpr int kBlockMergeSpill = 48 * kWave;              // keys of 256 lists of 12: more go to the merge by eight waves
 
 // 16 bytes per lane with the coherence of acquire_u64 (agent scope: not served from this XCD's L2).
 // Issue cost per wave is that of an 8-byte load, so two keys per load halve the request time.
 __device__ __forceinline__ void acquire_load16(u32x4 &dst, const void *p) {
     asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(dst) : "v"(p) : "memory");
 }
-__device__ __forceinline__ void wait_loads16(u32x4 (&r)[16]) {
-    asm volatile("s_waitcnt vmcnt(0)"
-                 : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]),
-                   "+v"(r[8]), "+v"(r[9]), "+v"(r[10]), "+v"(r[11]), "+v"(r[12]), "+v"(r[13]), "+v"(r[14]),
-                   "+v"(r[15]));
-}
-__device__ __forceinline__ void wait_loads24(u32x4 (&r)[24]) {
-    asm volatile("s_waitcnt vmcnt(0)"
-                 : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]),
-                   "+v"(r[8]), "+v"(r[9]), "+v"(r[10]), "+v"(r[11]), "+v"(r[12]), "+v"(r[13]), "+v"(r[14]),
-                   "+v"(r[15]), "+v"(r[16]), "+v"(r[17]), "+v"(r[18]), "+v"(r[19]), "+v"(r[20]), "+v"(r[21]),
-                   "+v"(r[22]), "+v"(r[23]));
+template <int N>
+__device__ __forceinline__ void wait_loads16(u32x4 (&r)[N]) {
+    if constexpr (N == 4)
+        asm volatile("s_waitcnt vmcnt(0)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+    else
+        asm volatile("s_waitcnt vmcnt(0)"
+                     : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
 }
 
 // The first active lane's value in every lane.  The row's log-sum-exp goes through this before it is subtracted
@@ -452,56 +450,73 @@ __device__ __forceinline__ float lane_uniform(float x) {
     return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));
 }
 
-// All `total` <= 64 U published keys of a hidden row (any order) are held in registers, U per lane
-// (U = 32 or 48: read as U / 2 pairs, `total` even and src 16-byte aligned; U = 4: one key per load).
-// With G = the power of two >= m, the lanes form G groups; every group's best logit is a different
-// key, so at least G >= m keys reach T = the smallest of the group maxima, and the m best keys are
-// among the keys whose logit reaches T (a few dozen).  Those are compacted into LDS and ranked by
-// counting.  Returns false, having written nothing, when more than kDirectMaxCand keys reach T
-// (massive ties): the caller then merges the sorted lists round by round.
-// lse_fn() is called once, after the wait for the keys, and returns the row's log-sum-exp (what it reduces was
-// requested by the caller before this call, so those loads and the keys' travel together); lse_out receives it.
-template <int U, bool FULL, typename LseFn>
-__device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__restrict__ src, int total, int m,
-                                                    LseFn &&lse_fn, float &lse_out, unsigned long long *stage,
-                                                    int *__restrict__ out_ids_row, float *__restrict__ out_logp_row,
-                                                    int lane) {
-    static_assert(U == 48 || U == 32 || U == 4, "unsupported register budget");
-    unsigned long long kreg[U];
-    if constexpr (U >= 32) {
-        u32x4 r[U / 2];
-        const int npairs = total >> 1;
-        // Straight-line code from the first request to the wait: the compiler does not know that these
-        // registers are still in flight, and a branch in between (say, around the requests past the end)
-        // makes it copy them at the join -- before their values have arrived.  Requests past the end
-        // re-read the last pair instead.
+// The log-sum-exp of up to 256 lists' (max, sum-exp) pairs, four per lane; one value in all lanes.
+__device__ __forceinline__ float lse_of_lists(const unsigned long long *__restrict__ pms_row, int B, int lane) {
+    unsigned long long ms[kDirectLists];
 #pragma unroll
-        for (int u = 0; u < U / 2; ++u) {
-            const int e = u * kWave + lane;
-            acquire_load16(r[u], src + 2 * (FULL ? e : min(e, npairs - 1)));
+    for (int x = 0; x < kDirectLists; ++x) ms[x] = acquire_u64(pms_row + min(lane + kWave * x, B - 1));
+    float lm = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < kDirectLists; ++x) lm = fmaxf(lm, __uint_as_float((unsigned)ms[x]));      // (past the end: the last list's again)
+    const float M = wave_max(lm);
+    float ls = 0.f;
+#pragma unroll
+    for (int x = 0; x < kDirectLists; ++x) {
+        const float e = __uint_as_float((unsigned)(ms[x] >> 32)) * __expf(__uint_as_float((unsigned)ms[x]) - M);
+        ls += lane + kWave * x < B ? e : 0.f;
+    }
+    return lane_uniform(M + __logf(wave_sum(ls)));
+}
+
+// Up to 256 lists of L keys, each in descending order, four lists per lane.  With G = the power of two >= m the lanes form G
+// groups; every group's best logit is a different key, so at least G >= m keys reach T = the smallest of the group maxima, and
+// the m best keys are among those whose logit does (a dozen or two).  Only the first D keys of every list are read at first: a
+// list's next key matters where the one before it reaches T, so the keys are looked at rank by rank until a rank has none (two
+// or three of them, as a rule; all L keys of all lists, one test each, took 0.5 us longer).  The candidates are compacted into
+// LDS and ranked by counting.  PAIRS: L is even, two keys to a load.
+// Returns false, having written nothing, when more than kDirectMaxCand keys reach T (massive ties): the caller then merges the
+// lists round by round.  lse_fn() is called once, when the results are about to be written.
+template <int D, bool PAIRS, typename LseFn>
+__device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__restrict__ src, int B, int L, int m,
+                                                    LseFn &&lse_fn, unsigned long long *stage, int *__restrict__ out_ids_row,
+                                                    float *__restrict__ out_logp_row, int lane) {
+    constexpr int X = kDirectLists;
+    static_assert(!PAIRS || D % 2 == 0, "whole pairs");
+    unsigned long long key[D][X];
+    if constexpr (PAIRS) {
+        u32x4 r[X * D / 2];
+        // Straight-line code from the first request to the wait: the compiler does not know that these registers are still in
+        // flight, and a branch in between makes it copy them at the join -- before their values have arrived.
+#pragma unroll
+        for (int x = 0; x < X; ++x) {
+#pragma unroll
+            for (int q = 0; q < D / 2; ++q) acquire_load16(r[x * (D / 2) + q], src + (size_t)min(lane + kWave * x, B - 1) * L + 2 * q);
         }
-        if constexpr (U == 32) wait_loads16(r);
-        else wait_loads24(r);
+        wait_loads16(r);
 #pragma unroll
-        for (int u = 0; u < U / 2; ++u) {
-            const bool valid = FULL || u * kWave + lane < npairs;
-            kreg[2 * u] = valid ? (((unsigned long long)r[u][1] << 32) | r[u][0]) : kNoKey;
-            kreg[2 * u + 1] = valid ? (((unsigned long long)r[u][3] << 32) | r[u][2]) : kNoKey;
+        for (int x = 0; x < X; ++x) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                const u32x4 &v = r[x * (D / 2) + j / 2];
+                key[j][x] = ((unsigned long long)v[2 * (j & 1) + 1] << 32) | v[2 * (j & 1)];
+            }
         }
     } else {
 #pragma unroll
-        for (int u = 0; u < U; ++u) kreg[u] = acquire_u64(src + min(u * kWave + lane, total - 1));
+        for (int j = 0; j < D; ++j) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (u * kWave + lane >= total) kreg[u] = kNoKey;
+            for (int x = 0; x < X; ++x) key[j][x] = acquire_u64(src + (size_t)min(lane + kWave * x, B - 1) * L + j);
         }
     }
-    const float lse = lse_fn();
-    lse_out = lse;
+#pragma unroll
+    for (int x = 0; x < X; ++x) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) key[j][x] = lane + kWave * x < B ? key[j][x] : kNoKey;
+    }
     unsigned top = 0u;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const unsigned o = (unsigned)(kreg[u] >> 32);
+    for (int x = 0; x < X; ++x) {
+        const unsigned o = (unsigned)(key[0][x] >> 32);
         top = o > top ? o : top;
     }
     unsigned T;
@@ -517,115 +532,88 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
     }
     T = T == 0u ? 1u : T;               // an empty group: every real key is a candidate (real keys have a non-zero high word)
     int ncand = 0;
+    // the lists' keys of one rank; whether any is a candidate
+    auto collect = [&](const unsigned long long (&k)[X]) -> bool {
+        unsigned best = 0u;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const bool c = (unsigned)(kreg[u] >> 32) >= T;
-        const unsigned long long mask = __ballot(c);
-        if (mask != 0ull) {
+        for (int x = 0; x < X; ++x) best = (unsigned)(k[x] >> 32) > best ? (unsigned)(k[x] >> 32) : best;
+        if (__ballot(best >= T) == 0ull) return false;
+#pragma unroll
+        for (int x = 0; x < X; ++x) {
+            const bool c = (unsigned)(k[x] >> 32) >= T;
+            const unsigned long long mask = __ballot(c);
             const int slot = ncand + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
                                                                     __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-            if (c && slot < kDirectMaxCand) stage[slot] = kreg[u];
+            if (c && slot < kDirectMaxCand) stage[slot] = k[x];
             ncand += __popcll(mask);
         }
+        return true;
+    };
+    bool more = true;
+#pragma unroll
+    for (int j = 0; j < D; ++j) more = more && collect(key[j]);
+    for (int j = D; more && j < L; ++j) {
+#pragma unroll
+        for (int x = 0; x < X; ++x) {
+            const unsigned long long k = acquire_u64(src + (size_t)min(lane + kWave * x, B - 1) * L + j);
+            key[D - 1][x] = (unsigned)(key[D - 1][x] >> 32) >= T ? k : kNoKey;
+        }
+        more = collect(key[D - 1]);
     }
     if (ncand > kDirectMaxCand) return false;
+    if (lane < kDirectPad) stage[ncand + lane] = kNoKey;      // (the ranking reads whole groups of keys)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int c = lane; c < ncand; c += kWave) {
-        const unsigned long long key = stage[c];
-        int above = 0;
-        int x = 0;
-        for (; x + 8 <= ncand; x += 8) {
-            unsigned long long t[8];
+    unsigned long long mine[kDirectMaxCand / kWave];
+    int above[kDirectMaxCand / kWave];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) t[q] = stage[x + q];      // every lane reads the same key: a broadcast
+    for (int c = 0; c < kDirectMaxCand / kWave; ++c) {
+        mine[c] = kNoKey;
+        above[c] = 0;
+        if (c * kWave >= ncand) break;      // (uniform)
+        mine[c] = c * kWave + lane < ncand ? stage[c * kWave + lane] : kNoKey;
+        for (int x = 0; x < ncand; x += kDirectPad) {
+            unsigned long long t[kDirectPad];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) above += t[q] > key ? 1 : 0;
+            for (int q = 0; q < kDirectPad; ++q) t[q] = stage[x + q];      // every lane reads the same key: a broadcast
+#pragma unroll
+            for (int q = 0; q < kDirectPad; ++q) above[c] += t[q] > mine[c] ? 1 : 0;
         }
-        for (; x < ncand; ++x) above += stage[x] > key ? 1 : 0;
-        if (above < m) {
-            store_result(out_ids_row, out_logp_row, (int)above, key_id(key), key_logit(key) - lse);
-        }
+    }
+    const float lse = lse_fn();
+#pragma unroll
+    for (int c = 0; c < kDirectMaxCand / kWave; ++c) {
+        if (mine[c] != kNoKey && above[c] < m)
+            store_result(out_ids_row, out_logp_row, above[c], key_id(mine[c]), key_logit(mine[c]) - lse);
     }
     __builtin_amdgcn_wave_barrier();
     return true;
 }
 
 // ------------------------------------------------------------------ final merge of one hidden row (one wave)
-// pms_row: [B] (max | sumexp << 32); pkeys_row: [B][L] keys, each list sorted
-// descending.  stage: wave-private LDS for (min(B, 256) + 1) * L keys.
+// pkeys_row: [B][L] keys, each list sorted descending.  stage: wave-private LDS for (min(B, 256) + 1) * L + kDirectPad keys.
 // Lists are merged 256 at a time (4 per lane); with CARRY the best m of one
 // group are carried into the next as one more list, so B is unbounded.
-template <bool CARRY>
-__device__ __forceinline__ void finalize_row(const unsigned long long *__restrict__ pms_row,
-                                             const unsigned long long *__restrict__ pkeys_row, int B, int L, int m,
+// lse_fn(): the row's log-sum-exp, one value in all lanes; called exactly once, when the results are about to be written.
+template <bool CARRY, typename LseFn>
+__device__ __forceinline__ void finalize_row(const unsigned long long *__restrict__ pkeys_row, int B, int L, int m, LseFn &&lse_fn,
                                              unsigned long long *stage, int *__restrict__ out_ids_row,
-                                             float *__restrict__ out_logp_row, float *__restrict__ out_lse_i,
-                                             float *__restrict__ lse_buf_i, int lane) {
+                                             float *__restrict__ out_logp_row, int lane) {
     constexpr int GROUP = kStepMaxBlocks;        // lists merged per pass
     constexpr int BQ = GROUP / kWave + (CARRY ? 1 : 0);   // lists per lane
     constexpr int U = 32;                        // 64-lane loads in flight per batch (16 KiB)
-    // log-sum-exp over all lists.  Up to GROUP lists the (max, sum) words are requested first and reduced only
-    // after the keys of the direct merge have been requested too: one trip to memory instead of two in a row.
-    const int total_keys = B * L;
-    const bool direct = m <= kWave && (total_keys <= 4 * kWave ||
-                                       (total_keys <= kDirectKeysPerLane * kWave && (total_keys & 1) == 0));
-    float lse;
-    if (direct && B <= GROUP) {
-        unsigned long long ms[GROUP / kWave];
-#pragma unroll
-        for (int q = 0; q < GROUP / kWave; ++q) ms[q] = acquire_u64(pms_row + min(lane + kWave * q, B - 1));
-        auto lse_fn = [&]() {
-            float lm = -INFINITY, ls = 0.f;
-#pragma unroll
-            for (int q = 0; q < GROUP / kWave; ++q) {
-                if (lane + kWave * q < B) {
-                    const float Mb = __uint_as_float((unsigned)ms[q]);
-                    const float Sb = __uint_as_float((unsigned)(ms[q] >> 32));
-                    const float Mn = fmaxf(lm, Mb);
-                    ls = ls * __expf(lm - Mn) + Sb * __expf(Mb - Mn);   // exp(-inf) = 0 on the first term
-                    lm = Mn;
-                }
-            }
-            const float M = wave_max(lm);
-            return lane_uniform(M + __logf(wave_sum(ls * __expf(lm - M))));
-        };
+    if (B <= GROUP && m <= kWave && B * L <= kBlockMergeSpill) {
         bool done;
-        if (total_keys == 32 * kWave)
-            done = finalize_row_direct<32, true>(pkeys_row, total_keys, m, lse_fn, lse, stage, out_ids_row, out_logp_row, lane);
-        else if (total_keys > 32 * kWave)
-            done = finalize_row_direct<48, false>(pkeys_row, total_keys, m, lse_fn, lse, stage, out_ids_row, out_logp_row, lane);
-        else if (total_keys > 4 * kWave)
-            done = finalize_row_direct<32, false>(pkeys_row, total_keys, m, lse_fn, lse, stage, out_ids_row, out_logp_row, lane);
+        if (L == 1)
+            done = finalize_row_direct<1, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        else if (L == 2)
+            done = finalize_row_direct<2, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        else if ((L & 1) == 0)
+            done = finalize_row_direct<4, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else
-            done = finalize_row_direct<4, false>(pkeys_row, total_keys, m, lse_fn, lse, stage, out_ids_row, out_logp_row, lane);
-        if (done) {
-            if (lane == 0) {
-                *lse_buf_i = lse;
-                if (out_lse_i) *out_lse_i = lse;
-            }
-            return;
-        }
-    } else {
-        float lm = -INFINITY, ls = 0.f;
-        unsigned long long ms[GROUP / kWave];
-        for (int b0 = 0; b0 < B; b0 += GROUP) {
-#pragma unroll
-            for (int q = 0; q < GROUP / kWave; ++q) ms[q] = acquire_u64(pms_row + min(b0 + lane + kWave * q, B - 1));
-#pragma unroll
-            for (int q = 0; q < GROUP / kWave; ++q) {
-                if (b0 + lane + kWave * q < B) {
-                    const float Mb = __uint_as_float((unsigned)ms[q]);
-                    const float Sb = __uint_as_float((unsigned)(ms[q] >> 32));
-                    const float Mn = fmaxf(lm, Mb);
-                    ls = ls * __expf(lm - Mn) + Sb * __expf(Mb - Mn);   // exp(-inf) = 0 on the first term
-                    lm = Mn;
-                }
-            }
-        }
-        const float M = wave_max(lm);
-        lse = lane_uniform(M + __logf(wave_sum(ls * __expf(lm - M))));
+            done = finalize_row_direct<3, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        if (done) return;
     }
 
     unsigned res_ord = 0u;
@@ -721,13 +709,61 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
         }
         __builtin_amdgcn_wave_barrier();
     }
+    const float lse = lse_fn();
     if (lane < m) {
         store_result(out_ids_row, out_logp_row, lane, (int)res_id, from_orderable_f32(res_ord) - lse);
     }
-    if (lane == 0) {
-        *lse_buf_i = lse;
-        if (out_lse_i) *out_lse_i = lse;
+}
+
+// The row's log-sum-exp over any number of lists.
+__device__ __forceinline__ float row_lse(const unsigned long long *__restrict__ pms_row, int B, int lane) {
+    if (B <= kStepMaxBlocks) return lse_of_lists(pms_row, B, lane);
+    float lm = -INFINITY, ls = 0.f;
+    for (int b0 = 0; b0 < B; b0 += kWave) {
+        const unsigned long long ms = acquire_u64(pms_row + min(b0 + lane, B - 1));
+        if (b0 + lane < B) {
+            const float Mb = __uint_as_float((unsigned)ms);
+            const float Sb = __uint_as_float((unsigned)(ms >> 32));
+            const float Mn = fmaxf(lm, Mb);
+            ls = ls * __expf(lm - Mn) + Sb * __expf(Mb - Mn);   // exp(-inf) = 0 on the first term
+            lm = Mn;
+        }
     }
+    const float M = wave_max(lm);
+    return lane_uniform(M + __logf(wave_sum(ls * __expf(lm - M))));
+}
+
+// A hidden row's merge by the first two waves of its workgroup (all its threads call this): the log-sum-exp is reduced in the
+// second wave while the first one selects (one after the other in one wave took 0.4 us longer).
+__device__ __forceinline__ void finalize_row_pair(const FinalizeArgs &f, int i, int o, unsigned long long *stage, float *s_lse, int lane, int w) {
+    const unsigned long long *pms_row = f.pms + (size_t)i * f.nlists, *pkeys_row = f.pkeys + (size_t)i * f.nlists * f.L;
+    if (w == 0) {
+        auto lse_fn = [&]() {
+            __syncthreads();
+            return *s_lse;
+        };
+        finalize_row<true>(pkeys_row, f.nlists, f.L, f.m, lse_fn, stage, f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, lane);
+    } else {
+        if (w == 1) {
+            const float lse = row_lse(pms_row, f.nlists, lane);
+            if (lane == 0) {
+                *s_lse = lse;
+                f.lse_buf[i] = lse;
+                if (f.out_lse) f.out_lse[o] = lse;
+            }
+        }
+        __syncthreads();
+    }
+}
+// The same by one wave.
+__device__ __forceinline__ void finalize_row_alone(const FinalizeArgs &f, int i, int o, unsigned long long *stage, int lane) {
+    const float lse = row_lse(f.pms + (size_t)i * f.nlists, f.nlists, lane);
+    if (lane == 0) {
+        f.lse_buf[i] = lse;
+        if (f.out_lse) f.out_lse[o] = lse;
+    }
+    finalize_row<true>(f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m, [lse]() { return lse; }, stage,
+                       f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, lane);
 }
 
 // ------------------------------------------------------------------ merge of many lists (eight waves per hidden row)
@@ -759,7 +795,7 @@ struct BlockMergeLds {
 __host__ __device__ __forceinline__ bool block_merge_pays(int n, int B, int L, int m) {
     const int total = B * L;
     return m <= kWave && B <= kBlockMergeMaxLists && total <= kBlockMergeMaxKeys &&
-           (B > kStepMaxBlocks || total > kDirectKeysPerLane * kWave || (n > kGemvMaxN && total > 1024));
+           (B > kStepMaxBlocks || total > kBlockMergeSpill || (n > kGemvMaxN && total > 1024));
 }
 
 template <int U>

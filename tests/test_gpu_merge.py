@@ -1,0 +1,47 @@
+"""The merge of up to 256 candidate lists per hidden row (one wave), where the best tokens lie unevenly among the lists."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2506_22694_amd as vt
+from paper_2506_22694_amd import synth
+from test_gpu_parity import check_step, run_step
+
+pytestmark = pytest.mark.gpu
+
+
+# `best` neighbouring tokens far above the field, from token `at` on: all of them in one list (ranks past the third or fourth of a list
+# are read only then), across two lists, in the last one; lists of every length and parity; heads of one list, of 39 and of 256
+@pytest.mark.parametrize("k,d", [(30, 128), (5000, 256), (32768, 128)])
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 7, 8, 10, 11])
+def test_best_tokens_in_few_lists(k, d, m):
+    n = 2
+    W, map_ = synth.trimmed_head_direct(k, d, seed=40 + m, dtype="bf16")
+    h = synth.hidden_rows(n, d, seed=k, dtype="bf16")
+    put = lambda a: torch.from_numpy(np.asarray(a).view(np.int16)).cuda().view(torch.bfloat16)
+    hd = put(h).float().sum(0)
+    for at, best in ((0, 11), (k // 2 - 5, 11), (k - 9, 9), (3, 2)):
+        Wd = put(W)
+        # logits 6, 6.5, .. for both hidden rows (up to rounding and their scalar product); the other tokens' are below 2
+        Wd[at:at + best] = (hd * torch.arange(6, 6 + best / 2, 0.5, device="cuda").unsqueeze(1) / d).bfloat16()
+        V = Wd.view(torch.int16).cpu().numpy().view(W.dtype)
+        ref = oracle.draft_head_step(h, V, map_, m)
+        ids, logp, lse = run_step(h, V, map_, m, return_lse=True)
+        assert check_step(ids, logp, ref, map_, m, lse) == 0
+
+
+# A small head beside a large one: the rows of either find their lists next to each other among empty ones
+@pytest.mark.parametrize("ks", [(30000, 300), (300, 30000), (8, 20000), (16384, 16000)])
+def test_lists_of_two_heads_merge_like_one_heads(ks):
+    n, d, m = 8, 256, 8
+    g = torch.Generator(device="cuda").manual_seed(ks[0])
+    heads = [(torch.randn(k, d, generator=g, device="cuda").mul_(0.1).bfloat16(), torch.arange(k, dtype=torch.int32, device="cuda")) for k in ks]
+    h = torch.randn(n, d, generator=g, device="cuda").bfloat16()
+    which = [0, 1] * 4
+    assert "heads=2" in vt.draft_head_step_multi_plan(n, d, ks, which, m)
+    ids, logp, lse = vt.draft_head_step_multi(h, heads, which, m, return_lse=True)
+    for i, q in enumerate(which):
+        one_ids, one_logp = vt.draft_head_step(h[i:i + 1].expand(2, d).contiguous(), heads[q][0], heads[q][1], m)
+        assert torch.equal(ids[i], one_ids[0])
+        assert (logp[i] - one_logp[0]).abs().max().item() <= 4e-6      # sums over other tiles: a few ulp of a log-sum-exp near 10
