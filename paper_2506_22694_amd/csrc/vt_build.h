@@ -10,8 +10,8 @@ namespace vt {
 constexpr int kHistBinsPerBlock = 65536;   // 16-bit bins privatised in LDS per workgroup (128 KiB, two per word)
 constexpr int kHistBlocks = 256;           // workgroups per launch: id-stream chunks x bin ranges
 constexpr int kHistThreads = 1024;
-constexpr int kHistUnroll = 6;            // 16-byte id vectors in flight per thread (4 / 6 / 8: 28.2 / 28.0 / 28.8 us at
-                                          // 10^7 ids, 141.8 / 137.8 / 135.7 us at 10^8)
+constexpr int kHistUnroll = 4;            // 16-byte id vectors in flight per thread (2 / 4 / 6: 24.9 / 22.1 / 22.8 us at
+                                          // 10^7 ids, 130 / 99 / 101 at 10^8, 64-bit 202 / 165 / 175)
 
 int hist_num_ranges(int V);
 int hist_num_chunks(int64_t n_ids, int V);

@@ -8,16 +8,17 @@
 // the low eight bits of every bin, and the upper eight of those groups of 256 ids that have any, which a flag tells (a few
 // dozen ids of a chunk exceed 255, next to each other where ids follow the frequency).
 // A second kernel sums the chunk histograms into the caller's int64 counters.  Ids outside [0, V) are skipped and tallied.
-// What bounds it at 10^8 ids is the reading of the stream once per range: 106 us, of which 100 remain without any LDS
-// atomic and 47 without the loads; a second batch in flight per thread makes it slower (109; 64-bit ids 214 against
-// 168): the two workgroups of a chunk drift apart and miss each other's lines in the L2.  At 10^7 ids (22.8 us; 25.4
-// with 16-bit rows and the last vectors of a chunk requested one by one) a fifth is the loads, a fifth the rows.
+// What bounds it is what a CU does per id and range: ten vector instructions (no branch, no mask) and an LDS atomic.  The waves
+// share their hottest bin through words of their own, without which the workgroups that have it took a third longer (10^8 ids, Zipf
+// 1.1: 135 -> 99 us; one id alone 670 -> 101); an LDS atomic under a mask per id cost four scalar instructions and a branch
+// (10^7 ids 25.0 -> 22.1 us, 64-bit 29.8 -> 28.4, in equal shares 21.6 -> 20.2).  Beyond that it is the reading of the stream once
+// per range: more in flight makes it slower (64-bit, 10^8: four vectors per thread 165 us, six 175, eight 205, six twice 200, two
+// 201), since the two workgroups of a chunk drift apart and miss each other's lines in the L2.
 //
-// A 16-bit bin never holds more than 15 bits for long: the increment that sets bit 15 (it sees the
-// old value 0x7FFF) takes 32768 back out of the bin and adds them to the result counter directly.
-// Between that increment and its subtraction the bin can only grow by the increments in flight in
-// the workgroup (a few thousand at most), far from 65536, so a bin never carries into its
-// neighbour in the same word, whatever the id distribution.
+// A 16-bit bin never holds much more than 15 bits: an increment that finds bit 15 set clears it, and whoever found it set when
+// clearing adds 32768 to the result counter.  Until then the bin can only grow by the increments in flight in the workgroup
+// (eight per thread, twice: 16384 at most), short of 65536, so a bin never carries into its neighbour in the same word,
+// whatever the id distribution.
 #include "vt_build.h"
 #include "vt_device.h"
 #include "vt_launch.h"
@@ -58,18 +59,37 @@ size_t hist_scratch_bytes(int V, int64_t n_ids) {
 }
 
 // `head` ids (fewer than one 16-byte vector) precede the first 16-byte aligned id.
+constexpr int kHistWaves = kHistThreads / kWave;
+constexpr unsigned kHistHot = 128;      // increments of one bin among a workgroup's first 8192 ids that make it a hot one
+// LDS: the bins, and behind them (see the kernel)
+constexpr unsigned kHistHotAt = kHistBinsPerBlock * 2, kHistAsideAt = kHistHotAt + 4 * kHistThreads, kHistHotBinAt = kHistAsideAt + 4 * kWave;
+constexpr unsigned kHistLaterAt = kHistHotBinAt + 4 * kHistWaves, kHistLds = kHistLaterAt + 4;
+constexpr unsigned kNoHot = 0xFFFFFFFFu;
 template <bool IDS64>
 __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *__restrict__ ids_v, long long n_ids,
                                                                     int head, int V, int nchunks,
                                                                     unsigned char *partial,
                                                                     unsigned long long *__restrict__ counts,
                                                                     unsigned long long *__restrict__ n_invalid) {
-    extern __shared__ __align__(16) unsigned words[];     // two 16-bit bins per word
+    // two 16-bit bins per word; behind them (one block of LDS, so that a bin's offset is its address)
+    //   hot     a word per thread: its ids of the wave's hottest bin
+    //   aside   a word per lane: where ids of other ranges go
+    //   hot_bin the waves' hottest bins, where their ids are many; and whether any are
+    extern __shared__ __align__(16) unsigned words[];
+    // (LDS addresses as numbers: what the compiler knows as a pointer it forms again for every access)
+    typedef __attribute__((address_space(3))) unsigned lds_word;
+    const unsigned base = (unsigned)(uintptr_t)(lds_word *)words;
     const int chunk = blockIdx.x, range = blockIdx.y;
     const int lo = range * kHistBinsPerBlock;
     const int nb = min(kHistBinsPerBlock, V - lo);
     const int nw = ((nb + 3) & ~3) >> 1;                  // whole groups of four bins: the rows are written by fours
+    const unsigned hot_at = base + kHistHotAt + 4u * threadIdx.x, aside_at = base + kHistAsideAt + 4u * (threadIdx.x & 63u);
+    unsigned &hot_word = words[kHistHotAt / 4 + threadIdx.x];
     for (int b = threadIdx.x; b < nw; b += kHistThreads) words[b] = 0u;
+    hot_word = 0u;
+    if (threadIdx.x < kWave) words[kHistAsideAt / 4 + threadIdx.x] = 0u;
+    if (threadIdx.x < kHistWaves) words[kHistHotBinAt / 4 + threadIdx.x] = kNoHot;
+    if (threadIdx.x == 0) words[kHistLaterAt / 4] = 0u;
     __syncthreads();
 
     // chunk boundaries in units of 16-byte vectors (4 int32 or 2 int64), tail handled by the last chunk
@@ -78,125 +98,162 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
     const long long nvec = (n_ids - head) / IPV;
     const long long v0 = nvec * chunk / nchunks, v1 = nvec * (chunk + 1) / nchunks;
     unsigned invalid = 0;
-    // One id.  (The scalar head and tail of the stream.)
+    // One id.  (The scalar head and tail of the stream, a few ids at most.)
     auto tally = [&](long long t) {
         if ((unsigned long long)t >= (unsigned long long)V) {
             invalid += 1u;
         } else {
             const unsigned b = (unsigned)((int)t - lo);
-            if (b < (unsigned)nb) {
-                const unsigned sh = (b & 1u) << 4;
-                const unsigned old = atomicAdd(&words[b >> 1], 1u << sh);
-                if (((old >> sh) & 0xFFFFu) == 0x7FFFu) {
-                    // this increment set bit 15: 32768 occurrences move from the bin to the result counter
-                    atomicSub(&words[b >> 1], 0x8000u << sh);
-                    atomicAdd(&counts[t], 32768ull);
-                }
-            }
+            if (b < (unsigned)nb) atomicAdd(&words[b >> 1], 1u << ((b & 1u) << 4));
         }
     };
+    // The wave's hottest bin, as far as it has seen: its ids are counted in words that the threads have to themselves.  (With
+    // Zipf ids eight lanes of 64 hit the hottest bin, and LDS atomics on one address queue.)
+    unsigned hot = kNoHot;
+    bool looked = false;
     // The ids of NV 16-byte vectors: all their LDS atomics are issued before the first result is looked at -- a
     // wave that waited for every atomic's return before the next id spent most of its time in that wait -- and the
-    // rare increment that sets bit 15 is handled behind one test for the whole batch.
+    // rare bin that has reached 32768 is handled behind one test for the whole batch.
     constexpr int IPV0 = IDS64 ? 2 : 4;
-    auto tally_ids = [&](auto ncount, const long long *t) {
+    auto tally_ids = [&](auto ncount, auto with_hot, unsigned *t, const unsigned *high) {
         constexpr int N = decltype(ncount)::value;
-        // ids outside [0, V): rare, so one test for the batch (the largest id as an unsigned number) and the count
-        // behind it; only the workgroups of range 0 report them
+        constexpr bool HOT = decltype(with_hot)::value;      // the wave has a hottest bin
+        // 64-bit ids with anything in the upper half are outside [0, V), V < 2^31: rare, so one test for the batch, which makes
+        // them 32-bit ids outside
+        if constexpr (IDS64) {
+            unsigned some = 0u;
+#pragma unroll
+            for (int q = 0; q < N; ++q) some |= high[q];
+            if (some != 0u) {
+#pragma unroll
+                for (int q = 0; q < N; ++q) t[q] = high[q] != 0u ? 0xFFFFFFFFu : t[q];
+            }
+        }
+        // ids outside [0, V): one test for the batch as well (the largest id; a negative one is a large unsigned number) and the
+        // count behind it; only the workgroups of range 0 report them
         if (range == 0) {
-            bool some;
-            if constexpr (IDS64) {
-                unsigned long long mx = (unsigned long long)t[0];
+            unsigned mx = t[0];
 #pragma unroll
-                for (int q = 1; q < N; ++q) mx = (unsigned long long)t[q] > mx ? (unsigned long long)t[q] : mx;
-                some = mx >= (unsigned long long)V;
-            } else {
-                unsigned mx = (unsigned)(int)t[0];       // a negative id is a large unsigned number
+            for (int q = 1; q < N; ++q) mx = t[q] > mx ? t[q] : mx;
+            if (mx >= (unsigned)V) {
 #pragma unroll
-                for (int q = 1; q < N; ++q) mx = (unsigned)(int)t[q] > mx ? (unsigned)(int)t[q] : mx;
-                some = mx >= (unsigned)V;
-            }
-            if (some) {
-#pragma unroll
-                for (int q = 0; q < N; ++q) invalid += (unsigned long long)t[q] >= (unsigned long long)V ? 1u : 0u;
+                for (int q = 0; q < N; ++q) invalid += t[q] >= (unsigned)V ? 1u : 0u;
             }
         }
-        unsigned b[N], inc[N], old[N];
-        bool in[N];
+        // Every lane adds somewhere -- its bin, its own word, or aside -- so that nothing is branched or masked per id.
+        unsigned b[N], at[N], inc[N], old[N];
 #pragma unroll
         for (int q = 0; q < N; ++q) {
-            // bin inside this range; an id outside [lo, lo + nb) -- a negative one too, V < 2^31 -- wraps far past nb
-            // (a 64-bit id is first checked as a whole: its low half alone could land anywhere)
-            b[q] = (unsigned)((int)t[q] - lo);
-            in[q] = b[q] < (unsigned)nb && (!IDS64 || (unsigned long long)t[q] < (unsigned long long)V);
-            inc[q] = 1u + (b[q] & 1u) * 0xFFFFu;        // 1 for the low half of the word, 0x10000 for the high one
-            old[q] = 0u;
+            // bin inside this range; an id outside [lo, lo + nb) wraps far past nb
+            b[q] = t[q] - (unsigned)lo;
+            const unsigned even = b[q] & ~1u;
+            asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(at[q]) : "v"(even), "s"(base));      // (the compiler takes one instruction more)
+            if constexpr (HOT) at[q] = b[q] == hot ? hot_at : at[q];
+            at[q] = b[q] < (unsigned)nb ? at[q] : aside_at;
+            inc[q] = 1u << (b[q] << 4 & 31u);        // 1 for the low half of the word, 0x10000 for the high one
         }
 #pragma unroll
-        for (int q = 0; q < N; ++q) {
-            if (in[q]) old[q] = atomicAdd(&words[b[q] >> 1], inc[q]);
-        }
-        // the increment that found 0x7FFF in its bin set bit 15
-        bool spill = false;
+        for (int q = 0; q < N; ++q) old[q] = __hip_atomic_fetch_add((lds_word *)(uintptr_t)at[q], inc[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        unsigned any = 0u;
 #pragma unroll
-        for (int q = 0; q < N; ++q) spill |= in[q] && (old[q] & (inc[q] * 0x7FFFu)) == inc[q] * 0x7FFFu;
-        if (spill) {
+        for (int q = 0; q < N; ++q) any |= old[q];
+        if ((any & 0x80008000u) != 0u) {
 #pragma unroll
             for (int q = 0; q < N; ++q) {
-                if (in[q] && (old[q] & (inc[q] * 0x7FFFu)) == inc[q] * 0x7FFFu) {
-                    // 32768 occurrences move from the bin to the result counter
-                    atomicSub(&words[b[q] >> 1], inc[q] * 0x8000u);
-                    atomicAdd(&counts[t[q]], 32768ull);
+                if ((old[q] & 0x80008000u) != 0u) {
+                    unsigned *const word = words + (at[q] - base) / 4;
+                    if (at[q] == aside_at) {
+                        *word = 0u;
+                    } else if (HOT && at[q] == hot_at) {
+                        atomicAdd(&counts[lo + (int)hot], (unsigned long long)(atomicExch(word, 0u) >> ((hot & 1u) << 4)));
+                    } else {
+                        // whoever finds bit 15 set when it is cleared moves the bin's 32768 to the result counter
+                        const unsigned was = atomicAnd(word, 0x7FFF7FFFu);
+                        if ((was & 0x8000u) != 0u) atomicAdd(&counts[lo + (int)(b[q] & ~1u)], 32768ull);
+                        if ((was & 0x80000000u) != 0u) atomicAdd(&counts[lo + (int)(b[q] | 1u)], 32768ull);
+                    }
                 }
+            }
+        }
+        if constexpr (!HOT) {
+            if (!looked) {
+                // once, after the first ids: the bin that the wave found fullest, where it is one of the workgroup's hottest
+                looked = true;
+                unsigned most = 0u, bin = 0u;
+#pragma unroll
+                for (int q = 0; q < N; ++q) {
+                    const unsigned o = at[q] == aside_at ? 0u : old[q] >> ((b[q] & 1u) << 4) & 0xFFFFu;
+                    bin = o > most ? b[q] : bin;
+                    most = o > most ? o : most;
+                }
+                const unsigned wave_most = wave_max_u32(most);
+                if (__ballot(true) == ~0ull && wave_most >= kHistHot)
+                    hot = (unsigned)__builtin_amdgcn_readlane((int)bin, __ffsll((long long)__ballot(most == wave_most)) - 1);
             }
         }
     };
     const u32x4 *vp = reinterpret_cast<const u32x4 *>(static_cast<const char *>(ids_v) + (size_t)head * IDB);
-    auto unpack = [&](const u32x4 q, long long *t) {
+    auto unpack = [&](const u32x4 q, unsigned *t, unsigned *high) {
+        t[0] = q.x;
         if constexpr (IDS64) {
-            t[0] = (long long)(((unsigned long long)q.y << 32) | q.x);
-            t[1] = (long long)(((unsigned long long)q.w << 32) | q.z);
+            high[0] = q.y;
+            t[1] = q.z;
+            high[1] = q.w;
         } else {
-            t[0] = (long long)(int)q.x;
-            t[1] = (long long)(int)q.y;
-            t[2] = (long long)(int)q.z;
-            t[3] = (long long)(int)q.w;
+            t[1] = q.y;
+            t[2] = q.z;
+            t[3] = q.w;
         }
     };
-    auto tally_vec = [&](const u32x4 q) {
-        long long t[IPV0];
-        unpack(q, t);
-        tally_ids(std::integral_constant<int, IPV0>{}, t);
+    auto tally_vec = [&](auto with_hot, const u32x4 q) {
+        unsigned t[IPV0], high[2];
+        unpack(q, t, high);
+        tally_ids(std::integral_constant<int, IPV0>{}, with_hot, t, high);
     };
-    auto tally_vec2 = [&](const u32x4 q0, const u32x4 q1) {
-        long long t[2 * IPV0];
-        unpack(q0, t);
-        unpack(q1, t + IPV0);
-        tally_ids(std::integral_constant<int, 2 * IPV0>{}, t);
+    auto tally_vec2 = [&](auto with_hot, const u32x4 q0, const u32x4 q1) {
+        unsigned t[2 * IPV0], high[4];
+        unpack(q0, t, high);
+        unpack(q1, t + IPV0, high + 2);
+        tally_ids(std::integral_constant<int, 2 * IPV0>{}, with_hot, t, high);
     };
     // kHistUnroll vectors per thread are requested at a time: one 16-byte load per
     // thread in flight (16 KiB per CU) is far below what the memory latency needs.  Plain (cached) loads:
     // the workgroups of one chunk (one per range) are dispatched to the same XCD and read the same ids at
     // about the same time, so three of the four reads can hit its L2; a streaming hint would drop the
     // lines after the first use (10^7 ids: 41.2 -> 35.1 us)
-    constexpr long long kBatch = (long long)kHistUnroll * kHistThreads;
+    // (Buffer loads: a uniform address and the thread's own offset.  With 64-bit addresses per thread the compiler kept one of
+    // them where the next vector arrives, and waited for a batch's first vector before it requested the others.)
+    constexpr int kBatch = kHistUnroll * kHistThreads;
     static_assert(kHistUnroll % 2 == 0, "vectors are counted in pairs");
-    long long v = v0 + threadIdx.x;
-    for (; v + kBatch - kHistThreads < v1; v += kBatch) {
-        u32x4 q[kHistUnroll];
+    const u32x4 *at_vec = vp + v0;
+    long long left = v1 - v0;
+    u32x4 q[kHistUnroll];
+    auto load_batch = [&](int vectors) {      // of `vectors` that are there; those past the end are zero, and not counted
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(at_vec), 0, vectors * 16, 0x00020000);
 #pragma unroll
-        for (int u = 0; u < kHistUnroll; ++u) q[u] = vp[v + (long long)u * kHistThreads];
+        for (int u = 0; u < kHistUnroll; ++u) q[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, threadIdx.x * 16, u * kHistThreads * 16, 0);
+    };
+    for (; left >= kBatch; left -= kBatch, at_vec += kBatch) {
+        load_batch(kBatch);
 #pragma unroll
-        for (int u = 0; u < kHistUnroll; u += 2) tally_vec2(q[u], q[u + 1]);
+        for (int u = 0; u < kHistUnroll; u += 2) {
+            if (hot != kNoHot)
+                tally_vec2(std::true_type{}, q[u], q[u + 1]);
+            else
+                tally_vec2(std::false_type{}, q[u], q[u + 1]);
+        }
     }
-    if (v < v1) {
-        // the last vectors, requested together as well (past the end: the first of them again, not counted)
-        u32x4 q[kHistUnroll - 1];
+    looked = true;      // (fewer lanes from here on)
+    if (left > 0) {
+        load_batch((int)left);
 #pragma unroll
-        for (int u = 0; u < kHistUnroll - 1; ++u) q[u] = vp[v + (long long)u * kHistThreads < v1 ? v + (long long)u * kHistThreads : v];
-#pragma unroll
-        for (int u = 0; u < kHistUnroll - 1; ++u) {
-            if (v + (long long)u * kHistThreads < v1) tally_vec(q[u]);
+        for (int u = 0; u < kHistUnroll; ++u) {
+            if (u * kHistThreads + (int)threadIdx.x < left) {
+                if (hot != kNoHot)
+                    tally_vec(std::true_type{}, q[u]);
+                else
+                    tally_vec(std::false_type{}, q[u]);
+            }
         }
     }
     if (chunk == 0 && (int)threadIdx.x < head) {   // scalar head
@@ -210,7 +267,43 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
             else tally((long long)static_cast<const int *>(ids_v)[i]);
         }
     }
+    // The threads' own words: the wave's sum goes to its bin at once while it is small (sixteen waves' 1023 at most beside the
+    // 49151 that a bin may hold: no carry), otherwise one wave adds the sums behind the barrier.
+    {
+        const unsigned sum = (unsigned)wave_sum_i32((int)(hot_word >> ((hot & 1u) << 4)));
+        if (lane_id() == 0 && sum != 0u) {
+            if (sum < 1024u) {
+                atomicAdd(&words[hot >> 1], sum << ((hot & 1u) << 4));
+            } else {
+                words[kHistHotAt / 4 + threadIdx.x] = sum;
+                words[kHistHotBinAt / 4 + (threadIdx.x >> 6)] = hot;
+                words[kHistLaterAt / 4] = 1u;
+            }
+        }
+    }
     __syncthreads();
+    if (words[kHistLaterAt / 4] != 0u) {      // (uniform)
+        if (threadIdx.x < kWave) {
+            // most often all waves have the same hottest bin: one lane adds all that belong to a bin
+            const int w = min((int)threadIdx.x, kHistWaves - 1);
+            const unsigned bin = words[kHistHotBinAt / 4 + w];
+            const unsigned n = bin != kNoHot && (int)threadIdx.x < kHistWaves ? words[kHistHotAt / 4 + kWave * w] : 0u;
+            unsigned long long left = __ballot(n != 0u);
+            while (left != 0ull) {
+                const int leader = __ffsll((long long)left) - 1;
+                const bool same = bin == (unsigned)__builtin_amdgcn_readlane((int)bin, leader);
+                const unsigned sum = (unsigned)wave_sum_i32(same ? (int)n : 0);
+                if ((int)threadIdx.x == leader) {
+                    unsigned &word = words[bin >> 1];
+                    const unsigned sh = (bin & 1u) << 4, total = (word >> sh & 0xFFFFu) + sum, keep = total & 0x7FFFu;
+                    word = (word & ~(0xFFFFu << sh)) | keep << sh;
+                    if (total != keep) atomicAdd(&counts[lo + (int)bin], (unsigned long long)(total - keep));
+                }
+                left &= ~__ballot(same);
+            }
+        }
+        __syncthreads();
+    }
     // A row of the scratch holds eight bits per id, half the size of the bins; rows of the upper eight bits lie behind them
     // and are written, and read back, for the groups of 256 ids alone that have any.  (Those bits added to the result by
     // atomics instead: all chunks to the same few counters, one behind the other where hot ids share a cache line -- Zipf ids
@@ -334,7 +427,7 @@ static_assert(kHistBlocks <= 257, "sums over the chunks of eight-bit parts fit 1
 hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V, long long *counts,
                          unsigned long long *n_invalid, void *partial, hipStream_t st) {
     const int nchunks = hist_num_chunks(n_ids, V);
-    const size_t lds = (size_t)kHistBinsPerBlock * sizeof(unsigned short);
+    const size_t lds = kHistLds;
     static LdsLimitOnce lds_limit;
     hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(hist_partial_kernel<false>),
                                                  reinterpret_cast<const void *>(hist_partial_kernel<true>)}, (int)lds);
