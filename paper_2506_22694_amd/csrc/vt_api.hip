@@ -580,12 +580,12 @@ int vt_count_tokens(const void *ids, int id_type, int64_t n_ids, int32_t V, int6
     if (n_ids == 0) return VT_OK;
     const size_t idb = id_type == VT_I64 ? 8 : 4;
     if (!aligned(ids, idb) || !aligned(counts, 8) || (n_invalid && !aligned(n_invalid, 8))) return VT_ERR_ALIGN;
-    if (ws == nullptr || !aligned(ws, 256) || ws_bytes < vt_count_tokens_ws_bytes(V, n_ids)) return VT_ERR_WORKSPACE;
+    if (ws == nullptr || !aligned(ws, 256) || ws_bytes < round_up(vt::hist_min_scratch_bytes(V, n_ids), 256)) return VT_ERR_WORKSPACE;
     (void)hipGetLastError();
     return device_status(vt::launch_count_tokens(ids, id_type == VT_I64, n_ids, V,
                                                  reinterpret_cast<long long *>(counts),
                                                  reinterpret_cast<unsigned long long *>(n_invalid),
-                                                 ws, static_cast<hipStream_t>(stream)));
+                                                 ws, ws_bytes, static_cast<hipStream_t>(stream)));
 }
 
 // ------------------------------------------------------------------ Eq. 1

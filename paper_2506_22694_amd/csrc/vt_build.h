@@ -10,15 +10,18 @@ namespace vt {
 constexpr int kHistBinsPerBlock = 65536;   // 16-bit bins privatised in LDS per workgroup (128 KiB, two per word)
 constexpr int kHistBlocks = 256;           // workgroups per launch: id-stream chunks x bin ranges
 constexpr int kHistThreads = 1024;
+constexpr int kHistChunkIds = 16384;      // ids of a chunk at least (4096 / 8192 / 16384 / 65536: 10^6 ids 17.0 / 17.0 / 14.6 / 16.1 us, 200 000
+                                          // 11.5 / 10.8 / 11.3 / 13.2, 64-bit 11.8 / 11.3 / 11.7 / 15.2)
 constexpr int kHistUnroll = 4;            // 16-byte id vectors in flight per thread (2 / 4 / 6: 24.9 / 22.1 / 22.8 us at
                                           // 10^7 ids, 130 / 99 / 101 at 10^8, 64-bit 202 / 165 / 175)
 
 int hist_num_ranges(int V);
 int hist_num_chunks(int64_t n_ids, int V);
 size_t hist_scratch_bytes(int V, int64_t n_ids);
-// partial: hist_scratch_bytes(V, n_ids), no initialisation
+size_t hist_min_scratch_bytes(int V, int64_t n_ids);
+// partial: hist_scratch_bytes(V, n_ids), or from hist_min_scratch_bytes(V, n_ids) on with fewer chunks; no initialisation
 hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V, long long *counts,
-                         unsigned long long *n_invalid, void *partial, hipStream_t st);
+                         unsigned long long *n_invalid, void *partial, size_t partial_bytes, hipStream_t st);
 
 // ---- Eq. 1 ----
 constexpr int kSelectThreads = 1024;

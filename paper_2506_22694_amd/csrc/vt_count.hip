@@ -28,16 +28,14 @@ namespace vt {
 
 int hist_num_ranges(int V) { return (V + kHistBinsPerBlock - 1) / kHistBinsPerBlock; }
 
-int hist_num_chunks(int64_t n_ids, int V) {
-    // at least 64K ids per chunk so that zeroing and flushing 128 KiB of LDS pays off; chunks x ranges = one
-    // round of workgroups over the 256 CUs
+// Chunks of at least `ids` ids; chunks x ranges = one round of workgroups over the 256 CUs at most
+static int chunks_of(int64_t n_ids, int V, int ids) {
     int cap = kHistBlocks / hist_num_ranges(V);
     if (cap < 1) cap = 1;
-    int64_t c = (n_ids + (1 << 16) - 1) >> 16;
-    if (c < 1) c = 1;
-    if (c > cap) c = cap;
-    return (int)c;
+    const int64_t c = (n_ids + ids - 1) / ids;
+    return c < 1 ? 1 : c > cap ? cap : (int)c;
 }
+int hist_num_chunks(int64_t n_ids, int V) { return chunks_of(n_ids, V, kHistChunkIds); }
 
 // What lies between the two kernels: rows of the low bytes and of the upper bytes of the chunks' bins, and a flag per group of
 // 256 ids and chunk: whether the group's upper bytes are there.
@@ -53,10 +51,13 @@ struct HistScratch {
         flags = high + pitch * nchunks;
     }
 };
-size_t hist_scratch_bytes(int V, int64_t n_ids) {
-    const HistScratch sc(nullptr, V, hist_num_chunks(n_ids, V));
-    return (size_t)hist_num_chunks(n_ids, V) * (2 * sc.pitch + sc.groups);
+static size_t chunk_bytes(int V) {
+    const HistScratch sc(nullptr, V, 1);
+    return 2 * sc.pitch + sc.groups;
 }
+size_t hist_scratch_bytes(int V, int64_t n_ids) { return hist_num_chunks(n_ids, V) * chunk_bytes(V); }
+// (a scratch of this size is enough, for fewer chunks)
+size_t hist_min_scratch_bytes(int V, int64_t n_ids) { return chunks_of(n_ids, V, 1 << 16) * chunk_bytes(V); }
 
 // `head` ids (fewer than one 16-byte vector) precede the first 16-byte aligned id.
 constexpr int kHistWaves = kHistThreads / kWave;
@@ -425,8 +426,10 @@ __global__ void __launch_bounds__(kReduceWaves *kWave) hist_reduce_kernel(unsign
 static_assert(kHistBlocks <= 257, "sums over the chunks of eight-bit parts fit 16 bits");
 
 hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V, long long *counts,
-                         unsigned long long *n_invalid, void *partial, hipStream_t st) {
-    const int nchunks = hist_num_chunks(n_ids, V);
+                         unsigned long long *n_invalid, void *partial, size_t partial_bytes, hipStream_t st) {
+    int nchunks = hist_num_chunks(n_ids, V);
+    if (nchunks * chunk_bytes(V) > partial_bytes) nchunks = (int)(partial_bytes / chunk_bytes(V));
+    if (nchunks < 1) return hipErrorInvalidValue;
     const size_t lds = kHistLds;
     static LdsLimitOnce lds_limit;
     hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(hist_partial_kernel<false>),

@@ -190,3 +190,26 @@ def test_rank_order_by_bins_of_sampled_counts(kind, V):
     for k in sorted({1, V // 3 + 1, V}):
         a, _ = vt.build_trimmed_head(dc, None, k, order="rank")
         assert np.array_equal(a.cpu().numpy(), order[:k]), k
+
+
+# Streams of few chunks: a workspace for chunks of 65536 ids (what callers of earlier versions may have stored) counts the same;
+# ids at the edges of chunks, of the hottest bin's own words, one id alone, ids outside [0, V) with bits in the upper half
+@pytest.mark.parametrize("V,n_ids", [(128256, 200_000), (700, 65537), (65537, 16385), (40000, 1_000_003)])
+@pytest.mark.parametrize("dtype", [torch.int32, torch.int64])
+def test_count_few_chunks(V, n_ids, dtype):
+    rng = np.random.default_rng(n_ids)
+    hot = np.where(rng.random(n_ids) < 0.3, V - 1, rng.integers(0, V, size=n_ids))
+    bad = rng.integers(-5, V + 5, size=n_ids)
+    if dtype == torch.int64:
+        bad[::97] += 1 << 32
+    L = vt.load_library()
+    chunk = 2 * ((V + 3) // 4 * 4) + (V + 255) // 256
+    small = ((n_ids + 65535) // 65536 * chunk + 255) // 256 * 256
+    assert small <= L.vt_count_tokens_ws_bytes(V, n_ids)
+    for ids in (hot, bad, np.full(n_ids, V // 2), rng.integers(0, 2, size=n_ids) * (V - 1)):
+        d = torch.from_numpy(ids).to(dtype).cuda()
+        want = np.bincount(ids[(ids >= 0) & (ids < V)], minlength=V)
+        for size in (small, L.vt_count_tokens_ws_bytes(V, n_ids)):
+            inv = torch.zeros(1, dtype=torch.int64, device="cuda")
+            c = vt.count_tokens(d, V, n_invalid=inv, ws=torch.full((size,), 255, dtype=torch.uint8, device="cuda"))
+            assert np.array_equal(c.cpu().numpy(), want) and inv.item() == n_ids - want.sum()
