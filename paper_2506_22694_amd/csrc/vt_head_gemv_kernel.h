@@ -348,7 +348,8 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_gemv_kernel(const Step
 
     {
         const int sstride = NP * a.tpitch;
-        for (int i = w; i < a.n; i += NW) {
+        const EpilogueShare share = epilogue_share(a.n, NW, w);
+        for (int i = share.row; i < a.n; i += NW) {
             const float *zrow = zt + (size_t)i * a.tpitch;
             float *full = a.out_logp_full ? a.out_logp_full + (size_t)i * a.k + row0 : nullptr;
             unsigned long long *pms_slot = a.pms + (size_t)i * a.nblocks + blockIdx.x;
@@ -358,9 +359,9 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_gemv_kernel(const Step
                                            smem + (((size_t)S * sstride * sizeof(float) + 15) & ~(size_t)15)) +
                                        (size_t)w * kLargeTileCandCap;
             if (rows_b <= 2 * kWave)
-                block_epilogue_small(zrow, S, sstride, rows_b, a.L, id0, id1, full, pms_slot, pk_slot, lane, cand);
+                block_epilogue_small(zrow, S, sstride, rows_b, a.L, id0, id1, full, pms_slot, pk_slot, lane, share, cand);
             else
-                block_epilogue_large(zrow, S, sstride, rows_b, a.L, a.map + row0, full, pms_slot, pk_slot, lane, cand);
+                block_epilogue_large(zrow, S, sstride, rows_b, a.L, a.map + row0, full, pms_slot, pk_slot, lane, share, cand);
         }
     }
 }

@@ -400,7 +400,8 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
         constexpr int kCandPerWave = (MAXW > kStepWaves || XG) ? 3 * kWave : 2 * kWave;      // one key per tile row
         unsigned long long *cand =
             reinterpret_cast<unsigned long long *>(smem + (ztile > 8192 ? ztile : 8192)) + (size_t)w * kCandPerWave;
-        for (int i = w; i < a.n; i += NW) {
+        const EpilogueShare share = epilogue_share(a.n, NW, w);
+        for (int i = share.row; i < a.n; i += NW) {
             const float *zrow = zt + (size_t)i * tp;
             float *full = a.out_logp_full ? a.out_logp_full + (size_t)i * a.k + row0 : nullptr;
             unsigned long long *pms_slot = a.pms + (size_t)i * a.nlists + blockIdx.x;
@@ -409,17 +410,17 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
                 // a hidden row of another head: nothing of this tile is its business -- an empty list, and a
                 // (max, sum-exp) pair that adds nothing to any log-sum-exp
                 if ((int)((mh.head_of_row >> (8 * i)) & 0xFFull) != hd) {
-                    if (lane == 0) publish_u64(pms_slot, (unsigned long long)__float_as_uint(-3.0e38f));
-                    if (lane < a.L) publish_u64(pk_slot + lane, kNoKey);
+                    if (share.lse && lane == 0) publish_u64(pms_slot, (unsigned long long)__float_as_uint(-3.0e38f));
+                    if (share.keys && lane < a.L) publish_u64(pk_slot + lane, kNoKey);
                     continue;
                 }
             }
             // the logit is the sum of the KS partial tiles, in wave order
             if constexpr (MAXW > kStepWaves || XG) {
                 const int idq3[3] = {id0, id1, id2};
-                block_epilogue_core<3>(zrow, KS, a.n * tp, rows_b, a.L, idq3, full, pms_slot, pk_slot, lane, cand);
+                block_epilogue_core<3>(zrow, KS, a.n * tp, rows_b, a.L, idq3, full, pms_slot, pk_slot, lane, share, cand);
             } else {
-                block_epilogue_small(zrow, KS, a.n * tp, rows_b, a.L, id0, id1, full, pms_slot, pk_slot, lane, cand);
+                block_epilogue_small(zrow, KS, a.n * tp, rows_b, a.L, id0, id1, full, pms_slot, pk_slot, lane, share, cand);
             }
         }
     }

@@ -102,26 +102,22 @@ __device__ __forceinline__ void wave_publish_top_by_threshold(const unsigned (&o
     if (c0) cand[__builtin_amdgcn_mbcnt_hi((unsigned)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m0, 0u))] = k0;
     if (c1)
         cand[n0 + __builtin_amdgcn_mbcnt_hi((unsigned)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m1, 0u))] = k1;
+    // (the ranking reads eight keys at a time; with all 128 taken there is nothing to fill)
+    if (lane < 8 && ncand + lane < 2 * kWave) cand[ncand + lane] = kNoKey;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (c0 || c1) {
         int a0 = 0, a1 = 0;
-        int x = 0;
-        for (; x + 4 <= ncand; x += 4) {
-            unsigned long long t[4];
+        for (int x = 0; x < ncand; x += 8) {
+            unsigned long long t[8];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) t[q] = cand[x + q];       // every lane reads the same key: a broadcast
+            for (int q = 0; q < 8; ++q) t[q] = cand[x + q];       // every lane reads the same key: a broadcast
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 8; ++q) {
                 a0 += t[q] > k0 ? 1 : 0;
                 a1 += t[q] > k1 ? 1 : 0;
             }
-        }
-        for (; x < ncand; ++x) {
-            const unsigned long long t = cand[x];
-            a0 += t > k0 ? 1 : 0;
-            a1 += t > k1 ? 1 : 0;
         }
         if (c0 && a0 < L) publish_u64(pkeys_slot + a0, k0);
         if (c1 && a1 < L) publish_u64(pkeys_slot + a1, k1);
@@ -130,7 +126,7 @@ __device__ __forceinline__ void wave_publish_top_by_threshold(const unsigned (&o
     __builtin_amdgcn_wave_barrier();     // the next row of this wave reuses cand
 }
 
-// The same for Q candidates per lane (tiles of more than 128 rows); `cap` keys fit `cand`.  Returns false,
+// The same for Q candidates per lane (tiles of more than 128 rows); `cap` keys (a multiple of eight) fit `cand`, Q * 64 where that is less.  Returns false,
 // having published nothing, when more than `cap` candidates reach the threshold.
 constexpr int kLargeTileCandCap = 256;
 template <int Q>
@@ -163,21 +159,21 @@ __device__ __forceinline__ bool wave_publish_top_by_threshold_q(const unsigned (
         }
     }
     if (ncand > cap) return false;
+    // (the ranking reads eight keys at a time; a list of all Q * 64 keys needs no filling)
+    if (lane < 8 && ncand + lane < min(cap, Q * kWave)) cand[ncand + lane] = kNoKey;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     for (int c = lane; c < ncand; c += kWave) {
         const unsigned long long key = cand[c];
         int above = 0;
-        int x = 0;
-        for (; x + 8 <= ncand; x += 8) {
+        for (int x = 0; x < ncand; x += 8) {
             unsigned long long t[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) t[q] = cand[x + q];
 #pragma unroll
             for (int q = 0; q < 8; ++q) above += t[q] > key ? 1 : 0;
         }
-        for (; x < ncand; ++x) above += cand[x] > key ? 1 : 0;
         if (above < L) publish_u64(pkeys_slot + above, key);
     }
     if (lane < L && lane >= ncand) publish_u64(pkeys_slot + lane, kNoKey);
@@ -189,36 +185,66 @@ __device__ __forceinline__ bool wave_publish_top_by_threshold_q(const unsigned (
 // zrow: the row's logit tile in LDS (S partial sums per logit, `sstride` floats
 // apart).  Publishes (max, sum-exp) and the L best keys of this workgroup.
 // QMAX*64 >= rows_b.  idq: target ids of tile rows lane + 64*q.
+// What bounds it: about 1.7 us of dependent LDS round trips and reductions after the stream's last load, not arithmetic
+// (run twice, the second time takes as long).  Where a workgroup has two waves per hidden row, one does the keys and the
+// other (max, sum-exp); the partial sums are read in one go; the keys are ranked in whole groups of eight.  Together:
+// 4 x 1024 x 256 in fp32 10.2 -> 9.7 us, a round on 5000 x 3072 57.9 -> 55.7,
+// n = 8 on 128256 x 3072 125.0 -> 123.8, two heads 43.2 -> 42.9, n = 1 on 32768 x 2048 25.1 -> 25.0.
+struct EpilogueShare {
+    int row;           // the wave's first hidden row, >= n: none; the next ones follow a workgroup's waves apart
+    bool keys, lse;
+};
+__device__ __forceinline__ EpilogueShare epilogue_share(int n, int waves, int w) {
+    if (2 * n > waves) return EpilogueShare{w, true, true};
+    return w < 2 * n ? EpilogueShare{w < n ? w : w - n, w < n, w >= n} : EpilogueShare{n, false, false};
+}
 template <int QMAX>
 __device__ __forceinline__ void block_epilogue_core(const float *zrow, int S, int sstride, int rows_b, int L,
                                                     const int (&idq)[QMAX], float *__restrict__ logp_full_row,
                                                     unsigned long long *__restrict__ pms_slot,
-                                                    unsigned long long *__restrict__ pkeys_slot, int lane,
+                                                    unsigned long long *__restrict__ pkeys_slot, int lane, const EpilogueShare &share,
                                                     unsigned long long *cand = nullptr) {
     unsigned ord[QMAX];
     int id[QMAX];
     float zq[QMAX];
     float lmax = -INFINITY;
+    // the sum over the partial logits in ascending order; every lane reads -- past the tile's end its last logit again -- and
+    // all reads of a round are made before the first is used (one after the other they took 0.4 us with four partials)
+    constexpr int kParts = QMAX <= 4 ? 4 : 1;
 #pragma unroll
-    for (int q = 0; q < QMAX; ++q) {
-        const int t = lane + q * kWave;
-        ord[q] = 0u;
-        id[q] = idq[q];
-        zq[q] = -INFINITY;
-        if (t < rows_b) {
-            float z = 0.f;
-            for (int s = 0; s < S; ++s) z += zrow[(size_t)s * sstride + t];
-            if (logp_full_row) logp_full_row[t] = z;
-            zq[q] = z;
-            ord[q] = orderable_f32(z);
-            lmax = fmaxf(lmax, z);
+    for (int q = 0; q < QMAX; ++q) zq[q] = 0.f;
+    for (int s0 = 0; s0 < S; s0 += kParts) {
+        float part[kParts][QMAX];
+#pragma unroll
+        for (int s = 0; s < kParts; ++s) {
+#pragma unroll
+            for (int q = 0; q < QMAX; ++q) part[s][q] = zrow[(size_t)min(s0 + s, S - 1) * sstride + min(lane + q * kWave, rows_b - 1)];
+        }
+#pragma unroll
+        for (int s = 0; s < kParts; ++s) {
+#pragma unroll
+            for (int q = 0; q < QMAX; ++q) zq[q] = s0 + s < S ? zq[q] + part[s][q] : zq[q];
         }
     }
-    const float M = wave_max(lmax);
-    float ls = 0.f;
 #pragma unroll
-    for (int q = 0; q < QMAX; ++q) ls += __expf(zq[q] - M);   // exp(-inf) = 0 for absent rows
-    const float Ssum = wave_sum(ls);
+    for (int q = 0; q < QMAX; ++q) {
+        const bool ok = lane + q * kWave < rows_b;
+        if (logp_full_row != nullptr && share.keys && ok) logp_full_row[lane + q * kWave] = zq[q];
+        id[q] = idq[q];
+        ord[q] = ok ? orderable_f32(zq[q]) : 0u;
+        zq[q] = ok ? zq[q] : -INFINITY;
+        lmax = fmaxf(lmax, zq[q]);
+    }
+    if (share.lse) {
+        const float M = wave_max(lmax);
+        float ls = 0.f;
+#pragma unroll
+        for (int q = 0; q < QMAX; ++q) ls += __expf(zq[q] - M);   // exp(-inf) = 0 for absent rows
+        const float Ssum = wave_sum(ls);
+        if (lane == 0)
+            publish_u64(pms_slot, ((unsigned long long)__float_as_uint(Ssum) << 32) | __float_as_uint(M));
+    }
+    if (!share.keys) return;
     bool published = false;
     if constexpr (QMAX == 2) {
         if (cand != nullptr && L >= 5) {       // up to four rounds are no slower than the threshold (measured)
@@ -233,18 +259,16 @@ __device__ __forceinline__ void block_epilogue_core(const float *zrow, int S, in
         const unsigned long long key = wave_select_top<QMAX>(ord, id, L, lane);
         if (lane < L) publish_u64(pkeys_slot + lane, key);
     }
-    if (lane == 0)
-        publish_u64(pms_slot, ((unsigned long long)__float_as_uint(Ssum) << 32) | __float_as_uint(M));
 }
 
 // small tiles (<= 128 rows): ids were prefetched by the caller
 __device__ __forceinline__ void block_epilogue_small(const float *zrow, int S, int sstride, int rows_b, int L, int id0,
                                                   int id1, float *__restrict__ logp_full_row,
                                                   unsigned long long *__restrict__ pms_slot,
-                                                  unsigned long long *__restrict__ pkeys_slot, int lane,
+                                                  unsigned long long *__restrict__ pkeys_slot, int lane, const EpilogueShare &share,
                                                   unsigned long long *cand = nullptr) {
     const int idq[2] = {id0, id1};
-    block_epilogue_core<2>(zrow, S, sstride, rows_b, L, idq, logp_full_row, pms_slot, pkeys_slot, lane, cand);
+    block_epilogue_core<2>(zrow, S, sstride, rows_b, L, idq, logp_full_row, pms_slot, pkeys_slot, lane, share, cand);
 }
 
 // large tiles (<= 1024 rows): ids are read here; QMAX logits per lane, sized to the tile (4, 8 or 16)
@@ -253,26 +277,26 @@ __device__ __forceinline__ void block_epilogue_large_q(const float *zrow, int S,
                                                        const int *__restrict__ map_tile,
                                                        float *__restrict__ logp_full_row,
                                                        unsigned long long *__restrict__ pms_slot,
-                                                       unsigned long long *__restrict__ pkeys_slot, int lane,
+                                                       unsigned long long *__restrict__ pkeys_slot, int lane, const EpilogueShare &share,
                                                        unsigned long long *cand) {
     int idq[QMAX];
 #pragma unroll
     for (int q = 0; q < QMAX; ++q) idq[q] = map_tile[min(lane + q * kWave, rows_b - 1)];
-    block_epilogue_core<QMAX>(zrow, S, sstride, rows_b, L, idq, logp_full_row, pms_slot, pkeys_slot, lane, cand);
+    block_epilogue_core<QMAX>(zrow, S, sstride, rows_b, L, idq, logp_full_row, pms_slot, pkeys_slot, lane, share, cand);
 }
 __device__ __forceinline__ void block_epilogue_large(const float *zrow, int S, int sstride, int rows_b, int L,
                                                   const int *__restrict__ map_tile,
                                                   float *__restrict__ logp_full_row,
                                                   unsigned long long *__restrict__ pms_slot,
-                                                  unsigned long long *__restrict__ pkeys_slot, int lane,
+                                                  unsigned long long *__restrict__ pkeys_slot, int lane, const EpilogueShare &share,
                                                   unsigned long long *cand = nullptr) {
     if (rows_b <= 4 * kWave)
-        block_epilogue_large_q<4>(zrow, S, sstride, rows_b, L, map_tile, logp_full_row, pms_slot, pkeys_slot, lane, cand);
+        block_epilogue_large_q<4>(zrow, S, sstride, rows_b, L, map_tile, logp_full_row, pms_slot, pkeys_slot, lane, share, cand);
     else if (rows_b <= 8 * kWave)
-        block_epilogue_large_q<8>(zrow, S, sstride, rows_b, L, map_tile, logp_full_row, pms_slot, pkeys_slot, lane, cand);
+        block_epilogue_large_q<8>(zrow, S, sstride, rows_b, L, map_tile, logp_full_row, pms_slot, pkeys_slot, lane, share, cand);
     else
         block_epilogue_large_q<kStepMaxRowsPerBlock / kWave>(zrow, S, sstride, rows_b, L, map_tile, logp_full_row,
-                                                             pms_slot, pkeys_slot, lane, cand);
+                                                             pms_slot, pkeys_slot, lane, share, cand);
 }
 
 // ------------------------------------------------------------------ four hidden rows per pass

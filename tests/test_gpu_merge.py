@@ -45,3 +45,28 @@ def test_lists_of_two_heads_merge_like_one_heads(ks):
         one_ids, one_logp = vt.draft_head_step(h[i:i + 1].expand(2, d).contiguous(), heads[q][0], heads[q][1], m)
         assert torch.equal(ids[i], one_ids[0])
         assert (logp[i] - one_logp[0]).abs().max().item() <= 4e-6      # sums over other tiles: a few ulp of a log-sum-exp near 10
+
+
+# Logits of two values and many ties: whole tiles reach the threshold of a tile's selection (64, 128 or 144 candidates at once), and the
+# better value lies in runs that end at the edges of tiles; up to four hidden rows share a row's work between two waves
+@pytest.mark.parametrize("dtype,k,d", [("bf16", 130, 128), ("bf16", 5000, 256), ("bf16", 32767, 128), ("bf16", 128256, 3072), ("f32", 1024, 128), ("f32", 7001, 128)])
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 8])
+@pytest.mark.parametrize("m", [4, 7, 11])
+def test_ties_in_whole_tiles(dtype, k, d, n, m):
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(k + n)
+    h = torch.ones(n, d, dtype=t, device="cuda")
+    high = torch.rand(k, generator=g, device="cuda") < 0.5
+    high[k // 2:] = False
+    high[:min(k, 200)] = True
+    level = torch.where(high, 2.0, -1.0)                        # (exact in bf16, and so are the sums over powers of two of columns)
+    W = (level / 128).unsqueeze(1).expand(k, d).to(t).contiguous()
+    z = (level.double() * d / 128)
+    map_ = torch.arange(k, dtype=torch.int32, device="cuda") * 2 + 1
+    ids, logp, lse = vt.draft_head_step(h, W, map_, m, return_lse=True)
+    order = torch.sort(z, descending=True, stable=True).indices[:m]
+    want = torch.logsumexp(z, 0)
+    assert torch.equal(ids, map_[order].expand(n, m))           # equal logits: the smaller id first
+    # sums of up to 128256 exponentials in fp32: a few ulp of a log-sum-exp below 64
+    assert (lse.double() - want).abs().max().item() <= 2e-5
+    assert (logp.double() - (z[order] - want)).abs().max().item() <= 2e-5
