@@ -432,7 +432,7 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
 // T threads: 128 when n * m <= 64, else 512 (the waves beyond the second only help with the ranking; with more
 // threads the merging wave would not have the registers it needs).  BLOCK: all eight waves merge.
 template <int T, bool BLOCK>
-__global__ void __launch_bounds__(T) step_finalize_tree_kernel(const FinalizeArgs f) {
+__global__ void __launch_bounds__(BLOCK ? kBlockMergeLaunch : T) step_finalize_tree_kernel(const FinalizeArgs f) {
     static_assert(!BLOCK || T == kBlockMergeThreads, "one workgroup size for the merge by eight waves");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_last;
@@ -460,7 +460,7 @@ __global__ void __launch_bounds__(T) step_finalize_tree_kernel(const FinalizeArg
         }
     }
     __syncthreads();
-    if (!s_last) return;
+    if (!s_last || w >= T / kWave) return;      // (the ranking's barriers are met by the waves that are left)
     TreeArgs t;
     t.parent_cum = f.tree_cum;
     t.vals = f.out_logp;
@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(T) step_finalize_tree_kernel(const FinalizeArg
 }
 
 // Merges the per-tile partials, many lists of them: eight waves per hidden row.
-__global__ void __launch_bounds__(kBlockMergeThreads) step_finalize_block_kernel(const FinalizeArgs f) {
+__global__ void __launch_bounds__(kBlockMergeLaunch) step_finalize_block_kernel(const FinalizeArgs f) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -595,7 +595,7 @@ hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t s
         const size_t need = (size_t)N2 * 12 + 256;
         const size_t bytes = lds > need ? lds : need;
         if (block)
-            hipLaunchKernelGGL((step_finalize_tree_kernel<512, true>), dim3(f.n), dim3(512), bytes, st, f);
+            hipLaunchKernelGGL((step_finalize_tree_kernel<512, true>), dim3(f.n), dim3(kBlockMergeLaunch), bytes, st, f);
         else if (N <= kWave)
             hipLaunchKernelGGL((step_finalize_tree_kernel<128, false>), dim3(f.n), dim3(128), bytes, st, f);
         else
@@ -603,7 +603,7 @@ hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t s
         return hipGetLastError();
     }
     if (block) {
-        hipLaunchKernelGGL(step_finalize_block_kernel, dim3(f.n), dim3(kBlockMergeThreads), lds, st, f);
+        hipLaunchKernelGGL(step_finalize_block_kernel, dim3(f.n), dim3(kBlockMergeLaunch), lds, st, f);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(step_finalize_kernel, dim3(f.n), dim3(2 * kWave), lds, st, f);

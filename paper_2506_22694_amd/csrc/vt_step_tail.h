@@ -348,7 +348,7 @@ __device__ __forceinline__ void block_epilogue_rows4(const float *zt, int tp, in
         // Selection by threshold: T = the L-th largest of the 16 lanes' best logits, so at least L logits reach
         // it and the L best of the row are among those that do -- about L + 2 of the 128.  They are compacted
         // into 16 keys of LDS per row and each finds its rank by counting: no L dependent rounds.  More than 16
-        // candidates in any row of the wave (many equal logits; 3 in 1000 rows otherwise): the rounds below.
+        // candidates in any row of the wave (3 in 1000 rows): the second form; more than 32 (many equal logits): the rounds.
         unsigned bo = ord[0];
 #pragma unroll
         for (int q = 1; q < Q; ++q) bo = ord[q] > bo ? ord[q] : bo;
@@ -386,6 +386,44 @@ __device__ __forceinline__ void block_epilogue_rows4(const float *zt, int tp, in
                 if (gl < L && gl >= total) publish_u64(slot + gl, kNoKey);
             }
             __builtin_amdgcn_wave_barrier();     // the wave's next rows reuse cand
+            return;
+        }
+        // 17 to 32 in a row: two rows after each other have 32 slots each, a lane ranks two keys.  (A tile of 64 hidden
+        // rows meets one such row in five times, so some tile of every launch does, and the launch ends with the last tile.)
+        if (__ballot(total > 32) == 0ull) {
+            unsigned long long *crow = cand + 32 * (g & 1);
+            const unsigned long long *cr = crow;
+            for (int half = 0; half < 2; ++half) {
+                const bool turn = (g >> 1) == half;
+                if (turn) {
+                    crow[gl] = kNoKey;
+                    crow[gl + 16] = kNoKey;
+                    int pos = (int)incl - cnt;
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        if (ord[q] >= T) crow[pos++] = ((unsigned long long)ord[q] << 32) | (unsigned)(~(unsigned)id[q]);
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const unsigned long long k0 = cr[gl], k1 = cr[gl + 16];
+                int r0 = 0, r1 = 0;
+#pragma unroll 8
+                for (int x = 0; x < 32; ++x) {
+                    const unsigned long long t = cr[x];
+                    r0 += t > k0 ? 1 : 0;
+                    r1 += t > k1 ? 1 : 0;
+                }
+                if (turn && active) {
+                    unsigned long long *slot = pkeys + ((size_t)i * nlists + blk) * L;
+                    if (gl < total && r0 < L) publish_u64(slot + r0, k0);
+                    if (gl + 16 < total && r1 < L) publish_u64(slot + r1, k1);
+                    if (gl < L && gl >= total) publish_u64(slot + gl, kNoKey);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();     // the next two rows, or the wave's next four, reuse cand
+            }
             return;
         }
     }
@@ -800,9 +838,13 @@ __device__ __forceinline__ void finalize_row_alone(const FinalizeArgs &f, int i,
 // rounds: m = 8, k = 65536 (512 lists) 10.0 -> 5.2 us, k = 128256 (668 lists of 64 hidden rows) 15.3 -> 5.4.  With more
 // than 8 hidden rows it is also the faster one for lists that one wave could hold (256 lists of 8 keys: n = 64 6.1 -> 5.4,
 // n = 128 6.7 -> 4.9); up to 8 rows the two tie (n = 8: 4.6 / 4.6), and so do they below about 1000 keys.
+// What is left is a chain: loads, a reduction, a barrier, one LDS atomic per wave, a barrier, the ranking.  The log-sum-exp is
+// reduced beside it in a ninth wave, and up to 2048 keys are loaded as four per thread, not eight with half of them twice
+// (with the second form of the selection in the tiles, 64 rows of 32768 x 4096 49.7 -> 49.4 us, 32 of 32959 x 4096 48.55 -> 48.2).
 // Returns false, having written nothing, when more than kBlockMaxCand keys reach T (massive ties).
 constexpr int kBlockMergeWaves = 8;
 constexpr int kBlockMergeThreads = kBlockMergeWaves * kWave;
+constexpr int kBlockMergeLaunch = kBlockMergeThreads + kWave;      // and a wave for the log-sum-exp
 constexpr int kBlockMergeMaxKeys = 32 * kBlockMergeThreads;
 constexpr int kBlockMergeMaxLists = 4 * kBlockMergeThreads;
 constexpr int kBlockMaxCand = 1024;
@@ -811,8 +853,8 @@ static_assert(kStepMaxK / kMfmaTileRows <= kBlockMergeMaxLists && kStepMaxK / kM
 
 struct BlockMergeLds {
     unsigned long long cand[kBlockMaxCand];
-    float wave_max[kBlockMergeWaves], wave_sum[kBlockMergeWaves];
     unsigned wave_kth[kBlockMergeWaves];
+    float lse;
     int ncand;
 };
 
@@ -828,24 +870,42 @@ __device__ __forceinline__ bool finalize_row_block(const unsigned long long *__r
                                                    int m, BlockMergeLds &s, int *__restrict__ out_ids_row,
                                                    float *__restrict__ out_logp_row, float *__restrict__ out_lse_i,
                                                    float *__restrict__ lse_buf_i, int lane, int w) {
-    constexpr int MS = kBlockMergeMaxLists / kBlockMergeThreads;
-    const int tid = w * kWave + lane;
-    unsigned long long ms[MS], key[U];
+    if (w == kBlockMergeWaves) {
+        float lm = -INFINITY, ls = 0.f;
+        for (int b0 = 0; b0 < B; b0 += 4 * kWave) {
+            unsigned long long ms[4];
 #pragma unroll
-    for (int q = 0; q < MS; ++q) ms[q] = acquire_u64(pms_row + min(tid + kBlockMergeThreads * q, B - 1));
+            for (int q = 0; q < 4; ++q) ms[q] = acquire_u64(pms_row + min(b0 + q * kWave + lane, B - 1));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (b0 + q * kWave + lane < B) {
+                    const float Mb = __uint_as_float((unsigned)ms[q]);
+                    const float Sb = __uint_as_float((unsigned)(ms[q] >> 32));
+                    const float Mn = fmaxf(lm, Mb);
+                    ls = ls * __expf(lm - Mn) + Sb * __expf(Mb - Mn);   // exp(-inf) = 0 on the first term
+                    lm = Mn;
+                }
+            }
+        }
+        __syncthreads();
+        const float M = wave_max(lm);
+        const float lse = lane_uniform(M + __logf(wave_sum(ls * __expf(lm - M))));
+        if (lane == 0) s.lse = lse;
+        __syncthreads();
+        if (s.ncand > kBlockMaxCand) {
+            __syncthreads();
+            return false;
+        }
+        if (lane == 0) {
+            *lse_buf_i = lse;
+            if (out_lse_i) *out_lse_i = lse;
+        }
+        return true;
+    }
+    const int tid = w * kWave + lane;
+    unsigned long long key[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) key[u] = acquire_u64(pkeys_row + min(u * kBlockMergeThreads + tid, total - 1));
-    float lm = -INFINITY, ls = 0.f;
-#pragma unroll
-    for (int q = 0; q < MS; ++q) {
-        if (tid + kBlockMergeThreads * q < B) {
-            const float Mb = __uint_as_float((unsigned)ms[q]);
-            const float Sb = __uint_as_float((unsigned)(ms[q] >> 32));
-            const float Mn = fmaxf(lm, Mb);
-            ls = ls * __expf(lm - Mn) + Sb * __expf(Mb - Mn);   // exp(-inf) = 0 on the first term
-            lm = Mn;
-        }
-    }
     unsigned top = 0u;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -853,34 +913,29 @@ __device__ __forceinline__ bool finalize_row_block(const unsigned long long *__r
         const unsigned o = (unsigned)(key[u] >> 32);
         top = o > top ? o : top;
     }
-    const float Mw = wave_max(lm);
-    const float Sw = w * kWave < B ? wave_sum(ls * __expf(lm - Mw)) : 0.f;
     const unsigned kth = m <= kBlockMergeWaves ? wave_max_u32(top)
                                                : wave_kth_largest_prefix16(top, (m + kBlockMergeWaves - 1) / kBlockMergeWaves);
-    if (lane == 0) {
-        s.wave_max[w] = Mw;
-        s.wave_sum[w] = Sw;
-        s.wave_kth[w] = kth;
-    }
+    if (lane == 0) s.wave_kth[w] = kth;
     if (tid == 0) s.ncand = 0;
     __syncthreads();
-    float M = s.wave_max[0];
     unsigned T = s.wave_kth[0];
 #pragma unroll
-    for (int q = 1; q < kBlockMergeWaves; ++q) {
-        M = fmaxf(M, s.wave_max[q]);
-        T = s.wave_kth[q] < T ? s.wave_kth[q] : T;
-    }
-    float S = 0.f;
-#pragma unroll
-    for (int q = 0; q < kBlockMergeWaves; ++q) S += s.wave_sum[q] * __expf(s.wave_max[q] - M);    // fixed order
-    const float lse = lane_uniform(M + __logf(S));
+    for (int q = 1; q < kBlockMergeWaves; ++q) T = s.wave_kth[q] < T ? s.wave_kth[q] : T;
     T = T == 0u ? 1u : T;               // a wave without keys: every real key is a candidate
+    int mine_n = 0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if ((unsigned)(key[u] >> 32) >= T) {
-            const int slot = atomicAdd(&s.ncand, 1);
-            if (slot < kBlockMaxCand) s.cand[slot] = key[u];
+    for (int u = 0; u < U; ++u) mine_n += __popcll(__ballot((unsigned)(key[u] >> 32) >= T));
+    if (mine_n != 0) {
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&s.ncand, mine_n);      // (one per wave: one per load of keys took a round trip each)
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool c = (unsigned)(key[u] >> 32) >= T;
+            const unsigned long long mask = __ballot(c);
+            const int slot = at + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+            if (c && slot < kBlockMaxCand) s.cand[slot] = key[u];
+            at += __popcll(mask);
         }
     }
     __syncthreads();
@@ -889,33 +944,29 @@ __device__ __forceinline__ bool finalize_row_block(const unsigned long long *__r
         __syncthreads();                // the caller reuses this LDS
         return false;
     }
+    const float lse = s.lse;
     for (int c = tid; c < ncand; c += kBlockMergeThreads) {
         const unsigned long long mine = s.cand[c];
         int above = 0;
-        int x = 0;
-        for (; x + 8 <= ncand; x += 8) {
+        for (int x = 0; x < ncand; x += 8) {
             unsigned long long t[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) t[q] = s.cand[x + q];      // every lane reads the same key: a broadcast
 #pragma unroll
-            for (int q = 0; q < 8; ++q) above += t[q] > mine ? 1 : 0;
+            for (int q = 0; q < 8; ++q) above += x + q < ncand && t[q] > mine ? 1 : 0;
         }
-        for (; x < ncand; ++x) above += s.cand[x] > mine ? 1 : 0;
         if (above < m) store_result(out_ids_row, out_logp_row, above, key_id(mine), key_logit(mine) - lse);
-    }
-    if (tid == 0) {
-        *lse_buf_i = lse;
-        if (out_lse_i) *out_lse_i = lse;
     }
     return true;
 }
 
-// Merges hidden row i of `f` with all eight waves; false: nothing written (massive ties), the rounds have to do it.
 __device__ __forceinline__ bool merge_row_block(const FinalizeArgs &f, int i, int o, BlockMergeLds &s, int lane, int w) {
     const unsigned long long *pms = f.pms + (size_t)i * f.nlists, *pkeys = f.pkeys + (size_t)i * f.nlists * f.L;
     int *ids = f.out_ids + (size_t)o * f.m;
     float *logp = f.out_logp + (size_t)o * f.m, *lse = f.out_lse ? f.out_lse + o : nullptr;
     const int total = f.nlists * f.L;
+    if (total <= 4 * kBlockMergeThreads)
+        return finalize_row_block<4>(pms, pkeys, f.nlists, total, f.m, s, ids, logp, lse, f.lse_buf + i, lane, w);
     if (total <= 8 * kBlockMergeThreads)
         return finalize_row_block<8>(pms, pkeys, f.nlists, total, f.m, s, ids, logp, lse, f.lse_buf + i, lane, w);
     if (total <= 16 * kBlockMergeThreads)

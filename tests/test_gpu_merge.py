@@ -70,3 +70,21 @@ def test_ties_in_whole_tiles(dtype, k, d, n, m):
     # sums of up to 128256 exponentials in fp32: a few ulp of a log-sum-exp below 64
     assert (lse.double() - want).abs().max().item() <= 2e-5
     assert (logp.double() - (z[order] - want)).abs().max().item() <= 2e-5
+
+
+# 17 to 32 equal best logits in a tile of 9 and more hidden rows (a row's candidates fill two slots per lane), one more, and rows next to
+# them where all the other tokens of the tile tie
+@pytest.mark.parametrize("n,k,d,best", [(9, 2000, 256, 17), (12, 32768, 256, 24), (12, 32959, 128, 32), (33, 33000, 128, 33), (64, 70000, 128, 20), (130, 40000, 128, 31)])
+@pytest.mark.parametrize("m", [1, 5, 8])
+def test_ties_of_some_tokens_in_tiles_of_many_rows(n, k, d, best, m):
+    W = torch.full((k, d), -0.25, dtype=torch.bfloat16, device="cuda")
+    W[torch.arange(k, device="cuda") % 128 < best] = 0.5
+    h = torch.where(torch.arange(n, device="cuda") % 3 == 1, -0.125, 0.125).bfloat16().unsqueeze(1).expand(n, d).contiguous()
+    map_ = torch.arange(k, dtype=torch.int32, device="cuda") * 2 + 1
+    ids, logp, lse = vt.draft_head_step(h, W, map_, m, return_lse=True)
+    z = h.double() @ W.double().T
+    order = torch.sort(z, dim=1, descending=True, stable=True).indices[:, :m]
+    want = torch.logsumexp(z, 1)
+    assert torch.equal(ids, map_[order])
+    assert (lse.double() - want).abs().max().item() <= 2e-5       # (fp32 sums of up to 70000 exponentials)
+    assert (logp.double() - (z.gather(1, order) - want.unsqueeze(1))).abs().max().item() <= 2e-5
