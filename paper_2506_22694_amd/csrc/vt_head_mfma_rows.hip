@@ -288,6 +288,12 @@ head_mfma_kernel(const MfmaArgs a) {
 // k-steps of MT * NTT products; the operands of one are read while the other is multiplied, the barrier that hands the
 // slot on sits between them, and the loads of the freed slot are spread over the products that follow it -- issued
 // in one go they kept the wave from its products (n = 256, k = 32768, d = 8192: 149 against 140 us).
+// From 129 hidden rows on a stage's pieces of h are asked for before W's: h comes from the L2 soon and keeps the queue
+// short for W behind it (with W first: n = 192, k = 32768, d = 3072 62.0 against 60.6 us, n = 160, d = 8192 131.8 / 128.1,
+// n = 256, d = 8192 167.6 / 165.9, n = 256, k = 5000, d = 4096 53.0 / 51.2; n = 200, d = 8192 a tie); with up to 128, where W's pieces
+// are the larger part, W comes first (n = 128, k = 5000, d = 3072: 29.4 us against 30.2 with h first).
+// The march of n = 256, d = 8192 is bound by power: the clock falls from 2.4 to 1.6 .. 1.9 GHz while loads and products run
+// together, and stays at 2.4 with either alone.
 // PACKED: h was re-laid by pack_h_kernel, a stage's pieces one after the other as they lie in LDS.
 template <int MT, int NTT, int NST, int NR, bool PACKED>
 __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const MfmaArgs a) {
@@ -296,6 +302,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
     constexpr int kPieces = (TM + TN) / 8, LPW = (kPieces + kStepWaves - 1) / kStepWaves;
     constexpr unsigned kStage = (TM + TN) * 128u;
     constexpr int NP = MT * NTT;               // products per k-step
+    constexpr bool kHiddenFirst = NTT >= 3;
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wn = w & 3, wm = w >> 2;
@@ -388,7 +395,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
 #pragma unroll
         for (int x = 0; x < NP; ++x) {
             if (x % kEvery == 0 && x / kEvery < LPW) {
-                if (more) load_piece(x / kEvery);
+                if (more) load_piece(kHiddenFirst ? LPW - 1 - x / kEvery : x / kEvery);
                 __builtin_amdgcn_sched_barrier(0);
             }
             product(x, a1, b1);
@@ -396,7 +403,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
         }
 #pragma unroll
         for (int j = 0; j < LPW; ++j) {
-            if (j * kEvery >= NP && more) load_piece(j);
+            if (j * kEvery >= NP && more) load_piece(kHiddenFirst ? LPW - 1 - j : j);
         }
         if (NR > 1 && march.rotate && --left == 0 && s + 1 < march.ns) {
             sums.close(acc, march.rot, closed);
@@ -436,18 +443,15 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
 }
 
 // Re-lays h for the kernel above: piece (stage u, 8 rows p) is 1 KiB, lane l's 16 bytes at 16 l (rows past n repeat
-// row n - 1; their products are never read).
-__global__ void __launch_bounds__(256) pack_h_kernel(const u32x4 *__restrict__ h, u32x4 *__restrict__ hp, int n, int d,
-                                                     int pieces, long long total) {
-    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (x >= total) return;
-    const int lane = (int)(x & 63);
-    const long long y = x >> 6;
-    const int p = (int)(y % pieces);
-    const long long u = y / pieces;
+// row n - 1; their products are never read).  A wave per piece: four stages of a workgroup, p = blockIdx.y (divided out of
+// one index in 64 bits, the address took longer than the copy).
+__global__ void __launch_bounds__(256) pack_h_kernel(const u32x4 *__restrict__ h, u32x4 *__restrict__ hp, int n, int d) {
+    const int lane = (int)(threadIdx.x & 63), p = (int)blockIdx.y;
+    const int u = (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (u >= d / kStageCols) return;
     const int r = 8 * p + (lane >> 3);
     const int c = (lane & 7) ^ ((r >> 1) & 7);
-    hp[x] = h[(long long)min(r, n - 1) * (d / 8) + u * 8 + c];
+    hp[((size_t)u * gridDim.y + p) * kWave + lane] = h[(size_t)min(r, n - 1) * (unsigned)(d / 8) + (unsigned)(u * 8 + c)];
 }
 
 template <auto kern>
@@ -527,10 +531,8 @@ hipError_t launch_wide(const MfmaArgs &a, size_t lds, hipStream_t st) {
     constexpr int NST = wide_stages(MT, NTT), NR = wide_ranges(MT, NTT);
     if (a.hpack == nullptr) return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, NR, false>>(a, kStepWaves * kWave, lds, st);
     if constexpr (NTT == 4) {
-        const int pieces = 8 * NTT;
-        const long long total = (long long)(a.d / kStageCols) * pieces * kWave;
-        hipLaunchKernelGGL(pack_h_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, static_cast<const u32x4 *>(a.h),
-                           static_cast<u32x4 *>(a.hpack), a.n, a.d, pieces, total);
+        hipLaunchKernelGGL(pack_h_kernel, dim3((unsigned)((a.d / kStageCols + 3) / 4), 8 * NTT), dim3(256), 0, st, static_cast<const u32x4 *>(a.h),
+                           static_cast<u32x4 *>(a.hpack), a.n, a.d);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, NR, true>>(a, kStepWaves * kWave, lds, st);
