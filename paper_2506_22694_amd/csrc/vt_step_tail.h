@@ -840,7 +840,8 @@ __device__ __forceinline__ void finalize_row_alone(const FinalizeArgs &f, int i,
 // n = 128 6.7 -> 4.9); up to 8 rows the two tie (n = 8: 4.6 / 4.6), and so do they below about 1000 keys.
 // What is left is a chain: loads, a reduction, a barrier, one LDS atomic per wave, a barrier, the ranking.  The log-sum-exp is
 // reduced beside it in a ninth wave, and up to 2048 keys are loaded as four per thread, not eight with half of them twice
-// (with the second form of the selection in the tiles, 64 rows of 32768 x 4096 49.7 -> 49.4 us, 32 of 32959 x 4096 48.55 -> 48.2).
+// (with the second form of the selection in the tiles, 64 rows of 32768 x 4096 51.3 -> 50.7 us, 12 of 5000 x 3072 16.8 -> 16.2;
+// with a comparison of places beside every one of keys instead of the empty keys behind the last half of that was lost).
 // Returns false, having written nothing, when more than kBlockMaxCand keys reach T (massive ties).
 constexpr int kBlockMergeWaves = 8;
 constexpr int kBlockMergeThreads = kBlockMergeWaves * kWave;
@@ -917,6 +918,8 @@ __device__ __forceinline__ bool finalize_row_block(const unsigned long long *__r
                                                : wave_kth_largest_prefix16(top, (m + kBlockMergeWaves - 1) / kBlockMergeWaves);
     if (lane == 0) s.wave_kth[w] = kth;
     if (tid == 0) s.ncand = 0;
+    // (the ranking reads eight keys at a time: what is behind the last candidate loses against all of them)
+    for (int x = tid; x < kBlockMaxCand; x += kBlockMergeThreads) s.cand[x] = kNoKey;
     __syncthreads();
     unsigned T = s.wave_kth[0];
 #pragma unroll
@@ -953,7 +956,7 @@ __device__ __forceinline__ bool finalize_row_block(const unsigned long long *__r
 #pragma unroll
             for (int q = 0; q < 8; ++q) t[q] = s.cand[x + q];      // every lane reads the same key: a broadcast
 #pragma unroll
-            for (int q = 0; q < 8; ++q) above += x + q < ncand && t[q] > mine ? 1 : 0;
+            for (int q = 0; q < 8; ++q) above += t[q] > mine ? 1 : 0;
         }
         if (above < m) store_result(out_ids_row, out_logp_row, above, key_id(mine), key_logit(mine) - lse);
     }
