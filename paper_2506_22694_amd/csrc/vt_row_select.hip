@@ -11,6 +11,9 @@
 //           so the m best logits are all >= T;
 //   pass 2  logits >= T become candidate keys in LDS (typically a few dozen), ranked by counting (rows of up to 32768
 //           logits stay in registers in between, longer ones are sifted as they go by: row_select_kernel);
+//   (up to 32768 logits a row is bound by a chain: the loads, a reduction, two barriers, a trip to the map, the ranking.  The
+//   ranking of the logits alone runs beside that trip, and the sum of exponentials waits for no barrier of its own: n = 128 on
+//   32768 x 2048, m = 16 43.1 -> 42.7 us, n = 16 on 5000 x 3072 18.1 -> 17.9, n = 64 on 16384 x 2048, m = 32 a tie)
 //   if more than 1024 logits reach T (massive ties, e.g. h = 0) the m best are extracted one by one.
 #include "vt_device.h"
 #include "vt_step.h"
@@ -24,16 +27,6 @@ constexpr int kRowWaves = kRowThreads / kWave;
 constexpr int kRowMaxCand = 1024;
 constexpr int kRowMaxRaw = 4096;      // rows of several stretches: logits above the first stretch's threshold
 
-__device__ __forceinline__ float block_sum_f32(float v, float *red, int lane, int w) {
-    v = wave_sum(v);
-    __syncthreads();
-    if (lane == 0) red[w] = v;
-    __syncthreads();
-    float r = 0.f;
-#pragma unroll
-    for (int q = 0; q < kRowWaves; ++q) r += red[q];     // fixed order: reproducible
-    return r;
-}
 __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v, unsigned long long *red, int lane,
                                                             int w) {
     v = wave_max_u64(v);
@@ -193,10 +186,14 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     const int i = blockIdx.x;
     const float *zr = z + (size_t)i * k;
     float v[kRowVals];
+    // (all of this is first used behind the barrier of row_threshold.  Candidates are ranked in whole groups of eight: what is
+    // behind the last one loses against all of them)
     if (tid == 0) {
-        s_nraw = 0u;       // (both are first used behind the barrier of row_threshold)
+        s_nraw = 0u;
         s_ncand = 0u;
     }
+    cand[tid] = kNoKey;
+    if constexpr (!SIFT) rawv[tid] = -INFINITY;
 
     // ---- pass 1: (max, sum-exp) and the thread's largest logit
     float lm = -INFINITY, ls = 0.f;
@@ -230,9 +227,11 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     }
     row_threshold(lm, m, tmax, lane, w, T, Mo);
     const float M = from_orderable_f32(Mo);      // k >= 1: some lane holds an element
-    const float S = block_sum_f32(lm == -INFINITY ? 0.f : ls * __expf(lm - M), redf, lane, w);
-    const float lse = M + __logf(S);
     const float Tf = threshold_f32(T);
+    {
+        const float Sw = wave_sum(lm == -INFINITY ? 0.f : ls * __expf(lm - M));
+        if (lane == 0) redf[w] = Sw;             // (summed up behind the barrier that the candidates need anyway)
+    }
 
     // ---- pass 2: every logit >= T is a candidate
     if constexpr (MODE == kRowWhole) {
@@ -256,40 +255,68 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     }
     const int nraw = (int)s_nraw;
     int ncand = nraw;
-    if (nraw <= (int)kRaw) {
+    if (SIFT && nraw <= (int)kRaw) {
         // the candidates' target ids, all requested at once
-        if constexpr (!SIFT) {
-            for (int c = tid; c < nraw; c += kRowThreads) cand[c] = make_key(rawv[c], map[rawj[c]]);
-            __syncthreads();
-        } else {
-            for (int c = tid; c < nraw; c += kRowThreads) {
-                if (rawv[c] >= Tf) {
-                    const unsigned slot = atomicAdd(&s_ncand, 1u);
-                    if (slot < (unsigned)kRowMaxCand) cand[slot] = make_key(rawv[c], map[rawj[c]]);
-                }
+        for (int c = tid; c < nraw; c += kRowThreads) {
+            if (rawv[c] >= Tf) {
+                const unsigned slot = atomicAdd(&s_ncand, 1u);
+                if (slot < (unsigned)kRowMaxCand) cand[slot] = make_key(rawv[c], map[rawj[c]]);
             }
-            __syncthreads();
-            ncand = (int)s_ncand;
         }
+        __syncthreads();
+        ncand = (int)s_ncand;
     }
+    float S = 0.f;
+#pragma unroll
+    for (int q = 0; q < kRowWaves; ++q) S += redf[q];     // fixed order: reproducible
+    const float lse = M + __logf(S);
     if (ncand <= kRowMaxCand) {
-        // rank by counting: keys are distinct (distinct target ids)
-        for (int c = tid; c < ncand; c += kRowThreads) {
-            const unsigned long long key = cand[c];
+        // rank by counting: keys are distinct (distinct target ids).  Without a thinning in between the logits alone are ranked
+        // while the trip to the map for the target id is under way; a logit that is there twice waits for the keys.
+        auto by_keys = [&](unsigned long long key) {
             unsigned above = 0;
-            int x = 0;
-            for (; x + 8 <= ncand; x += 8) {
+            for (int x = 0; x < ncand; x += 8) {
                 unsigned long long t[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) t[u] = cand[x + u];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) above += t[u] > key ? 1u : 0u;
             }
-            for (; x < ncand; ++x) above += cand[x] > key ? 1u : 0u;
-            if ((int)above < m) {
+            return (int)above;
+        };
+        auto store = [&](int above, unsigned long long key) {
+            if (above < m) {
                 out_ids[(size_t)i * m + above] = key_id(key);
                 out_logp[(size_t)i * m + above] = key_logit(key) - lse;
             }
+        };
+        static_assert(kRowMaxCand == kRowThreads && kRowMaxCand % 8 == 0 && kRaw % 8 == 0);
+        if constexpr (SIFT) {
+            if (tid < ncand) store(by_keys(cand[tid]), cand[tid]);
+        } else {
+            unsigned long long key = 0ull;
+            bool twice = false;
+            if (tid < ncand) {
+                const float mine = rawv[tid];
+                const int id = map[rawj[tid]];
+                int above = 0, equal = 0;
+                for (int x = 0; x < ncand; x += 8) {
+                    float t[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) t[u] = rawv[x + u];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        above += t[u] > mine ? 1 : 0;
+                        equal += t[u] == mine ? 1 : 0;
+                    }
+                }
+                key = make_key(mine, id);
+                cand[tid] = key;
+                twice = equal > 1;
+                if (!twice) store(above, key);
+            }
+            __syncthreads();
+            if (twice) store(by_keys(key), key);
         }
     } else {
         // massive ties: take the best remaining key, m times (each round re-reads the row from the L2)

@@ -88,3 +88,31 @@ def test_ties_of_some_tokens_in_tiles_of_many_rows(n, k, d, best, m):
     assert torch.equal(ids, map_[order])
     assert (lse.double() - want).abs().max().item() <= 2e-5       # (fp32 sums of up to 70000 exponentials)
     assert (logp.double() - (z.gather(1, order) - want.unsqueeze(1))).abs().max().item() <= 2e-5
+
+
+# Stored logits: a row's candidates are ranked by their logits alone unless one is there twice.  Pairs, triples and a run of equal logits
+# at the places around the m-th, target ids in no order; rows of one stretch and of several, aligned and not
+@pytest.mark.parametrize("n,k", [(16, 1500), (20, 5000), (33, 32767), (64, 32768), (17, 40001)])
+@pytest.mark.parametrize("m,run", [(9, 2), (16, 3), (16, 40), (33, 2)])
+def test_equal_logits_among_stored_ones(n, k, m, run):
+    d = 128
+    g = torch.Generator(device="cuda").manual_seed(k + m)
+    W = torch.zeros(k, d, dtype=torch.bfloat16, device="cuda")
+    W[:, 0] = torch.randint(-8, 1, (k,), generator=g, device="cuda").bfloat16()       # the field: ties below zero
+    places = torch.randperm(k, generator=g, device="cuda")
+    W[places[:m - 1], 0] = torch.arange(2, m + 1, device="cuda").bfloat16()           # m - 1 different logits
+    W[places[m - 1:m - 1 + run], 0] = 1.0                                             # the m-th: `run` times
+    if run > 2:
+        W[places[m + 60:m + 62], 0] = float(m)                                        # and the best one three times
+    h = torch.zeros(n, d, dtype=torch.bfloat16, device="cuda")
+    h[:, 0] = 2.0 ** -(torch.arange(n, device="cuda") % 3).float()
+    map_ = torch.randperm(4 * k, generator=g, device="cuda")[:k].int()
+    assert "row_select" in vt.draft_head_step_plan(n, k, d, m)
+    ids, logp, lse = vt.draft_head_step(h, W, map_, m, return_lse=True)
+    z = (h[:, :1].double() * W[:, 0].double())
+    by_id = torch.argsort(map_.long())
+    order = by_id[torch.sort(z[:, by_id], dim=1, descending=True, stable=True).indices[:, :m]]
+    want = torch.logsumexp(z, 1)
+    assert torch.equal(ids, map_[order])
+    assert (lse.double() - want).abs().max().item() <= 2e-5       # (fp32 sums of up to 40001 exponentials)
+    assert (logp.double() - (z.gather(1, order) - want.unsqueeze(1))).abs().max().item() <= 2e-5
