@@ -51,6 +51,9 @@ MIN_HAND_LOADS = {"vt_head_mfma.hip": 250, "vt_head_gemv_np1.hip": 150, "vt_head
 # (1138 today).
 MIN_LDS_LOADS = {"vt_head_mfma_rows.hip": 500}
 
+# The sources with buffer loads, which are checked for scalar offsets that the descriptor's size may not cover.
+BUFFER_LOADS = ("vt_count.hip",)
+
 
 def _scratch_users(remarks: str):
     """(kernel, bytes per lane) for every kernel the resource-usage remarks report with scratch memory."""
@@ -65,19 +68,34 @@ def _scratch_users(remarks: str):
     return out
 
 
-def _inflight_violations(src: str):
-    """Compiles src to gfx950 assembly (same flags as the object) and runs the in-flight register check."""
+def device_assembly(src: str) -> str:
+    """The gfx950 assembly of src, compiled with the flags of the object."""
+    r = subprocess.run([HIPCC] + FLAGS + ["--cuda-device-only", "-S", src, "-o", "-"], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc -S failed on {src}:\n{r.stderr}")
+    return r.stdout
+
+
+def _lint():
     try:
         from . import inflight_lint
     except ImportError:      # run as a script
         import inflight_lint
-    asm = os.path.join(OBJ, os.path.basename(src)[:-4] + ".s")
-    r = subprocess.run([HIPCC] + FLAGS + ["--cuda-device-only", "-S", src, "-o", asm], capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"hipcc -S failed on {src}:\n{r.stderr}")
-    with open(asm) as f:
-        text = f.read()
-    os.remove(asm)
+    return inflight_lint
+
+
+def _check_buffer_loads(src: str):
+    bad, loads = _lint().check_buffer_offsets(device_assembly(src))
+    if loads == 0:
+        raise RuntimeError(f"{os.path.basename(src)}: no buffer load found, the check of their offsets would pass anything")
+    if bad:
+        raise RuntimeError(f"{os.path.basename(src)}: buffer loads with a scalar offset that the descriptor's size may not "
+                           f"cover (kernel, line in the device assembly, text): {bad[:5]}")
+
+
+def _inflight_violations(src: str):
+    """Runs the in-flight register check on the gfx950 assembly of src."""
+    inflight_lint, text = _lint(), device_assembly(src)
     bad, followed = inflight_lint.check_asm(text)
     hazards, into_lds = inflight_lint.check_m0(text)
     floor = MIN_HAND_LOADS.get(os.path.basename(src), 0)
@@ -116,6 +134,12 @@ def _compile(src: str, force: bool) -> str:
                     raise RuntimeError(f"{base}: registers of hand-issued loads are touched before their wait "
                                        f"(kernel, line of the load, line and text of the instruction in the "
                                        f"device assembly): {touched[:5]}")
+        if base in BUFFER_LOADS and r.returncode == 0:
+            try:
+                _check_buffer_loads(src)
+            except RuntimeError:
+                os.remove(obj)
+                raise
         lines = r.stderr.splitlines()
         if check and r.returncode == 0:
             lines = []      # the remarks (and their source excerpts) are not diagnostics

@@ -229,13 +229,13 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
     const u32x4 *at_vec = vp + v0;
     long long left = v1 - v0;
     u32x4 q[kHistUnroll];
-    auto load_batch = [&](int vectors) {      // of `vectors` that are there; those past the end are zero, and not counted
-        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(at_vec), 0, vectors * 16, 0x00020000);
+    auto descriptor = [&](int vectors) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(at_vec), 0, vectors * 16, 0x00020000); };
+    for (; left >= kBatch; left -= kBatch, at_vec += kBatch) {
+        // (the scalar offsets stay below the size, which is a constant here.  They are no part of the check against it, or are
+        // subtracted from it: beside a smaller size they would reach past the end)
+        const auto rsrc = descriptor(kBatch);
 #pragma unroll
         for (int u = 0; u < kHistUnroll; ++u) q[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, threadIdx.x * 16, u * kHistThreads * 16, 0);
-    };
-    for (; left >= kBatch; left -= kBatch, at_vec += kBatch) {
-        load_batch(kBatch);
 #pragma unroll
         for (int u = 0; u < kHistUnroll; u += 2) {
             if (hot != kNoHot)
@@ -246,7 +246,11 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
     }
     looked = true;      // (fewer lanes from here on)
     if (left > 0) {
-        load_batch((int)left);
+        // (fewer than a batch; a thread past the end reads the last vector again, and does not count it)
+        const auto rsrc = descriptor((int)left);
+#pragma unroll
+        for (int u = 0; u < kHistUnroll; ++u)
+            q[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, min(u * kHistThreads + (int)threadIdx.x, (int)left - 1) * 16, 0, 0);
 #pragma unroll
         for (int u = 0; u < kHistUnroll; ++u) {
             if (u * kHistThreads + (int)threadIdx.x < left) {

@@ -14,6 +14,10 @@ write of M0 and such a load there must be a wait state (any other instruction). 
 for its own instructions and not inside inline assembly, so `check_m0` reports every hand-written load that
 directly follows a write of M0 on some path.
 
+A buffer load is checked against the size in its descriptor by its vector offset; its scalar offset is left out of that
+check or taken from the size, which wraps around where it is the larger one.  So a scalar offset other than zero belongs to
+a descriptor whose size is known when the code is compiled, and `check_buffer_offsets` reports every other.
+
 Model: loads return in the order they were issued, so after `s_waitcnt vmcnt(N)` a load is complete if at
 least N vector-memory loads were issued after it (stores and atomics are not counted: they may complete
 out of order with loads, which can only make the wait stronger than assumed here).
@@ -155,6 +159,55 @@ def check_m0(asm: str):
     return bad, loads
 
 
+_BUFFER_LOAD = re.compile(r"^buffer_load\w*\s+(?:v\S+, )?(?:v\S+|off), s\[(\d+):\d+\], (\S+)")
+_SCALAR_WRITE = re.compile(r"^(s_\w+)\s+s(?:(\d+)|\[(\d+):(\d+)\])(?:,\s*(\S+))?")
+_NO_WRITE = ("s_cmp", "s_bitcmp", "s_cbranch", "s_setpc", "s_store", "s_waitcnt")
+
+
+def _writes_scalar(x: Ins, reg: int):
+    """None, or whether the instruction's write of s<reg> is that of a constant."""
+    m = _SCALAR_WRITE.match(x.text)
+    if m is not None and not m.group(1).startswith(_NO_WRITE):
+        lo = int(m.group(2) or m.group(3))
+        if lo <= reg <= int(m.group(4) or lo):
+            return m.group(1) in ("s_mov_b32", "s_movk_i32") and re.match(r"^(0x)?[0-9a-f]+$", m.group(5) or "") is not None
+    if x.text.startswith(("v_readfirstlane", "v_readlane")) and re.match(rf"^\S+\s+s{reg}\b", x.text):
+        return False
+    return None
+
+
+def check_buffer_offsets(asm: str):
+    """(violations, buffer loads): a load with a scalar offset whose descriptor's size is not a constant on some path."""
+    bad, loads = [], 0
+    for name, ins, labels in _functions(asm):
+        before = [[] for _ in ins]
+        for i in range(len(ins)):
+            for j in _successors(ins, labels, i):
+                if j < len(ins):
+                    before[j].append(i)
+        for i, x in enumerate(ins):
+            if not x.text.startswith("buffer_load"):
+                continue
+            loads += 1
+            m = _BUFFER_LOAD.match(x.text)
+            if m is not None and m.group(2) == "0":
+                continue
+            seen, todo, constant = set(), [i], m is not None
+            while todo and constant:
+                j = todo.pop()
+                constant = j != 0      # (the function's start: whatever its caller left there)
+                for p in before[j]:
+                    w = _writes_scalar(ins[p], int(m.group(1)) + 2)
+                    if w is False:
+                        constant = False
+                    elif w is None and p not in seen:
+                        seen.add(p)
+                        todo.append(p)
+            if not constant:
+                bad.append((name, x.line, x.text))
+    return bad, loads
+
+
 def check_asm(asm: str, drains=None):
     """All violations in an assembly file, and the number of hand-issued loads that were followed."""
     bad, loads = [], 0
@@ -171,10 +224,12 @@ if __name__ == "__main__":
         text = open(path).read()
         violations, n = check_asm(text, compiler_waits)
         m0, n_lds = check_m0(text)
+        offsets, n_buffer = check_buffer_offsets(text)
         print(f"{path}: {n} hand-issued loads, {len(violations)} violations, "
               f"{len(compiler_waits)} compiler-inserted waits that cover hand-issued loads; "
-              f"{n_lds} hand-written loads into LDS, {len(m0)} directly behind a write of M0")
-        violations += m0
+              f"{n_lds} hand-written loads into LDS, {len(m0)} directly behind a write of M0; "
+              f"{n_buffer} buffer loads, {len(offsets)} with an offset that their size may not cover")
+        violations += m0 + offsets
         for v in violations[:20]:
             print("  ", v)
         for v in sorted(compiler_waits)[:20]:
