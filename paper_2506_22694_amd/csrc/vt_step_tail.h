@@ -51,6 +51,7 @@ __device__ __forceinline__ unsigned long long wave_select_top(unsigned (&ord)[Q]
     return res_ord == 0u ? kNoKey : (((unsigned long long)res_ord << 32) | (unsigned)(~res_id));
 }
 
+template <bool NEIGHBOURS>
 __device__ __forceinline__ unsigned wave_min_of_group_max_u32(unsigned v, int gsteps);
 
 // The largest value P << 16 such that at least `kth` lanes hold v >= P << 16 (0 if fewer than kth lanes hold anything
@@ -88,7 +89,7 @@ __device__ __forceinline__ void wave_publish_top_by_threshold(const unsigned (&o
     if (L <= 8) {
         int gsteps = 6;
         while ((kWave >> gsteps) < L) --gsteps;
-        T = wave_min_of_group_max_u32(top, gsteps);
+        T = wave_min_of_group_max_u32<false>(top, gsteps);
     } else {
         T = wave_kth_largest_prefix16(top, L);      // (16 or more groups would pass several times L candidates)
     }
@@ -141,7 +142,7 @@ __device__ __forceinline__ bool wave_publish_top_by_threshold_q(const unsigned (
     if (L <= 8) {
         int gsteps = 6;
         while ((kWave >> gsteps) < L) --gsteps;
-        T = wave_min_of_group_max_u32(top, gsteps);
+        T = wave_min_of_group_max_u32<false>(top, gsteps);
     } else {
         T = wave_kth_largest_prefix16(top, L);
     }
@@ -465,23 +466,37 @@ __device__ __forceinline__ void store_result(int *__restrict__ ids_row, float *_
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// ------------------------------------------------------------------ direct merge of at most 2048 keys (one wave)
-// Butterfly over the wave whose first `gsteps` steps take the maximum (inside groups of lanes that agree in their lowest bits)
-// and whose remaining steps take the minimum over those groups: the smallest group maximum.  (Groups of neighbouring
-// lanes would be empty where few neighbouring lists hold keys, as for a small head's rows beside a large one.)
+// ------------------------------------------------------------------ direct merge of at most kBlockMergeSpill keys (one wave)
+// Butterfly over the wave whose first `gsteps` steps take the maximum inside groups of 2^gsteps lanes and whose remaining steps
+// take the minimum over those groups: the smallest group maximum.  A group is NEIGHBOURS, or lanes that agree in their lowest bits.
+template <bool NEIGHBOURS>
 __device__ __forceinline__ unsigned wave_min_of_group_max_u32(unsigned v, int gsteps) {
-    auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    v = gsteps > 0 ? (r[0] > r[1] ? r[0] : r[1]) : (r[0] < r[1] ? r[0] : r[1]);
-    r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = gsteps > 1 ? (r[0] > r[1] ? r[0] : r[1]) : (r[0] < r[1] ? r[0] : r[1]);
-    unsigned t = dpp_mov<0x128>(v);     // row_ror:8
-    v = gsteps > 2 ? (v > t ? v : t) : (v < t ? v : t);
-    t = dpp_mov<0x141>(v);              // row_half_mirror
-    v = gsteps > 3 ? (v > t ? v : t) : (v < t ? v : t);
-    t = dpp_mov<0x4E>(v);               // quad_perm [2,3,0,1]
-    v = gsteps > 4 ? (v > t ? v : t) : (v < t ? v : t);
-    t = dpp_mov<0xB1>(v);               // quad_perm [1,0,3,2]
-    return gsteps > 5 ? (v > t ? v : t) : (v < t ? v : t);
+    int step = 0;
+    auto fold = [&](unsigned a, unsigned b) { v = gsteps > step++ ? (a > b ? a : b) : (a < b ? a : b); };
+    auto halves = [&]() {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        fold(r[0], r[1]);
+    };
+    auto rows = [&]() {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        fold(r[0], r[1]);
+    };
+    if constexpr (NEIGHBOURS) {
+        fold(v, dpp_mov<0xB1>(v));      // quad_perm [1,0,3,2]
+        fold(v, dpp_mov<0x4E>(v));      // quad_perm [2,3,0,1]
+        fold(v, dpp_mov<0x141>(v));     // row_half_mirror
+        fold(v, dpp_mov<0x140>(v));     // row_mirror
+        rows();
+        halves();
+    } else {
+        halves();
+        rows();
+        fold(v, dpp_mov<0x128>(v));     // row_ror:8
+        fold(v, dpp_mov<0x141>(v));     // row_half_mirror
+        fold(v, dpp_mov<0x4E>(v));      // quad_perm [2,3,0,1]
+        fold(v, dpp_mov<0xB1>(v));      // quad_perm [1,0,3,2]
+    }
+    return v;
 }
 
 constexpr int kDirectMaxCand = 128;
@@ -496,8 +511,13 @@ __device__ __forceinline__ void acquire_load16(u32x4 &dst, const void *p) {
 }
 template <int N>
 __device__ __forceinline__ void wait_loads16(u32x4 (&r)[N]) {
+    static_assert(N == 4 || N == 8 || N == 16);
     if constexpr (N == 4)
         asm volatile("s_waitcnt vmcnt(0)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+    else if constexpr (N == 16)
+        asm volatile("s_waitcnt vmcnt(0)"
+                     : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]),
+                       "+v"(r[8]), "+v"(r[9]), "+v"(r[10]), "+v"(r[11]), "+v"(r[12]), "+v"(r[13]), "+v"(r[14]), "+v"(r[15]));
     else
         asm volatile("s_waitcnt vmcnt(0)"
                      : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
@@ -530,9 +550,107 @@ __device__ __forceinline__ float lse_of_lists(const unsigned long long *__restri
     return lane_uniform(M + __logf(wave_sum(ls)));
 }
 
-// Up to 256 lists of L keys, each in descending order, four lists per lane.  With G = the power of two >= m the lanes form G
-// groups; every group's best logit is a different key, so at least G >= m keys reach T = the smallest of the group maxima, and
-// the m best keys are among those whose logit does (a dozen or two).  Only the first D keys of every list are read at first: a
+// A value that m keys reach, of the lanes' best logits: with G = the power of two >= m the lanes form G groups; every group's
+// best logit is a different key, so at least G >= m keys reach the smallest of the group maxima.
+template <bool NEIGHBOURS>
+__device__ __forceinline__ unsigned merge_threshold(unsigned top, int m) {
+    unsigned T;
+    if (m <= 8) {
+        int gsteps = 6;                 // G = 64 >> gsteps groups, G >= m
+        while ((kWave >> gsteps) < m) --gsteps;
+        T = wave_min_of_group_max_u32<NEIGHBOURS>(top, gsteps);
+    } else {
+        // 9 or more tokens: the power of two above m would make 16 or more groups and several times m candidates.
+        // Instead T = the upper 16 bits of the m-th largest of the lanes' best logits, found bit by bit with ballots
+        // (at least m lanes, hence m keys, reach it; if fewer than m lanes hold a key at all, T comes out as 0).
+        T = wave_kth_largest_prefix16(top, m);
+    }
+    return T == 0u ? 1u : T;            // an empty group: every real key is a candidate (real keys have a non-zero high word)
+}
+
+// Ranks the `ncand` keys in `stage` by counting and writes the m best.  false, with nothing written: there are more than
+// kDirectMaxCand (massive ties).  lse_fn() is called once, when the results are about to be written.
+template <typename LseFn>
+__device__ __forceinline__ bool rank_candidates(unsigned long long *stage, int ncand, int m, LseFn &&lse_fn,
+                                                int *__restrict__ out_ids_row, float *__restrict__ out_logp_row, int lane) {
+    if (ncand > kDirectMaxCand) return false;
+    if (lane < kDirectPad) stage[ncand + lane] = kNoKey;      // (the ranking reads whole groups of keys)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    unsigned long long mine[kDirectMaxCand / kWave];
+    int above[kDirectMaxCand / kWave];
+#pragma unroll
+    for (int c = 0; c < kDirectMaxCand / kWave; ++c) {
+        mine[c] = kNoKey;
+        above[c] = 0;
+        if (c * kWave >= ncand) break;      // (uniform)
+        mine[c] = c * kWave + lane < ncand ? stage[c * kWave + lane] : kNoKey;
+        for (int x = 0; x < ncand; x += kDirectPad) {
+            unsigned long long t[kDirectPad];
+#pragma unroll
+            for (int q = 0; q < kDirectPad; ++q) t[q] = stage[x + q];      // every lane reads the same key: a broadcast
+#pragma unroll
+            for (int q = 0; q < kDirectPad; ++q) above[c] += t[q] > mine[c] ? 1 : 0;
+        }
+    }
+    const float lse = lse_fn();
+#pragma unroll
+    for (int c = 0; c < kDirectMaxCand / kWave; ++c) {
+        if (mine[c] != kNoKey && above[c] < m)
+            store_result(out_ids_row, out_logp_row, above[c], key_id(mine[c]), key_logit(mine[c]) - lse);
+    }
+    __builtin_amdgcn_wave_barrier();
+    return true;
+}
+
+// Up to 64 U keys in any order, U per lane: few lists, of which some lanes would have none, and groups of lanes no key at all
+// (then every key is a candidate).  All of them are read in one go; U > 4: two to a load, `total` even.
+template <int U, typename LseFn>
+__device__ __forceinline__ bool finalize_row_flat(const unsigned long long *__restrict__ src, int total, int m, LseFn &&lse_fn,
+                                                  unsigned long long *stage, int *__restrict__ out_ids_row,
+                                                  float *__restrict__ out_logp_row, int lane) {
+    unsigned long long key[U];
+    if constexpr (U > 4) {
+        u32x4 r[U / 2];
+        const int npairs = total >> 1;
+        // Straight-line code from the first request to the wait: the compiler does not know that these registers are still in
+        // flight, and a branch in between makes it copy them at the join -- before their values have arrived.
+#pragma unroll
+        for (int u = 0; u < U / 2; ++u) acquire_load16(r[u], src + 2 * min(u * kWave + lane, npairs - 1));
+        wait_loads16(r);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const u32x4 &v = r[u / 2];
+            key[u] = (u / 2) * kWave + lane < npairs ? ((unsigned long long)v[2 * (u & 1) + 1] << 32) | v[2 * (u & 1)] : kNoKey;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = acquire_u64(src + min(u * kWave + lane, total - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = u * kWave + lane < total ? key[u] : kNoKey;
+    }
+    unsigned top = 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) top = (unsigned)(key[u] >> 32) > top ? (unsigned)(key[u] >> 32) : top;
+    const unsigned T = merge_threshold<true>(top, m);
+    int ncand = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool c = (unsigned)(key[u] >> 32) >= T;
+        const unsigned long long mask = __ballot(c);
+        if (mask != 0ull) {
+            const int slot = ncand + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+            if (c && slot < kDirectMaxCand) stage[slot] = key[u];
+            ncand += __popcll(mask);
+        }
+    }
+    return rank_candidates(stage, ncand, m, lse_fn, out_ids_row, out_logp_row, lane);
+}
+
+// Up to 256 lists of L keys, each in descending order, four lists per lane.  The m best keys are among those whose logit reaches
+// the threshold (a dozen or two; the groups are strided, since of neighbouring lanes all lists may be empty, as for a small head's
+// rows beside a large one).  Only the first D keys of every list are read at first: a
 // list's next key matters where the one before it reaches T, so the keys are looked at rank by rank until a rank has none (two
 // or three of them, as a rule; all L keys of all lists, one test each, took 0.5 us longer).  The candidates are compacted into
 // LDS and ranked by counting.  PAIRS: L is even, two keys to a load.
@@ -581,18 +699,7 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
         const unsigned o = (unsigned)(key[0][x] >> 32);
         top = o > top ? o : top;
     }
-    unsigned T;
-    if (m <= 8) {
-        int gsteps = 6;                 // G = 64 >> gsteps groups, G >= m
-        while ((kWave >> gsteps) < m) --gsteps;
-        T = wave_min_of_group_max_u32(top, gsteps);
-    } else {
-        // 9 or more tokens: the power of two above m would make 16 or more groups and several times m candidates.
-        // Instead T = the upper 16 bits of the m-th largest of the lanes' best logits, found bit by bit with ballots
-        // (at least m lanes, hence m keys, reach it; if fewer than m lanes hold a key at all, T comes out as 0).
-        T = wave_kth_largest_prefix16(top, m);
-    }
-    T = T == 0u ? 1u : T;               // an empty group: every real key is a candidate (real keys have a non-zero high word)
+    const unsigned T = merge_threshold<false>(top, m);
     int ncand = 0;
     // the lists' keys of one rank; whether any is a candidate
     auto collect = [&](const unsigned long long (&k)[X]) -> bool {
@@ -622,35 +729,7 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
         }
         more = collect(key[D - 1]);
     }
-    if (ncand > kDirectMaxCand) return false;
-    if (lane < kDirectPad) stage[ncand + lane] = kNoKey;      // (the ranking reads whole groups of keys)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    unsigned long long mine[kDirectMaxCand / kWave];
-    int above[kDirectMaxCand / kWave];
-#pragma unroll
-    for (int c = 0; c < kDirectMaxCand / kWave; ++c) {
-        mine[c] = kNoKey;
-        above[c] = 0;
-        if (c * kWave >= ncand) break;      // (uniform)
-        mine[c] = c * kWave + lane < ncand ? stage[c * kWave + lane] : kNoKey;
-        for (int x = 0; x < ncand; x += kDirectPad) {
-            unsigned long long t[kDirectPad];
-#pragma unroll
-            for (int q = 0; q < kDirectPad; ++q) t[q] = stage[x + q];      // every lane reads the same key: a broadcast
-#pragma unroll
-            for (int q = 0; q < kDirectPad; ++q) above[c] += t[q] > mine[c] ? 1 : 0;
-        }
-    }
-    const float lse = lse_fn();
-#pragma unroll
-    for (int c = 0; c < kDirectMaxCand / kWave; ++c) {
-        if (mine[c] != kNoKey && above[c] < m)
-            store_result(out_ids_row, out_logp_row, above[c], key_id(mine[c]), key_logit(mine[c]) - lse);
-    }
-    __builtin_amdgcn_wave_barrier();
-    return true;
+    return rank_candidates(stage, ncand, m, lse_fn, out_ids_row, out_logp_row, lane);
 }
 
 // ------------------------------------------------------------------ final merge of one hidden row (one wave)
@@ -667,7 +746,13 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
     constexpr int U = 32;                        // 64-lane loads in flight per batch (16 KiB)
     if (B <= GROUP && m <= kWave && B * L <= kBlockMergeSpill) {
         bool done;
-        if (L == 1)
+        // Fewer lists than lanes: the keys are dealt to the lanes one by one (n = 1, 17 lists of 8, m = 24 7.7 us a step; by
+        // lists 19.3, since lanes without one leave no threshold; n = 7, 11 lists of 8, m = 8 8.3 / 10.0)
+        if (B * L <= 4 * kWave)
+            done = finalize_row_flat<4>(pkeys_row, B * L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        else if (B < kWave && B * L <= 32 * kWave && (B * L & 1) == 0)
+            done = finalize_row_flat<32>(pkeys_row, B * L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        else if (L == 1)
             done = finalize_row_direct<1, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (L == 2)
             done = finalize_row_direct<2, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);

@@ -116,3 +116,29 @@ def test_equal_logits_among_stored_ones(n, k, m, run):
     assert torch.equal(ids, map_[order])
     assert (lse.double() - want).abs().max().item() <= 2e-5       # (fp32 sums of up to 40001 exponentials)
     assert (logp.double() - (z.gather(1, order) - want.unsqueeze(1))).abs().max().item() <= 2e-5
+
+
+# Fewer lists than lanes: keys dealt to the lanes up to 256 of them (four loads) and above (pairs), by lists again from 64 lists on and
+# for an odd number of keys above 256; more tokens than lists, and as many as a list holds; every token of the head, and ties of all of them
+@pytest.mark.parametrize("lists", [1, 5, 17, 32, 33, 36, 37, 63, 64, 65])
+@pytest.mark.parametrize("n,m", [(1, 7), (2, 8), (3, 24), (1, 33), (8, 16)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_merge_of_fewer_lists_than_lanes(lists, n, m, ties):
+    k, d = 8 * lists - 3, 128
+    m = min(m, k)
+    g = torch.Generator(device="cuda").manual_seed(lists + m)
+    plan = vt.draft_head_step_plan(n, k, d, m)
+    assert f"workgroups={lists} rows_per_workgroup=8" in plan and "step_finalize" in plan
+    W = torch.zeros(k, d, dtype=torch.bfloat16, device="cuda")
+    W[:, 0] = (torch.randint(0, 3, (k,), generator=g, device="cuda") if ties else torch.randperm(k, generator=g, device="cuda") / 64).bfloat16()
+    h = torch.zeros(n, d, dtype=torch.bfloat16, device="cuda")
+    h[:, 0] = 2.0 ** -(torch.arange(n, device="cuda") % 3).float()
+    map_ = torch.randperm(4 * k, generator=g, device="cuda")[:k].int()
+    ids, logp, lse = vt.draft_head_step(h, W, map_, m, return_lse=True)
+    z = h[:, :1].double() * W[:, 0].double()
+    by_id = torch.argsort(map_.long())
+    order = by_id[torch.sort(z[:, by_id], dim=1, descending=True, stable=True).indices[:, :m]]
+    want = torch.logsumexp(z, 1)
+    assert torch.equal(ids, map_[order])
+    assert (lse.double() - want).abs().max().item() <= 1e-5       # (fp32 sums of up to 517 exponentials, a log-sum-exp below 16)
+    assert (logp.double() - (z.gather(1, order) - want.unsqueeze(1))).abs().max().item() <= 1e-5
