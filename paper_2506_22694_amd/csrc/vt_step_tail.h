@@ -3,6 +3,7 @@
 // election of the last workgroup, and the final cross-workgroup merge
 // (lse, top-m, remap to target ids).
 #pragma once
+#include <type_traits>
 #include "vt_device.h"
 #include "vt_step.h"
 
@@ -650,13 +651,16 @@ __device__ __forceinline__ bool finalize_row_flat(const unsigned long long *__re
 
 // Up to 256 lists of L keys, each in descending order, four lists per lane.  The m best keys are among those whose logit reaches
 // the threshold (a dozen or two; the groups are strided, since of neighbouring lanes all lists may be empty, as for a small head's
-// rows beside a large one).  Only the first D keys of every list are read at first: a
-// list's next key matters where the one before it reaches T, so the keys are looked at rank by rank until a rank has none (two
-// or three of them, as a rule; all L keys of all lists, one test each, took 0.5 us longer).  The candidates are compacted into
-// LDS and ranked by counting.  PAIRS: L is even, two keys to a load.
+// rows beside a large one).  Only the first D keys of every list are read at first: a list's next key matters where the one before
+// it reaches T, so the keys are looked at rank by rank until a rank has none (two or three of them, as a rule; all L keys of all
+// lists, one test each, took 0.5 us longer).  Where the best tokens share a list (a head in order of frequency) what lies behind
+// the first D is asked for in one or two trips; a trip per rank took longer than the short lists save (n = 8, m = 8, k = 5000,
+// d = 3072, all in one list: 14.8 us with all keys read, 15.3, now 14.4; k = 32768 37.1 / 37.8 / 37.1, spread over the lists
+// 36.8 / 35.9 / 35.7; n = 4, m = 11, in one list 37.1 / 38.7 / 37.4; n = 4, m = 10, d = 2048 28.3 / 29.5 / 28.9).
+// The candidates are compacted into LDS and ranked by counting.  PAIRS: L is even, two keys to a load.  MORE: L may exceed D.
 // Returns false, having written nothing, when more than kDirectMaxCand keys reach T (massive ties): the caller then merges the
 // lists round by round.  lse_fn() is called once, when the results are about to be written.
-template <int D, bool PAIRS, typename LseFn>
+template <int D, bool PAIRS, bool MORE, typename LseFn>
 __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__restrict__ src, int B, int L, int m,
                                                     LseFn &&lse_fn, unsigned long long *stage, int *__restrict__ out_ids_row,
                                                     float *__restrict__ out_logp_row, int lane) {
@@ -711,23 +715,47 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
         for (int x = 0; x < X; ++x) {
             const bool c = (unsigned)(k[x] >> 32) >= T;
             const unsigned long long mask = __ballot(c);
-            const int slot = ncand + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
-                                                                    __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-            if (c && slot < kDirectMaxCand) stage[slot] = k[x];
-            ncand += __popcll(mask);
+            if (mask != 0ull) {
+                const int slot = ncand + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+                if (c && slot < kDirectMaxCand) stage[slot] = k[x];
+                ncand += __popcll(mask);
+            }
         }
         return true;
     };
     bool more = true;
 #pragma unroll
     for (int j = 0; j < D; ++j) more = more && collect(key[j]);
-    for (int j = D; more && j < L; ++j) {
+    if constexpr (!MORE) return rank_candidates(stage, ncand, m, lse_fn, out_ids_row, out_logp_row, lane);
+    int j = D;
+    // the next keys of the lists whose last one reaches T, up to eight of each to a trip
+    auto collect_next = [&](auto ranks) {
+        constexpr int R = decltype(ranks)::value;
+        unsigned long long next[R][X];
+        bool open[X];
 #pragma unroll
         for (int x = 0; x < X; ++x) {
-            const unsigned long long k = acquire_u64(src + (size_t)min(lane + kWave * x, B - 1) * L + j);
-            key[D - 1][x] = (unsigned)(key[D - 1][x] >> 32) >= T ? k : kNoKey;
+            open[x] = (unsigned)(key[D - 1][x] >> 32) >= T;
+            // (a list that is through asks for what the others of its kind ask for)
+            const unsigned long long *list = src + (open[x] ? (size_t)(lane + kWave * x) * L : (size_t)0);
+#pragma unroll
+            for (int q = 0; q < R; ++q) next[q][x] = acquire_u64(list + (open[x] ? min(j + q, L - 1) : 0));
         }
-        more = collect(key[D - 1]);
+#pragma unroll
+        for (int x = 0; x < X; ++x) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) next[q][x] = open[x] && j + q < L ? next[q][x] : kNoKey;
+            key[D - 1][x] = next[R - 1][x];
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) more = more && ncand <= kDirectMaxCand && collect(next[q]);
+        j += R;
+    };
+    while (more && j < L) {
+        if (L - j <= 4)
+            collect_next(std::integral_constant<int, 4>{});
+        else
+            collect_next(std::integral_constant<int, 8>{});
     }
     return rank_candidates(stage, ncand, m, lse_fn, out_ids_row, out_logp_row, lane);
 }
@@ -753,13 +781,15 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
         else if (B < kWave && B * L <= 32 * kWave && (B * L & 1) == 0)
             done = finalize_row_flat<32>(pkeys_row, B * L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (L == 1)
-            done = finalize_row_direct<1, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<1, false, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (L == 2)
-            done = finalize_row_direct<2, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<2, true, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        else if (L == 4)
+            done = finalize_row_direct<4, true, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if ((L & 1) == 0)
-            done = finalize_row_direct<4, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<4, true, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else
-            done = finalize_row_direct<3, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<3, false, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         if (done) return;
     }
 

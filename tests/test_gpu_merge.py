@@ -142,3 +142,30 @@ def test_merge_of_fewer_lists_than_lanes(lists, n, m, ties):
     assert torch.equal(ids, map_[order])
     assert (lse.double() - want).abs().max().item() <= 1e-5       # (fp32 sums of up to 517 exponentials, a log-sum-exp below 16)
     assert (logp.double() - (z.gather(1, order) - want.unsqueeze(1))).abs().max().item() <= 1e-5
+
+
+# The best tokens in one list, in two and in as many as there are, of the longest lists and of lists shorter than the tokens asked for
+# (eight keys of a list at a time behind its first three or four)
+@pytest.mark.parametrize("dtype,n,k,m", [("f32", 2, 2000, 12), ("f32", 3, 2040, 9), ("bf16", 2, 2000, 24), ("bf16", 4, 1999, 11), ("f32", 8, 2000, 64)])
+@pytest.mark.parametrize("spread", [1, 2, 5, 8, 250])
+def test_best_tokens_of_tiles_of_eight(dtype, n, k, m, spread):
+    d, t = 128, torch.bfloat16 if dtype == "bf16" else torch.float32
+    plan = vt.draft_head_step_plan(n, k, d, m, dtype=t)
+    assert "workgroups=25" in plan and "step_finalize" in plan
+    g = torch.Generator(device="cuda").manual_seed(m + spread)
+    value = torch.rand(k, generator=g, device="cuda") - 4
+    best = torch.randperm(k // 8, generator=g, device="cuda")[:spread]      # tiles
+    at = (best.unsqueeze(1) * 8 + torch.arange(8, device="cuda")).flatten()[:max(m, 8)]
+    value[at] = torch.randperm(at.numel(), generator=g, device="cuda") / 8.0
+    W = torch.zeros(k, d, dtype=t, device="cuda")
+    W[:, 0] = value.to(t)
+    h = torch.zeros(n, d, dtype=t, device="cuda")
+    h[:, 0] = 2.0 ** -(torch.arange(n, device="cuda") % 3).float()
+    map_ = torch.arange(k, dtype=torch.int32, device="cuda") * 2 + 1
+    ids, logp, lse = vt.draft_head_step(h, W, map_, m, return_lse=True)
+    z = h[:, :1].double() * W[:, 0].double()
+    order = torch.sort(z, dim=1, descending=True, stable=True).indices[:, :m]
+    want = torch.logsumexp(z, 1)
+    assert torch.equal(ids, map_[order])
+    assert (lse.double() - want).abs().max().item() <= 1e-5       # (fp32 sums of 2000 exponentials, a log-sum-exp below 16)
+    assert (logp.double() - (z.gather(1, order) - want.unsqueeze(1))).abs().max().item() <= 1e-5
