@@ -25,6 +25,7 @@ namespace {
 constexpr int kRowThreads = 1024;
 constexpr int kRowWaves = kRowThreads / kWave;
 constexpr int kRowMaxCand = 1024;
+constexpr int kRowMaxTokens = 64;     // tokens per row (m)
 constexpr int kRowMaxRaw = 4096;      // rows of several stretches: logits above the first stretch's threshold
 
 __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v, unsigned long long *red, int lane,
@@ -182,6 +183,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     __shared__ float rawv[kRaw];
     __shared__ int rawj[kRaw];
     __shared__ unsigned s_nraw, s_ncand;
+    __shared__ unsigned s_at[kRowMaxTokens];      // candidates with that many larger logits
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int i = blockIdx.x;
     const float *zr = z + (size_t)i * k;
@@ -193,7 +195,10 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         s_ncand = 0u;
     }
     cand[tid] = kNoKey;
-    if constexpr (!SIFT) rawv[tid] = -INFINITY;
+    if constexpr (!SIFT) {
+        rawv[tid] = -INFINITY;
+        if (tid < kRowMaxTokens) s_at[tid] = 0u;
+    }
 
     // ---- pass 1: (max, sum-exp) and the thread's largest logit
     float lm = -INFINITY, ls = 0.f;
@@ -272,7 +277,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     const float lse = M + __logf(S);
     if (ncand <= kRowMaxCand) {
         // rank by counting: keys are distinct (distinct target ids).  Without a thinning in between the logits alone are ranked
-        // while the trip to the map for the target id is under way; a logit that is there twice waits for the keys.
+        // while the trip to the map for the target id is under way; one that is there twice is ranked by its keys.
         auto by_keys = [&](unsigned long long key) {
             unsigned above = 0;
             for (int x = 0; x < ncand; x += 8) {
@@ -294,29 +299,27 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         if constexpr (SIFT) {
             if (tid < ncand) store(by_keys(cand[tid]), cand[tid]);
         } else {
+            // (equal logits meet at the place of the first of them: a second comparison per logit, for equality, took 5 us where a
+            // short row has no threshold and all of its 651 logits are candidates)
             unsigned long long key = 0ull;
-            bool twice = false;
+            int above = m;
             if (tid < ncand) {
                 const float mine = rawv[tid];
                 const int id = map[rawj[tid]];
-                int above = 0, equal = 0;
+                above = 0;
                 for (int x = 0; x < ncand; x += 8) {
                     float t[8];
 #pragma unroll
                     for (int u = 0; u < 8; ++u) t[u] = rawv[x + u];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        above += t[u] > mine ? 1 : 0;
-                        equal += t[u] == mine ? 1 : 0;
-                    }
+                    for (int u = 0; u < 8; ++u) above += t[u] > mine ? 1 : 0;
                 }
+                if (above < m) atomicAdd(&s_at[above], 1u);
                 key = make_key(mine, id);
                 cand[tid] = key;
-                twice = equal > 1;
-                if (!twice) store(above, key);
             }
             __syncthreads();
-            if (twice) store(by_keys(key), key);
+            if (above < m) store(s_at[above] > 1u ? by_keys(key) : above, key);
         }
     } else {
         // massive ties: take the best remaining key, m times (each round re-reads the row from the L2)
