@@ -288,10 +288,12 @@ head_mfma_kernel(const MfmaArgs a) {
 // k-steps of MT * NTT products; the operands of one are read while the other is multiplied, the barrier that hands the
 // slot on sits between them, and the loads of the freed slot are spread over the products that follow it -- issued
 // in one go they kept the wave from its products (n = 256, k = 32768, d = 8192: 149 against 140 us).
-// From 129 hidden rows on a stage's pieces of h are asked for before W's: h comes from the L2 soon and keeps the queue
-// short for W behind it (with W first: n = 192, k = 32768, d = 3072 62.0 against 60.6 us, n = 160, d = 8192 131.8 / 128.1,
-// n = 256, d = 8192 167.6 / 165.9, n = 256, k = 5000, d = 4096 53.0 / 51.2; n = 200, d = 8192 a tie); with up to 128, where W's pieces
-// are the larger part, W comes first (n = 128, k = 5000, d = 3072: 29.4 us against 30.2 with h first).
+// From 129 hidden rows on, and with 129 to 192 of them on tiles of 64 and more head rows, a stage's pieces of h are asked for
+// before W's: h comes from the L2 soon and keeps the queue short for W behind it (W first / h first, us: n = 256, k = 32768,
+// d = 5120 111.1 / 100.0, d = 3072 71.1 / 66.0, d = 8192 158.0 / 155.9; n = 181, k = 32768, d = 5120 90.5 / 85.9).
+// 129 to 192 rows on tiles of 32 tie on average, but h first is up to 5 % slower where d is a multiple of 1024 and not of 2048
+// (n = 181, d = 5120, k = 2950 48.0 / 50.3, k = 1500 46.6 / 49.0; d = 8192, k = 1500, n = 129 63.5 / 62.0); with up to 128 rows
+// W's pieces are the larger part (n = 128, k = 8192, d = 5120 39.8 / 42.3; n = 100, k = 24000 59.1 / 61.5).
 // The march of n = 256, d = 8192 is bound by power: the clock falls from 2.4 to 1.6 .. 1.9 GHz while loads and products run
 // together, and stays at 2.4 with either alone.
 // PACKED: h was re-laid by pack_h_kernel, a stage's pieces one after the other as they lie in LDS.
@@ -302,7 +304,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
     constexpr int kPieces = (TM + TN) / 8, LPW = (kPieces + kStepWaves - 1) / kStepWaves;
     constexpr unsigned kStage = (TM + TN) * 128u;
     constexpr int NP = MT * NTT;               // products per k-step
-    constexpr bool kHiddenFirst = NTT >= 3;
+    constexpr bool kHiddenFirst = NTT == 4 || (NTT == 3 && MT >= 2);
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wn = w & 3, wm = w >> 2;
