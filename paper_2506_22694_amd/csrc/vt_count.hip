@@ -305,6 +305,10 @@ __global__ void __launch_bounds__(kHistThreads) hist_partial_kernel(const void *
                     if (total != keep) atomicAdd(&counts[lo + (int)bin], (unsigned long long)(total - keep));
                 }
                 left &= ~__ballot(same);
+                // (the next leader's bin may share the word)
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             }
         }
         __syncthreads();

@@ -213,3 +213,14 @@ def test_count_few_chunks(V, n_ids, dtype):
             inv = torch.zeros(1, dtype=torch.int64, device="cuda")
             c = vt.count_tokens(d, V, n_invalid=inv, ws=torch.full((size,), 255, dtype=torch.uint8, device="cuda"))
             assert np.array_equal(c.cpu().numpy(), want) and inv.item() == n_ids - want.sum()
+
+
+# Waves of one workgroup whose hottest bins are neighbours, two to a word of LDS: every block of 256 ids belongs to one wave
+@pytest.mark.parametrize("dtype", [torch.int32, torch.int64])
+def test_count_hottest_bins_that_share_a_word(dtype):
+    V, n_ids = 3000, 4_000_000
+    rng = np.random.default_rng(5)
+    wave = np.arange(n_ids) // (256 if dtype == torch.int32 else 128)
+    ids = np.where(rng.random(n_ids) < 0.9, 1234 + wave % 2 + 2 * (wave % 6 == 5), rng.integers(0, V, size=n_ids))
+    c = vt.count_tokens(torch.from_numpy(ids).to(dtype).cuda(), V)
+    assert np.array_equal(c.cpu().numpy(), np.bincount(ids, minlength=V))
