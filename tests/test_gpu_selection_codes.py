@@ -224,3 +224,15 @@ def test_count_hottest_bins_that_share_a_word(dtype):
     ids = np.where(rng.random(n_ids) < 0.9, 1234 + wave % 2 + 2 * (wave % 6 == 5), rng.integers(0, V, size=n_ids))
     c = vt.count_tokens(torch.from_numpy(ids).to(dtype).cuda(), V)
     assert np.array_equal(c.cpu().numpy(), np.bincount(ids, minlength=V))
+
+
+# One chunk (a vocabulary of more ranges than there are workgroups): a thread's own word of its wave's hottest bin and the words
+# where ids of other ranges go reach 32768, with 80 million ids twice
+@pytest.mark.parametrize("dtype,n_ids", [(torch.int32, 80_000_000), (torch.int64, 40_000_000)])
+def test_count_one_id_in_one_chunk(dtype, n_ids):
+    V = 129 * 65536 + 77
+    for at in (V - 1, 65536 * 3 + 1):
+        ids = torch.full((n_ids,), at, dtype=dtype, device="cuda")
+        ids[::1001] = torch.arange(ids[::1001].numel(), device="cuda").to(dtype) % V
+        c = vt.count_tokens(ids, V)
+        assert torch.equal(c, torch.bincount(ids, minlength=V))
