@@ -236,3 +236,19 @@ def test_count_one_id_in_one_chunk(dtype, n_ids):
         ids[::1001] = torch.arange(ids[::1001].numel(), device="cuda").to(dtype) % V
         c = vt.count_tokens(ids, V)
         assert torch.equal(c, torch.bincount(ids, minlength=V))
+
+
+# Streams whose chunks hold no whole batch of vectors (4096 of 16 bytes), just one, and one vector more; from an aligned id and not
+@pytest.mark.parametrize("dtype", [torch.int32, torch.int64])
+@pytest.mark.parametrize("off", [0, 1])
+def test_count_around_one_batch(dtype, off):
+    V = 128256
+    rng = np.random.default_rng(off)
+    per = 4 if dtype == torch.int32 else 2
+    for n_ids in (1, per - 1, per, 4096 * per - 1, 4096 * per, 4096 * per + 1, 4097 * per, 2 * 4096 * per, 2 * 4096 * per + per, 40000, 3 * 4096 * per + 5):
+        for ids in (rng.integers(0, V, size=n_ids), np.full(n_ids, 70000), rng.integers(-3, 40, size=n_ids)):
+            d = torch.from_numpy(np.concatenate([np.full(off, 9), ids])).to(dtype).cuda()[off:]
+            inv = torch.zeros(1, dtype=torch.int64, device="cuda")
+            c = vt.count_tokens(d, V, n_invalid=inv)
+            assert np.array_equal(c.cpu().numpy(), np.bincount(ids[ids >= 0], minlength=V)), n_ids
+            assert inv.item() == (ids < 0).sum()
