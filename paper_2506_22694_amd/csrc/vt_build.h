@@ -10,8 +10,9 @@ namespace vt {
 constexpr int kHistBinsPerBlock = 65536;   // 16-bit bins privatised in LDS per workgroup (128 KiB, two per word)
 constexpr int kHistBlocks = 256;           // workgroups per launch: id-stream chunks x bin ranges
 constexpr int kHistThreads = 1024;
-constexpr int kHistChunkIds = 16384;      // ids of a chunk at least (4096 / 8192 / 16384 / 65536: 10^6 ids 17.0 / 17.0 / 14.6 / 16.1 us, 200 000
-                                          // 11.5 / 10.8 / 11.3 / 13.2, 64-bit 11.8 / 11.3 / 11.7 / 15.2)
+constexpr int kHistChunkIds = 16384;      // ids of a chunk at least, with up to seven ranges (this kernel at V = 128256 with chunks of
+                                          // 4096 / 8192 / 16384 / 32768 / 65536: 10^6 ids 16.8 / 16.6 / 14.5 / 14.0 / 16.0 us, 64-bit
+                                          // 17.2 / 16.6 / 15.0 / 15.2 / 18.3, 200 000 11.4 / 10.6 / 11.1 / 12.5 / 13.6)
 constexpr int kHistUnroll = 4;            // 16-byte id vectors in flight per thread (2 / 4 / 6: 24.9 / 22.1 / 22.8 us at
                                           // 10^7 ids, 130 / 99 / 101 at 10^8, 64-bit 202 / 165 / 175)
 
