@@ -61,7 +61,7 @@ struct RankBufs {
     unsigned *totals;              // [kRankBins]
     unsigned *start;               // [kWideBins] place of the first id of each bin of large counts
     unsigned long long *splitters; // [kSplitters] descending, zeros behind
-    unsigned long long *pairs[2];  // ids of the bins of several values, by place; what the radix passes move them to (where `rows` are)
+    unsigned *ids[2];              // of the bins of several values, by place; what the radix passes move them to (where `rows` are)
 };
 
 __device__ __forceinline__ int lanes_below(unsigned long long m) {
@@ -189,7 +189,7 @@ __device__ __forceinline__ int rank_bin(unsigned long long c, const unsigned lon
 __device__ __forceinline__ bool one_value(int bin) { return bin >= kWideBins || (bin & 1) != 0; }
 
 __global__ void __launch_bounds__(kRankSortThreads) rank_hist_kernel(const long long *__restrict__ counts, int n, RankBufs b) {
-    __shared__ unsigned h[kRankBins];
+    __shared__ __align__(16) unsigned h[kRankBins];      // (read by fours)
     __shared__ unsigned long long sp[kRankSortThreads];
     __shared__ int s_n;
     const int tid = threadIdx.x;
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_scatter_kernel(const lo
     place = __builtin_amdgcn_sad_u8(bytes_before(x.w, 12), 0u, place);
     if (in) {
         if (!one_value(bin))
-            b.pairs[0][place] = (unsigned)j;
+            b.ids[0][place] = (unsigned)j;
         else if (place < (unsigned)n_ids)
             out_ids[place] = j;
     }
@@ -331,7 +331,7 @@ struct RadixLds {
     unsigned short before[kRunGroups * kDigits];     // elements of a digit in the step's groups of 64 before
 };
 
-// Places [lo, lo + length) of pairs[0] by their counts: LSD passes of this workgroup over the digits in which the
+// Places [lo, lo + length) of ids[0] by their counts: LSD passes of this workgroup over the digits in which the
 // counts differ, between the two buffers.  Nobody else touches those places.
 __device__ __forceinline__ void sort_by_radix(const long long *__restrict__ counts, const RankBufs &b, unsigned lo,
                                               unsigned length, int n_ids, int *__restrict__ out_ids, RadixLds &s) {
@@ -341,7 +341,7 @@ __device__ __forceinline__ void sort_by_radix(const long long *__restrict__ coun
     __syncthreads();
     unsigned long long ones = 0, zeros = 0;
     for (unsigned x = tid; x < length; x += kRankSortThreads) {
-        const unsigned long long c = (unsigned long long)counts[(unsigned)b.pairs[src][lo + x]];
+        const unsigned long long c = (unsigned long long)counts[b.ids[src][lo + x]];
         ones |= c;
         zeros |= ~c;
     }
@@ -355,21 +355,21 @@ __device__ __forceinline__ void sort_by_radix(const long long *__restrict__ coun
     const unsigned long long differ = s.ones & s.zeros;
     for (int shift = 0; shift < 64; shift += 8) {
         if (((differ >> shift) & 255ull) == 0ull) continue;      // (uniform)
-        const unsigned long long *from = b.pairs[src] + lo;
-        unsigned long long *to = b.pairs[src ^ 1] + lo;
+        const unsigned *from = b.ids[src] + lo;
+        unsigned *to = b.ids[src ^ 1] + lo;
         // element x0 + (u 16 + w) 64 + lane of the run, and 255 - its digit (256: past the end)
-        unsigned long long pair[kRunPer];
+        unsigned id[kRunPer];
         int dgt[kRunPer];
         auto load_step = [&](unsigned x0) {
 #pragma unroll
             for (int u = 0; u < kRunPer; ++u) {
                 const unsigned x = x0 + u * kRankSortThreads + tid;
-                pair[u] = x < length ? from[x] : 0ull;
+                id[u] = x < length ? from[x] : 0u;
             }
 #pragma unroll
             for (int u = 0; u < kRunPer; ++u) {
                 const unsigned x = x0 + u * kRankSortThreads + tid;
-                dgt[u] = x < length ? 255 - (int)(((unsigned long long)counts[(unsigned)pair[u]] >> shift) & 255ull) : 256;
+                dgt[u] = x < length ? 255 - (int)(((unsigned long long)counts[id[u]] >> shift) & 255ull) : 256;
             }
         };
         if (tid < kDigits) s.base[tid] = 0u;
@@ -430,7 +430,7 @@ __device__ __forceinline__ void sort_by_radix(const long long *__restrict__ coun
                     unsigned pos = s.base[dgt[u]] + s.before[(u * kSortWaves + w) * kDigits + dgt[u]] + (unsigned)lanes_below(same[u]);
 #pragma unroll
                     for (int q = 0; q < u; ++q) pos += s.part[q * kDigits + dgt[u]];
-                    to[pos] = pair[u];
+                    to[pos] = id[u];
                 }
             }
             __syncthreads();
@@ -444,7 +444,7 @@ __device__ __forceinline__ void sort_by_radix(const long long *__restrict__ coun
     }
     static_assert(kRunPer * kDigits == kRankSortThreads, "a thread per digit and quarter");
     for (unsigned x = tid; x < length && lo + x < (unsigned)n_ids; x += kRankSortThreads)
-        out_ids[lo + x] = (int)(unsigned)b.pairs[src][lo + x];
+        out_ids[lo + x] = (int)b.ids[src][lo + x];
     __syncthreads();
 }
 
@@ -466,7 +466,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long 
         if (blockIdx.x < kSplitters) lower = b.splitters[blockIdx.x];
         if (length == 0u || lo >= (unsigned)n_ids) return;      // (uniform) nothing there, or nobody asks for it
     }
-    auto id_at = [&](unsigned x) { return WHOLE ? x : (unsigned)b.pairs[0][lo + x]; };
+    auto id_at = [&](unsigned x) { return WHOLE ? x : b.ids[0][lo + x]; };
     const int N = sort_size((int)min(length, (unsigned)kRunMax));
     if (tid == 0) s_far = length > (unsigned)kRunMax ? 1 : 0;
     __syncthreads();
@@ -487,7 +487,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long 
     if (s_far != 0) {                     // (uniform)
         __syncthreads();
         if constexpr (WHOLE) {
-            for (int x = tid; x < n; x += kRankSortThreads) b.pairs[0][x] = (unsigned)x;
+            for (int x = tid; x < n; x += kRankSortThreads) b.ids[0][x] = (unsigned)x;
             __syncthreads();
         }
         sort_by_radix(counts, b, lo, length, n_ids, out_ids, s.radix);
@@ -841,14 +841,14 @@ void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_id
     char *p = static_cast<char *>(scratch);
     const int nblk = (n + kRankSortThreads - 1) / kRankSortThreads;
     RankBufs b{};
-    b.pairs[0] = reinterpret_cast<unsigned long long *>(p);
-    p += round256((size_t)n * 8);
-    b.pairs[1] = reinterpret_cast<unsigned long long *>(p);
+    b.ids[0] = reinterpret_cast<unsigned *>(p);
+    p += round256((size_t)n * 4);
+    b.ids[1] = reinterpret_cast<unsigned *>(p);
     if (n <= kRunMax) {
         hipLaunchKernelGGL(rank_runs_kernel<true>, dim3(1), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
         return;
     }
-    // (12 KiB per 1024 ids, more than the 8 KiB that the radix passes write there)
+    // (12 KiB per 1024 ids, more than the 4 KiB that the radix passes write there)
     b.rows = reinterpret_cast<unsigned *>(p);
     p += round256((size_t)nblk * kRankBins * 4);
     b.totals = reinterpret_cast<unsigned *>(p);
@@ -862,7 +862,7 @@ void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_id
     hipLaunchKernelGGL(rank_scatter_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
     hipLaunchKernelGGL(rank_runs_kernel<false>, dim3(kSplitters + 1), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
 }
-static_assert(kRankBins * 4 >= 8 * kRankSortThreads, "the radix passes' second buffer lies where the rows are");
+static_assert(kRankBins * 4 >= 4 * kRankSortThreads, "the radix passes' second buffer lies where the rows are");
 
 // (likewise: ids and counts in order, sums per workgroup, and the sort's buffers)
 size_t choose_k_ws_bytes(int V) {
