@@ -108,23 +108,17 @@ __device__ __forceinline__ void wave_sort_steps(unsigned long long &v, int lane)
     }
 }
 
-// Merges R <= 8 neighbouring runs of len = 2^lg values each, all over v[0 .. N): every value looks up how many go ahead of it in
-// the other runs, searches that do not wait for each other.  Up to PER values per thread.
-template <int PER>
+// Merges R <= 8 neighbouring runs of len = 2^lg values each, all over v[0 .. N), N <= 1024: every value looks up how many go
+// ahead of it in the other runs, searches that do not wait for each other.
 __device__ __forceinline__ void merge_runs(unsigned long long *v, int N, int lg, int R) {
-    const int tid = threadIdx.x, len = 1 << lg;
-    unsigned long long x[PER];
-    int place[PER];
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int i = r * kRankSortThreads + tid;
-        x[r] = 0ull;
-        place[r] = 0;
-        if (i >= N) continue;
-        x[r] = v[i];
+    const int i = threadIdx.x, len = 1 << lg;
+    unsigned long long x = 0ull;
+    int place = 0;
+    if (i < N) {
+        x = v[i];
         const int run = (i >> lg) & (R - 1);
         const unsigned long long *first = v + (i & ~(R * len - 1));
-        place[r] = (i & ~(R * len - 1)) + (i & (len - 1));
+        place = (i & ~(R * len - 1)) + (i & (len - 1));
         int ahead[8] = {};
         // (steps len / 2, .., 2, 1 and 1 once more: as many as len values go ahead)
         for (int l = lg - 1; l >= -1; --l) {
@@ -133,43 +127,99 @@ __device__ __forceinline__ void merge_runs(unsigned long long *v, int N, int lg,
             for (int q = 0; q < 8; ++q) {
                 if (q < R) {      // (uniform)
                     const unsigned long long t = first[(q << lg) + ahead[q] + step - 1];
-                    ahead[q] += t > x[r] || (t == x[r] && q < run) ? step : 0;      // of equal values the earlier run's go ahead
+                    ahead[q] += t > x || (t == x && q < run) ? step : 0;      // of equal values the earlier run's go ahead
                 }
             }
         }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) place[r] += q < R && q != run ? ahead[q] : 0;
+        for (int q = 0; q < 8; ++q) place += q < R && q != run ? ahead[q] : 0;
     }
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        if (r * kRankSortThreads + tid < N) v[place[r]] = x[r];
-    }
+    if (i < N) v[place] = x;
     __syncthreads();
 }
 
-// Sorts v[0 .. N) in LDS, largest first; N a power of two, 64 .. kRunMax.  All threads of the workgroup call it behind a
+// Sorts v[0 .. N) in LDS, largest first; N a power of two, 64 .. 1024.  All threads of the workgroup call it behind a
 // barrier and find the result behind another.  64 values at a time are sorted in a wave's registers, then runs are merged,
-// eight at a time, longer ones four (fewer searches per value, where there are several values per thread).
-// 512 values by bitonic steps in LDS took 10 us, this way 1.5.
+// eight at a time.  512 values by bitonic steps in LDS took 10 us, this way 1.5.
 __device__ __forceinline__ void sort_descending(unsigned long long *v, int N) {
-    const int lane = lane_id();
-    for (int i = threadIdx.x; i < N; i += kRankSortThreads) {
-        unsigned long long x = v[i];
-        wave_sort_steps<2, 1>(x, lane);
-        v[i] = x;
+    // (so that the second merge is known to be of two runs: 0.8 us of 5)
+    __builtin_assume(N >= kWave && N <= kRankSortThreads);
+    if ((int)threadIdx.x < N) {
+        unsigned long long x = v[threadIdx.x];
+        wave_sort_steps<2, 1>(x, lane_id());
+        v[threadIdx.x] = x;
     }
     __syncthreads();
-    if (N <= kRankSortThreads) {
-        if (N > kWave) merge_runs<1>(v, N, 6, min(N >> 6, 8));
-        if (N > 8 * kWave) merge_runs<1>(v, N, 9, N >> 9);
-    } else {
-        constexpr int kPer = kRunMax / kRankSortThreads;
-        merge_runs<kPer>(v, N, 6, 8);
-        merge_runs<kPer>(v, N, 9, min(N >> 9, 4));
-        if (N > 32 * kWave) merge_runs<kPer>(v, N, 11, N >> 11);
+    if (N > kWave) merge_runs(v, N, 6, min(N >> 6, 8));
+    if (N > 8 * kWave) merge_runs(v, N, 9, N >> 9);
+}
+
+// Sorts v[0 .. N) in LDS, N a multiple of 1024 up to kRunMax, by the `bits` bits from kPlaceBits on, largest first; equal ones keep their
+// order.  All threads call it behind a barrier and find the result behind another.  LSD passes of eight bits with the values in
+// registers: a wave has N / 16 neighbours, and its lanes of one digit find each other with ballots.  A pass takes 1 to 2 us; merging
+// the runs of 8192 values took searches of 70.
+struct DigitLds {
+    unsigned short at[kSortWaves * kDigits];      // [wave][digit]
+    unsigned part[kSortWaves];
+};
+__device__ __forceinline__ void sort_by_digits(unsigned long long *v, int N, int bits, DigitLds &s) {
+    constexpr int kPer = kRunMax / kRankSortThreads;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, R = N / kRankSortThreads;
+    for (int shift = kPlaceBits; shift < kPlaceBits + bits; shift += 8) {
+        unsigned long long x[kPer];
+        int d[kPer];
+        unsigned local[kPer];
+        reinterpret_cast<unsigned *>(s.at)[tid] = 0u;
+        reinterpret_cast<unsigned *>(s.at)[tid + kRankSortThreads] = 0u;
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) x[r] = r < R ? v[(w * R + r) * kWave + lane] : 0ull;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            if (r < R) {      // (uniform)
+                d[r] = 255 - (int)((x[r] >> shift) & 255ull);
+                const unsigned long long same = match_lanes<8>(d[r]);
+                const unsigned short before = s.at[w * kDigits + d[r]];
+                local[r] = before + (unsigned)lanes_below(same);
+                if (lanes_below(same) == 0) s.at[w * kDigits + d[r]] = (unsigned short)(before + __popcll(same));
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+        }
+        __syncthreads();
+        // sums of a digit per wave -> places: thread (digit, four of the waves)
+        unsigned short *const own = s.at + (tid & 3) * 4 * kDigits + (tid >> 2);
+        unsigned n[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n[q] = own[q * kDigits];
+        const unsigned sum = n[0] + n[1] + n[2] + n[3];
+        unsigned upto = sum;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const unsigned t = __shfl_up(upto, o);
+            if (lane >= o) upto += t;
+        }
+        if (lane == kWave - 1) s.part[w] = upto;
+        __syncthreads();
+        unsigned run = upto - sum;
+#pragma unroll
+        for (int q = 0; q < kSortWaves; ++q) run += q < w ? s.part[q] : 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            own[q * kDigits] = (unsigned short)run;
+            run += n[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            if (r < R) v[s.at[w * kDigits + d[r]] + local[r]] = x[r];
+        }
+        __syncthreads();
     }
 }
+static_assert(kSortWaves * kDigits == 4 * kRankSortThreads && kRunMax <= 65535, "four sums to a thread, places of 16 bits");
 __device__ __forceinline__ int sort_size(int n) { return n <= kWave ? kWave : 1 << (32 - __clz(n - 1)); }
 
 // The id whose count is sample i of 1024: one of every n / 1024 neighbours, not the same of all.
@@ -453,10 +503,14 @@ template <bool WHOLE>
 __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long long *__restrict__ counts, int n, int n_ids, RankBufs b,
                                                                      int *__restrict__ out_ids) {
     __shared__ union {
-        unsigned long long key[kRunMax];
+        struct {
+            unsigned long long key[kRunMax];
+            DigitLds digits;
+        };
         RadixLds radix;
     } s;
     __shared__ int s_far;
+    __shared__ unsigned s_top;
     const int tid = threadIdx.x;
     unsigned lo = 0, length = (unsigned)n;
     unsigned long long lower = 0;         // below all counts of the bin
@@ -467,21 +521,31 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long 
         if (length == 0u || lo >= (unsigned)n_ids) return;      // (uniform) nothing there, or nobody asks for it
     }
     auto id_at = [&](unsigned x) { return WHOLE ? x : b.ids[0][lo + x]; };
-    const int N = sort_size((int)min(length, (unsigned)kRunMax));
-    if (tid == 0) s_far = length > (unsigned)kRunMax ? 1 : 0;
+    const bool few = length <= kRankSortThreads;
+    const int N = few ? sort_size((int)length) : (int)((length + kRankSortThreads - 1) / kRankSortThreads * kRankSortThreads);
+    if (tid == 0) {
+        s_far = length > (unsigned)kRunMax ? 1 : 0;
+        s_top = 0u;
+    }
     __syncthreads();
     if (length <= (unsigned)kRunMax) {
         bool far = false;
+        unsigned long long ones = 0ull;
         for (int x = tid; x < N; x += kRankSortThreads) {
             unsigned long long key = 0ull;
             if (x < (int)length) {
                 const unsigned long long above = (unsigned long long)counts[id_at((unsigned)x)] - lower;
                 far |= (above >> (64 - kPlaceBits)) != 0ull;
+                ones |= above;
                 key = (above << kPlaceBits) | (unsigned)(kRunMax - 1 - x);
             }
             s.key[x] = key;
         }
         if (__ballot(far) != 0ull && (tid & 63) == 0) s_far = 1;
+        if (!few) {      // how many bits there are to sort by
+            const unsigned top = wave_max_u32(ones == 0ull ? 0u : 64u - (unsigned)__clzll((long long)ones));
+            if ((tid & 63) == 0) atomicMax(&s_top, top);
+        }
         __syncthreads();
     }
     if (s_far != 0) {                     // (uniform)
@@ -493,7 +557,10 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long 
         sort_by_radix(counts, b, lo, length, n_ids, out_ids, s.radix);
         return;
     }
-    if (length > 1u) sort_descending(s.key, N);
+    if (!few)
+        sort_by_digits(s.key, N, (int)s_top, s.digits);
+    else if (length > 1u)
+        sort_descending(s.key, N);
     for (unsigned x = tid; x < length; x += kRankSortThreads) {
         if (lo + x < (unsigned)n_ids) out_ids[lo + x] = (int)id_at(kRunMax - 1 - ((unsigned)s.key[x] & (kRunMax - 1)));
     }

@@ -252,3 +252,34 @@ def test_count_around_one_batch(dtype, off):
             c = vt.count_tokens(d, V, n_invalid=inv)
             assert np.array_equal(c.cpu().numpy(), np.bincount(ids[ids >= 0], minlength=V)), n_ids
             assert inv.item() == (ids < 0).sum()
+
+
+# A bin's ids are sorted by comparisons up to 1024 of them and by digits of eight bits above: at the edges of both, by no digit, by one
+# and a bit, by all that the keys hold (51 bits), with few values and many
+@pytest.mark.parametrize("V", [1023, 1024, 1025, 2048, 2049, 5000, 8192])
+@pytest.mark.parametrize("bits", [0, 1, 8, 9, 16, 38, 51])
+def test_rank_order_of_one_bin(V, bits):
+    rng = np.random.default_rng(V + bits)
+    few = rng.integers(0, 1 << bits, size=5)
+    for c in (rng.integers(0, 1 << bits, size=V), rng.choice(few, size=V), np.sort(rng.integers(0, 1 << bits, size=V))):
+        order = np.lexsort((np.arange(V), -c))
+        for k in (1, V // 2, V):
+            a, _ = vt.build_trimmed_head(torch.from_numpy(c).cuda(), None, k, order="rank")
+            assert np.array_equal(a.cpu().numpy(), order[:k]), k
+
+
+# More than 512 workgroups (their tallies are summed up in two rounds), bins between splitters of a thousand ids and more: a few values
+# to a bin and many, values below 2048, large ones alone
+@pytest.mark.parametrize("V", [524288, 524289, 1_000_003])
+@pytest.mark.parametrize("kind", ["below 4000", "2048 to 4096", "below 2^24", "heavy tail", "equal"])
+def test_rank_order_of_large_vocabularies(V, kind):
+    g = torch.Generator(device="cuda").manual_seed(V)
+    if kind == "heavy tail":
+        c = (1e9 / (1 + torch.randperm(V, generator=g, device="cuda").double()) ** 1.1).long()
+    else:
+        lo, hi = {"below 4000": (0, 4000), "2048 to 4096": (2048, 4096), "below 2^24": (0, 1 << 24), "equal": (5000, 5001)}[kind]
+        c = torch.randint(lo, hi, (V,), generator=g, device="cuda")
+    order = torch.sort(c, descending=True, stable=True).indices.int()
+    for k in (1, V // 3, V):
+        a, _ = vt.build_trimmed_head(c, None, k, order="rank")
+        assert torch.equal(a, order[:k]), k
