@@ -155,18 +155,19 @@ __device__ __forceinline__ void sort_descending(unsigned long long *v, int N) {
     if (N > 8 * kWave) merge_runs(v, N, 9, N >> 9);
 }
 
-// Sorts v[0 .. N) in LDS, N a multiple of 1024 up to kRunMax, by the `bits` bits from kPlaceBits on, largest first; equal ones keep their
-// order.  All threads call it behind a barrier and find the result behind another.  LSD passes of eight bits with the values in
-// registers: a wave has N / 16 neighbours, and its lanes of one digit find each other with ballots.  A pass takes 1 to 2 us; merging
-// the runs of 8192 values took searches of 70.
+// Sorts v[0 .. N) in LDS, N a multiple of 1024 up to kRunMax, by the bits from kPlaceBits on, largest first; equal ones keep their
+// order.  differ: which of those bits are set in some and clear in others.  All threads call it behind a barrier and find the result
+// behind another.  LSD passes of eight bits with the values in registers: a wave has N / 16 neighbours, and its lanes of one digit
+// find each other with ballots.  A pass takes 2 to 4 us; merging the runs of 8192 values took searches of 55.
 struct DigitLds {
     unsigned short at[kSortWaves * kDigits];      // [wave][digit]
     unsigned part[kSortWaves];
 };
-__device__ __forceinline__ void sort_by_digits(unsigned long long *v, int N, int bits, DigitLds &s) {
+__device__ __forceinline__ void sort_by_digits(unsigned long long *v, int N, unsigned long long differ, DigitLds &s) {
     constexpr int kPer = kRunMax / kRankSortThreads;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, R = N / kRankSortThreads;
-    for (int shift = kPlaceBits; shift < kPlaceBits + bits; shift += 8) {
+    for (int shift = kPlaceBits; shift < 64; shift += 8) {
+        if (((differ >> (shift - kPlaceBits)) & 255ull) == 0ull) continue;      // (uniform)
         unsigned long long x[kPer];
         int d[kPer];
         unsigned local[kPer];
@@ -381,17 +382,17 @@ struct RadixLds {
     unsigned short before[kRunGroups * kDigits];     // elements of a digit in the step's groups of 64 before
 };
 
-// Places [lo, lo + length) of ids[0] by their counts: LSD passes of this workgroup over the digits in which the
-// counts differ, between the two buffers.  Nobody else touches those places.
-__device__ __forceinline__ void sort_by_radix(const long long *__restrict__ counts, const RankBufs &b, unsigned lo,
+// Places [lo, lo + length) of ids by their counts: LSD passes of this workgroup over the digits in which the
+// counts differ, between that buffer and another.  Nobody else touches those places.
+__device__ __forceinline__ void sort_by_radix(const long long *__restrict__ counts, unsigned *ids, unsigned *other, unsigned lo,
                                               unsigned length, int n_ids, int *__restrict__ out_ids, RadixLds &s) {
-    int src = 0;
+    unsigned *from = ids + lo, *to = other + lo;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (tid == 0) s.ones = s.zeros = 0ull;
     __syncthreads();
     unsigned long long ones = 0, zeros = 0;
     for (unsigned x = tid; x < length; x += kRankSortThreads) {
-        const unsigned long long c = (unsigned long long)counts[b.ids[src][lo + x]];
+        const unsigned long long c = (unsigned long long)counts[from[x]];
         ones |= c;
         zeros |= ~c;
     }
@@ -405,8 +406,6 @@ __device__ __forceinline__ void sort_by_radix(const long long *__restrict__ coun
     const unsigned long long differ = s.ones & s.zeros;
     for (int shift = 0; shift < 64; shift += 8) {
         if (((differ >> shift) & 255ull) == 0ull) continue;      // (uniform)
-        const unsigned *from = b.ids[src] + lo;
-        unsigned *to = b.ids[src ^ 1] + lo;
         // element x0 + (u 16 + w) 64 + lane of the run, and 255 - its digit (256: past the end)
         unsigned id[kRunPer];
         int dgt[kRunPer];
@@ -490,28 +489,122 @@ __device__ __forceinline__ void sort_by_radix(const long long *__restrict__ coun
             }
         }
         __syncthreads();                // what was written is read by other waves
-        src ^= 1;
+        unsigned *const written = to;
+        to = from;
+        from = written;
     }
     static_assert(kRunPer * kDigits == kRankSortThreads, "a thread per digit and quarter");
     for (unsigned x = tid; x < length && lo + x < (unsigned)n_ids; x += kRankSortThreads)
-        out_ids[lo + x] = (int)b.ids[src][lo + x];
+        out_ids[lo + x] = (int)from[x];
     __syncthreads();
+}
+
+struct RunLds {
+    union {
+        struct {
+            unsigned long long key[kRunMax];
+            DigitLds digits;
+        };
+        RadixLds radix;
+    };
+    unsigned long long ones, zeros;
+    int far, mixed;
+};
+
+// Order-preserving code of 51 bits: counts below 2^45, of larger ones the 46 highest bits with their exponent.
+__device__ __forceinline__ unsigned long long far_code(unsigned long long c) {
+    if (c < (1ull << 45)) return c;
+    const int e = 63 - __clzll((long long)c);
+    return ((unsigned long long)(e - 44) << 45) + ((c >> (e - 45)) & ((1ull << 45) - 1ull));
+}
+
+// Orders places [lo, lo + length) by (count, place), none of the counts below `lower`.  WHOLE: all ids, the places are the ids.
+template <bool WHOLE>
+__device__ __forceinline__ void sort_run(const long long *__restrict__ counts, unsigned *ids, unsigned *other, unsigned lo, unsigned length,
+                                         unsigned long long lower, int n_ids, int *__restrict__ out_ids, RunLds &s) {
+    const int tid = threadIdx.x;
+    auto id_at = [&](unsigned x) { return WHOLE ? x : ids[lo + x]; };
+    auto by_radix = [&]() {
+        __syncthreads();
+        if constexpr (WHOLE) {
+            for (unsigned x = tid; x < length; x += kRankSortThreads) ids[x] = x;
+            __syncthreads();
+        }
+        sort_by_radix(counts, ids, other, lo, length, n_ids, out_ids, s.radix);
+    };
+    if (length > (unsigned)kRunMax) {
+        by_radix();
+        return;
+    }
+    const bool few = length <= kRankSortThreads;
+    const int N = few ? sort_size((int)length) : (int)((length + kRankSortThreads - 1) / kRankSortThreads * kRankSortThreads);
+    if (tid == 0) {
+        s.far = s.mixed = 0;
+        s.ones = s.zeros = 0ull;
+    }
+    __syncthreads();
+    unsigned long long ones, zeros;
+    auto make_keys = [&](auto code) {
+        ones = zeros = 0ull;
+        for (int x = tid; x < N; x += kRankSortThreads) {
+            unsigned long long key = 0ull;
+            if (x < (int)length) {
+                const unsigned long long above = code((unsigned long long)counts[id_at((unsigned)x)] - lower);
+                ones |= above;
+                zeros |= ~above;
+                key = (above << kPlaceBits) | (unsigned)(kRunMax - 1 - x);
+            }
+            s.key[x] = key;
+        }
+    };
+    auto find_bits = [&]() {
+        ones = wave_or_u64(ones);
+        zeros = wave_or_u64(zeros);
+        if ((tid & 63) == 0) {
+            atomicOr(&s.ones, ones);
+            atomicOr(&s.zeros, zeros);
+        }
+    };
+    make_keys([](unsigned long long above) { return above; });
+    if (__ballot((ones >> (64 - kPlaceBits)) != 0ull) != 0ull && (tid & 63) == 0) s.far = 1;
+    if (!few) find_bits();
+    __syncthreads();
+    const bool far = s.far != 0;          // (uniform)
+    if (far) {
+        // counts 2^51 and more apart: by a code, which settles all of them but neighbours that share their 46 highest bits, if any
+        // (by radix passes the bins of V = 128256 counts of all magnitudes took 77 us, not 32)
+        if (tid == 0) s.ones = s.zeros = 0ull;
+        __syncthreads();
+        make_keys(far_code);
+        if (!few) find_bits();
+        __syncthreads();
+    }
+    if (!few)
+        sort_by_digits(s.key, N, s.ones & s.zeros, s.digits);
+    else if (length > 1u)
+        sort_descending(s.key, N);
+    auto place_at = [&](unsigned x) { return (unsigned)(kRunMax - 1) - ((unsigned)s.key[x] & (unsigned)(kRunMax - 1)); };
+    if (far) {
+        bool mixed = false;
+        for (unsigned x = tid; x + 1 < length; x += kRankSortThreads)
+            mixed |= (unsigned long long)counts[id_at(place_at(x))] < (unsigned long long)counts[id_at(place_at(x + 1))];
+        if (mixed) s.mixed = 1;
+        __syncthreads();
+        if (s.mixed != 0) {               // (uniform)
+            by_radix();
+            return;
+        }
+    }
+    for (unsigned x = tid; x < length; x += kRankSortThreads) {
+        if (lo + x < (unsigned)n_ids) out_ids[lo + x] = (int)id_at(place_at(x));
+    }
 }
 
 // WHOLE: one bin of all n ids.
 template <bool WHOLE>
 __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long long *__restrict__ counts, int n, int n_ids, RankBufs b,
                                                                      int *__restrict__ out_ids) {
-    __shared__ union {
-        struct {
-            unsigned long long key[kRunMax];
-            DigitLds digits;
-        };
-        RadixLds radix;
-    } s;
-    __shared__ int s_far;
-    __shared__ unsigned s_top;
-    const int tid = threadIdx.x;
+    __shared__ RunLds s;
     unsigned lo = 0, length = (unsigned)n;
     unsigned long long lower = 0;         // below all counts of the bin
     if constexpr (!WHOLE) {
@@ -520,50 +613,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long 
         if (blockIdx.x < kSplitters) lower = b.splitters[blockIdx.x];
         if (length == 0u || lo >= (unsigned)n_ids) return;      // (uniform) nothing there, or nobody asks for it
     }
-    auto id_at = [&](unsigned x) { return WHOLE ? x : b.ids[0][lo + x]; };
-    const bool few = length <= kRankSortThreads;
-    const int N = few ? sort_size((int)length) : (int)((length + kRankSortThreads - 1) / kRankSortThreads * kRankSortThreads);
-    if (tid == 0) {
-        s_far = length > (unsigned)kRunMax ? 1 : 0;
-        s_top = 0u;
-    }
-    __syncthreads();
-    if (length <= (unsigned)kRunMax) {
-        bool far = false;
-        unsigned long long ones = 0ull;
-        for (int x = tid; x < N; x += kRankSortThreads) {
-            unsigned long long key = 0ull;
-            if (x < (int)length) {
-                const unsigned long long above = (unsigned long long)counts[id_at((unsigned)x)] - lower;
-                far |= (above >> (64 - kPlaceBits)) != 0ull;
-                ones |= above;
-                key = (above << kPlaceBits) | (unsigned)(kRunMax - 1 - x);
-            }
-            s.key[x] = key;
-        }
-        if (__ballot(far) != 0ull && (tid & 63) == 0) s_far = 1;
-        if (!few) {      // how many bits there are to sort by
-            const unsigned top = wave_max_u32(ones == 0ull ? 0u : 64u - (unsigned)__clzll((long long)ones));
-            if ((tid & 63) == 0) atomicMax(&s_top, top);
-        }
-        __syncthreads();
-    }
-    if (s_far != 0) {                     // (uniform)
-        __syncthreads();
-        if constexpr (WHOLE) {
-            for (int x = tid; x < n; x += kRankSortThreads) b.ids[0][x] = (unsigned)x;
-            __syncthreads();
-        }
-        sort_by_radix(counts, b, lo, length, n_ids, out_ids, s.radix);
-        return;
-    }
-    if (!few)
-        sort_by_digits(s.key, N, (int)s_top, s.digits);
-    else if (length > 1u)
-        sort_descending(s.key, N);
-    for (unsigned x = tid; x < length; x += kRankSortThreads) {
-        if (lo + x < (unsigned)n_ids) out_ids[lo + x] = (int)id_at(kRunMax - 1 - ((unsigned)s.key[x] & (kRunMax - 1)));
-    }
+    sort_run<WHOLE>(counts, b.ids[0], b.ids[1], lo, length, lower, n_ids, out_ids, s);
 }
 
 }  // namespace

@@ -256,7 +256,7 @@ def test_count_around_one_batch(dtype, off):
 
 # A bin's ids are sorted by comparisons up to 1024 of them and by digits of eight bits above: at the edges of both, by no digit, by one
 # and a bit, by all that the keys hold (51 bits), with few values and many
-@pytest.mark.parametrize("V", [1023, 1024, 1025, 2048, 2049, 5000, 8192])
+@pytest.mark.parametrize("V", [1023, 1024, 1025, 2048, 2049, 4096, 4097, 8192])
 @pytest.mark.parametrize("bits", [0, 1, 8, 9, 16, 38, 51])
 def test_rank_order_of_one_bin(V, bits):
     rng = np.random.default_rng(V + bits)
@@ -283,3 +283,24 @@ def test_rank_order_of_large_vocabularies(V, kind):
     for k in (1, V // 3, V):
         a, _ = vt.build_trimmed_head(c, None, k, order="rank")
         assert torch.equal(a, order[:k]), k
+
+
+# Counts 2^51 and more apart in one bin: ordered by their highest 51 bits where that settles them, by all where it does not (neighbours
+# that differ in their lowest bits alone, in no order, beside equal ones); within the 1024 that are compared, and above
+@pytest.mark.parametrize("V", [2, 700, 1024, 1025, 8192, 30011])
+@pytest.mark.parametrize("kind", ["all magnitudes", "settled", "mixed", "equal and far"])
+def test_rank_order_of_counts_far_apart(V, kind):
+    rng = np.random.default_rng(V)
+    c = rng.integers(0, 2**63 - 1, size=V)
+    if kind == "all magnitudes":
+        c >>= rng.integers(0, 63, size=V)
+    elif kind == "settled":
+        c &= ~np.int64(0xFFFF)
+    elif kind == "mixed":
+        c[::3] = (1 << 62) + rng.integers(0, 2000, size=c[::3].size)
+    else:
+        c = rng.choice([0, 1, 1 << 62, (1 << 62) + 1, 1 << 40], size=V)
+    order = np.lexsort((np.arange(V), -c))
+    for k in sorted({1, V // 3 + 1, V}):
+        a, _ = vt.build_trimmed_head(torch.from_numpy(c).cuda(), None, k, order="rank")
+        assert np.array_equal(a.cpu().numpy(), order[:k]), k
