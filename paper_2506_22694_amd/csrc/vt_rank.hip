@@ -60,6 +60,12 @@ static_assert(kRunMax == 1 << kPlaceBits);
 // 25 in place of 15, 38 in place of 23.  (Below 3800 ids the scratch would not hold the tables of the others.)
 constexpr int kRankWholeMax = 4096;
 
+// Workgroups that find the splitters each for itself; more of them, of which two share a CU at a time, read what one has found in a
+// launch before (equal counts of 2048 and more, each for itself / one for all: V = 300 000 30.4 / 27.6 us, 524 288 34.2 / 31.3,
+// 10^6 57.0 / 46.0, 16 * 10^6 633 / 369; after 10^7 tokens, few of them large, V = 128256 18.6 / 20.1, 300 000 24.8 / 25.7, 524 288
+// 29.8 / 30.2, 4 * 10^6 103 / 94).
+constexpr int kOwnSplitters = 400;
+
 struct RankBufs {
     unsigned *rows;                // [nblk][kRankBins] ids of every workgroup per bin; after rank_scan those of the workgroups before
     unsigned *totals;              // [kRankBins]
@@ -243,16 +249,9 @@ __device__ __forceinline__ int rank_bin(unsigned long long c, const unsigned lon
 }
 __device__ __forceinline__ bool one_value(int bin) { return bin >= kWideBins || (bin & 1) != 0; }
 
-__global__ void __launch_bounds__(kRankSortThreads) rank_hist_kernel(const long long *__restrict__ counts, int n, RankBufs b) {
-    __shared__ __align__(16) unsigned h[kRankBins];      // (read by fours)
-    __shared__ unsigned long long sp[kRankSortThreads];
-    __shared__ int s_n;
+// The splitters, from the thread's sample v: sp[0 .. kSplitters) of 1024 values in LDS.  Behind a barrier; ends with one.
+__device__ __forceinline__ void find_splitters(unsigned long long v, unsigned long long *sp, int &s_n) {
     const int tid = threadIdx.x;
-    const int j = blockIdx.x * kRankSortThreads + tid;
-    const bool in = j < n;
-    const unsigned long long c = in ? (unsigned long long)counts[j] : 0ull;
-    const unsigned long long v = (unsigned long long)counts[sample_id(tid, n)];
-    for (int i = tid; i < kRankBins; i += kRankSortThreads) h[i] = 0u;
     sp[tid] = 0ull;
     if (tid == 0) s_n = 0;
     __syncthreads();
@@ -272,7 +271,37 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_hist_kernel(const long 
         if (tid < kSplitters) sp[tid] = x;
         __syncthreads();
     }
-    if (blockIdx.x == 0 && tid < kSplitters) b.splitters[tid] = sp[tid];
+}
+__global__ void __launch_bounds__(kRankSortThreads) rank_split_kernel(const long long *__restrict__ counts, int n, RankBufs b) {
+    __shared__ unsigned long long sp[kRankSortThreads];
+    __shared__ int s_n;
+    find_splitters((unsigned long long)counts[sample_id(threadIdx.x, n)], sp, s_n);
+    if (threadIdx.x < kSplitters) b.splitters[threadIdx.x] = sp[threadIdx.x];
+}
+
+// OWN: every workgroup finds the splitters for itself; else rank_split has.
+template <bool OWN>
+__global__ void __launch_bounds__(kRankSortThreads) rank_hist_kernel(const long long *__restrict__ counts, int n, RankBufs b) {
+    __shared__ __align__(16) unsigned h[kRankBins];      // (read by fours)
+    __shared__ unsigned long long sp[OWN ? kRankSortThreads : kSplitters];
+    const int tid = threadIdx.x;
+    const int j = blockIdx.x * kRankSortThreads + tid;
+    const bool in = j < n;
+    const unsigned long long c = in ? (unsigned long long)counts[j] : 0ull;
+    unsigned long long v = 0ull;
+    if constexpr (OWN)
+        v = (unsigned long long)counts[sample_id(tid, n)];
+    else if (tid < kSplitters)
+        v = b.splitters[tid];
+    for (int i = tid; i < kRankBins; i += kRankSortThreads) h[i] = 0u;
+    if constexpr (OWN) {
+        __shared__ int s_n;
+        find_splitters(v, sp, s_n);
+        if (blockIdx.x == 0 && tid < kSplitters) b.splitters[tid] = sp[tid];
+    } else {
+        if (tid < kSplitters) sp[tid] = v;
+        __syncthreads();
+    }
     wave_tally(h, rank_bin(c, sp), in);
     __syncthreads();
     uint4 *row = reinterpret_cast<uint4 *>(b.rows + (size_t)blockIdx.x * kRankBins);
@@ -977,7 +1006,12 @@ void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_id
     b.start = reinterpret_cast<unsigned *>(p);
     p += round256(kWideBins * 4);
     b.splitters = reinterpret_cast<unsigned long long *>(p);
-    hipLaunchKernelGGL(rank_hist_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, b);
+    if (nblk <= kOwnSplitters) {
+        hipLaunchKernelGGL(rank_hist_kernel<true>, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, b);
+    } else {
+        hipLaunchKernelGGL(rank_split_kernel, dim3(1), dim3(kRankSortThreads), 0, st, counts, n, b);
+        hipLaunchKernelGGL(rank_hist_kernel<false>, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, b);
+    }
     auto scan = nblk <= 8 * kSortWaves ? rank_scan_kernel<8> : rank_scan_kernel<32>;
     hipLaunchKernelGGL(scan, dim3(kScanBlocks), dim3(kRankSortThreads), 0, st, nblk, b);
     hipLaunchKernelGGL(rank_scatter_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);

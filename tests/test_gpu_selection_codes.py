@@ -268,9 +268,10 @@ def test_rank_order_of_one_bin(V, bits):
             assert np.array_equal(a.cpu().numpy(), order[:k]), k
 
 
-# More than 512 workgroups (their tallies are summed up in two rounds), bins between splitters of a thousand ids and more: a few values
+# Up to 400 workgroups (each finds the splitters for itself) and more, up to 512 of them and more (their tallies are summed up in two
+# rounds), bins between splitters of a thousand ids and more: a few values
 # to a bin and many, values below 2048, large ones alone
-@pytest.mark.parametrize("V", [524288, 524289, 1_000_003])
+@pytest.mark.parametrize("V", [409600, 409601, 524288, 524289, 1_000_003])
 @pytest.mark.parametrize("kind", ["below 4000", "2048 to 4096", "below 2^24", "heavy tail", "equal"])
 def test_rank_order_of_large_vocabularies(V, kind):
     g = torch.Generator(device="cuda").manual_seed(V)
