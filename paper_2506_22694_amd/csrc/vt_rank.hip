@@ -6,27 +6,28 @@
 //
 // rank_*: a counting sort over bins that follow the counts, then a sort inside the bins that hold several values.
 //   Counts below 2048 have a bin each (all but a few hundred of a vocabulary's counts, after 10^7 tokens).  Larger counts are
-//   told apart by up to 512 splitters, counts of a fixed sample of 1024 ids (every second one where more of them are large): a bin for every splitter's own value and one
-//   for what lies between two of them, so that a bin of several values holds a few hundred ids wherever the counts lie, and
-//   values that many ids share have bins of their own.
+//   told apart by up to 512 splitters, counts of a fixed sample of 1024 ids (every second one where more of them are large): a
+//   bin for every splitter's own value and one for what lies between two of them, so that a bin of several values holds a few
+//   hundred ids wherever the counts lie, and values that many ids share have bins of their own.
 //   One workgroup per 1024 consecutive ids; "earlier in the input" is (workgroup, wave, lane) order, so that equal counts
 //   stay in ascending-id order:
-//     rank_hist     every workgroup sorts the sample (the same one) and tallies its ids per bin
+//     rank_split    sorts the sample, where there are more than 400 workgroups
+//     rank_hist     every workgroup tallies its ids per bin (and sorts the sample, the same one, for itself otherwise)
 //     rank_scan     sums the tallies up over the workgroups, bin by bin
 //     rank_scatter  places every id: its bin, the workgroups before, the waves before (a byte per bin and wave in LDS), the
 //                   lanes before (lanes of one bin find each other with twelve ballots).  Ids of one-value bins go to the
 //                   result at once
-//     rank_runs     a workgroup per bin of several values orders its ids by (count, id) in LDS; more than 8192 of them, or
-//                   counts 2^51 apart, by radix passes of that workgroup
-//   Four launches in a fixed sequence, nothing read back; launches are most of what it costs (a kernel of the chain 3 to 4 us,
-//   whatever it does).  Up to 8192 ids the last kernel alone, on one bin of all ids.
-//   Against eight launches of LSD passes over 24-bit codes (us): V = 128256 after 10^7 tokens 43.8 -> 18.9, 10^9 44 -> 25, 10^11
-//   47 -> 31; uniform below 2^20 53 -> 34, in 2^40 .. 2^40 + 2^20 49 -> 31, half of them in 2^35 .. 2^35 + 2^13 52 -> 37; V = 32000
-//   after 10^7 35 -> 17; V = 10^6 138 -> 42.  Slower at V = 10^6, where a bin between splitters holds 2000 ids, for counts below
-//   4000 in equal shares (103 -> 130) and for equal counts of 2048 and more (52 -> 57).
-//   The splitters are sorted in every workgroup: a launch of its own for them costs more than the 5 us that 1024 large samples
-//   take (a handful, as a rule: half a microsecond).  512 samples instead of 1024 take 2 us less there and leave bins twice as
-//   long (2^40 .. 2^40 + 2^20: 56 against 31).
+//     rank_runs     a workgroup per bin of several values orders its ids by (count, id) in LDS: up to 1024 by comparisons, up to
+//                   8192 by digits of eight bits.  Longer bins are shared by all workgroups where they are few, and go through
+//                   radix passes of their own workgroup where they are many
+//   Four or five launches in a fixed sequence, nothing read back; launches are most of what it costs (a kernel of the chain 3 to
+//   4 us, whatever it does).  Up to 4096 ids the last kernel alone, on one bin of all ids.
+//   Against eight launches of LSD passes over 24-bit codes (us): V = 128256 after 10^7 tokens 44 -> 19, 10^9 44 -> 25, 10^11
+//   47 -> 31 to 34; uniform below 2^20 53 -> 31, 2048 to 4096 34 -> 30, in 2^40 .. 2^40 + 2^20 49 -> 31; V = 32000 after 10^7 35 -> 16;
+//   V = 8192 31 -> 15; V = 10^6 after 10^7 137 -> 44, 10^11 140 -> 84 to 111, uniform below 4000 103 -> 66, below 2^20 162 -> 75, equal
+//   52 -> 46; V = 4 * 10^6 after 10^7 947 -> 94, uniform below 2^20 1119 -> 507.  Slower only where 20 000 and more large counts all avoid
+//   the sample (V = 128256, 38 000 of them: 51 -> 61; V = 10^6, 100 000 of them: 150 -> 122).
+//   512 samples instead of 1024 take 2 us less to sort and leave bins twice as long.
 // choose_*: no sort: a histogram over bins of counts (exact below 2048) with the mass of every bin, walked from the
 //   largest counts down to the bin in which the mass reaches ceil(P * total).  With the read-back of k 107 us behind a full
 //   sort, now 31.  Where that bin holds several values all workgroups histogram the next eleven bits of its ids, and the
@@ -71,7 +72,8 @@ struct RankBufs {
     unsigned *totals;              // [kRankBins]
     unsigned *start;               // [kWideBins] place of the first id of each bin of large counts
     unsigned long long *splitters; // [kSplitters] descending, zeros behind
-    unsigned *ids[2];              // of the bins of several values, by place; what the radix passes move them to (where `rows` are)
+    unsigned *ids[3];              // of the bins of several values, by place; what slices and radix passes move them to (where `rows` are)
+    unsigned *n_long;              // bins of more than kRunMax ids
 };
 
 __device__ __forceinline__ int lanes_below(unsigned long long m) {
@@ -350,7 +352,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_scatter_kernel(const lo
     __shared__ __align__(16) unsigned char wcnt[kRankBins * kSortWaves];      // [bin][wave] ids
     __shared__ __align__(16) unsigned base[kRankBins];      // place of this workgroup's first id of the bin
     __shared__ unsigned long long sp[kSplitters];
-    __shared__ unsigned part[kSortWaves];
+    __shared__ unsigned part[kSortWaves], s_long;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int j = blockIdx.x * kRankSortThreads + tid;
     const bool in = j < n;
@@ -372,6 +374,7 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_scatter_kernel(const lo
         if (lane >= o) upto += t;
     }
     if (lane == kWave - 1) part[w] = upto;
+    if (tid == 0) s_long = 0u;
     __syncthreads();
     unsigned above = upto - sum;
 #pragma unroll
@@ -379,13 +382,18 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_scatter_kernel(const lo
     if (tid < kBinWords) {
         const uint4 first = make_uint4(above, above + tot.x, above + tot.x + tot.y, above + tot.x + tot.y + tot.z);
         *reinterpret_cast<uint4 *>(base + 4 * tid) = make_uint4(first.x + bef.x, first.y + bef.y, first.z + bef.z, first.w + bef.w);
-        if (blockIdx.x == 0 && tid < kWideBins / 4) reinterpret_cast<uint4 *>(b.start)[tid] = first;
+        if (blockIdx.x == 0 && tid < kWideBins / 4) {
+            reinterpret_cast<uint4 *>(b.start)[tid] = first;
+            const unsigned n_long = (tot.x > (unsigned)kRunMax ? 1u : 0u) + (tot.z > (unsigned)kRunMax ? 1u : 0u);
+            if (n_long != 0u) atomicAdd(&s_long, n_long);
+        }
     }
     const int bin = rank_bin(c, sp);
     const unsigned long long same = match_lanes<12>(bin) & __ballot(in);
     const int below = lanes_below(same);
     if (in && below == 0) wcnt[bin * kSortWaves + w] = (unsigned char)__popcll(same);
     __syncthreads();
+    if (blockIdx.x == 0 && tid == 0) *b.n_long = s_long;
     // ids of the bin in the waves before: bytes 0 .. w - 1 of sixteen
     const uint4 x = *reinterpret_cast<const uint4 *>(wcnt + bin * kSortWaves);
     auto bytes_before = [&](unsigned v, int first) {
@@ -633,20 +641,112 @@ __device__ __forceinline__ void sort_run(const long long *__restrict__ counts, u
     }
 }
 
+// Slice t of S of a bin: what lies between two of the values that divide a sample of the bin's own ids into S parts, or is the lower
+// one.  Found, moved to the place that it has in the result, in order, and sorted there.
+__device__ __forceinline__ void sort_slice(const long long *__restrict__ counts, const RankBufs &b, unsigned lo, unsigned length, unsigned t, unsigned S,
+                                           unsigned long long lower, int n_ids, int *__restrict__ out_ids, RunLds &s, unsigned (&part)[2][kSortWaves]) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    __syncthreads();                      // (what was sorted before is written out)
+    s.key[tid] = (unsigned long long)counts[b.ids[0][lo + (unsigned)((unsigned long long)length * (unsigned)tid / kRankSortThreads)]];
+    __syncthreads();
+    sort_descending(s.key, kRankSortThreads);
+    const bool first = t == 0u;
+    const unsigned long long high = first ? 0ull : s.key[t * kRankSortThreads / S];
+    const unsigned long long low = t == S - 1u ? lower : s.key[(t + 1u) * kRankSortThreads / S];
+    // a wave has a sixteenth of the bin, in order
+    const unsigned begin = (unsigned)((unsigned long long)length * (unsigned)w / kSortWaves);
+    const unsigned end = (unsigned)((unsigned long long)length * (unsigned)(w + 1) / kSortWaves);
+    auto for_each = [&](auto &&f) {
+        constexpr int kLoads = 16;
+        for (unsigned x0 = begin; x0 < end; x0 += kLoads * kWave) {
+            unsigned id[kLoads];
+            unsigned long long c[kLoads];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) id[u] = b.ids[0][lo + min(x0 + u * kWave + lane, end - 1u)];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) c[u] = (unsigned long long)counts[id[u]];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const bool there = x0 + u * kWave + lane < end, above = !first && c[u] >= high;
+                f(id[u], there && !above && c[u] >= low, there && above);
+            }
+        }
+    };
+    // a wave keeps what it finds, as long as there is room
+    constexpr unsigned kKept = 2 * kRunMax / kSortWaves;
+    unsigned *const kept = reinterpret_cast<unsigned *>(s.key) + (unsigned)w * kKept;
+    __syncthreads();                      // (everyone has the two values)
+    unsigned n_in = 0u, n_above = 0u;
+    for_each([&](unsigned id, bool in, bool above) {
+        const unsigned long long mask = __ballot(in);
+        const unsigned at = n_in + (unsigned)lanes_below(mask);
+        if (in && at < kKept) kept[at] = id;
+        n_in += (unsigned)__popcll(mask);
+        n_above += (unsigned)__popcll(__ballot(above));
+    });
+    if (lane == 0) {
+        part[0][w] = n_in;
+        part[1][w] = n_above;
+    }
+    __syncthreads();
+    unsigned total = 0u, before = 0u, at = lo;
+#pragma unroll
+    for (int q = 0; q < kSortWaves; ++q) {
+        total += part[0][q];
+        before += q < w ? part[0][q] : 0u;
+        at += part[1][q];
+    }
+    if (total == 0u || at >= (unsigned)n_ids) return;      // (uniform)
+    unsigned to = at + before;
+    if (n_in <= kKept) {                  // (uniform over the wave)
+        for (unsigned x = (unsigned)lane; x < n_in; x += kWave) b.ids[1][to + x] = kept[x];
+    } else {
+        for_each([&](unsigned id, bool in, bool) {
+            const unsigned long long mask = __ballot(in);
+            if (in) b.ids[1][to + (unsigned)lanes_below(mask)] = id;
+            to += (unsigned)__popcll(mask);
+        });
+    }
+    __syncthreads();
+    sort_run<false>(counts, b.ids[1], b.ids[2], at, total, low, n_ids, out_ids, s);
+}
+
 // WHOLE: one bin of all n ids.
+// Bins too long for LDS go to radix passes of their workgroups where there are many, as between 512 splitters of millions of ids, all
+// large.  Where they are few (neighbours far apart in the sample, or large counts that all avoid it) all workgroups share them: a slice
+// costs a reading of the whole bin, but by 500 workgroups and not by one (V = 128256, 38 000 large counts, none of them in the sample:
+// 61 us, by one workgroup 312; V = 10^6, 100 000 122 / 1200; V = 10^6, all large, of all magnitudes 119 / 211).
+constexpr unsigned kSharedBins = 64, kSliceIds = 2048, kMaxSlices = 512;
 template <bool WHOLE>
 __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long long *__restrict__ counts, int n, int n_ids, RankBufs b,
                                                                      int *__restrict__ out_ids) {
     __shared__ RunLds s;
-    unsigned lo = 0, length = (unsigned)n;
-    unsigned long long lower = 0;         // below all counts of the bin
-    if constexpr (!WHOLE) {
-        lo = b.start[2 * blockIdx.x];
-        length = b.start[2 * blockIdx.x + 1] - lo;
-        if (blockIdx.x < kSplitters) lower = b.splitters[blockIdx.x];
-        if (length == 0u || lo >= (unsigned)n_ids) return;      // (uniform) nothing there, or nobody asks for it
+    if constexpr (WHOLE) {
+        sort_run<true>(counts, b.ids[0], b.ids[1], 0u, (unsigned)n, 0ull, n_ids, out_ids, s);
+    } else {
+        auto lower_of = [&](unsigned bin) { return bin < (unsigned)kSplitters ? b.splitters[bin] : 0ull; };      // below all counts of the bin
+        const unsigned lo = b.start[2 * blockIdx.x], length = b.start[2 * blockIdx.x + 1] - lo, n_long = *b.n_long;
+        const unsigned long long lower = lower_of(blockIdx.x);
+        const bool shared = n_long != 0u && n_long <= kSharedBins;      // (uniform)
+        // (unless nothing is there, or nobody asks for it)
+        if (length != 0u && lo < (unsigned)n_ids && !(shared && length > (unsigned)kRunMax))
+            sort_run<false>(counts, b.ids[0], b.ids[1], lo, length, lower, n_ids, out_ids, s);
+        if (!shared) return;
+        __shared__ unsigned part[2][kSortWaves];
+        unsigned slices = 0u;             // of the bins before: a workgroup takes every gridDim-th
+        for (int i0 = 0; i0 <= kSplitters; i0 += kWave) {
+            const int i = min(i0 + (int)(threadIdx.x & 63), kSplitters);
+            const unsigned bin_lo = b.start[2 * i], bin_length = b.start[2 * i + 1] - bin_lo;
+            for (unsigned long long m = __ballot(i == i0 + (int)(threadIdx.x & 63) && bin_length > (unsigned)kRunMax && bin_lo < (unsigned)n_ids); m != 0ull; m &= m - 1ull) {
+                const int l = __ffsll((long long)m) - 1;
+                const unsigned q_lo = (unsigned)__builtin_amdgcn_readlane((int)bin_lo, l), q_length = (unsigned)__builtin_amdgcn_readlane((int)bin_length, l);
+                const unsigned S = min((q_length + kSliceIds - 1u) / kSliceIds, kMaxSlices);
+                for (unsigned t = (blockIdx.x + gridDim.x - slices % gridDim.x) % gridDim.x; t < S; t += gridDim.x)
+                    sort_slice(counts, b, q_lo, q_length, t, S, lower_of((unsigned)(i0 + l)), n_ids, out_ids, s, part);
+                slices += S;
+            }
+        }
     }
-    sort_run<WHOLE>(counts, b.ids[0], b.ids[1], lo, length, lower, n_ids, out_ids, s);
 }
 
 }  // namespace
@@ -994,11 +1094,12 @@ void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_id
     b.ids[0] = reinterpret_cast<unsigned *>(p);
     p += round256((size_t)n * 4);
     b.ids[1] = reinterpret_cast<unsigned *>(p);
+    b.ids[2] = reinterpret_cast<unsigned *>(p + round256((size_t)n * 4));
     if (n <= kRankWholeMax) {
         hipLaunchKernelGGL(rank_runs_kernel<true>, dim3(1), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
         return;
     }
-    // (12 KiB per 1024 ids, more than the 4 KiB that the radix passes write there)
+    // (12 KiB per 1024 ids, more than the two times 4 KiB that slices and radix passes write there)
     b.rows = reinterpret_cast<unsigned *>(p);
     p += round256((size_t)nblk * kRankBins * 4);
     b.totals = reinterpret_cast<unsigned *>(p);
@@ -1006,6 +1107,7 @@ void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_id
     b.start = reinterpret_cast<unsigned *>(p);
     p += round256(kWideBins * 4);
     b.splitters = reinterpret_cast<unsigned long long *>(p);
+    b.n_long = reinterpret_cast<unsigned *>(p + kSplitters * 8);
     if (nblk <= kOwnSplitters) {
         hipLaunchKernelGGL(rank_hist_kernel<true>, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, b);
     } else {
@@ -1017,7 +1119,7 @@ void launch_rank_sort(const long long *counts, int n, void *scratch, int *out_id
     hipLaunchKernelGGL(rank_scatter_kernel, dim3(nblk), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
     hipLaunchKernelGGL(rank_runs_kernel<false>, dim3(kSplitters + 1), dim3(kRankSortThreads), 0, st, counts, n, n_ids, b, out_ids);
 }
-static_assert(kRankBins * 4 >= 4 * kRankSortThreads, "the radix passes' second buffer lies where the rows are");
+static_assert(kRankBins * 4 >= 8 * kRankSortThreads, "two buffers of ids lie where the rows are");
 
 // (likewise: ids and counts in order, sums per workgroup, and the sort's buffers)
 size_t choose_k_ws_bytes(int V) {

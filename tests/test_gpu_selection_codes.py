@@ -305,3 +305,45 @@ def test_rank_order_of_counts_far_apart(V, kind):
     for k in sorted({1, V // 3 + 1, V}):
         a, _ = vt.build_trimmed_head(torch.from_numpy(c).cuda(), None, k, order="rank")
         assert np.array_equal(a.cpu().numpy(), order[:k]), k
+
+
+def _sample(V):
+    """The ids that the splitters are taken from."""
+    i = np.arange(1024, dtype=np.uint64)
+    return ((i << np.uint64(16) | i * np.uint64(40503) & np.uint64(0xFFFF)) * np.uint64(V)) // np.uint64(1 << 26)
+
+
+# One bin of more ids than LDS holds, shared by all workgroups: large counts that avoid the sample, with as many values as ids, with one
+# and with two, and with values that also avoid the sample of the bin itself (a slice is then too long as well); two such bins
+@pytest.mark.parametrize("V", [20011, 65536, 131072, 1_000_003])
+@pytest.mark.parametrize("kind", ["all", "one value", "two values", "slices", "two bins", "far"])
+def test_rank_order_of_long_bins(V, kind):
+    rng = np.random.default_rng(V)
+    c = rng.integers(3000, 10**7, size=V)
+    if kind == "one value":
+        c[:] = 77777
+    elif kind == "two values":
+        c = rng.integers(0, 2, size=V) * 5000 + 5000
+    elif kind == "far":
+        c = rng.integers(3000, 2**62, size=V) >> rng.integers(0, 40, size=V)
+    c[_sample(V)] = rng.integers(0, 200, size=1024)
+    if kind == "slices":
+        inside = np.flatnonzero(c >= 2048)
+        c[inside[np.arange(1024) * inside.size // 1024]] = 4_000_000
+    if kind == "two bins":
+        c[_sample(V)[:512]] = 5_000_000
+    order = torch.sort(torch.from_numpy(c).cuda(), descending=True, stable=True).indices.int()
+    for k in sorted({1, V // 3 + 1, V}):
+        a, _ = vt.build_trimmed_head(torch.from_numpy(c).cuda(), None, k, order="rank")
+        assert torch.equal(a, order[:k]), k
+
+
+# So many long bins that every one is left to its workgroup, most of them within LDS beside some that are shared
+@pytest.mark.parametrize("V", [2_000_000, 6_000_001])
+def test_rank_order_of_millions_of_large_counts(V):
+    g = torch.Generator(device="cuda").manual_seed(V)
+    c = torch.randint(2048, 1 << 30, (V,), generator=g, device="cuda")
+    order = torch.sort(c, descending=True, stable=True).indices.int()
+    for k in (1, V // 2, V):
+        a, _ = vt.build_trimmed_head(c, None, k, order="rank")
+        assert torch.equal(a, order[:k]), k

@@ -45,3 +45,18 @@ def test_more_tokens_than_lists():
         captured.append(graph.replay)
     many, few = _times(*captured)
     assert many < 1.5 * few, (many, few)
+
+
+# Large counts that avoid the ids which the splitters are sampled from: one workgroup ordered all 38 000 of them (322 us; no such counts 37)
+def test_large_counts_outside_the_sample():
+    V = 128256
+    i = torch.arange(1024, dtype=torch.int64, device="cuda")
+    sample = ((i << 16 | i * 40503 & 0xFFFF) * V) >> 26
+    g = torch.Generator(device="cuda").manual_seed(1)
+    spread = torch.where(torch.rand(V, generator=g, device="cuda") < 0.3, torch.randint(10**5, 10**7, (V,), generator=g, device="cuda"), 5)
+    hidden = spread.clone()
+    hidden[sample] = 5
+    ws = torch.empty(vt.load_library().vt_build_trimmed_head_ws_bytes(V, 8, V), dtype=torch.uint8, device="cuda")
+    out = torch.empty(V, dtype=torch.int32, device="cuda")
+    t = _times(*[lambda c=c: vt.build_trimmed_head(c, None, V, ws=ws, out_map=out, order="rank") for c in (hidden, spread)])
+    assert t[0] < 4 * t[1], t
