@@ -110,12 +110,18 @@ def _check(status: int) -> None:
 
 
 # The handle of the current stream, without a Stream object around it (0.1 us; torch.cuda.current_stream takes 2.3, a sixth of
-# a draft step's way through this module).
+# a draft step's way through this module).  It is no public function and wants an index, which every tensor's device has; the
+# public one serves where either is missing.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    if _raw_stream is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
-# (the prototypes below take plain integers for pointers: an object around each costs 0.1 us)
+# (the prototypes above take plain integers for pointers: an object around each costs 0.1 us)
 def _ptr(t):
     return None if t is None else t.data_ptr()
 

@@ -370,3 +370,16 @@ def test_multi_head_argument_errors(lib):
     assert build(V=900) == 2                      # k[0] = 1000 > V
     assert build(map=(ctypes.c_void_p * 2)(0x1000, None)) == 1
     assert build(wsb=16) == 5
+
+
+def test_stream_handle_without_the_raw_function_or_a_device_index(monkeypatch):
+    from types import SimpleNamespace
+    from paper_2506_22694_amd import binding
+    asked = []
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: asked.append(device) or SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(binding, "_raw_stream", lambda index: 100 + index, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: 100 + index, raising=False)
+    assert binding._stream(torch.device("cuda", 3)) == 103 and asked == []
+    assert binding._stream(torch.device("cuda")) == 77 and asked == [torch.device("cuda")]
+    monkeypatch.setattr(binding, "_raw_stream", None, raising=False)
+    assert binding._stream(torch.device("cuda", 3)) == 77 and asked[1:] == [torch.device("cuda", 3)]
