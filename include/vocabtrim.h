@@ -85,7 +85,10 @@ const char *vt_last_device_error(void);
  *   n_invalid  device uint64, in/out, nullable: ids < 0 or >= V are skipped
  *              and added here, so sum(counts) + *n_invalid grows by n_ids
  *   ws         >= vt_count_tokens_ws_bytes(V, n_ids) bytes; contents need no
- *              initialisation
+ *              initialisation.  Less is accepted down to what chunks of 65536
+ *              ids take (sizes that earlier versions returned): the ids are then
+ *              counted by fewer workgroups, which is slower for short streams;
+ *              below that VT_ERR_WORKSPACE
  * ---------------------------------------------------------------------- */
 int vt_count_tokens(const void *ids, int id_type, int64_t n_ids, int32_t V, int64_t *counts,
                     uint64_t *n_invalid, void *ws, size_t ws_bytes, void *stream);

@@ -1181,7 +1181,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         f.L = p.L;
         f.n = n;
         f.m = m;
-                f.out_ids = out_ids;
+        f.out_ids = out_ids;
         f.out_logp = out_logp;
         f.out_lse = out_lse;
         f.lse_buf = lse_buf;

@@ -8,19 +8,14 @@
 
 namespace vt {
 
-// exact below 2^EXACT_LOG; above, MANT_LOG bits after the leading one
-template <int EXACT_LOG, int MANT_LOG>
-__device__ __forceinline__ unsigned count_code(unsigned long long c) {
-    if (c < (1ull << EXACT_LOG)) return (unsigned)c;
-    const int e = 63 - __clzll((long long)c);
-    return (1u << EXACT_LOG) + ((unsigned)(e - EXACT_LOG) << MANT_LOG) +
-           (unsigned)((c >> (e - MANT_LOG)) & ((1ull << MANT_LOG) - 1));
-}
-
-// ---- histogram bins: exact below 2048 (a bin is one value), then 32 bins per power of two
+// ---- histogram bins: exact below 2048 (a bin is one value), then 32 bins per power of two: five bits after the leading one
 constexpr int kBinExact = 2048;
 constexpr int kBins = kBinExact + (64 - 11) * 32;      // 3744
-__device__ __forceinline__ int count_bin(unsigned long long c) { return (int)count_code<11, 5>(c); }
+__device__ __forceinline__ int count_bin(unsigned long long c) {
+    if (c < (unsigned long long)kBinExact) return (int)c;
+    const int e = 63 - __clzll((long long)c);
+    return kBinExact + ((e - 11) << 5) + (int)((c >> (e - 5)) & 31ull);
+}
 // bin >= kBinExact: its counts c have c >> shift == prefix
 __device__ __forceinline__ int bin_shift(int bin) { return 11 + ((bin - kBinExact) >> 5) - 5; }
 __device__ __forceinline__ unsigned long long bin_prefix(int bin) { return 32ull + (unsigned)((bin - kBinExact) & 31); }

@@ -67,7 +67,7 @@ size_t hist_min_scratch_bytes(int V, int64_t n_ids) { return chunks_of(n_ids, V,
 
 // `head` ids (fewer than one 16-byte vector) precede the first 16-byte aligned id.
 constexpr int kHistWaves = kHistThreads / kWave;
-constexpr unsigned kHistHot = 128;      // increments of one bin among a workgroup's first 8192 ids that make it a hot one
+constexpr unsigned kHistHot = 128;      // increments of one bin among a workgroup's first two vectors per thread (8192 ids, 4096 of 64 bits) that make it a hot one
 // LDS: the bins, and behind them (see the kernel)
 constexpr unsigned kHistHotAt = kHistBinsPerBlock * 2, kHistAsideAt = kHistHotAt + 4 * kHistThreads, kHistHotBinAt = kHistAsideAt + 4 * kWave;
 constexpr unsigned kHistLaterAt = kHistHotBinAt + 4 * kHistWaves, kHistLds = kHistLaterAt + 4;
@@ -450,8 +450,11 @@ hipError_t launch_count_tokens(const void *ids, bool ids64, int64_t n_ids, int V
     if (nchunks < 1) return hipErrorInvalidValue;
     const size_t lds = kHistLds;
     static LdsLimitOnce lds_limit;
-    hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(hist_partial_kernel<false, false>), reinterpret_cast<const void *>(hist_partial_kernel<true, false>),
-                                                 reinterpret_cast<const void *>(hist_partial_kernel<false, true>), reinterpret_cast<const void *>(hist_partial_kernel<true, true>)}, (int)lds);
+    hipError_t e = allow_dynamic_lds(lds_limit,
+                                     {reinterpret_cast<const void *>(hist_partial_kernel<false, false>),
+                                      reinterpret_cast<const void *>(hist_partial_kernel<true, false>),
+                                      reinterpret_cast<const void *>(hist_partial_kernel<false, true>),
+                                      reinterpret_cast<const void *>(hist_partial_kernel<true, true>)}, (int)lds);
     if (e != hipSuccess) return e;
     // ids before the first 16-byte boundary are counted one by one
     const int idb = ids64 ? 8 : 4;

@@ -737,7 +737,8 @@ __global__ void __launch_bounds__(kRankSortThreads) rank_runs_kernel(const long 
         for (int i0 = 0; i0 <= kSplitters; i0 += kWave) {
             const int i = min(i0 + (int)(threadIdx.x & 63), kSplitters);
             const unsigned bin_lo = b.start[2 * i], bin_length = b.start[2 * i + 1] - bin_lo;
-            for (unsigned long long m = __ballot(i == i0 + (int)(threadIdx.x & 63) && bin_length > (unsigned)kRunMax && bin_lo < (unsigned)n_ids); m != 0ull; m &= m - 1ull) {
+            const bool is_long = i == i0 + (int)(threadIdx.x & 63) && bin_length > (unsigned)kRunMax && bin_lo < (unsigned)n_ids;
+            for (unsigned long long m = __ballot(is_long); m != 0ull; m &= m - 1ull) {
                 const int l = __ffsll((long long)m) - 1;
                 const unsigned q_lo = (unsigned)__builtin_amdgcn_readlane((int)bin_lo, l), q_length = (unsigned)__builtin_amdgcn_readlane((int)bin_length, l);
                 const unsigned S = min((q_length + kSliceIds - 1u) / kSliceIds, kMaxSlices);

@@ -762,15 +762,15 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
 
 // ------------------------------------------------------------------ final merge of one hidden row (one wave)
 // pkeys_row: [B][L] keys, each list sorted descending.  stage: wave-private LDS for (min(B, 256) + 1) * L + kDirectPad keys.
-// Lists are merged 256 at a time (4 per lane); with CARRY the best m of one
+// Lists are merged 256 at a time (4 per lane); the best m of one
 // group are carried into the next as one more list, so B is unbounded.
 // lse_fn(): the row's log-sum-exp, one value in all lanes; called exactly once, when the results are about to be written.
-template <bool CARRY, typename LseFn>
+template <typename LseFn>
 __device__ __forceinline__ void finalize_row(const unsigned long long *__restrict__ pkeys_row, int B, int L, int m, LseFn &&lse_fn,
                                              unsigned long long *stage, int *__restrict__ out_ids_row,
                                              float *__restrict__ out_logp_row, int lane) {
     constexpr int GROUP = kStepMaxBlocks;        // lists merged per pass
-    constexpr int BQ = GROUP / kWave + (CARRY ? 1 : 0);   // lists per lane
+    constexpr int BQ = GROUP / kWave + 1;        // lists per lane
     constexpr int U = 32;                        // 64-lane loads in flight per batch (16 KiB)
     if (B <= GROUP && m <= kWave && B * L <= kBlockMergeSpill) {
         bool done;
@@ -819,18 +819,16 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
                 }
             }
         }
-        if constexpr (CARRY) {
-            // the previous pass's result (lane r holds rank r) joins as list number Bc
-            if (lane < L)
-                stage[total + lane] = (b0 > 0 && lane < m && res_ord != 0u)
-                                          ? (((unsigned long long)res_ord << 32) | (unsigned)(~res_id))
-                                          : kNoKey;
-        }
+        // the previous pass's result (lane r holds rank r) joins as list number Bc
+        if (lane < L)
+            stage[total + lane] = (b0 > 0 && lane < m && res_ord != 0u)
+                                      ? (((unsigned long long)res_ord << 32) | (unsigned)(~res_id))
+                                      : kNoKey;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         // m rounds over the heads of the sorted lists
-        const int nl = Bc + (CARRY ? 1 : 0);
+        const int nl = Bc + 1;
         unsigned ord[BQ];
         int id[BQ];
         int pos[BQ];
@@ -919,7 +917,7 @@ __device__ __forceinline__ void finalize_row_pair(const FinalizeArgs &f, int i, 
             __syncthreads();
             return *s_lse;
         };
-        finalize_row<true>(pkeys_row, f.nlists, f.L, f.m, lse_fn, stage, f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, lane);
+        finalize_row(pkeys_row, f.nlists, f.L, f.m, lse_fn, stage, f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, lane);
     } else {
         if (w == 1) {
             const float lse = row_lse(pms_row, f.nlists, lane);
@@ -939,7 +937,7 @@ __device__ __forceinline__ void finalize_row_alone(const FinalizeArgs &f, int i,
         f.lse_buf[i] = lse;
         if (f.out_lse) f.out_lse[o] = lse;
     }
-    finalize_row<true>(f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m, [lse]() { return lse; }, stage,
+    finalize_row(f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m, [lse]() { return lse; }, stage,
                        f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, lane);
 }
 
