@@ -655,8 +655,8 @@ __device__ __forceinline__ bool finalize_row_flat(const unsigned long long *__re
 // it reaches T, so the keys are looked at rank by rank until a rank has none (two or three of them, as a rule; all L keys of all
 // lists, one test each, took 0.5 us longer).  Where the best tokens share a list (a head in order of frequency) what lies behind
 // the first D is asked for in one or two trips; a trip per rank took longer than the short lists save (n = 8, m = 8, k = 5000,
-// d = 3072, all in one list: 14.8 us with all keys read, 15.3, now 14.4; k = 32768 37.1 / 37.8 / 37.1, spread over the lists
-// 36.8 / 35.9 / 35.7; n = 4, m = 11, in one list 37.1 / 38.7 / 37.4; n = 4, m = 10, d = 2048 28.3 / 29.5 / 28.9).
+// d = 3072, all in one list: 14.6 us with all keys read, 14.9, now 14.2; k = 32768 36.9 / 37.8 / 37.1, spread over the lists
+// 37.0 / 35.8 / 35.8; n = 4, m = 11, in one list 37.0 / 38.6 / 37.6; n = 4, m = 10, d = 2048 28.0 / 29.3 / 28.7).
 // The candidates are compacted into LDS and ranked by counting.  PAIRS: L is even, two keys to a load.  MORE: L may exceed D.
 // Returns false, having written nothing, when more than kDirectMaxCand keys reach T (massive ties): the caller then merges the
 // lists round by round.  lse_fn() is called once, when the results are about to be written.
@@ -727,10 +727,10 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
 #pragma unroll
     for (int j = 0; j < D; ++j) more = more && collect(key[j]);
     if constexpr (!MORE) return rank_candidates(stage, ncand, m, lse_fn, out_ids_row, out_logp_row, lane);
-    int j = D;
-    // the next keys of the lists whose last one reaches T, up to eight of each to a trip
-    auto collect_next = [&](auto ranks) {
-        constexpr int R = decltype(ranks)::value;
+    // the next keys of the lists whose last one reaches T, four of each to a trip (with a second form for eight the code of the usual
+    // case took 0.25 us longer to come through)
+    constexpr int R = 4;
+    for (int j = D; more && j < L; j += R) {
         unsigned long long next[R][X];
         bool open[X];
 #pragma unroll
@@ -749,13 +749,6 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
         }
 #pragma unroll
         for (int q = 0; q < R; ++q) more = more && ncand <= kDirectMaxCand && collect(next[q]);
-        j += R;
-    };
-    while (more && j < L) {
-        if (L - j <= 4)
-            collect_next(std::integral_constant<int, 4>{});
-        else
-            collect_next(std::integral_constant<int, 8>{});
     }
     return rank_candidates(stage, ncand, m, lse_fn, out_ids_row, out_logp_row, lane);
 }
@@ -775,8 +768,10 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
     if (B <= GROUP && m <= kWave && B * L <= kBlockMergeSpill) {
         bool done;
         // Fewer lists than lanes: the keys are dealt to the lanes one by one (n = 1, 17 lists of 8, m = 24 7.7 us a step; by
-        // lists 19.3, since lanes without one leave no threshold; n = 7, 11 lists of 8, m = 8 8.3 / 10.0)
-        if (B * L <= 4 * kWave)
+        // lists 19.3, since lanes without one leave no threshold; n = 7, 11 lists of 8, m = 8 8.3 / 10.0).  (The usual case first.)
+        if (B >= kWave && L > 4 && (L & 1) == 0)
+            done = finalize_row_direct<4, true, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        else if (B * L <= 4 * kWave)
             done = finalize_row_flat<4>(pkeys_row, B * L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (B < kWave && B * L <= 32 * kWave && (B * L & 1) == 0)
             done = finalize_row_flat<32>(pkeys_row, B * L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
