@@ -1030,6 +1030,7 @@ int run_step_heads_fused(const void *h, int n, int d, const void *const *W_trim,
     f.pms = a.pms;
     f.pkeys = a.pkeys;
     f.nlists = p.nlists;
+    f.several_heads = t.n_heads > 1 ? 1 : 0;
     f.L = p.L;
     f.n = n;
     f.m = m;

@@ -140,6 +140,7 @@ struct FinalizeArgs {
     const unsigned long long *pms;
     const unsigned long long *pkeys;
     int nlists, L, n, m;
+    int several_heads;        // of a row's lists those of its own head alone hold keys
     int *out_ids;
     float *out_logp;
     float *out_lse;           // or null

@@ -512,16 +512,10 @@ __device__ __forceinline__ void acquire_load16(u32x4 &dst, const void *p) {
 }
 template <int N>
 __device__ __forceinline__ void wait_loads16(u32x4 (&r)[N]) {
-    static_assert(N == 4 || N == 8 || N == 16);
-    if constexpr (N == 4)
-        asm volatile("s_waitcnt vmcnt(0)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
-    else if constexpr (N == 16)
-        asm volatile("s_waitcnt vmcnt(0)"
-                     : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]),
-                       "+v"(r[8]), "+v"(r[9]), "+v"(r[10]), "+v"(r[11]), "+v"(r[12]), "+v"(r[13]), "+v"(r[14]), "+v"(r[15]));
-    else
-        asm volatile("s_waitcnt vmcnt(0)"
-                     : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
+    static_assert(N % 4 == 0 && N <= 24);
+    // (the first of them waits for all)
+#pragma unroll
+    for (int q = 0; q < N; q += 4) asm volatile("s_waitcnt vmcnt(0)" : "+v"(r[q]), "+v"(r[q + 1]), "+v"(r[q + 2]), "+v"(r[q + 3]));
 }
 
 // The first active lane's value in every lane.  The row's log-sum-exp goes through this before it is subtracted
@@ -657,10 +651,11 @@ __device__ __forceinline__ bool finalize_row_flat(const unsigned long long *__re
 // the first D is asked for in one or two trips; a trip per rank took longer than the short lists save (n = 8, m = 8, k = 5000,
 // d = 3072, all in one list: 14.6 us with all keys read, 14.9, now 14.2; k = 32768 36.9 / 37.8 / 37.1, spread over the lists
 // 37.0 / 35.8 / 35.8; n = 4, m = 11, in one list 37.0 / 38.6 / 37.6; n = 4, m = 10, d = 2048 28.0 / 29.3 / 28.7).
-// The candidates are compacted into LDS and ranked by counting.  PAIRS: L is even, two keys to a load.  MORE: L may exceed D.
+// The candidates are compacted into LDS and ranked by counting.  PAIRS: L is even, two keys to a load.  MORE: L may exceed
+// D, and so many keys of a list are asked for at a time then (two forms, of four and eight, in one took the usual case 0.25 us longer).
 // Returns false, having written nothing, when more than kDirectMaxCand keys reach T (massive ties): the caller then merges the
 // lists round by round.  lse_fn() is called once, when the results are about to be written.
-template <int D, bool PAIRS, bool MORE, typename LseFn>
+template <int D, bool PAIRS, int MORE, typename LseFn>
 __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__restrict__ src, int B, int L, int m,
                                                     LseFn &&lse_fn, unsigned long long *stage, int *__restrict__ out_ids_row,
                                                     float *__restrict__ out_logp_row, int lane) {
@@ -726,10 +721,9 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
     bool more = true;
 #pragma unroll
     for (int j = 0; j < D; ++j) more = more && collect(key[j]);
-    if constexpr (!MORE) return rank_candidates(stage, ncand, m, lse_fn, out_ids_row, out_logp_row, lane);
-    // the next keys of the lists whose last one reaches T, four of each to a trip (with a second form for eight the code of the usual
-    // case took 0.25 us longer to come through)
-    constexpr int R = 4;
+    if constexpr (MORE == 0) return rank_candidates(stage, ncand, m, lse_fn, out_ids_row, out_logp_row, lane);
+    // the next keys of the lists whose last one reaches T, R of each to a trip
+    constexpr int R = MORE > 0 ? MORE : 1;
     for (int j = D; more && j < L; j += R) {
         unsigned long long next[R][X];
         bool open[X];
@@ -759,7 +753,7 @@ __device__ __forceinline__ bool finalize_row_direct(const unsigned long long *__
 // group are carried into the next as one more list, so B is unbounded.
 // lse_fn(): the row's log-sum-exp, one value in all lanes; called exactly once, when the results are about to be written.
 template <typename LseFn>
-__device__ __forceinline__ void finalize_row(const unsigned long long *__restrict__ pkeys_row, int B, int L, int m, LseFn &&lse_fn,
+__device__ __forceinline__ void finalize_row(const unsigned long long *__restrict__ pkeys_row, int B, int L, int m, bool several_heads, LseFn &&lse_fn,
                                              unsigned long long *stage, int *__restrict__ out_ids_row,
                                              float *__restrict__ out_logp_row, int lane) {
     constexpr int GROUP = kStepMaxBlocks;        // lists merged per pass
@@ -769,22 +763,26 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
         bool done;
         // Fewer lists than lanes: the keys are dealt to the lanes one by one (n = 1, 17 lists of 8, m = 24 7.7 us a step; by
         // lists 19.3, since lanes without one leave no threshold; n = 7, 11 lists of 8, m = 8 8.3 / 10.0).  (The usual case first.)
-        if (B >= kWave && L > 4 && (L & 1) == 0)
-            done = finalize_row_direct<4, true, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        if (B >= kWave && L == 8)
+            done = finalize_row_direct<4, true, 4>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (B * L <= 4 * kWave)
             done = finalize_row_flat<4>(pkeys_row, B * L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+        else if (several_heads && m > 8 && (B * L & 1) == 0)
+            // (a small head's lists alone leave no threshold either: n = 4, m = 10, heads of 1378, 236, 560 and 93 rows 12.9 us, by
+            // lists 16.2.  Up to eight tokens a few lists are a few groups, by lists 11.6 against 12.3)
+            done = finalize_row_flat<48>(pkeys_row, B * L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (B < kWave && B * L <= 32 * kWave && (B * L & 1) == 0)
             done = finalize_row_flat<32>(pkeys_row, B * L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (L == 1)
-            done = finalize_row_direct<1, false, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<1, false, 0>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (L == 2)
-            done = finalize_row_direct<2, true, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<2, true, 0>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if (L == 4)
-            done = finalize_row_direct<4, true, false>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<4, true, 0>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else if ((L & 1) == 0)
-            done = finalize_row_direct<4, true, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<4, true, 8>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         else
-            done = finalize_row_direct<3, false, true>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
+            done = finalize_row_direct<3, false, 8>(pkeys_row, B, L, m, lse_fn, stage, out_ids_row, out_logp_row, lane);
         if (done) return;
     }
 
@@ -912,7 +910,7 @@ __device__ __forceinline__ void finalize_row_pair(const FinalizeArgs &f, int i, 
             __syncthreads();
             return *s_lse;
         };
-        finalize_row(pkeys_row, f.nlists, f.L, f.m, lse_fn, stage, f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, lane);
+        finalize_row(pkeys_row, f.nlists, f.L, f.m, f.several_heads != 0, lse_fn, stage, f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, lane);
     } else {
         if (w == 1) {
             const float lse = row_lse(pms_row, f.nlists, lane);
@@ -932,7 +930,7 @@ __device__ __forceinline__ void finalize_row_alone(const FinalizeArgs &f, int i,
         f.lse_buf[i] = lse;
         if (f.out_lse) f.out_lse[o] = lse;
     }
-    finalize_row(f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m, [lse]() { return lse; }, stage,
+    finalize_row(f.pkeys + (size_t)i * f.nlists * f.L, f.nlists, f.L, f.m, f.several_heads != 0, [lse]() { return lse; }, stage,
                        f.out_ids + (size_t)o * f.m, f.out_logp + (size_t)o * f.m, lane);
 }
 

@@ -169,3 +169,20 @@ def test_best_tokens_of_tiles_of_eight(dtype, n, k, m, spread):
     assert torch.equal(ids, map_[order])
     assert (lse.double() - want).abs().max().item() <= 1e-5       # (fp32 sums of 2000 exponentials, a log-sum-exp below 16)
     assert (logp.double() - (z.gather(1, order) - want.unsqueeze(1))).abs().max().item() <= 1e-5
+
+
+# Several heads and more than eight tokens: a row's keys are all read and dealt to the lanes, or by lists where their number is odd; rows
+# of one list, of a few and of most of them
+@pytest.mark.parametrize("ks", [(1378, 236, 560, 93), (29045, 946, 72), (30000, 65), (16385, 16384)])
+@pytest.mark.parametrize("n,m", [(4, 9), (4, 10), (8, 10), (3, 11)])
+def test_lists_of_several_heads_with_more_than_eight_tokens(ks, n, m):
+    d = 256
+    g = torch.Generator(device="cuda").manual_seed(sum(ks) + m)
+    heads = [(torch.randn(k, d, generator=g, device="cuda").mul_(0.1).bfloat16(), torch.arange(k, dtype=torch.int32, device="cuda")) for k in ks]
+    h = torch.randn(n, d, generator=g, device="cuda").bfloat16()
+    which = [i % len(ks) for i in range(n)]
+    ids, logp, lse = vt.draft_head_step_multi(h, heads, which, m, return_lse=True)
+    for i, q in enumerate(which):
+        one_ids, one_logp = vt.draft_head_step(h[i:i + 1].expand(2, d).contiguous(), heads[q][0], heads[q][1], m)
+        assert torch.equal(ids[i], one_ids[0])
+        assert (logp[i] - one_logp[0]).abs().max().item() <= 4e-6      # sums over other tiles: a few ulp of a log-sum-exp near 10
