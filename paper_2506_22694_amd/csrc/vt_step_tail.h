@@ -759,7 +759,8 @@ __device__ __forceinline__ void finalize_row(const unsigned long long *__restric
     constexpr int GROUP = kStepMaxBlocks;        // lists merged per pass
     constexpr int BQ = GROUP / kWave + 1;        // lists per lane
     constexpr int U = 32;                        // 64-lane loads in flight per batch (16 KiB)
-    if (B <= GROUP && m <= kWave && B * L <= kBlockMergeSpill) {
+    // (64 tokens: the threshold is the worst of the lanes' best keys, which more than kDirectMaxCand reach wherever there are so many)
+    if (B <= GROUP && B * L <= (m < kWave ? kBlockMergeSpill : kDirectMaxCand)) {
         bool done;
         // Fewer lists than lanes: the keys are dealt to the lanes one by one (n = 1, 17 lists of 8, m = 24 7.7 us a step; by
         // lists 19.3, since lanes without one leave no threshold; n = 7, 11 lists of 8, m = 8 8.3 / 10.0).  (The usual case first.)
