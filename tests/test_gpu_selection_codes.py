@@ -31,7 +31,7 @@ def _counts(kind, V, rng):
 @pytest.mark.parametrize("kind", ["around 2048", "around 2^19", "large and equal", "large, few values", "powers of two", "heavy tail"])
 def test_selection_at_the_edges_of_the_codes(kind, V):
     if kind == "large, few values" and V > 4097:
-        V = 4097          # (ordered by counting inside a run: one run of all ids)
+        V = 4097          # (one bin of all ids, one more of them than one workgroup takes)
     rng = np.random.default_rng(V + len(kind))
     c = np.asarray(_counts(kind, V, rng), dtype=np.int64)
     dc = torch.from_numpy(c).cuda()
@@ -129,7 +129,7 @@ def test_choice_of_k_among_large_counts(kind, V):
         assert vt.choose_k(dc, top_p=P) == oracle.choose_k_top_p(c, P), P
 
 
-# Rank order: counts of 2^19 and more that share a code, in runs around the lengths that are ordered differently (16, 256, 1024)
+# Rank order: large counts in clusters of 1 to 9000 ids, far apart from each other and near inside
 def _counts_in_runs(lengths, V, rng):
     c = rng.integers(0, 1000, size=V)
     at = 0
@@ -172,7 +172,8 @@ def test_count_hot_ids_side_by_side(V, n_ids, hot, dtype):
     assert np.array_equal(c.cpu().numpy(), 2 * np.bincount(ids, minlength=V))
 
 
-# Rank order by bins: all ids in one workgroup and one more, a ragged last one, one round of the sum over workgroups and two;
+# Rank order by bins: one workgroup, several, a ragged last one, the sum over workgroups by eight rows of a wave (up to 128 workgroups) and
+# by thirty-two (two rounds of that: test_rank_order_of_large_vocabularies);
 # `crowded`: no id of the sample is large, so one bin holds all large counts; `far`: counts of a bin too far apart for keys in LDS
 @pytest.mark.parametrize("V", [1, 64, 8191, 8192, 8193, 131072, 131073])
 @pytest.mark.parametrize("kind", ["uniform", "crowded", "far", "shared"])
