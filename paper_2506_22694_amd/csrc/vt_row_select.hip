@@ -12,8 +12,8 @@
 //   pass 2  logits >= T become candidate keys in LDS (typically a few dozen), ranked by counting (rows of up to 32768
 //           logits stay in registers in between, longer ones are sifted as they go by: row_select_kernel);
 //   (up to 32768 logits a row is bound by a chain: the loads, a reduction, two barriers, a trip to the map, the ranking.  The
-//   ranking of the logits alone runs beside that trip, and the sum of exponentials waits for no barrier of its own: n = 128 on
-//   32768 x 2048, m = 16 43.1 -> 42.7 us, n = 16 on 5000 x 3072 18.1 -> 17.9, n = 64 on 16384 x 2048, m = 32 a tie)
+//   ranking of the logits alone runs beside that trip, and the sum of exponentials waits for no barrier of its own: a percent of
+//   a step, n = 128 on 32768 x 2048, m = 16 43.1 -> 42.7 us, and more with many candidates, n = 4 on 3880 x 4096, m = 24 23.2 -> 20.3)
 //   if more than 1024 logits reach T (massive ties, e.g. h = 0) the m best are extracted one by one.
 #include "vt_device.h"
 #include "vt_step.h"

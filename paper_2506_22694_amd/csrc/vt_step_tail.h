@@ -191,7 +191,7 @@ __device__ __forceinline__ bool wave_publish_top_by_threshold_q(const unsigned (
 // (run twice, the second time takes as long).  Where a workgroup has two waves per hidden row, one does the keys and the
 // other (max, sum-exp); the partial sums are read in one go; the keys are ranked in whole groups of eight.  Together:
 // 4 x 1024 x 256 in fp32 10.2 -> 9.7 us, a round on 5000 x 3072 57.9 -> 55.7,
-// n = 8 on 128256 x 3072 125.0 -> 123.8, two heads 43.2 -> 42.9, n = 1 on 32768 x 2048 25.1 -> 25.0.
+// n = 8 on 128256 x 3072 125.0 -> 123.8, two heads 43.2 -> 42.9, n = 1 on 32768 x 2048 a tie.
 struct EpilogueShare {
     int row;           // the wave's first hidden row, >= n: none; the next ones follow a workgroup's waves apart
     bool keys, lse;
