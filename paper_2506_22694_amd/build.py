@@ -12,6 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvocabtrim.so")
+BIND = os.path.join(PKG, "_vt_bind.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -151,11 +152,32 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def build_binding(force: bool = False) -> str:
+    """The native part of the Python binding: host code against torch's headers, no GPU code in it."""
+    src = os.path.join(CSRC, "vt_bind.cpp")
+    if force or _stale(BIND, [src] + glob.glob(os.path.join(ROOT, "include", "*.h"))):
+        import sysconfig
+
+        import torch
+        from torch.utils.cpp_extension import include_paths
+        lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+        cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared",
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
+               *("-I" + p for p in include_paths()), "-I" + sysconfig.get_paths()["include"], src, "-o", BIND,
+               "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"{cmd[0]} failed on {src}:\n{r.stderr}")
+    return BIND
+
+
 def build_library(force: bool = False, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = _sources()
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
+        binding = ex.submit(build_binding, force)
         objs = list(ex.map(lambda s: _compile(s, force), srcs))
+        binding.result()
     if force or _stale(LIB, objs):
         r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs,
                            capture_output=True, text=True)

@@ -431,6 +431,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
                    hipStream_t st, const TreeFuse &tf);
 
 int pick_chunk(int n, int k, int d, int m, int dtype);
+int step_chunk(int n, int k, int d, int m, int dtype);      // the same, from what is kept of the last shapes
 
 // several heads' tiles in one launch (defined with the launch code below)
 constexpr int kNotFused = -1;
@@ -442,7 +443,7 @@ int run_step_heads_fused(const void *h, int n, int d, const void *const *W_trim,
 // All n rows of a validated step: consecutive launch groups of `chunk` rows on one workspace.
 int run_step_rows(const void *h, int n, const void *W_trim, int w_type, int k, int d, const int32_t *map, int m,
                   int32_t *out_ids, float *out_logp, float *out_lse, float *out_logp_full, void *ws, hipStream_t st) {
-    const int chunk = pick_chunk(n, k, d, m, w_type);
+    const int chunk = step_chunk(n, k, d, m, w_type);
     if (chunk == 0) return VT_ERR_SHAPE;
     const size_t row_bytes = (size_t)d * elem_size(w_type);
     for (int i0 = 0; i0 < n; i0 += chunk) {
@@ -546,6 +547,35 @@ int pick_chunk(int n, int k, int d, int m, int dtype) {
     }
     return 0;
 }
+
+// What a step of one shape comes to: the groups its rows run in, the workspace it asks for, the plan of a whole group.  A step is
+// asked three times and more -- size check, launch, and a program repeats its few shapes -- at 0.06 us a plan and eight plans a call,
+// so the last answers are kept per host thread.
+struct StepShape {
+    int n = 0, k = 0, d = 0, m = 0, dtype = -1;
+    int chunk = 0;
+    size_t ws_bytes = 0;
+    StepPlan plan;             // of `chunk` rows
+    bool is(int n_, int k_, int d_, int m_, int dtype_) const { return n == n_ && k == k_ && d == d_ && m == m_ && dtype == dtype_; }
+};
+const StepShape &step_shape(int n, int k, int d, int m, int dtype) {
+    constexpr unsigned kKept = 8;
+    static thread_local StepShape kept[kKept];
+    StepShape &s = kept[((unsigned)n * 7u + (unsigned)m * 3u + (unsigned)k + (unsigned)d / 128u + (unsigned)dtype) % kKept];
+    if (!s.is(n, k, d, m, dtype)) {
+        s.dtype = -1;
+        s.chunk = pick_chunk(n, k, d, m, dtype);
+        s.ws_bytes = step_ws_bytes(n, k, d, m);
+        s.plan = s.chunk != 0 ? plan_step(s.chunk, k, d, m, dtype) : StepPlan{};
+        s.n = n;
+        s.k = k;
+        s.d = d;
+        s.m = m;
+        s.dtype = dtype;
+    }
+    return s;
+}
+int step_chunk(int n, int k, int d, int m, int dtype) { return step_shape(n, k, d, m, dtype).chunk; }
 
 }  // namespace
 
@@ -740,9 +770,9 @@ int vt_draft_head_step(const void *h, int h_type, int32_t n, const void *W_trim,
         !aligned(out_ids, 4) || !aligned(out_logp, 4) || (out_lse && !aligned(out_lse, 4)) ||
         (out_logp_full && !aligned(out_logp_full, 4)))
         return VT_ERR_ALIGN;
-    if (pick_chunk(n, k, d, m, w_type) == 0) return VT_ERR_SHAPE;
-    if (ws == nullptr || !aligned(ws, 256) || ws_bytes < vt_draft_head_step_ws_bytes(n, k, d, m))
-        return VT_ERR_WORKSPACE;
+    const StepShape &shape = step_shape(n, k, d, m, w_type);
+    if (shape.chunk == 0) return VT_ERR_SHAPE;
+    if (ws == nullptr || !aligned(ws, 256) || ws_bytes < shape.ws_bytes) return VT_ERR_WORKSPACE;
     (void)hipGetLastError();
     const int rc = run_step_rows(h, n, W_trim, w_type, k, d, map, m, out_ids, out_logp, out_lse, out_logp_full, ws,
                                  static_cast<hipStream_t>(stream));
@@ -756,7 +786,7 @@ int vt_draft_head_step_static(const void *h, int h_type, int32_t n, const void *
     // the size check comes first and touches no device: a shape is either out of range altogether (0) or needs
     // more than the library's own array holds
     if (n <= 0 || k <= 0 || d <= 0 || m < 1) return VT_ERR_SHAPE;
-    const size_t need = vt_draft_head_step_ws_bytes(n, k, d, m);
+    const size_t need = step_shape(n, k, d, m, w_type).ws_bytes;
     if (need == 0) return VT_ERR_SHAPE;
     if (need > (size_t)VT_STATIC_WS_BYTES) return VT_ERR_WORKSPACE;
     void *ws = nullptr;
@@ -912,19 +942,20 @@ int vt_draft_tree_level(const void *h, int h_type, int32_t n, const void *W_trim
         !aligned(out_ids, 4) || !aligned(out_logp, 4) || !aligned(parent_cum, 4) || !aligned(out_parent, 4) ||
         !aligned(out_token, 4) || !aligned(out_cum, 4))
         return VT_ERR_ALIGN;
-    const int chunk = pick_chunk(n, k, d, m, w_type);
+    const StepShape &shape = step_shape(n, k, d, m, w_type);
+    const int chunk = shape.chunk;
     if (chunk == 0) return VT_ERR_SHAPE;
-    if (ws == nullptr || !aligned(ws, 256) || ws_bytes < vt_draft_head_step_ws_bytes(n, k, d, m))
-        return VT_ERR_WORKSPACE;
+    if (ws == nullptr || !aligned(ws, 256) || ws_bytes < shape.ws_bytes) return VT_ERR_WORKSPACE;
     (void)hipGetLastError();
     hipStream_t st = static_cast<hipStream_t>(stream);
     // one launch when the small-n kernel covers the whole step: its last workgroup also ranks the candidates
     // (the same kernel as vt_draft_head_step would use for this shape, so both calls return the same bits)
     // ... or, on the matrix-core path, when its merge kernel (one workgroup per hidden row) covers all rows: the
     // workgroup that finishes last ranks the candidates
-    const StepPlan small = plan_step(n, k, d, m, w_type);
+    // (rows in several groups: no plan covers them all)
+    const StepPlan small = chunk >= n ? shape.plan : StepPlan{};
     const bool fuse_gemv = small.ok && small.gemv && n * m <= vt::kStepWaves * 64;
-    const bool fuse_mfma = small.ok && small.mfma && !small.row_select && chunk >= n && n * m <= vt::kFinalizeTreeMaxN;
+    const bool fuse_mfma = small.ok && small.mfma && !small.row_select && n * m <= vt::kFinalizeTreeMaxN;
     if (fuse_gemv || fuse_mfma) {
         TreeFuse tf;
         tf.cum = parent_cum;
@@ -1046,8 +1077,9 @@ int run_step_heads_fused(const void *h, int n, int d, const void *const *W_trim,
 int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, int d, const int32_t *map, int m,
                    int32_t *out_ids, float *out_logp, float *out_lse, float *out_logp_full, void *ws,
                    hipStream_t st, const TreeFuse &tf) {
-    const StepPlan p = plan_step(n, k, d, m, w_type);
-    if (!p.ok) return VT_ERR_SHAPE;
+    const StepShape &shape = step_shape(n, k, d, m, w_type);
+    if (shape.chunk != n) return VT_ERR_SHAPE;
+    const StepPlan p = shape.plan;
     char *wsb = static_cast<char *>(ws);
     unsigned long long *pms = reinterpret_cast<unsigned long long *>(wsb + p.off_pms);
     unsigned long long *pkeys = reinterpret_cast<unsigned long long *>(wsb + p.off_pkeys);
