@@ -181,6 +181,10 @@ size_t vt_choose_k_ws_bytes(int32_t V);
  *                  need no initialisation, before the first step or between
  *                  steps, whatever their shapes (as long as the size suffices)
  *                  and whatever an earlier step that never completed left behind.
+ *                  Less is accepted down to what earlier versions asked for: a step
+ *                  of more than 8 rows on a head of few rows then keeps lists of
+ *                  candidates instead of (partial) logits, which is slower, and its
+ *                  logits may round differently in the last bits.
  * ---------------------------------------------------------------------- */
 int vt_draft_head_step(const void *h, int h_type, int32_t n, const void *W_trim, int w_type,
                        int32_t k, int32_t d, const int32_t *map, int32_t m, int32_t *out_ids,
@@ -203,10 +207,12 @@ int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_ty
  * results (bit for bit) and errors as for vt_draft_head_step, without ws /
  * ws_bytes: the partial results of the step live in an array of
  * VT_STATIC_WS_BYTES bytes that the library itself holds on every GPU it runs
- * on, from the first use of the library on that GPU until the process ends.
+ * on, from the first use of the library on that GPU until the process ends
+ * (the partial logits of steps of more than 8 rows on heads of few rows, which
+ * vt_draft_head_step cuts into slices of the columns, in another one of 48 MiB).
  * The call allocates and frees nothing (its first call on a device asks the
  * runtime for the array's address; make that call outside stream capture).
- *   - A shape whose vt_draft_head_step_ws_bytes(n, k, d, m) exceeds
+ *   - A shape for which vt_draft_head_step accepts no workspace of
  *     VT_STATIC_WS_BYTES returns VT_ERR_WORKSPACE and enqueues nothing (for
  *     example n = 256 rows with 16 tokens per row at k = 32768, whose per-row
  *     tail stores 32 MiB of logits); the paper's shapes (up to 64 tree nodes x
@@ -321,7 +327,8 @@ int vt_tree_rerank(const float *cum, int32_t N, int32_t T, int32_t *out_idx, voi
  * step for the n frontier nodes followed by vt_tree_expand on its result,
  * with the same outputs as the two calls (bit for bit).  Where one kernel of
  * the step sees every row's result (always for n <= 8; up to 64 rows and
- * n * m <= 512 on the bf16 matrix-core path) no launch is added: the
+ * n * m <= 512 on the bf16 matrix-core path, unless the step stores logits:
+ * more than 8 tokens per row, heads of few long rows) no launch is added: the
  * workgroup that finishes the step last also ranks the n * m candidates;
  * other shapes run the step and then the expansion kernel.
  *   arguments as in vt_draft_head_step (no out_lse / out_logp_full) and

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
+#include <cstring>
 #include <mutex>
 
 #include "vt_build.h"
@@ -32,23 +33,28 @@ inline int launch_status() { return device_status(hipGetLastError()); }
 // GPU, alive from the moment the code object is loaded on it until the process ends.  In host code the array's
 // name is only a handle; the device address is asked for once per device and kept.
 static __device__ __align__(256) unsigned char scratch[VT_STATIC_WS_BYTES];
+// ... and of the steps that plan_stored() has run by slices, which have the bits of vt_draft_head_step's only if they run the same
+// way: 256 hidden rows by 256 tiles of 160 logits, 4 MiB of re-laid h and the small parts of a workspace at most.
+constexpr size_t kStaticStoredBytes = (size_t)48 << 20;
+static __device__ __align__(256) unsigned char stored_scratch[kStaticStoredBytes];
 std::mutex g_scratch_mutex;
-void *g_scratch_ptr[64] = {};      // per device ordinal; written under the mutex, never changed afterwards
+void *g_scratch_ptr[2][64] = {};      // per device ordinal; written under the mutex, never changed afterwards
 
-int static_scratch_of_current_device(void **out) {
+int static_scratch_of_current_device(bool stored, void **out) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return device_status(e);
     if (dev < 0 || dev >= 64) return device_status(hipErrorInvalidDevice);
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    if (g_scratch_ptr[dev] == nullptr) {
+    void *&known = g_scratch_ptr[stored ? 1 : 0][dev];
+    if (known == nullptr) {
         void *p = nullptr;
-        e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        e = stored ? hipGetSymbolAddress(&p, HIP_SYMBOL(stored_scratch)) : hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return device_status(e);
         if (p == nullptr) return device_status(hipErrorInvalidSymbol);
-        g_scratch_ptr[dev] = p;
+        known = p;
     }
-    *out = g_scratch_ptr[dev];
+    *out = known;
     return VT_OK;
 }
 
@@ -87,10 +93,12 @@ struct StepPlan {
     int row_groups = 0, ids_off = 0, passes = 1;
     bool twin = false;
     bool wide = false;         // more than 64 hidden rows
+    int splits = 1;            // more than 8 hidden rows: slices of the columns, a workgroup each per tile
     size_t list_room = 0;      // ... bytes that the lists of fewer hidden rows may take on smaller tiles
 };
 
 using vt::kTicketBytes;
+int slice_pitch(int k) { return (k + 3) / 4 * 4; }      // floats from one hidden row's partial logits to the next one's
 
 // fixed: a tile shape the caller has chosen (several heads in one launch): waves, column split, number of tiles
 struct FixedTiles {
@@ -107,12 +115,38 @@ struct FixedTiles {
 bool stores_logits(int n, int m, int tile_rows) {
     return m > vt::kRowSelectMinLManyRows || (n * m >= vt::kRowSelectMinWork && tile_rows < vt::kMfmaTileRows);
 }
+// What follows from a tile's row groups (and extra rows, kernel, slices): waves, LDS, number of workgroups.
+void cut_many_rows(StepPlan &p, int n, int k, int m) {
+    size_t ring, tile;                                // LDS: the stages; the logit tile and the candidate keys after them
+    p.passes = 1;
+    if (!p.wide) {
+        p.nwaves = p.row_groups <= 4 ? vt::kStepWaves : p.row_groups;
+        const int rows_in_lds = 16 * (p.row_groups + (p.extra_rows != 0 ? 1 : 0));
+        ring = vt::rows_ring_bytes(p.NT, p.row_groups, p.extra_rows != 0, p.twin);
+        tile = round_up((size_t)n * (rows_in_lds + 1) * sizeof(float), 16);
+    } else {
+        const int MT = p.row_groups / 2, NTT = p.NT / 4;
+        p.nwaves = vt::kStepWaves;
+        ring = vt::wide_ring_bytes(MT, NTT);
+        tile = round_up((size_t)n * (32 * MT + 1) * sizeof(float), 16);
+        if (tile + vt::kStepWaves * 512 > (size_t)vt::kMaxDynamicLds - 1024) {
+            p.passes = 2;
+            tile = round_up((size_t)32 * NTT * (32 * MT + 1) * sizeof(float), 16);
+        }
+    }
+    const int tile_rows = 16 * p.row_groups + p.extra_rows;
+    p.mfma = true;
+    p.nlists = p.nblocks = (k + tile_rows - 1) / tile_rows * p.splits;
+    p.L = m < tile_rows ? m : tile_rows;
+    tile += (size_t)p.nwaves * 64 * sizeof(unsigned long long);      // 4 x 16 candidate keys per wave
+    p.ids_off = (int)round_up(ring > tile ? ring : tile, 16);
+    p.lds = (size_t)p.ids_off + vt::kMfmaMaxWaves * 16 * sizeof(int);
+}
 // More than 8 hidden rows, bf16: how the head is cut into tiles (kernel variant, LDS, number of tiles).
 void plan_many_rows(StepPlan &p, int n, int k, int d, int m) {
     const int CUS = round_workgroups();
     const int R = (k + CUS - 1) / CUS;                // rows per tile for one tile per CU
     const int G = (R + 15) / 16;                      // ... in 16-row groups
-    size_t ring, tile;                                // LDS: the stages; the logit tile and the candidate keys after them
     // Microseconds of `rounds` rounds of tiles of `rows` rows, roughly: W at a CU's share of the HBM rate, h from the L2,
     // and about 7 us for a round's first loads and its epilogue.
     const int n_padded = n <= 32 ? 32 : n <= vt::kRowsKernelMaxN ? vt::kRowsKernelMaxN : vt::kMfmaMaxN;
@@ -145,10 +179,6 @@ void plan_many_rows(StepPlan &p, int n, int k, int d, int m) {
             p.twin = paired <= cost(16 * p.row_groups);
             if (p.twin) p.row_groups = vt::kStepWaves;
         }
-        p.nwaves = p.row_groups <= 4 ? vt::kStepWaves : p.row_groups;
-        const int rows_in_lds = 16 * (p.row_groups + (p.extra_rows != 0 ? 1 : 0));
-        ring = vt::rows_ring_bytes(NT, p.row_groups, p.extra_rows != 0, p.twin);
-        tile = round_up((size_t)n * (rows_in_lds + 1) * sizeof(float), 16);
     } else {
         const int NTT = n <= 128 ? 2 : n <= 192 ? 3 : 4;
         p.wide = true;
@@ -166,21 +196,8 @@ void plan_many_rows(StepPlan &p, int n, int k, int d, int m) {
         for (int x : {1, 2, 3, 5})
             if (!fits(32 * x) && cost(32 * x) <= cost(32 * MT)) p.list_room = (size_t)VT_STATIC_WS_BYTES - 65536;
         p.row_groups = 2 * MT;
-        p.nwaves = vt::kStepWaves;
-        ring = vt::wide_ring_bytes(MT, NTT);
-        tile = round_up((size_t)n * (32 * MT + 1) * sizeof(float), 16);
-        if (tile + vt::kStepWaves * 512 > (size_t)vt::kMaxDynamicLds - 1024) {
-            p.passes = 2;
-            tile = round_up((size_t)32 * NTT * (32 * MT + 1) * sizeof(float), 16);
-        }
     }
-    const int tile_rows = 16 * p.row_groups + p.extra_rows;
-    p.mfma = true;
-    p.nlists = p.nblocks = (k + tile_rows - 1) / tile_rows;
-    p.L = m < tile_rows ? m : tile_rows;
-    tile += (size_t)p.nwaves * 64 * sizeof(unsigned long long);      // 4 x 16 candidate keys per wave
-    p.ids_off = (int)round_up(ring > tile ? ring : tile, 16);
-    p.lds = (size_t)p.ids_off + vt::kMfmaMaxWaves * 16 * sizeof(int);
+    cut_many_rows(p, n, k, m);
 }
 StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, const FixedTiles &fixed = FixedTiles{});
 // force_gemv: the caller needs what only the small-n kernel offers (row picking, the fused tree level)
@@ -411,6 +428,62 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
     return p;
 }
 
+// The same step with its logits stored, and the columns cut into slices where that pays: larger tiles then (each hidden row is
+// read once per tile, so small tiles of many hidden rows are bound by reading h), a workgroup per tile and slice, and
+// row_select_kernel adds the partial logits up.  ok = false: the plan itself is the better one.
+// The costs are microseconds, fitted to 945 shapes (n = 16 .. 256, k = 4300 .. 20000, d = 1024 .. 8192, m = 4, 8, 16; 5 %
+// off on average): W at a CU's share of the HBM rate, h from the L2, and the tail.  Two slices gain least and are the first to
+// lose on another card.  Up to 64 rows a tree level is fused behind the merge of lists, which stored logits give up: there
+// the slices have to gain what its launch costs.  Measured (us, plan / slices): n = 224, k = 4300, d = 8192 81.9 / 36.5,
+// k = 10000, d = 4096 54.7 / 39.3, n = 160, k = 6500, d = 4096 40.7 / 30.2, n = 100, k = 4300, d = 2048 21.9 / 18.2, n = 64, k = 4300,
+// d = 4096 24.1 / 18.8; what the rule leaves: n = 100, k = 14000, d = 4096 37.1 / 39.3, n = 32, k = 10000, d = 4096 22.9 / 24.9.
+// Up to d = 8192, the longest rows measured.
+StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
+    StepPlan p = whole;
+    p.ok = false;
+    if (!whole.ok || !whole.mfma || n <= vt::kGemvMaxN || k > vt::kRowSelectWhole || d > 8192) return p;
+    const int CUS = round_workgroups();
+    const bool few = n <= vt::kRowsKernelMaxN;
+    const int hrows = whole.wide ? 16 * whole.NT : whole.NT * 16;      // hidden rows of the tiles
+    const int rows = 16 * whole.row_groups + whole.extra_rows, rounds = (whole.nlists + CUS - 1) / CUS;
+    const double as_planned = 9.0 + rounds * ((double)rows * d / 18e3 + (double)hrows * d / 38e3) +
+                              (whole.row_select ? k * (2.2e-6 * n + 3.5e-5) : rounds * 0.03 * n - 0.6);
+    double best = as_planned;
+    for (int g : {4, 8, 10}) {
+        if (few && g > 8) continue;
+        const int tiles = (k + 16 * g - 1) / (16 * g), S = CUS / tiles;
+        if (S < (few ? 4 : g > 8 ? 3 : 2) || d / 128 < 2 * S) continue;
+        const double t = 10.3 + (double)16 * g * d / S / 19e3 + (double)hrows * d / S / 34e3 + (double)S * k * (1.8e-6 * n + 6.5e-5);
+        if (t < best && t < (S == 2 ? 0.90 : 0.93) * as_planned && (!few || t < as_planned - 4.0)) {
+            best = t;
+            p.row_groups = g;
+            p.splits = S;
+        }
+    }
+    if (p.splits > 1) {
+        p.extra_rows = 0;
+        p.twin = false;
+    } else if (few || whole.row_select || rows >= vt::kMfmaTileRows || n * m < 256 || (double)n * (m * m / 2 + 12) * 34e3 < (double)k * k) {
+        return p;
+    }
+    // (in one piece: lists of more than 64 hidden rows cost a tile 6 to 10 us, the logits of small heads less.  n = 256 / 128, lists / stored:
+    // k = 4300, m = 8 29.5 / 25.4 and 20.0 / 18.2 us on average of d = 1024, 2048 and 4096; k = 10000, m = 8 -7 and -4 %, m = 4 -4 and +2 %)
+    p.row_select = true;
+    p.list_room = 0;
+    cut_many_rows(p, n, k, m);
+    size_t off = round_up(p.off_lse + (size_t)n * sizeof(float), 256);
+    p.off_zbuf = off;
+    off = round_up(off + (size_t)p.splits * n * slice_pitch(k) * sizeof(float), 256);
+    p.off_hpack = 0;
+    if (p.wide && vt::packs_h(p.NT / 4, n, d)) {
+        p.off_hpack = off;
+        off = round_up(off + (size_t)d * p.NT * 32, 256);
+    }
+    p.bytes = off;
+    p.ok = p.lds <= (size_t)vt::kMaxDynamicLds;
+    return p;
+}
+
 // Hidden rows handled per launch group.  A step whose n no single plan covers (more than 256 rows; more
 // than 8 rows in fp32 or with d not a multiple of 128; very long fp32 rows) runs as consecutive groups
 // of `chunk` rows, each streaming W_trim again -- slower, but every shape has an answer.
@@ -427,7 +500,7 @@ struct TreeFuse {
     int indexed = 0;
 };
 int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, int d, const int32_t *map, int m,
-                   int32_t *out_ids, float *out_logp, float *out_lse, float *out_logp_full, void *ws,
+                   int32_t *out_ids, float *out_logp, float *out_lse, float *out_logp_full, void *ws, size_t ws_bytes,
                    hipStream_t st, const TreeFuse &tf);
 
 int pick_chunk(int n, int k, int d, int m, int dtype);
@@ -442,7 +515,7 @@ int run_step_heads_fused(const void *h, int n, int d, const void *const *W_trim,
 
 // All n rows of a validated step: consecutive launch groups of `chunk` rows on one workspace.
 int run_step_rows(const void *h, int n, const void *W_trim, int w_type, int k, int d, const int32_t *map, int m,
-                  int32_t *out_ids, float *out_logp, float *out_lse, float *out_logp_full, void *ws, hipStream_t st) {
+                  int32_t *out_ids, float *out_logp, float *out_lse, float *out_logp_full, void *ws, size_t ws_bytes, hipStream_t st) {
     const int chunk = step_chunk(n, k, d, m, w_type);
     if (chunk == 0) return VT_ERR_SHAPE;
     const size_t row_bytes = (size_t)d * elem_size(w_type);
@@ -451,7 +524,7 @@ int run_step_rows(const void *h, int n, const void *W_trim, int w_type, int k, i
         const int rc = run_step_group(static_cast<const char *>(h) + (size_t)i0 * row_bytes, nc, W_trim, w_type, k, d, map,
                                       m, out_ids + (size_t)i0 * m, out_logp + (size_t)i0 * m,
                                       out_lse ? out_lse + i0 : nullptr,
-                                      out_logp_full ? out_logp_full + (size_t)i0 * k : nullptr, ws, st, TreeFuse{});
+                                      out_logp_full ? out_logp_full + (size_t)i0 * k : nullptr, ws, ws_bytes, st, TreeFuse{});
         if (rc != VT_OK) return rc;
     }
     return VT_OK;
@@ -481,19 +554,32 @@ size_t step_ws_bytes(int n, int k, int d, int m) {
     return b;
 }
 
+// The same with room for plan_stored()'s plans: of n rows and, at the ends of the kernels' ranges, of fewer.  What a program asks for;
+// a step accepts step_ws_bytes(), the size that earlier versions returned.
+size_t full_step_ws_bytes(int n, int k, int d, int m) {
+    size_t b = step_ws_bytes(n, k, d, m);
+    for (int r : {32, 64, 128, 192, 256, n > vt::kMfmaMaxN ? n % vt::kMfmaMaxN : n}) {
+        if (b == 0 || r < 1 || r > n) continue;
+        const StepPlan p = plan_stored(plan_step(r, k, d, m, VT_BF16), r, k, d, m);
+        if (p.ok && p.bytes > b) b = p.bytes;
+    }
+    return b;
+}
+
 // Layout of a multi-head workspace: the step workspace first, then the staged hidden rows and the staged results
 // of one head's rows.
 struct MultiLayout {
     size_t off_h = 0, off_ids = 0, off_logp = 0, off_lse = 0, bytes = 0;
 };
-MultiLayout multi_layout(int n, int d, const int32_t *k, int n_heads, int m) {
+MultiLayout multi_layout(int n, int d, const int32_t *k, int n_heads, int m, bool full) {
     // consecutive steps repeat their shapes: the last answer is kept per host thread
     struct Key {
         int n = 0, d = 0, m = 0, n_heads = 0;
         int32_t k[VT_MAX_HEADS] = {};
         MultiLayout L;
     };
-    static thread_local Key last;
+    static thread_local Key kept[2];
+    Key &last = kept[full ? 1 : 0];
     if (last.n == n && last.d == d && last.m == m && last.n_heads == n_heads) {
         bool same = true;
         for (int hd = 0; hd < n_heads; ++hd) same = same && last.k[hd] == k[hd];
@@ -504,7 +590,7 @@ MultiLayout multi_layout(int n, int d, const int32_t *k, int n_heads, int m) {
     for (int hd = 0; hd < n_heads; ++hd) {
         // a head may receive any number of the n rows, and the plan (hence its workspace) changes with it
         for (int nn = 1; nn <= n; ++nn) {
-            const size_t b = step_ws_bytes(nn, k[hd], d, m);
+            const size_t b = full ? full_step_ws_bytes(nn, k[hd], d, m) : step_ws_bytes(nn, k[hd], d, m);
             if (b > step) step = b;
         }
     }
@@ -554,9 +640,10 @@ int pick_chunk(int n, int k, int d, int m, int dtype) {
 struct StepShape {
     int n = 0, k = 0, d = 0, m = 0, dtype = -1;
     int chunk = 0;
-    size_t ws_bytes = 0;
-    StepPlan plan;             // of `chunk` rows
+    size_t ws_bytes = 0;       // that a step asks for; with more it may run as plan_stored() has it
+    StepPlan plan, stored;     // of `chunk` rows
     bool is(int n_, int k_, int d_, int m_, int dtype_) const { return n == n_ && k == k_ && d == d_ && m == m_ && dtype == dtype_; }
+    const StepPlan &with(size_t bytes) const { return stored.ok && stored.bytes <= bytes ? stored : plan; }
 };
 const StepShape &step_shape(int n, int k, int d, int m, int dtype) {
     constexpr unsigned kKept = 8;
@@ -567,6 +654,7 @@ const StepShape &step_shape(int n, int k, int d, int m, int dtype) {
         s.chunk = pick_chunk(n, k, d, m, dtype);
         s.ws_bytes = step_ws_bytes(n, k, d, m);
         s.plan = s.chunk != 0 ? plan_step(s.chunk, k, d, m, dtype) : StepPlan{};
+        s.stored = plan_stored(s.plan, s.chunk, k, d, m);
         s.n = n;
         s.k = k;
         s.d = d;
@@ -686,7 +774,7 @@ int vt_choose_k(const int64_t *counts, int32_t V, int mode, double p, int64_t mi
 
 // ------------------------------------------------------------------ Algorithm 2, drafting lines
 size_t vt_draft_head_step_ws_bytes(int32_t n, int32_t k, int32_t d, int32_t m) {
-    return step_ws_bytes(n, k, d, m);      // sized for either element type
+    return full_step_ws_bytes(n, k, d, m);      // sized for either element type
 }
 
 int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_type, char *text, size_t text_bytes) {
@@ -695,15 +783,20 @@ int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_ty
     if (text == nullptr || text_bytes == 0) return VT_ERR_NULL;
     const int chunk = pick_chunk(n, k, d, m, w_type);
     if (chunk == 0) return VT_ERR_SHAPE;
-    const StepPlan p = plan_step(chunk, k, d, m, w_type);
+    StepPlan p = plan_step(chunk, k, d, m, w_type);
     if (!p.ok) return VT_ERR_SHAPE;
+    // (with a workspace of vt_draft_head_step_ws_bytes)
+    const StepPlan stored = plan_stored(p, chunk, k, d, m);
+    if (stored.ok) p = stored;
     char head[160];
     if (p.gemv) {
         std::snprintf(head, sizeof head, "head_gemv_kernel<%s,%d,%d> workgroups=%d rows_per_workgroup=%d column_segments=%d",
                       w_type == VT_BF16 ? "bf16" : "f32", p.NP, p.CS, p.nblocks, p.rpb, p.S);
     } else if (p.wide) {
-        std::snprintf(head, sizeof head, "%shead_mfma_wide_kernel<%d> workgroups=%d tile_rows=%d",
-                      p.off_hpack != 0 ? "pack_h_kernel + " : "", p.NT <= 8 ? 1 : 2, p.nlists, 16 * p.row_groups);
+        char by_slices[32] = "";
+        if (p.splits > 1) std::snprintf(by_slices, sizeof by_slices, " column_slices=%d", p.splits);
+        std::snprintf(head, sizeof head, "%shead_mfma_wide_kernel<%d> workgroups=%d tile_rows=%d%s",
+                      p.off_hpack != 0 ? "pack_h_kernel + " : "", p.NT <= 8 ? 1 : 2, p.nlists, 16 * p.row_groups, by_slices);
     } else {
         // (the second template argument: the most waves of the instantiation)
         std::snprintf(head, sizeof head, "head_mfma_kernel<%d,%d> workgroups=%d tile_rows=%d waves=%d column_split=%d%s", p.NT,
@@ -711,6 +804,7 @@ int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_ty
                       : p.NT > 1 && p.nwaves <= vt::kMfmaFewWaves ? vt::kMfmaFewWaves
                                                                          : vt::kMfmaMaxWaves,
                       p.nlists, 16 * p.row_groups + p.extra_rows, p.nwaves, p.ksplit, p.twin ? " workgroups_per_cu=2" : "");
+        if (p.splits > 1) std::snprintf(head + std::strlen(head), sizeof head - std::strlen(head), " column_slices=%d", p.splits);
     }
     const char *tail = p.row_select ? " + row_select_kernel" : " + step_finalize_kernel";
     char groups[48] = "";
@@ -774,7 +868,7 @@ int vt_draft_head_step(const void *h, int h_type, int32_t n, const void *W_trim,
     if (shape.chunk == 0) return VT_ERR_SHAPE;
     if (ws == nullptr || !aligned(ws, 256) || ws_bytes < shape.ws_bytes) return VT_ERR_WORKSPACE;
     (void)hipGetLastError();
-    const int rc = run_step_rows(h, n, W_trim, w_type, k, d, map, m, out_ids, out_logp, out_lse, out_logp_full, ws,
+    const int rc = run_step_rows(h, n, W_trim, w_type, k, d, map, m, out_ids, out_logp, out_lse, out_logp_full, ws, ws_bytes,
                                  static_cast<hipStream_t>(stream));
     if (rc != VT_OK) return rc;
     return launch_status();
@@ -786,16 +880,17 @@ int vt_draft_head_step_static(const void *h, int h_type, int32_t n, const void *
     // the size check comes first and touches no device: a shape is either out of range altogether (0) or needs
     // more than the library's own array holds
     if (n <= 0 || k <= 0 || d <= 0 || m < 1) return VT_ERR_SHAPE;
-    const size_t need = step_shape(n, k, d, m, w_type).ws_bytes;
-    if (need == 0) return VT_ERR_SHAPE;
-    if (need > (size_t)VT_STATIC_WS_BYTES) return VT_ERR_WORKSPACE;
+    const StepShape &shape = step_shape(n, k, d, m, w_type);
+    if (shape.ws_bytes == 0) return VT_ERR_SHAPE;
+    if (shape.ws_bytes > (size_t)VT_STATIC_WS_BYTES) return VT_ERR_WORKSPACE;
+    const bool stored = shape.stored.ok && shape.stored.bytes > (size_t)VT_STATIC_WS_BYTES && shape.stored.bytes <= kStaticStoredBytes;
     void *ws = nullptr;
-    const int rc = static_scratch_of_current_device(&ws);
+    const int rc = static_scratch_of_current_device(stored, &ws);
     if (rc != VT_OK) return rc;
     // Nothing has to be cleared here: a step rewrites everything it reads in the array before it reads it (the
     // one counted word, the ticket of a fused tree level, is zeroed by the kernel that runs before its user).
     return vt_draft_head_step(h, h_type, n, W_trim, w_type, k, d, map, m, out_ids, out_logp, out_lse, out_logp_full,
-                              ws, (size_t)VT_STATIC_WS_BYTES, stream);
+                              ws, stored ? kStaticStoredBytes : (size_t)VT_STATIC_WS_BYTES, stream);
 }
 
 // ------------------------------------------------------------------ several heads in one step
@@ -805,7 +900,7 @@ size_t vt_draft_head_step_multi_ws_bytes(int32_t n, int32_t d, const int32_t *k,
     for (int hd = 0; hd < n_heads; ++hd) {
         if (k[hd] < 1 || k[hd] > vt::kStepMaxK) return 0;
     }
-    return multi_layout(n, d, k, n_heads, m).bytes;
+    return multi_layout(n, d, k, n_heads, m, true).bytes;
 }
 
 int vt_draft_head_step_multi(const void *h, int h_type, int32_t n, int32_t d, const void *const *W_trim, int w_type,
@@ -838,7 +933,9 @@ int vt_draft_head_step_multi(const void *h, int h_type, int32_t n, int32_t d, co
         if (!aligned(W_trim[hd], 16) || !aligned(map[hd], 4)) return VT_ERR_ALIGN;
         if (pick_chunk(rows[hd].n, k[hd], d, m, w_type) == 0) return VT_ERR_SHAPE;
     }
-    const MultiLayout L = multi_layout(n, d, k, n_heads, m);
+    // (sizes that earlier versions returned have no room for plan_stored()'s plans)
+    MultiLayout L = multi_layout(n, d, k, n_heads, m, true);
+    if (ws_bytes < L.bytes) L = multi_layout(n, d, k, n_heads, m, false);
     if (ws == nullptr || !aligned(ws, 256) || ws_bytes < L.bytes) return VT_ERR_WORKSPACE;
     (void)hipGetLastError();
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -857,7 +954,7 @@ int vt_draft_head_step_multi(const void *h, int h_type, int32_t n, int32_t d, co
             // the head's rows lie next to each other in h: the step reads and writes them in place
             const int rc = run_step_rows(static_cast<const char *>(h) + (size_t)first * row_bytes, R.n, W_trim[hd], w_type,
                                          k[hd], d, map[hd], m, out_ids + (size_t)first * m, out_logp + (size_t)first * m,
-                                         out_lse ? out_lse + first : nullptr, nullptr, ws, st);
+                                         out_lse ? out_lse + first : nullptr, nullptr, ws, L.off_h, st);
             if (rc != VT_OK) return rc;
             continue;
         }
@@ -868,7 +965,7 @@ int vt_draft_head_step_multi(const void *h, int h_type, int32_t n, int32_t d, co
             pick.indexed = 1;
             for (int i = 0; i < R.n; ++i) pick.row_pack |= (unsigned long long)(R.idx[i] & 0xFF) << (8 * i);
             const int rc = run_step_group(h, R.n, W_trim[hd], w_type, k[hd], d, map[hd], m, out_ids, out_logp, out_lse,
-                                          nullptr, ws, st, pick);
+                                          nullptr, ws, L.off_h, st, pick);
             if (rc != VT_OK) return rc;
             continue;
         }
@@ -877,7 +974,7 @@ int vt_draft_head_step_multi(const void *h, int h_type, int32_t n, int32_t d, co
         float *lse_s = reinterpret_cast<float *>(wsb + L.off_lse);
         vt::launch_gather_h_rows(h, wsb + L.off_h, row_bytes, R, st);
         const int rc = run_step_rows(wsb + L.off_h, R.n, W_trim[hd], w_type, k[hd], d, map[hd], m, ids_s, logp_s, lse_s,
-                                     nullptr, ws, st);
+                                     nullptr, ws, L.off_h, st);
         if (rc != VT_OK) return rc;
         vt::launch_scatter_rows(ids_s, logp_s, lse_s, m, out_ids, out_logp, out_lse, R, st);
     }
@@ -953,7 +1050,7 @@ int vt_draft_tree_level(const void *h, int h_type, int32_t n, const void *W_trim
     // ... or, on the matrix-core path, when its merge kernel (one workgroup per hidden row) covers all rows: the
     // workgroup that finishes last ranks the candidates
     // (rows in several groups: no plan covers them all)
-    const StepPlan small = chunk >= n ? shape.plan : StepPlan{};
+    const StepPlan small = chunk >= n ? shape.with(ws_bytes) : StepPlan{};
     const bool fuse_gemv = small.ok && small.gemv && n * m <= vt::kStepWaves * 64;
     const bool fuse_mfma = small.ok && small.mfma && !small.row_select && n * m <= vt::kFinalizeTreeMaxN;
     if (fuse_gemv || fuse_mfma) {
@@ -963,14 +1060,14 @@ int vt_draft_tree_level(const void *h, int h_type, int32_t n, const void *W_trim
         tf.parent = out_parent;
         tf.token = out_token;
         tf.score = out_cum;
-        const int rc = run_step_group(h, n, W_trim, w_type, k, d, map, m, out_ids, out_logp, nullptr, nullptr, ws, st, tf);
+        const int rc = run_step_group(h, n, W_trim, w_type, k, d, map, m, out_ids, out_logp, nullptr, nullptr, ws, ws_bytes, st, tf);
         if (rc != VT_OK) return rc;
         return launch_status();
     }
     for (int i0 = 0; i0 < n; i0 += chunk) {
         const int nc = n - i0 < chunk ? n - i0 : chunk;
         const int rc = run_step_group(static_cast<const char *>(h) + (size_t)i0 * row_bytes, nc, W_trim, w_type, k, d, map,
-                                      m, out_ids + (size_t)i0 * m, out_logp + (size_t)i0 * m, nullptr, nullptr, ws, st,
+                                      m, out_ids + (size_t)i0 * m, out_logp + (size_t)i0 * m, nullptr, nullptr, ws, ws_bytes, st,
                                       TreeFuse{});
         if (rc != VT_OK) return rc;
     }
@@ -1075,11 +1172,11 @@ int run_step_heads_fused(const void *h, int n, int d, const void *const *W_trim,
 }
 
 int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, int d, const int32_t *map, int m,
-                   int32_t *out_ids, float *out_logp, float *out_lse, float *out_logp_full, void *ws,
+                   int32_t *out_ids, float *out_logp, float *out_lse, float *out_logp_full, void *ws, size_t ws_bytes,
                    hipStream_t st, const TreeFuse &tf) {
     const StepShape &shape = step_shape(n, k, d, m, w_type);
     if (shape.chunk != n) return VT_ERR_SHAPE;
-    const StepPlan p = shape.plan;
+    const StepPlan p = shape.with(ws_bytes);
     char *wsb = static_cast<char *>(ws);
     unsigned long long *pms = reinterpret_cast<unsigned long long *>(wsb + p.off_pms);
     unsigned long long *pkeys = reinterpret_cast<unsigned long long *>(wsb + p.off_pkeys);
@@ -1144,7 +1241,8 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
             if (e != hipSuccess) return device_status(e);
         }
         if (p.row_select) {
-            vt::launch_row_select(a.zbuf, map, n, k, m, out_ids, out_logp, out_lse, lse_buf, st);
+            const hipError_t e = vt::launch_row_select(a.zbuf, map, n, k, m, 1, k, nullptr, out_ids, out_logp, out_lse, lse_buf, st);
+            if (e != hipSuccess) return device_status(e);
             if (out_logp_full != nullptr) vt::launch_sub_lse(out_logp_full, lse_buf, n, k, st);
             if (tf.cum != nullptr) {       // the fused tree level needs the merge kernel: run the expansion kernel
                 vt::TreeArgs t;
@@ -1185,7 +1283,13 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         a.out_logp_full = out_logp_full;
         a.hpack = p.off_hpack != 0 ? static_cast<void *>(wsb + p.off_hpack) : nullptr;
         a.zbuf = nullptr;
-        if (p.row_select) a.zbuf = out_logp_full != nullptr ? out_logp_full : reinterpret_cast<float *>(wsb + p.off_zbuf);
+        a.splits = p.splits;
+        a.slice_units = d / 128 / p.splits;
+        a.slice_more = d / 128 % p.splits;
+        a.slice_ranges = d % (2048 * p.splits) == 0 ? 1 : 0;
+        a.zpitch = p.splits > 1 ? slice_pitch(k) : k;
+        if (p.row_select) a.zbuf = out_logp_full != nullptr && p.splits == 1 ? out_logp_full : reinterpret_cast<float *>(wsb + p.off_zbuf);
+        a.zvec = a.zpitch % 4 == 0 && aligned(a.zbuf, 16) ? 1 : 0;
         a.row_pack = tf.row_pack;
         a.indexed = tf.indexed;
         a.ksplit = p.ksplit;
@@ -1201,7 +1305,8 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
                                           : vt::launch_head_mfma_rows(p.NT, a, p.lds, st);
         if (e != hipSuccess) return device_status(e);
         if (p.row_select) {
-            vt::launch_row_select(a.zbuf, map, n, k, m, out_ids, out_logp, out_lse, lse_buf, st);
+            e = vt::launch_row_select(a.zbuf, map, n, k, m, a.splits, a.zpitch, out_logp_full, out_ids, out_logp, out_lse, lse_buf, st);
+            if (e != hipSuccess) return device_status(e);
             if (out_logp_full != nullptr) vt::launch_sub_lse(out_logp_full, lse_buf, n, k, st);
             return VT_OK;
         }

@@ -9,12 +9,16 @@
 // 151 at 128 bytes unswizzled) and every 8 lanes still load one 128-byte line.
 //
 // The tile's logits meet in LDS (over the ring) and the workgroup epilogue produces (max, sum-exp) and the best
-// candidates per hidden row; a merge kernel finishes the step.  Or the logits are stored for row_select_kernel.
+// candidates per hidden row; a merge kernel finishes the step.  Or the logits go straight from the accumulators to memory for
+// row_select_kernel (16 bytes per lane; by way of LDS they took a tile of 128 x 224 4.7 us, now 1.5: n = 256, k = 32768, d = 8192
+// 157.7 -> 155.5 us, n = 33, k = 21900, d = 4096, m = 16 42.9 / 41.1) -- those of all columns, or of a slice of them: heads of few
+// rows are cut into larger tiles and slices (plan_stored in vt_api.hip).
 #include "vt_device.h"
 #include "vt_launch.h"
 #include "vt_ranges.h"
 #include "vt_step.h"
 #include "vt_step_tail.h"
+#include <type_traits>
 
 namespace vt {
 
@@ -60,15 +64,22 @@ __device__ __forceinline__ void wait_stage_and_sync(int younger) {
 }
 
 // Where a workgroup's march over ns stages starts and where its ranges end.
-template <int NR>
+template <int NR, bool SLICES>
 struct March {
     int ns, rot, start, step, last, last_length;
     bool rotate;
-    __device__ __forceinline__ March(int ns_, int d) : ns(ns_) {
-        rotate = NR > 1 && d % 2048 == 0 && (NR > 2 || d >= 4096);
+    // Slices of the columns (of ns stages each) start in different places anyway; where those are whole multiples of 4 KiB
+    // apart a slice has ranges to itself (n = 32, k = 14000, d = 8192, two slices 57.3 -> 50.6 us; elsewhere 2 to 10 % slower).
+    __device__ __forceinline__ March(int ns_, int d, int slice_ranges) : ns(ns_) {
+        rotate = NR > 1 && (SLICES ? slice_ranges != 0 && ns >= 2 * NR : d % 2048 == 0 && (NR > 2 || d >= 4096));
         rot = rotate ? first_range<NR>((int)blockIdx.x) : 0;
-        // stages from one start to the next
-        step = NR == 2 ? 16 : range_step<NR>(ns, d);
+        // stages from one start to the next (an even number of them: a stage may be two blocks of 64 columns)
+        if constexpr (SLICES) {
+            step = ns / NR & ~1;
+            if (step % 32 == 0) step = NR == 2 ? 16 : step + 32 / NR;
+        } else {
+            step = NR == 2 ? 16 : range_step<NR>(ns, d);
+        }
         start = bound(rot);
         last = NR - 1 - rot;
         last_length = ns - bound(NR - 1);
@@ -83,12 +94,39 @@ struct March {
     __device__ __forceinline__ int length_of(int j) const { return j == last ? last_length : step; }
 };
 
+// What becomes of a tile's logits: lists of candidates (or logits by way of LDS, where zbuf is not aligned), logits straight from the
+// accumulators, or those of a slice of the columns, blockIdx.y.  Kernels of their own: as a branch in one kernel they took every
+// step 0.2 to 0.5 us (n = 16, k = 9735, d = 3072 17.5 / 17.8, n = 80, k = 35010, d = 1024 23.6 / 24.1).
+enum TileOut { kTileLists, kTileStored, kTileSlices };
+// The columns of a workgroup: the first stage of 64, and how many.
+template <TileOut OUT>
+struct Columns {
+    int slice, first, stages;
+    __device__ __forceinline__ explicit Columns(const MfmaArgs &a) {
+        if constexpr (OUT == kTileSlices) {
+            slice = (int)blockIdx.y;
+            first = 2 * (slice * a.slice_units + min(slice, a.slice_more));
+            stages = 2 * (a.slice_units + (slice < a.slice_more ? 1 : 0));
+        } else {
+            slice = 0;
+            first = 0;
+            stages = a.d / kStageCols;
+        }
+    }
+};
+
 // Tile logits in LDS: hidden row i at i * pitch floats.
 __device__ __forceinline__ void store_logits4(float *dst, const f32x4 &v) {
     dst[0] = v.x;
     dst[1] = v.y;
     dst[2] = v.z;
     dst[3] = v.w;
+}
+
+// Four logits of a hidden row straight from the accumulators to zbuf, if the tile has them (16-byte aligned; where k is no
+// multiple of four the last group reaches into the row's padding).
+__device__ __forceinline__ void store_z4(float *z, int i, int n, int pitch, int row, int rows_b, const f32x4 &v) {
+    if (i < n && row < rows_b) *reinterpret_cast<f32x4 *>(z + (size_t)i * pitch + row) = v;
 }
 
 // Workgroup epilogue on the logit tile of hidden rows i_lo .. i_hi - 1 (row i at zt + (i - i_lo) * tp), Q * 16 >= rows_b.
@@ -99,7 +137,7 @@ __device__ __forceinline__ void tile_epilogue(const MfmaArgs &a, const float *zt
         // one wave copies a hidden row's logits of this tile (contiguous in z) at a time
         for (int i = i_lo + w; i < i_hi; i += nwaves) {
             const float *src = zt + (size_t)(i - i_lo) * tp;
-            float *dst = a.zbuf + (size_t)i * a.k + row0;
+            float *dst = a.zbuf + (size_t)i * a.zpitch + row0;
             for (int t = lane; t < rows_b; t += kWave) dst[t] = src[t];
         }
         return;
@@ -130,7 +168,7 @@ __device__ __forceinline__ void tile_epilogue(const MfmaArgs &a, const float *zt
 // reads nothing, are hidden behind the other one's march.  k = 65536, n = 64, d = 2048 57.3 -> 51.4 us, n = 9 50.8 -> 46.6.
 // k = 32768, d = 4096: n = 64 43.0 us with the logits stored, n = 32 42.1 (a plain read of the 268 MB: 40.8; the
 // register-staged kernel before this one: 52.0 and 46.5).
-template <int NT, int MAXW, int TPW, int KB, int NST, int LPW, bool X, int WGS>
+template <int NT, int MAXW, int TPW, int KB, int NST, int LPW, bool X, int WGS, TileOut OUT>
 __global__ void __launch_bounds__(MAXW *kWave) __attribute__((amdgpu_waves_per_eu(WGS == 1 ? 1 : WGS * ((MAXW + 3) / 4), WGS * ((MAXW + 3) / 4))))
 head_mfma_kernel(const MfmaArgs a) {
     static_assert(!X || (MAXW == kStepWaves && TPW == NT), "the ninth group belongs to tiles of eight waves");
@@ -145,12 +183,13 @@ head_mfma_kernel(const MfmaArgs a) {
     if (a.ticket_clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
         __hip_atomic_store(a.ticket_clear, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int tile_rows = 16 * RG + (X ? a.extra_rows : 0);
+    const Columns<OUT> columns(a);
     const int row0 = blockIdx.x * tile_rows;
     const int rows_b = min(tile_rows, a.k - row0);
     const unsigned rs = (unsigned)a.d * 2u;
-    const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs;
-    const char *hb = static_cast<const char *>(a.h);
-    const March<NR> march(a.d / kStageCols, a.d);
+    const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs + (size_t)columns.first * 128;
+    const char *hb = static_cast<const char *>(a.h) + (size_t)columns.first * 128;
+    const March<NR, OUT == kTileSlices> march(columns.stages, a.d, OUT == kTileSlices ? a.slice_ranges : 0);
     const unsigned block_bytes = (unsigned)(GR + NT) * kGroupBytes, stage_bytes = KB * block_bytes;
     const int nstages = march.ns / KB;             // (d is a multiple of 128: an even number of blocks)
 
@@ -182,7 +221,7 @@ head_mfma_kernel(const MfmaArgs a) {
         }
     };
     // the tile's target ids, ahead of everything else
-    if (w == 0) {
+    if (OUT == kTileLists && w == 0) {
 #pragma unroll
         for (int q = 0; q < 3; ++q)
             lds_load4((unsigned)a.ids_off + q * kWave * 4, (unsigned)min(q * kWave + lane, rows_b - 1) * 4u, a.map + row0);
@@ -259,27 +298,36 @@ head_mfma_kernel(const MfmaArgs a) {
         sums.close(acc, march.rot, closed);
         sums.total(acc);
     }
-    wait_and_sync<0>();      // every wave is done with the ring: it becomes the logit tile
-
-    float *zt = reinterpret_cast<float *>(smem);
-    const int tp = 16 * GR + 1;
-    if (active) {
+    if constexpr (OUT != kTileLists) {
+        float *z = a.zbuf + (size_t)columns.slice * a.n * a.zpitch + row0;
+        if (active) {
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-            const int i = 16 * (t0 + t) + lrow;
-            if (i < a.n) store_logits4(zt + (size_t)i * tp + 16 * rg + 4 * lgrp, acc[t]);
+            for (int t = 0; t < TPW; ++t) store_z4(z, 16 * (t0 + t) + lrow, a.n, a.zpitch, 16 * rg + 4 * lgrp, min(rows_b, 16 * RG), acc[t]);
         }
+        if (ninth) store_z4(z, 16 * w + lrow, a.n, a.zpitch, kMfmaTileRows + 4 * lgrp, rows_b, acc[NA - 1]);
+    } else {
+        wait_and_sync<0>();      // every wave is done with the ring: it becomes the logit tile
+
+        float *zt = reinterpret_cast<float *>(smem);
+        const int tp = 16 * GR + 1;
+        if (active) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                const int i = 16 * (t0 + t) + lrow;
+                if (i < a.n) store_logits4(zt + (size_t)i * tp + 16 * rg + 4 * lgrp, acc[t]);
+            }
+        }
+        if (ninth) {
+            const int i = 16 * w + lrow;
+            if (i < a.n) store_logits4(zt + (size_t)i * tp + kMfmaTileRows + 4 * lgrp, acc[NA - 1]);
+        }
+        __syncthreads();
+        const int *lds_ids = reinterpret_cast<const int *>(smem + a.ids_off);
+        unsigned long long *cand =
+            reinterpret_cast<unsigned long long *>(smem + (((size_t)a.n * tp * sizeof(float) + 15) & ~(size_t)15));
+        constexpr int Q = X ? 9 : MAXW > kStepWaves ? kMfmaMaxWaves : 8;
+        tile_epilogue<Q>(a, zt, tp, 0, a.n, row0, rows_b, lds_ids, cand, NW, w, lane);
     }
-    if (ninth) {
-        const int i = 16 * w + lrow;
-        if (i < a.n) store_logits4(zt + (size_t)i * tp + kMfmaTileRows + 4 * lgrp, acc[NA - 1]);
-    }
-    __syncthreads();
-    const int *lds_ids = reinterpret_cast<const int *>(smem + a.ids_off);
-    unsigned long long *cand =
-        reinterpret_cast<unsigned long long *>(smem + (((size_t)a.n * tp * sizeof(float) + 15) & ~(size_t)15));
-    constexpr int Q = X ? 9 : MAXW > kStepWaves ? kMfmaMaxWaves : 8;
-    tile_epilogue<Q>(a, zt, tp, 0, a.n, row0, rows_b, lds_ids, cand, NW, w, lane);
 }
 
 // ---------------------------------------------------------------- 65 .. 256 hidden rows
@@ -297,7 +345,7 @@ head_mfma_kernel(const MfmaArgs a) {
 // The march of n = 256, d = 8192 is bound by power: the clock falls from 2.4 to 1.6 .. 1.9 GHz while loads and products run
 // together, and stays at 2.4 with either alone.
 // PACKED: h was re-laid by pack_h_kernel, a stage's pieces one after the other as they lie in LDS.
-template <int MT, int NTT, int NST, int NR, bool PACKED>
+template <int MT, int NTT, int NST, int NR, bool PACKED, TileOut OUT>
 __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const MfmaArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int TM = 32 * MT, TN = 64 * NTT;
@@ -310,12 +358,14 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
     const int wn = w & 3, wm = w >> 2;
     if (a.ticket_clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
         __hip_atomic_store(a.ticket_clear, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const Columns<OUT> columns(a);
     const int row0 = blockIdx.x * TM;
     const int rows_b = min(TM, a.k - row0);
     const unsigned rs = (unsigned)a.d * 2u;
-    const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs;
-    const char *hb = static_cast<const char *>(a.h);
-    const March<NR> march(a.d / kStageCols, a.d);
+    const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs + (size_t)columns.first * 128;
+    // (re-laid: a stage's pieces lie one after the other)
+    const char *hb = PACKED ? static_cast<const char *>(a.hpack) + (size_t)columns.first * (TN * 128) : static_cast<const char *>(a.h) + (size_t)columns.first * 128;
+    const March<NR, OUT == kTileSlices> march(columns.stages, a.d, OUT == kTileSlices ? a.slice_ranges : 0);
 
     unsigned voff[LPW], lds_at[LPW];
 #pragma unroll
@@ -335,7 +385,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
     auto aim = [&](int s, int slot) {
         const size_t u = (size_t)march.stage_of(s);
         pw = Wt + u * 128;
-        ph = PACKED ? static_cast<const char *>(a.hpack) + u * (TN * 128) : hb + u * 128;
+        ph = hb + u * (PACKED ? TN * 128 : 128);
         at = (unsigned)slot * kStage;
     };
     auto load_piece = [&](int j) {
@@ -345,7 +395,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
         else
             lds_load16<false>(at + lds_at[j], voff[j], ph);
     };
-    if (w == 0) {
+    if (OUT == kTileLists && w == 0) {
 #pragma unroll
         for (int q = 0; q < (TM + kWave - 1) / kWave; ++q)
             lds_load4((unsigned)a.ids_off + q * kWave * 4, (unsigned)min(q * kWave + lane, rows_b - 1) * 4u, a.map + row0);
@@ -417,30 +467,40 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
         sums.close(acc, march.rot, closed);
         sums.total(acc);
     }
-    wait_and_sync<0>();      // every wave is done with the ring: it becomes the logit tile
-
-    // logit tile: all hidden rows at once, or (a.passes = 2) the lower and upper half of the wave columns in turn
-    float *zt = reinterpret_cast<float *>(smem);
-    constexpr int tp = TM + 1;
-    const int *lds_ids = reinterpret_cast<const int *>(smem + a.ids_off);
-    const int per_pass = TN / a.passes;            // hidden rows per pass
-    unsigned long long *cand = reinterpret_cast<unsigned long long *>(
-        smem + (((size_t)min(per_pass, a.n) * tp * sizeof(float) + 15) & ~(size_t)15));
-    for (int pass = 0; pass < a.passes; ++pass) {
-        const int i_lo = pass * per_pass, i_hi = min(a.n, i_lo + per_pass);
-        if (i_lo >= i_hi) break;                   // (uniform)
-        if (pass > 0) __syncthreads();             // the tile of the pass before is done with
+    if constexpr (OUT != kTileLists) {
+        float *z = a.zbuf + (size_t)columns.slice * a.n * a.zpitch + row0;
 #pragma unroll
         for (int t = 0; t < NTT; ++t) {
-            const int i = 16 * (wn * NTT + t) + lrow;
-            if (i >= i_lo && i < i_hi) {
 #pragma unroll
-                for (int m = 0; m < MT; ++m)
-                    store_logits4(zt + (size_t)(i - i_lo) * tp + 16 * (wm * MT + m) + 4 * lgrp, acc[m * NTT + t]);
-            }
+            for (int m = 0; m < MT; ++m)
+                store_z4(z, 16 * (wn * NTT + t) + lrow, a.n, a.zpitch, 16 * (wm * MT + m) + 4 * lgrp, rows_b, acc[m * NTT + t]);
         }
-        __syncthreads();
-        tile_epilogue<2 * MT>(a, zt, tp, i_lo, i_hi, row0, rows_b, lds_ids, cand, kStepWaves, w, lane);
+    } else {
+        wait_and_sync<0>();      // every wave is done with the ring: it becomes the logit tile
+
+        // logit tile: all hidden rows at once, or (a.passes = 2) the lower and upper half of the wave columns in turn
+        float *zt = reinterpret_cast<float *>(smem);
+        constexpr int tp = TM + 1;
+        const int *lds_ids = reinterpret_cast<const int *>(smem + a.ids_off);
+        const int per_pass = TN / a.passes;            // hidden rows per pass
+        unsigned long long *cand = reinterpret_cast<unsigned long long *>(
+            smem + (((size_t)min(per_pass, a.n) * tp * sizeof(float) + 15) & ~(size_t)15));
+        for (int pass = 0; pass < a.passes; ++pass) {
+            const int i_lo = pass * per_pass, i_hi = min(a.n, i_lo + per_pass);
+            if (i_lo >= i_hi) break;                   // (uniform)
+            if (pass > 0) __syncthreads();             // the tile of the pass before is done with
+#pragma unroll
+            for (int t = 0; t < NTT; ++t) {
+                const int i = 16 * (wn * NTT + t) + lrow;
+                if (i >= i_lo && i < i_hi) {
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+                        store_logits4(zt + (size_t)(i - i_lo) * tp + 16 * (wm * MT + m) + 4 * lgrp, acc[m * NTT + t]);
+                }
+            }
+            __syncthreads();
+            tile_epilogue<2 * MT>(a, zt, tp, i_lo, i_hi, row0, rows_b, lds_ids, cand, kStepWaves, w, lane);
+        }
     }
 }
 
@@ -461,7 +521,7 @@ hipError_t launch_tile(const MfmaArgs &a, int threads, size_t lds, hipStream_t s
     static LdsLimitOnce lds_limit;
     const hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(kern)}, kMaxDynamicLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(a.nlists), dim3(threads), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(a.nlists / a.splits, a.splits), dim3(threads), lds, st, a);
     return hipGetLastError();
 }
 
@@ -500,10 +560,20 @@ static_assert(rows_variant_ok(2, 9, false) && rows_variant_ok(2, 10, false) && r
 static_assert(rows_variant_ok(4, 1, false) && rows_variant_ok(4, 2, false) && rows_variant_ok(4, 3, false) && rows_variant_ok(4, 4, false));
 static_assert(rows_variant_ok(4, 5, false) && rows_variant_ok(4, 6, false) && rows_variant_ok(4, 7, false) && rows_variant_ok(4, 8, false));
 static_assert(rows_variant_ok(4, 9, false) && rows_variant_ok(4, 10, false) && rows_variant_ok(4, 11, false) && rows_variant_ok(4, 12, false));
+TileOut tile_out(const MfmaArgs &a) { return a.zbuf == nullptr || a.zvec == 0 ? kTileLists : a.splits > 1 ? kTileSlices : kTileStored; }
+// (slices: tiles of 64 and of 128 rows, one workgroup to a CU; unaligned logits go through LDS and have no slices)
 template <int NT, int RG, bool X, bool TWIN = false>
 hipError_t launch_rows(const MfmaArgs &a, size_t lds, hipStream_t st) {
     constexpr RowsVariant v = rows_variant(NT, RG, X, TWIN);
-    return launch_tile<head_mfma_kernel<NT, v.max_waves, v.tpw, v.blocks, v.stages, v.loads, X, TWIN ? 2 : 1>>(a, a.nwaves * kWave, lds, st);
+    auto launch = [&](auto out) {
+        return launch_tile<head_mfma_kernel<NT, v.max_waves, v.tpw, v.blocks, v.stages, v.loads, X, TWIN ? 2 : 1, decltype(out)::value>>(
+            a, a.nwaves * kWave, lds, st);
+    };
+    if (tile_out(a) == kTileStored) return launch(std::integral_constant<TileOut, kTileStored>{});
+    if constexpr ((RG == 4 || RG == 8) && !X && !TWIN) {
+        if (tile_out(a) == kTileSlices) return launch(std::integral_constant<TileOut, kTileSlices>{});
+    }
+    return a.splits == 1 ? launch(std::integral_constant<TileOut, kTileLists>{}) : hipErrorInvalidValue;
 }
 template <int NT>
 hipError_t launch_rows_nt(const MfmaArgs &a, size_t lds, hipStream_t st) {
@@ -528,16 +598,28 @@ constexpr int wide_ranges(int MT, int NTT) {
     const int acc = 4 * MT * NTT, ops = 8 * (MT + NTT);
     return 5 * acc + ops <= 208 ? 8 : 3 * acc + ops <= 208 ? 4 : 2;
 }
+// (slices: tiles of 64, 128 and 160 rows)
+template <int MT, int NTT, bool PACKED>
+hipError_t launch_wide_as(const MfmaArgs &a, size_t lds, hipStream_t st) {
+    constexpr int NST = wide_stages(MT, NTT), NR = wide_ranges(MT, NTT);
+    auto launch = [&](auto out) {
+        return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, NR, PACKED, decltype(out)::value>>(a, kStepWaves * kWave, lds, st);
+    };
+    if (tile_out(a) == kTileStored) return launch(std::integral_constant<TileOut, kTileStored>{});
+    if constexpr (MT == 2 || MT == 4 || MT == 5) {
+        if (tile_out(a) == kTileSlices) return launch(std::integral_constant<TileOut, kTileSlices>{});
+    }
+    return a.splits == 1 ? launch(std::integral_constant<TileOut, kTileLists>{}) : hipErrorInvalidValue;
+}
 template <int MT, int NTT>
 hipError_t launch_wide(const MfmaArgs &a, size_t lds, hipStream_t st) {
-    constexpr int NST = wide_stages(MT, NTT), NR = wide_ranges(MT, NTT);
-    if (a.hpack == nullptr) return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, NR, false>>(a, kStepWaves * kWave, lds, st);
+    if (a.hpack == nullptr) return launch_wide_as<MT, NTT, false>(a, lds, st);
     if constexpr (NTT == 4) {
         hipLaunchKernelGGL(pack_h_kernel, dim3((unsigned)((a.d / kStageCols + 3) / 4), 8 * NTT), dim3(256), 0, st, static_cast<const u32x4 *>(a.h),
                            static_cast<u32x4 *>(a.hpack), a.n, a.d);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, NR, true>>(a, kStepWaves * kWave, lds, st);
+        return launch_wide_as<MT, NTT, true>(a, lds, st);
     }
     return hipErrorInvalidValue;
 }

@@ -46,6 +46,7 @@ __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v
 // (-inf past the end).  All loads are issued before the first use.
 constexpr int kRowVals = 32;
 constexpr int kRowSpan = kRowThreads * kRowVals;     // 32768 logits per stretch
+static_assert(kRowSpan == kRowSelectWhole);
 
 // VEC: four consecutive logits per load (k a multiple of 4, row 16-byte aligned): thread t's value u is logit
 // base + 4 * ((u / 4) * kRowThreads + t) + u % 4; otherwise logit base + u * kRowThreads + t.
@@ -53,12 +54,12 @@ template <bool VEC>
 __device__ __forceinline__ int stretch_index(int base, int u, int tid) {
     return VEC ? base + 4 * ((u >> 2) * kRowThreads + tid) + (u & 3) : base + u * kRowThreads + tid;
 }
-template <bool VEC>
+template <bool VEC, int VALS>
 __device__ __forceinline__ void load_stretch(const float *__restrict__ zr, int base, int k, int tid,
-                                             float (&v)[kRowVals]) {
+                                             float (&v)[VALS]) {
     if constexpr (VEC) {
 #pragma unroll
-        for (int q = 0; q < kRowVals / 4; ++q) {
+        for (int q = 0; q < VALS / 4; ++q) {
             const int j = base + 4 * (q * kRowThreads + tid);
             float4 t = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
             if (j < k) t = *reinterpret_cast<const float4 *>(zr + j);
@@ -69,11 +70,42 @@ __device__ __forceinline__ void load_stretch(const float *__restrict__ zr, int b
         }
     } else {
 #pragma unroll
-        for (int u = 0; u < kRowVals; ++u) {
+        for (int u = 0; u < VALS; ++u) {
             const int j = base + u * kRowThreads + tid;
             v[u] = j < k ? zr[j] : -INFINITY;
         }
     }
+}
+
+// The row's logits from `splits` partial ones, `stride` floats apart, added up in the order of the slices (rows 16-byte aligned,
+// whole groups of four; what lies behind k in the last one is not a logit).  64 values of a thread are requested at a time.
+template <int VALS>
+__device__ __forceinline__ void load_slices(const float *__restrict__ zr, int splits, size_t stride, int k, int tid, float (&v)[VALS]) {
+    constexpr int PER = 64 / VALS;
+#pragma unroll
+    for (int u = 0; u < VALS; ++u) v[u] = 0.f;
+    for (int s0 = 0; s0 < splits; s0 += PER) {
+        float4 t[PER][VALS / 4];
+#pragma unroll
+        for (int s = 0; s < PER; ++s) {
+            const float *zs = zr + (size_t)min(s0 + s, splits - 1) * stride;
+#pragma unroll
+            for (int q = 0; q < VALS / 4; ++q) t[s][q] = *reinterpret_cast<const float4 *>(zs + min(4 * (q * kRowThreads + tid), (k - 1) & ~3));
+        }
+#pragma unroll
+        for (int s = 0; s < PER; ++s) {
+            const bool there = s0 + s < splits;
+#pragma unroll
+            for (int q = 0; q < VALS / 4; ++q) {
+                v[4 * q] += there ? t[s][q].x : 0.f;
+                v[4 * q + 1] += there ? t[s][q].y : 0.f;
+                v[4 * q + 2] += there ? t[s][q].z : 0.f;
+                v[4 * q + 3] += there ? t[s][q].w : 0.f;
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < VALS; ++u) v[u] = stretch_index<true>(0, u, tid) < k ? v[u] : -INFINITY;
 }
 
 // One exchange through LDS gives the row maximum M and a value T that at least m of the logits seen so far reach: every
@@ -117,15 +149,16 @@ __device__ __forceinline__ void row_threshold(float lm, int m, unsigned *tmax, i
 __device__ __forceinline__ float threshold_f32(unsigned T) { return T == 0u ? -INFINITY : from_orderable_f32(T); }
 
 // Folds one stretch into the lane's (max, sum-exp).
-__device__ __forceinline__ void fold_stretch(const float (&v)[kRowVals], float &lm, float &ls) {
+template <int VALS>
+__device__ __forceinline__ void fold_stretch(const float (&v)[VALS], float &lm, float &ls) {
     float cm = v[0];
 #pragma unroll
-    for (int u = 1; u < kRowVals; ++u) cm = fmaxf(cm, v[u]);
+    for (int u = 1; u < VALS; ++u) cm = fmaxf(cm, v[u]);
     const float mn = fmaxf(lm, cm);
     if (mn != -INFINITY) {
         float cs = 0.f;
 #pragma unroll
-        for (int u = 0; u < kRowVals; ++u) cs += __expf(v[u] - mn);     // exp(-inf) = 0 past the end
+        for (int u = 0; u < VALS; ++u) cs += __expf(v[u] - mn);     // exp(-inf) = 0 past the end
         ls = ls * __expf(lm - mn) + cs;
         lm = mn;
     }
@@ -133,11 +166,11 @@ __device__ __forceinline__ void fold_stretch(const float (&v)[kRowVals], float &
 
 // Every logit of a stretch that reaches Tf, with its position, into `val` / `pos` (cap entries; n counts on -- STOP: a lane
 // that finds no room goes on no further: where everything reaches Tf tens of thousands of increments queue on one address).
-template <bool VEC, bool STOP>
-__device__ __forceinline__ void collect_stretch(const float (&v)[kRowVals], int base, int k, int tid, float Tf, float *val,
+template <bool VEC, bool STOP, int VALS>
+__device__ __forceinline__ void collect_stretch(const float (&v)[VALS], int base, int k, int tid, float Tf, float *val,
                                                 int *pos, unsigned *n, unsigned cap) {
 #pragma unroll
-    for (int g = 0; g < kRowVals; g += 4) {
+    for (int g = 0; g < VALS; g += 4) {
         // (four logits to a branch: a dozen of a thousand threads' groups holds one)
         if (fmaxf(fmaxf(v[g], v[g + 1]), fmaxf(v[g + 2], v[g + 3])) >= Tf) {
 #pragma unroll
@@ -168,12 +201,19 @@ __device__ __forceinline__ void collect_stretch(const float (&v)[kRowVals], int 
 // found bit by bit, and passes several times as many logits as the row's own (whole step, once against twice: n = 1,
 // k = 63000, m = 24 28.2 / 24.8 us, n = 4, k = 128256, m = 64 47.7 / 43.3; but n = 16, k = 65536, m = 24 30.6 / 32).
 enum RowMode { kRowWhole, kRowSift, kRowTwice };
-template <RowMode MODE, bool VEC>
+// VALS: values per thread and stretch; fewer than 32 for rows that fit them (what a thread holds past the row's end costs it an
+// exponential and a comparison like any other: n = 40, k = 4149, d = 2048, m = 10 17.4 -> 15.9 us, n = 12, k = 10860, d = 3072, m = 16
+// 19.8 -> 19.2).  SLICED: z is [splits][gridDim.x][pitch], see load_slices; z_out, or null: where the
+// sums go.
+template <RowMode MODE, bool VEC, int VALS, bool SLICED>
 __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__restrict__ z, const int *__restrict__ map,
-                                                                 int k, int m, int *__restrict__ out_ids,
+                                                                 int k, int m, int splits, int pitch, float *__restrict__ z_out,
+                                                                 int *__restrict__ out_ids,
                                                                  float *__restrict__ out_logp,
                                                                  float *__restrict__ out_lse,
                                                                  float *__restrict__ lse_buf) {
+    static_assert(!SLICED || (MODE == kRowWhole && VEC), "slices of rows that one stretch holds");
+    static_assert(VALS == kRowVals || MODE == kRowWhole, "rows of several stretches");
     constexpr bool SIFT = MODE == kRowSift;
     constexpr unsigned kRaw = SIFT ? kRowMaxRaw : kRowMaxCand;
     __shared__ float redf[kRowWaves];
@@ -186,8 +226,8 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     __shared__ unsigned s_at[kRowMaxTokens];      // candidates with that many larger logits
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int i = blockIdx.x;
-    const float *zr = z + (size_t)i * k;
-    float v[kRowVals];
+    const float *zr = z + (size_t)i * (SLICED ? pitch : k);
+    float v[VALS];
     // (all of this is first used behind the barrier of row_threshold.  Candidates are ranked in whole groups of eight: what is
     // behind the last one loses against all of them)
     if (tid == 0) {
@@ -202,31 +242,42 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
 
     // ---- pass 1: (max, sum-exp) and the thread's largest logit
     float lm = -INFINITY, ls = 0.f;
-    load_stretch<VEC>(zr, 0, k, tid, v);
+    if constexpr (SLICED) {
+        load_slices(zr, splits, (size_t)gridDim.x * pitch, k, tid, v);
+        if (z_out != nullptr) {
+#pragma unroll
+            for (int u = 0; u < VALS; ++u) {
+                const int j = stretch_index<VEC>(0, u, tid);
+                if (j < k) z_out[(size_t)i * k + j] = v[u];
+            }
+        }
+    } else {
+        load_stretch<VEC, VALS>(zr, 0, k, tid, v);
+    }
     unsigned T, Mo;
     if constexpr (MODE == kRowWhole) {
         fold_stretch(v, lm, ls);
     } else if constexpr (MODE == kRowTwice) {
         fold_stretch(v, lm, ls);
         for (int base = kRowSpan; base < k; base += kRowSpan) {
-            load_stretch<VEC>(zr, base, k, tid, v);
+            load_stretch<VEC, VALS>(zr, base, k, tid, v);
             fold_stretch(v, lm, ls);
         }
     } else {
-        float v2[kRowVals];
-        load_stretch<VEC>(zr, kRowSpan, k, tid, v2);
+        float v2[VALS];
+        load_stretch<VEC, VALS>(zr, kRowSpan, k, tid, v2);
         fold_stretch(v, lm, ls);
         row_threshold(lm, m, tmax_first, lane, w, T, Mo);
         const float Tf1 = threshold_f32(T);
-        collect_stretch<VEC, SIFT>(v, 0, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, SIFT, VALS>(v, 0, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
         for (int base = kRowSpan; base < k; base += 2 * kRowSpan) {
-            load_stretch<VEC>(zr, base + kRowSpan, k, tid, v);
+            load_stretch<VEC, VALS>(zr, base + kRowSpan, k, tid, v);
             fold_stretch(v2, lm, ls);
-            collect_stretch<VEC, SIFT>(v2, base, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+            collect_stretch<VEC, SIFT, VALS>(v2, base, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
             if (base + kRowSpan < k) {
-                load_stretch<VEC>(zr, base + 2 * kRowSpan, k, tid, v2);
+                load_stretch<VEC, VALS>(zr, base + 2 * kRowSpan, k, tid, v2);
                 fold_stretch(v, lm, ls);
-                collect_stretch<VEC, SIFT>(v, base + kRowSpan, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+                collect_stretch<VEC, SIFT, VALS>(v, base + kRowSpan, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
             }
         }
     }
@@ -240,12 +291,12 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
 
     // ---- pass 2: every logit >= T is a candidate
     if constexpr (MODE == kRowWhole) {
-        collect_stretch<VEC, SIFT>(v, 0, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, SIFT, VALS>(v, 0, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
         __syncthreads();
     } else if constexpr (MODE == kRowTwice) {
         for (int base = 0; base < k; base += kRowSpan) {
-            load_stretch<VEC>(zr, base, k, tid, v);
-            collect_stretch<VEC, SIFT>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+            load_stretch<VEC, VALS>(zr, base, k, tid, v);
+            collect_stretch<VEC, SIFT, VALS>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
         }
         __syncthreads();
     } else if (s_nraw > kRaw) {
@@ -253,8 +304,8 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         if (tid == 0) s_nraw = 0u;
         __syncthreads();
         for (int base = 0; base < k; base += kRowSpan) {
-            load_stretch<VEC>(zr, base, k, tid, v);
-            collect_stretch<VEC, SIFT>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+            load_stretch<VEC, VALS>(zr, base, k, tid, v);
+            collect_stretch<VEC, SIFT, VALS>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
         }
         __syncthreads();
     }
@@ -327,9 +378,9 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         for (int r = 0; r < m; ++r) {
             unsigned long long best = kNoKey;
             for (int base = 0; base < k; base += kRowSpan) {
-                if (MODE != kRowWhole) load_stretch<VEC>(zr, base, k, tid, v);
+                if (MODE != kRowWhole) load_stretch<VEC, VALS>(zr, base, k, tid, v);
 #pragma unroll
-                for (int u = 0; u < kRowVals; ++u) {
+                for (int u = 0; u < VALS; ++u) {
                     const int j = stretch_index<VEC>(base, u, tid);
                     if (j < k && v[u] >= Tf) {
                         const unsigned long long key = make_key(v[u], map[j]);
@@ -351,13 +402,26 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     }
 }
 
-void launch_row_select(const float *z, const int *map, int n, int k, int m, int *out_ids, float *out_logp,
-                       float *out_lse, float *lse_buf, hipStream_t st) {
+// splits > 1: z is [splits][n][pitch], pitch a multiple of four, k <= kRowSpan; z_out [n, k] or null takes the sums.
+hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, float *z_out, int *out_ids,
+                             float *out_logp, float *out_lse, float *lse_buf, hipStream_t st) {
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, splits, pitch, z_out, out_ids, out_logp, out_lse, lse_buf);
+        return hipGetLastError();
+    };
+    if (splits > 1) {
+        if (k > kRowSpan || pitch % 4 != 0 || pitch < k || (reinterpret_cast<uintptr_t>(z) & 15) != 0) return hipErrorInvalidValue;
+        if (k <= 8 * kRowThreads) return launch(&row_select_kernel<kRowWhole, true, 8, true>);
+        if (k <= 16 * kRowThreads) return launch(&row_select_kernel<kRowWhole, true, 16, true>);
+        return launch(&row_select_kernel<kRowWhole, true, kRowVals, true>);
+    }
     const bool vec = (k & 3) == 0 && (reinterpret_cast<uintptr_t>(z) & 15) == 0;
-    auto pick = [&](auto whole, auto sift, auto twice) { return k <= kRowSpan ? whole : n <= kGemvMaxN && m > kRowWaves ? twice : sift; };
-    auto kern = vec ? pick(&row_select_kernel<kRowWhole, true>, &row_select_kernel<kRowSift, true>, &row_select_kernel<kRowTwice, true>)
-                    : pick(&row_select_kernel<kRowWhole, false>, &row_select_kernel<kRowSift, false>, &row_select_kernel<kRowTwice, false>);
-    hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, out_ids, out_logp, out_lse, lse_buf);
+    if (k <= 8 * kRowThreads) return vec ? launch(&row_select_kernel<kRowWhole, true, 8, false>) : launch(&row_select_kernel<kRowWhole, false, 8, false>);
+    if (k <= 16 * kRowThreads) return vec ? launch(&row_select_kernel<kRowWhole, true, 16, false>) : launch(&row_select_kernel<kRowWhole, false, 16, false>);
+    if (k <= kRowSpan) return vec ? launch(&row_select_kernel<kRowWhole, true, kRowVals, false>) : launch(&row_select_kernel<kRowWhole, false, kRowVals, false>);
+    if (n <= kGemvMaxN && m > kRowWaves)
+        return vec ? launch(&row_select_kernel<kRowTwice, true, kRowVals, false>) : launch(&row_select_kernel<kRowTwice, false, kRowVals, false>);
+    return vec ? launch(&row_select_kernel<kRowSift, true, kRowVals, false>) : launch(&row_select_kernel<kRowSift, false, kRowVals, false>);
 }
 
 }  // namespace vt

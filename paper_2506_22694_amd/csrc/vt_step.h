@@ -76,6 +76,7 @@ inline bool packs_h(int NTT, int n, int d) { return NTT == 4 && (size_t)n * d * 
 constexpr int kRowSelectMinL = 11;
 constexpr int kRowSelectMinLManyRows = 8;
 constexpr int kRowSelectMinWork = 1792; // ... where also many rows with many tokens on small tiles do (n * min(m, tile rows))
+constexpr int kRowSelectWhole = 32768;  // a row of so many stored logits stays in the registers of its workgroup
 // small-n path: the same switch when L > 12 - n / 2 (measured crossovers: L = 8 at n = 8, 10 at n = 4, 11-12 at n = 1)
 constexpr int kGemvRowSelectBase = 12;
 constexpr int kMfmaPrefetchUnits = 3;  // 128-column units of W_trim in flight per wave; an h chunk that has a successor
@@ -117,6 +118,12 @@ struct MfmaArgs {
     int ids_off;
     int passes;
     int twin;                 // tiles of half a CU's LDS: two workgroups per CU
+    // more than 8 hidden rows: slices of the columns (grid.y; 1: none), slice i of slice_units units of 128 columns, the first
+    // slice_more of them one unit longer; slice_ranges: they start whole multiples of 4 KiB apart.  zbuf is
+    // [splits][n][zpitch] and row_select_kernel adds the slices up (zpitch = k without slices)
+    int splits, slice_units, slice_more, slice_ranges;
+    int zpitch;
+    int zvec;                 // more than 8 hidden rows: zbuf is 16-byte aligned and zpitch a multiple of four
     // or null: a word the kernel sets to zero (the merge kernel behind it counts its workgroups there when a tree
     // level is fused; the kernel boundary orders the two)
     unsigned *ticket_clear;
@@ -198,8 +205,9 @@ struct RowList {
 void launch_gather_h_rows(const void *h, void *staging, size_t row_bytes, const RowList &rows, hipStream_t st);
 void launch_scatter_rows(const int *ids_s, const float *logp_s, const float *lse_s, int m, int *out_ids,
                          float *out_logp, float *out_lse, const RowList &rows, hipStream_t st);
-// per-row tail on stored logits z [n, k]: lse, the m best logits and their target ids (one workgroup per row)
-void launch_row_select(const float *z, const int *map, int n, int k, int m, int *out_ids, float *out_logp,
-                       float *out_lse, float *lse_buf, hipStream_t st);
+// per-row tail on stored logits z [n, k]: lse, the m best logits and their target ids (one workgroup per row).  splits > 1: z is
+// [splits][n][pitch], partial logits of the columns' slices; their sums go to z_out [n, k] as well unless it is null
+hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, float *z_out, int *out_ids,
+                             float *out_logp, float *out_lse, float *lse_buf, hipStream_t st);
 
 }  // namespace vt

@@ -1,0 +1,99 @@
+"""Steps of more than 8 hidden rows on heads of few rows: tiles whose columns are cut into slices, stored logits in whole rows of
+8, 16 and 32 values per thread, against fp64 on the device."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2506_22694_amd as vt
+from paper_2506_22694_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(n, k, d, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    W = torch.randn(k, d, generator=g, device="cuda", dtype=torch.bfloat16).mul_(0.02)
+    h = torch.randn(n, d, generator=g, device="cuda", dtype=torch.bfloat16)
+    # equal rows, in the first and last tile and slot: their logits are equal bit for bit
+    same = sorted({0, 63, 64, k // 2, k - 2, k - 1})
+    W[same] = W[3].clone()
+    return h, W, torch.randperm(2 * k, generator=g, device="cuda")[:k].sort().values.to(torch.int32), same
+
+
+def _check(h, W, map_, same, m, got):
+    ids, logp, lse, full = got
+    z = h.double() @ W.double().t()
+    ref = z - z.logsumexp(1, keepdim=True)
+    # fp32 sums of d products of size 0.02, |logit| <= 20, in up to eight slices and ranges: a few ulp of 20 (2e-6) each
+    assert (full - ref).abs().max().item() < 5e-5
+    assert (logp - ref.topk(m, 1).values).abs().max().item() < 5e-5
+    assert (lse - z.logsumexp(1)).abs().max().item() < 5e-5
+    dup = full[:, torch.tensor(same, device="cuda")]
+    assert torch.equal(dup, dup[:, :1].expand_as(dup))
+    # the tokens are those of the step's own logits, equal ones in ascending order of their ids
+    order = torch.sort(full, dim=1, descending=True, stable=True).indices[:, :m]
+    assert torch.equal(ids, map_[order])
+    assert torch.equal(logp, torch.gather(full, 1, order))
+
+
+# Slices: the kernels' ranges of hidden rows and their edges, tiles of 64, 128 and 160 rows, two to eight slices of equal and of
+# unequal length, slices whole multiples of 4 KiB apart (which have ranges of their own), ragged last tiles, k on and off multiples
+# of four, h re-laid, rows of one, two and four stretches of 4096 logits
+@pytest.mark.parametrize("n,k,d,m,slices,tile", [
+    (9, 4300, 8192, 8, 7, 128), (32, 4097, 8192, 4, 7, 128), (33, 6001, 8192, 10, 5, 128), (64, 5002, 8192, 16, 6, 128),
+    (65, 4303, 4096, 8, 7, 128), (128, 8193, 3072, 1, 3, 128), (129, 4096, 2048, 8, 4, 64), (160, 10001, 4096, 4, 3, 128),
+    (192, 6500, 4096, 10, 5, 128), (193, 5000, 8192, 4, 6, 128), (224, 14000, 8192, 8, 2, 128), (256, 14001, 8192, 16, 2, 128),
+    (256, 4100, 8064, 8, 7, 128), (256, 9999, 5248, 33, 3, 128), (100, 4096, 8192, 64, 4, 64), (250, 2050, 2048, 8, 7, 64), (128, 11900, 8192, 9, 3, 160), (300, 4300, 4096, 8, 3, 64)])
+def test_step_by_slices_of_the_columns(n, k, d, m, slices, tile):
+    plan = vt.draft_head_step_plan(n, k, d, m)
+    assert f"tile_rows={tile} " in plan and f"column_slices={slices} + row_select" in plan, plan
+    h, W, map_, same = _inputs(n, k, d, seed=n + k)
+    _check(h, W, map_, same, m, vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True))
+
+
+# Stored logits of heads that one or two values per lane and load hold, without slices: rows of 8 and 16 values per thread and their
+# edges, k on and off multiples of four, more logits than candidates (hidden row of zeros)
+@pytest.mark.parametrize("n,k,d,m", [
+    (12, 8192, 128, 16), (12, 8193, 256, 9), (20, 16384, 128, 10), (17, 16385, 128, 12), (9, 16381, 128, 64), (200, 4099, 256, 8), (70, 4100, 1024, 8),
+    (256, 9000, 1024, 8), (3, 8191, 128, 20)])
+def test_stored_logits_of_short_rows(n, k, d, m):
+    assert "row_select" in vt.draft_head_step_plan(n, k, d, m) and "slices" not in vt.draft_head_step_plan(n, k, d, m)
+    h, W, map_, same = _inputs(n, k, d, seed=k)
+    h[n // 2] = 0
+    _check(h, W, map_, same, m, vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True))
+
+
+# The library's own memory, a tree level, several heads and a workspace of the size that earlier versions asked for
+@pytest.mark.parametrize("n,k,d,m", [(224, 4300, 4096, 4), (40, 4300, 8192, 8), (70, 4100, 1024, 8)])
+def test_the_other_ways_to_a_stored_step(n, k, d, m):
+    assert "row_select" in vt.draft_head_step_plan(n, k, d, m)
+    h, W, map_, same = _inputs(n, k, d)
+    ids, logp, lse, full = vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True)
+    _check(h, W, map_, same, m, (ids, logp, lse, full))
+    plain = vt.draft_head_step(h, W, map_, m)
+    assert torch.equal(plain[0], ids) and torch.equal(plain[1], logp)
+    a, b = torch.empty_like(ids), torch.empty_like(logp)
+    vt.draft_head_step_static(h, W, map_, m, a, b)
+    assert torch.equal(a, ids) and torch.equal(b, logp)
+    cum = torch.linspace(-3, 0, n, device="cuda")
+    parent, token, score, a, b = vt.draft_tree_level(h, W, map_, m, cum, 5)
+    assert torch.equal(a, ids) and torch.equal(b, logp)
+    for x, y in zip(vt.tree_expand(cum, logp, ids, 5), (parent, token, score)):
+        assert torch.equal(x, y)
+    a, b = vt.draft_head_step_multi(h, [(W, map_)], [0] * n, m)
+    assert torch.equal(a, ids) and torch.equal(b, logp)
+    # the smallest workspace that is accepted: the tokens and log-probs are those of its logits, which may round differently
+    L, ws = vt.load_library(), vt.StepWorkspace(n, k, d, m, h.device)
+    a, b = torch.empty_like(ids), torch.empty_like(logp)
+    step = lambda size: L.vt_draft_head_step(h.data_ptr(), 1, n, W.data_ptr(), 1, k, d, map_.data_ptr(), m, a.data_ptr(), b.data_ptr(), None, None,
+                                             ws.buf.data_ptr(), ctypes.c_size_t(size), None)
+    lo, hi = 0, ws.nbytes // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        status = step(256 * mid)
+        assert status in (0, 5)
+        lo, hi = (lo, mid) if status == 0 else (mid, hi)
+    assert step(256 * hi) == 0 and 256 * hi < ws.nbytes and 256 * hi <= binding.VT_STATIC_WS_BYTES
+    torch.cuda.synchronize()
+    assert (b - logp).abs().max().item() < 5e-5 and (a != ids).sum().item() <= 2 + ids.numel() // 256
