@@ -248,13 +248,17 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     request_dword(ids[0], head_map + row0 + min(lane, rows_b - 1));
     request_dword(ids[1], head_map + row0 + min(lane + kWave, rows_b - 1));
     request_dword(ids[2], head_map + row0 + min(lane + 2 * kWave, rows_b - 1));
+    // The first unit of W is asked for ahead of h, whose addresses take longer to form than its way takes from the L2 (k = 32768,
+    // d = 2048, n = 1 25.3 -> 24.7 us, k = 5000, d = 3072, n = 1 12.9 -> 12.4, k = 8192, d = 2048, n = 8 13.5 -> 13.2; two units first
+    // 25.1, 13.1 and 13.8, all three 25.3, 13.3 and 14.2).
+    constexpr int kAhead = 1, kBehind = kPrefetchUnits - kAhead;
+#pragma unroll
+    for (int x = 0; x < kAhead; ++x) load_unit(x, areg[x]);
     fetch_chunk(0);                       // everything waits for it
 #pragma unroll
-    for (int x = 0; x < kPrefetchUnits; ++x) {
-        load_unit(x, areg[x]);
-    }
-    wait_pieces<4 * kPrefetchUnits>(hp);  // the W prefetch stays in flight
-    wait_ids<4 * kPrefetchUnits>(ids);    // older than the chunk: they have landed too
+    for (int x = kAhead; x < kPrefetchUnits; ++x) load_unit(x, areg[x]);
+    wait_pieces<4 * kBehind>(hp);         // the other units stay in flight
+    wait_ids<4 * kBehind>(ids);           // older than the chunk: they have landed too
     store_chunk(0);
     __syncthreads();
     const int id0 = ids[0], id1 = ids[1], id2 = ids[2];
