@@ -484,6 +484,83 @@ __global__ void __launch_bounds__(BLOCK ? kBlockMergeLaunch : T) step_finalize_t
     tree_select_by_count<T, true>(t, N2, keys, cnt, wave_tot);
 }
 
+// The same for one or two hidden rows in one workgroup, two waves per row as in the merge without a level: the results meet in LDS,
+// and nobody takes a ticket, waits for stores or reads other workgroups' results back (a level of n = 1, k = 5000, d = 3072, m = 8
+// 14.0 -> 13.7 us, n = 2, m = 4 14.1 -> 13.4).  More rows' waves are in each other's way on one CU (n = 4, k = 5000, d = 1024 11.4 /
+// 11.6, n = 8, k = 5000, d = 3072 15.9 / 16.3).
+template <int T>
+__global__ void __launch_bounds__(T) step_finalize_tree_few_kernel(const FinalizeArgs f, int stage_keys) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ float s_lse[T / (2 * kWave)], s_logp[T];
+    __shared__ int s_ids[T];
+    static_assert(T / (2 * kWave) * 64 <= T, "a thread per candidate: up to 64 tokens per row");
+    __shared__ unsigned long long s_keys[T];
+    __shared__ unsigned s_above[T];
+    const int lane = lane_id(), tid = (int)threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = f.n * f.m;
+    int N2 = kWave;
+    while (N2 < N) N2 <<= 1;
+    // (on its way while the rows are merged)
+    const float parent = tid < N ? f.tree_cum[tid / f.m] : 0.f;
+    s_above[tid] = 0u;
+    constexpr int kRows = T / (2 * kWave);
+    if (w < f.n) {
+        auto lse_fn = [&]() {
+            __syncthreads();
+            return s_lse[w];
+        };
+        finalize_row(f.pkeys + (size_t)w * f.nlists * f.L, f.nlists, f.L, f.m, false, lse_fn, reinterpret_cast<unsigned long long *>(smem) + (size_t)w * stage_keys,
+                     s_ids + w * f.m, s_logp + w * f.m, lane);
+    } else {
+        const int i = w - kRows;
+        if (i >= 0 && i < f.n) {
+            const float lse = row_lse(f.pms + (size_t)i * f.nlists, f.nlists, lane);
+            if (lane == 0) {
+                s_lse[i] = lse;
+                f.lse_buf[i] = lse;
+                if (f.out_lse) f.out_lse[i] = lse;
+            }
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+    int id = 0;
+    if (tid < N2) {
+        unsigned long long key = kNoKey;
+        if (tid < N) {
+            id = s_ids[tid];
+            const float logp = s_logp[tid];
+            f.out_ids[tid] = id;
+            f.out_logp[tid] = logp;
+            key = make_key(__fadd_rn(parent, logp), tid);      // one fp32 addition
+        }
+        s_keys[tid] = key;
+    }
+    __syncthreads();
+    // T / N2 threads share a candidate's scan
+    const int c = tid & (N2 - 1), part = tid / N2, each = N2 * N2 / T;
+    const unsigned long long mine = s_keys[c];
+    unsigned above = 0;
+    for (int j = part * each; j < (part + 1) * each; j += 4) {
+        unsigned long long t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = s_keys[j + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) above += t[u] > mine ? 1u : 0u;
+    }
+    if (N2 < T) {
+        if (above != 0u) atomicAdd(&s_above[c], above);
+        __syncthreads();
+        above = s_above[c];
+    }
+    if (tid < N && (int)above < f.tree_K) {
+        f.tree_parent[above] = tid / f.m;
+        f.tree_token[above] = id;
+        f.tree_score[above] = key_logit(mine);
+    }
+}
+
 // Merges the per-tile partials, many lists of them: eight waves per hidden row.
 __global__ void __launch_bounds__(kBlockMergeLaunch) step_finalize_block_kernel(const FinalizeArgs f) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -504,6 +581,8 @@ __global__ void __launch_bounds__(2 * kWave) step_finalize_kernel(const Finalize
     finalize_row_pair(f, i, o, reinterpret_cast<unsigned long long *>(smem), &s_lse, lane_id(),
                       __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
 }
+
+constexpr int kTreeFewLds = kMaxDynamicLds - 8 * 1024;      // (the kernel's own arrays beside it)
 
 template <int MAXW, bool XG = false>
 hipError_t launch_mfma_inst(const MfmaArgs &a, size_t lds, hipStream_t st) {
@@ -587,6 +666,11 @@ hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t s
                                       reinterpret_cast<const void *>(step_finalize_tree_kernel<512, true>)},
                                      kMaxDynamicLds);
     if (e != hipSuccess) return e;
+    static LdsLimitOnce few_limit;
+    e = allow_dynamic_lds(few_limit,
+                          {reinterpret_cast<const void *>(step_finalize_tree_few_kernel<128>),
+                           reinterpret_cast<const void *>(step_finalize_tree_few_kernel<256>)}, kTreeFewLds);
+    if (e != hipSuccess) return e;
     const bool block = block_merge_pays(f.n, f.nlists, f.L, f.m);
     lds += kDirectPad * sizeof(unsigned long long);
     if (block && lds < sizeof(BlockMergeLds)) lds = sizeof(BlockMergeLds);
@@ -594,6 +678,14 @@ hipError_t launch_step_finalize(const FinalizeArgs &f, size_t lds, hipStream_t s
         // one hidden row per workgroup; LDS: the merge's staging, then the ranking's keys and counters
         const int N = f.n * f.m;
         if (f.indexed || N > kFinalizeTreeMaxN || f.ticket == nullptr) return hipErrorInvalidValue;
+        if (!block && f.n <= 2 && f.n * lds <= (size_t)kTreeFewLds) {
+            const int stage_keys = (int)(lds / sizeof(unsigned long long));
+            if (f.n == 1)
+                hipLaunchKernelGGL(step_finalize_tree_few_kernel<128>, dim3(1), dim3(128), lds, st, f, stage_keys);
+            else
+                hipLaunchKernelGGL(step_finalize_tree_few_kernel<256>, dim3(1), dim3(256), 2 * lds, st, f, stage_keys);
+            return hipGetLastError();
+        }
         int N2 = kWave;
         while (N2 < N) N2 <<= 1;
         const size_t need = (size_t)N2 * 12 + 256;
