@@ -1289,7 +1289,8 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         a.slice_ranges = d % (2048 * p.splits) == 0 ? 1 : 0;
         a.zpitch = p.splits > 1 ? slice_pitch(k) : k;
         if (p.row_select) a.zbuf = out_logp_full != nullptr && p.splits == 1 ? out_logp_full : reinterpret_cast<float *>(wsb + p.off_zbuf);
-        a.zvec = a.zpitch % 4 == 0 && aligned(a.zbuf, 16) ? 1 : 0;
+        // (a group of four must not reach into the next tile, whose workgroup stores there, nor behind the row)
+        a.zvec = a.zpitch % 4 == 0 && aligned(a.zbuf, 16) && (16 * p.row_groups + p.extra_rows) % 4 == 0 ? 1 : 0;
         a.row_pack = tf.row_pack;
         a.indexed = tf.indexed;
         a.ksplit = p.ksplit;

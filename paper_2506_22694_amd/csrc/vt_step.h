@@ -123,7 +123,7 @@ struct MfmaArgs {
     // [splits][n][zpitch] and row_select_kernel adds the slices up (zpitch = k without slices)
     int splits, slice_units, slice_more, slice_ranges;
     int zpitch;
-    int zvec;                 // more than 8 hidden rows: zbuf is 16-byte aligned and zpitch a multiple of four
+    int zvec;                 // more than 8 hidden rows: zbuf is 16-byte aligned, zpitch and the tile's rows multiples of four
     // or null: a word the kernel sets to zero (the merge kernel behind it counts its workgroups there when a tree
     // level is fused; the kernel boundary orders the two)
     unsigned *ticket_clear;

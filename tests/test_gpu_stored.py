@@ -64,6 +64,24 @@ def test_stored_logits_of_short_rows(n, k, d, m):
     _check(h, W, map_, same, m, vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True))
 
 
+# Tiles of 129 to 139 rows: the logits of a tile end inside a group of four, and so do those of the last one
+@pytest.mark.parametrize("n,k,d,m,tile", [(17, 33008, 256, 16, 129), (40, 33280, 128, 10, 130), (12, 35328, 128, 9, 138), (64, 35364, 128, 16, 139)])
+def test_stored_logits_of_tiles_that_are_no_multiple_of_four(n, k, d, m, tile):
+    plan = vt.draft_head_step_plan(n, k, d, m)
+    assert f"tile_rows={tile} " in plan and "row_select" in plan, plan
+    h, W, map_, same = _inputs(n, k, d, seed=k)
+    # the logits' buffer is the caller's: what lies behind it stays
+    full = torch.full((n * k + 64,), 7.0, device="cuda")
+    ids, logp, lse = torch.empty((n, m), dtype=torch.int32, device="cuda"), torch.empty((n, m), device="cuda"), torch.empty(n, device="cuda")
+    ws = vt.StepWorkspace(n, k, d, m, h.device)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    rc = vt.load_library().vt_draft_head_step(p(h), 1, n, p(W), 1, k, d, p(map_), m, p(ids), p(logp), p(lse), p(full), p(ws.buf),
+                                                   ctypes.c_size_t(ws.buf.numel()), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    assert bool((full[n * k:] == 7.0).all())
+    _check(h, W, map_, same, m, (ids, logp, lse, full[:n * k].view(n, k)))
+
+
 # The library's own memory, a tree level, several heads and a workspace of the size that earlier versions asked for
 @pytest.mark.parametrize("n,k,d,m", [(224, 4300, 4096, 4), (40, 4300, 8192, 8), (70, 4100, 1024, 8)])
 def test_the_other_ways_to_a_stored_step(n, k, d, m):
