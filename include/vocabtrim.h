@@ -208,8 +208,8 @@ int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_ty
  * ws_bytes: the partial results of the step live in an array of
  * VT_STATIC_WS_BYTES bytes that the library itself holds on every GPU it runs
  * on, from the first use of the library on that GPU until the process ends
- * (the partial logits of steps of more than 8 rows on heads of few rows, which
- * vt_draft_head_step cuts into slices of the columns, in another one of 48 MiB).
+ * (steps of more than 8 rows that vt_draft_head_step runs on stored logits,
+ * given the workspace it asks for, in another one of 48 MiB).
  * The call allocates and frees nothing (its first call on a device asks the
  * runtime for the array's address; make that call outside stream capture).
  *   - A shape for which vt_draft_head_step accepts no workspace of

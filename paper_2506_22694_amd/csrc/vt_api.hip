@@ -33,7 +33,7 @@ inline int launch_status() { return device_status(hipGetLastError()); }
 // GPU, alive from the moment the code object is loaded on it until the process ends.  In host code the array's
 // name is only a handle; the device address is asked for once per device and kept.
 static __device__ __align__(256) unsigned char scratch[VT_STATIC_WS_BYTES];
-// ... and of the steps that plan_stored() has run by slices, which have the bits of vt_draft_head_step's only if they run the same
+// ... and of the steps that plan_stored() has run on stored logits, which have the bits of vt_draft_head_step's only if they run the same
 // way: 256 hidden rows by 256 tiles of 160 logits, 4 MiB of re-laid h and the small parts of a workspace at most.
 constexpr size_t kStaticStoredBytes = (size_t)48 << 20;
 static __device__ __align__(256) unsigned char stored_scratch[kStaticStoredBytes];
@@ -94,6 +94,8 @@ struct StepPlan {
     bool twin = false;
     bool wide = false;         // more than 64 hidden rows
     int splits = 1;            // more than 8 hidden rows: slices of the columns, a workgroup each per tile
+    int parts = 0;             // ... stored logits: parts of a row with a (max, sum-exp) each, of part_rows rows, per_tile to a tile
+    int part_rows = 0, per_tile = 0;
     size_t list_room = 0;      // ... bytes that the lists of fewer hidden rows may take on smaller tiles
 };
 
@@ -428,6 +430,18 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
     return p;
 }
 
+// Parts of a row of stored logits, what a wave of the matrix-core kernels holds of it (16 logits, or half of a tile).  False: too many.
+bool row_parts(StepPlan &p, int k) {
+    p.extra_rows = (p.extra_rows + 3) / 4 * 4;      // (groups of four logits do not reach into the next tile)
+    const int tile_rows = 16 * p.row_groups + p.extra_rows, tiles = (k + tile_rows - 1) / tile_rows;
+    p.per_tile = p.wide ? 2 : p.row_groups + (p.extra_rows != 0 ? 1 : 0);
+    p.part_rows = p.wide ? 8 * p.row_groups : 16;
+    p.parts = (tiles - 1) * p.per_tile + (k - (tiles - 1) * tile_rows + p.part_rows - 1) / p.part_rows;
+    if (p.parts <= vt::kRowPartsMax) return true;
+    p.parts = 0;
+    return false;
+}
+
 // The same step with its logits stored, and the columns cut into slices where that pays: larger tiles then (each hidden row is
 // read once per tile, so small tiles of many hidden rows are bound by reading h), a workgroup per tile and slice, and
 // row_select_kernel adds the partial logits up.  ok = false: the plan itself is the better one.
@@ -441,16 +455,22 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
 StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     StepPlan p = whole;
     p.ok = false;
-    if (!whole.ok || !whole.mfma || n <= vt::kGemvMaxN || k > vt::kRowSelectWhole || d > 8192) return p;
+    if (!whole.ok || !whole.mfma || n <= vt::kGemvMaxN || (k > vt::kRowSelectWhole && !whole.row_select)) return p;
+    const bool sliceable = k <= vt::kRowSelectWhole && d <= 8192;
     const int CUS = round_workgroups();
     const bool few = n <= vt::kRowsKernelMaxN;
     const int hrows = whole.wide ? 16 * whole.NT : whole.NT * 16;      // hidden rows of the tiles
     const int rows = 16 * whole.row_groups + whole.extra_rows, rounds = (whole.nlists + CUS - 1) / CUS;
+    // Lists of up to 8 tokens take a tile's epilogue 5 to 10 us from 129 hidden rows on, and the logits of rows of up to 32768 with their
+    // parts less (lists / parts: n = 217, k = 26262, d = 3072, m = 4 61.4 / 57.5 us, n = 100, k = 29182, d = 1024, m = 8 24.4 / 23.1, n = 145,
+    // k = 9145, m = 1 -2 %; n = 66, m = 8 1.6 % faster, but n = 76, k = 22786, m = 1 28.9 / 30.1, n = 90, m = 4 29.5 / 29.8)
+    const bool by_parts = whole.row_select || (!few && n >= 65 + 9 * (vt::kRowSelectMinLManyRows - m));
     const double as_planned = 9.0 + rounds * ((double)rows * d / 18e3 + (double)hrows * d / 38e3) +
-                              (whole.row_select ? k * (2.2e-6 * n + 3.5e-5) : rounds * 0.03 * n - 0.6);
+                              (!whole.row_select ? rounds * 0.03 * n - 0.6 : std::max(k * (2.2e-6 * n + 3.5e-5), few ? 1.5 : 0.0));
     double best = as_planned;
     for (int g : {4, 8, 10}) {
-        if (few && g > 8) continue;
+        // (d = 1024: parts / slices n = 194, k = 5070, m = 4 18.6 / 20.1 us, n = 135, k = 4461, m = 1 16.5 / 16.7)
+        if (!sliceable || (few && g > 8) || (by_parts && d <= 1024)) continue;
         const int tiles = (k + 16 * g - 1) / (16 * g), S = CUS / tiles;
         if (S < (few ? 4 : g > 8 ? 3 : 2) || d / 128 < 2 * S) continue;
         const double t = 10.3 + (double)16 * g * d / S / 19e3 + (double)hrows * d / S / 34e3 + (double)S * k * (1.8e-6 * n + 6.5e-5);
@@ -463,7 +483,9 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     if (p.splits > 1) {
         p.extra_rows = 0;
         p.twin = false;
-    } else if (few || whole.row_select || rows >= vt::kMfmaTileRows || n * m < 256 || (double)n * (m * m / 2 + 12) * 34e3 < (double)k * k) {
+    } else if (by_parts && row_parts(p, k)) {
+        // in one piece, with the (max, sum-exp) of the rows' parts
+    } else if (!sliceable || few || whole.row_select || rows >= vt::kMfmaTileRows || n * m < 256 || (double)n * (m * m / 2 + 12) * 34e3 < (double)k * k) {
         return p;
     }
     // (in one piece: lists of more than 64 hidden rows cost a tile 6 to 10 us, the logits of small heads less.  n = 256 / 128, lists / stored:
@@ -472,6 +494,10 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     p.list_room = 0;
     cut_many_rows(p, n, k, m);
     size_t off = round_up(p.off_lse + (size_t)n * sizeof(float), 256);
+    if (p.parts != 0) {
+        p.off_pms = off;
+        off = round_up(off + (size_t)n * (k / 14 + 32) * sizeof(unsigned long long), 256);      // (of the smallest tiles)
+    }
     p.off_zbuf = off;
     off = round_up(off + (size_t)p.splits * n * slice_pitch(k) * sizeof(float), 256);
     p.off_hpack = 0;
@@ -554,12 +580,12 @@ size_t step_ws_bytes(int n, int k, int d, int m) {
     return b;
 }
 
-// The same with room for plan_stored()'s plans: of n rows and, at the ends of the kernels' ranges, of fewer.  What a program asks for;
-// a step accepts step_ws_bytes(), the size that earlier versions returned.
+// The same with room for plan_stored()'s plans, of n rows and of fewer (slices come and go with the rows).  What a program asks for; a
+// step accepts step_ws_bytes(), the size that earlier versions returned.
 size_t full_step_ws_bytes(int n, int k, int d, int m) {
     size_t b = step_ws_bytes(n, k, d, m);
-    for (int r : {32, 64, 128, 192, 256, n > vt::kMfmaMaxN ? n % vt::kMfmaMaxN : n}) {
-        if (b == 0 || r < 1 || r > n) continue;
+    if (b == 0) return 0;
+    for (int r = vt::kGemvMaxN + 1; r <= n && r <= vt::kMfmaMaxN; ++r) {
         const StepPlan p = plan_stored(plan_step(r, k, d, m, VT_BF16), r, k, d, m);
         if (p.ok && p.bytes > b) b = p.bytes;
     }
@@ -590,9 +616,11 @@ MultiLayout multi_layout(int n, int d, const int32_t *k, int n_heads, int m, boo
     for (int hd = 0; hd < n_heads; ++hd) {
         // a head may receive any number of the n rows, and the plan (hence its workspace) changes with it
         for (int nn = 1; nn <= n; ++nn) {
-            const size_t b = full ? full_step_ws_bytes(nn, k[hd], d, m) : step_ws_bytes(nn, k[hd], d, m);
+            const size_t b = step_ws_bytes(nn, k[hd], d, m);
             if (b > step) step = b;
         }
+        const size_t b = full ? full_step_ws_bytes(n, k[hd], d, m) : 0;
+        if (b > step) step = b;
     }
     // ... and several heads' tiles in one launch: at most one tile per CU, whatever their shape
     if (n <= vt::kGemvMaxN) {
@@ -1241,9 +1269,9 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
             if (e != hipSuccess) return device_status(e);
         }
         if (p.row_select) {
-            const hipError_t e = vt::launch_row_select(a.zbuf, map, n, k, m, 1, k, nullptr, out_ids, out_logp, out_lse, lse_buf, st);
+            const hipError_t e = vt::launch_row_select(a.zbuf, map, n, k, m, 1, k, nullptr, out_ids, out_logp, out_lse, lse_buf, nullptr, st);
             if (e != hipSuccess) return device_status(e);
-            if (out_logp_full != nullptr) vt::launch_sub_lse(out_logp_full, lse_buf, n, k, st);
+            if (out_logp_full != nullptr) vt::launch_sub_lse(out_logp_full, k, out_logp_full, lse_buf, n, k, st);
             if (tf.cum != nullptr) {       // the fused tree level needs the merge kernel: run the expansion kernel
                 vt::TreeArgs t;
                 t.parent_cum = tf.cum;
@@ -1287,8 +1315,9 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         a.slice_units = d / 128 / p.splits;
         a.slice_more = d / 128 % p.splits;
         a.slice_ranges = d % (2048 * p.splits) == 0 ? 1 : 0;
-        a.zpitch = p.splits > 1 ? slice_pitch(k) : k;
-        if (p.row_select) a.zbuf = out_logp_full != nullptr && p.splits == 1 ? out_logp_full : reinterpret_cast<float *>(wsb + p.off_zbuf);
+        a.zpitch = p.splits > 1 || p.parts != 0 ? slice_pitch(k) : k;
+        a.parts = p.parts;
+        if (p.row_select) a.zbuf = out_logp_full != nullptr && p.splits == 1 && p.parts == 0 ? out_logp_full : reinterpret_cast<float *>(wsb + p.off_zbuf);
         // (a group of four must not reach into the next tile, whose workgroup stores there, nor behind the row)
         a.zvec = a.zpitch % 4 == 0 && aligned(a.zbuf, 16) && (16 * p.row_groups + p.extra_rows) % 4 == 0 ? 1 : 0;
         a.row_pack = tf.row_pack;
@@ -1306,9 +1335,14 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
                                           : vt::launch_head_mfma_rows(p.NT, a, p.lds, st);
         if (e != hipSuccess) return device_status(e);
         if (p.row_select) {
-            e = vt::launch_row_select(a.zbuf, map, n, k, m, a.splits, a.zpitch, out_logp_full, out_ids, out_logp, out_lse, lse_buf, st);
+            const vt::RowParts parts{pms, p.parts, p.per_tile, p.part_rows, 16 * p.row_groups + p.extra_rows};
+            e = vt::launch_row_select(a.zbuf, map, n, k, m, a.splits, a.zpitch, out_logp_full, out_ids, out_logp, out_lse, lse_buf,
+                                      p.parts != 0 ? &parts : nullptr, st);
             if (e != hipSuccess) return device_status(e);
-            if (out_logp_full != nullptr) vt::launch_sub_lse(out_logp_full, lse_buf, n, k, st);
+            if (out_logp_full != nullptr) {
+                const float *z = p.parts != 0 ? a.zbuf : out_logp_full;
+                vt::launch_sub_lse(z, p.parts != 0 ? a.zpitch : k, out_logp_full, lse_buf, n, k, st);
+            }
             return VT_OK;
         }
         vt::FinalizeArgs f{};
@@ -1335,7 +1369,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         if (e != hipSuccess) return device_status(e);
     }
     if (out_logp_full != nullptr)
-        vt::launch_sub_lse(out_logp_full, lse_buf, n, k, st);
+        vt::launch_sub_lse(out_logp_full, k, out_logp_full, lse_buf, n, k, st);
     return VT_OK;
 }
 

@@ -12,7 +12,8 @@
 // candidates per hidden row; a merge kernel finishes the step.  Or the logits go straight from the accumulators to memory for
 // row_select_kernel (16 bytes per lane; by way of LDS they took a tile of 128 x 224 4.7 us, now 1.5: n = 256, k = 32768, d = 8192
 // 157.7 -> 155.5 us, n = 33, k = 21900, d = 4096, m = 16 42.9 / 41.1) -- those of all columns, or of a slice of them: heads of few
-// rows are cut into larger tiles and slices (plan_stored in vt_api.hip).
+// rows are cut into larger tiles and slices (plan_stored in vt_api.hip).  Beside all columns' logits goes the (max, sum-exp) of what each
+// wave holds of a row, 1 to 2 us for n = 256 where the lists of m tokens take 10.
 #include "vt_device.h"
 #include "vt_launch.h"
 #include "vt_ranges.h"
@@ -127,6 +128,35 @@ __device__ __forceinline__ void store_logits4(float *dst, const f32x4 &v) {
 // multiple of four the last group reaches into the row's padding).
 __device__ __forceinline__ void store_z4(float *z, int i, int n, int pitch, int row, int rows_b, const f32x4 &v) {
     if (i < n && row < rows_b) *reinterpret_cast<f32x4 *>(z + (size_t)i * pitch + row) = v;
+}
+
+// (max, sum-exp) of a hidden row's logits in this wave, four in every accumulator v[x * STEP], 16 rows of the head each: a lane
+// has its four, three more lanes (16, 32 and 48 further) the others.
+template <int N, int STEP>
+__device__ __forceinline__ void publish_part(const f32x4 *v, unsigned long long *pms, bool there, int lgrp) {
+    auto across = [](float x, auto op) {
+        auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        unsigned y = op(r[0], r[1]);
+        r = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+        return __uint_as_float(op(r[0], r[1]));
+    };
+    float top = fmaxf(fmaxf(v[0].x, v[0].y), fmaxf(v[0].z, v[0].w));
+#pragma unroll
+    for (int x = 1; x < N; ++x) top = fmaxf(top, fmaxf(fmaxf(v[x * STEP].x, v[x * STEP].y), fmaxf(v[x * STEP].z, v[x * STEP].w)));
+    top = across(top, OpMaxF32{});
+    float sum = 0.f;
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+        sum += (__expf(v[x * STEP].x - top) + __expf(v[x * STEP].y - top)) + (__expf(v[x * STEP].z - top) + __expf(v[x * STEP].w - top));
+    sum = across(sum, OpAddF32{});
+    if (there && lgrp == 0) *pms = ((unsigned long long)__float_as_uint(sum) << 32) | __float_as_uint(top);
+}
+// Logits behind the tile's end (its last row again) become -inf: nothing of the row.
+__device__ __forceinline__ void end_rows(f32x4 &v, int row, int rows_b) {
+    v.x = row < rows_b ? v.x : -INFINITY;
+    v.y = row + 1 < rows_b ? v.y : -INFINITY;
+    v.z = row + 2 < rows_b ? v.z : -INFINITY;
+    v.w = row + 3 < rows_b ? v.w : -INFINITY;
 }
 
 // Workgroup epilogue on the logit tile of hidden rows i_lo .. i_hi - 1 (row i at zt + (i - i_lo) * tp), Q * 16 >= rows_b.
@@ -300,11 +330,31 @@ head_mfma_kernel(const MfmaArgs a) {
     }
     if constexpr (OUT != kTileLists) {
         float *z = a.zbuf + (size_t)columns.slice * a.n * a.zpitch + row0;
+        const bool by_parts = OUT == kTileStored && a.parts != 0;
+        if (by_parts && (rows_b < 16 * GR)) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) end_rows(acc[t], 16 * rg + 4 * lgrp, rows_b);
+            if (X) end_rows(acc[NA - 1], kMfmaTileRows + 4 * lgrp, rows_b);
+        }
         if (active) {
 #pragma unroll
             for (int t = 0; t < TPW; ++t) store_z4(z, 16 * (t0 + t) + lrow, a.n, a.zpitch, 16 * rg + 4 * lgrp, min(rows_b, 16 * RG), acc[t]);
         }
         if (ninth) store_z4(z, 16 * w + lrow, a.n, a.zpitch, kMfmaTileRows + 4 * lgrp, rows_b, acc[NA - 1]);
+        if (by_parts) {
+            unsigned long long *pms = a.pms + (size_t)blockIdx.x * GR;
+            if (active) {
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) {
+                    const int i = 16 * (t0 + t) + lrow;
+                    publish_part<1, 1>(acc + t, pms + (size_t)i * a.parts + rg, i < a.n && 16 * rg < rows_b, lgrp);
+                }
+            }
+            if (ninth) {
+                const int i = 16 * w + lrow;
+                publish_part<1, 1>(acc + NA - 1, pms + (size_t)i * a.parts + kStepWaves, i < a.n && kMfmaTileRows < rows_b, lgrp);
+            }
+        }
     } else {
         wait_and_sync<0>();      // every wave is done with the ring: it becomes the logit tile
 
@@ -469,11 +519,24 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
     }
     if constexpr (OUT != kTileLists) {
         float *z = a.zbuf + (size_t)columns.slice * a.n * a.zpitch + row0;
+        const bool by_parts = OUT == kTileStored && a.parts != 0;
+        if (by_parts && rows_b < TM) {
+#pragma unroll
+            for (int x = 0; x < NP; ++x) end_rows(acc[x], 16 * (wm * MT + x / NTT) + 4 * lgrp, rows_b);
+        }
 #pragma unroll
         for (int t = 0; t < NTT; ++t) {
 #pragma unroll
             for (int m = 0; m < MT; ++m)
                 store_z4(z, 16 * (wn * NTT + t) + lrow, a.n, a.zpitch, 16 * (wm * MT + m) + 4 * lgrp, rows_b, acc[m * NTT + t]);
+        }
+        if (by_parts) {
+            unsigned long long *pms = a.pms + 2 * blockIdx.x + wm;
+#pragma unroll
+            for (int t = 0; t < NTT; ++t) {
+                const int i = 16 * (wn * NTT + t) + lrow;
+                publish_part<MT, NTT>(acc + t, pms + (size_t)i * a.parts, i < a.n && 16 * wm * MT < rows_b, lgrp);
+            }
         }
     } else {
         wait_and_sync<0>();      // every wave is done with the ring: it becomes the logit tile

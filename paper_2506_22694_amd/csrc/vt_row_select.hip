@@ -15,6 +15,8 @@
 //   ranking of the logits alone runs beside that trip, and the sum of exponentials waits for no barrier of its own: a percent of
 //   a step, n = 128 on 32768 x 2048, m = 16 43.1 -> 42.7 us, and more with many candidates, n = 4 on 3880 x 4096, m = 24 23.2 -> 20.3)
 //   if more than 1024 logits reach T (massive ties, e.g. h = 0) the m best are extracted one by one.
+// Where the matrix-core kernel leaves the (max, sum-exp) of a row's parts beside the logits, all of this reads a few dozen parts
+// instead of the row (row_select_parts_kernel).
 #include "vt_device.h"
 #include "vt_step.h"
 
@@ -191,6 +193,51 @@ __device__ __forceinline__ void collect_stretch(const float (&v)[VALS], int base
     }
 }
 
+// The m best of ncand <= kRowMaxCand candidates by counting: the logits alone are ranked while the trip to the map for the target
+// ids is under way; one that is there twice is ranked by its keys (distinct target ids: distinct keys).  Equal logits meet at the
+// place of the first of them: a second comparison per logit, for equality, took 5 us where a short row has no threshold
+// and all of its 651 logits are candidates.  All threads call it; rawv is -inf behind the candidates, cand kNoKey, s_at zero.
+__device__ __forceinline__ int keys_above(const unsigned long long *cand, int ncand, unsigned long long key) {
+    unsigned above = 0;
+    for (int x = 0; x < ncand; x += 8) {
+        unsigned long long t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = cand[x + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) above += t[u] > key ? 1u : 0u;
+    }
+    return (int)above;
+}
+__device__ __forceinline__ void rank_candidates(const float *rawv, const int *rawj, unsigned long long *cand, unsigned *s_at,
+                                                const int *__restrict__ map, int ncand, int m, float lse, int *__restrict__ ids, float *__restrict__ logp) {
+    const int tid = threadIdx.x;
+    unsigned long long key = 0ull;
+    int above = m;
+    if (tid < ncand) {
+        const float mine = rawv[tid];
+        const int id = map[rawj[tid]];
+        above = 0;
+        for (int x = 0; x < ncand; x += 8) {
+            float t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = rawv[x + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) above += t[u] > mine ? 1 : 0;
+        }
+        if (above < m) atomicAdd(&s_at[above], 1u);
+        key = make_key(mine, id);
+        cand[tid] = key;
+    }
+    __syncthreads();
+    if (above < m) {
+        if (s_at[above] > 1u) above = keys_above(cand, ncand, key);
+        if (above < m) {
+            ids[above] = key_id(key);
+            logp[above] = key_logit(key) - lse;
+        }
+    }
+}
+
 // kRowWhole: the row fits one stretch (k <= 32768), which stays in registers for the second pass.  kRowSift: longer rows are
 // read once, too: the first stretch's threshold is one that m logits of the row reach, so what later stretches have to offer above it
 // is collected as they go by (with the next stretch requested before the one at hand is folded), and the row's own
@@ -327,50 +374,19 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     for (int q = 0; q < kRowWaves; ++q) S += redf[q];     // fixed order: reproducible
     const float lse = M + __logf(S);
     if (ncand <= kRowMaxCand) {
-        // rank by counting: keys are distinct (distinct target ids).  Without a thinning in between the logits alone are ranked
-        // while the trip to the map for the target id is under way; one that is there twice is ranked by its keys.
-        auto by_keys = [&](unsigned long long key) {
-            unsigned above = 0;
-            for (int x = 0; x < ncand; x += 8) {
-                unsigned long long t[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) t[u] = cand[x + u];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) above += t[u] > key ? 1u : 0u;
-            }
-            return (int)above;
-        };
-        auto store = [&](int above, unsigned long long key) {
-            if (above < m) {
-                out_ids[(size_t)i * m + above] = key_id(key);
-                out_logp[(size_t)i * m + above] = key_logit(key) - lse;
-            }
-        };
         static_assert(kRowMaxCand == kRowThreads && kRowMaxCand % 8 == 0 && kRaw % 8 == 0);
         if constexpr (SIFT) {
-            if (tid < ncand) store(by_keys(cand[tid]), cand[tid]);
-        } else {
-            // (equal logits meet at the place of the first of them: a second comparison per logit, for equality, took 5 us where a
-            // short row has no threshold and all of its 651 logits are candidates)
-            unsigned long long key = 0ull;
-            int above = m;
+            // (thinned out: the keys are there)
             if (tid < ncand) {
-                const float mine = rawv[tid];
-                const int id = map[rawj[tid]];
-                above = 0;
-                for (int x = 0; x < ncand; x += 8) {
-                    float t[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) t[u] = rawv[x + u];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) above += t[u] > mine ? 1 : 0;
+                const unsigned long long key = cand[tid];
+                const int above = keys_above(cand, ncand, key);
+                if (above < m) {
+                    out_ids[(size_t)i * m + above] = key_id(key);
+                    out_logp[(size_t)i * m + above] = key_logit(key) - lse;
                 }
-                if (above < m) atomicAdd(&s_at[above], 1u);
-                key = make_key(mine, id);
-                cand[tid] = key;
             }
-            __syncthreads();
-            if (above < m) store(s_at[above] > 1u ? by_keys(key) : above, key);
+        } else {
+            rank_candidates(rawv, rawj, cand, s_at, map, ncand, m, lse, out_ids + (size_t)i * m, out_logp + (size_t)i * m);
         }
     } else {
         // massive ties: take the best remaining key, m times (each round re-reads the row from the L2)
@@ -402,9 +418,208 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     }
 }
 
+// The same on rows whose parts' (max, sum-exp) are there, 16 to 80 logits each: a threshold that at least m parts' maxima reach is one
+// that m logits reach, and only the parts that reach it are read.  A CU reads a row of 32768 logits in 4 us and takes as many
+// exponentials of them; the parts' sums cost the kernel before a wave's few registers (n = 179, k = 35010, d = 1024, m = 16: this kernel 13.5 -> 6.6 us,
+// the step 42.0 -> 31.1; n = 256, k = 32768, d = 8192 11.4 -> 7.1; n = 10, k = 113259, d = 3072, m = 10 130.8 -> 123.1).  What is left is a chain of
+// trips: the parts, their logits, the map.  E: parts per thread.
+// Parts that are read, about 54 (m <= 16) or 130 (m = 64) of them where logits are random: a wave whose best parts are none of the 256 best
+// (512 with several parts to a wave) is one row in a million.  More: many equal logits.
+constexpr int kMaxPicked = 512;
+__device__ __forceinline__ int picked_limit(int m) { return m <= kRowWaves ? kMaxPicked / 2 : kMaxPicked; }
+template <int E>
+__global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const float *__restrict__ z, const int *__restrict__ map, int k, int m, int pitch,
+                                                                       RowParts rp, int *__restrict__ out_ids, float *__restrict__ out_logp,
+                                                                       float *__restrict__ out_lse, float *__restrict__ lse_buf) {
+    __shared__ float redf[kRowWaves];
+    __shared__ unsigned long long red64[kRowWaves];
+    __shared__ unsigned tmax[2 * kRowWaves];
+    __shared__ unsigned long long cand[kRowMaxCand];
+    __shared__ float rawv[kRowMaxCand];
+    __shared__ int rawj[kRowMaxCand];
+    __shared__ int2 picked[kMaxPicked];           // the parts: first logit, behind the last
+    __shared__ unsigned s_npicked, s_nraw;
+    __shared__ unsigned s_at[kRowMaxTokens];      // candidates with that many larger logits
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int i = blockIdx.x;
+    const float *zr = z + (size_t)i * pitch;
+    const unsigned long long *pr = rp.pms + (size_t)i * rp.parts;
+    // every wave has its share of every stretch of the row
+    unsigned long long part[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) part[e] = pr[min(e * kRowThreads + lane * kRowWaves + w, rp.parts - 1)];
+    if (tid == 0) {
+        s_npicked = 0u;
+        s_nraw = 0u;
+    }
+    cand[tid] = kNoKey;
+    rawv[tid] = -INFINITY;
+    if (tid < kRowMaxTokens) s_at[tid] = 0u;
+    float lm = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (e * kRowThreads + lane * kRowWaves + w >= rp.parts) part[e] = 0xFF800000ull;      // (-inf, 0)
+        lm = fmaxf(lm, __uint_as_float((unsigned)part[e]));
+    }
+    unsigned T, Mo;
+    row_threshold(lm, m, tmax, lane, w, T, Mo);
+    const float M = from_orderable_f32(Mo);
+    const float Tf = threshold_f32(T);
+    float ls = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const float top = __uint_as_float((unsigned)part[e]);
+        ls += __uint_as_float((unsigned)(part[e] >> 32)) * __expf(top - M);
+        if (top >= Tf) {
+            const int x = e * kRowThreads + lane * kRowWaves + w;
+            if (x < rp.parts) {
+                const unsigned slot = atomicAdd(&s_npicked, 1u);
+                const int tile = x / rp.per_tile * rp.tile_rows, first = tile + x % rp.per_tile * rp.part_rows;
+                if (slot < (unsigned)kMaxPicked) picked[slot] = make_int2(first, min(k, min(tile + rp.tile_rows, first + rp.part_rows)));
+            }
+        }
+    }
+    const float Sw = wave_sum(ls);
+    if (lane == 0) redf[w] = Sw;
+    __syncthreads();
+    const int npicked = (int)s_npicked;
+    float S = 0.f;
+#pragma unroll
+    for (int q = 0; q < kRowWaves; ++q) S += redf[q];     // fixed order: reproducible
+    const float lse = M + __logf(S);
+
+    // Logits of the picked parts, four to a load
+    const int vecs = rp.part_rows / 4, total = npicked * vecs;
+    auto collect = [&]() {
+        float Tt = Tf;      // (a thread that finds no room goes on no further, see collect_stretch)
+        for (int x0 = 0; x0 < total; x0 += 2 * kRowThreads) {
+            float4 v[2];
+            int j[2], end[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int x = x0 + u * kRowThreads + tid, from = min(x, total - 1);
+                const int2 p = picked[from / vecs];
+                j[u] = p.x + from % vecs * 4;
+                end[u] = x < total ? p.y : 0;
+                v[u] = *reinterpret_cast<const float4 *>(zr + min(j[u], pitch - 4));
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (j[u] < end[u] && fmaxf(fmaxf(v[u].x, v[u].y), fmaxf(v[u].z, v[u].w)) >= Tt) {
+                    const float q[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        if (q[c] >= Tt && j[u] + c < k) {
+                            const unsigned slot = atomicAdd(&s_nraw, 1u);
+                            if (slot < (unsigned)kRowMaxCand) {
+                                rawv[slot] = q[c];
+                                rawj[slot] = j[u] + c;
+                            } else {
+                                Tt = INFINITY;
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    };
+    int ncand = kRowMaxCand + 1;
+    if (npicked <= picked_limit(m)) {
+        collect();
+        ncand = (int)s_nraw;
+    }
+    if (ncand <= kRowMaxCand) {
+        rank_candidates(rawv, rawj, cand, s_at, map, ncand, m, lse, out_ids + (size_t)i * m, out_logp + (size_t)i * m);
+    } else {
+        // Many equal logits, or many large ones side by side.  Every thread's best key, of which at least m reach Tk; all that reach Tk
+        // are ranked: two readings of the row, where one per token took n = 256, k = 32768, d = 2048, m = 16 with all logits equal
+        // 266 us (now 76; n = 100, k = 20000, m = 8 87 / 55).  Too many again: one per token.
+        auto for_keys = [&](auto f) {
+            for (int j0 = 0; j0 < k; j0 += 8 * kRowThreads) {
+                float v[8];
+                int id[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int j = min(j0 + u * kRowThreads + tid, k - 1);
+                    v[u] = zr[j];
+                    id[u] = map[j];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (j0 + u * kRowThreads + tid < k && v[u] >= Tf) f(make_key(v[u], id[u]));
+                }
+            }
+        };
+        unsigned long long best = kNoKey;
+        for_keys([&](unsigned long long key) { best = key > best ? key : best; });
+        unsigned long long Tk = kNoKey;
+        for (int q = 0; q < m; q += kRowWaves) {
+            Tk = wave_max_u64(best);
+            if (best == Tk) best = kNoKey;
+        }
+        __syncthreads();      // (s_nraw has been read)
+        if (tid == 0) s_nraw = 0u;
+        if (lane == 0) red64[w] = Tk;
+        __syncthreads();
+        Tk = red64[0];
+#pragma unroll
+        for (int q = 1; q < kRowWaves; ++q) Tk = red64[q] < Tk ? red64[q] : Tk;
+        for_keys([&](unsigned long long key) {
+            if (key >= Tk) {
+                const unsigned slot = atomicAdd(&s_nraw, 1u);
+                if (slot < (unsigned)kRowMaxCand) cand[slot] = key;
+                else Tk = ~0ull;      // (no room: nothing more to find)
+            }
+        });
+        __syncthreads();
+        const int nkeys = (int)s_nraw;
+        if (nkeys <= kRowMaxCand) {
+            if (tid < nkeys) {
+                const unsigned long long key = cand[tid];
+                const int above = keys_above(cand, nkeys, key);
+                if (above < m) {
+                    out_ids[(size_t)i * m + above] = key_id(key);
+                    out_logp[(size_t)i * m + above] = key_logit(key) - lse;
+                }
+            }
+        } else {
+            unsigned long long prev = ~0ull;
+            for (int r = 0; r < m; ++r) {
+                best = kNoKey;
+                for_keys([&](unsigned long long key) { best = key < prev && key > best ? key : best; });
+                best = block_max_u64(best, red64, lane, w);
+                if (tid == 0) {
+                    out_ids[(size_t)i * m + r] = key_id(best);
+                    out_logp[(size_t)i * m + r] = key_logit(best) - lse;
+                }
+                prev = best;
+            }
+        }
+    }
+    if (tid == 0) {
+        lse_buf[i] = lse;
+        if (out_lse != nullptr) out_lse[i] = lse;
+    }
+}
+
 // splits > 1: z is [splits][n][pitch], pitch a multiple of four, k <= kRowSpan; z_out [n, k] or null takes the sums.
 hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, float *z_out, int *out_ids,
-                             float *out_logp, float *out_lse, float *lse_buf, hipStream_t st) {
+                             float *out_logp, float *out_lse, float *lse_buf, const RowParts *by_parts, hipStream_t st) {
+    if (by_parts != nullptr) {
+        const RowParts &rp = *by_parts;
+        if (splits != 1 || pitch % 4 != 0 || pitch < k || (reinterpret_cast<uintptr_t>(z) & 15) != 0 || rp.parts < 1 || rp.parts > kRowPartsMax ||
+            rp.part_rows % 4 != 0 || rp.tile_rows % 4 != 0 || rp.per_tile * rp.part_rows < rp.tile_rows ||
+            (int64_t)((rp.parts + rp.per_tile - 1) / rp.per_tile) * rp.tile_rows < k)
+            return hipErrorInvalidValue;
+        auto launch = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, pitch, rp, out_ids, out_logp, out_lse, lse_buf);
+            return hipGetLastError();
+        };
+        if (rp.parts <= kRowThreads) return launch(&row_select_parts_kernel<1>);
+        if (rp.parts <= 2 * kRowThreads) return launch(&row_select_parts_kernel<2>);
+        return launch(&row_select_parts_kernel<8>);
+    }
     auto launch = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, splits, pitch, z_out, out_ids, out_logp, out_lse, lse_buf);
         return hipGetLastError();

@@ -124,10 +124,21 @@ struct MfmaArgs {
     int splits, slice_units, slice_more, slice_ranges;
     int zpitch;
     int zvec;                 // more than 8 hidden rows: zbuf is 16-byte aligned, zpitch and the tile's rows multiples of four
+    // stored logits of more than 8 hidden rows, zvec != 0, no slices: parts of a hidden row whose (max, sum-exp) go to pms [n][parts]
+    // beside the logits (RowParts); 0: none
+    int parts;
     // or null: a word the kernel sets to zero (the merge kernel behind it counts its workgroups there when a tree
     // level is fused; the kernel boundary orders the two)
     unsigned *ticket_clear;
 };
+
+// The parts of a row of logits: tiles of tile_rows logits, each of per_tile parts of part_rows (a multiple of four; a tile's last
+// part and the row's may be shorter).
+struct RowParts {
+    const unsigned long long *pms;     // [n][parts]  max | sumexp << 32
+    int parts, per_tile, part_rows, tile_rows;
+};
+constexpr int kRowPartsMax = 8192;     // of a row that row_select_kernel takes
 
 // Several heads in one launch of the matrix-core kernel (up to 8 hidden rows in all): the tiles of head i are the
 // workgroups tile_first[i] .. tile_first[i + 1] - 1, each head cut into tiles of the launch's height on its own
@@ -190,8 +201,8 @@ hipError_t launch_head_gemv_np2(bool bf16, int CS, const StepArgs &a, size_t lds
 hipError_t launch_head_gemv_np4(bool bf16, int CS, const StepArgs &a, size_t lds, hipStream_t st);
 hipError_t launch_head_gemv_np8(bool bf16, int CS, const StepArgs &a, size_t lds, hipStream_t st);
 
-// logp_full[i, j] -= lse[i]
-void launch_sub_lse(float *logp_full, const float *lse, int n, int k, hipStream_t st);
+// logp_full[i, j] = z[i, j] - lse[i], z's rows `pitch` floats apart (z may be logp_full)
+void launch_sub_lse(const float *z, int pitch, float *logp_full, const float *lse, int n, int k, hipStream_t st);
 // zero the arrival counters
 void launch_ws_clear(unsigned *p, int nwords, hipStream_t st);
 void launch_stream_read(const void *p, size_t bytes, unsigned *sink, hipStream_t st);
@@ -207,7 +218,9 @@ void launch_scatter_rows(const int *ids_s, const float *logp_s, const float *lse
                          float *out_logp, float *out_lse, const RowList &rows, hipStream_t st);
 // per-row tail on stored logits z [n, k]: lse, the m best logits and their target ids (one workgroup per row).  splits > 1: z is
 // [splits][n][pitch], partial logits of the columns' slices; their sums go to z_out [n, k] as well unless it is null
+// by_parts, or null: only the parts with the largest logits are read (splits = 1, parts <= kRowPartsMax, z 16-byte aligned and pitch a
+// multiple of four that the logits fill up with -inf)
 hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, float *z_out, int *out_ids,
-                             float *out_logp, float *out_lse, float *lse_buf, hipStream_t st);
+                             float *out_logp, float *out_lse, float *lse_buf, const RowParts *by_parts, hipStream_t st);
 
 }  // namespace vt

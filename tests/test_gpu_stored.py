@@ -21,7 +21,7 @@ def _inputs(n, k, d, seed=0):
     return h, W, torch.randperm(2 * k, generator=g, device="cuda")[:k].sort().values.to(torch.int32), same
 
 
-def _check(h, W, map_, same, m, got):
+def _check(h, W, map_, same, m, got, by_id=True):
     ids, logp, lse, full = got
     z = h.double() @ W.double().t()
     ref = z - z.logsumexp(1, keepdim=True)
@@ -33,8 +33,13 @@ def _check(h, W, map_, same, m, got):
     assert torch.equal(dup, dup[:, :1].expand_as(dup))
     # the tokens are those of the step's own logits, equal ones in ascending order of their ids
     order = torch.sort(full, dim=1, descending=True, stable=True).indices[:, :m]
-    assert torch.equal(ids, map_[order])
     assert torch.equal(logp, torch.gather(full, 1, order))
+    if by_id:
+        assert torch.equal(ids, map_[order])
+    else:      # (large logits differ by less than the rounding of their log-probs: which of those comes first is in the logits alone)
+        at = torch.searchsorted(map_, ids)
+        assert torch.equal(map_[at], ids) and torch.equal(torch.gather(full, 1, at), logp)
+        assert all(len(set(row)) == m for row in ids.tolist())
 
 
 # Slices: the kernels' ranges of hidden rows and their edges, tiles of 64, 128 and 160 rows, two to eight slices of equal and of
@@ -64,22 +69,79 @@ def test_stored_logits_of_short_rows(n, k, d, m):
     _check(h, W, map_, same, m, vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True))
 
 
-# Tiles of 129 to 139 rows: the logits of a tile end inside a group of four, and so do those of the last one
+# Heads for tiles of 129 to 139 rows: the logits of such a tile, and of the last one, end inside a group of four.  With all of the
+# workspace, and with the smallest that is accepted (tiles of just that many rows)
 @pytest.mark.parametrize("n,k,d,m,tile", [(17, 33008, 256, 16, 129), (40, 33280, 128, 10, 130), (12, 35328, 128, 9, 138), (64, 35364, 128, 16, 139)])
 def test_stored_logits_of_tiles_that_are_no_multiple_of_four(n, k, d, m, tile):
     plan = vt.draft_head_step_plan(n, k, d, m)
-    assert f"tile_rows={tile} " in plan and "row_select" in plan, plan
+    assert f"tile_rows={(tile + 3) // 4 * 4} " in plan and "row_select" in plan, plan
     h, W, map_, same = _inputs(n, k, d, seed=k)
     # the logits' buffer is the caller's: what lies behind it stays
     full = torch.full((n * k + 64,), 7.0, device="cuda")
     ids, logp, lse = torch.empty((n, m), dtype=torch.int32, device="cuda"), torch.empty((n, m), device="cuda"), torch.empty(n, device="cuda")
-    ws = vt.StepWorkspace(n, k, d, m, h.device)
+    ws, L = vt.StepWorkspace(n, k, d, m, h.device), vt.load_library()
     p = lambda t: ctypes.c_void_p(t.data_ptr())
-    rc = vt.load_library().vt_draft_head_step(p(h), 1, n, p(W), 1, k, d, p(map_), m, p(ids), p(logp), p(lse), p(full), p(ws.buf),
-                                                   ctypes.c_size_t(ws.buf.numel()), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
-    assert rc == 0
-    assert bool((full[n * k:] == 7.0).all())
-    _check(h, W, map_, same, m, (ids, logp, lse, full[:n * k].view(n, k)))
+    step = lambda size: L.vt_draft_head_step(p(h), 1, n, p(W), 1, k, d, p(map_), m, p(ids), p(logp), p(lse), p(full), p(ws.buf),
+                                             ctypes.c_size_t(size), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    lo, hi = 0, ws.nbytes // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if step(256 * mid) == 0 else (mid, hi)
+    for size in (256 * hi, ws.nbytes):
+        full.fill_(7.0)
+        assert step(size) == 0
+        assert bool((full[n * k:] == 7.0).all())
+        _check(h, W, map_, same, m, (ids, logp, lse, full[:n * k].view(n, k)))
+
+
+# Stored logits of which only the parts with the largest are read: both kernels and every tile height, tiles of 132 to 144 rows, last
+# tiles of one row and of one part, one, two and eight parts per thread, fewer parts than waves, rows off multiples of four, rounds,
+# two workgroups to a CU, h re-laid.  Hidden row 0 has 1500 large logits side by side (more than the candidates' room where the parts
+# beside them set the threshold), hidden row 1 is zero (all logits tie)
+@pytest.mark.parametrize("n,k,d,m", [
+    (9, 130, 128, 9), (10, 4097, 256, 16), (33, 8200, 128, 64), (64, 12289, 128, 10), (20, 20001, 128, 33), (40, 26001, 256, 16), (12, 33008, 256, 10),
+    (64, 36865, 128, 64), (17, 44003, 128, 12), (24, 65537, 128, 16), (64, 100001, 128, 9), (9, 131073, 128, 64), (65, 7000, 128, 8), (100, 4100, 1024, 4),
+    (128, 12001, 128, 1), (129, 16383, 256, 8), (150, 20002, 128, 64), (192, 32768, 256, 8), (193, 30001, 128, 5), (256, 32767, 128, 64), (200, 40001, 128, 16),
+    (256, 70001, 128, 9), (256, 5000, 8192, 33), (256, 24000, 8192, 16)])
+def test_stored_logits_by_parts(n, k, d, m):
+    plan = vt.draft_head_step_plan(n, k, d, m)
+    assert "row_select" in plan, plan
+    h, W, map_, same = _inputs(n, k, d, seed=n + m)
+    h[1] = 0
+    lo = k // 3 // 4 * 4
+    W[lo:lo + 1500] += (0.1 * h[0].float() / h[0].float().norm()).to(W.dtype)
+    W[same] = W[3].clone()
+    ids, logp, lse, full = vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True)
+    _check(h, W, map_, same, m, (ids, logp, lse, full), by_id=False)
+    assert torch.equal(ids[1], map_[:m])
+    plain = vt.draft_head_step(h, W, map_, m)
+    assert torch.equal(plain[0], ids) and torch.equal(plain[1], logp)
+
+
+# All logits of a row equal, and as many above: the lowest ids, wherever they lie -- first, last, at random, and away from one wave of
+# the workgroup that looks for them (which then has none of the best)
+@pytest.mark.parametrize("n,k,d,m", [(70, 9000, 128, 8), (256, 32768, 128, 16), (12, 40004, 128, 64), (128, 20001, 128, 8)])
+@pytest.mark.parametrize("order", ["ascending", "descending", "random", "apart"])
+def test_equal_logits_by_parts(n, k, d, m, order):
+    assert "row_select" in vt.draft_head_step_plan(n, k, d, m)
+    h, W, _, same = _inputs(n, k, d)
+    h[2:] = 0
+    W[:4096] = W[0].clone()      # row 1: 4096 equal logits, and those of `same`
+    h[1] = W[0] * 50
+    ids = torch.arange(k, device="cuda", dtype=torch.int32)
+    if order == "descending":
+        ids = ids.flip(0)
+    elif order == "random":
+        ids = ids[torch.randperm(k, device="cuda")]
+    elif order == "apart":
+        first = (torch.arange(k, device="cuda") % 1024 < 64).int()
+        ids = torch.argsort(torch.argsort(first, stable=True), stable=True).int()
+    got, logp = vt.draft_head_step(h, W, ids, m)
+    z = h[:2].double() @ W.double().t()
+    assert (logp[:2] - (z - z.logsumexp(1, keepdim=True)).topk(m, 1).values).abs().max().item() < 5e-5
+    assert torch.equal(got[1], torch.cat([ids[:4096], ids[[j for j in same if j >= 4096]]]).sort().values[:m])
+    assert torch.equal(got[2:], torch.arange(m, device="cuda", dtype=torch.int32).expand(n - 2, m))
+    assert (logp[2:] + torch.log(torch.tensor(float(k)))).abs().max().item() < 5e-6
 
 
 # The library's own memory, a tree level, several heads and a workspace of the size that earlier versions asked for
