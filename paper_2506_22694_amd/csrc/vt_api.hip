@@ -430,16 +430,35 @@ StepPlan plan_step_impl(int n, int k, int d, int m, int dtype, bool force_gemv, 
     return p;
 }
 
-// Parts of a row of stored logits, what a wave of the matrix-core kernels holds of it (16 logits, or half of a tile).  False: too many.
-bool row_parts(StepPlan &p, int k) {
+// Parts of a row of stored logits: what a wave of the matrix-core kernels for more than 8 hidden rows holds of it (16 logits, or half
+// of a tile), 64 logits of a tile up to 8.  False: too many.
+bool row_parts(StepPlan &p, int n, int k) {
     p.extra_rows = (p.extra_rows + 3) / 4 * 4;      // (groups of four logits do not reach into the next tile)
-    const int tile_rows = 16 * p.row_groups + p.extra_rows, tiles = (k + tile_rows - 1) / tile_rows;
-    p.per_tile = p.wide ? 2 : p.row_groups + (p.extra_rows != 0 ? 1 : 0);
-    p.part_rows = p.wide ? 8 * p.row_groups : 16;
+    const int tile_rows = p.gemv ? p.rpb : 16 * p.row_groups + p.extra_rows, tiles = (k + tile_rows - 1) / tile_rows;
+    p.part_rows = n <= vt::kGemvMaxN ? vt::kFewRowsPart : p.wide ? 8 * p.row_groups : 16;
+    p.per_tile = (tile_rows + p.part_rows - 1) / p.part_rows;
     p.parts = (tiles - 1) * p.per_tile + (k - (tiles - 1) * tile_rows + p.part_rows - 1) / p.part_rows;
+    if (!p.gemv) p.nlists = p.nblocks = tiles;
     if (p.parts <= vt::kRowPartsMax) return true;
     p.parts = 0;
     return false;
+}
+// The layout of a workspace for logits in `splits` slices.
+void lay_out_stored(StepPlan &p, int n, int k, int d) {
+    size_t off = round_up(p.off_lse + (size_t)n * sizeof(float), 256);
+    if (p.parts != 0) {
+        p.off_pms = off;
+        const size_t parts = n <= vt::kGemvMaxN ? (size_t)p.parts : (size_t)k / 14 + 32;      // (of the smallest tiles)
+        off = round_up(off + n * parts * sizeof(unsigned long long), 256);
+    }
+    p.off_zbuf = off;
+    off = round_up(off + (size_t)p.splits * n * slice_pitch(k) * sizeof(float), 256);
+    p.off_hpack = 0;
+    if (p.wide && vt::packs_h(p.NT / 4, n, d)) {
+        p.off_hpack = off;
+        off = round_up(off + (size_t)d * p.NT * 32, 256);
+    }
+    p.bytes = off;
 }
 
 // The same step with its logits stored, and the columns cut into slices where that pays: larger tiles then (each hidden row is
@@ -455,6 +474,16 @@ bool row_parts(StepPlan &p, int k) {
 StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     StepPlan p = whole;
     p.ok = false;
+    // Up to 8 hidden rows parts pay where a row's whole reading takes longer than a second trip (whole / by parts: n = 2, d = 3072, m = 16,
+    // k = 16000 24.0 / 24.2 us, 18000 28.8 / 28.3, 32975 43.0 / 38.2; n = 4, d = 1024, m = 64, k = 30000 22.4 / 22.6; n = 4, k = 79094, d = 2048,
+    // m = 16 66.7 / 57.4) -- and on rows so short that a wave of row_select_kernel holds none of their groups of four, where
+    // all logits become candidates (n = 4, k = 3000, d = 1024, m = 16 46.8 / 10.7)
+    const bool few_by_parts = k > (m <= 16 ? vt::kRowSelectWhole / 2 : vt::kRowSelectWhole) || (k % 4 == 0 && k <= 15 * 256);
+    if (whole.ok && n <= vt::kGemvMaxN && whole.row_select && few_by_parts && row_parts(p, n, k)) {
+        lay_out_stored(p, n, k, d);
+        p.ok = true;
+        return p;
+    }
     if (!whole.ok || !whole.mfma || n <= vt::kGemvMaxN || (k > vt::kRowSelectWhole && !whole.row_select)) return p;
     const bool sliceable = k <= vt::kRowSelectWhole && d <= 8192;
     const int CUS = round_workgroups();
@@ -483,7 +512,7 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     if (p.splits > 1) {
         p.extra_rows = 0;
         p.twin = false;
-    } else if (by_parts && row_parts(p, k)) {
+    } else if (by_parts && row_parts(p, n, k)) {
         // in one piece, with the (max, sum-exp) of the rows' parts
     } else if (!sliceable || few || whole.row_select || rows >= vt::kMfmaTileRows || n * m < 256 || (double)n * (m * m / 2 + 12) * 34e3 < (double)k * k) {
         return p;
@@ -493,19 +522,7 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     p.row_select = true;
     p.list_room = 0;
     cut_many_rows(p, n, k, m);
-    size_t off = round_up(p.off_lse + (size_t)n * sizeof(float), 256);
-    if (p.parts != 0) {
-        p.off_pms = off;
-        off = round_up(off + (size_t)n * (k / 14 + 32) * sizeof(unsigned long long), 256);      // (of the smallest tiles)
-    }
-    p.off_zbuf = off;
-    off = round_up(off + (size_t)p.splits * n * slice_pitch(k) * sizeof(float), 256);
-    p.off_hpack = 0;
-    if (p.wide && vt::packs_h(p.NT / 4, n, d)) {
-        p.off_hpack = off;
-        off = round_up(off + (size_t)d * p.NT * 32, 256);
-    }
-    p.bytes = off;
+    lay_out_stored(p, n, k, d);
     p.ok = p.lds <= (size_t)vt::kMaxDynamicLds;
     return p;
 }
@@ -585,9 +602,12 @@ size_t step_ws_bytes(int n, int k, int d, int m) {
 size_t full_step_ws_bytes(int n, int k, int d, int m) {
     size_t b = step_ws_bytes(n, k, d, m);
     if (b == 0) return 0;
-    for (int r = vt::kGemvMaxN + 1; r <= n && r <= vt::kMfmaMaxN; ++r) {
-        const StepPlan p = plan_stored(plan_step(r, k, d, m, VT_BF16), r, k, d, m);
-        if (p.ok && p.bytes > b) b = p.bytes;
+    for (int r = 1; r <= n && r <= vt::kMfmaMaxN; ++r) {
+        for (int dtype : {VT_BF16, VT_F32}) {
+            if (dtype == VT_F32 && r > vt::kGemvMaxN) continue;
+            const StepPlan p = plan_stored(plan_step(r, k, d, m, dtype), r, k, d, m);
+            if (p.ok && p.bytes > b) b = p.bytes;
+        }
     }
     return b;
 }
@@ -1227,7 +1247,9 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         a.pkeys = pkeys;
         a.out_logp_full = out_logp_full;
         a.zbuf = nullptr;
-        if (p.row_select) a.zbuf = out_logp_full != nullptr ? out_logp_full : reinterpret_cast<float *>(wsb + p.off_zbuf);
+        a.zpitch = p.parts != 0 ? slice_pitch(k) : k;
+        a.parts = p.parts;
+        if (p.row_select) a.zbuf = out_logp_full != nullptr && p.parts == 0 ? out_logp_full : reinterpret_cast<float *>(wsb + p.off_zbuf);
         if (tf.indexed && (p.row_select || out_logp_full != nullptr)) return VT_ERR_SHAPE;
         a.row_pack = tf.indexed ? tf.row_pack : 0x0706050403020100ull;
         // a tree level fused behind the merge kernel: rows in order, at most kFinalizeTreeMaxN candidates
@@ -1269,9 +1291,11 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
             if (e != hipSuccess) return device_status(e);
         }
         if (p.row_select) {
-            const hipError_t e = vt::launch_row_select(a.zbuf, map, n, k, m, 1, k, nullptr, out_ids, out_logp, out_lse, lse_buf, nullptr, st);
+            const vt::RowParts parts{pms, p.parts, p.per_tile, p.part_rows, p.rpb};
+            const hipError_t e = vt::launch_row_select(a.zbuf, map, n, k, m, 1, a.zpitch, nullptr, out_ids, out_logp, out_lse, lse_buf,
+                                                       p.parts != 0 ? &parts : nullptr, st);
             if (e != hipSuccess) return device_status(e);
-            if (out_logp_full != nullptr) vt::launch_sub_lse(out_logp_full, k, out_logp_full, lse_buf, n, k, st);
+            if (out_logp_full != nullptr) vt::launch_sub_lse(a.zbuf, a.zpitch, out_logp_full, lse_buf, n, k, st);
             if (tf.cum != nullptr) {       // the fused tree level needs the merge kernel: run the expansion kernel
                 vt::TreeArgs t;
                 t.parent_cum = tf.cum;

@@ -389,10 +389,11 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     if (a.zbuf != nullptr) {
         // store-only tail: the tile's logits go to z [n, k]; a workgroup per hidden row finishes the step
         // (row_select_kernel).  One wave copies a hidden row's 128 logits (512 contiguous bytes) at a time.
+        const int per_tile = (tile_rows + kFewRowsPart - 1) / kFewRowsPart;
         for (int i = w; i < a.n; i += NW) {
             const float *src = zt + (size_t)i * tp;
-            float *dst = a.zbuf + (size_t)i * a.k + row0;
-            for (int t = lane; t < rows_b; t += kWave) dst[t] = src[t];
+            store_logits(a.zbuf + (size_t)i * a.zpitch + row0, a.parts != 0 ? a.pms + (size_t)i * a.parts + blockIdx.x * per_tile : nullptr, rows_b, lane,
+                         [&](int t) { return src[t]; });
         }
         return;
     }

@@ -54,7 +54,9 @@ struct StepArgs {
     unsigned long long *pms;    // [n, nblocks]  max | sumexp << 32
     unsigned long long *pkeys;  // [n, nblocks, L] candidate keys, sorted descending per list
     float *out_logp_full;     // [n, k] or null (raw logits are written first, lse subtracted later)
-    float *zbuf;              // [n, k] or null: store the logits and leave the rest of the step to row_select_kernel
+    float *zbuf;              // [n, zpitch] or null: store the logits and leave the rest of the step to row_select_kernel
+    int zpitch;
+    int parts;                // ... and the (max, sum-exp) of their parts to pms [n][parts]; 0: none
     // hidden row i is row (row_pack >> 8 i) & 255 of h: 0x0706050403020100 for rows 0 .. n-1, other values when
     // the rows are picked out of a larger batch (several heads per call)
     unsigned long long row_pack;
@@ -97,7 +99,7 @@ struct MfmaArgs {
     unsigned long long *pkeys;  // [n, nlists, L]
     float *out_logp_full;     // [n, k] or null
     void *hpack;              // more than 64 hidden rows: or null; h re-laid stage by stage, d * 512 bytes
-    float *zbuf;              // [n, k] or null: store the logits and leave the rest of the step to row_select_kernel
+    float *zbuf;              // [n, zpitch] or null: store the logits and leave the rest of the step to row_select_kernel
     // indexed != 0 (n <= 8 only): hidden row i is row (row_pack >> 8 i) & 255 of h -- rows picked out of a
     // larger batch (several heads per call); the merge kernel maps the output rows the same way
     unsigned long long row_pack;
@@ -124,8 +126,8 @@ struct MfmaArgs {
     int splits, slice_units, slice_more, slice_ranges;
     int zpitch;
     int zvec;                 // more than 8 hidden rows: zbuf is 16-byte aligned, zpitch and the tile's rows multiples of four
-    // stored logits of more than 8 hidden rows, zvec != 0, no slices: parts of a hidden row whose (max, sum-exp) go to pms [n][parts]
-    // beside the logits (RowParts); 0: none
+    // stored logits (of more than 8 hidden rows: zvec != 0, no slices): parts of a hidden row whose (max, sum-exp) go to
+    // pms [n][parts] beside the logits (RowParts); 0: none
     int parts;
     // or null: a word the kernel sets to zero (the merge kernel behind it counts its workgroups there when a tree
     // level is fused; the kernel boundary orders the two)
@@ -139,6 +141,7 @@ struct RowParts {
     int parts, per_tile, part_rows, tile_rows;
 };
 constexpr int kRowPartsMax = 8192;     // of a row that row_select_kernel takes
+constexpr int kFewRowsPart = 64;       // logits of a part, up to 8 hidden rows
 
 // Several heads in one launch of the matrix-core kernel (up to 8 hidden rows in all): the tiles of head i are the
 // workgroups tile_first[i] .. tile_first[i + 1] - 1, each head cut into tiles of the launch's height on its own
@@ -219,7 +222,7 @@ void launch_scatter_rows(const int *ids_s, const float *logp_s, const float *lse
 // per-row tail on stored logits z [n, k]: lse, the m best logits and their target ids (one workgroup per row).  splits > 1: z is
 // [splits][n][pitch], partial logits of the columns' slices; their sums go to z_out [n, k] as well unless it is null
 // by_parts, or null: only the parts with the largest logits are read (splits = 1, parts <= kRowPartsMax, z 16-byte aligned and pitch a
-// multiple of four that the logits fill up with -inf)
+// multiple of four)
 hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, float *z_out, int *out_ids,
                              float *out_logp, float *out_lse, float *lse_buf, const RowParts *by_parts, hipStream_t st);
 

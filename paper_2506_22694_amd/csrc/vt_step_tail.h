@@ -301,6 +301,23 @@ __device__ __forceinline__ void block_epilogue_large(const float *zrow, int S, i
                                                              pms_slot, pkeys_slot, lane, share, cand);
 }
 
+// --------------------------------------------------------------------- logits of a tile to memory
+// One wave stores a hidden row's logits of this tile (up to 8 hidden rows), and beside them, unless pms is null, the (max, sum-exp)
+// of every 64 of them, by which row_select_kernel finds the parts it reads.
+static_assert(kFewRowsPart == kWave);
+template <typename Logit>
+__device__ __forceinline__ void store_logits(float *__restrict__ z, unsigned long long *__restrict__ pms, int rows_b, int lane, Logit logit) {
+    for (int t0 = 0; t0 < rows_b; t0 += kWave) {
+        const int t = t0 + lane;
+        float v = -INFINITY;
+        if (t < rows_b) z[t] = v = logit(t);
+        if (pms != nullptr) {
+            const float top = wave_max(v), sum = wave_sum(__expf(v - top));
+            if (lane == 0) pms[t0 / kWave] = ((unsigned long long)__float_as_uint(sum) << 32) | __float_as_uint(top);
+        }
+    }
+}
+
 // ------------------------------------------------------------------ four hidden rows per pass
 // Tiles of at most 16 Q logits per hidden row (Q = 8: 128 rows, Q = 9: 144) and L <= 16: the 16 lanes of DPP row g
 // rank hidden row i0 + g (Q logits per lane), so a wave finishes four hidden rows in

@@ -11,10 +11,10 @@ from paper_2506_22694_amd import binding
 pytestmark = pytest.mark.gpu
 
 
-def _inputs(n, k, d, seed=0):
+def _inputs(n, k, d, seed=0, dtype=torch.bfloat16):
     g = torch.Generator(device="cuda").manual_seed(seed)
-    W = torch.randn(k, d, generator=g, device="cuda", dtype=torch.bfloat16).mul_(0.02)
-    h = torch.randn(n, d, generator=g, device="cuda", dtype=torch.bfloat16)
+    W = torch.randn(k, d, generator=g, device="cuda", dtype=dtype).mul_(0.02)
+    h = torch.randn(n, d, generator=g, device="cuda", dtype=dtype)
     # equal rows, in the first and last tile and slot: their logits are equal bit for bit
     same = sorted({0, 63, 64, k // 2, k - 2, k - 1})
     W[same] = W[3].clone()
@@ -96,17 +96,20 @@ def test_stored_logits_of_tiles_that_are_no_multiple_of_four(n, k, d, m, tile):
 
 # Stored logits of which only the parts with the largest are read: both kernels and every tile height, tiles of 132 to 144 rows, last
 # tiles of one row and of one part, one, two and eight parts per thread, fewer parts than waves, rows off multiples of four, rounds,
-# two workgroups to a CU, h re-laid.  Hidden row 0 has 1500 large logits side by side (more than the candidates' room where the parts
+# two workgroups to a CU, h re-laid; up to 8 rows both kernels, their parts of 64 and shorter ones.  Hidden row 0 has 1500 large logits side by side (more than the candidates' room where the parts
 # beside them set the threshold), hidden row 1 is zero (all logits tie)
 @pytest.mark.parametrize("n,k,d,m", [
     (9, 130, 128, 9), (10, 4097, 256, 16), (33, 8200, 128, 64), (64, 12289, 128, 10), (20, 20001, 128, 33), (40, 26001, 256, 16), (12, 33008, 256, 10),
     (64, 36865, 128, 64), (17, 44003, 128, 12), (24, 65537, 128, 16), (64, 100001, 128, 9), (9, 131073, 128, 64), (65, 7000, 128, 8), (100, 4100, 1024, 4),
     (128, 12001, 128, 1), (129, 16383, 256, 8), (150, 20002, 128, 64), (192, 32768, 256, 8), (193, 30001, 128, 5), (256, 32767, 128, 64), (200, 40001, 128, 16),
-    (256, 70001, 128, 9), (256, 5000, 8192, 33), (256, 24000, 8192, 16)])
+    (256, 70001, 128, 9), (256, 5000, 8192, 33), (256, 24000, 8192, 16),
+    (2, 16385, 512, 16), (8, 33008, 1024, 16), (3, 33013, 4096, 12), (5, 50204, 1024, 16), (2, 131075, 256, 64), (4, 3000, 1024, 16), (2, 40000, 2304, 33),
+    (3, 20003, 256, -16), (8, 3840, 512, -64)])
 def test_stored_logits_by_parts(n, k, d, m):
-    plan = vt.draft_head_step_plan(n, k, d, m)
+    dtype, m = (torch.float32, -m) if m < 0 else (torch.bfloat16, m)      # (up to 8 rows: both element types)
+    plan = vt.draft_head_step_plan(n, k, d, m, dtype)
     assert "row_select" in plan, plan
-    h, W, map_, same = _inputs(n, k, d, seed=n + m)
+    h, W, map_, same = _inputs(n, k, d, seed=n + m, dtype=dtype)
     h[1] = 0
     lo = k // 3 // 4 * 4
     W[lo:lo + 1500] += (0.1 * h[0].float() / h[0].float().norm()).to(W.dtype)
