@@ -147,6 +147,32 @@ def test_equal_logits_by_parts(n, k, d, m, order):
     assert (logp[2:] + torch.log(torch.tensor(float(k)))).abs().max().item() < 5e-6
 
 
+# Head rows whose logits are -inf: a whole tile's, the last one's (alone in its part on some of the shapes), and all but three.  Log-sum-exp
+# and log-probs are those of the other logits
+@pytest.mark.parametrize("n,k,d,m", [
+    (9, 16385, 128, 12), (17, 33008, 256, 16), (128, 12001, 128, 1), (256, 32767, 128, 9), (224, 4301, 4096, 4), (2, 33025, 512, 16), (5, 50204, 1024, 16),
+    (4, 3000, 1024, 16)])
+def test_logits_of_minus_infinity(n, k, d, m):
+    assert "row_select" in vt.draft_head_step_plan(n, k, d, m)
+    h, W, map_, _ = _inputs(n, k, d, seed=k)
+    h[:, 0] = 1
+    every = torch.arange(k, device="cuda")
+    for gone in ((every >= k // 2) & (every < k // 2 + 512) | (every == k - 1), (every != 5) & (every != k // 3) & (every != k - 1)):
+        Wx = W.clone()
+        Wx[gone, 0] = -float("inf")
+        ids, logp, lse, full = vt.draft_head_step(h, Wx, map_, m, return_lse=True, return_full=True)
+        z = h.double() @ Wx.double().t()
+        assert (lse - z.logsumexp(1)).abs().max().item() < 5e-5
+        ref = z - z.logsumexp(1, keepdim=True)
+        for got, want in ((full, ref), (logp, ref.topk(m, 1).values)):
+            there = want > -float("inf")
+            assert torch.equal(got > -float("inf"), there) and not bool(got.isnan().any())
+            assert (got - want)[there].abs().max().item() < 5e-5
+        # (what is left of m tokens is -inf, in ascending order of their ids)
+        order = torch.sort(full, dim=1, descending=True, stable=True).indices[:, :m]
+        assert torch.equal(ids, map_[order])
+
+
 # The library's own memory, a tree level, several heads and a workspace of the size that earlier versions asked for
 @pytest.mark.parametrize("n,k,d,m", [(224, 4300, 4096, 4), (40, 4300, 8192, 8), (70, 4100, 1024, 8)])
 def test_the_other_ways_to_a_stored_step(n, k, d, m):
