@@ -88,6 +88,7 @@ struct StepPlan {
     // workspace layout (byte offsets)
     size_t off_lse = 0, off_pms = 0, off_pkeys = 0, off_hpack = 0, off_zbuf = 0, bytes = 0;
     bool row_select = false;   // matrix-core path: logits stored, one workgroup per hidden row finishes
+    bool instead_of_lists = false;      // ... which a smaller workspace would have as lists
     int extra_rows = 0;        // matrix-core path: tile rows past the 128th
     // more than 8 hidden rows: 16-row groups of a tile, LDS offset of its target ids, epilogue passes
     int row_groups = 0, ids_off = 0, passes = 1;
@@ -519,6 +520,7 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     }
     // (in one piece: lists of more than 64 hidden rows cost a tile 6 to 10 us, the logits of small heads less.  n = 256 / 128, lists / stored:
     // k = 4300, m = 8 29.5 / 25.4 and 20.0 / 18.2 us on average of d = 1024, 2048 and 4096; k = 10000, m = 8 -7 and -4 %, m = 4 -4 and +2 %)
+    p.instead_of_lists = !whole.row_select;
     p.row_select = true;
     p.list_room = 0;
     cut_many_rows(p, n, k, m);
@@ -1292,7 +1294,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         }
         if (p.row_select) {
             const vt::RowParts parts{pms, p.parts, p.per_tile, p.part_rows, p.rpb};
-            const hipError_t e = vt::launch_row_select(a.zbuf, map, n, k, m, 1, a.zpitch, nullptr, out_ids, out_logp, out_lse, lse_buf,
+            const hipError_t e = vt::launch_row_select(a.zbuf, map, n, k, m, 1, a.zpitch, false, nullptr, out_ids, out_logp, out_lse, lse_buf,
                                                        p.parts != 0 ? &parts : nullptr, st);
             if (e != hipSuccess) return device_status(e);
             if (out_logp_full != nullptr) vt::launch_sub_lse(a.zbuf, a.zpitch, out_logp_full, lse_buf, n, k, st);
@@ -1360,7 +1362,7 @@ int run_step_group(const void *h, int n, const void *W_trim, int w_type, int k, 
         if (e != hipSuccess) return device_status(e);
         if (p.row_select) {
             const vt::RowParts parts{pms, p.parts, p.per_tile, p.part_rows, 16 * p.row_groups + p.extra_rows};
-            e = vt::launch_row_select(a.zbuf, map, n, k, m, a.splits, a.zpitch, out_logp_full, out_ids, out_logp, out_lse, lse_buf,
+            e = vt::launch_row_select(a.zbuf, map, n, k, m, a.splits, a.zpitch, p.instead_of_lists, out_logp_full, out_ids, out_logp, out_lse, lse_buf,
                                       p.parts != 0 ? &parts : nullptr, st);
             if (e != hipSuccess) return device_status(e);
             if (out_logp_full != nullptr) {

@@ -252,9 +252,13 @@ enum RowMode { kRowWhole, kRowSift, kRowTwice };
 // exponential and a comparison like any other: n = 40, k = 4149, d = 2048, m = 10 17.4 -> 15.9 us, n = 12, k = 10860, d = 3072, m = 16
 // 19.8 -> 19.2).  SLICED: z is [splits][gridDim.x][pitch], see load_slices; z_out, or null: where the
 // sums go.
+// NaN reaches no threshold.  A row with fewer than m other logits is ranked by the codes of all its logits, so that its tokens are
+// tokens of the head -- and so is, with nan_by_code, any row with a NaN: a step that keeps lists where its workspace has no room
+// for logits has the same tokens either way.
 template <RowMode MODE, bool VEC, int VALS, bool SLICED>
 __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__restrict__ z, const int *__restrict__ map,
-                                                                 int k, int m, int splits, int pitch, float *__restrict__ z_out,
+                                                                 int k, int m, int splits, int pitch, int nan_by_code,
+                                                                 float *__restrict__ z_out,
                                                                  int *__restrict__ out_ids,
                                                                  float *__restrict__ out_logp,
                                                                  float *__restrict__ out_lse,
@@ -373,7 +377,8 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
 #pragma unroll
     for (int q = 0; q < kRowWaves; ++q) S += redf[q];     // fixed order: reproducible
     const float lse = M + __logf(S);
-    if (ncand <= kRowMaxCand) {
+    const bool by_code = ncand < m || (nan_by_code != 0 && lse != lse);
+    if (ncand <= kRowMaxCand && !by_code) {
         static_assert(kRowMaxCand == kRowThreads && kRowMaxCand % 8 == 0 && kRaw % 8 == 0);
         if constexpr (SIFT) {
             // (thinned out: the keys are there)
@@ -389,7 +394,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
             rank_candidates(rawv, rawj, cand, s_at, map, ncand, m, lse, out_ids + (size_t)i * m, out_logp + (size_t)i * m);
         }
     } else {
-        // massive ties: take the best remaining key, m times (each round re-reads the row from the L2)
+        // massive ties, NaN: take the best remaining key, m times (each round re-reads the row from the L2)
         unsigned long long prev = ~0ull;
         for (int r = 0; r < m; ++r) {
             unsigned long long best = kNoKey;
@@ -398,7 +403,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
 #pragma unroll
                 for (int u = 0; u < VALS; ++u) {
                     const int j = stretch_index<VEC>(base, u, tid);
-                    if (j < k && v[u] >= Tf) {
+                    if (j < k && (v[u] >= Tf || by_code)) {
                         const unsigned long long key = make_key(v[u], map[j]);
                         if (key < prev && key > best) best = key;
                     }
@@ -429,7 +434,7 @@ constexpr int kMaxPicked = 512;
 __device__ __forceinline__ int picked_limit(int m) { return m <= kRowWaves ? kMaxPicked / 2 : kMaxPicked; }
 template <int E>
 __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const float *__restrict__ z, const int *__restrict__ map, int k, int m, int pitch,
-                                                                       RowParts rp, int *__restrict__ out_ids, float *__restrict__ out_logp,
+                                                                       int nan_by_code, RowParts rp, int *__restrict__ out_ids, float *__restrict__ out_logp,
                                                                        float *__restrict__ out_lse, float *__restrict__ lse_buf) {
     __shared__ float redf[kRowWaves];
     __shared__ unsigned long long red64[kRowWaves];
@@ -531,7 +536,8 @@ __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const flo
         collect();
         ncand = (int)s_nraw;
     }
-    if (ncand <= kRowMaxCand) {
+    const bool by_code = ncand < m || (nan_by_code != 0 && lse != lse);
+    if (ncand <= kRowMaxCand && !by_code) {
         rank_candidates(rawv, rawj, cand, s_at, map, ncand, m, lse, out_ids + (size_t)i * m, out_logp + (size_t)i * m);
     } else {
         // Many equal logits, or many large ones side by side.  Every thread's best key, of which at least m reach Tk; all that reach Tk
@@ -549,7 +555,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const flo
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    if (j0 + u * kRowThreads + tid < k && v[u] >= Tf) f(make_key(v[u], id[u]));
+                    if (j0 + u * kRowThreads + tid < k && (v[u] >= Tf || by_code)) f(make_key(v[u], id[u]));
                 }
             }
         };
@@ -606,8 +612,8 @@ __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const flo
 }
 
 // splits > 1: z is [splits][n][pitch], pitch a multiple of four, k <= kRowSpan; z_out [n, k] or null takes the sums.
-hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, float *z_out, int *out_ids,
-                             float *out_logp, float *out_lse, float *lse_buf, const RowParts *by_parts, hipStream_t st) {
+hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, bool nan_by_code, float *z_out,
+                             int *out_ids, float *out_logp, float *out_lse, float *lse_buf, const RowParts *by_parts, hipStream_t st) {
     if (by_parts != nullptr) {
         const RowParts &rp = *by_parts;
         if (splits != 1 || pitch % 4 != 0 || pitch < k || (reinterpret_cast<uintptr_t>(z) & 15) != 0 || rp.parts < 1 || rp.parts > kRowPartsMax ||
@@ -615,7 +621,7 @@ hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m
             (int64_t)((rp.parts + rp.per_tile - 1) / rp.per_tile) * rp.tile_rows < k)
             return hipErrorInvalidValue;
         auto launch = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, pitch, rp, out_ids, out_logp, out_lse, lse_buf);
+            hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, pitch, nan_by_code ? 1 : 0, rp, out_ids, out_logp, out_lse, lse_buf);
             return hipGetLastError();
         };
         if (rp.parts <= kRowThreads) return launch(&row_select_parts_kernel<1>);
@@ -623,7 +629,7 @@ hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m
         return launch(&row_select_parts_kernel<8>);
     }
     auto launch = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, splits, pitch, z_out, out_ids, out_logp, out_lse, lse_buf);
+        hipLaunchKernelGGL(kern, dim3(n), dim3(kRowThreads), 0, st, z, map, k, m, splits, pitch, nan_by_code ? 1 : 0, z_out, out_ids, out_logp, out_lse, lse_buf);
         return hipGetLastError();
     };
     if (splits > 1) {

@@ -223,7 +223,8 @@ void launch_scatter_rows(const int *ids_s, const float *logp_s, const float *lse
 // [splits][n][pitch], partial logits of the columns' slices; their sums go to z_out [n, k] as well unless it is null
 // by_parts, or null: only the parts with the largest logits are read (splits = 1, parts <= kRowPartsMax, z 16-byte aligned and pitch a
 // multiple of four)
-hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, float *z_out, int *out_ids,
-                             float *out_logp, float *out_lse, float *lse_buf, const RowParts *by_parts, hipStream_t st);
+// nan_by_code: rows with a NaN are ranked by the codes of their logits, as the lists are
+hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, bool nan_by_code, float *z_out,
+                             int *out_ids, float *out_logp, float *out_lse, float *lse_buf, const RowParts *by_parts, hipStream_t st);
 
 }  // namespace vt

@@ -173,6 +173,49 @@ def test_logits_of_minus_infinity(n, k, d, m):
         assert torch.equal(ids, map_[order])
 
 
+# Rows of NaN have tokens of the head for tokens, the lowest ids, as lists give them; so has a row with fewer other logits than tokens.
+# One NaN among a row's logits comes where it does with the smallest workspace that is accepted, which may keep lists
+@pytest.mark.parametrize("n,k,d,m", [
+    (224, 4300, 4096, 4), (20, 4806, 8192, 8), (128, 12001, 128, 8), (217, 26262, 128, 4), (9, 16385, 128, 12), (256, 32767, 128, 64), (24, 65537, 128, 16),
+    (2, 33025, 512, 16), (3, 8191, 128, 20), (4, 100000, 128, 33)])
+def test_logits_that_are_nan(n, k, d, m):
+    assert "row_select" in vt.draft_head_step_plan(n, k, d, m)
+    h, W, map_, _ = _inputs(n, k, d, seed=k)
+    good = vt.draft_head_step(h, W, map_, m)
+    hx = h.clone()
+    hx[0] = float("nan")
+    hx[n - 1, d // 2] = float("nan")
+    out = {"out_ids": torch.full((n, m), -1, dtype=torch.int32, device="cuda"), "out_logp": torch.zeros((n, m), device="cuda")}
+    ids, logp = vt.draft_head_step(hx, W, map_, m, **out)
+    for i in (0, n - 1):
+        assert torch.equal(ids[i], map_[:m]) and bool(logp[i].isnan().all())
+    assert torch.equal(ids[1:n - 1], good[0][1:n - 1]) and torch.equal(logp[1:n - 1], good[1][1:n - 1])
+    ws, L = vt.StepWorkspace(n, k, d, m, h.device), vt.load_library()
+    a, b = torch.empty_like(ids), torch.empty_like(logp)
+    for nan in (0x7FC0, 0x7FC0 - 0x8000):      # positive and negative ones
+        Wx = W.clone()
+        Wx.view(torch.int16)[k // 2] = nan
+        out["out_ids"].fill_(-1)
+        ids, logp = vt.draft_head_step(h, Wx, map_, m, **out)
+        assert bool(logp.isnan().all()) and bool(torch.isin(ids, map_).all())
+        assert all(len(set(row)) == m for row in ids.tolist())
+        step = lambda size: L.vt_draft_head_step(h.data_ptr(), 1, n, Wx.data_ptr(), 1, k, d, map_.data_ptr(), m, a.data_ptr(), b.data_ptr(), None, None,
+                                                 ws.buf.data_ptr(), size, torch.cuda.current_stream().cuda_stream)
+        lo, hi = 0, ws.nbytes // 256
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (lo, mid) if step(256 * mid) == 0 else (mid, hi)
+        assert step(256 * hi) == 0
+        # (logits that agree to rounding may change places)
+        assert torch.equal(a == map_[k // 2], ids == map_[k // 2]) and (a != ids).sum().item() <= 2 + ids.numel() // 256
+    if m > 1:
+        Wx[:] = float("nan")
+        Wx[k // 3] = 0
+        out["out_ids"].fill_(-1)
+        ids, logp = vt.draft_head_step(h, Wx, map_, m, **out)
+        assert bool(torch.isin(ids, map_).all()) and all(len(set(row)) == m for row in ids.tolist())
+
+
 # The library's own memory, a tree level, several heads and a workspace of the size that earlier versions asked for
 @pytest.mark.parametrize("n,k,d,m", [(224, 4300, 4096, 4), (40, 4300, 8192, 8), (70, 4100, 1024, 8)])
 def test_the_other_ways_to_a_stored_step(n, k, d, m):
