@@ -692,6 +692,7 @@ struct StepShape {
     int chunk = 0;
     size_t ws_bytes = 0;       // that a step asks for; with more it may run as plan_stored() has it
     StepPlan plan, stored;     // of `chunk` rows
+    size_t stored_bytes = 0;   // the most that a plan_stored() of its groups takes: of `chunk` rows, of what is left of n
     bool is(int n_, int k_, int d_, int m_, int dtype_) const { return n == n_ && k == k_ && d == d_ && m == m_ && dtype == dtype_; }
     const StepPlan &with(size_t bytes) const { return stored.ok && stored.bytes <= bytes ? stored : plan; }
 };
@@ -705,6 +706,11 @@ const StepShape &step_shape(int n, int k, int d, int m, int dtype) {
         s.ws_bytes = step_ws_bytes(n, k, d, m);
         s.plan = s.chunk != 0 ? plan_step(s.chunk, k, d, m, dtype) : StepPlan{};
         s.stored = plan_stored(s.plan, s.chunk, k, d, m);
+        s.stored_bytes = s.stored.ok ? s.stored.bytes : 0;
+        if (s.chunk != 0 && n % s.chunk != 0) {
+            const StepPlan rest = plan_stored(plan_step(n % s.chunk, k, d, m, dtype), n % s.chunk, k, d, m);
+            if (rest.ok && rest.bytes > s.stored_bytes) s.stored_bytes = rest.bytes;
+        }
         s.n = n;
         s.k = k;
         s.d = d;
@@ -933,7 +939,7 @@ int vt_draft_head_step_static(const void *h, int h_type, int32_t n, const void *
     const StepShape &shape = step_shape(n, k, d, m, w_type);
     if (shape.ws_bytes == 0) return VT_ERR_SHAPE;
     if (shape.ws_bytes > (size_t)VT_STATIC_WS_BYTES) return VT_ERR_WORKSPACE;
-    const bool stored = shape.stored.ok && shape.stored.bytes > (size_t)VT_STATIC_WS_BYTES && shape.stored.bytes <= kStaticStoredBytes;
+    const bool stored = shape.stored_bytes > (size_t)VT_STATIC_WS_BYTES && shape.stored_bytes <= kStaticStoredBytes;
     void *ws = nullptr;
     const int rc = static_scratch_of_current_device(stored, &ws);
     if (rc != VT_OK) return rc;

@@ -216,6 +216,18 @@ def test_logits_that_are_nan(n, k, d, m):
         assert bool(torch.isin(ids, map_).all()) and all(len(set(row)) == m for row in ids.tolist())
 
 
+# More than 256 rows run in groups: a whole one that keeps lists and the rest by slices whose logits the library's own 4 MiB do not hold
+@pytest.mark.parametrize("n,k,d,m", [(464, 3045, 1280, 9), (588, 2885, 1280, 37), (716, 2696, 1280, 13), (300, 4300, 4096, 4)])
+def test_groups_of_rows_on_the_librarys_own_memory(n, k, d, m):
+    assert "slices" in vt.draft_head_step_plan(n % 256, k, d, m)
+    h, W, map_, same = _inputs(n, k, d, seed=n)
+    ids, logp, lse, full = vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True)
+    _check(h, W, map_, same, m, (ids, logp, lse, full))
+    a, b = torch.empty_like(ids), torch.empty_like(logp)
+    vt.draft_head_step_static(h, W, map_, m, a, b)
+    assert torch.equal(a, ids) and torch.equal(b, logp)
+
+
 # The library's own memory, a tree level, several heads and a workspace of the size that earlier versions asked for
 @pytest.mark.parametrize("n,k,d,m", [(224, 4300, 4096, 4), (40, 4300, 8192, 8), (70, 4100, 1024, 8)])
 def test_the_other_ways_to_a_stored_step(n, k, d, m):
