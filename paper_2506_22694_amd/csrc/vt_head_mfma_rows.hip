@@ -64,26 +64,46 @@ __device__ __forceinline__ void wait_stage_and_sync(int younger) {
     }
 }
 
+// What becomes of a tile's logits: lists of candidates (or logits by way of LDS, where zbuf is not aligned), logits straight from the
+// accumulators, or those of a slice of the columns, blockIdx.y, with ranges of its own that its tiles rotate or in one order.  Kernels of their own: as a branch in one kernel they took every
+// step 0.2 to 0.5 us (n = 16, k = 9735, d = 3072 17.5 / 17.8, n = 80, k = 35010, d = 1024 23.6 / 24.1).
+enum TileOut { kTileLists, kTileStored, kTileSlices, kTileSlicesInOrder };
+constexpr bool in_slices(TileOut out) { return out == kTileSlices || out == kTileSlicesInOrder; }
+
 // Where a workgroup's march over ns stages starts and where its ranges end.
-template <int NR, bool SLICES>
+template <int NR, TileOut OUT>
 struct March {
     int ns, rot, start, step, last, last_length;
-    bool rotate;
+    bool ranges;
     // Slices of the columns (of ns stages each) start in different places anyway; where those are whole multiples of 4 KiB
     // apart a slice has ranges to itself (n = 32, k = 14000, d = 8192, two slices 57.3 -> 50.6 us; elsewhere 2 to 10 % slower).
-    __device__ __forceinline__ March(int ns_, int d, int slice_ranges) : ns(ns_) {
-        rotate = NR > 1 && (SLICES ? slice_ranges != 0 && ns >= 2 * NR : d % 2048 == 0 && (NR > 2 || d >= 4096));
-        rot = rotate ? first_range<NR>((int)blockIdx.x) : 0;
-        // stages from one start to the next (an even number of them: a stage may be two blocks of 64 columns)
-        if constexpr (SLICES) {
-            step = ns / NR & ~1;
-            if (step % 32 == 0) step = NR == 2 ? 16 : step + 32 / NR;
+    // In order: all tiles of a slice start in one place, another one for each slice, and the sums of any number of ranges take one
+    // set of registers.  A chain of additions is no longer there than an eighth of the row, what the tiles in one piece have where they
+    // have ranges: a slice in one chain had up to twice the error of those (n = 126, k = 5389, d = 8192, three slices: log-probs of the
+    // best tokens 3.0e-7 off, 1.5e-7 in one piece and in short chains).
+    __device__ __forceinline__ March(int ns_, int d, int slice_ranges, int slice, int splits) : ns(ns_) {
+        if constexpr (OUT == kTileSlicesInOrder) {
+            ranges = d % 2048 == 0;
+            rot = 0;
+            // (an even number of stages: one of the kernel may be two blocks of 64 columns)
+            step = d / (8 * kStageCols) & ~1;
+            start = slice_ranges != 0 ? 32 * slice / splits & ~1 : 0;      // (of 32 and more)
+            last = -1;
+            last_length = 0;
         } else {
-            step = NR == 2 ? 16 : range_step<NR>(ns, d);
+            ranges = OUT == kTileSlices || (NR > 1 && d % 2048 == 0 && (NR > 2 || d >= 4096));
+            rot = ranges ? first_range<NR>((int)blockIdx.x) : 0;
+            // stages from one start to the next
+            if constexpr (OUT == kTileSlices) {
+                step = ns / NR & ~1;
+                if (step % 32 == 0) step += 32 / NR;
+            } else {
+                step = NR == 2 ? 16 : range_step<NR>(ns, d);
+            }
+            start = bound(rot);
+            last = NR - 1 - rot;
+            last_length = ns - bound(NR - 1);
         }
-        start = bound(rot);
-        last = NR - 1 - rot;
-        last_length = ns - bound(NR - 1);
     }
     __device__ __forceinline__ int bound(int r) const { return r * step; }
     // stage of the row that is multiplied at step s < ns
@@ -95,16 +115,12 @@ struct March {
     __device__ __forceinline__ int length_of(int j) const { return j == last ? last_length : step; }
 };
 
-// What becomes of a tile's logits: lists of candidates (or logits by way of LDS, where zbuf is not aligned), logits straight from the
-// accumulators, or those of a slice of the columns, blockIdx.y.  Kernels of their own: as a branch in one kernel they took every
-// step 0.2 to 0.5 us (n = 16, k = 9735, d = 3072 17.5 / 17.8, n = 80, k = 35010, d = 1024 23.6 / 24.1).
-enum TileOut { kTileLists, kTileStored, kTileSlices };
 // The columns of a workgroup: the first stage of 64, and how many.
 template <TileOut OUT>
 struct Columns {
     int slice, first, stages;
     __device__ __forceinline__ explicit Columns(const MfmaArgs &a) {
-        if constexpr (OUT == kTileSlices) {
+        if constexpr (in_slices(OUT)) {
             slice = (int)blockIdx.y;
             first = 2 * (slice * a.slice_units + min(slice, a.slice_more));
             stages = 2 * (a.slice_units + (slice < a.slice_more ? 1 : 0));
@@ -203,7 +219,7 @@ __global__ void __launch_bounds__(MAXW *kWave) __attribute__((amdgpu_waves_per_e
 head_mfma_kernel(const MfmaArgs a) {
     static_assert(!X || (MAXW == kStepWaves && TPW == NT), "the ninth group belongs to tiles of eight waves");
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int NR = 8;
+    constexpr int NR = OUT == kTileSlicesInOrder ? 2 : 8;
     constexpr int NA = TPW + (X ? 1 : 0);      // accumulators: own row group, and the ninth
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -219,7 +235,7 @@ head_mfma_kernel(const MfmaArgs a) {
     const unsigned rs = (unsigned)a.d * 2u;
     const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs + (size_t)columns.first * 128;
     const char *hb = static_cast<const char *>(a.h) + (size_t)columns.first * 128;
-    const March<NR, OUT == kTileSlices> march(columns.stages, a.d, OUT == kTileSlices ? a.slice_ranges : 0);
+    const March<NR, OUT> march(columns.stages, a.d, a.slice_ranges, columns.slice, a.splits);
     const unsigned block_bytes = (unsigned)(GR + NT) * kGroupBytes, stage_bytes = KB * block_bytes;
     const int nstages = march.ns / KB;             // (d is a multiple of 128: an even number of blocks)
 
@@ -283,7 +299,7 @@ head_mfma_kernel(const MfmaArgs a) {
     for (int s = 0; s < nstages; ++s) {
         wait_stage_and_sync<LPW, NST - 2>(nstages - 1 - s);      // stage s is in LDS, the slot of stage s - 1 is free
         if (s + NST - 1 < nstages) load_stage(s + NST - 1, slot == 0 ? NST - 1 : slot - 1);
-        if (march.rotate) {
+        if (march.ranges) {
             if (left == 0) {
                 sums.close(acc, march.rot, closed);
                 ++closed;
@@ -324,7 +340,7 @@ head_mfma_kernel(const MfmaArgs a) {
             }
         }
     }
-    if (march.rotate) {
+    if (march.ranges) {
         sums.close(acc, march.rot, closed);
         sums.total(acc);
     }
@@ -415,7 +431,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
     const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs + (size_t)columns.first * 128;
     // (re-laid: a stage's pieces lie one after the other)
     const char *hb = PACKED ? static_cast<const char *>(a.hpack) + (size_t)columns.first * (TN * 128) : static_cast<const char *>(a.h) + (size_t)columns.first * 128;
-    const March<NR, OUT == kTileSlices> march(columns.stages, a.d, OUT == kTileSlices ? a.slice_ranges : 0);
+    const March<NR, OUT> march(columns.stages, a.d, a.slice_ranges, columns.slice, a.splits);
 
     unsigned voff[LPW], lds_at[LPW];
 #pragma unroll
@@ -507,13 +523,13 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
         for (int j = 0; j < LPW; ++j) {
             if (j * kEvery >= NP && more) load_piece(kHiddenFirst ? LPW - 1 - j : j);
         }
-        if (NR > 1 && march.rotate && --left == 0 && s + 1 < march.ns) {
+        if (NR > 1 && march.ranges && --left == 0 && s + 1 < march.ns) {
             sums.close(acc, march.rot, closed);
             ++closed;
             left = march.length_of(closed);
         }
     }
-    if (NR > 1 && march.rotate) {
+    if (NR > 1 && march.ranges) {
         sums.close(acc, march.rot, closed);
         sums.total(acc);
     }
@@ -623,7 +639,10 @@ static_assert(rows_variant_ok(2, 9, false) && rows_variant_ok(2, 10, false) && r
 static_assert(rows_variant_ok(4, 1, false) && rows_variant_ok(4, 2, false) && rows_variant_ok(4, 3, false) && rows_variant_ok(4, 4, false));
 static_assert(rows_variant_ok(4, 5, false) && rows_variant_ok(4, 6, false) && rows_variant_ok(4, 7, false) && rows_variant_ok(4, 8, false));
 static_assert(rows_variant_ok(4, 9, false) && rows_variant_ok(4, 10, false) && rows_variant_ok(4, 11, false) && rows_variant_ok(4, 12, false));
-TileOut tile_out(const MfmaArgs &a) { return a.zbuf == nullptr || a.zvec == 0 ? kTileLists : a.splits > 1 ? kTileSlices : kTileStored; }
+TileOut tile_out(const MfmaArgs &a) {
+    if (a.zbuf == nullptr || a.zvec == 0) return kTileLists;
+    return a.splits == 1 ? kTileStored : a.slice_ranges != 0 ? kTileSlices : kTileSlicesInOrder;
+}
 // (slices: tiles of 64 and of 128 rows, one workgroup to a CU; unaligned logits go through LDS and have no slices)
 template <int NT, int RG, bool X, bool TWIN = false>
 hipError_t launch_rows(const MfmaArgs &a, size_t lds, hipStream_t st) {
@@ -635,6 +654,7 @@ hipError_t launch_rows(const MfmaArgs &a, size_t lds, hipStream_t st) {
     if (tile_out(a) == kTileStored) return launch(std::integral_constant<TileOut, kTileStored>{});
     if constexpr ((RG == 4 || RG == 8) && !X && !TWIN) {
         if (tile_out(a) == kTileSlices) return launch(std::integral_constant<TileOut, kTileSlices>{});
+        if (tile_out(a) == kTileSlicesInOrder) return launch(std::integral_constant<TileOut, kTileSlicesInOrder>{});
     }
     return a.splits == 1 ? launch(std::integral_constant<TileOut, kTileLists>{}) : hipErrorInvalidValue;
 }
@@ -661,16 +681,21 @@ constexpr int wide_ranges(int MT, int NTT) {
     const int acc = 4 * MT * NTT, ops = 8 * (MT + NTT);
     return 5 * acc + ops <= 208 ? 8 : 3 * acc + ops <= 208 ? 4 : 2;
 }
-// (slices: tiles of 64, 128 and 160 rows)
+// (slices: tiles of 64, 128 and 160 rows; two ranges that tiles rotate would be chains of a quarter of the row and more)
 template <int MT, int NTT, bool PACKED>
 hipError_t launch_wide_as(const MfmaArgs &a, size_t lds, hipStream_t st) {
     constexpr int NST = wide_stages(MT, NTT), NR = wide_ranges(MT, NTT);
     auto launch = [&](auto out) {
-        return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, NR, PACKED, decltype(out)::value>>(a, kStepWaves * kWave, lds, st);
+        constexpr TileOut OUT = decltype(out)::value;
+        return launch_tile<head_mfma_wide_kernel<MT, NTT, NST, (OUT == kTileSlicesInOrder ? 2 : NR), PACKED, OUT>>(a, kStepWaves * kWave, lds, st);
     };
-    if (tile_out(a) == kTileStored) return launch(std::integral_constant<TileOut, kTileStored>{});
+    const TileOut out = tile_out(a);
+    if (out == kTileStored) return launch(std::integral_constant<TileOut, kTileStored>{});
     if constexpr (MT == 2 || MT == 4 || MT == 5) {
-        if (tile_out(a) == kTileSlices) return launch(std::integral_constant<TileOut, kTileSlices>{});
+        if constexpr (NR > 2) {
+            if (out == kTileSlices) return launch(std::integral_constant<TileOut, kTileSlices>{});
+        }
+        if (out == kTileSlices || out == kTileSlicesInOrder) return launch(std::integral_constant<TileOut, kTileSlicesInOrder>{});
     }
     return a.splits == 1 ? launch(std::integral_constant<TileOut, kTileLists>{}) : hipErrorInvalidValue;
 }

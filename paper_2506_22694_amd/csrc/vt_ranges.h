@@ -17,7 +17,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // accumulated from zero in ascending order and the sums are added up as a balanced tree,
 // ((R0 + R1) + (R2 + R3)) + ((R4 + R5) + (R6 + R7)): float addition commutes, so the ranges can finish in any rotation.
 // The partial sums a rotation needs to hold: the open half of a pair, one sum per quad, and for an odd start the
-// second half of its pair, whose first half comes last.  NR = 4 and 2 are the same tree, cut off.
+// second half of its pair, whose first half comes last.  NR = 4 and 2 are the same tree, cut off.  (NR = 2 takes any number
+// of ranges that finish in the same order in every tile.)
 template <int NR, int N>
 struct RangeSums {
     static constexpr int kSets = NR == 8 ? 4 : NR == 4 ? 2 : NR == 2 ? 1 : 0;

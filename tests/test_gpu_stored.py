@@ -57,6 +57,29 @@ def test_step_by_slices_of_the_columns(n, k, d, m, slices, tile):
     _check(h, W, map_, same, m, vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True))
 
 
+# Slices add up no longer chains than the tiles in one piece that a smaller workspace has: no larger error (of 500 and more log-probs, whose
+# errors' 2-norm is known to a few percent; a chain twice as long has 1.4 to 2 times the error)
+@pytest.mark.parametrize("n,k,d,m", [(126, 5389, 8192, 4), (200, 14066, 8192, 4), (224, 4300, 4096, 4), (136, 12835, 8192, 4)])
+def test_slices_are_as_close_to_fp64_as_one_piece(n, k, d, m):
+    assert "column_slices" in vt.draft_head_step_plan(n, k, d, m)
+    h, W, map_, _ = _inputs(n, k, d, seed=k)
+    z = h.double() @ W.double().t()
+    top = (z - z.logsumexp(1, keepdim=True)).topk(m, 1).values
+    ws, L = vt.StepWorkspace(n, k, d, m, h.device), vt.load_library()
+    a, b = torch.empty((n, m), dtype=torch.int32, device="cuda"), torch.empty((n, m), device="cuda")
+    step = lambda size: L.vt_draft_head_step(h.data_ptr(), 1, n, W.data_ptr(), 1, k, d, map_.data_ptr(), m, a.data_ptr(), b.data_ptr(), None, None,
+                                             ws.buf.data_ptr(), size, torch.cuda.current_stream().cuda_stream)
+    lo, hi = 0, ws.nbytes // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if step(256 * mid) == 0 else (mid, hi)
+    error = []
+    for size in (256 * hi, ws.nbytes):
+        assert step(size) == 0
+        error.append((b - top).norm().item())
+    assert error[1] < 1.2 * error[0]
+
+
 # Stored logits of heads that one or two values per lane and load hold, without slices: rows of 8 and 16 values per thread and their
 # edges, k on and off multiples of four, more logits than candidates (hidden row of zeros)
 @pytest.mark.parametrize("n,k,d,m", [
