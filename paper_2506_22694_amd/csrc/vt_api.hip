@@ -476,10 +476,9 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     StepPlan p = whole;
     p.ok = false;
     // Up to 8 hidden rows parts pay where a row's whole reading takes longer than a second trip (whole / by parts: n = 2, d = 3072, m = 16,
-    // k = 16000 24.0 / 24.2 us, 18000 28.8 / 28.3, 32975 43.0 / 38.2; n = 4, d = 1024, m = 64, k = 30000 22.4 / 22.6; n = 4, k = 79094, d = 2048,
-    // m = 16 66.7 / 57.4) -- and on rows so short that a wave of row_select_kernel holds none of their groups of four, where
-    // all logits become candidates (n = 4, k = 3000, d = 1024, m = 16 46.8 / 10.7)
-    const bool few_by_parts = k > (m <= 16 ? vt::kRowSelectWhole / 2 : vt::kRowSelectWhole) || (k % 4 == 0 && k <= 15 * 256);
+    // k = 16000 24.0 / 24.2 us, 18000 28.8 / 28.3, 32975 43.0 / 38.2; n = 4, d = 1024, m = 64, k = 30000 22.4 / 22.6, k = 3000, m = 16 9.6 / 10.9;
+    // n = 4, k = 79094, d = 2048, m = 16 66.7 / 57.4)
+    const bool few_by_parts = k > (m <= 16 ? vt::kRowSelectWhole / 2 : vt::kRowSelectWhole);
     if (whole.ok && n <= vt::kGemvMaxN && whole.row_select && few_by_parts && row_parts(p, n, k)) {
         lay_out_stored(p, n, k, d);
         p.ok = true;

@@ -79,6 +79,23 @@ __device__ __forceinline__ void load_stretch(const float *__restrict__ zr, int b
     }
 }
 
+// A thread's place in a stretch.  Groups of four of a row that has fewer than threads go to the waves in equal shares: with them
+// in order the last waves have none, their maxima leave the row without a threshold (row_threshold), and all its logits are candidates
+// -- beyond 1024 of them the tokens are found one after the other (five slices, n = 128, k = 3000, d = 4096, m = 16 56.4 -> 20.3 us,
+// n = 250, k = 2050 56.1 / 21.8, n = 20, k = 1500, d = 8192, m = 64 151.6 / 19.7; in one piece, n = 4, k = 3000, d = 1024, m = 16 46.8 / 9.6).
+// Threads without a group have the last place, which lies behind the row.
+template <bool VEC, int VALS>
+__device__ __forceinline__ int stretch_place(int k, int tid, int lane, int w) {
+    if constexpr (VEC && VALS == 8) {
+        const int groups = (k + 3) / 4;
+        if (groups < kRowThreads) {
+            const int first = w * groups / kRowWaves, behind = (w + 1) * groups / kRowWaves;
+            return first + lane < behind ? first + lane : kRowThreads - 1;
+        }
+    }
+    return tid;
+}
+
 // The row's logits from `splits` partial ones, `stride` floats apart, added up in the order of the slices (rows 16-byte aligned,
 // whole groups of four; what lies behind k in the last one is not a logit).  64 values of a thread are requested at a time.
 template <int VALS>
@@ -278,6 +295,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int i = blockIdx.x;
     const float *zr = z + (size_t)i * (SLICED ? pitch : k);
+    const int at = stretch_place<VEC, VALS>(k, tid, lane, w);
     float v[VALS];
     // (all of this is first used behind the barrier of row_threshold.  Candidates are ranked in whole groups of eight: what is
     // behind the last one loses against all of them)
@@ -294,16 +312,16 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     // ---- pass 1: (max, sum-exp) and the thread's largest logit
     float lm = -INFINITY, ls = 0.f;
     if constexpr (SLICED) {
-        load_slices(zr, splits, (size_t)gridDim.x * pitch, k, tid, v);
+        load_slices(zr, splits, (size_t)gridDim.x * pitch, k, at, v);
         if (z_out != nullptr) {
 #pragma unroll
             for (int u = 0; u < VALS; ++u) {
-                const int j = stretch_index<VEC>(0, u, tid);
+                const int j = stretch_index<VEC>(0, u, at);
                 if (j < k) z_out[(size_t)i * k + j] = v[u];
             }
         }
     } else {
-        load_stretch<VEC, VALS>(zr, 0, k, tid, v);
+        load_stretch<VEC, VALS>(zr, 0, k, at, v);
     }
     unsigned T, Mo;
     if constexpr (MODE == kRowWhole) {
@@ -311,24 +329,24 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     } else if constexpr (MODE == kRowTwice) {
         fold_stretch(v, lm, ls);
         for (int base = kRowSpan; base < k; base += kRowSpan) {
-            load_stretch<VEC, VALS>(zr, base, k, tid, v);
+            load_stretch<VEC, VALS>(zr, base, k, at, v);
             fold_stretch(v, lm, ls);
         }
     } else {
         float v2[VALS];
-        load_stretch<VEC, VALS>(zr, kRowSpan, k, tid, v2);
+        load_stretch<VEC, VALS>(zr, kRowSpan, k, at, v2);
         fold_stretch(v, lm, ls);
         row_threshold(lm, m, tmax_first, lane, w, T, Mo);
         const float Tf1 = threshold_f32(T);
-        collect_stretch<VEC, SIFT, VALS>(v, 0, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, SIFT, VALS>(v, 0, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
         for (int base = kRowSpan; base < k; base += 2 * kRowSpan) {
-            load_stretch<VEC, VALS>(zr, base + kRowSpan, k, tid, v);
+            load_stretch<VEC, VALS>(zr, base + kRowSpan, k, at, v);
             fold_stretch(v2, lm, ls);
-            collect_stretch<VEC, SIFT, VALS>(v2, base, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+            collect_stretch<VEC, SIFT, VALS>(v2, base, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
             if (base + kRowSpan < k) {
-                load_stretch<VEC, VALS>(zr, base + 2 * kRowSpan, k, tid, v2);
+                load_stretch<VEC, VALS>(zr, base + 2 * kRowSpan, k, at, v2);
                 fold_stretch(v, lm, ls);
-                collect_stretch<VEC, SIFT, VALS>(v, base + kRowSpan, k, tid, Tf1, rawv, rawj, &s_nraw, kRaw);
+                collect_stretch<VEC, SIFT, VALS>(v, base + kRowSpan, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
             }
         }
     }
@@ -342,12 +360,12 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
 
     // ---- pass 2: every logit >= T is a candidate
     if constexpr (MODE == kRowWhole) {
-        collect_stretch<VEC, SIFT, VALS>(v, 0, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, SIFT, VALS>(v, 0, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
         __syncthreads();
     } else if constexpr (MODE == kRowTwice) {
         for (int base = 0; base < k; base += kRowSpan) {
-            load_stretch<VEC, VALS>(zr, base, k, tid, v);
-            collect_stretch<VEC, SIFT, VALS>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+            load_stretch<VEC, VALS>(zr, base, k, at, v);
+            collect_stretch<VEC, SIFT, VALS>(v, base, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
         }
         __syncthreads();
     } else if (s_nraw > kRaw) {
@@ -355,8 +373,8 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         if (tid == 0) s_nraw = 0u;
         __syncthreads();
         for (int base = 0; base < k; base += kRowSpan) {
-            load_stretch<VEC, VALS>(zr, base, k, tid, v);
-            collect_stretch<VEC, SIFT, VALS>(v, base, k, tid, Tf, rawv, rawj, &s_nraw, kRaw);
+            load_stretch<VEC, VALS>(zr, base, k, at, v);
+            collect_stretch<VEC, SIFT, VALS>(v, base, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
         }
         __syncthreads();
     }
@@ -399,10 +417,10 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         for (int r = 0; r < m; ++r) {
             unsigned long long best = kNoKey;
             for (int base = 0; base < k; base += kRowSpan) {
-                if (MODE != kRowWhole) load_stretch<VEC, VALS>(zr, base, k, tid, v);
+                if (MODE != kRowWhole) load_stretch<VEC, VALS>(zr, base, k, at, v);
 #pragma unroll
                 for (int u = 0; u < VALS; ++u) {
-                    const int j = stretch_index<VEC>(base, u, tid);
+                    const int j = stretch_index<VEC>(base, u, at);
                     if (j < k && (v[u] >= Tf || by_code)) {
                         const unsigned long long key = make_key(v[u], map[j]);
                         if (key < prev && key > best) best = key;

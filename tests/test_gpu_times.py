@@ -60,3 +60,19 @@ def test_large_counts_outside_the_sample():
     out = torch.empty(V, dtype=torch.int32, device="cuda")
     t = _times(*[lambda c=c: vt.build_trimmed_head(c, None, V, ws=ws, out_map=out, order="rank") for c in (hidden, spread)])
     assert t[0] < 4 * t[1], t
+
+
+# Rows of fewer groups of four logits than the workgroup's last wave begins with, in slices: they had no threshold, and their tokens were
+# found one after the other (n = 128, k = 3000, d = 4096, m = 16 56 us, k = 4300 23)
+def test_short_rows_in_slices():
+    n, d, m = 128, 4096, 16
+    h, calls = torch.randn(n, d, device="cuda").bfloat16(), []
+    for k in (3000, 4300):
+        assert "column_slices" in vt.draft_head_step_plan(n, k, d, m)
+        W = torch.randn(k, d, device="cuda").mul_(0.02).bfloat16()
+        args = (h, W, torch.arange(k, dtype=torch.int32, device="cuda"), m)
+        kept = {"ws": vt.StepWorkspace(n, k, d, m, W.device), "out_ids": torch.empty((n, m), dtype=torch.int32, device="cuda"),
+                "out_logp": torch.empty((n, m), device="cuda")}
+        calls.append(lambda args=args, kept=kept: vt.draft_head_step(*args, **kept))
+    short, long = _times(*calls)
+    assert short < 1.4 * long, (short, long)
