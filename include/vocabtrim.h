@@ -210,8 +210,9 @@ int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_ty
  * on, from the first use of the library on that GPU until the process ends
  * (steps of more than 8 rows that vt_draft_head_step runs on stored logits,
  * given the workspace it asks for, in another one of 48 MiB).
- * The call allocates and frees nothing (its first call on a device asks the
- * runtime for the array's address; make that call outside stream capture).
+ * The call allocates and frees nothing (its first call on a device, of
+ * whatever shape, asks the runtime for the addresses of both arrays; make that
+ * call outside stream capture).
  *   - A shape for which vt_draft_head_step accepts no workspace of
  *     VT_STATIC_WS_BYTES returns VT_ERR_WORKSPACE and enqueues nothing (for
  *     example n = 256 rows with 16 tokens per row at k = 32768, whose per-row

@@ -31,14 +31,15 @@ inline int launch_status() { return device_status(hipGetLastError()); }
 // ---------------------------------------------------------------- library-owned step workspace
 // Device memory of the draft step for callers that cannot allocate (vt_draft_head_step_static): one array per
 // GPU, alive from the moment the code object is loaded on it until the process ends.  In host code the array's
-// name is only a handle; the device address is asked for once per device and kept.
+// name is only a handle; the device address is asked for once per device and kept (both arrays' by the first call that uses either:
+// a program makes that call outside stream capture).
 static __device__ __align__(256) unsigned char scratch[VT_STATIC_WS_BYTES];
 // ... and of the steps that plan_stored() has run on stored logits, which have the bits of vt_draft_head_step's only if they run the same
 // way: 256 hidden rows by 256 tiles of 160 logits, 4 MiB of re-laid h and the small parts of a workspace at most.
 constexpr size_t kStaticStoredBytes = (size_t)48 << 20;
 static __device__ __align__(256) unsigned char stored_scratch[kStaticStoredBytes];
 std::mutex g_scratch_mutex;
-void *g_scratch_ptr[2][64] = {};      // per device ordinal; written under the mutex, never changed afterwards
+void *g_scratch_ptr[64][2] = {};      // per device ordinal; written under the mutex, never changed afterwards
 
 int static_scratch_of_current_device(bool stored, void **out) {
     int dev = 0;
@@ -46,15 +47,17 @@ int static_scratch_of_current_device(bool stored, void **out) {
     if (e != hipSuccess) return device_status(e);
     if (dev < 0 || dev >= 64) return device_status(hipErrorInvalidDevice);
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    void *&known = g_scratch_ptr[stored ? 1 : 0][dev];
-    if (known == nullptr) {
-        void *p = nullptr;
-        e = stored ? hipGetSymbolAddress(&p, HIP_SYMBOL(stored_scratch)) : hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+    void **const known = g_scratch_ptr[dev];
+    if (known[0] == nullptr || known[1] == nullptr) {
+        void *p[2] = {nullptr, nullptr};
+        e = hipGetSymbolAddress(&p[0], HIP_SYMBOL(scratch));
+        if (e == hipSuccess) e = hipGetSymbolAddress(&p[1], HIP_SYMBOL(stored_scratch));
         if (e != hipSuccess) return device_status(e);
-        if (p == nullptr) return device_status(hipErrorInvalidSymbol);
-        known = p;
+        if (p[0] == nullptr || p[1] == nullptr) return device_status(hipErrorInvalidSymbol);
+        known[0] = p[0];
+        known[1] = p[1];
     }
-    *out = known;
+    *out = known[stored ? 1 : 0];
     return VT_OK;
 }
 

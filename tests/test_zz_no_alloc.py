@@ -5,6 +5,10 @@ kernels), and through it those of the oracle; two calls in a row share the array
 smaller input, so nothing the first call left behind may leak into the second.
 """
 
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -90,3 +94,40 @@ def test_static_scratch_step_rejects_shapes_beyond_its_array():
     with pytest.raises(vt.VocabTrimError) as e:
         vt.draft_head_step_static(dh, dW, dmap, m, oi, ol)
     assert e.value.status == 5
+
+
+# A process whose first call is a small shape, and which captures a shape that has the array for stored logits: the first call has asked
+# for both arrays' addresses
+_CAPTURED = """
+import torch
+import paper_2506_22694_amd as vt
+g = torch.Generator(device="cuda").manual_seed(3)
+def case(n, k, d, m):
+    W = torch.randn(k, d, generator=g, device="cuda").mul_(0.02).bfloat16()
+    h = torch.randn(n, d, generator=g, device="cuda").bfloat16()
+    out = torch.empty((n, m), dtype=torch.int32, device="cuda"), torch.empty((n, m), device="cuda")
+    return (h, W, torch.arange(k, dtype=torch.int32, device="cuda"), m), out
+args, out = case(4, 1024, 256, 4)
+vt.draft_head_step_static(*args, *out)
+args, out = case(224, 4300, 4096, 4)
+assert "column_slices" in vt.draft_head_step_plan(224, 4300, 4096, 4)
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    vt.draft_head_step_static(*args, *out)
+for _ in range(3):
+    out[0].zero_()
+    out[1].zero_()
+    graph.replay()
+    eager = vt.draft_head_step(*args)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], eager[0]) and torch.equal(out[1], eager[1])
+print("captured")
+"""
+
+
+@pytest.mark.gpu
+def test_static_scratch_step_captured_after_a_call_of_another_shape():
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _CAPTURED], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "captured" in r.stdout, r.stderr
