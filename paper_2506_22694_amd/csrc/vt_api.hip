@@ -465,6 +465,18 @@ void lay_out_stored(StepPlan &p, int n, int k, int d) {
     p.bytes = off;
 }
 
+// Up to 8 hidden rows parts pay where a row's whole reading takes longer than a second trip (whole / by parts: n = 2, d = 3072, m = 16,
+// k = 16000 24.0 / 24.2 us, 18000 28.8 / 28.3, 32975 43.0 / 38.2; n = 4, d = 1024, m = 64, k = 30000 22.4 / 22.6, k = 3000, m = 16 9.6 / 10.9;
+// n = 4, k = 79094, d = 2048, m = 16 66.7 / 57.4)
+bool few_rows_by_parts(int k, int m) { return k > (m <= 16 ? vt::kRowSelectWhole / 2 : vt::kRowSelectWhole); }
+// Slices of the columns beside tiles of 16 g rows: as many as fill the chip, of 256 columns and more; 1: none.  Up to d = 8192, the
+// longest rows measured.
+constexpr int kSliceGroups[] = {4, 8, 10};
+int slices_of(int k, int d, int g) {
+    const int tiles = (k + 16 * g - 1) / (16 * g), S = round_workgroups() / tiles;
+    return S >= 2 && k <= vt::kRowSelectWhole && d <= 8192 && d / 128 >= 2 * S ? S : 1;
+}
+
 // The same step with its logits stored, and the columns cut into slices where that pays: larger tiles then (each hidden row is
 // read once per tile, so small tiles of many hidden rows are bound by reading h), a workgroup per tile and slice, and
 // row_select_kernel adds the partial logits up.  ok = false: the plan itself is the better one.
@@ -474,15 +486,10 @@ void lay_out_stored(StepPlan &p, int n, int k, int d) {
 // the slices have to gain what its launch costs.  Measured (us, plan / slices): n = 224, k = 4300, d = 8192 81.9 / 36.5,
 // k = 10000, d = 4096 54.7 / 39.3, n = 160, k = 6500, d = 4096 40.7 / 30.2, n = 100, k = 4300, d = 2048 21.9 / 18.2, n = 64, k = 4300,
 // d = 4096 24.1 / 18.8; what the rule leaves: n = 100, k = 14000, d = 4096 37.1 / 39.3, n = 32, k = 10000, d = 4096 22.9 / 24.9.
-// Up to d = 8192, the longest rows measured.
 StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     StepPlan p = whole;
     p.ok = false;
-    // Up to 8 hidden rows parts pay where a row's whole reading takes longer than a second trip (whole / by parts: n = 2, d = 3072, m = 16,
-    // k = 16000 24.0 / 24.2 us, 18000 28.8 / 28.3, 32975 43.0 / 38.2; n = 4, d = 1024, m = 64, k = 30000 22.4 / 22.6, k = 3000, m = 16 9.6 / 10.9;
-    // n = 4, k = 79094, d = 2048, m = 16 66.7 / 57.4)
-    const bool few_by_parts = k > (m <= 16 ? vt::kRowSelectWhole / 2 : vt::kRowSelectWhole);
-    if (whole.ok && n <= vt::kGemvMaxN && whole.row_select && few_by_parts && row_parts(p, n, k)) {
+    if (whole.ok && n <= vt::kGemvMaxN && whole.row_select && few_rows_by_parts(k, m) && row_parts(p, n, k)) {
         lay_out_stored(p, n, k, d);
         p.ok = true;
         return p;
@@ -500,11 +507,11 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     const double as_planned = 9.0 + rounds * ((double)rows * d / 18e3 + (double)hrows * d / 38e3) +
                               (!whole.row_select ? rounds * 0.03 * n - 0.6 : std::max(k * (2.2e-6 * n + 3.5e-5), few ? 1.5 : 0.0));
     double best = as_planned;
-    for (int g : {4, 8, 10}) {
+    for (int g : kSliceGroups) {
         // (d = 1024: parts / slices n = 194, k = 5070, m = 4 18.6 / 20.1 us, n = 135, k = 4461, m = 1 16.5 / 16.7)
-        if (!sliceable || (few && g > 8) || (by_parts && d <= 1024)) continue;
-        const int tiles = (k + 16 * g - 1) / (16 * g), S = CUS / tiles;
-        if (S < (few ? 4 : g > 8 ? 3 : 2) || d / 128 < 2 * S) continue;
+        if ((few && g > 8) || (by_parts && d <= 1024)) continue;
+        const int S = slices_of(k, d, g);
+        if (S < (few ? 4 : g > 8 ? 3 : 2)) continue;
         const double t = 10.3 + (double)16 * g * d / S / 19e3 + (double)hrows * d / S / 34e3 + (double)S * k * (1.8e-6 * n + 6.5e-5);
         if (t < best && t < (S == 2 ? 0.90 : 0.93) * as_planned && (!few || t < as_planned - 4.0)) {
             best = t;
@@ -603,17 +610,49 @@ size_t step_ws_bytes(int n, int k, int d, int m) {
 
 // The same with room for plan_stored()'s plans, of n rows and of fewer (slices come and go with the rows).  What a program asks for; a
 // step accepts step_ws_bytes(), the size that earlier versions returned.
-size_t full_step_ws_bytes(int n, int k, int d, int m) {
+// Not all of up to 256 row counts are planned, but from n rows down until what is left cannot be more, whatever its slices: n = 256,
+// k = 32768, d = 8192, m = 16 27.8 -> 1.6 us, k = 4300, d = 4096, m = 8 25.5 / 19.6, n = 64, k = 32768, m = 8 3.0 / 0.9 (step_ws_bytes() alone
+// 0.4 to 0.9).
+size_t plan_full_step_ws_bytes(int n, int k, int d, int m) {
     size_t b = step_ws_bytes(n, k, d, m);
     if (b == 0) return 0;
-    for (int r = 1; r <= n && r <= vt::kMfmaMaxN; ++r) {
-        for (int dtype : {VT_BF16, VT_F32}) {
-            if (dtype == VT_F32 && r > vt::kGemvMaxN) continue;
-            const StepPlan p = plan_stored(plan_step(r, k, d, m, dtype), r, k, d, m);
-            if (p.ok && p.bytes > b) b = p.bytes;
-        }
+    auto room_for = [&](int r, int dtype) {
+        const StepPlan p = plan_stored(plan_step(r, k, d, m, dtype), r, k, d, m);
+        if (p.ok && p.bytes > b) b = p.bytes;
+    };
+    for (int r = n < vt::kGemvMaxN ? n : vt::kGemvMaxN; r >= 1 && few_rows_by_parts(k, m); --r) {
+        room_for(r, VT_BF16);
+        room_for(r, VT_F32);
     }
+    int most = 1;
+    for (int g : kSliceGroups) {
+        const int S = slices_of(k, d, g);
+        if (S > most) most = S;
+    }
+    // (lay_out_stored()'s, with room for every rounding)
+    auto at_most = [&](int r) {
+        const size_t row = sizeof(float) + ((size_t)k / 14 + 32) * sizeof(unsigned long long) + (size_t)most * slice_pitch(k) * sizeof(float);
+        return (size_t)vt::kTicketBytes + r * row + (size_t)d * 512 + 5 * 256;
+    };
+    // (up to 8 tokens: a smaller batch keeps lists, unless it has the four slices that up to 64 rows ask for)
+    const int fewest = m > vt::kRowSelectMinLManyRows ? vt::kGemvMaxN
+                       : k > vt::kRowSelectWhole      ? vt::kRowSelectMinWork / m - 1
+                       : most < 4                     ? vt::kRowsKernelMaxN
+                                                      : vt::kGemvMaxN;
+    for (int r = n < vt::kMfmaMaxN ? n : vt::kMfmaMaxN; r > fewest && at_most(r) > b; --r) room_for(r, VT_BF16);
     return b;
+}
+size_t full_step_ws_bytes(int n, int k, int d, int m) {
+    // programs repeat their few shapes (a step without a workspace of its own asks in every call): the last answers are kept per host thread
+    struct Size {
+        int n = 0, k = 0, d = 0, m = 0;
+        size_t bytes = 0;
+    };
+    constexpr unsigned kKept = 64;
+    static thread_local Size kept[kKept];
+    Size &s = kept[((unsigned)n * 7u + (unsigned)m * 3u + (unsigned)k + (unsigned)d / 128u) % kKept];
+    if (s.n != n || s.k != k || s.d != d || s.m != m) s = Size{n, k, d, m, plan_full_step_ws_bytes(n, k, d, m)};
+    return s.bytes;
 }
 
 // Layout of a multi-head workspace: the step workspace first, then the staged hidden rows and the staged results

@@ -1,5 +1,6 @@
 """Plans and workspace sizes of the draft step, which are pure host functions (no device here: 256 CUs are assumed)."""
 import ctypes
+import time
 
 import pytest
 import torch
@@ -43,3 +44,18 @@ def test_rows_too_long_for_the_offsets_inside_a_tile_are_refused(lib, n):
     assert step(d) == 6 and b"invalid argument" in lib.vt_last_device_error()
     if not torch.cuda.is_available():      # (never launched on the fake addresses where there is a device)
         assert step(d - 128) == 6 and b"invalid argument" not in lib.vt_last_device_error()
+
+
+# A step without a workspace of its own asks for the size in every call: a shape's second answer takes no plans (20 us of them for 256 rows)
+def test_the_size_of_a_workspace_is_kept(lib):
+    def microseconds(*shape):
+        best = 1e9
+        for _ in range(20):
+            start = time.perf_counter()
+            for _ in range(100):
+                lib.vt_draft_head_step_ws_bytes(*shape)
+            best = min(best, time.perf_counter() - start)
+        return best * 1e4
+    smallest = microseconds(1, 1000, 128, 1)
+    for shape in ((256, 4300, 4096, 8), (256, 32768, 8192, 16), (64, 32768, 4096, 8)):
+        assert microseconds(*shape) < 4 * smallest
