@@ -117,3 +117,18 @@ def test_plain_calls_take_the_native_way(monkeypatch):
     for call, args in _calls("cuda").values():
         call(**args)
     assert taken == [("step", 0), ("step_static", 0), ("level", 0), ("rerank", 0), ("count", 0)]
+
+
+def test_calls_without_their_results_do_not_try_the_native_way(monkeypatch):
+    class Refuses:
+        def __getattr__(self, name):
+            raise AssertionError(f"{name} is tried")
+    vt.load_library()
+    monkeypatch.setattr(binding, "_bind", Refuses())
+    host = _calls("cpu")
+    ws = object.__new__(vt.StepWorkspace)      # (what a host tensor is refused with comes before anything is read of it)
+    for name, missing in (("step", ("out_ids", "out_logp")), ("level", ("out_ids", "out_logp", "out")), ("rerank", ("out",))):
+        call, args = host[name]
+        for gone in missing:
+            with pytest.raises(ValueError):
+                call(**{**args, **({"ws": ws} if "ws" in args else {}), gone: None})
