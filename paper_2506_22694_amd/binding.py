@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sysconfig
 
 import torch
 
@@ -99,16 +100,19 @@ def load_library() -> ctypes.CDLL:
 # them.  A draft step takes 6.1 us of the host's time instead of 9.9, a draft round of three levels and a rerank 48 instead of 57.5
 # (20 of them the caller's own tensor operations).  It answers -1 to a call that is not plain, and the functions below go
 # on as they do without it -- after a C++ exception, 1.3 us, so that a call without its results is not tried.
+# It reads torch's tensors where its headers say they keep their fields: built for another torch or interpreter it is left
+# alone, and everything works without it.
 _bind = None
+BIND_ABI = f"torch {torch.__version__} {torch.version.git_version} {sysconfig.get_config_var('SOABI')}"
 
 
 def _connect(L) -> None:
     global _bind
     try:
         from . import _vt_bind
-    except ImportError:      # (built for another interpreter or another torch: everything works without it)
+    except ImportError:
         return
-    if _raw_stream is None:
+    if _raw_stream is None or getattr(_vt_bind, "built_for", None) != BIND_ABI:
         return
     _vt_bind.connect(_raw_stream, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.vt_draft_head_step, L.vt_draft_head_step_static, L.vt_draft_tree_level, L.vt_tree_rerank, L.vt_count_tokens)))

@@ -6,13 +6,16 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
+import warnings
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvocabtrim.so")
-BIND = os.path.join(PKG, "_vt_bind.so")
+BIND = os.path.join(PKG, "_vt_bind" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+BIND_STAMP = os.path.join(OBJ, "vt_bind.command")      # how BIND was built
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -152,22 +155,49 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _binding_command(src: str) -> list[str]:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+
+    from .binding import BIND_ABI
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", f'-DVT_BUILT_FOR="{BIND_ABI}"',
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
+            *("-I" + p for p in include_paths()), "-I" + sysconfig.get_paths()["include"], src, "-o", BIND,
+            "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
+def _binding_stamp(cmd) -> str:
+    return "\n".join(c.replace(ROOT, ".") for c in cmd)      # (a tree may be moved)
+
+
+def _binding_stale(cmd, deps) -> bool:
+    """The sources are newer, or it was built by another command: for another torch or interpreter."""
+    if _stale(BIND, deps) or not os.path.exists(BIND_STAMP):
+        return True
+    with open(BIND_STAMP) as f:
+        return f.read() != _binding_stamp(cmd)
+
+
 def build_binding(force: bool = False) -> str:
     """The native part of the Python binding: host code against torch's headers, no GPU code in it."""
     src = os.path.join(CSRC, "vt_bind.cpp")
-    if force or _stale(BIND, [src] + glob.glob(os.path.join(ROOT, "include", "*.h"))):
-        import sysconfig
-
-        import torch
-        from torch.utils.cpp_extension import include_paths
-        lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-        cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared",
-               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
-               *("-I" + p for p in include_paths()), "-I" + sysconfig.get_paths()["include"], src, "-o", BIND,
-               "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        if r.returncode != 0:
-            raise RuntimeError(f"{cmd[0]} failed on {src}:\n{r.stderr}")
+    cmd = _binding_command(src)
+    if force or _binding_stale(cmd, [src] + glob.glob(os.path.join(ROOT, "include", "*.h"))):
+        # (a build that fails leaves none behind, and none of the name without the interpreter's tag that it once had)
+        for old in (BIND, BIND_STAMP, os.path.join(PKG, "_vt_bind.so")):
+            if os.path.exists(old):
+                os.remove(old)
+        try:
+            r = subprocess.run(cmd, capture_output=True, text=True)
+            failure = r.stderr if r.returncode != 0 else None
+        except OSError as e:
+            failure = str(e)
+        if failure is not None:
+            warnings.warn(f"the native part of the binding is left out (plain calls go through Python): {cmd[0]} failed on {src}:\n{failure}")
+            return BIND
+        with open(BIND_STAMP, "w") as f:
+            f.write(_binding_stamp(cmd))
     return BIND
 
 

@@ -245,4 +245,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_vt_bind", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__vt_bind(void) { return PyModule_Create(&module); }
+// built_for: the torch and the interpreter whose headers this was compiled with (binding.py compares them with its own)
+PyMODINIT_FUNC PyInit__vt_bind(void) {
+    PyObject *m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_for", VT_BUILT_FOR) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,9 +1,11 @@
 """Plain calls take the native way through the binding, others Python's: the same results, and the same refusals."""
+import os
+
 import pytest
 import torch
 
 import paper_2506_22694_amd as vt
-from paper_2506_22694_amd import binding
+from paper_2506_22694_amd import binding, build
 
 
 class Sub(torch.Tensor):
@@ -84,6 +86,29 @@ def _compare(monkeypatch, dev, seen):
 def test_the_native_way_is_built():
     vt.load_library()
     assert binding._bind is not None
+
+
+def test_a_native_way_built_for_another_torch_is_left_alone(monkeypatch):
+    L = vt.load_library()
+    monkeypatch.setattr(binding, "_bind", None)
+    monkeypatch.setattr(binding, "BIND_ABI", binding.BIND_ABI.replace(torch.__version__, "1.0.0"))
+    binding._connect(L)
+    assert binding._bind is None
+    # ... and built anew
+    src = os.path.join(build.CSRC, "vt_bind.cpp")
+    assert build._binding_stale(build._binding_command(src), [])
+    monkeypatch.undo()
+    assert not build._binding_stale(build._binding_command(src), [])
+
+
+def test_a_binding_that_does_not_build_is_left_out(monkeypatch, tmp_path):
+    monkeypatch.setattr(build, "BIND", str(tmp_path / "_vt_bind.so"))
+    monkeypatch.setattr(build, "BIND_STAMP", str(tmp_path / "vt_bind.command"))
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    monkeypatch.setenv("CXX", str(tmp_path / "no such compiler"))
+    with pytest.warns(UserWarning, match="left out"):
+        build.build_binding()
+    assert not os.path.exists(build.BIND)
 
 
 def test_host_tensors_are_refused_the_same_way(monkeypatch):
