@@ -903,7 +903,11 @@ int vt_draft_head_step_plan(int32_t n, int32_t k, int32_t d, int32_t m, int w_ty
                       p.nlists, 16 * p.row_groups + p.extra_rows, p.nwaves, p.ksplit, p.twin ? " workgroups_per_cu=2" : "");
         if (p.splits > 1) std::snprintf(head + std::strlen(head), sizeof head - std::strlen(head), " column_slices=%d", p.splits);
     }
-    const char *tail = p.row_select ? " + row_select_kernel" : " + step_finalize_kernel";
+    char tail[48];
+    if (p.parts != 0)
+        std::snprintf(tail, sizeof tail, " + row_select_parts_kernel parts=%d", p.parts);
+    else
+        std::snprintf(tail, sizeof tail, " + %s", p.row_select ? "row_select_kernel" : "step_finalize_kernel");
     char groups[48] = "";
     if (chunk < n) std::snprintf(groups, sizeof groups, " x %d row groups", (n + chunk - 1) / chunk);
     std::snprintf(text, text_bytes, "%s%s%s", head, tail, groups);

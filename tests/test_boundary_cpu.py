@@ -102,7 +102,8 @@ def test_step_plan_is_a_pure_host_function_and_follows_the_head(lib):
     assert _plan(lib, 4, 4096, 256, 4, VT_F32)[1].startswith("head_gemv_kernel<f32,4,")
     # many hidden rows, many tokens per row
     assert _plan(lib, 256, 32768, 8192, 16)[1] == (
-        "pack_h_kernel + head_mfma_wide_kernel<2> workgroups=256 tile_rows=128 + row_select_kernel")
+        "pack_h_kernel + head_mfma_wide_kernel<2> workgroups=256 tile_rows=128 + row_select_parts_kernel parts=512")
+    assert _plan(lib, 8, 16000, 3072, 16)[1].endswith(" + row_select_kernel")
     # errors: shape, dtype, no buffer
     assert _plan(lib, 0, 32768, 3072, 8)[0] == VT_ERR_SHAPE
     assert _plan(lib, 8, 32768, 3072, 65)[0] == VT_ERR_SHAPE

@@ -1,6 +1,7 @@
-"""Steps of more than 8 hidden rows on heads of few rows: tiles whose columns are cut into slices, stored logits in whole rows of
-8, 16 and 32 values per thread, against fp64 on the device."""
+"""Steps on stored logits: tiles whose columns are cut into slices, whole rows of 8, 16 and 32 values per thread, rows of which only the
+parts with the largest logits are read, against fp64 on the device."""
 import ctypes
+import re
 
 import pytest
 import torch
@@ -36,7 +37,7 @@ def _check(h, W, map_, same, m, got, by_id=True):
     assert torch.equal(logp, torch.gather(full, 1, order))
     if by_id:
         assert torch.equal(ids, map_[order])
-    else:      # (large logits differ by less than the rounding of their log-probs: which of those comes first is in the logits alone)
+    else:      # (large logits, or many, differ by less than the rounding of their log-probs: which of those comes first is in the logits alone)
         at = torch.searchsorted(map_, ids)
         assert torch.equal(map_[at], ids) and torch.equal(torch.gather(full, 1, at), logp)
         assert all(len(set(row)) == m for row in ids.tolist())
@@ -49,7 +50,8 @@ def _check(h, W, map_, same, m, got, by_id=True):
     (9, 4300, 8192, 8, 7, 128), (32, 4097, 8192, 4, 7, 128), (33, 6001, 8192, 10, 5, 128), (64, 5002, 8192, 16, 6, 128),
     (65, 4303, 4096, 8, 7, 128), (128, 8193, 3072, 1, 3, 128), (129, 4096, 2048, 8, 4, 64), (160, 10001, 4096, 4, 3, 128),
     (192, 6500, 4096, 10, 5, 128), (193, 5000, 8192, 4, 6, 128), (224, 14000, 8192, 8, 2, 128), (256, 14001, 8192, 16, 2, 128),
-    (256, 4100, 8064, 8, 7, 128), (256, 9999, 5248, 33, 3, 128), (100, 4096, 8192, 64, 4, 64), (250, 2050, 2048, 8, 7, 64), (128, 11900, 8192, 9, 3, 160), (300, 4300, 4096, 8, 3, 64)])
+    (256, 4100, 8064, 8, 7, 128), (256, 9999, 5248, 33, 3, 128), (100, 4096, 8192, 64, 4, 64), (250, 2050, 2048, 8, 7, 64),
+    (128, 11900, 8192, 9, 3, 160), (300, 4300, 4096, 8, 3, 64)])
 def test_step_by_slices_of_the_columns(n, k, d, m, slices, tile):
     plan = vt.draft_head_step_plan(n, k, d, m)
     assert f"tile_rows={tile} " in plan and f"column_slices={slices} + row_select" in plan, plan
@@ -80,16 +82,42 @@ def test_slices_are_as_close_to_fp64_as_one_piece(n, k, d, m):
     assert error[1] < 1.2 * error[0]
 
 
-# Stored logits of heads that one or two values per lane and load hold, without slices: rows of 8 and 16 values per thread and their
-# edges, k on and off multiples of four, more logits than candidates (hidden row of zeros)
+# Stored logits that are read in whole rows: of 8, 16 and 32 values per thread and their edges, of two stretches and more, k on and off
+# multiples of four, fewer groups of four than threads, more logits than candidates (hidden row of zeros).  Up to 8 hidden rows of heads that
+# are not read by parts; more of them with the smallest workspace that is accepted, which has no room for the parts (up to 8 tokens
+# it keeps lists)
 @pytest.mark.parametrize("n,k,d,m", [
-    (12, 8192, 128, 16), (12, 8193, 256, 9), (20, 16384, 128, 10), (17, 16385, 128, 12), (9, 16381, 128, 64), (200, 4099, 256, 8), (70, 4100, 1024, 8),
-    (256, 9000, 1024, 8), (3, 8191, 128, 20)])
-def test_stored_logits_of_short_rows(n, k, d, m):
-    assert "row_select" in vt.draft_head_step_plan(n, k, d, m) and "slices" not in vt.draft_head_step_plan(n, k, d, m)
-    h, W, map_, same = _inputs(n, k, d, seed=k)
+    (3, 8191, 128, 20), (8, 8192, 256, 16), (4, 8193, 128, 24), (2, 16384, 128, 16), (8, 16381, 128, 64), (5, 16385, 256, 17), (6, 32768, 128, 40),
+    (8, 32767, 128, 20),
+    (4, 3000, 1024, 16), (3, 4092, 128, 33), (7, 4096, 128, 17), (3, 2060, 256, -16), (8, 3840, 512, -64),
+    (24, 8192, 128, 16), (24, 8193, 256, 9), (20, 16384, 128, 10), (17, 16385, 128, 12), (40, 16381, 128, 64), (33, 32768, 128, 16),
+    (40, 3000, 128, 33), (9, 131073, 128, 64),
+    (24, 65537, 128, 16), (100, 50000, 128, 9), (200, 4099, 256, 8), (70, 4100, 1024, 8), (256, 9000, 1024, 8)])
+def test_stored_logits_in_whole_rows(n, k, d, m):
+    dtype, m = (torch.float32, -m) if m < 0 else (torch.bfloat16, m)
+    plan = vt.draft_head_step_plan(n, k, d, m, dtype)
+    h, W, map_, same = _inputs(n, k, d, seed=k, dtype=dtype)
     h[n // 2] = 0
-    _check(h, W, map_, same, m, vt.draft_head_step(h, W, map_, m, return_lse=True, return_full=True))
+    if n <= 8:
+        assert plan.endswith("row_select_kernel") and "slices" not in plan, plan
+    ws, L = vt.StepWorkspace(n, k, d, m, h.device), vt.load_library()
+    ids, logp = torch.empty((n, m), dtype=torch.int32, device="cuda"), torch.empty((n, m), device="cuda")
+    lse, full = torch.empty(n, device="cuda"), torch.empty((n, k), device="cuda")
+    code = int(dtype == torch.bfloat16)
+    step = lambda size: L.vt_draft_head_step(h.data_ptr(), code, n, W.data_ptr(), code, k, d, map_.data_ptr(), m,
+                                             ids.data_ptr(), logp.data_ptr(), lse.data_ptr(), full.data_ptr(), ws.buf.data_ptr(), size,
+                                             torch.cuda.current_stream().cuda_stream)
+    lo, hi = 0, ws.nbytes // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if step(256 * mid) == 0 else (mid, hi)
+    if n > 8 and m > 8:
+        parts = re.search(r"row_select_parts_kernel parts=(\d+)$", plan)
+        assert 256 * hi < 4 * n * k + 8 * n * (int(parts[1]) if parts else 8192), (plan, hi)
+    for size in (256 * hi, ws.nbytes):
+        full.fill_(7.0)
+        assert step(size) == 0
+        _check(h, W, map_, same, m, (ids, logp, lse, full), by_id=k < 50000)      # (see there)
 
 
 # Heads for tiles of 129 to 139 rows: the logits of such a tile, and of the last one, end inside a group of four.  With all of the
@@ -119,19 +147,23 @@ def test_stored_logits_of_tiles_that_are_no_multiple_of_four(n, k, d, m, tile):
 
 # Stored logits of which only the parts with the largest are read: both kernels and every tile height, tiles of 132 to 144 rows, last
 # tiles of one row and of one part, one, two and eight parts per thread, fewer parts than waves, rows off multiples of four, rounds,
-# two workgroups to a CU, h re-laid; up to 8 rows both kernels, their parts of 64 and shorter ones.  Hidden row 0 has 1500 large logits side by side (more than the candidates' room where the parts
+# two workgroups to a CU, h re-laid; up to 8 rows both kernels, their parts of 64 and shorter ones.  And the same inputs by slices, and with
+# more parts than the kernel takes.  Hidden row 0 has 1500 large logits side by side (more than the candidates' room where the parts
 # beside them set the threshold), hidden row 1 is zero (all logits tie)
-@pytest.mark.parametrize("n,k,d,m", [
-    (9, 130, 128, 9), (10, 4097, 256, 16), (33, 8200, 128, 64), (64, 12289, 128, 10), (20, 20001, 128, 33), (40, 26001, 256, 16), (12, 33008, 256, 10),
-    (64, 36865, 128, 64), (17, 44003, 128, 12), (24, 65537, 128, 16), (64, 100001, 128, 9), (9, 131073, 128, 64), (65, 7000, 128, 8), (100, 4100, 1024, 4),
-    (128, 12001, 128, 1), (129, 16383, 256, 8), (150, 20002, 128, 64), (192, 32768, 256, 8), (193, 30001, 128, 5), (256, 32767, 128, 64), (200, 40001, 128, 16),
-    (256, 70001, 128, 9), (256, 5000, 8192, 33), (256, 24000, 8192, 16),
-    (2, 16385, 512, 16), (8, 33008, 1024, 16), (3, 33013, 4096, 12), (5, 50204, 1024, 16), (2, 131075, 256, 64), (4, 3000, 1024, 16), (2, 40000, 2304, 33),
-    (3, 20003, 256, -16), (8, 3840, 512, -64)])
-def test_stored_logits_by_parts(n, k, d, m):
+@pytest.mark.parametrize("n,k,d,m,each", [
+    (9, 130, 128, 9, 1), (10, 4097, 256, 16, 1), (33, 8200, 128, 64, 1), (64, 12289, 128, 10, 1), (20, 20001, 128, 33, 2), (40, 26001, 256, 16, 2),
+    (12, 33008, 256, 10, 8), (64, 36865, 128, 64, 8), (17, 44003, 128, 12, 8), (24, 65537, 128, 16, 8), (64, 100001, 128, 9, 8),
+    (9, 131072, 128, 64, 8), (65, 7000, 128, 8, 1), (76, 4100, 1024, 7, 1), (128, 12001, 128, 1, 1), (129, 16383, 256, 8, 1),
+    (150, 20002, 128, 64, 1), (192, 32768, 256, 8, 1), (193, 30001, 128, 5, 1), (256, 32767, 128, 64, 1), (200, 40001, 128, 16, 1),
+    (256, 70001, 128, 9, 1), (256, 24000, 8192, 16, 1), (2, 16385, 512, 16, 1), (8, 33008, 1024, 16, 1), (3, 33013, 4096, 12, 1),
+    (5, 50204, 1024, 16, 1), (2, 131075, 256, 64, 8), (2, 40000, 2304, 33, 1), (4, 100000, 128, 33, 2), (3, 20003, 256, -16, 1),
+    (12, 8192, 128, 16, 1), (12, 8193, 256, 9, 1), (9, 16381, 128, 64, 1),
+    (256, 5000, 8192, 33, 0), (9, 131073, 128, 64, 0)])
+def test_stored_logits_by_parts(n, k, d, m, each):
     dtype, m = (torch.float32, -m) if m < 0 else (torch.bfloat16, m)      # (up to 8 rows: both element types)
     plan = vt.draft_head_step_plan(n, k, d, m, dtype)
-    assert "row_select" in plan, plan
+    parts = re.search(r" \+ row_select_parts_kernel parts=(\d+)$", plan)
+    assert "row_select" in plan and (parts is None if each == 0 else {1: 0, 2: 1024, 8: 2048}[each] < int(parts[1]) <= 1024 * each), plan
     h, W, map_, same = _inputs(n, k, d, seed=n + m, dtype=dtype)
     h[1] = 0
     lo = k // 3 // 4 * 4
@@ -149,7 +181,7 @@ def test_stored_logits_by_parts(n, k, d, m):
 @pytest.mark.parametrize("n,k,d,m", [(70, 9000, 128, 8), (256, 32768, 128, 16), (12, 40004, 128, 64), (128, 20001, 128, 8)])
 @pytest.mark.parametrize("order", ["ascending", "descending", "random", "apart"])
 def test_equal_logits_by_parts(n, k, d, m, order):
-    assert "row_select" in vt.draft_head_step_plan(n, k, d, m)
+    assert "row_select_parts_kernel" in vt.draft_head_step_plan(n, k, d, m)
     h, W, _, same = _inputs(n, k, d)
     h[2:] = 0
     W[:4096] = W[0].clone()      # row 1: 4096 equal logits, and those of `same`
