@@ -261,10 +261,9 @@ __device__ __forceinline__ void rank_candidates(const float *rawv, const int *ra
 // threshold thins that out at the end.  A row whose first stretch says little (more than kRowMaxRaw logits above its
 // threshold) is read again.  Reading longer rows twice cost k = 65536, n = 256 24.3 us (now 21.0),
 // k = 128256, n = 256 40.6 (27.9), n = 16 20.5 (17.3): up to 64 rows what is left is the rate at which one CU reads a row.
-// kRowTwice: up to 8 hidden rows of more than 16 tokens are read twice all the same: the first stretch's threshold is then
-// found bit by bit, and passes several times as many logits as the row's own (whole step, once against twice: n = 1,
-// k = 63000, m = 24 28.2 / 24.8 us, n = 4, k = 128256, m = 64 47.7 / 43.3; but n = 16, k = 65536, m = 24 30.6 / 32).
-enum RowMode { kRowWhole, kRowSift, kRowTwice };
+// (Reading twice was the faster one up to 8 hidden rows of more than 16 tokens, n = 4, k = 128256, m = 64 47.7 us once, 43.3 twice; those
+// are read by parts now, for which any workspace that a step of theirs accepts has room.)
+enum RowMode { kRowWhole, kRowSift };
 // VALS: values per thread and stretch; fewer than 32 for rows that fit them (what a thread holds past the row's end costs it an
 // exponential and a comparison like any other: n = 40, k = 4149, d = 2048, m = 10 17.4 -> 15.9 us, n = 12, k = 10860, d = 3072, m = 16
 // 19.8 -> 19.2).  SLICED: z is [splits][gridDim.x][pitch], see load_slices; z_out, or null: where the
@@ -326,12 +325,6 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     unsigned T, Mo;
     if constexpr (MODE == kRowWhole) {
         fold_stretch(v, lm, ls);
-    } else if constexpr (MODE == kRowTwice) {
-        fold_stretch(v, lm, ls);
-        for (int base = kRowSpan; base < k; base += kRowSpan) {
-            load_stretch<VEC, VALS>(zr, base, k, at, v);
-            fold_stretch(v, lm, ls);
-        }
     } else {
         float v2[VALS];
         load_stretch<VEC, VALS>(zr, kRowSpan, k, at, v2);
@@ -361,12 +354,6 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     // ---- pass 2: every logit >= T is a candidate
     if constexpr (MODE == kRowWhole) {
         collect_stretch<VEC, SIFT, VALS>(v, 0, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
-        __syncthreads();
-    } else if constexpr (MODE == kRowTwice) {
-        for (int base = 0; base < k; base += kRowSpan) {
-            load_stretch<VEC, VALS>(zr, base, k, at, v);
-            collect_stretch<VEC, SIFT, VALS>(v, base, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
-        }
         __syncthreads();
     } else if (s_nraw > kRaw) {
         __syncthreads();
@@ -660,8 +647,6 @@ hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m
     if (k <= 8 * kRowThreads) return vec ? launch(&row_select_kernel<kRowWhole, true, 8, false>) : launch(&row_select_kernel<kRowWhole, false, 8, false>);
     if (k <= 16 * kRowThreads) return vec ? launch(&row_select_kernel<kRowWhole, true, 16, false>) : launch(&row_select_kernel<kRowWhole, false, 16, false>);
     if (k <= kRowSpan) return vec ? launch(&row_select_kernel<kRowWhole, true, kRowVals, false>) : launch(&row_select_kernel<kRowWhole, false, kRowVals, false>);
-    if (n <= kGemvMaxN && m > kRowWaves)
-        return vec ? launch(&row_select_kernel<kRowTwice, true, kRowVals, false>) : launch(&row_select_kernel<kRowTwice, false, kRowVals, false>);
     return vec ? launch(&row_select_kernel<kRowSift, true, kRowVals, false>) : launch(&row_select_kernel<kRowSift, false, kRowVals, false>);
 }
 
