@@ -495,15 +495,17 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
         return p;
     }
     if (!whole.ok || !whole.mfma || n <= vt::kGemvMaxN || (k > vt::kRowSelectWhole && !whole.row_select)) return p;
-    const bool sliceable = k <= vt::kRowSelectWhole && d <= 8192;
     const int CUS = round_workgroups();
     const bool few = n <= vt::kRowsKernelMaxN;
     const int hrows = whole.wide ? 16 * whole.NT : whole.NT * 16;      // hidden rows of the tiles
     const int rows = 16 * whole.row_groups + whole.extra_rows, rounds = (whole.nlists + CUS - 1) / CUS;
     // Lists of up to 8 tokens take a tile's epilogue 5 to 10 us from 129 hidden rows on, and the logits of rows of up to 32768 with their
     // parts less (lists / parts: n = 217, k = 26262, d = 3072, m = 4 61.4 / 57.5 us, n = 100, k = 29182, d = 1024, m = 8 24.4 / 23.1, n = 145,
-    // k = 9145, m = 1 -2 %; n = 66, m = 8 1.6 % faster, but n = 76, k = 22786, m = 1 28.9 / 30.1, n = 90, m = 4 29.5 / 29.8)
-    const bool by_parts = whole.row_select || (!few && n >= 65 + 9 * (vt::kRowSelectMinLManyRows - m));
+    // k = 9145, m = 1 -2 %; n = 66, m = 8 1.6 % faster, but n = 76, k = 22786, m = 1 28.9 / 30.1, n = 90, m = 4 29.5 / 29.8).  Fewer rows of 5
+    // to 7 tokens on small tiles gain 1 % (n = 76, k = 1493, d = 2048, m = 6 21.9 / 20.8, n = 72, k = 2846, d = 1024, m = 5 15.1 / 14.1, most a
+    // tie), of 3 and 4 they lose (n = 85, k = 7225, d = 1024, m = 4 14.9 / 15.2; with all logits read, not the parts alone, n = 70, k = 809,
+    // d = 2048 20.2 / 32.8)
+    const bool by_parts = whole.row_select || (!few && (n >= 65 + 9 * (vt::kRowSelectMinLManyRows - m) || (m >= 5 && rows < vt::kMfmaTileRows)));
     const double as_planned = 9.0 + rounds * ((double)rows * d / 18e3 + (double)hrows * d / 38e3) +
                               (!whole.row_select ? rounds * 0.03 * n - 0.6 : std::max(k * (2.2e-6 * n + 3.5e-5), few ? 1.5 : 0.0));
     double best = as_planned;
@@ -522,13 +524,9 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     if (p.splits > 1) {
         p.extra_rows = 0;
         p.twin = false;
-    } else if (by_parts && row_parts(p, n, k)) {
-        // in one piece, with the (max, sum-exp) of the rows' parts
-    } else if (!sliceable || few || whole.row_select || rows >= vt::kMfmaTileRows || n * m < 256 || (double)n * (m * m / 2 + 12) * 34e3 < (double)k * k) {
-        return p;
+    } else if (!by_parts || !row_parts(p, n, k)) {
+        return p;      // (in one piece only with the (max, sum-exp) of the rows' parts)
     }
-    // (in one piece: lists of more than 64 hidden rows cost a tile 6 to 10 us, the logits of small heads less.  n = 256 / 128, lists / stored:
-    // k = 4300, m = 8 29.5 / 25.4 and 20.0 / 18.2 us on average of d = 1024, 2048 and 4096; k = 10000, m = 8 -7 and -4 %, m = 4 -4 and +2 %)
     p.instead_of_lists = !whole.row_select;
     p.row_select = true;
     p.list_room = 0;

@@ -59,3 +59,11 @@ def test_the_size_of_a_workspace_is_kept(lib):
     smallest = microseconds(1, 1000, 128, 1)
     for shape in ((256, 4300, 4096, 8), (256, 32768, 8192, 16), (64, 32768, 4096, 8)):
         assert microseconds(*shape) < 4 * smallest
+
+
+# 65 and more rows with few tokens: lists, or logits by parts; logits that are read in whole rows lose to both
+@pytest.mark.parametrize("n,k,d,m", [(70, 809, 2048, 4), (91, 450, 4096, 3), (79, 733, 1024, 6), (100, 4100, 1024, 4), (105, 306, 1024, 3), (128, 12001, 128, 8),
+                                     (72, 2846, 1024, 5), (69, 467, 5120, 6)])
+def test_small_heads_do_not_store_logits_to_read_whole_rows(lib, n, k, d, m):
+    rc, text = _plan(lib, n, k, d, m)
+    assert rc == 0 and (text.endswith("step_finalize_kernel") or "row_select_parts_kernel" in text), text
