@@ -474,7 +474,7 @@ bool few_rows_by_parts(int k, int m) { return k > (m <= 16 ? vt::kRowSelectWhole
 constexpr int kSliceGroups[] = {4, 8, 10};
 int slices_of(int k, int d, int g) {
     const int tiles = (k + 16 * g - 1) / (16 * g), S = round_workgroups() / tiles;
-    return S >= 2 && k <= vt::kRowSelectWhole && d <= 8192 && d / 128 >= 2 * S ? S : 1;
+    return S >= 2 && k <= vt::kRowSelectSlices && d <= 8192 && d / 128 >= 2 * S ? S : 1;
 }
 
 // The same step with its logits stored, and the columns cut into slices where that pays: larger tiles then (each hidden row is

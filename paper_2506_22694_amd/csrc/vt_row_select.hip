@@ -14,7 +14,7 @@
 //   (up to 32768 logits a row is bound by a chain: the loads, a reduction, two barriers, a trip to the map, the ranking.  The
 //   ranking of the logits alone runs beside that trip, and the sum of exponentials waits for no barrier of its own: a percent of
 //   a step, n = 128 on 32768 x 2048, m = 16 43.1 -> 42.7 us, and more with many candidates, n = 4 on 3880 x 4096, m = 24 23.2 -> 20.3)
-//   if more than 1024 logits reach T (massive ties, e.g. h = 0) the m best are extracted one by one.
+//   if more than 1024 logits reach T (massive ties, e.g. h = 0) a second threshold is found among their keys (rank_by_keys).
 // Where the matrix-core kernel leaves the (max, sum-exp) of a row's parts beside the logits, all of this reads a few dozen parts
 // instead of the row (row_select_parts_kernel).
 #include "vt_device.h"
@@ -183,9 +183,8 @@ __device__ __forceinline__ void fold_stretch(const float (&v)[VALS], float &lm, 
     }
 }
 
-// Every logit of a stretch that reaches Tf, with its position, into `val` / `pos` (cap entries; n counts on -- STOP: a lane
-// that finds no room goes on no further: where everything reaches Tf tens of thousands of increments queue on one address).
-template <bool VEC, bool STOP, int VALS>
+// Every logit of a stretch that reaches Tf, with its position, into `val` / `pos` (cap entries; n counts on, until a lane finds no room).
+template <bool VEC, int VALS>
 __device__ __forceinline__ void collect_stretch(const float (&v)[VALS], int base, int k, int tid, float Tf, float *val,
                                                 int *pos, unsigned *n, unsigned cap) {
 #pragma unroll
@@ -202,8 +201,9 @@ __device__ __forceinline__ void collect_stretch(const float (&v)[VALS], int base
                     if (slot < cap) {
                         val[slot] = v[u];
                         pos[slot] = j;
+                    } else {
+                        Tf = INFINITY;
                     }
-                    if (STOP && slot >= cap) Tf = INFINITY;
                 }
             }
         }
@@ -255,6 +255,133 @@ __device__ __forceinline__ void rank_candidates(const float *rawv, const int *ra
     }
 }
 
+// More logits than candidates: many equal ones (a row of zeros: a batch's padding), many large ones side by side, NaN.  for_keys(f) calls f
+// with the key of every logit that may be among the m best.  Every thread's best key, and of those the largest threshold that m of
+// them reach for sure, of three: m of one wave's, a quarter of m in each of four waves, a sixteenth in all.  What reaches it is ranked: two
+// readings of the row.  With the last of the three alone, which nearly all threads' keys reach where logits are equal and ids ascending,
+// ranking took 25 us (n = 128, k = 12001, d = 1024, m = 1, a single reading now, 40.5 -> 19.9 us, n = 100, k = 20000, m = 8 45.5 / 30.5), one reading per
+// token more (n = 2, k = 16384, m = 16 95.8 / 21.2, n = 4, k = 30000, m = 64 535 / 32).  Too many all the same: one token per reading.
+constexpr int kKeyThresholds = 3;
+// The kth largest v of the wave's lanes, bit by bit: of each half those from the highest in which lanes still in question differ (equal
+// logits differ in a few bits of their ids; all 64 bits took 14 us).  All 64 lanes take part, kth <= 64.
+struct OpOrU32 {
+    __device__ __forceinline__ unsigned operator()(unsigned a, unsigned b) const { return a | b; }
+};
+__device__ __forceinline__ unsigned kth_largest_of(unsigned v, unsigned long long &alive, int &kth) {
+    const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)v, __ffsll((long long)alive) - 1);
+    const unsigned differ = wave_allreduce_u32((alive >> lane_id() & 1ull) != 0ull ? v ^ first : 0u, OpOrU32{});
+    const int bits = 32 - __clz((int)__builtin_amdgcn_readfirstlane((int)differ));
+    unsigned T = bits < 32 ? first >> bits << bits : 0u;
+    for (int b = bits - 1; b >= 0; --b) {
+        const unsigned long long ones = __ballot((v >> b) & 1u) & alive;
+        const int c = __popcll(ones);
+        if (c >= kth) {
+            alive = ones;
+            T |= 1u << b;
+        } else {
+            kth -= c;
+            alive &= ~ones;
+        }
+    }
+    return T;
+}
+__device__ __forceinline__ unsigned long long wave_kth_largest_u64(unsigned long long v, int kth) {
+    unsigned long long alive = ~0ull;
+    const unsigned long long high = kth_largest_of((unsigned)(v >> 32), alive, kth);
+    return high << 32 | kth_largest_of((unsigned)v, alive, kth);
+}
+// The keys of a row's logits that reach Tf (all: of all its logits), from memory.
+template <typename F>
+__device__ __forceinline__ void for_row_keys(const float *__restrict__ zr, const int *__restrict__ map, int k, float Tf, bool all, F f) {
+    for (int j0 = 0; j0 < k; j0 += 8 * kRowThreads) {
+        float v[8];
+        int id[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int j = min(j0 + u * kRowThreads + (int)threadIdx.x, k - 1);
+            v[u] = zr[j];
+            id[u] = map[j];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (j0 + u * kRowThreads + (int)threadIdx.x < k && (v[u] >= Tf || all)) f(make_key(v[u], id[u]));
+        }
+    }
+}
+template <typename ForKeys>
+__device__ __forceinline__ void rank_by_keys(ForKeys for_keys, int m, float lse, unsigned long long *cand, unsigned *s_count,
+                                             unsigned long long (&of_waves)[kKeyThresholds][kRowWaves], unsigned long long (&thresholds)[kKeyThresholds],
+                                             int *__restrict__ ids, float *__restrict__ logp) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    unsigned long long best = kNoKey;
+    for_keys([&](unsigned long long key) { best = key > best ? key : best; });
+    if (m == 1) {
+        best = block_max_u64(best, of_waves[0], lane, w);
+        if (tid == 0) {
+            ids[0] = key_id(best);
+            logp[0] = key_logit(best) - lse;
+        }
+        return;
+    }
+    // (1, 4 and 16 waves)
+    int kth = 0;
+    unsigned long long of_wave = kNoKey;
+    for (int x = 0; x < kKeyThresholds; ++x) {
+        const int share = (m + (1 << 2 * x) - 1) >> 2 * x;
+        if (share != kth) of_wave = wave_kth_largest_u64(best, share);
+        kth = share;
+        if (lane == 0) of_waves[x][w] = of_wave;
+    }
+    __syncthreads();      // (and the count of before has been read)
+    if (tid == 0) *s_count = 0u;
+    if (tid < kKeyThresholds) thresholds[tid] = ~0ull;
+    cand[tid] = kNoKey;
+    __syncthreads();
+    if (tid < kKeyThresholds * kRowWaves) {
+        const int x = tid / kRowWaves;
+        const unsigned long long mine = of_waves[x][tid % kRowWaves];
+        int above = 0;
+#pragma unroll
+        for (int q = 0; q < kRowWaves; ++q) above += of_waves[x][q] > mine ? 1 : 0;
+        if (above < 1 << 2 * x) atomicMin(&thresholds[x], mine);
+    }
+    __syncthreads();
+    unsigned long long T = thresholds[0];
+#pragma unroll
+    for (int x = 1; x < kKeyThresholds; ++x) T = thresholds[x] > T ? thresholds[x] : T;
+    for_keys([&](unsigned long long key) {
+        if (key >= T) {
+            const unsigned slot = atomicAdd(s_count, 1u);
+            if (slot < (unsigned)kRowMaxCand) cand[slot] = key;
+            else T = ~0ull;      // (no room: nothing more to find)
+        }
+    });
+    __syncthreads();
+    const int nkeys = (int)*s_count;
+    if (nkeys <= kRowMaxCand) {
+        if (tid < nkeys) {
+            const unsigned long long key = cand[tid];
+            const int above = keys_above(cand, nkeys, key);
+            if (above < m) {
+                ids[above] = key_id(key);
+                logp[above] = key_logit(key) - lse;
+            }
+        }
+        return;
+    }
+    unsigned long long prev = ~0ull;
+    for (int r = 0; r < m; ++r) {
+        best = kNoKey;
+        for_keys([&](unsigned long long key) { best = key < prev && key > best ? key : best; });
+        best = block_max_u64(best, of_waves[0], lane, w);
+        if (tid == 0) {
+            ids[r] = key_id(best);
+            logp[r] = key_logit(best) - lse;
+        }
+        prev = best;
+    }
+}
+
 // kRowWhole: the row fits one stretch (k <= 32768), which stays in registers for the second pass.  kRowSift: longer rows are
 // read once, too: the first stretch's threshold is one that m logits of the row reach, so what later stretches have to offer above it
 // is collected as they go by (with the next stretch requested before the one at hand is folded), and the row's own
@@ -284,7 +411,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
     constexpr bool SIFT = MODE == kRowSift;
     constexpr unsigned kRaw = SIFT ? kRowMaxRaw : kRowMaxCand;
     __shared__ float redf[kRowWaves];
-    __shared__ unsigned long long red64[kRowWaves];
+    __shared__ unsigned long long of_waves[kKeyThresholds][kRowWaves], thresholds[kKeyThresholds];
     __shared__ unsigned tmax[2 * kRowWaves], tmax_first[2 * kRowWaves];
     __shared__ unsigned long long cand[kRowMaxCand];
     __shared__ float rawv[kRaw];
@@ -331,15 +458,15 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         fold_stretch(v, lm, ls);
         row_threshold(lm, m, tmax_first, lane, w, T, Mo);
         const float Tf1 = threshold_f32(T);
-        collect_stretch<VEC, SIFT, VALS>(v, 0, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, VALS>(v, 0, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
         for (int base = kRowSpan; base < k; base += 2 * kRowSpan) {
             load_stretch<VEC, VALS>(zr, base + kRowSpan, k, at, v);
             fold_stretch(v2, lm, ls);
-            collect_stretch<VEC, SIFT, VALS>(v2, base, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
+            collect_stretch<VEC, VALS>(v2, base, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
             if (base + kRowSpan < k) {
                 load_stretch<VEC, VALS>(zr, base + 2 * kRowSpan, k, at, v2);
                 fold_stretch(v, lm, ls);
-                collect_stretch<VEC, SIFT, VALS>(v, base + kRowSpan, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
+                collect_stretch<VEC, VALS>(v, base + kRowSpan, k, at, Tf1, rawv, rawj, &s_nraw, kRaw);
             }
         }
     }
@@ -353,7 +480,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
 
     // ---- pass 2: every logit >= T is a candidate
     if constexpr (MODE == kRowWhole) {
-        collect_stretch<VEC, SIFT, VALS>(v, 0, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
+        collect_stretch<VEC, VALS>(v, 0, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
         __syncthreads();
     } else if (s_nraw > kRaw) {
         __syncthreads();
@@ -361,7 +488,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
         __syncthreads();
         for (int base = 0; base < k; base += kRowSpan) {
             load_stretch<VEC, VALS>(zr, base, k, at, v);
-            collect_stretch<VEC, SIFT, VALS>(v, base, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
+            collect_stretch<VEC, VALS>(v, base, k, at, Tf, rawv, rawj, &s_nraw, kRaw);
         }
         __syncthreads();
     }
@@ -399,28 +526,24 @@ __global__ void __launch_bounds__(kRowThreads) row_select_kernel(const float *__
             rank_candidates(rawv, rawj, cand, s_at, map, ncand, m, lse, out_ids + (size_t)i * m, out_logp + (size_t)i * m);
         }
     } else {
-        // massive ties, NaN: take the best remaining key, m times (each round re-reads the row from the L2)
-        unsigned long long prev = ~0ull;
-        for (int r = 0; r < m; ++r) {
-            unsigned long long best = kNoKey;
-            for (int base = 0; base < k; base += kRowSpan) {
-                if (MODE != kRowWhole) load_stretch<VEC, VALS>(zr, base, k, at, v);
+        auto for_keys = [&](auto f) {
+            if constexpr (SLICED) {
+                // (the sums are nowhere but here)
 #pragma unroll
-                for (int u = 0; u < VALS; ++u) {
-                    const int j = stretch_index<VEC>(base, u, at);
-                    if (j < k && (v[u] >= Tf || by_code)) {
-                        const unsigned long long key = make_key(v[u], map[j]);
-                        if (key < prev && key > best) best = key;
+                for (int g = 0; g < VALS; g += 8) {
+                    int id[8];      // (requested together)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) id[u] = map[min(stretch_index<VEC>(0, g + u, at), k - 1)];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        if (stretch_index<VEC>(0, g + u, at) < k && (v[g + u] >= Tf || by_code)) f(make_key(v[g + u], id[u]));
                     }
                 }
+            } else {
+                for_row_keys(zr, map, k, Tf, by_code, f);
             }
-            best = block_max_u64(best, red64, lane, w);
-            if (tid == 0) {
-                out_ids[(size_t)i * m + r] = key_id(best);
-                out_logp[(size_t)i * m + r] = key_logit(best) - lse;
-            }
-            prev = best;
-        }
+        };
+        rank_by_keys(for_keys, m, lse, cand, &s_nraw, of_waves, thresholds, out_ids + (size_t)i * m, out_logp + (size_t)i * m);
     }
     if (tid == 0) {
         lse_buf[i] = lse;
@@ -442,7 +565,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const flo
                                                                        int nan_by_code, RowParts rp, int *__restrict__ out_ids, float *__restrict__ out_logp,
                                                                        float *__restrict__ out_lse, float *__restrict__ lse_buf) {
     __shared__ float redf[kRowWaves];
-    __shared__ unsigned long long red64[kRowWaves];
+    __shared__ unsigned long long of_waves[kKeyThresholds][kRowWaves], thresholds[kKeyThresholds];
     __shared__ unsigned tmax[2 * kRowWaves];
     __shared__ unsigned long long cand[kRowMaxCand];
     __shared__ float rawv[kRowMaxCand];
@@ -503,7 +626,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const flo
     // Logits of the picked parts, four to a load
     const int vecs = rp.part_rows / 4, total = npicked * vecs;
     auto collect = [&]() {
-        float Tt = Tf;      // (a thread that finds no room goes on no further, see collect_stretch)
+        float Tt = Tf;      // (a thread that finds no room goes on no further)
         for (int x0 = 0; x0 < total; x0 += 2 * kRowThreads) {
             float4 v[2];
             int j[2], end[2];
@@ -545,70 +668,8 @@ __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const flo
     if (ncand <= kRowMaxCand && !by_code) {
         rank_candidates(rawv, rawj, cand, s_at, map, ncand, m, lse, out_ids + (size_t)i * m, out_logp + (size_t)i * m);
     } else {
-        // Many equal logits, or many large ones side by side.  Every thread's best key, of which at least m reach Tk; all that reach Tk
-        // are ranked: two readings of the row, where one per token took n = 256, k = 32768, d = 2048, m = 16 with all logits equal
-        // 266 us (now 76; n = 100, k = 20000, m = 8 87 / 55).  Too many again: one per token.
-        auto for_keys = [&](auto f) {
-            for (int j0 = 0; j0 < k; j0 += 8 * kRowThreads) {
-                float v[8];
-                int id[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int j = min(j0 + u * kRowThreads + tid, k - 1);
-                    v[u] = zr[j];
-                    id[u] = map[j];
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    if (j0 + u * kRowThreads + tid < k && (v[u] >= Tf || by_code)) f(make_key(v[u], id[u]));
-                }
-            }
-        };
-        unsigned long long best = kNoKey;
-        for_keys([&](unsigned long long key) { best = key > best ? key : best; });
-        unsigned long long Tk = kNoKey;
-        for (int q = 0; q < m; q += kRowWaves) {
-            Tk = wave_max_u64(best);
-            if (best == Tk) best = kNoKey;
-        }
-        __syncthreads();      // (s_nraw has been read)
-        if (tid == 0) s_nraw = 0u;
-        if (lane == 0) red64[w] = Tk;
-        __syncthreads();
-        Tk = red64[0];
-#pragma unroll
-        for (int q = 1; q < kRowWaves; ++q) Tk = red64[q] < Tk ? red64[q] : Tk;
-        for_keys([&](unsigned long long key) {
-            if (key >= Tk) {
-                const unsigned slot = atomicAdd(&s_nraw, 1u);
-                if (slot < (unsigned)kRowMaxCand) cand[slot] = key;
-                else Tk = ~0ull;      // (no room: nothing more to find)
-            }
-        });
-        __syncthreads();
-        const int nkeys = (int)s_nraw;
-        if (nkeys <= kRowMaxCand) {
-            if (tid < nkeys) {
-                const unsigned long long key = cand[tid];
-                const int above = keys_above(cand, nkeys, key);
-                if (above < m) {
-                    out_ids[(size_t)i * m + above] = key_id(key);
-                    out_logp[(size_t)i * m + above] = key_logit(key) - lse;
-                }
-            }
-        } else {
-            unsigned long long prev = ~0ull;
-            for (int r = 0; r < m; ++r) {
-                best = kNoKey;
-                for_keys([&](unsigned long long key) { best = key < prev && key > best ? key : best; });
-                best = block_max_u64(best, red64, lane, w);
-                if (tid == 0) {
-                    out_ids[(size_t)i * m + r] = key_id(best);
-                    out_logp[(size_t)i * m + r] = key_logit(best) - lse;
-                }
-                prev = best;
-            }
-        }
+        rank_by_keys([&](auto f) { for_row_keys(zr, map, k, Tf, by_code, f); }, m, lse, cand, &s_nraw, of_waves, thresholds, out_ids + (size_t)i * m,
+                     out_logp + (size_t)i * m);
     }
     if (tid == 0) {
         lse_buf[i] = lse;
@@ -616,7 +677,7 @@ __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const flo
     }
 }
 
-// splits > 1: z is [splits][n][pitch], pitch a multiple of four, k <= kRowSpan; z_out [n, k] or null takes the sums.
+// splits > 1: z is [splits][n][pitch], pitch a multiple of four, k <= kRowSelectSlices; z_out [n, k] or null takes the sums.
 hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m, int splits, int pitch, bool nan_by_code, float *z_out,
                              int *out_ids, float *out_logp, float *out_lse, float *lse_buf, const RowParts *by_parts, hipStream_t st) {
     if (by_parts != nullptr) {
@@ -638,10 +699,10 @@ hipError_t launch_row_select(const float *z, const int *map, int n, int k, int m
         return hipGetLastError();
     };
     if (splits > 1) {
-        if (k > kRowSpan || pitch % 4 != 0 || pitch < k || (reinterpret_cast<uintptr_t>(z) & 15) != 0) return hipErrorInvalidValue;
+        static_assert(kRowSelectSlices == 16 * kRowThreads);
+        if (k > kRowSelectSlices || pitch % 4 != 0 || pitch < k || (reinterpret_cast<uintptr_t>(z) & 15) != 0) return hipErrorInvalidValue;
         if (k <= 8 * kRowThreads) return launch(&row_select_kernel<kRowWhole, true, 8, true>);
-        if (k <= 16 * kRowThreads) return launch(&row_select_kernel<kRowWhole, true, 16, true>);
-        return launch(&row_select_kernel<kRowWhole, true, kRowVals, true>);
+        return launch(&row_select_kernel<kRowWhole, true, 16, true>);
     }
     const bool vec = (k & 3) == 0 && (reinterpret_cast<uintptr_t>(z) & 15) == 0;
     if (k <= 8 * kRowThreads) return vec ? launch(&row_select_kernel<kRowWhole, true, 8, false>) : launch(&row_select_kernel<kRowWhole, false, 8, false>);

@@ -79,6 +79,7 @@ constexpr int kRowSelectMinL = 11;
 constexpr int kRowSelectMinLManyRows = 8;
 constexpr int kRowSelectMinWork = 1792; // ... where also many rows with many tokens on small tiles do (n * min(m, tile rows))
 constexpr int kRowSelectWhole = 32768;  // a row of so many stored logits stays in the registers of its workgroup
+constexpr int kRowSelectSlices = 16384; // ... and one of logits in slices; two slices of longer rows are more tiles than CUs
 // small-n path: the same switch when L > 12 - n / 2 (measured crossovers: L = 8 at n = 8, 10 at n = 4, 11-12 at n = 1)
 constexpr int kGemvRowSelectBase = 12;
 constexpr int kMfmaPrefetchUnits = 3;  // 128-column units of W_trim in flight per wave; an h chunk that has a successor

@@ -178,10 +178,13 @@ def test_stored_logits_by_parts(n, k, d, m, each):
 
 # All logits of a row equal, and as many above: the lowest ids, wherever they lie -- first, last, at random, and away from one wave of
 # the workgroup that looks for them (which then has none of the best)
-@pytest.mark.parametrize("n,k,d,m", [(70, 9000, 128, 8), (256, 32768, 128, 16), (12, 40004, 128, 64), (128, 20001, 128, 8)])
+@pytest.mark.parametrize("n,k,d,m,tail", [
+    (70, 9000, 128, 8, "parts"), (256, 32768, 128, 16, "parts"), (12, 40004, 128, 64, "parts"), (128, 20001, 128, 8, "parts"), (128, 12001, 128, 1, "parts"),
+    (8, 8192, 128, 16, "whole"), (3, 16381, 128, 64, "whole"), (4, 30001, 128, 17, "whole"), (9, 131073, 128, 33, "whole"), (224, 5000, 4096, 4, "slices")])
 @pytest.mark.parametrize("order", ["ascending", "descending", "random", "apart"])
-def test_equal_logits_by_parts(n, k, d, m, order):
-    assert "row_select_parts_kernel" in vt.draft_head_step_plan(n, k, d, m)
+def test_equal_logits(n, k, d, m, tail, order):
+    plan = vt.draft_head_step_plan(n, k, d, m)
+    assert plan.endswith("row_select_kernel") and ("column_slices" in plan) == (tail == "slices") if tail != "parts" else "row_select_parts_kernel" in plan, plan
     h, W, _, same = _inputs(n, k, d)
     h[2:] = 0
     W[:4096] = W[0].clone()      # row 1: 4096 equal logits, and those of `same`
