@@ -181,10 +181,10 @@ size_t vt_choose_k_ws_bytes(int32_t V);
  *                  need no initialisation, before the first step or between
  *                  steps, whatever their shapes (as long as the size suffices)
  *                  and whatever an earlier step that never completed left behind.
- *                  Less is accepted down to what earlier versions asked for: a step
- *                  of more than 8 rows on a head of few rows then keeps lists of
- *                  candidates instead of (partial) logits, which is slower, and its
- *                  logits may round differently in the last bits.
+ *                  Less is accepted down to what earlier versions asked for: steps
+ *                  for whose stored logits, or what goes beside them, there is no
+ *                  room then keep lists of candidates or read more of the logits,
+ *                  which is slower, and may round differently in the last bits.
  * ---------------------------------------------------------------------- */
 int vt_draft_head_step(const void *h, int h_type, int32_t n, const void *W_trim, int w_type,
                        int32_t k, int32_t d, const int32_t *map, int32_t m, int32_t *out_ids,
