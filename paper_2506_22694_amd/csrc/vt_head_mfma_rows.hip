@@ -65,8 +65,9 @@ __device__ __forceinline__ void wait_stage_and_sync(int younger) {
 }
 
 // What becomes of a tile's logits: lists of candidates (or logits by way of LDS, where zbuf is not aligned), logits straight from the
-// accumulators, or those of a slice of the columns, blockIdx.y, with ranges of its own that its tiles rotate or in one order.  Kernels of their own: as a branch in one kernel they took every
-// step 0.2 to 0.5 us (n = 16, k = 9735, d = 3072 17.5 / 17.8, n = 80, k = 35010, d = 1024 23.6 / 24.1).
+// accumulators, or those of a slice of the columns, blockIdx.y, with ranges of its own that its tiles rotate, or in order.  Kernels of
+// their own: as a branch in one kernel they took every step 0.2 to 0.5 us (n = 16, k = 9735, d = 3072 17.5 / 17.8, n = 80, k = 35010,
+// d = 1024 23.6 / 24.1).
 enum TileOut { kTileLists, kTileStored, kTileSlices, kTileSlicesInOrder };
 constexpr bool in_slices(TileOut out) { return out == kTileSlices || out == kTileSlicesInOrder; }
 
@@ -77,17 +78,17 @@ struct March {
     bool ranges;
     // Slices of the columns (of ns stages each) start in different places anyway; where those are whole multiples of 4 KiB
     // apart a slice has ranges to itself (n = 32, k = 14000, d = 8192, two slices 57.3 -> 50.6 us; elsewhere 2 to 10 % slower).
-    // In order: all tiles of a slice start in one place, another one for each slice, and the sums of any number of ranges take one
-    // set of registers.  A chain of additions is no longer there than an eighth of the row, what the tiles in one piece have where they
-    // have ranges: a slice in one chain had up to twice the error of those (n = 126, k = 5389, d = 8192, three slices: log-probs of the
-    // best tokens 3.0e-7 off, 1.5e-7 in one piece and in short chains).
-    __device__ __forceinline__ March(int ns_, int d, int slice_ranges, int slice, int splits) : ns(ns_) {
+    // In order: all tiles of a slice start at its first column, and the sums of any number of ranges take one set of registers.
+    // A chain of additions is no longer in slices than an eighth of the row, what the tiles in one piece have where they have ranges: a
+    // slice in one chain had up to twice the error of those (n = 126, k = 5389, d = 8192, three slices: log-probs of the best tokens
+    // 3.0e-7 off, 1.5e-7 in one piece and in short chains).
+    __device__ __forceinline__ March(int ns_, int d) : ns(ns_) {
         if constexpr (OUT == kTileSlicesInOrder) {
             ranges = d % 2048 == 0;
             rot = 0;
             // (an even number of stages: one of the kernel may be two blocks of 64 columns)
             step = d / (8 * kStageCols) & ~1;
-            start = slice_ranges != 0 ? 32 * slice / splits & ~1 : 0;      // (of 32 and more)
+            start = 0;
             last = -1;
             last_length = 0;
         } else {
@@ -235,7 +236,7 @@ head_mfma_kernel(const MfmaArgs a) {
     const unsigned rs = (unsigned)a.d * 2u;
     const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs + (size_t)columns.first * 128;
     const char *hb = static_cast<const char *>(a.h) + (size_t)columns.first * 128;
-    const March<NR, OUT> march(columns.stages, a.d, a.slice_ranges, columns.slice, a.splits);
+    const March<NR, OUT> march(columns.stages, a.d);
     const unsigned block_bytes = (unsigned)(GR + NT) * kGroupBytes, stage_bytes = KB * block_bytes;
     const int nstages = march.ns / KB;             // (d is a multiple of 128: an even number of blocks)
 
@@ -340,10 +341,7 @@ head_mfma_kernel(const MfmaArgs a) {
             }
         }
     }
-    if (march.ranges) {
-        sums.close(acc, march.rot, closed);
-        sums.total(acc);
-    }
+    if (march.ranges) sums.template finish<OUT == kTileSlicesInOrder>(acc, march.rot, closed);
     if constexpr (OUT != kTileLists) {
         float *z = a.zbuf + (size_t)columns.slice * a.n * a.zpitch + row0;
         const bool by_parts = OUT == kTileStored && a.parts != 0;
@@ -431,7 +429,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
     const char *Wt = static_cast<const char *>(a.W) + (size_t)row0 * rs + (size_t)columns.first * 128;
     // (re-laid: a stage's pieces lie one after the other)
     const char *hb = PACKED ? static_cast<const char *>(a.hpack) + (size_t)columns.first * (TN * 128) : static_cast<const char *>(a.h) + (size_t)columns.first * 128;
-    const March<NR, OUT> march(columns.stages, a.d, a.slice_ranges, columns.slice, a.splits);
+    const March<NR, OUT> march(columns.stages, a.d);
 
     unsigned voff[LPW], lds_at[LPW];
 #pragma unroll
@@ -529,10 +527,7 @@ __global__ void __launch_bounds__(kStepWaves *kWave) head_mfma_wide_kernel(const
             left = march.length_of(closed);
         }
     }
-    if (NR > 1 && march.ranges) {
-        sums.close(acc, march.rot, closed);
-        sums.total(acc);
-    }
+    if (NR > 1 && march.ranges) sums.template finish<OUT == kTileSlicesInOrder>(acc, march.rot, closed);
     if constexpr (OUT != kTileLists) {
         float *z = a.zbuf + (size_t)columns.slice * a.n * a.zpitch + row0;
         const bool by_parts = OUT == kTileStored && a.parts != 0;
@@ -681,7 +676,9 @@ constexpr int wide_ranges(int MT, int NTT) {
     const int acc = 4 * MT * NTT, ops = 8 * (MT + NTT);
     return 5 * acc + ops <= 208 ? 8 : 3 * acc + ops <= 208 ? 4 : 2;
 }
-// (slices: tiles of 64, 128 and 160 rows; two ranges that tiles rotate would be chains of a quarter of the row and more)
+// (slices: tiles of 64, 128 and 160 rows.  Two ranges that tiles rotate are chains of an eighth of the row from four slices on -- n = 250,
+// k = 7000, d = 8192 46.8 us, in order 50.1 -- and longer ones with two and three: in order, n = 224, k = 14000, d = 8192 74.6 / 75.9,
+// n = 256 83.4 / 87.0, n = 256, k = 9000, d = 6144 47.3 / 50.0)
 template <int MT, int NTT, bool PACKED>
 hipError_t launch_wide_as(const MfmaArgs &a, size_t lds, hipStream_t st) {
     constexpr int NST = wide_stages(MT, NTT), NR = wide_ranges(MT, NTT);
@@ -692,9 +689,7 @@ hipError_t launch_wide_as(const MfmaArgs &a, size_t lds, hipStream_t st) {
     const TileOut out = tile_out(a);
     if (out == kTileStored) return launch(std::integral_constant<TileOut, kTileStored>{});
     if constexpr (MT == 2 || MT == 4 || MT == 5) {
-        if constexpr (NR > 2) {
-            if (out == kTileSlices) return launch(std::integral_constant<TileOut, kTileSlices>{});
-        }
+        if (out == kTileSlices && (NR > 2 || a.splits >= 4)) return launch(std::integral_constant<TileOut, kTileSlices>{});
         if (out == kTileSlices || out == kTileSlicesInOrder) return launch(std::integral_constant<TileOut, kTileSlicesInOrder>{});
     }
     return a.splits == 1 ? launch(std::integral_constant<TileOut, kTileLists>{}) : hipErrorInvalidValue;

@@ -77,6 +77,17 @@ struct RangeSums {
             for (int i = 0; i < N; ++i) acc[i] = set[0][i] + set[1][i];
         }
     }
+    // ... with the last range still in acc
+    template <bool IN_ORDER>
+    __device__ __forceinline__ void finish(f32x4 (&acc)[N], int rot, int j) {
+        if constexpr (IN_ORDER) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i] += set[0][i];
+        } else {
+            close(acc, rot, j);
+            total(acc);
+        }
+    }
 };
 
 // Columns from one range's start to the next, in units of which a row of d holds `units`: NR equal ranges -- where those

@@ -61,7 +61,8 @@ def test_step_by_slices_of_the_columns(n, k, d, m, slices, tile):
 
 # Slices add up no longer chains than the tiles in one piece that a smaller workspace has: no larger error (of 500 and more log-probs, whose
 # errors' 2-norm is known to a few percent; a chain twice as long has 1.4 to 2 times the error)
-@pytest.mark.parametrize("n,k,d,m", [(126, 5389, 8192, 4), (200, 14066, 8192, 4), (224, 4300, 4096, 4), (136, 12835, 8192, 4)])
+@pytest.mark.parametrize("n,k,d,m", [(126, 5389, 8192, 4), (200, 14066, 8192, 4), (224, 4300, 4096, 4), (136, 12835, 8192, 4), (250, 7000, 8192, 4),
+                                     (256, 9000, 6144, 8)])
 def test_slices_are_as_close_to_fp64_as_one_piece(n, k, d, m):
     assert "column_slices" in vt.draft_head_step_plan(n, k, d, m)
     h, W, map_, _ = _inputs(n, k, d, seed=k)
