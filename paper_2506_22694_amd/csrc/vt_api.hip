@@ -500,12 +500,20 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     const int hrows = whole.wide ? 16 * whole.NT : whole.NT * 16;      // hidden rows of the tiles
     const int rows = 16 * whole.row_groups + whole.extra_rows, rounds = (whole.nlists + CUS - 1) / CUS;
     // Lists of up to 8 tokens take a tile's epilogue 5 to 10 us from 129 hidden rows on, and the logits of rows of up to 32768 with their
-    // parts less (lists / parts: n = 217, k = 26262, d = 3072, m = 4 61.4 / 57.5 us, n = 100, k = 29182, d = 1024, m = 8 24.4 / 23.1, n = 145,
-    // k = 9145, m = 1 -2 %; n = 66, m = 8 1.6 % faster, but n = 76, k = 22786, m = 1 28.9 / 30.1, n = 90, m = 4 29.5 / 29.8).  Fewer rows of 5
-    // to 7 tokens on small tiles gain 1 % (n = 76, k = 1493, d = 2048, m = 6 21.9 / 20.8, n = 72, k = 2846, d = 1024, m = 5 15.1 / 14.1, most a
-    // tie), of 3 and 4 they lose (n = 85, k = 7225, d = 1024, m = 4 14.9 / 15.2; with all logits read, not the parts alone, n = 70, k = 809,
-    // d = 2048 20.2 / 32.8)
-    const bool by_parts = whole.row_select || (!few && (n >= 65 + 9 * (vt::kRowSelectMinLManyRows - m) || (m >= 5 && rows < vt::kMfmaTileRows)));
+    // parts less (lists / parts: n = 217, k = 26262, d = 3072, m = 4 61.4 / 57.5 us, n = 70, k = 26000, d = 1024, m = 8 22.5 / 20.4).  Of 5 to 7
+    // tokens they do from 92, 83 and 74 rows on, on small tiles from the first (n = 92, k = 10000, d = 1024, m = 5 18.7 / 16.6), and of up to
+    // 4 where the hidden rows fill their tiles (n = 119, k = 19000, m = 1 ... 4 a tie to 1.5 %, n = 136 -2 to 1 %, n = 150 2 to 5 %; n = 110,
+    // k = 30000, d = 1024, m = 3 -3 %).  Tiles on nearly all CUs store later than fewer of them (n = 96, d = 1024, m = 6: 240 tiles 22.3 /
+    // 22.5, 241 22.2 / 23.1; n = 128, k = 32768, m = 4 23.6 / 25.1, m = 8 26.5 / 25.1; n = 160, k = 28000, d = 8192, m = 2 112.2 / 114.9, n = 180,
+    // d = 1536 34.9 / 34.4)
+    const bool all_cus = whole.nlists > CUS - 16;
+    auto parts_pay = [&]() {
+        if (m >= vt::kRowSelectMinLManyRows) return true;
+        if (all_cus && rows > vt::kMfmaTileRows / 2) return n >= (m <= 4 ? 176 : 145);
+        if (m <= 4) return n >= 145 || (!all_cus && n >= 119 && n <= 128);
+        return n >= 65 + 9 * (vt::kRowSelectMinLManyRows - m) || rows < vt::kMfmaTileRows;
+    };
+    const bool by_parts = whole.row_select || (!few && parts_pay());
     const double as_planned = 9.0 + rounds * ((double)rows * d / 18e3 + (double)hrows * d / 38e3) +
                               (!whole.row_select ? rounds * 0.03 * n - 0.6 : std::max(k * (2.2e-6 * n + 3.5e-5), few ? 1.5 : 0.0));
     double best = as_planned;
