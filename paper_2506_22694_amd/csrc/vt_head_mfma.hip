@@ -77,8 +77,8 @@ __device__ __forceinline__ void wait_unit(u32x4 (&b)[4]) {
 // 40.8 / 57.4; all rows cut into near-equal groups whose (group, part) tasks are dealt to the waves: 40.8 / 50.5;
 // nine waves of 16 rows on 229 CUs: 41.4 / 51.4; the small-n kernel: 41.8 / 51.7.  The planner uses it where rows
 // are not a multiple of 2 KiB.)
-// MH: the tiles of several heads in one launch (see MultiHeadTable); one group of hidden rows, all of h in LDS.
-template <int MAXW, bool XG = false, bool MH = false>
+// MH: the tiles of several heads in one launch (see MultiHeadTable); one group of hidden rows, all of h in LDS.  H_FIRST: see h_first().
+template <int MAXW, bool XG = false, bool MH = false, bool H_FIRST = false>
 __global__ void __launch_bounds__(MAXW *kWave) __attribute__((amdgpu_waves_per_eu(1, (MAXW + 3) / 4)))
 head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, SingleHead> mh) {
     static_assert(!MH || !XG, "several heads per launch: plain tiles");
@@ -250,8 +250,8 @@ head_mfma_kernel(const MfmaArgs a, const std::conditional_t<MH, MultiHeadTable, 
     request_dword(ids[2], head_map + row0 + min(lane + 2 * kWave, rows_b - 1));
     // The first unit of W is asked for ahead of h, whose addresses take longer to form than its way takes from the L2 (k = 32768,
     // d = 2048, n = 1 25.3 -> 24.7 us, k = 5000, d = 3072, n = 1 12.9 -> 12.4, k = 8192, d = 2048, n = 8 13.5 -> 13.2; two units first
-    // 25.1, 13.1 and 13.8, all three 25.3, 13.3 and 14.2).
-    constexpr int kAhead = 1, kBehind = kPrefetchUnits - kAhead;
+    // 25.1, 13.1 and 13.8, all three 25.3, 13.3 and 14.2) -- or behind it, see h_first().
+    constexpr int kAhead = H_FIRST ? 0 : 1, kBehind = kPrefetchUnits - kAhead;
 #pragma unroll
     for (int x = 0; x < kAhead; ++x) load_unit(x, areg[x]);
     fetch_chunk(0);                       // everything waits for it
@@ -585,15 +585,21 @@ __global__ void __launch_bounds__(2 * kWave) step_finalize_kernel(const Finalize
 
 constexpr int kTreeFewLds = kMaxDynamicLds - 8 * 1024;      // (the kernel's own arrays beside it)
 
-template <int MAXW, bool XG = false>
+template <int MAXW, bool XG = false, bool H_FIRST = false>
 hipError_t launch_mfma_inst(const MfmaArgs &a, size_t lds, hipStream_t st) {
-    auto kern = head_mfma_kernel<MAXW, XG, false>;
+    auto kern = head_mfma_kernel<MAXW, XG, false, H_FIRST>;
     static LdsLimitOnce lds_limit;
     hipError_t e = allow_dynamic_lds(lds_limit, {reinterpret_cast<const void *>(kern)}, kMaxDynamicLds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(a.nlists), dim3((MAXW == kStepWaves ? kStepWaves : a.nwaves) * kWave), lds, st, a,
                        SingleHead{});
     return hipGetLastError();
+}
+// Four waves to a group of 16 rows have so little of W each that they wait for h, and for the more of it the longer: h first (W's first unit
+// first / h first: n = 8, d = 4096, k = 3329 14.57 / 14.27 us, k = 5000 15.14 / 14.89, k = 6500 16.11 / 15.95, k = 8192 a tie, n = 8, d = 3072, k = 5000
+// 13.95 / 13.74, n = 6 13.54 / 13.40, k = 6500 -0.5 %; n = 8, d = 2048 and n = 5, d = 4096 -0.3 and -0.6 %).
+bool h_first(const MfmaArgs &a) {
+    return a.ksplit == 4 && a.nwaves == kStepWaves && a.n >= 6 && a.n * a.d > 16384 && a.nlists <= (a.n == 8 ? 208 : 160);
 }
 template <int MAXW>
 hipError_t launch_mfma_multi_inst(const MfmaArgs &a, const MultiHeadTable &t, size_t lds, hipStream_t st) {
@@ -632,6 +638,7 @@ hipError_t launch_head_mfma(const MfmaArgs &a, size_t lds, hipStream_t st) {
     }
     if ((size_t)a.d * 2 >= ((size_t)1 << 24)) return hipErrorInvalidValue;      // row offsets inside a tile: 24-bit factors
     if (a.extra_rows != 0) return launch_mfma_inst<kStepWaves, true>(a, lds, st);
+    if (h_first(a)) return launch_mfma_inst<kStepWaves, false, true>(a, lds, st);
     return a.nwaves == kStepWaves ? launch_mfma_inst<kStepWaves>(a, lds, st) : launch_mfma_inst<kMfmaMaxWaves>(a, lds, st);
 }
 

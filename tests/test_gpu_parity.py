@@ -293,6 +293,22 @@ def test_step_full_size_configs_every_logprob(k, d, n, m):
     assert torch.equal(oi, oi2) and torch.equal(ol, ol2)
 
 
+# Small heads whose waves ask for h ahead of W: from six rows of more than 16384 elements in all on, up to 160 tiles of 32 rows, with eight rows 208, at
+# both sides of each line, a last tile of one row; a row's bits are those of fewer rows, which ask for W first
+@pytest.mark.parametrize("k,n,d", [(6656, 8, 4096), (6657, 8, 4096), (5120, 6, 3072), (5121, 6, 3072), (4000, 7, 2560), (3329, 8, 2048), (3041, 8, 4096)])
+def test_step_on_small_heads_with_h_first(k, n, d):
+    m = 8
+    W, map_ = synth.trimmed_head_direct(k, d, seed=k + n, dtype="bf16")
+    h = synth.hidden_rows(n, d, seed=k + n, dtype="bf16")
+    ref = oracle.draft_head_step(h, W, map_, m)
+    oi, ol, lse, full = run_step(h, W, map_, m, return_lse=True, return_full=True)
+    assert check_step(oi, ol, ref, map_, m, lse) <= 1
+    check_full(full, ref)
+    for rows in (slice(0, 4), slice(n - 4, n)):
+        few = run_step(h[rows], W, map_, m)
+        assert torch.equal(few[0], oi[rows]) and torch.equal(few[1], ol[rows])
+
+
 # Trimmed sizes the paper itself uses: the head sizes of its main tables divided by the hidden size (32975 and
 # 32959 for the two EAGLE drafters, 33008 for the independent drafter) and the sweet spots of its ablation over
 # k (22786 and 35010).  None is a multiple of a tile.
