@@ -148,7 +148,7 @@ __device__ __forceinline__ void store_z4(float *z, int i, int n, int pitch, int 
 }
 
 // (max, sum-exp) of a hidden row's logits in this wave, four in every accumulator v[x * STEP], 16 rows of the head each: a lane
-// has its four, three more lanes (16, 32 and 48 further) the others.  (-inf - -inf is NaN: logits that are all -inf add nothing)
+// has its four, three more lanes (16, 32 and 48 further) the others.  (Of logits that are all -inf NaN, see row_select_parts_kernel.)
 template <int N, int STEP>
 __device__ __forceinline__ void publish_part(const f32x4 *v, unsigned long long *pms, bool there, int lgrp) {
     auto across = [](float x, auto op) {
@@ -166,7 +166,7 @@ __device__ __forceinline__ void publish_part(const f32x4 *v, unsigned long long 
     for (int x = 0; x < N; ++x)
         sum += (__expf(v[x * STEP].x - top) + __expf(v[x * STEP].y - top)) + (__expf(v[x * STEP].z - top) + __expf(v[x * STEP].w - top));
     sum = across(sum, OpAddF32{});
-    if (there && lgrp == 0) *pms = ((unsigned long long)__float_as_uint(top == -INFINITY ? 0.f : sum) << 32) | __float_as_uint(top);
+    if (there && lgrp == 0) *pms = ((unsigned long long)__float_as_uint(sum) << 32) | __float_as_uint(top);
 }
 // Logits behind the tile's end (its last row again) become -inf: nothing of the row.
 __device__ __forceinline__ void end_rows(f32x4 &v, int row, int rows_b) {

@@ -604,7 +604,9 @@ __global__ void __launch_bounds__(kRowThreads) row_select_parts_kernel(const flo
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const float top = __uint_as_float((unsigned)part[e]);
-        ls += __uint_as_float((unsigned)(part[e] >> 32)) * __expf(top - M);
+        // (-inf - -inf is NaN, in the part's sum: logits that are all -inf add nothing.  Here and not where the sum is made: 20 bytes ahead of
+        // the other epilogue moved it in its lines of instructions, n = 8, k = 1200, d = 2048, m = 1 9.01 -> 9.11 us)
+        ls += top == -INFINITY ? 0.f : __uint_as_float((unsigned)(part[e] >> 32)) * __expf(top - M);
         if (top >= Tf) {
             const int x = e * kRowThreads + at;
             if (x < rp.parts) {

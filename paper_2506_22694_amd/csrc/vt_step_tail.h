@@ -303,7 +303,7 @@ __device__ __forceinline__ void block_epilogue_large(const float *zrow, int S, i
 
 // --------------------------------------------------------------------- logits of a tile to memory
 // One wave stores a hidden row's logits of this tile (up to 8 hidden rows), and beside them, unless pms is null, the (max, sum-exp)
-// of every 64 of them, by which row_select_kernel finds the parts it reads.  (-inf - -inf is NaN: logits that are all -inf add nothing)
+// of every 64 of them, by which row_select_kernel finds the parts it reads (of logits that are all -inf NaN, see there).
 static_assert(kFewRowsPart == kWave);
 template <typename Logit>
 __device__ __forceinline__ void store_logits(float *__restrict__ z, unsigned long long *__restrict__ pms, int rows_b, int lane, Logit logit) {
@@ -313,7 +313,7 @@ __device__ __forceinline__ void store_logits(float *__restrict__ z, unsigned lon
         if (t < rows_b) z[t] = v = logit(t);
         if (pms != nullptr) {
             const float top = wave_max(v), sum = wave_sum(__expf(v - top));
-            if (lane == 0) pms[t0 / kWave] = ((unsigned long long)__float_as_uint(top == -INFINITY ? 0.f : sum) << 32) | __float_as_uint(top);
+            if (lane == 0) pms[t0 / kWave] = ((unsigned long long)__float_as_uint(sum) << 32) | __float_as_uint(top);
         }
     }
 }
