@@ -469,6 +469,14 @@ void lay_out_stored(StepPlan &p, int n, int k, int d) {
 // k = 16000 24.0 / 24.2 us, 18000 28.8 / 28.3, 32975 43.0 / 38.2; n = 4, d = 1024, m = 64, k = 30000 22.4 / 22.6, k = 3000, m = 16 9.6 / 10.9;
 // n = 4, k = 79094, d = 2048, m = 16 66.7 / 57.4)
 bool few_rows_by_parts(int k, int m) { return k > (m <= 16 ? vt::kRowSelectWhole / 2 : vt::kRowSelectWhole); }
+// More of them, where a thread of row_select_kernel has eight logits at most: parts against whole rows of eight 1.60 for k = 700, d = 1024, m = 33 and
+// 64 (m = 10 1.06), 1.28 for k = 1293, n = 9, m = 64, 1.0 to 1.17 for k = 2048 and 3000, 1.0 to 1.05 for k = 4608, n <= 64 and k = 7001 0.98 to 1.04, k = 7600
+// 0.89 to 1.06, k = 8190, n = 64 0.97, n = 81 and k = 6138 0.92 to 1.0; n > 64 off multiples of four, logits one by one, m = 10 and 16 0.90 to
+// 1.04 (n = 256, k = 4501), m = 64 0.96 to 2.1.
+bool whole_rows_pay(int n, int k, int m) {
+    if (n <= vt::kRowsKernelMaxN) return k <= 7168;
+    return k <= 4608 && (m > 16 || k % 4 == 0);
+}
 // Slices of the columns beside tiles of 16 g rows: as many as fill the chip, of 256 columns and more; 1: none.  Up to d = 8192, the
 // longest rows measured.
 constexpr int kSliceGroups[] = {4, 8, 10};
@@ -502,15 +510,15 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     // Lists of up to 8 tokens take a tile's epilogue 5 to 10 us from 129 hidden rows on, and the logits of rows of up to 32768 with their
     // parts less (lists / parts: n = 217, k = 26262, d = 3072, m = 4 61.4 / 57.5 us, n = 70, k = 26000, d = 1024, m = 8 22.5 / 20.4).  Of 5 to 7
     // tokens they do from 92, 83 and 74 rows on, on small tiles from the first (n = 92, k = 10000, d = 1024, m = 5 18.7 / 16.6), and of up to
-    // 4 where the hidden rows fill their tiles (n = 119, k = 19000, m = 1 ... 4 a tie to 1.5 %, n = 136 -2 to 1 %, n = 150 2 to 5 %; n = 110,
-    // k = 30000, d = 1024, m = 3 -3 %).  Tiles on nearly all CUs store later than fewer of them (n = 96, d = 1024, m = 6: 240 tiles 22.3 /
-    // 22.5, 241 22.2 / 23.1; n = 128, k = 32768, m = 4 23.6 / 25.1, m = 8 26.5 / 25.1; n = 160, k = 28000, d = 8192, m = 2 112.2 / 114.9, n = 180,
-    // d = 1536 34.9 / 34.4)
+    // 4 where the hidden rows fill their tiles (n = 119, k = 19000, m = 3 and 4 1 %, m = 1 and 2 a tie, on tiles of 48 3 %; n = 136 -2 to 1 %,
+    // n = 150 2 to 5 %; n = 110, k = 30000, d = 1024, m = 3 -3 %, n = 124, k = 21867, d = 1536, m = 2 26.7 / 27.4).  Tiles on nearly all CUs
+    // store later than fewer of them (n = 96, d = 1024, m = 6: 240 tiles 22.3 / 22.5, 241 22.2 / 23.1; n = 128, k = 32768, m = 4 23.6 / 25.1, m = 8
+    // 26.5 / 25.1; n = 160, k = 28000, d = 8192, m = 2 112.2 / 114.9, n = 180, d = 1536 34.9 / 34.4)
     const bool all_cus = whole.nlists > CUS - 16;
     auto parts_pay = [&]() {
         if (m >= vt::kRowSelectMinLManyRows) return true;
         if (all_cus && rows > vt::kMfmaTileRows / 2) return n >= (m <= 4 ? 176 : 145);
-        if (m <= 4) return n >= 145 || (!all_cus && n >= 119 && n <= 128);
+        if (m <= 4) return n >= 145 || (!all_cus && n >= 119 && n <= 128 && (m >= 3 || rows <= vt::kMfmaTileRows / 2));
         return n >= 65 + 9 * (vt::kRowSelectMinLManyRows - m) || rows < vt::kMfmaTileRows;
     };
     const bool by_parts = whole.row_select || (!few && parts_pay());
@@ -532,7 +540,7 @@ StepPlan plan_stored(const StepPlan &whole, int n, int k, int d, int m) {
     if (p.splits > 1) {
         p.extra_rows = 0;
         p.twin = false;
-    } else if (!by_parts || !row_parts(p, n, k)) {
+    } else if (!by_parts || (whole.row_select && whole_rows_pay(n, k, m)) || !row_parts(p, n, k)) {
         return p;      // (in one piece only with the (max, sum-exp) of the rows' parts)
     }
     p.instead_of_lists = !whole.row_select;

@@ -79,15 +79,15 @@ __device__ __forceinline__ void load_stretch(const float *__restrict__ zr, int b
     }
 }
 
-// A thread's place in a stretch.  Groups of four of a row that has fewer than threads go to the waves in equal shares: with them
+// A thread's place in a stretch.  Groups of four (or logits) of a row that has fewer than threads go to the waves in equal shares: with them
 // in order the last waves have none, their maxima leave the row without a threshold (row_threshold), and all its logits are candidates
 // -- beyond 1024 of them the tokens are found one after the other (five slices, n = 128, k = 3000, d = 4096, m = 16 56.4 -> 20.3 us,
 // n = 250, k = 2050 56.1 / 21.8, n = 20, k = 1500, d = 8192, m = 64 151.6 / 19.7; in one piece, n = 4, k = 3000, d = 1024, m = 16 46.8 / 9.6).
 // Threads without a group have the last place, which lies behind the row.
 template <bool VEC, int VALS>
 __device__ __forceinline__ int stretch_place(int k, int tid, int lane, int w) {
-    if constexpr (VEC && VALS == 8) {
-        const int groups = (k + 3) / 4;
+    if constexpr (VALS == 8) {
+        const int groups = VEC ? (k + 3) / 4 : k;
         if (groups < kRowThreads) {
             const int first = w * groups / kRowWaves, behind = (w + 1) * groups / kRowWaves;
             return first + lane < behind ? first + lane : kRowThreads - 1;

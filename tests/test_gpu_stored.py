@@ -92,7 +92,8 @@ def test_slices_are_as_close_to_fp64_as_one_piece(n, k, d, m):
     (8, 32767, 128, 20),
     (4, 3000, 1024, 16), (3, 4092, 128, 33), (7, 4096, 128, 17), (3, 2060, 256, -16), (8, 3840, 512, -64),
     (24, 8192, 128, 16), (24, 8193, 256, 9), (20, 16384, 128, 10), (17, 16385, 128, 12), (40, 16381, 128, 64), (33, 32768, 128, 16),
-    (40, 3000, 128, 33), (9, 131073, 128, 64),
+    (40, 3000, 128, 33), (9, 131073, 128, 64), (9, 65, 128, 64), (40, 66, 128, 9), (64, 651, 128, 33), (9, 1023, 256, 64), (24, 1025, 128, 10), (150, 961, 128, 33),
+    (64, 7168, 128, 16), (65, 4608, 128, 9),
     (24, 65537, 128, 16), (100, 50000, 128, 9), (200, 4099, 256, 8), (70, 4100, 1024, 8), (256, 9000, 1024, 8)])
 def test_stored_logits_in_whole_rows(n, k, d, m):
     dtype, m = (torch.float32, -m) if m < 0 else (torch.bfloat16, m)
@@ -152,7 +153,7 @@ def test_stored_logits_of_tiles_that_are_no_multiple_of_four(n, k, d, m, tile):
 # more parts than the kernel takes.  Hidden row 0 has 1500 large logits side by side (more than the candidates' room where the parts
 # beside them set the threshold), hidden row 1 is zero (all logits tie)
 @pytest.mark.parametrize("n,k,d,m,each", [
-    (9, 130, 128, 9, 1), (10, 4097, 256, 16, 1), (33, 8200, 128, 64, 1), (64, 12289, 128, 10, 1), (20, 20001, 128, 33, 2), (40, 26001, 256, 16, 2),
+    (9, 130, 128, 9, 0), (10, 4097, 256, 16, 0), (33, 8200, 128, 64, 1), (64, 12289, 128, 10, 1), (20, 20001, 128, 33, 2), (40, 26001, 256, 16, 2),
     (12, 33008, 256, 10, 8), (64, 36865, 128, 64, 8), (17, 44003, 128, 12, 8), (24, 65537, 128, 16, 8), (64, 100001, 128, 9, 8),
     (9, 131072, 128, 64, 8), (65, 7000, 128, 8, 1), (76, 4100, 1024, 7, 1), (128, 12001, 128, 1, 1), (129, 16383, 256, 8, 1),
     (150, 20002, 128, 64, 1), (192, 32768, 256, 8, 1), (193, 30001, 128, 5, 1), (256, 32767, 128, 64, 1), (200, 40001, 128, 16, 1),
