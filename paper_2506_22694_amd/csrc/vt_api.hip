@@ -471,11 +471,11 @@ void lay_out_stored(StepPlan &p, int n, int k, int d) {
 bool few_rows_by_parts(int k, int m) { return k > (m <= 16 ? vt::kRowSelectWhole / 2 : vt::kRowSelectWhole); }
 // More of them, where a thread of row_select_kernel has eight logits at most: parts against whole rows of eight 1.60 for k = 700, d = 1024, m = 33 and
 // 64 (m = 10 1.06), 1.28 for k = 1293, n = 9, m = 64, 1.0 to 1.17 for k = 2048 and 3000, 1.0 to 1.05 for k = 4608, n <= 64 and k = 7001 0.98 to 1.04, k = 7600
-// 0.89 to 1.06, k = 8190, n = 64 0.97, n = 81 and k = 6138 0.92 to 1.0; n > 64 off multiples of four, logits one by one, m = 10 and 16 0.90 to
+// 0.89 to 1.06, k = 8190, n = 64 0.97, n = 81 and k = 6138 0.92 to 1.0; n > 64 off multiples of four, logits one by one, m = 10 to 33 0.90 to
 // 1.04 (n = 256, k = 4501), m = 64 0.96 to 2.1.
 bool whole_rows_pay(int n, int k, int m) {
     if (n <= vt::kRowsKernelMaxN) return k <= 7168;
-    return k <= 4608 && (m > 16 || k % 4 == 0);
+    return k <= 4608 && (m > 40 || k % 4 == 0);
 }
 // Slices of the columns beside tiles of 16 g rows: as many as fill the chip, of 256 columns and more; 1: none.  Up to d = 8192, the
 // longest rows measured.

@@ -72,7 +72,7 @@ def test_small_heads_do_not_store_logits_to_read_whole_rows(lib, n, k, d, m):
 # More than 8 rows: heads so short that a thread has eight of a row's logits at most are read whole, longer ones by parts (n = 9, k = 1293, d = 1024, m = 64
 # took 1.28 times as long by parts, n = 24, k = 700 1.6)
 @pytest.mark.parametrize("n,k,m,whole", [(9, 1293, 64, True), (24, 700, 33, True), (64, 7168, 16, True), (64, 7169, 16, False), (64, 8192, 64, False), (65, 4608, 10, True),
-                                         (65, 4609, 64, False), (128, 4501, 16, False), (128, 4501, 17, True), (256, 3000, 16, True)])
+                                         (65, 4609, 64, False), (128, 4501, 16, False), (128, 4501, 33, False), (128, 4501, 48, True), (256, 3000, 16, True)])
 def test_short_rows_of_stored_logits_are_read_whole(lib, n, k, m, whole):
     rc, text = _plan(lib, n, k, 512, m)
     assert rc == 0 and text.endswith(" + row_select_kernel" if whole else f" parts={text.rpartition('=')[2]}") and "slices" not in text, text
